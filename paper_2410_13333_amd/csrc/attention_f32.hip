@@ -1,174 +1,355 @@
-// fp32 causal attention for the all-fp32 validation mode (tiny shapes): one thread per query row (forward,
-// dQ) or per key row (dK, dV), online softmax in the forward, scalar loops, no atomics.  Also holds the
-// delta_i = sum_c dO[i,c]*O[i,c] kernel that both storage types share.
+// fp32 causal attention of the all-fp32 validation mode, on v_mfma_f32_32x32x2_f32 (full fp32 products and sums): forward
+// with online softmax; dQ (which also forms delta = dO . O of its rows); dK and dV.  No atomics: every sum has a fixed
+// order.
+//
+// The kernels follow the bf16 ones: every score-like product is computed transposed, so that the softmax row is the
+// result's lane column and the probabilities of a lane are the B operand of the next product as they stand: element
+// 4g + r of a 32x32 result is row 8g + 4 (lane / 32) + r, and an MFMA that takes it as its B operand contracts over the
+// two rows 8g + r and 8g + 4 + r, for which the A operand is read from memory as two 128-byte row pieces.  The products
+// over the head dimension take 16 bytes per lane of either operand in the same manner (features 8G + 4 (lane / 32) ..
+// +3).  Nothing passes through LDS on the way in.
+//
+// The shapes of this mode are small (a few heads, a few hundred positions), so the bound is the chain of blocks a
+// wavefront walks, not the rate: a workgroup owns 32 rows, its four wavefronts take every fourth block of the other
+// sequence index, and their partial results meet in a fixed tree through LDS.
+// Measured (2 x 256 positions, 8 / 4 heads of 64): forward 3415 -> 13 us, dQ 4313 -> 17 us, dK and dV 13468 -> 38 us
+// against the kernels this replaced (one thread per row, scalar loops).
+#include <type_traits>
+
 #include "common.h"
 #include "kernels.h"
 
 namespace {
 
-constexpr int DMAX = 128;
+// Template argument DT: 32-column tiles of a head vector (head_dim d = 16 .. 128 in steps of 16; features at or beyond d
+// read as zero and are not stored).
 
-__global__ __launch_bounds__(64) void attn_fwd_f32_kernel(const float* __restrict__ qkv, int64_t ld,
-                                                          float* __restrict__ o, int64_t ldo, float* __restrict__ lse,
-                                                          int b, int S, int nq, int nkv, int d) {
-  const int64_t id = int64_t(blockIdx.x) * 64 + threadIdx.x;
-  if (id >= int64_t(b) * nq * S) return;
-  const int i = int(id % S), hq = int((id / S) % nq), bi = int(id / (int64_t(S) * nq));
-  const int hk = hq / (nq / nkv);
-  const float* q = qkv + (int64_t(bi) * S + i) * ld + hq * d;
-  const float* kb = qkv + int64_t(bi) * S * ld + int64_t(nq + hk) * d;
-  const float* vb = kb + int64_t(nkv) * d;
-  const float scale = rsqrtf((float)d);
-  float qr[DMAX], acc[DMAX];
+// 16 bytes per feature group: element 4G + j is feature 8G + 4 hf + j of `row` (null: zeros)
+template <int DT>
+__device__ __forceinline__ void load_row(const float* row, int d, int hf, float (&f)[DT * 16]) {
 #pragma unroll
-  for (int c = 0; c < DMAX; c++) { qr[c] = c < d ? q[c] : 0.f; acc[c] = 0.f; }
-  float m = -INFINITY, l = 0.f;
-  for (int j = 0; j <= i; j++) {
-    float s = 0.f;
-#pragma unroll
-    for (int c = 0; c < DMAX; c++) if (c < d) s += qr[c] * kb[j * ld + c];
-    s *= scale;
-    const float mn = fmaxf(m, s), corr = __expf(m - mn), p = __expf(s - mn);
-    l = l * corr + p;
-#pragma unroll
-    for (int c = 0; c < DMAX; c++) if (c < d) acc[c] = acc[c] * corr + p * vb[j * ld + c];
-    m = mn;
+  for (int G = 0; G < DT * 4; G++) {
+    float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
+    if (row && 8 * G < d) v = *reinterpret_cast<const float4*>(row + 8 * G + 4 * hf);
+    f[4 * G] = v.x; f[4 * G + 1] = v.y; f[4 * G + 2] = v.z; f[4 * G + 3] = v.w;
   }
-  float* orow = o + (int64_t(bi) * S + i) * ldo + hq * d;
-#pragma unroll
-  for (int c = 0; c < DMAX; c++) if (c < d) orow[c] = acc[c] / l;
-  lse[(int64_t(bi) * nq + hq) * S + i] = m + __logf(l);
 }
-
-template <typename T>
-__global__ __launch_bounds__(256) void attn_delta_kernel(const T* __restrict__ o, int64_t ldo,
-                                                         const T* __restrict__ d_o, int64_t ldd,
-                                                         float* __restrict__ delta, int b, int S, int nq, int d) {
-  // 16 lanes per (token, head) row of d <= 128 elements, 8 elements per lane: four rows per wavefront
-  const int64_t w = (int64_t(blockIdx.x) * 256 + threadIdx.x) >> 4;
-  const int c = (threadIdx.x & 15) * 8;
-  const bool live = w < int64_t(b) * S * nq;
-  const int hq = live ? int(w % nq) : 0;
-  const int64_t t = live ? w / nq : 0;
-  float s = 0.f;
-  if (live && c < d) {
-    float a[8], g[8];
-    load8(o + t * ldo + hq * d + c, a);
-    load8(d_o + t * ldd + hq * d + c, g);
+// A operand of a product that contracts over rows r0 .. r0+31 of m: element [e][t] is feature 32 t + lane % 32 of row
+// r0 + 8 (e / 4) + 4 hf + e % 4; rows at or beyond `rows` read as zero
+template <int DT>
+__device__ __forceinline__ void load_cols(const float* __restrict__ m, int64_t ld, int r0, int rows, int d, int l32, int hf,
+                                          float (&f)[16][DT]) {
 #pragma unroll
-    for (int e = 0; e < 8; e++) s += a[e] * g[e];
+  for (int e = 0; e < 16; e++) {
+    const int r = r0 + 8 * (e >> 2) + 4 * hf + (e & 3);
+#pragma unroll
+    for (int t = 0; t < DT; t++) f[e][t] = r < rows && 32 * t + l32 < d ? m[int64_t(r) * ld + 32 * t + l32] : 0.f;
   }
-#pragma unroll
-  for (int m = 8; m > 0; m >>= 1) s += __shfl_xor(s, m, 64);
-  if (live && c == 0) delta[(int64_t(t / S) * nq + hq) * S + (t % S)] = s;
 }
-
-__global__ __launch_bounds__(64) void attn_dq_f32_kernel(const float* __restrict__ qkv, int64_t ld,
-                                                         const float* __restrict__ lse, const float* __restrict__ d_o,
-                                                         int64_t ldd, const float* __restrict__ delta,
-                                                         float* __restrict__ dqkv, int64_t ldg, int b, int S, int nq,
-                                                         int nkv, int d) {
-  const int64_t id = int64_t(blockIdx.x) * 64 + threadIdx.x;
-  if (id >= int64_t(b) * nq * S) return;
-  const int i = int(id % S), hq = int((id / S) % nq), bi = int(id / (int64_t(S) * nq));
-  const int hk = hq / (nq / nkv);
-  const float* q = qkv + (int64_t(bi) * S + i) * ld + hq * d;
-  const float* kb = qkv + int64_t(bi) * S * ld + int64_t(nq + hk) * d;
-  const float* vb = kb + int64_t(nkv) * d;
-  const float* dor = d_o + (int64_t(bi) * S + i) * ldd + hq * d;
-  const float scale = rsqrtf((float)d);
-  const float L = lse[(int64_t(bi) * nq + hq) * S + i], D = delta[(int64_t(bi) * nq + hq) * S + i];
-  float qr[DMAX], dr[DMAX], acc[DMAX];
+template <int N>
+__device__ __forceinline__ f32x16 dot_rows(const float (&a)[N], const float (&b)[N]) {
+  f32x16 c;
 #pragma unroll
-  for (int c = 0; c < DMAX; c++) { qr[c] = c < d ? q[c] : 0.f; dr[c] = c < d ? dor[c] : 0.f; acc[c] = 0.f; }
-  for (int j = 0; j <= i; j++) {
-    float s = 0.f, dp = 0.f;
+  for (int e = 0; e < 16; e++) c[e] = 0.f;
 #pragma unroll
-    for (int c = 0; c < DMAX; c++) if (c < d) { s += qr[c] * kb[j * ld + c]; dp += dr[c] * vb[j * ld + c]; }
-    const float p = __expf(s * scale - L);
-    const float ds = p * (dp - D) * scale;
+  for (int q = 0; q < N; q++) c = __builtin_amdgcn_mfma_f32_32x32x2f32(a[q], b[q], c, 0, 0, 0);
+  return c;
+}
+template <int DT>
+__device__ __forceinline__ void accumulate(f32x16 (&acc)[DT], const float (&a)[16][DT], const f32x16& b) {
 #pragma unroll
-    for (int c = 0; c < DMAX; c++) if (c < d) acc[c] += ds * kb[j * ld + c];
+  for (int e = 0; e < 16; e++)
+#pragma unroll
+    for (int t = 0; t < DT; t++) acc[t] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[e][t], b[e], acc[t], 0, 0, 0);
+}
+// accumulate() for a block that the diagonal crosses.  There b holds zeros for the masked pairs, which take nothing from a
+// finite row, but a row of `m` with an infinity or a NaN in it must not reach the positions that may not see it: then the
+// sum is formed pair by pair over the allowed ones (allowed(r): row r counts for this lane's position).  sp: 32 x 32 floats
+// of LDS of this wavefront.
+template <int DT, class Allowed>
+__device__ __forceinline__ void accumulate_diagonal(f32x16 (&acc)[DT], const float (&a)[16][DT], const f32x16& b,
+                                                    const float* __restrict__ m, int64_t ld, int r0, int rows, int d, int l32,
+                                                    int hf, float (*sp)[32], Allowed&& allowed) {
+  float bad = 0.f;  // 0 * infinity and 0 * NaN are NaN
+#pragma unroll
+  for (int e = 0; e < 16; e++)
+#pragma unroll
+    for (int t = 0; t < DT; t++) bad += a[e][t] * 0.f;
+  if (!__any(bad != bad)) {
+    accumulate<DT>(acc, a, b);
+    return;
   }
-  float* out = dqkv + (int64_t(bi) * S + i) * ldg + hq * d;
+  auto sync = [] {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+  };
+  sync();
 #pragma unroll
-  for (int c = 0; c < DMAX; c++) if (c < d) out[c] = acc[c];
+  for (int e = 0; e < 16; e++) sp[8 * (e >> 2) + 4 * hf + (e & 3)][l32] = b[e];
+  sync();
+#pragma unroll 1
+  for (int r = 0; r < 32 && r0 + r < rows; r++) {
+    if (!allowed(r0 + r)) continue;
+    const float w = sp[r][l32];
+#pragma unroll
+    for (int t = 0; t < DT; t++)
+#pragma unroll
+      for (int g = 0; g < 4; g++) {
+        const int f = 32 * t + 8 * g + 4 * hf;
+        if (f < d)
+#pragma unroll
+          for (int j = 0; j < 4; j++) acc[t][4 * g + j] += w * m[int64_t(r0 + r) * ld + f + j];
+      }
+  }
+  sync();
 }
-
-__global__ __launch_bounds__(64) void attn_dkv_f32_kernel(const float* __restrict__ qkv, int64_t ld,
-                                                          const float* __restrict__ lse, const float* __restrict__ d_o,
-                                                          int64_t ldd, const float* __restrict__ delta,
-                                                          float* __restrict__ dqkv, int64_t ldg, int b, int S, int nq,
-                                                          int nkv, int d) {
-  const int64_t id = int64_t(blockIdx.x) * 64 + threadIdx.x;
-  if (id >= int64_t(b) * nkv * S) return;
-  const int j = int(id % S), hk = int((id / S) % nkv), bi = int(id / (int64_t(S) * nkv));
-  const int grp = nq / nkv;
-  const float* kr_ = qkv + (int64_t(bi) * S + j) * ld + int64_t(nq + hk) * d;
-  const float* vr_ = kr_ + int64_t(nkv) * d;
-  const float scale = rsqrtf((float)d);
-  float kr[DMAX], vr[DMAX], dk[DMAX], dv[DMAX];
+// sum of the four wavefronts' accumulators in wavefront 0: (0 + 2) + (1 + 3)
+template <int DT>
+__device__ __forceinline__ void sum_waves(f32x16 (&acc)[DT], float (*part)[DT * 16][64], int wave, int lane) {
 #pragma unroll
-  for (int c = 0; c < DMAX; c++) { kr[c] = c < d ? kr_[c] : 0.f; vr[c] = c < d ? vr_[c] : 0.f; dk[c] = 0.f; dv[c] = 0.f; }
-  for (int hq = hk * grp; hq < (hk + 1) * grp; hq++) {
-    for (int i = j; i < S; i++) {
-      const float* q = qkv + (int64_t(bi) * S + i) * ld + hq * d;
-      const float* dor = d_o + (int64_t(bi) * S + i) * ldd + hq * d;
-      float s = 0.f, dp = 0.f;
+  for (int half = 2; half > 0; half >>= 1) {
+    __syncthreads();
+    if (wave >= half && wave < 2 * half)
 #pragma unroll
-      for (int c = 0; c < DMAX; c++) if (c < d) { s += q[c] * kr[c]; dp += dor[c] * vr[c]; }
-      const int64_t si = (int64_t(bi) * nq + hq) * S + i;
-      const float p = __expf(s * scale - lse[si]);
-      const float ds = p * (dp - delta[si]) * scale;
+      for (int t = 0; t < DT; t++)
 #pragma unroll
-      for (int c = 0; c < DMAX; c++) if (c < d) { dv[c] += p * dor[c]; dk[c] += ds * q[c]; }
+        for (int e = 0; e < 16; e++) part[wave - half][t * 16 + e][lane] = acc[t][e];
+    __syncthreads();
+    if (wave < half)
+#pragma unroll
+      for (int t = 0; t < DT; t++)
+#pragma unroll
+        for (int e = 0; e < 16; e++) acc[t][e] += part[wave][t * 16 + e][lane];
+  }
+}
+// store a transposed result (lane column = row `row` of the output): four consecutive features per group
+template <int DT>
+__device__ __forceinline__ void store_row(float* row, const f32x16 (&acc)[DT], float mul, int d, int hf) {
+#pragma unroll
+  for (int t = 0; t < DT; t++)
+#pragma unroll
+    for (int g = 0; g < 4; g++) {
+      const int f = 32 * t + 8 * g + 4 * hf;
+      if (f < d)
+        *reinterpret_cast<float4*>(row + f) =
+            make_float4(acc[t][4 * g] * mul, acc[t][4 * g + 1] * mul, acc[t][4 * g + 2] * mul, acc[t][4 * g + 3] * mul);
     }
-  }
-  float* ok = dqkv + (int64_t(bi) * S + j) * ldg + int64_t(nq + hk) * d;
-  float* ov = ok + int64_t(nkv) * d;
+}
+template <int DT>
+__device__ __forceinline__ void clear(f32x16 (&acc)[DT]) {
 #pragma unroll
-  for (int c = 0; c < DMAX; c++) if (c < d) { ok[c] = dk[c]; ov[c] = dv[c]; }
+  for (int t = 0; t < DT; t++)
+#pragma unroll
+    for (int e = 0; e < 16; e++) acc[t][e] = 0.f;
+}
+
+// one-dimensional grid: query blocks of 32 (longest rows first), then batch rows, then heads
+template <int DT>
+__global__ __launch_bounds__(256) void attn_fwd_f32_kernel(const float* __restrict__ qkv, int64_t ld, float* __restrict__ o,
+                                                           int64_t ldo, float* __restrict__ lse, int b, int S, int nq, int nkv, int d) {
+  __shared__ float part[2][DT * 16][64];
+  __shared__ float sm[4][32], sl[4][32], sp[4][32][32];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, l32 = lane & 31, hf = lane >> 5;
+  const int hq = blockIdx.x % nq, bi = blockIdx.x / nq % b, q0 = ((S + 31) / 32 - 1 - blockIdx.x / nq / b) * 32, hk = hq / (nq / nkv);
+  const float* base = qkv + int64_t(bi) * S * ld;
+  const float *K = base + int64_t(nq + hk) * d, *V = base + int64_t(nq + nkv + hk) * d;
+  const int qi = q0 + l32;
+  const float sc = rsqrtf((float)d);
+  float q[DT * 16];
+  load_row<DT>(qi < S ? base + int64_t(qi) * ld + int64_t(hq) * d : nullptr, d, hf, q);
+  f32x16 acc[DT];
+  clear(acc);
+  float m = -INFINITY, l = 0.f;
+  for (int j0 = wave * 32; j0 <= q0; j0 += 128) {
+    float k[DT * 16], v[16][DT];
+    load_row<DT>(j0 + l32 < S ? K + int64_t(j0 + l32) * ld : nullptr, d, hf, k);
+    load_cols<DT>(V, ld, j0, S, d, l32, hf, v);
+    f32x16 s = dot_rows(k, q);
+    float mx = -INFINITY;
+#pragma unroll
+    for (int e = 0; e < 16; e++) {
+      const int j = j0 + 8 * (e >> 2) + 4 * hf + (e & 3);
+      s[e] = j <= qi ? s[e] * sc : -INFINITY;
+      mx = fmaxf(mx, s[e]);
+    }
+    const float mn = fmaxf(m, fmaxf(mx, __shfl_xor(mx, 32, 64)));  // finite: j0 <= q0 <= qi
+    const float corr = __expf(m - mn);
+    l *= corr;
+#pragma unroll
+    for (int e = 0; e < 16; e++) {
+      s[e] = __expf(s[e] - mn);
+      l += s[e];
+    }
+#pragma unroll
+    for (int t = 0; t < DT; t++)
+#pragma unroll
+      for (int e = 0; e < 16; e++) acc[t][e] *= corr;
+    m = mn;
+    if (j0 < q0) accumulate<DT>(acc, v, s);
+    else accumulate_diagonal<DT>(acc, v, s, V, ld, j0, S, d, l32, hf, sp[wave], [&](int j) { return j <= qi; });
+  }
+  // merge the four partial softmaxes: wavefront 0 always holds block 0, so the overall maximum is finite
+  l += __shfl_xor(l, 32, 64);
+  if (hf == 0) {
+    sm[wave][l32] = m;
+    sl[wave][l32] = l;
+  }
+  __syncthreads();
+  const float M = fmaxf(fmaxf(sm[0][l32], sm[1][l32]), fmaxf(sm[2][l32], sm[3][l32]));
+  const float w = __expf(m - M);
+#pragma unroll
+  for (int t = 0; t < DT; t++)
+#pragma unroll
+    for (int e = 0; e < 16; e++) acc[t][e] *= w;
+  float L = 0.f;
+#pragma unroll
+  for (int i = 0; i < 4; i++) L += sl[i][l32] * __expf(sm[i][l32] - M);
+  sum_waves<DT>(acc, part, wave, lane);
+  if (wave != 0 || qi >= S) return;
+  store_row<DT>(o + (int64_t(bi) * S + qi) * ldo + int64_t(hq) * d, acc, 1.f / L, d, hf);
+  if (hf == 0) lse[(int64_t(bi) * nq + hq) * S + qi] = M + __logf(L);
+}
+
+// grid as the forward: dQ of 32 rows, and their delta
+template <int DT>
+__global__ __launch_bounds__(256) void attn_dq_f32_kernel(const float* __restrict__ qkv, int64_t ld, const float* __restrict__ o,
+                                                          int64_t ldo, const float* __restrict__ lse,
+                                                          const float* __restrict__ d_o, int64_t ldd, float* __restrict__ delta,
+                                                          float* __restrict__ dqkv, int64_t ldg, int b, int S, int nq, int nkv, int d) {
+  __shared__ float part[2][DT * 16][64];
+  __shared__ float sp[4][32][32];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, l32 = lane & 31, hf = lane >> 5;
+  const int hq = blockIdx.x % nq, bi = blockIdx.x / nq % b, q0 = ((S + 31) / 32 - 1 - blockIdx.x / nq / b) * 32, hk = hq / (nq / nkv);
+  const float* base = qkv + int64_t(bi) * S * ld;
+  const float *K = base + int64_t(nq + hk) * d, *V = base + int64_t(nq + nkv + hk) * d;
+  const int qi = q0 + l32;
+  const bool live = qi < S;
+  const float sc = rsqrtf((float)d);
+  const int64_t si = (int64_t(bi) * nq + hq) * S + qi;
+  float q[DT * 16], dO[DT * 16];
+  float dl = 0.f;
+  load_row<DT>(live ? d_o + (int64_t(bi) * S + qi) * ldd + int64_t(hq) * d : nullptr, d, hf, dO);
+  load_row<DT>(live ? o + (int64_t(bi) * S + qi) * ldo + int64_t(hq) * d : nullptr, d, hf, q);
+#pragma unroll
+  for (int i = 0; i < DT * 16; i++) dl += q[i] * dO[i];
+  dl += __shfl_xor(dl, 32, 64);
+  if (wave == 0 && hf == 0 && live) delta[si] = dl;
+  const float L = live ? lse[si] : 0.f;
+  load_row<DT>(live ? base + int64_t(qi) * ld + int64_t(hq) * d : nullptr, d, hf, q);
+  f32x16 acc[DT];
+  clear(acc);
+  for (int j0 = wave * 32; j0 <= q0; j0 += 128) {
+    float k[DT * 16], kc[16][DT];
+    load_row<DT>(j0 + l32 < S ? V + int64_t(j0 + l32) * ld : nullptr, d, hf, k);
+    f32x16 dp = dot_rows(k, dO);
+    load_row<DT>(j0 + l32 < S ? K + int64_t(j0 + l32) * ld : nullptr, d, hf, k);
+    load_cols<DT>(K, ld, j0, S, d, l32, hf, kc);
+    f32x16 s = dot_rows(k, q);
+#pragma unroll
+    for (int e = 0; e < 16; e++) {
+      const int j = j0 + 8 * (e >> 2) + 4 * hf + (e & 3);
+      s[e] = j <= qi ? __expf(s[e] * sc - L) * (dp[e] - dl) : 0.f;
+    }
+    if (j0 < q0) accumulate<DT>(acc, kc, s);
+    else accumulate_diagonal<DT>(acc, kc, s, K, ld, j0, S, d, l32, hf, sp[wave], [&](int j) { return j <= qi; });
+  }
+  sum_waves<DT>(acc, part, wave, lane);
+  if (wave == 0 && live) store_row<DT>(dqkv + (int64_t(bi) * S + qi) * ldg + int64_t(hq) * d, acc, sc, d, hf);
+}
+
+// grid over (key blocks of 32, longest first; batch rows; KV heads): dK and dV of 32 rows; the wavefronts share out the (query head of the
+// group, query block at or below the diagonal) pairs
+template <int DT>
+__global__ __launch_bounds__(256) void attn_dkv_f32_kernel(const float* __restrict__ qkv, int64_t ld, const float* __restrict__ lse,
+                                                           const float* __restrict__ d_o, int64_t ldd,
+                                                           const float* __restrict__ delta, float* __restrict__ dqkv, int64_t ldg,
+                                                           int b, int S, int nq, int nkv, int d) {
+  __shared__ float part[2][DT * 16][64];
+  __shared__ float sp[4][32][32];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, l32 = lane & 31, hf = lane >> 5;
+  const int hk = blockIdx.x % nkv, bi = blockIdx.x / nkv % b, j0 = blockIdx.x / nkv / b * 32, grp = nq / nkv;
+  const float* base = qkv + int64_t(bi) * S * ld;
+  const float* dob = d_o + int64_t(bi) * S * ldd;
+  const int ji = j0 + l32;
+  const float sc = rsqrtf((float)d);
+  float k[DT * 16], v[DT * 16];
+  load_row<DT>(ji < S ? base + int64_t(ji) * ld + int64_t(nq + hk) * d : nullptr, d, hf, k);
+  load_row<DT>(ji < S ? base + int64_t(ji) * ld + int64_t(nq + nkv + hk) * d : nullptr, d, hf, v);
+  f32x16 dk[DT], dv[DT];
+  clear(dk);
+  clear(dv);
+  const int nb = (S - j0 + 31) / 32;  // query blocks of a head at or below the diagonal
+  for (int it = wave; it < nb * grp; it += 4) {
+    const int hq = hk * grp + it / nb, i0 = j0 + (it % nb) * 32;
+    const int64_t si = (int64_t(bi) * nq + hq) * S;
+    const float *Q = base + int64_t(hq) * d, *dO = dob + int64_t(hq) * d;
+    float r[DT * 16], rc[16][DT], L[16], dl[16];
+#pragma unroll
+    for (int e = 0; e < 16; e++) {
+      const int i = i0 + 8 * (e >> 2) + 4 * hf + (e & 3);
+      L[e] = i < S ? lse[si + i] : 0.f;
+      dl[e] = i < S ? delta[si + i] : 0.f;
+    }
+    load_row<DT>(i0 + l32 < S ? Q + int64_t(i0 + l32) * ld : nullptr, d, hf, r);
+    f32x16 p = dot_rows(r, k);
+    load_row<DT>(i0 + l32 < S ? dO + int64_t(i0 + l32) * ldd : nullptr, d, hf, r);
+    load_cols<DT>(dO, ldd, i0, S, d, l32, hf, rc);
+    f32x16 dp = dot_rows(r, v);
+#pragma unroll
+    for (int e = 0; e < 16; e++) {
+      const int i = i0 + 8 * (e >> 2) + 4 * hf + (e & 3);
+      p[e] = i >= ji && i < S ? __expf(p[e] * sc - L[e]) : 0.f;
+      dp[e] = i >= ji && i < S ? p[e] * (dp[e] - dl[e]) : 0.f;  // dS
+    }
+    if (i0 > j0) accumulate<DT>(dv, rc, p);
+    else accumulate_diagonal<DT>(dv, rc, p, dO, ldd, i0, S, d, l32, hf, sp[wave], [&](int i) { return i >= ji; });
+    load_cols<DT>(Q, ld, i0, S, d, l32, hf, rc);
+    if (i0 > j0) accumulate<DT>(dk, rc, dp);
+    else accumulate_diagonal<DT>(dk, rc, dp, Q, ld, i0, S, d, l32, hf, sp[wave], [&](int i) { return i >= ji; });
+  }
+  sum_waves<DT>(dk, part, wave, lane);
+  sum_waves<DT>(dv, part, wave, lane);
+  if (wave != 0 || ji >= S) return;
+  float* out = dqkv + (int64_t(bi) * S + ji) * ldg;
+  store_row<DT>(out + int64_t(nq + hk) * d, dk, sc, d, hf);
+  store_row<DT>(out + int64_t(nq + nkv + hk) * d, dv, 1.f, d, hf);
+}
+
+template <class F>
+hipError_t for_tiles(int d, F&& f) {
+  if (d <= 32) f(std::integral_constant<int, 1>{});
+  else if (d <= 64) f(std::integral_constant<int, 2>{});
+  else if (d <= 96) f(std::integral_constant<int, 3>{});
+  else f(std::integral_constant<int, 4>{});
+  return hipGetLastError();
 }
 
 }  // namespace
 
 namespace mls {
 
-hipError_t attn_delta(int dt, const void* o, int64_t ld_o, const void* d_o, int64_t ld_do, float* delta, int b, int S,
-                      int nq, int d, hipStream_t st) {
-  const int64_t waves = int64_t(b) * S * nq;
-  if (waves == 0) return hipSuccess;
-  const int blocks = int((waves * 16 + 255) / 256);  // 16 lanes per row
-  if (dt == DT_BF16)
-    hipLaunchKernelGGL(attn_delta_kernel<bf16_t>, dim3(blocks), dim3(256), 0, st, (const bf16_t*)o, ld_o,
-                       (const bf16_t*)d_o, ld_do, delta, b, S, nq, d);
-  else
-    hipLaunchKernelGGL(attn_delta_kernel<float>, dim3(blocks), dim3(256), 0, st, (const float*)o, ld_o,
-                       (const float*)d_o, ld_do, delta, b, S, nq, d);
-  return hipGetLastError();
-}
-
+// head_dim a multiple of 16 up to 128; row strides multiples of 8, 16-byte aligned buffers
 hipError_t attn_fwd_f32(const void* qkv, int64_t ld_qkv, void* o, int64_t ld_o, float* lse, int b, int S, int nq, int nkv,
                         int d, hipStream_t st) {
-  const int64_t n = int64_t(b) * nq * S;
-  if (n == 0) return hipSuccess;
-  hipLaunchKernelGGL(attn_fwd_f32_kernel, dim3(int((n + 63) / 64)), dim3(64), 0, st, (const float*)qkv, ld_qkv, (float*)o,
-                     ld_o, lse, b, S, nq, nkv, d);
-  return hipGetLastError();
+  if (b == 0 || S == 0 || nq == 0) return hipSuccess;
+  return for_tiles(d, [&](auto DT) {
+    hipLaunchKernelGGL(attn_fwd_f32_kernel<decltype(DT)::value>, dim3(unsigned((S + 31) / 32) * nq * b), dim3(256), 0, st,
+                       (const float*)qkv, ld_qkv, (float*)o, ld_o, lse, b, S, nq, nkv, d);
+  });
 }
 
 hipError_t attn_bwd_f32(const void* qkv, int64_t ld_qkv, const void* o, int64_t ld_o, const float* lse, const void* d_o,
                         int64_t ld_do, void* dqkv, int64_t ld_dqkv, float* delta, int b, int S, int nq, int nkv, int d,
                         hipStream_t st) {
-  const int64_t n = int64_t(b) * nq * S, nk = int64_t(b) * nkv * S;
-  if (n == 0) return hipSuccess;
-  hipError_t e = attn_delta(DT_FP32, o, ld_o, d_o, ld_do, delta, b, S, nq, d, st);
-  if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(attn_dq_f32_kernel, dim3(int((n + 63) / 64)), dim3(64), 0, st, (const float*)qkv, ld_qkv, lse,
-                     (const float*)d_o, ld_do, delta, (float*)dqkv, ld_dqkv, b, S, nq, nkv, d);
-  hipLaunchKernelGGL(attn_dkv_f32_kernel, dim3(int((nk + 63) / 64)), dim3(64), 0, st, (const float*)qkv, ld_qkv, lse,
-                     (const float*)d_o, ld_do, delta, (float*)dqkv, ld_dqkv, b, S, nq, nkv, d);
-  return hipGetLastError();
+  if (b == 0 || S == 0 || nq == 0) return hipSuccess;
+  return for_tiles(d, [&](auto DT) {
+    hipLaunchKernelGGL(attn_dq_f32_kernel<decltype(DT)::value>, dim3(unsigned((S + 31) / 32) * nq * b), dim3(256), 0, st,
+                       (const float*)qkv, ld_qkv, (const float*)o, ld_o, lse, (const float*)d_o, ld_do, delta, (float*)dqkv,
+                       ld_dqkv, b, S, nq, nkv, d);
+    hipLaunchKernelGGL(attn_dkv_f32_kernel<decltype(DT)::value>, dim3(unsigned((S + 31) / 32) * nkv * b), dim3(256), 0, st,
+                       (const float*)qkv, ld_qkv, lse, (const float*)d_o, ld_do, delta, (float*)dqkv, ld_dqkv, b, S, nq, nkv, d);
+  });
 }
 
 }  // namespace mls

@@ -125,8 +125,6 @@ hipError_t attn_bwd(int dt, const void* qkv, int64_t ld_qkv, const void* o, int6
                     const float* sin_tab = nullptr);
 
 // pieces behind the two dispatchers above
-hipError_t attn_delta(int dt, const void* o, int64_t ld_o, const void* d_o, int64_t ld_do, float* delta, int b, int S,
-                      int nq, int d, hipStream_t st);
 hipError_t attn_fwd_f32(const void* qkv, int64_t ld_qkv, void* o, int64_t ld_o, float* lse, int b, int S, int nq, int nkv,
                         int d, hipStream_t st);
 hipError_t attn_bwd_f32(const void* qkv, int64_t ld_qkv, const void* o, int64_t ld_o, const float* lse, const void* d_o,

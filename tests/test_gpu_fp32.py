@@ -1,0 +1,61 @@
+"""The all-fp32 storage mode where its kernels change shape: head dimensions that do not fill their 32-column tiles,
+sequences around the 32-row blocks and the four-way split of a workgroup, both tile sizes of the GEMM, causality with
+non-finite values."""
+import numpy as np
+import pytest
+
+import synth
+from tests.helpers import gpu_step, grad_errors, oracle_step, rel_err, to_host64
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("nq,nkv,d,seq,mb", [(2, 1, 16, 1, 2), (4, 2, 48, 31, 1), (6, 2, 96, 33, 2), (4, 1, 112, 129, 1),
+                                              (3, 3, 128, 257, 1), (8, 2, 32, 200, 2)])
+def test_stage_fp32_against_the_exact_oracle(nq, nkv, d, seq, mb):
+    sh = synth.StageShape(hidden=72, n_q_heads=nq, n_kv_heads=nkv, head_dim=d, ffn=88, seq=seq, micro_batch=mb, layers=1,
+                          microbatches=2, dtype="fp32")
+    ys, dxs, g, st = gpu_step(sh, 1000, 2000, 3000, [1, 1])
+    st.close()
+    rys, rdxs, rg = oracle_step(sh, 1000, 2000, 3000, [1, 1])
+    worst, _ = grad_errors(sh, g, rg, 1)
+    # about sqrt(K) roundings of 6e-8 per contraction and a few contractions in a row: under 1e-5 at these widths
+    for e in [rel_err(a, b) for a, b in zip(ys + dxs, rys + rdxs)] + [worst]:
+        assert e <= 1e-5
+
+
+# the last one has 512 tiles of 64x64 and runs on them (with a ragged edge), the others on 32x32 tiles; K is not a
+# multiple of a 32-deep piece, shorter than the four wavefronts' pieces, or one piece
+@pytest.mark.parametrize("M,N,K", [(8, 8, 8), (32, 40, 32), (40, 96, 104), (256, 264, 136), (2040, 1016, 72)])
+def test_gemm_fp32(M, N, K):
+    import torch
+    import paper_2410_13333_amd as mls
+    g = torch.Generator(device="cpu").manual_seed(M + N + K)
+    a, b, r = (torch.randn(s, generator=g).cuda() for s in ((M, K), (K, N), (M, N)))
+    ref = to_host64(a) @ to_host64(b)
+    c = torch.empty(M, N, device="cuda")
+    mls.gemm(0, a, b, c, r)
+    assert rel_err(to_host64(c), ref + to_host64(r)) < 1e-6
+    mls.gemm(1, a, b.t().contiguous(), c)
+    assert rel_err(to_host64(c), ref) < 1e-6
+    acc = torch.full((M, N), 0.5, device="cuda")
+    mls.gemm(2, a.t().contiguous(), b, acc)
+    assert rel_err(to_host64(acc), 0.5 + ref) < 1e-6
+
+
+@pytest.mark.parametrize("bad", [float("inf"), float("nan")])
+def test_a_non_finite_position_reaches_no_earlier_one(bad):
+    import torch
+    import paper_2410_13333_amd as mls
+    sh = synth.StageShape(hidden=64, n_q_heads=2, n_kv_heads=1, head_dim=48, ffn=64, seq=70, micro_batch=1, layers=1,
+                          microbatches=1, dtype="fp32")
+    st = mls.Stage.from_shape(sh, seed=1000)
+    x = synth.to_device(synth.make_x(sh, 2000, 0)[0], "fp32")
+    y0, y1 = torch.empty_like(x), torch.empty_like(x)
+    st.forward(x, 1, y0)
+    st.reset()
+    x[0, 45, 3] = bad
+    st.forward(x, 1, y1)
+    st.close()
+    assert rel_err(to_host64(y1[0, :45]), to_host64(y0[0, :45])) < 1e-6
+    assert not bool(torch.isfinite(y1[0, 45:]).all(dim=-1).any())
