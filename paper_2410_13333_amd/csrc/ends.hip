@@ -17,17 +17,19 @@ namespace {
 constexpr int TH = 256;
 constexpr int MAX_MB = 16;  // micro-batches one scatter launch covers
 
-// ---- x[t, :] = embed[tokens[t], :] (zero row for an id outside the table); one thread per 8 columns
+// ---- x[t, :] = embed[tokens[t], :] (zero row for an id outside the table); one thread per 8 columns.  The thread of a
+// row's first columns also keeps the id for the backward (a copy of its own cost 4.5 us per micro-batch beside 15).
 template <typename T>
-__global__ __launch_bounds__(TH) void embed_gather_kernel(const int32_t* __restrict__ tok, const T* __restrict__ E,
-                                                          int64_t ld_e, T* __restrict__ x, int64_t total, int h,
-                                                          int V) {
+__global__ __launch_bounds__(TH) void embed_gather_kernel(const int32_t* __restrict__ tok, int32_t* __restrict__ keep,
+                                                          const T* __restrict__ E, int64_t ld_e, T* __restrict__ x,
+                                                          int64_t total, int h, int V) {
   const int64_t id = int64_t(blockIdx.x) * TH + threadIdx.x;
   if (id >= total) return;
   const int cpr = h >> 3;
   const int64_t t = id / cpr;
   const int c = int(id % cpr) * 8;
   const int v = tok[t];
+  if (c == 0) keep[t] = v;
   float val[8];
   if (v >= 0 && v < V) {
     load8(E + int64_t(v) * ld_e + c, val);
@@ -39,64 +41,88 @@ __global__ __launch_bounds__(TH) void embed_gather_kernel(const int32_t* __restr
 }
 
 // ---- grads_embed[v, :] += sum of the dX rows at the positions that hold token v, in ascending (micro-batch,
-// position) order.  One workgroup per table row: it scans the token ids 256 at a time, shares the match masks
-// through LDS and then every thread walks the matches in order for its own columns.  No atomics: each table row
-// has one owner, so the result is bitwise reproducible.
+// position) order.
+// HBM-bound: dX once, and the fp32 rows that some position names read and written.  A workgroup owns SC_ROWS table rows
+// and a slice of 2048 columns: it scans the token ids of all micro-batches (64 KB from L2 at 16384 positions; the
+// one-row-per-workgroup form this replaces read 2 GB of ids for 32000 rows), collects the matches as (row, position)
+// keys in LDS, sorts them, and then every thread walks the sorted list for its own eight columns, requesting up to
+// SC_AHEAD rows of dX at a time.  The list is emptied when it may overflow, and at the end.  Neither the sort nor the
+// owner of a row depends on the order in which the matches were found: bitwise reproducible, no float atomics.
+// Measured (4 micro-batches of 4096 uniform tokens, 32000 x 4096): 562 -> 143 us (610 MB, 4.3 TB/s).
 struct TokPtrs { const int32_t* p[MAX_MB]; };
-template <typename T, int MAXC>
+constexpr int SC_ROWS = 16;    // table rows of a workgroup: 4 bits of a key, 28 hold MAX_MB * 2^24 positions
+constexpr int SC_CAP = 2048;   // keys of the list (twice 8 KiB of LDS: eight workgroups per CU)
+constexpr int SC_SCAN = 4;     // ids per thread between two looks at the list's length
+constexpr int SC_AHEAD = 8;
+template <typename T>
 __global__ __launch_bounds__(TH) void embed_scatter_kernel(TokPtrs tp, int n, const T* __restrict__ dX, int Ttok, int h,
-                                                           float* __restrict__ gE) {
-  __shared__ unsigned long long masks[TH / 64];
-  const int v = blockIdx.x, cpr = h >> 3;
-  float acc[MAXC][8];
+                                                           int V, float* __restrict__ gE) {
+  __shared__ uint32_t key[SC_CAP], sorted[SC_CAP];
+  __shared__ int count;
+  const int v0 = blockIdx.x * SC_ROWS, rows = min(SC_ROWS, V - v0);
+  const int c = (blockIdx.y * TH + threadIdx.x) * 8;
+  const bool mine = c < h;
+
+  auto flush = [&](int L) {  // (called by the whole workgroup, the keys published)
+    for (int i = threadIdx.x; i < L; i += TH) {
+      const uint32_t k = key[i];
+      int rank = 0;
+      for (int q = 0; q < L; q++) rank += key[q] < k;
+      sorted[rank] = k;
+    }
+    __syncthreads();
+    for (int i = 0; i < L;) {
+      const uint32_t row = sorted[i] >> 28;
+      int end = i + 1;
+      while (end < L && sorted[end] >> 28 == row) end++;
+      if (mine) {
+        float* p = gE + int64_t(v0 + row) * h + c;
+        float g[8], acc[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+        load8(p, g);
+        for (int at = i; at < end; at += SC_AHEAD) {
+          float d[SC_AHEAD][8];
 #pragma unroll
-  for (int i = 0; i < MAXC; i++)
+          for (int q = 0; q < SC_AHEAD; q++)
+            if (at + q < end) load8(dX + int64_t(sorted[at + q] & 0x0fffffffu) * h + c, d[q]);
 #pragma unroll
-    for (int e = 0; e < 8; e++) acc[i][e] = 0.f;
-  bool any = false;
+          for (int q = 0; q < SC_AHEAD; q++)
+            if (at + q < end)
+#pragma unroll
+              for (int e = 0; e < 8; e++) acc[e] += d[q][e];
+        }
+#pragma unroll
+        for (int e = 0; e < 8; e++) g[e] += acc[e];
+        store8(p, g);
+      }
+      i = end;
+    }
+    __syncthreads();
+    if (threadIdx.x == 0) count = 0;
+    __syncthreads();
+  };
+
+  if (threadIdx.x == 0) count = 0;
+  __syncthreads();
   for (int mb = 0; mb < n; mb++) {
     const int32_t* tok = tp.p[mb];
-    for (int base = 0; base < Ttok; base += TH) {
-      const int pos = base + threadIdx.x;
-      const unsigned long long m = __ballot(pos < Ttok && tok[pos] == v);
-      if ((threadIdx.x & 63) == 0) masks[threadIdx.x >> 6] = m;
-      __syncthreads();
+    for (int base = 0; base < Ttok; base += SC_SCAN * TH) {
+      int t[SC_SCAN];
 #pragma unroll
-      for (int w = 0; w < TH / 64; w++) {
-        unsigned long long mm = masks[w];
-        while (mm) {
-          const int bit = __ffsll((long long)mm) - 1;
-          mm &= mm - 1;
-          any = true;
-          const T* row = dX + (int64_t(mb) * Ttok + base + w * 64 + bit) * h;
-#pragma unroll
-          for (int i = 0; i < MAXC; i++) {
-            const int c = threadIdx.x + i * TH;
-            if (c < cpr) {
-              float d[8];
-              load8(row + c * 8, d);
-#pragma unroll
-              for (int e = 0; e < 8; e++) acc[i][e] += d[e];
-            }
-          }
-        }
+      for (int q = 0; q < SC_SCAN; q++) {
+        const int pos = base + q * TH + threadIdx.x;
+        t[q] = pos < Ttok ? tok[pos] : -1;
       }
+#pragma unroll
+      for (int q = 0; q < SC_SCAN; q++)
+        if (t[q] >= v0 && t[q] < v0 + rows)
+          key[atomicAdd(&count, 1)] = uint32_t(t[q] - v0) << 28 | uint32_t(mb * Ttok + base + q * TH + threadIdx.x);
       __syncthreads();
+      const int L = count;
+      __syncthreads();
+      if (L > SC_CAP - SC_SCAN * TH) flush(L);  // uniform: the next scan may not fit
     }
   }
-  if (!any) return;
-#pragma unroll
-  for (int i = 0; i < MAXC; i++) {
-    const int c = threadIdx.x + i * TH;
-    if (c < cpr) {
-      float g[8];
-      float* p = gE + int64_t(v) * h + c * 8;
-      load8(p, g);
-#pragma unroll
-      for (int e = 0; e < 8; e++) g[e] += acc[i][e];
-      store8(p, g);
-    }
-  }
+  if (count > 0) flush(count);
 }
 
 // ---- cross-entropy of one row of logits per workgroup, and its gradient in place:
@@ -352,13 +378,13 @@ int mls_embed_forward(mls_ends* s, const int32_t* tokens, void* x) {
   if ((uintptr_t(tokens) & 3) || (uintptr_t(x) & 15)) return fail(MLS_E_CONFIG, "mls_embed_forward: x must be 16-byte aligned");
   if (s->e_count >= s->c.max_inflight) return fail(MLS_E_STASH, "embedding stash full: max_inflight micro-batches already forwarded");
   const int slot = (s->e_head + s->e_count) % s->c.max_inflight;
-  HIP_TRY(hipMemcpyAsync(s->tok + size_t(slot) * s->T, tokens, size_t(s->T) * 4, hipMemcpyDeviceToDevice, s->st));
+  int32_t* keep = s->tok + size_t(slot) * s->T;
   const int64_t total = int64_t(s->T) * (s->c.hidden >> 3);
   if (s->dt == mls::DT_BF16)
-    hipLaunchKernelGGL(embed_gather_kernel<bf16_t>, dim3(blocks_for(total)), dim3(TH), 0, s->st, tokens,
+    hipLaunchKernelGGL(embed_gather_kernel<bf16_t>, dim3(blocks_for(total)), dim3(TH), 0, s->st, tokens, keep,
                        (const bf16_t*)s->embed, s->ld_h, (bf16_t*)x, total, s->c.hidden, s->c.vocab);
   else
-    hipLaunchKernelGGL(embed_gather_kernel<float>, dim3(blocks_for(total)), dim3(TH), 0, s->st, tokens,
+    hipLaunchKernelGGL(embed_gather_kernel<float>, dim3(blocks_for(total)), dim3(TH), 0, s->st, tokens, keep,
                        (const float*)s->embed, s->ld_h, (float*)x, total, s->c.hidden, s->c.vocab);
   HIP_TRY(hipGetLastError());
   s->e_count++;
@@ -372,7 +398,7 @@ int mls_embed_backward(mls_ends* s, const void* dX, float* grads, int32_t n) {
   if (!dX || !grads) return fail(MLS_E_NULL, "mls_embed_backward: null argument");
   if ((uintptr_t(dX) | uintptr_t(grads)) & 15) return fail(MLS_E_CONFIG, "mls_embed_backward: dX and grads must be 16-byte aligned");
   if (n > s->e_count) return fail(MLS_E_STASH, "n_microbatches exceeds the kept embedding micro-batches");
-  const int h = s->c.hidden, cpr = h >> 3;
+  const int h = s->c.hidden;
   const size_t act = size_t(s->T) * h * s->es;
   for (int i0 = 0; i0 < n; i0 += MAX_MB) {
     const int m = n - i0 < MAX_MB ? n - i0 : MAX_MB;
@@ -380,14 +406,10 @@ int mls_embed_backward(mls_ends* s, const void* dX, float* grads, int32_t n) {
     for (int i = 0; i < m; i++) tp.p[i] = s->tok + size_t((s->e_head + i0 + i) % s->c.max_inflight) * s->T;
     const char* dx = (const char*)dX + size_t(i0) * act;
     float* gE = grads + s->off_e;
-#define SCATTER(TY, C)                                                                                              \
-  hipLaunchKernelGGL((embed_scatter_kernel<TY, C>), dim3(s->c.vocab), dim3(TH), 0, s->st, tp, m, (const TY*)dx, s->T, h, gE)
-    const int mc = cpr <= 2 * TH ? 2 : cpr <= 4 * TH ? 4 : 8;
-    if (s->dt == mls::DT_BF16) {
-      if (mc == 2) SCATTER(bf16_t, 2); else if (mc == 4) SCATTER(bf16_t, 4); else SCATTER(bf16_t, 8);
-    } else {
-      if (mc == 2) SCATTER(float, 2); else if (mc == 4) SCATTER(float, 4); else SCATTER(float, 8);
-    }
+#define SCATTER(TY)                                                                                                  \
+  hipLaunchKernelGGL(embed_scatter_kernel<TY>, dim3((s->c.vocab + SC_ROWS - 1) / SC_ROWS, (h / 8 + TH - 1) / TH), dim3(TH), 0, \
+                     s->st, tp, m, (const TY*)dx, s->T, h, s->c.vocab, gE)
+    if (s->dt == mls::DT_BF16) SCATTER(bf16_t); else SCATTER(float);
 #undef SCATTER
     HIP_TRY(hipGetLastError());
   }

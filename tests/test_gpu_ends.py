@@ -276,3 +276,31 @@ def test_fullsize_7b_head_and_embedding():
     off, r, c = en.param_layout("embed")
     assert rel_err(to_host64(grads)[off:off + r * c].reshape(r, c), ref) <= 1e-6
     en.close()
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "fp32"])
+@pytest.mark.parametrize("hidden,vocab,seq,kind", [(2056, 24, 1500, "one"), (64, 1000, 1100, "few"), (4104, 40, 3, "edge")])
+def test_embedding_gradient_of_crowded_rows(dtype, hidden, vocab, seq, kind):
+    """Tokens that all fall on one table row, or on a few of one workgroup's rows (the list of matches fills up and is
+    emptied more than once), the last rows of a vocabulary that is no multiple of a workgroup's share, a last column
+    slice of one chunk, ids outside the table."""
+    import torch
+    import paper_2410_13333_amd as mls
+    n = 3
+    sh = synth.EndsShape(hidden=hidden, vocab=vocab, seq=seq, micro_batch=1, microbatches=n, dtype=dtype)
+    en = mls.Ends.from_shape(sh, seed=1100)
+    rng = np.random.default_rng(hidden)
+    toks = [{"one": np.full(seq, vocab - 1), "few": rng.integers(990, 1000, seq),
+             "edge": np.array([vocab - 1, -1, vocab])}[kind].astype(np.int32) for _ in range(n)]
+    x = torch.empty((seq, hidden), dtype=en.tdtype, device="cuda")
+    for t in toks:
+        en.embed_forward(torch.from_numpy(t).cuda(), x)
+    dX = torch.randn(n, seq, hidden, device="cuda").to(en.tdtype)
+    grads = torch.full((en.grad_elems,), 0.25, device="cuda")
+    en.embed_backward(dX, grads, n)
+    en.close()
+    ref = 0.25 + sum(oe.embed_backward(t, to_host64(dX[i]), vocab) for i, t in enumerate(toks))
+    g = to_host64(grads)
+    # a running fp32 sum of 4500 terms: well under 4500 * 2^-24 relative
+    assert rel_err(g[:vocab * hidden].reshape(vocab, hidden), ref) <= 1e-5
+    assert (g[vocab * hidden:] == 0.25).all()
