@@ -351,23 +351,53 @@ __global__ __launch_bounds__(EW_THREADS) void gu_permute_kernel(const bf16_t* __
   *reinterpret_cast<uint4*>(dst + t * ld_dst + (to_interleaved ? ci : c)) = v;
 }
 
-// dst[c][r] = src[r][c] for a rows x cols bf16 matrix (rows, cols multiples of 8): 64 x 64 tiles through LDS, padded
-// against bank conflicts; 256 threads, each moves 16 elements
-__global__ __launch_bounds__(256) void transpose_bf16_kernel(const bf16_t* __restrict__ src, int64_t ld_src,
-                                                             bf16_t* __restrict__ dst, int64_t ld_dst, int rows, int cols) {
-  __shared__ bf16_t tile[64][66];
-  const int r0 = blockIdx.y * 64, c0 = blockIdx.x * 64;
-  const int tx = threadIdx.x & 63, ty = threadIdx.x >> 6;
+// ---------------------------------------------------------------- parameters into their places (bf16)
+// One launch places up to MAX_SPREAD matrices: dst (row stride ld_dst; columns in the interleaved gate/up order if gu_f > 0)
+// and the transposed copy dst_t, from one read of src.  HBM-bound.  128 x 128 tiles, so that every row piece of all three
+// matrices is 256 bytes; a tile goes through LDS with the 16-byte chunks of a row XORed by its group of eight rows (the
+// transposing reads take one column of 16 groups: 16 different chunks, no bank conflicts).  Rows and columns are
+// multiples of 8 wherever dst_t is written.
+// Measured (the matrices of a 4096 x 11008 layer, 405 MB in, 810 MB out): 425 us as copies, a column permutation and
+// 64 x 64 transposes with 2-byte accesses; 256 us as one pass (4.75 TB/s).
+struct SpreadList {
+  mls::Spread m[mls::MAX_SPREAD];
+  int first[mls::MAX_SPREAD];  // first tile of each matrix
+  int n;
+};
+__global__ __launch_bounds__(256) void spread_bf16_kernel(SpreadList L) {
+  __shared__ uint4 tile[128 * 16];
+  int w = 0;
+  while (w + 1 < L.n && int(blockIdx.x) >= L.first[w + 1]) w++;
+  const mls::Spread& m = L.m[w];
+  const bf16_t* src = (const bf16_t*)m.src;
+  bf16_t *dst = (bf16_t*)m.dst, *dst_t = (bf16_t*)m.dst_t;
+  const int at = int(blockIdx.x) - L.first[w], tx = (m.cols + 127) / 128;
+  const int r0 = at / tx * 128, c0 = at % tx * 128;
+  const int ch = threadIdx.x & 15, tr = threadIdx.x >> 4;
+  const int col = c0 + ch * 8, icol = m.gu_f > 0 ? gu_interleaved_col(col, m.gu_f) : col;
 #pragma unroll
-  for (int i = 0; i < 16; i++) {
-    const int r = ty + i * 4;
-    if (r0 + r < rows && c0 + tx < cols) tile[r][tx] = src[int64_t(r0 + r) * ld_src + c0 + tx];
+  for (int i = 0; i < 8; i++) {
+    const int r = i * 16 + tr;
+    if (r0 + r < m.rows && col < m.cols) {
+      const uint4 v = *reinterpret_cast<const uint4*>(src + int64_t(r0 + r) * m.ld_src + col);
+      if (dst) *reinterpret_cast<uint4*>(dst + int64_t(r0 + r) * m.ld_dst + icol) = v;
+      tile[r * 16 + (ch ^ (r >> 3))] = v;
+    }
   }
+  if (!dst_t) return;
   __syncthreads();
+  const uint16_t* t16 = reinterpret_cast<const uint16_t*>(tile);
+  const int rg = threadIdx.x & 15;  // rows r0 + 8 rg .. +7
 #pragma unroll
-  for (int i = 0; i < 16; i++) {
-    const int c = ty + i * 4;
-    if (c0 + c < cols && r0 + tx < rows) dst[int64_t(c0 + c) * ld_dst + r0 + tx] = tile[tx][c];
+  for (int i = 0; i < 8; i++) {
+    const int c = i * 16 + (threadIdx.x >> 4), gc = c0 + c;
+    if (gc < m.cols && r0 + rg * 8 < m.rows) {
+      uint32_t e[8];
+#pragma unroll
+      for (int q = 0; q < 8; q++) e[q] = t16[((rg * 8 + q) * 16 + ((c >> 3) ^ rg)) * 8 + (c & 7)];
+      const uint4 v = make_uint4(e[0] | e[1] << 16, e[2] | e[3] << 16, e[4] | e[5] << 16, e[6] | e[7] << 16);
+      *reinterpret_cast<uint4*>(dst_t + int64_t(m.gu_f > 0 ? gu_interleaved_col(gc, m.gu_f) : gc) * m.ld_t + r0 + rg * 8) = v;
+    }
   }
 }
 
@@ -475,10 +505,19 @@ hipError_t gu_permute(const void* src, int64_t ld_src, void* dst, int64_t ld_dst
   return hipGetLastError();
 }
 
-hipError_t transpose_bf16(const void* src, int64_t ld_src, void* dst, int64_t ld_dst, int rows, int cols, hipStream_t st) {
-  if (rows == 0 || cols == 0) return hipSuccess;
-  hipLaunchKernelGGL(transpose_bf16_kernel, dim3((cols + 63) / 64, (rows + 63) / 64), dim3(256), 0, st, (const bf16_t*)src,
-                     ld_src, (bf16_t*)dst, ld_dst, rows, cols);
+hipError_t spread_bf16(const Spread* list, int n, hipStream_t st) {
+  if (n < 0 || n > MAX_SPREAD) return hipErrorInvalidValue;
+  SpreadList L = {};
+  int64_t tiles = 0;
+  for (int i = 0; i < n; i++) {
+    if (list[i].rows <= 0 || list[i].cols <= 0) continue;
+    L.m[L.n] = list[i];
+    L.first[L.n++] = int(tiles);
+    tiles += int64_t((list[i].rows + 127) / 128) * ((list[i].cols + 127) / 128);
+  }
+  if (tiles == 0) return hipSuccess;
+  if (tiles > INT32_MAX) return hipErrorInvalidValue;
+  hipLaunchKernelGGL(spread_bf16_kernel, dim3(unsigned(tiles)), dim3(256), 0, st, L);
   return hipGetLastError();
 }
 

@@ -294,6 +294,12 @@ void param_tensors(const mls_ends* s, PT (&t)[3]) {
   t[2] = {s->off_w, s->wlm, h, V, s->ld_v, 8, 0.02, 0.0};
 }
 
+// the transposed copy of w_lm from w_lm (bf16 storage)
+hipError_t transpose_wlm(mls_ends* s) {
+  const mls::Spread m = {s->wlm, s->ld_v, nullptr, 0, s->wlm_t, s->ld_h, s->c.hidden, s->c.vocab, 0};
+  return mls::spread_bf16(&m, 1, s->st);
+}
+
 }  // namespace
 
 extern "C" {
@@ -350,9 +356,9 @@ int mls_ends_init(const mls_ends_config* cfg, uint64_t seed, void* hip_stream, m
       release(s);
       return fail_hip(e, "weight generator");
     }
-  if (s->wlm_t && (e = mls::transpose_bf16(s->wlm, s->ld_v, s->wlm_t, s->ld_h, c.hidden, c.vocab, s->st)) != hipSuccess) {
+  if (s->wlm_t && (e = transpose_wlm(s)) != hipSuccess) {
     release(s);
-    return fail_hip(e, "transpose_bf16");
+    return fail_hip(e, "spread_bf16");
   }
   if ((e = hipStreamSynchronize(s->st)) != hipSuccess) {
     release(s);
@@ -522,8 +528,16 @@ int mls_ends_set_params(mls_ends* s, const void* src) {
   if (!s || !src) return fail(MLS_E_NULL, "mls_ends_set_params: null argument");
   PT t[3];
   param_tensors(s, t);
-  for (auto& q : t) HIP_TRY(copy2d(s, q.ptr, q.ld, (const char*)src + q.off * s->es, q.cols, q.rows, q.cols));
-  if (s->wlm_t) HIP_TRY(mls::transpose_bf16(s->wlm, s->ld_v, s->wlm_t, s->ld_h, s->c.hidden, s->c.vocab, s->st));
+  if (s->wlm_t && !(uintptr_t(src) & 15)) {  // bf16: all three in one pass, the transposed w_lm with them
+    mls::Spread m[3];
+    for (int i = 0; i < 3; i++)
+      m[i] = {(const char*)src + t[i].off * s->es, t[i].cols, t[i].ptr, t[i].ld, i == 2 ? s->wlm_t : nullptr, s->ld_h,
+              int(t[i].rows), int(t[i].cols), 0};
+    HIP_TRY(mls::spread_bf16(m, 3, s->st));
+  } else {
+    for (auto& q : t) HIP_TRY(copy2d(s, q.ptr, q.ld, (const char*)src + q.off * s->es, q.cols, q.rows, q.cols));
+    if (s->wlm_t) HIP_TRY(transpose_wlm(s));
+  }
   HIP_TRY(hipStreamSynchronize(s->st));
   return MLS_OK;
 }

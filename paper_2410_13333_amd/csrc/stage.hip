@@ -170,16 +170,17 @@ int check_config(const mls_config& c) {
 
 int64_t padded(int64_t n) { return n % 256 == 0 ? n + 64 : n; }
 
-// the six parameter tensors of a layer: public offset, internal offset, rows, cols, internal row stride
-struct PTensor { size_t off, ioff; int64_t rows, cols, ld; uint32_t tid; double scale, offset; };
+// the six parameter tensors of a layer: public offset, internal offset, rows, cols, internal row stride; ld_t > 0: offset and
+// row stride of the transposed copy (bf16 storage)
+struct PTensor { size_t off, ioff; int64_t rows, cols, ld; uint32_t tid; double scale, offset; size_t toff; int64_t ld_t; };
 void param_tensors(const mls_stage* s, PTensor (&t)[6]) {
   const mls_config& c = s->c;
-  t[0] = {s->off_g1, s->ioff_g1, 1, c.hidden, c.hidden, MLS_P_GAMMA1, 0.02, 1.0};
-  t[1] = {s->off_wqkv, s->ioff_wqkv, c.hidden, s->qkvw, s->ld_qkv, MLS_P_WQKV, 0.02, 0.0};
-  t[2] = {s->off_wo, s->ioff_wo, s->qd, c.hidden, s->ld_h, MLS_P_WO, 0.02, 0.0};
-  t[3] = {s->off_g2, s->ioff_g2, 1, c.hidden, c.hidden, MLS_P_GAMMA2, 0.02, 1.0};
-  t[4] = {s->off_wgu, s->ioff_wgu, c.hidden, 2 * int64_t(c.ffn), s->ld_gu, MLS_P_WGU, 0.02, 0.0};
-  t[5] = {s->off_wd, s->ioff_wd, c.ffn, c.hidden, s->ld_h, MLS_P_WD, 0.02, 0.0};
+  t[0] = {s->off_g1, s->ioff_g1, 1, c.hidden, c.hidden, MLS_P_GAMMA1, 0.02, 1.0, 0, 0};
+  t[1] = {s->off_wqkv, s->ioff_wqkv, c.hidden, s->qkvw, s->ld_qkv, MLS_P_WQKV, 0.02, 0.0, s->toff_wqkv, s->ld_h};
+  t[2] = {s->off_wo, s->ioff_wo, s->qd, c.hidden, s->ld_h, MLS_P_WO, 0.02, 0.0, s->toff_wo, s->ld_qd};
+  t[3] = {s->off_g2, s->ioff_g2, 1, c.hidden, c.hidden, MLS_P_GAMMA2, 0.02, 1.0, 0, 0};
+  t[4] = {s->off_wgu, s->ioff_wgu, c.hidden, 2 * int64_t(c.ffn), s->ld_gu, MLS_P_WGU, 0.02, 0.0, s->toff_wgu, s->ld_h};
+  t[5] = {s->off_wd, s->ioff_wd, c.ffn, c.hidden, s->ld_h, MLS_P_WD, 0.02, 0.0, s->toff_wd, s->ld_f};
 }
 
 int init_weights(mls_stage* s, uint64_t seed) {
@@ -192,16 +193,27 @@ int init_weights(mls_stage* s, uint64_t seed) {
   return MLS_OK;
 }
 
-// the transposed weight copies of every layer from the current weights (bf16 storage)
-int refresh_transposed(mls_stage* s) {
-  if (!s->params_t) return MLS_OK;
-  const mls_config& c = s->c;
-  for (int l = 0; l < c.max_layers; l++) {
-    HIP_TRY(mls::transpose_bf16(s->param(l, s->ioff_wqkv), s->ld_qkv, s->param_t(l, s->toff_wqkv), s->ld_h, c.hidden, s->qkvw, s->st));
-    HIP_TRY(mls::transpose_bf16(s->param(l, s->ioff_wo), s->ld_h, s->param_t(l, s->toff_wo), s->ld_qd, s->qd, c.hidden, s->st));
-    HIP_TRY(mls::transpose_bf16(s->param(l, s->ioff_wgu), s->ld_gu, s->param_t(l, s->toff_wgu), s->ld_h, c.hidden, 2 * c.ffn, s->st));
-    HIP_TRY(mls::transpose_bf16(s->param(l, s->ioff_wd), s->ld_h, s->param_t(l, s->toff_wd), s->ld_f, c.ffn, c.hidden, s->st));
+// One layer's parameters (bf16 storage) into their places.  src: the layer's tensors in the public layout, written to the
+// internal one and its transposed copies; null: the transposed copies alone, from the current internal weights.
+int place_layer(mls_stage* s, int layer, const char* src) {
+  PTensor t[6];
+  param_tensors(s, t);
+  mls::Spread m[6];
+  int n = 0;
+  for (auto& e : t) {
+    if (!src && !e.ld_t) continue;
+    const bool gu = e.tid == MLS_P_WGU && s->fuse_gu;
+    m[n].src = src ? src + e.off * s->es : s->param(layer, e.ioff);
+    m[n].ld_src = src ? e.cols : e.ld;
+    m[n].dst = src ? s->param(layer, e.ioff) : nullptr;
+    m[n].ld_dst = e.ld;
+    m[n].dst_t = e.ld_t ? s->param_t(layer, e.toff) : nullptr;
+    m[n].ld_t = e.ld_t;
+    m[n].rows = int(e.rows);
+    m[n].cols = int(e.cols);
+    m[n++].gu_f = gu && src ? s->c.ffn : 0;
   }
+  HIP_TRY(mls::spread_bf16(m, n, s->st));
   return MLS_OK;
 }
 
@@ -453,10 +465,11 @@ int mls_stage_init(const mls_config* cfg, uint64_t seed, void* hip_stream, mls_s
     release(s);
     return rc;
   }
-  if (int rc = refresh_transposed(s)) {
-    release(s);
-    return rc;
-  }
+  for (int l = 0; s->params_t && l < c.max_layers; l++)
+    if (int rc = place_layer(s, l, nullptr)) {
+      release(s);
+      return rc;
+    }
   if ((e = hipStreamSynchronize(s->st)) != hipSuccess) {
     release(s);
     return fail_hip(e, "hipStreamSynchronize");
@@ -631,7 +644,11 @@ int mls_stage_set_params(mls_stage* s, const void* src) {
   if (!s || !src) return fail(MLS_E_NULL, "mls_stage_set_params: null argument");
   PTensor t[6];
   param_tensors(s, t);
-  for (int l = 0; l < s->c.max_layers; l++)
+  // bf16: one pass per layer; a source that its 16-byte accesses cannot read goes through copies
+  const bool one_pass = s->params_t && !(uintptr_t(src) & 15);
+  for (int l = 0; one_pass && l < s->c.max_layers; l++)
+    if (int rc = place_layer(s, l, (const char*)src + size_t(l) * s->layer_params * s->es)) return rc;
+  for (int l = 0; !one_pass && l < s->c.max_layers; l++) {
     for (auto& e : t) {
       const char* p = (const char*)src + (size_t(l) * s->layer_params + e.off) * s->es;
       if (e.tid == MLS_P_WGU && s->fuse_gu)
@@ -639,7 +656,9 @@ int mls_stage_set_params(mls_stage* s, const void* src) {
       else
         HIP_TRY(copy2d(s, s->param(l, e.ioff), e.ld, p, e.cols, e.rows, e.cols));
     }
-  if (int rc = refresh_transposed(s)) return rc;
+    if (s->params_t)
+      if (int rc = place_layer(s, l, nullptr)) return rc;
+  }
   HIP_TRY(hipStreamSynchronize(s->st));
   return MLS_OK;
 }

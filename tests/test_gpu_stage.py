@@ -336,3 +336,28 @@ def test_rotary_epilogue_of_the_qkv_projection(nq, nkv, d, seq, mb):
         assert e <= 2e-3, (name, e)
     # per-head check on the last head of k and the last rows: a wrong pairing or position would be O(1) there
     assert rel_err(got[-64:, qd + kvd - d:qd + kvd], ref[-64:, qd + kvd - d:qd + kvd]) <= 2e-3
+
+
+@pytest.mark.parametrize("ffn", [328, 352])  # separate and interleaved gate/up columns
+@pytest.mark.parametrize("shift", [0, 1])    # a source at a 16-byte boundary (one pass) and off it (copies)
+def test_set_params_from_any_address(ffn, shift):
+    """Rows and columns that are no multiple of a 128 x 128 tile; both routes leave the same parameters and the same
+    transposed copies (the forward reads those, the backward the parameters themselves)."""
+    import torch
+    import paper_2410_13333_amd as mls
+    sh = RAGGED.with_(ffn=ffn, layers=2)
+    a, b = mls.Stage.from_shape(sh, seed=1000), mls.Stage.from_shape(sh, seed=7)
+    p = a.get_params()
+    buf = torch.zeros(p.numel() + 8, dtype=p.dtype, device="cuda")
+    buf[shift:shift + p.numel()] = p
+    b.set_params(buf[shift:shift + p.numel()])
+    assert torch.equal(b.get_params(), p)
+    out = []
+    for st in (a, b):
+        x = to_device(synth.make_x(sh, 2000, 0)[0], sh.dtype)
+        y, dx, g = torch.empty_like(x), torch.empty_like(x), torch.zeros(st.grad_elems, device="cuda")
+        st.forward(x, 2, y)
+        st.backward(x, g, 1, dx)
+        out.append((y, dx, g))
+        st.close()
+    assert all(torch.equal(u, v) for u, v in zip(*out))
