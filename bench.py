@@ -19,7 +19,7 @@ ROOT = os.path.dirname(os.path.abspath(__file__))
 sys.path.insert(0, ROOT)
 
 PEAK_BF16_TFLOPS = 2500.0   # MI355X dense bf16 MFMA
-# HBM bytes per GEMM launch (average over all gemm16_kernel and gemm_dma_kernel dispatches of a step), from the rocprofv3 --pmc
+# HBM bytes per GEMM launch (average over all gemm16_kernel and gemm_t16_kernel dispatches of a step), from the rocprofv3 --pmc
 # FETCH_SIZE / WRITE_SIZE runs summarised in profiles/stage_7b_4x4_hbm_traffic.txt:
 # (2.0 * 364308 KiB fetched + 1.0 * 85181 KiB written) * 1024.  Only valid for the default workload.
 PROFILED_GEMM_TRAFFIC = {"7b": 8.33e8}
@@ -408,7 +408,7 @@ def main():
         "frac_of_bf16_mfma_peak": tflops / PEAK_BF16_TFLOPS,
         "tau_ms_per_layer_microbatch": ms / (K * M),
         "model_flops_per_step": flops_step,
-        "roofline": {"bound": "mfma", "kernel": "gemm16_kernel (256x256 tiles) + gemm_dma_kernel (column remainders)", "achieved": achieved, "peak": PEAK_BF16_TFLOPS,
+        "roofline": {"bound": "mfma", "kernel": "gemm16_kernel (256x256 tiles) + gemm_t16_kernel (column remainders)", "achieved": achieved, "peak": PEAK_BF16_TFLOPS,
                      "unit": "TFLOP/s", "frac": achieved / PEAK_BF16_TFLOPS, "traffic": PROFILED_GEMM_TRAFFIC.get(a.workload),
                      "flops_per_launch": gemm_flops_launch, "avg_launch_ms": gemm_ms / gemm_n},
         "kernel_classes": classes,

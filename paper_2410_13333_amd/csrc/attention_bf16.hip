@@ -25,7 +25,7 @@ namespace {
 typedef __attribute__((ext_vector_type(4))) int i32x4;
 
 // 16 bytes per lane from a raw buffer straight into LDS (64 lanes fill 1 KiB at lds_byte); out-of-range lanes
-// are zero-filled.  Inline asm so that the waits are placed by hand (see gemm_bf16_dma.hip).
+// are zero-filled.  Inline asm so that the waits are placed by hand (see gemm_bf16_t16.hip).
 __device__ __forceinline__ void dma16(i32x4 rsrc, uint32_t voff, uint32_t lds_byte) {
   asm volatile("s_mov_b32 m0, %0\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds" ::"s"(lds_byte), "v"(voff), "s"(rsrc)
                : "memory");

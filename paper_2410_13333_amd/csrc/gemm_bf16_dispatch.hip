@@ -1,0 +1,181 @@
+// Which kernels run a bf16 contraction: whole rounds of 256x256 tiles on gemm_bf16_m16.hip, the rest on the smaller tiles
+// of gemm_bf16_t16.hip.  Host code only.
+#include <algorithm>
+#include <cmath>
+
+#include "kernels.h"
+
+namespace {
+
+constexpr int CUS = 256;
+
+struct Plan {
+  int n1;    // leading columns (a multiple of 256, possibly 0, or all) that run on 256x256 tiles
+  int tile;  // T16_*: how the columns from n1 on run
+};
+
+// Estimated microseconds of M x N outputs over a contraction of `it` 64-deep k-tiles, from a fit to stand-alone timings of
+// every tile size at 66 shapes (the products of layers with 135 to 4096 tokens and hidden widths 256 to 8192, all three
+// forms, N(0,1) operands).
+//   256x256, 256x128, 128x128: one workgroup per CU.  A round costs base + it * c; c depends on how full the chip is
+//     (clock and L2 bandwidth are shared): 256x256 1.00 us per k-tile on a few CUs, 1.38 on all; 256x128 0.60 and 0.85;
+//     128x128 0.36 and 0.51.
+//   128x64, 64x64: two and three workgroups per CU.  A lone workgroup is a chain of waits (0.26, 0.21 us per k-tile);
+//     past that the loads of a CU's workgroups add up.
+// The plan with the smallest estimate is on average 0.4 % slower than the fastest one measured at those shapes; the worst
+// is 12 % (768 x 4096 over 1008: 18 us instead of 16).
+enum { TILE_M16 = -1 };
+double estimate(int tile, int64_t M, int64_t N, int64_t it) {
+  struct Round { int bm, bn; double lo, hi, base; };
+  struct Load { int bm, bn; double lone, c0, c1, base; };
+  const Round r = tile == TILE_M16 ? Round{256, 256, 1.00, 1.38, 7.0}
+                  : tile == mls::T16_256x128 ? Round{256, 128, 0.60, 0.85, 5.5} : Round{128, 128, 0.36, 0.51, 4.5};
+  if (tile == TILE_M16 || tile == mls::T16_256x128 || tile == mls::T16_128x128) {
+    const int64_t w = ((M + r.bm - 1) / r.bm) * ((N + r.bn - 1) / r.bn), full = w / CUS;
+    const double part = double(w % CUS) / CUS;
+    return double(full) * (double(it) * r.hi + r.base) + (part > 0 ? double(it) * (r.lo + (r.hi - r.lo) * part) + r.base : 0.0);
+  }
+  const Load l = tile == mls::T16_128x64 ? Load{128, 64, 0.26, 0.20, 0.215, 4.0} : Load{64, 64, 0.21, 0.15, 0.165, 3.2};
+  const double load = double(((M + l.bm - 1) / l.bm) * ((N + l.bn - 1) / l.bn)) / CUS;
+  return l.base * std::max(1.0, load / 2) + double(it) * std::max(l.lone, l.c0 + l.c1 * load);
+}
+
+Plan plan(int M, int N, int64_t K, bool m16) {
+  const int64_t it = (K + 63) / 64, tm = (M + 255) / 256, tn = (N + 255) / 256;
+  const int n1 = int(tm * tn / CUS * CUS / tm) * 256;  // columns that whole rounds of 256x256 tiles cover
+  Plan best = {N, mls::T16_256x128};
+  double t = m16 ? estimate(TILE_M16, M, N, it) : HUGE_VAL;
+  for (int tile : {mls::T16_256x128, mls::T16_128x128, mls::T16_128x64, mls::T16_64x64}) {
+    const double all = estimate(tile, M, N, it);
+    if (all < t) {
+      t = all;
+      best = {0, tile};
+    }
+    if (!m16 || n1 == 0 || n1 >= N) continue;
+    const double both = estimate(TILE_M16, M, n1, it) + estimate(tile, M, N - n1, it) + 1.5;  // (and one more launch)
+    if (both < t) {
+      t = both;
+      best = {n1, tile};
+    }
+  }
+  return best;
+}
+
+// the columns from n1 on of a problem whose B is given for all of them
+mls::T16Problem columns_from(mls::T16Problem p, int n1) {
+  const bool nt = p.form == mls::T16_NT || p.form == mls::T16_NT_SWIGLU || p.form == mls::T16_NT_ROPE;
+  if (nt) {
+    p.B = (const uint16_t*)p.B + int64_t(n1) * p.ldb;
+    p.bb = uint32_t(int64_t(p.N - n1) * p.ldb * 2);
+  } else {
+    if (p.B) p.B = (const uint16_t*)p.B + n1;
+    for (int i = 0; i < p.nseg; i++) p.seg_b[i] = (const uint16_t*)p.seg_b[i] + n1;
+  }
+  p.N -= n1;
+  p.col0 = n1;
+  return p;
+}
+
+// `big(n1)` runs the leading n1 columns on 256x256 tiles
+template <class Big>
+hipError_t run(const mls::T16Problem& p, int mode, hipStream_t st, Big&& big) {
+  const Plan pl = plan(p.M, p.N, int64_t(p.K) * std::max(1, p.nseg), mls::gemm_m16_ok(mode, p.K));
+  if (pl.n1 > 0)
+    if (hipError_t e = big(pl.n1)) return e;
+  if (pl.n1 == p.N) return hipSuccess;
+  return mls::gemm_t16(columns_from(p, pl.n1), pl.tile, st);
+}
+
+mls::T16Problem problem(int form, const void* A, const void* B, void* C, int M, int N, int K, int64_t lda, int64_t ldb,
+                        int64_t ldc, uint32_t ab, uint32_t bb) {
+  mls::T16Problem p = {};
+  p.form = form;
+  p.A = A; p.B = B; p.C = C;
+  p.M = M; p.N = N; p.K = K;
+  p.lda = lda; p.ldb = ldb; p.ldc = ldc;
+  p.ab = ab; p.bb = bb;
+  return p;
+}
+
+}  // namespace
+
+namespace mls {
+
+// true if the DMA kernels can run this problem: every operand (plus one tile of slack) addressable with a 31-bit byte
+// offset
+bool gemm_bf16_dma_ok(int mode, int M, int N, int K, int64_t lda, int64_t ldb) {
+  const int64_t a_rows = mode == GEMM_TN ? K : M, b_rows = mode == GEMM_NT ? N : K;
+  const int64_t lim = int64_t(1) << 31;
+  return (a_rows + 512) * lda * 2 < lim && (b_rows + 512) * ldb * 2 < lim && K > 0;
+}
+
+hipError_t gemm_bf16_dma(int mode, const void* A, const void* B, void* C, const void* R, int M, int N, int K,
+                         int64_t lda, int64_t ldb, int64_t ldc, int64_t ldr, hipStream_t st) {
+  if (M == 0 || N == 0) return hipSuccess;
+  const int64_t a_rows = mode == GEMM_TN ? K : M, b_rows = mode == GEMM_NT ? N : K;
+  const uint32_t ab = uint32_t(a_rows * lda * 2), bb = uint32_t(b_rows * ldb * 2);
+  T16Problem p = problem(mode == GEMM_NN ? T16_NN : mode == GEMM_NT ? T16_NT : T16_TN, A, B, C, M, N, K, lda, ldb, ldc, ab, bb);
+  p.R = R;
+  p.ldr = ldr;
+  return run(p, mode, st, [&](int n1) { return gemm_m16(mode, A, B, C, R, M, n1, K, lda, ldb, ldc, ldr, ab, bb, st); });
+}
+
+bool gemm_tn_segments_ok(int kseg, int64_t lda, int64_t ldb) { return gemm_bf16_dma_ok(GEMM_TN, 8, 8, kseg, lda, ldb); }
+
+// C[M,N] += sum_i A_i[kseg,M]^T * B_i[kseg,N] (fp32 C), the contraction of all pieces accumulated in registers and
+// added to C once: the weight gradient of several micro-batches in one launch.  nseg <= 16.
+hipError_t gemm_bf16_tn_segments(const void* const* A, const void* const* B, int nseg, void* C, int M, int N, int kseg,
+                                 int64_t lda, int64_t ldb, int64_t ldc, hipStream_t st, int gu_f, bool overwrite) {
+  if (M == 0 || N == 0 || nseg == 0 || kseg == 0) return hipSuccess;
+  if (nseg > 16 || (gu_f > 0 && (gu_f % 32 || N != 2 * gu_f))) return hipErrorInvalidValue;
+  const uint32_t ab = uint32_t(int64_t(kseg) * lda * 2), bb = uint32_t(int64_t(kseg) * ldb * 2);
+  T16Problem p = problem(T16_TN_SEGS, A[0], nullptr, C, M, N, kseg, lda, ldb, ldc, ab, bb);
+  p.nseg = nseg;
+  for (int i = 0; i < nseg; i++) {
+    p.seg_a[i] = A[i];
+    p.seg_b[i] = B[i];
+  }
+  p.ldx = overwrite ? 1 : 0;
+  p.xf = gu_f;
+  return run(p, GEMM_TN, st, [&](int n1) {
+    return gemm_m16_tn_segments(A, B, nseg, C, M, n1, kseg, lda, ldb, ldc, ab, bb, st, gu_f, overwrite);
+  });
+}
+
+bool gemm_swiglu_ok(int M, int f, int K, int64_t lda, int64_t ldw) {
+  return f > 0 && f % 32 == 0 && gemm_bf16_dma_ok(GEMM_NT, M, 2 * f, K, lda, ldw);
+}
+
+hipError_t gemm_bf16_swiglu(const void* A, const void* W, void* GU, void* Z, int M, int f, int K, int64_t lda,
+                            int64_t ldw, int64_t ldgu, int64_t ldz, hipStream_t st) {
+  if (M == 0 || f == 0) return hipSuccess;
+  if (!gemm_swiglu_ok(M, f, K, lda, ldw)) return hipErrorInvalidValue;
+  const uint32_t ab = uint32_t(int64_t(M) * lda * 2), wb = uint32_t(int64_t(2 * f) * ldw * 2);
+  T16Problem p = problem(T16_NT_SWIGLU, A, W, GU, M, 2 * f, K, lda, ldw, ldgu, ab, wb);
+  p.X = Z;
+  p.ldx = ldz;
+  return run(p, GEMM_NT, st, [&](int n1) { return gemm_m16_swiglu(A, W, GU, Z, M, n1, K, lda, ldw, ldgu, ldz, ab, wb, st); });
+}
+
+bool gemm_rope_ok(int M, int N, int K, int64_t lda, int64_t ldw, int seq, int rot_cols, int head_dim) {
+  return (head_dim == 64 || head_dim == 128) && seq > 0 && rot_cols >= 0 && rot_cols <= N && rot_cols % head_dim == 0 &&
+         N % head_dim == 0 && gemm_bf16_dma_ok(GEMM_NT, M, N, K, lda, ldw);
+}
+
+hipError_t gemm_bf16_rope(const void* A, const void* W, void* C, int M, int N, int K, int64_t lda, int64_t ldw, int64_t ldc,
+                          const float* cos_tab, const float* sin_tab, int seq, int rot_cols, int head_dim, hipStream_t st) {
+  if (M == 0 || N == 0) return hipSuccess;
+  if (!cos_tab || !sin_tab || !gemm_rope_ok(M, N, K, lda, ldw, seq, rot_cols, head_dim)) return hipErrorInvalidValue;
+  const uint32_t ab = uint32_t(int64_t(M) * lda * 2), wb = uint32_t(int64_t(N) * ldw * 2);
+  T16Problem p = problem(T16_NT_ROPE, A, W, C, M, N, K, lda, ldw, ldc, ab, wb);
+  p.cos_tab = cos_tab;
+  p.sin_tab = sin_tab;
+  p.seq = seq;
+  p.rot_cols = rot_cols;
+  p.head_dim = head_dim;
+  return run(p, GEMM_NT, st, [&](int n1) {
+    return gemm_m16_rope(A, W, C, M, n1, K, lda, ldw, ldc, ab, wb, cos_tab, sin_tab, seq, rot_cols, head_dim, st);
+  });
+}
+
+}  // namespace mls

@@ -35,7 +35,7 @@
 // Restrictions, checked by the launcher: K (and the piece length of a segmented contraction) a multiple of 32, of
 // 64 when A is stored [row][k], so that no k-tile is ragged and no pair straddles the end; everything else (ragged
 // M and N) is handled by out-of-range requests that zero-fill.  The launcher covers whole 256-column tiles; the
-// column remainder of a problem runs on the kernels of gemm_bf16_dma.hip.
+// column remainder of a problem runs on the kernels of gemm_bf16_t16.hip.
 #include <type_traits>
 #include <utility>
 
@@ -431,7 +431,10 @@ __global__ __launch_bounds__(NW * 64) void gemm16_kernel(const bf16_t* __restric
     // on its SIMD here: as plain loads, used right away, the entries cost their full latency in every block (48 us per
     // launch at the 7B shape), and held in registers ahead of time they spill.  A row of a slot keeps its 16-byte
     // chunks XORed with the row index (bank conflicts), applied on the global-address side.
-    const bool use_rope = EPI == E_ROPE && col0 + int(ccol0) < rope.rot_cols;  // wave-uniform: whole heads; v is not rotated
+    // columns of this wavefront that are rotated: whole heads; v, behind them, is not (with heads of 64 columns both can lie
+    // in its 128)
+    const int rot = EPI == E_ROPE ? rope.rot_cols - (col0 + int(ccol0)) : 0;
+    const bool use_rope = rot > 0;
     constexpr int RING0 = 32768, RING_SLOT = 8192;
     const uint32_t ring = lds0 + RING0 + wave * (3 * RING_SLOT);
     const unsigned char* ringp = smem + RING0 + wave * (3 * RING_SLOT);
@@ -501,7 +504,7 @@ __global__ __launch_bounds__(NW * 64) void gemm16_kernel(const bf16_t* __restric
           const unsigned char* slot = ringp + (i % 3) * RING_SLOT + l16 * (64 * TP);
 #pragma unroll
           for (int j = 0; j < 8; j++) {
-            if ((j % (2 * TP)) >= TP) continue;  // second halves go with their firsts
+            if ((j % (2 * TP)) >= TP || 16 * j >= rot) continue;  // second halves go with their firsts
             const int jp = j + TP;
             const int ch = ((j % TP) * 4 + g4) ^ sw;  // chunk of features 16 (j % TP) + 4 g4 .. +3
             const float4 cs = *reinterpret_cast<const float4*>(slot + (ch << 4));
@@ -610,24 +613,22 @@ hipError_t gemm_m16(int mode, const void* A, const void* B, void* C, const void*
 
 
 // GU[M, N = 2f] = A[M,K] W[K, 2f] (interleaved gate/up columns), Z[M, f] = silu(gate) * up; N a multiple of 256 here.
-// w_nk: W is given transposed, [2f][K] with row stride ldw.
+// W is given transposed, [2f][K] with row stride ldw.
 hipError_t gemm_m16_swiglu(const void* A, const void* W, void* GU, void* Z, int M, int N, int K, int64_t lda, int64_t ldw,
-                           int64_t ldgu, int64_t ldz, uint32_t ab, uint32_t bb, hipStream_t st, bool w_nk) {
+                           int64_t ldgu, int64_t ldz, uint32_t ab, uint32_t bb, hipStream_t st) {
   const bf16_t* a = static_cast<const bf16_t*>(A);
   const bf16_t* w = static_cast<const bf16_t*>(W);
-  if (w_nk) return launch16<false, false, E_SWIGLU, false>(a, w, GU, nullptr, M, N, K, lda, ldw, ldgu, 0, ab, bb, st, nullptr, Z, ldz, 0, nullptr);
-  return launch16<false, true, E_SWIGLU, false>(a, w, GU, nullptr, M, N, K, lda, ldw, ldgu, 0, ab, bb, st, nullptr, Z, ldz, 0, nullptr);
+  return launch16<false, false, E_SWIGLU, false>(a, w, GU, nullptr, M, N, K, lda, ldw, ldgu, 0, ab, bb, st, nullptr, Z, ldz, 0, nullptr);
 }
 // C[M, N] = A[M,K] W[K,N] with the head vectors in the columns below rot_cols rotated by the angle of their row's
-// position.  w_nk: W is given transposed, [N][K] with row stride ldw.
+// position.  W is given transposed, [N][K] with row stride ldw.
 hipError_t gemm_m16_rope(const void* A, const void* W, void* C, int M, int N, int K, int64_t lda, int64_t ldw, int64_t ldc,
                          uint32_t ab, uint32_t bb, const float* cos_tab, const float* sin_tab, int seq, int rot_cols,
-                         int head_dim, hipStream_t st, bool w_nk) {
+                         int head_dim, hipStream_t st) {
   const RopeArgs ra = {cos_tab, sin_tab, seq, rot_cols, head_dim};
   const bf16_t* a = static_cast<const bf16_t*>(A);
   const bf16_t* w = static_cast<const bf16_t*>(W);
-  if (w_nk) return launch16<false, false, E_ROPE, false>(a, w, C, nullptr, M, N, K, lda, ldw, ldc, 0, ab, bb, st, nullptr, nullptr, 0, 0, &ra);
-  return launch16<false, true, E_ROPE, false>(a, w, C, nullptr, M, N, K, lda, ldw, ldc, 0, ab, bb, st, nullptr, nullptr, 0, 0, &ra);
+  return launch16<false, false, E_ROPE, false>(a, w, C, nullptr, M, N, K, lda, ldw, ldc, 0, ab, bb, st, nullptr, nullptr, 0, 0, &ra);
 }
 
 // C[M, N] (+)= sum_i A_i[kseg, M]^T B_i[kseg, N] in fp32 over nseg <= 16 pieces (kseg a multiple of 32), N a multiple

@@ -1,0 +1,506 @@
+// bf16 GEMM on v_mfma_f32_16x16x32_bf16 for everything that whole rounds of 256x256 tiles (gemm_bf16_m16.hip) do not
+// cover: the columns left over, problems with fewer tiles than CUs, contraction lengths that are no multiple of its
+// k-tile.  Smaller tiles of the same design, 4 wavefronts per workgroup:
+//   256x128   half the work per workgroup
+//   128x128   a quarter
+//   128x64    an eighth
+//   64x64     small problems: what bounds them is the chain of one tile, so as many tiles as possible
+// (for both of the last two 64x128 where the epilogue needs a whole head or a gate/up pair inside one wavefront)
+//
+// Main loop: k-tiles are 64 deep (128 bytes of a [row][k] operand's row: whole cache lines), NS stages in LDS filled by
+// buffer_load_dwordx4 ... lds.  A k-tile is two steps of one MFMA's depth, whose fragments live in two register sets:
+//   first half   MFMAs of step 0, the LDS reads of step 1 in between;
+//   wait for this wavefront's share of tile t+1, one workgroup barrier: tile t is read, tile t+1 is there;
+//   second half  MFMAs of step 1, the LDS reads of tile t+1's step 0 and the requests for tile t+NS (into tile t's stage)
+//                in between.
+// So no MFMA waits for LDS, there is one barrier per 64 of depth, and a tile is requested NS - 1/2 iterations before it is
+// read.  As in the 256x256 kernel the MFMAs, reads and requests are volatile asm in their issue order.  The contraction
+// may end inside a k-tile: lanes whose 16-byte chunk (or k-row) lies beyond the end request out of range and get zeros.
+//
+// What bounds them: at full chips the data moved per product (a 256x128 tile pulls 1.5 times the bytes per FLOP of a 256x256
+// one from L2, about 13 TB/s in all at every size here) and, with it, the power limit: 256x128 runs 1 060 .. 1 130 TFLOP/s
+// on N(0,1) operands and 1 450 on zeros (2048 x 4096 x 11008), 128x128 1 000 .. 1 080.  On a few workgroups the chain of a
+// k-tile (0.21 us at 64x64).  The tiles they replace ran on v_mfma_f32_32x32x16 with plain two-stage (256x128) or
+// three-stage (128x128) pipelines: 822 TFLOP/s in the 2048-token 7B layer (256x128), 10 us instead of 4.3 .. 7.8 on a
+// 256-token layer's products (128x128).
+//
+// LDS map of a stage: the A tile, then the B tile.  [row][64 k]: 128-byte rows, the eight 16-byte chunks permuted by
+// (row >> 1) & 7.  [k][col]: rows of the tile's width, XOR swizzled (swz_kcol); both on the global-address side, both
+// free of bank conflicts for the reads.
+#include <type_traits>
+#include <utility>
+
+#include "common.h"
+#include "kernels.h"
+
+namespace {
+
+typedef __attribute__((ext_vector_type(4))) int i32x4;
+typedef __attribute__((ext_vector_type(2))) int i32x2;
+
+constexpr int BK = 64;
+constexpr uint32_t OOB = 0x80000000u;
+constexpr int MAX_SEGS = 16;
+
+enum { E_BF16 = 0, E_F32 = 1, E_SWIGLU = 2, E_ROPE = 3 };
+
+template <class F, int... I>
+__device__ __forceinline__ void static_for_impl(F&& f, std::integer_sequence<int, I...>) {
+  (f(std::integral_constant<int, I>{}), ...);
+}
+template <int N, class F>
+__device__ __forceinline__ void static_for(F&& f) {
+  static_for_impl(f, std::make_integer_sequence<int, N>{});
+}
+
+struct SegArgs {
+  const bf16_t* a[MAX_SEGS];
+  const bf16_t* b[MAX_SEGS];
+  int nseg;
+};
+struct RopeArgs {
+  const float* cos_tab;
+  const float* sin_tab;
+  int seq, rot_cols, head_dim;
+};
+
+__device__ __forceinline__ i32x4 make_rsrc(const void* p, uint32_t bytes) {
+  const uint64_t a = (uint64_t)p;
+  i32x4 r;
+  r[0] = (int)(uint32_t)a;
+  r[1] = (int)((uint32_t)(a >> 32) & 0xffffu);  // stride 0: raw buffer, byte offsets
+  r[2] = (int)bytes;
+  r[3] = 0x00020000;
+  return r;
+}
+// 16 bytes per lane from a raw buffer straight into LDS: 64 lanes fill 1 KiB at lds_byte.  soff is a scalar byte
+// offset added to the address; it is not part of the range check (voff >= num_records zero-fills).
+__device__ __forceinline__ void dma16s(i32x4 rsrc, uint32_t voff, uint32_t soff, uint32_t lds_byte) {
+  asm volatile("s_mov_b32 m0, %0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds" ::"s"(lds_byte), "v"(voff), "s"(rsrc), "s"(soff)
+               : "memory");
+}
+template <int N>
+__device__ __forceinline__ void wait_vmcnt() {
+  asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");
+}
+__device__ __forceinline__ void wait_lgkm0() { asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory"); }
+__device__ __forceinline__ void wave_lds_sync() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+// C tile (16 columns x 16 rows, transposed product): lane l ends up with C[row l%16][cols 4*(l/16) .. +3]
+__device__ __forceinline__ void mfma16(f32x4& c, const i32x4& bfrag, const i32x4& afrag) {
+  asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+a"(c) : "v"(bfrag), "v"(afrag));
+}
+template <int OFF>
+__device__ __forceinline__ void lds_read16(i32x4& f, uint32_t addr) {
+  asm volatile("ds_read_b128 %0, %1 offset:%2" : "=v"(f) : "v"(addr), "n"(OFF) : "memory");
+}
+// transposing read of a [k][col] tile: two 8-byte reads (k-rows kr and kr+4 of the lane's group of eight); ROW bytes per
+// k-row
+template <int OFF, int ROW>
+__device__ __forceinline__ void lds_read16_tr(i32x4& f, uint32_t addr) {
+  i32x2 lo, hi;
+  asm volatile("ds_read_b64_tr_b16 %0, %2 offset:%3\n\tds_read_b64_tr_b16 %1, %2 offset:%4"
+               : "=&v"(lo), "=&v"(hi)
+               : "v"(addr), "n"(OFF), "n"(OFF + 4 * ROW)
+               : "memory");
+  f = i32x4{lo[0], lo[1], hi[0], hi[1]};  // (the two halves are allocated as one register quad: no copies)
+}
+
+// [k][col] tiles of CB 16-byte chunks per k-row: XOR applied to the chunk index of k-row kr.  A transposing 8-byte read
+// takes, per group of 16 lanes, 32 bytes from each of k-rows kr0 .. kr0+3, and 32 lanes (two groups, k-rows 8 apart) go
+// through the 64 banks (256 bytes) together: the eight 32-byte pieces must lie in eight different places of a bank round.
+// Rows of 256 bytes or more: bits 2, 3 from kr & 3, bit 1 from bit 3 of kr; rows of 128 bytes alternate between the
+// halves of a round by themselves, the rest comes from bits 1 and 3 of kr.
+template <int CB>
+__device__ __forceinline__ constexpr int swz_kcol(int kr) {
+  return CB >= 16 ? ((kr & 3) << 2) | (((kr >> 3) & 1) << 1) : (((kr >> 1) & 1) << 2) | (((kr >> 3) & 1) << 1);
+}
+
+// Wavefront tile: (16 WTM) x (16 WTN); WGM x (4 / WGM) wavefronts.
+template <int WTM, int WTN, int WGM, bool ATR, bool BTR, int EPI, bool SEG, int NS>
+struct Cfg {
+  static constexpr int WGN = 4 / WGM, BM = 16 * WTM * WGM, BN = 16 * WTN * WGN;
+  static constexpr int A_BYTES = BM * BK * 2, B_BYTES = BN * BK * 2, STAGE = A_BYTES + B_BYTES, LDS = NS * STAGE;
+  static constexpr int NQA = BM / 32, NQB = BN / 32;  // requests per wavefront and k-tile
+  // workgroups a CU can hold by LDS (of 160 KiB); registers follow
+  static constexpr int PER_CU = LDS > 80 * 1024 ? 1 : LDS > 53 * 1024 ? 2 : 3;
+};
+
+template <int WTM, int WTN, int WGM, bool ATR, bool BTR, int EPI, bool SEG, int NS>
+__global__ __launch_bounds__(256, (Cfg<WTM, WTN, WGM, ATR, BTR, EPI, SEG, NS>::PER_CU)) void gemm_t16_kernel(
+    const bf16_t* __restrict__ A, const bf16_t* __restrict__ B, void* __restrict__ Cv, const bf16_t* __restrict__ R, int M,
+    int N, int K, int64_t lda, int64_t ldb, int64_t ldc, int64_t ldr, uint32_t a_bytes, uint32_t b_bytes, int tiles_m,
+    int col0, void* __restrict__ Xv, int64_t ldx, int xf, SegArgs segs, RopeArgs rope) {
+  using G = Cfg<WTM, WTN, WGM, ATR, BTR, EPI, SEG, NS>;
+  constexpr int BM = G::BM, BN = G::BN;
+  extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
+  // tile of this workgroup: each XCD gets a contiguous run of tiles, walked in groups of about 1024 rows, N fastest
+  const int nwg = gridDim.x, pid = blockIdx.x;
+  const int xcd = pid & 7, q8 = nwg >> 3, rem = nwg & 7;
+  const int tile = xcd * q8 + (xcd < rem ? xcd : rem) + (pid >> 3);
+  const int gm = min(1024 / BM, tiles_m);
+  const int per_group = gm * (nwg / tiles_m), grp = tile / per_group, first_m = grp * gm;
+  const int gsz = min(tiles_m - first_m, gm), in_grp = tile - grp * per_group;
+  const int m0 = (first_m + in_grp % gsz) * BM, n0 = (in_grp / gsz) * BN;
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int wm = (wave % WGM) * (16 * WTM), wn = (wave / WGM) * (16 * WTN);
+  const int l16 = lane & 15, g4 = lane >> 4;
+  const uint32_t lds0 = (uint32_t)(uintptr_t)(MLS_LDS unsigned char*)smem;
+
+  // ---- requests: fixed per-lane byte offsets, the k-tile enters as a scalar.  klim: contraction indices of the tile that
+  // exist (BK except for the last tile of a piece).
+  constexpr int NQA = G::NQA, NQB = G::NQB, NREQ = NQA + NQB;
+  constexpr int CA = BM / 8, CB = BN / 8;  // 16-byte chunks per k-row of a [k][col] tile
+  uint32_t goa[NQA], gob[NQB];
+  auto set_offsets = [&](int klim) {
+#pragma unroll
+    for (int i = 0; i < NQA; i++) {
+      const int q = wave * NQA + i;
+      if (ATR) {
+        const int kr = q * (64 / CA) + lane / CA, c = (lane % CA) ^ swz_kcol<CA>(kr);
+        goa[i] = m0 + c * 8 < M && kr < klim ? uint32_t((int64_t(kr) * lda + m0 + c * 8) * 2) : OOB;
+      } else {
+        const int r = q * 8 + (lane >> 3), c = (lane & 7) ^ ((r >> 1) & 7);
+        goa[i] = m0 + r < M && c * 8 < klim ? uint32_t((int64_t(m0 + r) * lda + c * 8) * 2) : OOB;
+      }
+    }
+#pragma unroll
+    for (int i = 0; i < NQB; i++) {
+      const int q = wave * NQB + i;
+      if (BTR) {
+        const int kr = q * (64 / CB) + lane / CB, c = (lane % CB) ^ swz_kcol<CB>(kr);
+        gob[i] = n0 + c * 8 < N && kr < klim ? uint32_t((int64_t(kr) * ldb + n0 + c * 8) * 2) : OOB;
+      } else {
+        const int r = q * 8 + (lane >> 3), c = (lane & 7) ^ ((r >> 1) & 7);
+        gob[i] = n0 + r < N && c * 8 < klim ? uint32_t((int64_t(n0 + r) * ldb + c * 8) * 2) : OOB;
+      }
+    }
+  };
+  const int tps = (K + BK - 1) / BK, krem = K - (tps - 1) * BK;  // k-tiles per piece, depth of the last one
+  const int nk = (SEG ? segs.nseg : 1) * tps;
+  const uint32_t ka = ATR ? uint32_t(lda * (BK * 2)) : BK * 2, kb = BTR ? uint32_t(ldb * (BK * 2)) : BK * 2;
+  const i32x4 dead_a = make_rsrc(A, 0), dead_b = make_rsrc(B, 0);
+  i32x4 ra = make_rsrc(SEG ? segs.a[0] : A, a_bytes), rb = make_rsrc(SEG ? segs.b[0] : B, b_bytes);
+  int rq_tile = 0, rq_seg = 0, rq_in = 0;  // request cursor: next k-tile, its piece and its index inside the piece
+  set_offsets(tps == 1 ? krem : BK);
+  auto request = [&](uint32_t stage, auto DC) {  // request D of this wavefront for the cursor's k-tile
+    constexpr int d = decltype(DC)::value;
+    const bool live = rq_tile < nk;
+    if constexpr (d < NQA) dma16s(live ? ra : dead_a, goa[d], uint32_t(rq_in) * ka, lds0 + stage + (wave * NQA + d) * 1024);
+    else dma16s(live ? rb : dead_b, gob[d - NQA], uint32_t(rq_in) * kb, lds0 + stage + G::A_BYTES + (wave * NQB + d - NQA) * 1024);
+  };
+  auto advance = [&]() {
+    rq_tile++;
+    rq_in++;
+    if (SEG && rq_in == tps) {
+      rq_in = 0;
+      rq_seg++;
+      const int i = rq_seg < segs.nseg ? rq_seg : segs.nseg - 1;
+      ra = make_rsrc(segs.a[i], a_bytes);
+      rb = make_rsrc(segs.b[i], b_bytes);
+      if (krem < BK && tps > 1) set_offsets(BK);
+    }
+    if (krem < BK && tps > 1 && rq_in == tps - 1) set_offsets(krem);
+  };
+
+  // ---- fragment addresses inside stage 0: for a [row][64 k] operand one per step (the permutation turns the step into an
+  // XOR), fragment i at +2048 i; for a [k][col] operand one per fragment, the step at +32 k-rows
+  constexpr int NAA = ATR ? WTM : 2, NBA = BTR ? WTN : 2;
+  uint32_t fa_b[NAA], fb_b[NBA];
+#pragma unroll
+  for (int i = 0; i < NAA; i++) {
+    const int kr = g4 * 8 + (l16 >> 2), col = wm + i * 16 + (l16 & 3) * 4;
+    fa_b[i] = lds0 + (ATR ? kr * (BM * 2) + (((col >> 3) ^ swz_kcol<CA>(kr)) << 4) + (col & 7) * 2
+                          : (wm + l16) * 128 + (((i * 4 + g4) ^ ((l16 >> 1) & 7)) << 4));
+  }
+#pragma unroll
+  for (int j = 0; j < NBA; j++) {
+    const int kr = g4 * 8 + (l16 >> 2), col = wn + j * 16 + (l16 & 3) * 4;
+    fb_b[j] = lds0 + G::A_BYTES + (BTR ? kr * (BN * 2) + (((col >> 3) ^ swz_kcol<CB>(kr)) << 4) + (col & 7) * 2
+                                       : (wn + l16) * 128 + (((j * 4 + g4) ^ ((l16 >> 1) & 7)) << 4));
+  }
+  i32x4 fa[2][WTM], fb[2][WTN];
+  // LDS read n (A fragments first) of step ST of the tile in `stage` into fragment set ST
+  auto rd = [&](auto STC, auto NC, uint32_t stage) {
+    constexpr int st = decltype(STC)::value, n = decltype(NC)::value;
+    if constexpr (n < WTM) {
+      if constexpr (ATR) lds_read16_tr<st * 32 * BM * 2, BM * 2>(fa[st][n], fa_b[n] + stage);
+      else lds_read16<n * 2048>(fa[st][n], fa_b[st] + stage);
+    } else {
+      if constexpr (BTR) lds_read16_tr<st * 32 * BN * 2, BN * 2>(fb[st][n - WTM], fb_b[n - WTM] + stage);
+      else lds_read16<(n - WTM) * 2048>(fb[st][n - WTM], fb_b[st] + stage);
+    }
+  };
+  f32x4 c[WTM][WTN];
+#pragma unroll
+  for (int i = 0; i < WTM; i++)
+#pragma unroll
+    for (int j = 0; j < WTN; j++) c[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+
+  constexpr int NM = WTM * WTN, NR = WTM + WTN;
+  using S0 = std::integral_constant<int, 0>;
+  using S1 = std::integral_constant<int, 1>;
+  // prologue: tiles 0 .. NS-1 requested, step 0 of tile 0 read
+#pragma unroll
+  for (int s = 0; s < NS; s++) {
+    static_for<NREQ>([&](auto DC) { request(s * G::STAGE, DC); });
+    advance();
+  }
+  wait_vmcnt<(NS - 1) * NREQ>();
+  __builtin_amdgcn_s_barrier();
+  static_for<NR>([&](auto NC) { rd(S0{}, NC, 0); });
+  wait_lgkm0();
+
+  uint32_t cur = 0;
+  for (int t = 0; t < nk; t++) {
+    const uint32_t nxt = cur == (NS - 1) * G::STAGE ? 0 : cur + G::STAGE;
+    // first half: the reads go out over the first three quarters of the MFMAs
+    static_for<NM>([&](auto MC) {
+      constexpr int m = decltype(MC)::value, span = NM * 3 / 4 > 0 ? NM * 3 / 4 : 1;
+      mfma16(c[m / WTN][m % WTN], fb[0][m % WTN], fa[0][m / WTN]);
+      static_for<NR>([&](auto RC) {
+        if constexpr (decltype(RC)::value * span / NR == m) rd(S1{}, RC, cur);
+      });
+    });
+    wait_lgkm0();                      // this wavefront's reads of tile t are back
+    wait_vmcnt<(NS - 2) * NREQ>();     // its share of tile t+1 has landed
+    __builtin_amdgcn_s_barrier();
+    // second half: the reads of tile t+1 over its first part; the requests for tile t+NS into the stage just freed are
+    // spread over all of it (as a burst in either part they cost 5 to 8 %)
+    static_for<NM>([&](auto MC) {
+      constexpr int m = decltype(MC)::value, span = NM / 2 > 0 ? NM / 2 : 1;
+      mfma16(c[m / WTN][m % WTN], fb[1][m % WTN], fa[1][m / WTN]);
+      static_for<NR>([&](auto RC) {
+        if constexpr (decltype(RC)::value * span / NR == m) rd(S0{}, RC, nxt);
+      });
+      static_for<NREQ>([&](auto DC) {
+        if constexpr (decltype(DC)::value * NM / NREQ == m) request(cur, DC);
+      });
+    });
+    // the fragments must have arrived before anything but the issue order above: what follows branches, and the compiler,
+    // to which a read's result is there at once, may move registers around a branch
+    wait_lgkm0();
+    advance();
+    // the compiler does not see MFMAs written as asm and inserts no wait states behind them: whatever it places at the
+    // loop exit must find the last result written
+    asm volatile("s_nop 15" ::: "memory");
+    cur = nxt;
+  }
+  wait_vmcnt<0>();
+  __syncthreads();
+
+  // ---- epilogue.  Lane l holds, of MFMA tile (i, j): C[row 16 i + l%16][cols 16 j + 4 (l/16) .. +3].
+  const int64_t crow0 = m0 + wm, ccol0 = n0 + wn;
+  if constexpr (EPI == E_F32) {
+    // C (+)= acc in fp32, straight from the accumulator layout (16 bytes per lane); xf > 0: the columns are in the
+    // interleaved gate/up order and go to their public places
+    float* C = reinterpret_cast<float*>(Cv);
+#pragma unroll
+    for (int i = 0; i < WTM; i++) {
+      const int64_t row = crow0 + i * 16 + l16;
+      if (row >= M) continue;
+#pragma unroll
+      for (int j = 0; j < WTN; j++) {
+        const int col = int(ccol0) + j * 16 + g4 * 4;
+        if (col >= N) continue;
+        float4* p = reinterpret_cast<float4*>(C + row * ldc + (xf > 0 ? gu_public_col(col0 + col, xf) : col0 + col));
+        float4 t = make_float4(0.f, 0.f, 0.f, 0.f);
+        if (ldx == 0) t = *p;  // ldx != 0 in this mode: store, do not accumulate
+        t.x += c[i][j][0]; t.y += c[i][j][1]; t.z += c[i][j][2]; t.w += c[i][j][3];
+        *p = t;
+      }
+    }
+  } else {
+    // bf16 output through a per-wavefront staging area (16 rows x 16 WTN columns, 16-byte chunks XOR-swizzled by row) so
+    // that the stores move whole rows.  The fused forms work on the fp32 accumulators first:
+    //   E_ROPE    a head lies inside the wavefront's columns: both values of a rotary pair (i, i + head_dim/2) sit in
+    //             the same lane, head_dim/32 MFMA tiles apart: rotate, then round once;
+    //   E_SWIGLU  columns come as 32 gates, their 32 ups, ...: the up of a gate sits two MFMA tiles to the right in
+    //             the same lane; C gets both, X[row][f] their product silu(gate) * up formed in fp32.
+    constexpr int CH = 2 * WTN, RPI = 64 / CH;  // chunks per row, rows per store instruction
+    unsigned char* ws = smem + wave * (16 * CH * 16 * 2);
+    unsigned char* wz = ws + 16 * CH * 16;
+    bf16_t* C = reinterpret_cast<bf16_t*>(Cv);
+    // columns of this wavefront that are rotated: whole heads (v, behind them, is not)
+    const int rot = EPI == E_ROPE ? rope.rot_cols - (col0 + int(ccol0)) : 0;
+#pragma unroll
+    for (int i = 0; i < WTM; i++) {
+      const int64_t row = crow0 + i * 16 + l16;
+      float v[WTN][4];
+#pragma unroll
+      for (int j = 0; j < WTN; j++)
+#pragma unroll
+        for (int e = 0; e < 4; e++) v[j][e] = c[i][j][e];
+      if constexpr (EPI == E_BF16) {
+        if (R) {
+#pragma unroll
+          for (int j = 0; j < WTN; j++) {
+            const int col = int(ccol0) + j * 16 + g4 * 4;
+            if (row < M && col < N) {
+              float r4[4];
+              load4(R + row * ldr + col0 + col, r4);
+              v[j][0] += r4[0]; v[j][1] += r4[1]; v[j][2] += r4[2]; v[j][3] += r4[3];
+            }
+          }
+        }
+      }
+      if constexpr (EPI == E_ROPE) {
+        // TP = MFMA tiles between the halves of a pair
+        auto rotate = [&](auto TPC) {
+          constexpr int TP = decltype(TPC)::value;
+          const int64_t pos = row < M ? row % rope.seq : 0;
+          const float* ct = rope.cos_tab + pos * (16 * TP) + g4 * 4;
+          const float* sn = rope.sin_tab + pos * (16 * TP) + g4 * 4;
+#pragma unroll
+          for (int p = 0; p < TP; p++) {
+            const float4 c4 = *reinterpret_cast<const float4*>(ct + 16 * p), s4 = *reinterpret_cast<const float4*>(sn + 16 * p);
+            const float cc[4] = {c4.x, c4.y, c4.z, c4.w}, ss[4] = {s4.x, s4.y, s4.z, s4.w};
+#pragma unroll
+            for (int j = p; j + TP < WTN; j += 2 * TP)
+#pragma unroll
+              for (int e = 0; e < 4 && 16 * j < rot; e++) {
+                const float u1 = v[j][e], u2 = v[j + TP][e];
+                v[j][e] = u1 * cc[e] - u2 * ss[e];
+                v[j + TP][e] = u1 * ss[e] + u2 * cc[e];
+              }
+          }
+        };
+        if (rot > 0) {
+          if (rope.head_dim == 128) rotate(std::integral_constant<int, 4>{}); else rotate(std::integral_constant<int, 2>{});
+        }
+      }
+#pragma unroll
+      for (int j = 0; j < WTN; j++) {
+        uint2 o;
+        o.x = pack_bf16x2(v[j][0], v[j][1]);
+        o.y = pack_bf16x2(v[j][2], v[j][3]);
+        const int ch = j * 2 + (g4 >> 1);
+        *reinterpret_cast<uint2*>(ws + l16 * (CH * 16) + ((ch ^ (l16 & (CH - 1))) << 4) + (g4 & 1) * 8) = o;
+      }
+      if constexpr (EPI == E_SWIGLU) {
+        // gate tiles 4n, 4n+1 with their ups 4n+2, 4n+3 -> product tiles 2n, 2n+1
+#pragma unroll
+        for (int zb = 0; zb < WTN / 2; zb++) {
+          const int jg = (zb >> 1) * 4 + (zb & 1), ju = jg + 2;
+          float z[4];
+#pragma unroll
+          for (int e = 0; e < 4; e++) z[e] = v[jg][e] * sigmoidf_(v[jg][e]) * v[ju][e];
+          uint2 o;
+          o.x = pack_bf16x2(z[0], z[1]);
+          o.y = pack_bf16x2(z[2], z[3]);
+          const int ch = zb * 2 + (g4 >> 1);
+          *reinterpret_cast<uint2*>(wz + l16 * (CH * 8) + ((ch ^ (l16 & (CH / 2 - 1))) << 4) + (g4 & 1) * 8) = o;
+        }
+      }
+      wave_lds_sync();
+#pragma unroll
+      for (int q = 0; q < 16 / RPI; q++) {
+        const int rr = q * RPI + lane / CH, chk = lane % CH;
+        const uint4 o = *reinterpret_cast<const uint4*>(ws + rr * (CH * 16) + ((chk ^ (rr & (CH - 1))) << 4));
+        const int64_t grow = crow0 + i * 16 + rr;
+        const int gcol = int(ccol0) + chk * 8;
+        if (grow < M && gcol < N) *reinterpret_cast<uint4*>(C + grow * ldc + col0 + gcol) = o;
+      }
+      if constexpr (EPI == E_SWIGLU) {
+        bf16_t* X = reinterpret_cast<bf16_t*>(Xv);
+        constexpr int ZCH = CH / 2, ZRPI = 64 / ZCH;
+#pragma unroll
+        for (int q = 0; q < (16 + ZRPI - 1) / ZRPI; q++) {
+          const int rr = q * ZRPI + lane / ZCH, chk = lane % ZCH;
+          if (rr < 16) {
+            const uint4 o = *reinterpret_cast<const uint4*>(wz + rr * (CH * 8) + ((chk ^ (rr & (ZCH - 1))) << 4));
+            const int64_t grow = crow0 + i * 16 + rr;
+            const int gcol = int(ccol0) + (chk >> 2) * 64 + (chk & 3) * 8;  // the gate column of this chunk's first product
+            const int zcol = ((col0 + int(ccol0)) >> 1) + chk * 8;       // its place among the f products
+            if (grow < M && gcol < N) *reinterpret_cast<uint4*>(X + grow * ldx + zcol) = o;
+          }
+        }
+      }
+      wave_lds_sync();
+    }
+  }
+}
+
+// everything a launch needs (the epilogues take what they need of it)
+struct Args {
+  const bf16_t *A, *B;
+  void* C;
+  const bf16_t* R;
+  int M, N, K;
+  int64_t lda, ldb, ldc, ldr;
+  uint32_t ab, bb;
+  hipStream_t st;
+  int col0;
+  void* X;
+  int64_t ldx;
+  int xf;
+  SegArgs segs;
+  RopeArgs rope;
+};
+
+template <int WTM, int WTN, int WGM, bool ATR, bool BTR, int EPI, bool SEG, int NS>
+hipError_t launch_t16(const Args& a) {
+  using G = Cfg<WTM, WTN, WGM, ATR, BTR, EPI, SEG, NS>;
+  auto kern = gemm_t16_kernel<WTM, WTN, WGM, ATR, BTR, EPI, SEG, NS>;
+  static std::atomic<uint64_t> lds_raised{0};
+  if (hipError_t e = mls::raise_lds_limit(reinterpret_cast<const void*>(kern), G::LDS, lds_raised)) return e;
+  const int tm = (a.M + G::BM - 1) / G::BM, tn = (a.N + G::BN - 1) / G::BN;
+  hipLaunchKernelGGL(kern, dim3(unsigned(tm) * tn), dim3(256), G::LDS, a.st, a.A, a.B, a.C, a.R, a.M, a.N, a.K, a.lda, a.ldb, a.ldc,
+                     a.ldr, a.ab, a.bb, tm, a.col0, a.X, a.ldx, a.xf, a.segs, a.rope);
+  return hipGetLastError();
+}
+
+// the tile sizes of one form; the fused epilogues need 64 (gate/up) or 128 (head) columns per wavefront
+template <bool ATR, bool BTR, int EPI, bool SEG>
+hipError_t run(int tile, const Args& a) {
+  if constexpr (EPI == E_ROPE) {
+    if (tile == mls::T16_256x128) return launch_t16<4, 8, 4, ATR, BTR, EPI, SEG, 3>(a);
+    if (tile == mls::T16_128x128) return launch_t16<2, 8, 4, ATR, BTR, EPI, SEG, 4>(a);
+    return launch_t16<1, 8, 4, ATR, BTR, EPI, SEG, 3>(a);
+  } else {
+    if (tile == mls::T16_256x128) return launch_t16<8, 4, 2, ATR, BTR, EPI, SEG, 3>(a);
+    if (tile == mls::T16_128x128) return launch_t16<4, 4, 2, ATR, BTR, EPI, SEG, 4>(a);
+    if constexpr (EPI == E_SWIGLU) {
+      return launch_t16<2, 4, 2, ATR, BTR, EPI, SEG, 3>(a);
+    } else {
+      if (tile == mls::T16_128x64) return launch_t16<4, 2, 2, ATR, BTR, EPI, SEG, 3>(a);
+      return launch_t16<2, 2, 2, ATR, BTR, EPI, SEG, 3>(a);
+    }
+  }
+}
+
+}  // namespace
+
+namespace mls {
+
+hipError_t gemm_t16(const T16Problem& p, int tile, hipStream_t st) {
+  if (p.M <= 0 || p.N <= 0 || p.K <= 0 || p.nseg < 0 || p.nseg > MAX_SEGS) return hipErrorInvalidValue;
+  Args a = {};
+  a.A = (const bf16_t*)p.A; a.B = (const bf16_t*)p.B; a.C = p.C; a.R = (const bf16_t*)p.R;
+  a.M = p.M; a.N = p.N; a.K = p.K;
+  a.lda = p.lda; a.ldb = p.ldb; a.ldc = p.ldc; a.ldr = p.ldr;
+  a.ab = p.ab; a.bb = p.bb;
+  a.st = st;
+  a.col0 = p.col0;
+  a.X = p.X; a.ldx = p.ldx; a.xf = p.xf;
+  a.rope = {p.cos_tab, p.sin_tab, p.seq, p.rot_cols, p.head_dim};
+  a.segs.nseg = p.nseg;
+  for (int i = 0; i < p.nseg; i++) {
+    a.segs.a[i] = (const bf16_t*)p.seg_a[i];
+    a.segs.b[i] = (const bf16_t*)p.seg_b[i];
+  }
+  switch (p.form) {
+    case T16_NN: return run<false, true, E_BF16, false>(tile, a);
+    case T16_NT: return run<false, false, E_BF16, false>(tile, a);
+    case T16_TN: return run<true, true, E_F32, false>(tile, a);
+    case T16_TN_SEGS: return run<true, true, E_F32, true>(tile, a);
+    case T16_NT_SWIGLU: return run<false, false, E_SWIGLU, false>(tile, a);
+    case T16_NT_ROPE: return run<false, false, E_ROPE, false>(tile, a);
+  }
+  return hipErrorInvalidValue;
+}
+
+}  // namespace mls

@@ -50,29 +50,51 @@ bool gemm_m16_ok(int mode, int K);
 hipError_t gemm_m16(int mode, const void* A, const void* B, void* C, const void* R, int M, int N, int K, int64_t lda,
                     int64_t ldb, int64_t ldc, int64_t ldr, uint32_t ab, uint32_t bb, hipStream_t st);
 hipError_t gemm_m16_swiglu(const void* A, const void* W, void* GU, void* Z, int M, int N, int K, int64_t lda, int64_t ldw,
-                           int64_t ldgu, int64_t ldz, uint32_t ab, uint32_t bb, hipStream_t st, bool w_nk);
+                           int64_t ldgu, int64_t ldz, uint32_t ab, uint32_t bb, hipStream_t st);
 hipError_t gemm_m16_rope(const void* A, const void* W, void* C, int M, int N, int K, int64_t lda, int64_t ldw, int64_t ldc,
                          uint32_t ab, uint32_t bb, const float* cos_tab, const float* sin_tab, int seq, int rot_cols,
-                         int head_dim, hipStream_t st, bool w_nk);
+                         int head_dim, hipStream_t st);
 hipError_t gemm_m16_tn_segments(const void* const* A, const void* const* B, int nseg, void* C, int M, int N, int kseg,
                                 int64_t lda, int64_t ldb, int64_t ldc, uint32_t ab, uint32_t bb, hipStream_t st, int gu_f,
                                 bool overwrite);
+// everything else on smaller tiles of the same instruction (gemm_bf16_t16.hip): any K (a multiple of 8 where an operand is
+// stored [row][k]).  The columns of B (for NN / TN from pointer B on, for NT from row 0 of B on) are columns col0 .. of C
+// (and R, X), which are not offset.
+enum { T16_256x128 = 0, T16_128x128 = 1, T16_128x64 = 2, T16_64x64 = 3 };  // (the last two: 64x128 for the fused epilogues)
+enum { T16_NN, T16_NT, T16_TN, T16_TN_SEGS, T16_NT_SWIGLU, T16_NT_ROPE };
+struct T16Problem {
+  int form;
+  const void *A, *B;
+  void* C;
+  const void* R;
+  int M, N, K;  // T16_TN_SEGS: K = depth of one piece
+  int64_t lda, ldb, ldc, ldr;
+  uint32_t ab, bb;  // byte lengths of A and B (of one piece)
+  int col0;
+  void* X;      // SwiGLU: the product; TN forms: ldx != 0 stores instead of adding
+  int64_t ldx;
+  int xf;       // TN_SEGS: the gate/up width if the columns are in the interleaved order
+  int nseg;
+  const void *seg_a[16], *seg_b[16];
+  const float *cos_tab, *sin_tab;
+  int seq, rot_cols, head_dim;
+};
+hipError_t gemm_t16(const T16Problem& p, int tile, hipStream_t st);
 hipError_t fill_zero_f32(float* p, size_t n, hipStream_t st);
 // SwiGLU fused into the gate/up contraction (bf16, f % 32 == 0, DMA path).  Interleaved gate/up column order:
 // 32 gate columns, the 32 up columns of the same indices, and so on (gu_interleaved_col in common.h).
 //   GU[M, 2f] = A[M,K] W[K, 2f] (W and GU interleaved), Z[M, f] = silu(gate) * up
-// w_nk: W is given transposed, [2f][K] (rows in the interleaved order) with row stride ldw.
-bool gemm_swiglu_ok(int M, int f, int K, int64_t lda, int64_t ldw, bool w_nk = false);
+// W is given transposed, [2f][K] (rows in the interleaved order) with row stride ldw.
+bool gemm_swiglu_ok(int M, int f, int K, int64_t lda, int64_t ldw);
 hipError_t gemm_bf16_swiglu(const void* A, const void* W, void* GU, void* Z, int M, int f, int K, int64_t lda,
-                            int64_t ldw, int64_t ldgu, int64_t ldz, hipStream_t st, bool w_nk = false);
+                            int64_t ldw, int64_t ldgu, int64_t ldz, hipStream_t st);
 // The rotary embedding fused into the q|k|v projection (bf16, DMA path): C[M, N] = A[M,K] W[K,N] rounded to bf16, then
 // every head vector (head_dim = 64 or 128 columns) in the columns below rot_cols rotated by the angle of its row's
 // position row % seq, pairs (i, i + head_dim/2); cos_tab, sin_tab: [seq][head_dim/2] fp32.
-// w_nk: W is given transposed, [N][K] with row stride ldw.
-bool gemm_rope_ok(int M, int N, int K, int64_t lda, int64_t ldw, int seq, int rot_cols, int head_dim, bool w_nk = false);
+// W is given transposed, [N][K] with row stride ldw.
+bool gemm_rope_ok(int M, int N, int K, int64_t lda, int64_t ldw, int seq, int rot_cols, int head_dim);
 hipError_t gemm_bf16_rope(const void* A, const void* W, void* C, int M, int N, int K, int64_t lda, int64_t ldw, int64_t ldc,
-                          const float* cos_tab, const float* sin_tab, int seq, int rot_cols, int head_dim, hipStream_t st,
-                          bool w_nk = false);
+                          const float* cos_tab, const float* sin_tab, int seq, int rot_cols, int head_dim, hipStream_t st);
 hipError_t gemm_f32(int mode, const void* A, const void* B, void* C, const void* R, int M, int N, int K, int64_t lda,
                     int64_t ldb, int64_t ldc, int64_t ldr, hipStream_t st);
 

@@ -234,17 +234,14 @@ int layer_forward(mls_stage* s, int layer, const char* x, char* e, void* out, in
   const int64_t lh = s->ld_h, lq = s->ld_qkv, lo = s->ld_qd, lg = s->ld_gu, lf = s->ld_f;
   LAUNCH(CLS_NORM, mls::rmsnorm_fwd(s->dt, x, lh, s->param(layer, s->ioff_g1), e + L.a, lh, (float*)(e + L.r1), T, h,
                                     c.rms_eps, s->st));
-  // with the transposed weight copies every product runs as X (W^T)^T, W^T being the [row][k] operand
+  // with the transposed weight copies (bf16 storage) every product runs as X (W^T)^T, W^T being the [row][k] operand
   const bool wt = s->params_t != nullptr;
   if (s->fuse_rope) {  // the rotation of q and k is the epilogue of their projection
-    if (wt)
-      LAUNCH(CLS_GEMM_NN, mls::gemm_bf16_rope(e + L.a, s->param_t(layer, s->toff_wqkv), e + L.qkv, T, s->qkvw, h, lh, lh, lq, s->cos_tab,
-                                              s->sin_tab, c.seq, s->qd + s->kvd, c.head_dim, s->st, true));
-    else
-      LAUNCH(CLS_GEMM_NN, mls::gemm_bf16_rope(e + L.a, s->param(layer, s->ioff_wqkv), e + L.qkv, T, s->qkvw, h, lh, lq, lq, s->cos_tab,
-                                              s->sin_tab, c.seq, s->qd + s->kvd, c.head_dim, s->st));
+    LAUNCH(CLS_GEMM_NN, mls::gemm_bf16_rope(e + L.a, s->param_t(layer, s->toff_wqkv), e + L.qkv, T, s->qkvw, h, lh, lh, lq, s->cos_tab,
+                                            s->sin_tab, c.seq, s->qd + s->kvd, c.head_dim, s->st));
   } else {
-    LAUNCH(CLS_GEMM_NN, gemm(s, mls::GEMM_NN, e + L.a, s->param(layer, s->ioff_wqkv), e + L.qkv, nullptr, T, s->qkvw, h, lh, lq, lq));
+    if (wt) LAUNCH(CLS_GEMM_NN, gemm(s, mls::GEMM_NT, e + L.a, s->param_t(layer, s->toff_wqkv), e + L.qkv, nullptr, T, s->qkvw, h, lh, lh, lq));
+    else LAUNCH(CLS_GEMM_NN, gemm(s, mls::GEMM_NN, e + L.a, s->param(layer, s->ioff_wqkv), e + L.qkv, nullptr, T, s->qkvw, h, lh, lq, lq));
     LAUNCH(CLS_ROPE, mls::rope_inplace(s->dt, e + L.qkv, s->cos_tab, s->sin_tab, T, c.seq, c.n_q_heads + c.n_kv_heads,
                                        c.head_dim, lq, 1.f, s->st));
   }
@@ -255,10 +252,10 @@ int layer_forward(mls_stage* s, int layer, const char* x, char* e, void* out, in
   LAUNCH(CLS_NORM, mls::rmsnorm_fwd(s->dt, e + L.h, lh, s->param(layer, s->ioff_g2), e + L.b, lh, (float*)(e + L.r2), T, h,
                                     c.rms_eps, s->st));
   if (s->fuse_gu) {
-    if (wt) LAUNCH(CLS_GEMM_NN, mls::gemm_bf16_swiglu(e + L.b, s->param_t(layer, s->toff_wgu), e + L.gu, e + L.z, T, f, h, lh, lh, lg, lf, s->st, true));
-    else LAUNCH(CLS_GEMM_NN, mls::gemm_bf16_swiglu(e + L.b, s->param(layer, s->ioff_wgu), e + L.gu, e + L.z, T, f, h, lh, lg, lg, lf, s->st));
+    LAUNCH(CLS_GEMM_NN, mls::gemm_bf16_swiglu(e + L.b, s->param_t(layer, s->toff_wgu), e + L.gu, e + L.z, T, f, h, lh, lh, lg, lf, s->st));
   } else {
-    LAUNCH(CLS_GEMM_NN, gemm(s, mls::GEMM_NN, e + L.b, s->param(layer, s->ioff_wgu), e + L.gu, nullptr, T, 2 * f, h, lh, lg, lg));
+    if (wt) LAUNCH(CLS_GEMM_NN, gemm(s, mls::GEMM_NT, e + L.b, s->param_t(layer, s->toff_wgu), e + L.gu, nullptr, T, 2 * f, h, lh, lh, lg));
+    else LAUNCH(CLS_GEMM_NN, gemm(s, mls::GEMM_NN, e + L.b, s->param(layer, s->ioff_wgu), e + L.gu, nullptr, T, 2 * f, h, lh, lg, lg));
     LAUNCH(CLS_SWIGLU, mls::swiglu_fwd(s->dt, e + L.gu, lg, e + L.z, lf, T, f, s->st));
   }
   // `out` is either the next layer's x (row stride ld_h) or the caller's dense y
@@ -355,10 +352,10 @@ void layout(mls_stage* s) {
   s->toff_wgu = s->toff_wo + h * s->ld_qd;
   s->toff_wd = s->toff_wgu + 2 * f * s->ld_h;
   s->tlayer_params = s->toff_wd + h * s->ld_f;
-  s->fuse_gu = s->dt == mls::DT_BF16 && mls::gemm_swiglu_ok(s->T, c.ffn, c.hidden, s->ld_h, s->ld_gu) &&
+  s->fuse_gu = s->dt == mls::DT_BF16 && mls::gemm_swiglu_ok(s->T, c.ffn, c.hidden, s->ld_h, s->ld_h) &&
                mls::gemm_tn_segments_ok(s->T, s->ld_h, s->ld_gu);
 
-  s->fuse_rope = s->dt == mls::DT_BF16 && mls::gemm_rope_ok(s->T, s->qkvw, c.hidden, s->ld_h, s->ld_qkv, c.seq,
+  s->fuse_rope = s->dt == mls::DT_BF16 && mls::gemm_rope_ok(s->T, s->qkvw, c.hidden, s->ld_h, s->ld_h, c.seq,
                                                             s->qd + s->kvd, c.head_dim);
 
   LayerStash& L = s->ls;

@@ -138,3 +138,37 @@ def test_empty_contraction():
     assert L.mls_gemm(mls.MLS_BF16, 2, p(buf), M, p(buf), N, p(acc), N, None, M, N, 0, st) == 0
     torch.cuda.synchronize()
     assert float(c.float().abs().max()) == 0.0 and float((acc - 0.5).abs().max()) == 0.0
+
+
+# by the plan of gemm_bf16_dispatch.hip: 64x64 tiles; 128x64; 128x128; 256x128; 256x256 tiles with a 64x64 and a 128x64 tail.
+# K: one k-tile that is not full, a last k-tile of one 16-byte chunk, more k-tiles than stages
+@pytest.mark.parametrize("M,N,K", [(72, 136, 24), (72, 136, 1032), (1000, 2056, 1096), (2040, 2040, 392), (2000, 3000, 1032),
+                                   (2048, 4096, 328), (4096, 4360, 136), (4088, 5128, 200)])
+def test_bf16_every_tile_size(M, N, K):
+    test_bf16_three_modes(M, N, K)
+
+
+@pytest.mark.parametrize("M,N,K", [(72, 136, 77), (1000, 2056, 1091), (2040, 2040, 390), (2000, 3000, 1025)])
+def test_bf16_weight_gradient_over_any_token_count(M, N, K):
+    """C += A^T B over K tokens, K no multiple of 8 (the C ABI's mls_gemm refuses such a K; a stage's weight gradients
+    have it): through a one-layer stage's w_d, whose operands are captured."""
+    import synth
+    import torch
+    import paper_2410_13333_amd as mls
+    sh = synth.StageShape(hidden=N // 8 * 8, n_q_heads=1, n_kv_heads=1, head_dim=64, ffn=M // 8 * 8, seq=K, micro_batch=1,
+                          layers=1, microbatches=2)
+    st = mls.Stage.from_shape(sh, seed=1)
+    x = torch.randn(2, 1, K, sh.hidden, device="cuda").to(torch.bfloat16)
+    dy, dx, y = torch.randn_like(x), torch.empty_like(x), torch.empty_like(x[0])
+    g = torch.full((st.grad_elems,), 0.5, device="cuda")
+    ref = 0.5
+    for i in range(2):
+        st.forward(x[i], 1, y)
+    z = [to_host64(st.debug_read("z", 0, i)) for i in range(2)]
+    st.backward(dy, g, 2, dx)
+    for i in range(2):  # two pieces in one contraction
+        ref = ref + z[i].T @ to_host64(dy[i].reshape(K, -1))
+    off, r, c = st.param_layout(0, "w_d")
+    got = to_host64(g[off:off + r * c]).reshape(r, c)
+    st.close()
+    assert rel_err(got, ref) < 1e-5

@@ -361,3 +361,18 @@ def test_set_params_from_any_address(ffn, shift):
         out.append((y, dx, g))
         st.close()
     assert all(torch.equal(u, v) for u, v in zip(*out))
+
+
+@pytest.mark.parametrize("nq,nkv,seq", [(56, 7, 4096), (2, 1, 72)])
+def test_rotary_epilogue_with_an_odd_number_of_rotated_64_column_heads(nq, nkv, seq):
+    """The last rotated head and the first head of v share a wavefront's 128 columns, on 256x256 tiles and on small ones."""
+    test_rotary_epilogue_of_the_qkv_projection(nq, nkv, 64, seq, 1)
+
+
+@pytest.mark.parametrize("nq,nkv,d,ffn,seq,mb", [(16, 16, 128, 544, 2048, 1), (33, 1, 64, 992, 700, 3), (12, 12, 128, 2048, 1500, 1)])
+def test_fused_epilogues_on_mid_size_tiles(nq, nkv, d, ffn, seq, mb):
+    """Rotary and SwiGLU epilogues on 256x128, 128x128 and 64x128 tiles with ragged rows: a whole layer against the exact
+    oracle."""
+    sh = synth.StageShape(hidden=264, n_q_heads=nq, n_kv_heads=nkv, head_dim=d, ffn=ffn, seq=seq, micro_batch=mb, layers=1,
+                          microbatches=1)
+    _check(sh, [1], 1e-2)
