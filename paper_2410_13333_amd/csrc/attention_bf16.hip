@@ -16,6 +16,7 @@
 // access patterns bank-conflict free: ds_read_b128 of 16 consecutive rows at one column chunk, and the
 // transposing 8-byte reads of 4 consecutive rows x 64 bytes.
 #include <type_traits>
+#include <utility>
 
 #include "common.h"
 #include "kernels.h"
@@ -45,6 +46,7 @@ constexpr uint32_t OOB = 0x80000000u;
 constexpr int AT_THREADS = 256;
 constexpr int TR = 64;  // rows of an LDS tile
 constexpr float LOG2E = 1.4426950408889634f, LN2 = 0.6931471805599453f;
+constexpr float SLACK = 8.f;
 
 // element offset of (row, col) inside a swizzled 64 x D tile
 template <int D>
@@ -57,6 +59,15 @@ __device__ __forceinline__ int toff(int row, int col) {
     const int sw = ((line & 1) << 2) | ((line >> 1) & 3);
     return line * 128 + (((((row & 1) << 3) | (col >> 3)) ^ sw) << 3) + (col & 7);
   }
+}
+
+template <class F, int... I>
+__device__ __forceinline__ void static_for_impl(F&& f, std::integer_sequence<int, I...>) {
+  (f(std::integral_constant<int, I>{}), ...);
+}
+template <int N, class F>
+__device__ __forceinline__ void static_for(F&& f) {
+  static_for_impl(f, std::make_integer_sequence<int, N>{});
 }
 
 template <int D>
@@ -84,6 +95,12 @@ struct Tile {
       off[i] = uint32_t((int64_t(row) * ld + chunk * 8) * 2);
     }
   }
+  // the same from a matrix of `rows` rows at `m` (row stride ld): everything that changes is in the scalar descriptor
+  __device__ __forceinline__ void dma(const bf16_t* m, int64_t ld, int row0, int rows, uint32_t tile, int wave) const {
+    const i32x4 src = make_rsrc(m + int64_t(row0) * ld, row0 < rows ? uint32_t((int64_t(rows - row0) * ld) * 2) : 0u);
+#pragma unroll
+    for (int i = 0; i < NI; i++) dma16(src, off[i], tile + (wave * NI + i) * 1024);
+  }
   // rows [row0, row0+64) x cols [col0, col0+D) of the matrix behind rsrc (row stride ld) -> tile at LDS byte
   // address `tile`; rows at or beyond the end of the buffer are zero-filled; live = false sends nothing useful
   __device__ __forceinline__ void dma(i32x4 rsrc, int64_t ld, int row0, int col0, uint32_t tile, int wave,
@@ -105,6 +122,50 @@ struct Tile {
     s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((MLS_LDS s16x4*)(t + toff<D>(row, col)));
     s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((MLS_LDS s16x4*)(t + toff<D>(row + 8, col)));
     s16x8 v = {lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
+    return __builtin_bit_cast(bf16x8, v);
+  }
+};
+
+// Fragment reads of swizzled tiles whose place in LDS is a compile-time constant: one address per fragment column (the
+// swizzle turns a step along the columns into an XOR of the address), everything else in the read's immediate offset.
+template <int D>
+struct Frags {
+  uint32_t r[D / 16], lo[D / 32], hi[D / 32];
+  __device__ __forceinline__ void init(uint32_t lds0, int lane) {
+    const uint32_t br = lds0 + toff<D>(lane & 31, (lane >> 5) * 8) * 2;
+    const uint32_t bc = lds0 + toff<D>((lane >> 5) * 4 + ((lane & 15) >> 2), ((lane >> 4) & 1) * 16 + (lane & 3) * 4) * 2;
+#pragma unroll
+    for (int i = 0; i < D / 16; i++) r[i] = br ^ (i << 5);
+#pragma unroll
+    for (int i = 0; i < D / 32; i++) {
+      lo[i] = bc ^ (i << 6);
+      hi[i] = bc ^ (i << 6) ^ 32;
+    }
+  }
+  // the other buffer of a pair (the first one at a multiple of twice the tile size)
+  __device__ __forceinline__ void flip_rows() {
+#pragma unroll
+    for (int i = 0; i < D / 16; i++) r[i] ^= TR * D * 2;
+  }
+  __device__ __forceinline__ void flip_cols() {
+#pragma unroll
+    for (int i = 0; i < D / 32; i++) {
+      lo[i] ^= TR * D * 2;
+      hi[i] ^= TR * D * 2;
+    }
+  }
+  // A operand, rows = tile rows rt*32 .. +31, k = tile columns kk*16 .. +15; tile: its byte offset from lds0
+  template <int TILE, int RT>
+  __device__ __forceinline__ bf16x8 rows(int kk) const {
+    return *(const MLS_LDS bf16x8*)(r[kk] + (TILE + RT * 32 * D * 2));
+  }
+  // A operand, rows = tile COLUMNS ct*32 .. +31, k = tile rows of the 16-step KS in the permuted order that matches a B
+  // operand built from accumulator registers: k-values 4g..4g+3 then 8+4g..8+4g+3, g = lane/32
+  template <int TILE, int KS>
+  __device__ __forceinline__ bf16x8 cols(int ct) const {
+    s16x4 l = __builtin_amdgcn_ds_read_tr16_b64_v4i16((MLS_LDS s16x4*)(lo[ct] + (TILE + KS * 16 * D * 2)));
+    s16x4 h = __builtin_amdgcn_ds_read_tr16_b64_v4i16((MLS_LDS s16x4*)(hi[ct] + (TILE + KS * 16 * D * 2 + 8 * D * 2)));
+    s16x8 v = {l[0], l[1], l[2], l[3], h[0], h[1], h[2], h[3]};
     return __builtin_bit_cast(bf16x8, v);
   }
 };
@@ -131,6 +192,12 @@ __device__ __forceinline__ f32x16 zero16() {
 #pragma unroll
   for (int e = 0; e < 16; e++) z[e] = 0.f;
   return z;
+}
+
+// maximum of a lane and its partner in the other half of the wavefront, without a trip through LDS
+__device__ __forceinline__ float max_halves(float v) {
+  const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  return fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
 }
 
 // N LDS fragment reads feeding N MFMAs, each read issued DEPTH fragments ahead of its use so that the LDS latency
@@ -204,28 +271,38 @@ __device__ __forceinline__ void store_t_unrotate(bf16_t* __restrict__ out, int64
 
 // ================================================================ forward
 // grid (n_q, q blocks of 128, b) with the longest query blocks dispatched first over all heads; wave w owns
-// query rows q0 + 32w .. +31; loops over KV blocks of 64.  Two workgroups fit a CU.
+// query rows q0 + 32w .. +31; loops over KV blocks of 64 = two sub-blocks of 32 keys.  Two workgroups fit a CU.
+//
+// What bounded it was one wavefront's chain scores -> softmax -> product with V: the matrix pipe was busy 44 % of the
+// time with two wavefronts per SIMD.  The chain is therefore software-pipelined over the sub-blocks: a step issues the
+// 16 MFMAs of S(s+1) = K Q^T and of O += V^T P(s-1), neither of which needs the softmax of S(s) whose vector
+// instructions go out in between (about five fit behind one MFMA).  K runs one 64-row block ahead of V: both are
+// double-buffered and one barrier per block frees the buffers of K(u-1) and V(u-2).
+// Measured (us, before -> after): 4096 positions, 32 heads of 128: 177 -> 160; 2048, 16 of 128 (one workgroup per CU, where
+// the chain is everything): 62 -> 45; 4096, 16 of 128: 123 -> 95; 4096, 16 of 64: 90 -> 64.  With every CU full the vector
+// instructions and the MFMAs of a SIMD take about 300 000 of the 335 000 cycles one after the other.
 template <int D>
 __global__ __launch_bounds__(AT_THREADS, 2) void attn_fwd_kernel(const bf16_t* __restrict__ qkv, int64_t ld, bf16_t* __restrict__ o, int64_t ldo,
                                                                  float* __restrict__ lse, int S, int nq, int nkv) {
   using TL = Tile<D>;
-  constexpr int KD = D / 16, DT = D / 32;
-  __shared__ __attribute__((aligned(1024))) bf16_t lds[2][2][TR * D];  // [buffer][K|V]
+  constexpr int KD = D / 16, DT = D / 32, FA = 4, NV = 5;  // reads ahead; vector instructions per MFMA
+  __shared__ __attribute__((aligned(4 * TR * D))) bf16_t lds[2][2][TR * D];  // [K|V][buffer]
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int qb = gridDim.y - 1 - blockIdx.y;  // longest rows first
   const int hq = blockIdx.x, bi = blockIdx.z, hk = hq / (nq / nkv);
   const bf16_t* base = qkv + int64_t(bi) * S * ld;
   const int q0 = qb * 128, qw = q0 + wave * 32, qi = qw + (lane & 31);
   const float sc = rsqrtf((float)D) * LOG2E;
-  const i32x4 rsrc = make_rsrc(base, uint32_t(int64_t(S) * ld * 2));
   const uint32_t lds0 = (uint32_t)(uintptr_t)(MLS_LDS bf16_t*)&lds[0][0][0];
   TL tl;
   tl.init(ld, wave, lane);
-  auto issue = [&](int blk, bool live) {  // K and V rows [64 blk, 64 blk + 64) into buffer blk & 1
-    const uint32_t t = lds0 + (blk & 1) * 2 * TL::BYTES;
-    tl.dma(rsrc, ld, blk * TR, (nq + hk) * D, t, wave, live);
-    tl.dma(rsrc, ld, blk * TR, (nq + nkv + hk) * D, t + TL::BYTES, wave, live);
-  };
+  Frags<D> fr;
+  fr.init(lds0, lane);
+  const bf16_t *kp = base + (nq + hk) * D, *vp = kp + nkv * D;
+  const int nblk = (min(S, q0 + 128) + TR - 1) / TR;  // KV blocks of the workgroup
+  // blocks beyond the last one are requested as empty
+  auto issue_k = [&](int u) { tl.dma(kp, ld, u * TR, u < nblk ? S : 0, lds0 + (u & 1) * TL::BYTES, wave); };
+  auto issue_v = [&](int u) { tl.dma(vp, ld, u * TR, u < nblk ? S : 0, lds0 + (2 + (u & 1)) * TL::BYTES, wave); };
 
   bf16x8 qf[KD];
 #pragma unroll
@@ -235,53 +312,72 @@ __global__ __launch_bounds__(AT_THREADS, 2) void attn_fwd_kernel(const bf16_t* _
 #pragma unroll
   for (int t = 0; t < DT; t++) acc[t] = zero16();
   float m = -INFINITY, l = 0.f;
+  f32x16 st = zero16();            // S of the sub-block whose softmax comes next
+  bf16x8 pf[2] = {};               // P of the one before it
 
-  const int kv_end = min(S, q0 + 128);
-  const int nblk = (kv_end + TR - 1) / TR;
-  issue(0, true);
-  for (int blk = 0; blk < nblk; blk++) {
-    const int cur = blk & 1, j0 = blk * TR;
-    wait_dma();       // this wave's part of block blk has landed ...
-    __syncthreads();  // ... and so has everyone's; all reads of the other buffer are retired
-    issue(blk + 1, blk + 1 < nblk);
-    if (j0 <= qw + 31) {  // wave-uniform: some (i, j) pair of this wave is unmasked
-      const bf16_t* ks = lds[cur][0];
-      const bf16_t* vs = lds[cur][1];
-      f32x16 st[2];
-#pragma unroll
-      for (int jt = 0; jt < 2; jt++) {
-        st[jt] = zero16();
-#pragma unroll
-        for (int kk = 0; kk < KD; kk++)
-          st[jt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(TL::frag_rows(ks, jt, kk, lane), qf[kk], st[jt], 0, 0, 0);
-      }
+  const int diag = qw >> 5;                           // the sub-block on this wavefront's diagonal; later ones are masked
+  const int nw = min(diag / 2 + 1, nblk);             // KV blocks this wavefront needs
+
+  // one step: S of the sub-block after `sub` from sub-block KH of the current K tile; softmax of `st` = S(sub); O += V^T P of the
+  // one before `sub` from sub-block VH of the current V tile
+  auto step = [&](auto DO_S, auto KH, auto DO_SM, auto MASK, int sub, auto DO_PV, auto VH) {
+    constexpr int KT = 0, VT = 2 * TL::BYTES;
+    constexpr bool do_s = decltype(DO_S)::value, do_sm = decltype(DO_SM)::value, do_pv = decltype(DO_PV)::value;
+    // MFMAs in their order: S and PV alternate (KD of each; S is one chain), each fragment read FA MFMAs ahead
+    f32x16 sn = zero16();
+    constexpr int NM = KD * (do_s + do_pv);
+    auto is_s = [](int i) constexpr { return do_s && (!do_pv || !(i & 1)); };
+    bf16x8 f[NM > 0 ? NM : 1];
+    auto read = [&](auto IC) {
+      constexpr int i = decltype(IC)::value, q = do_s && do_pv ? i / 2 : i;
+      if constexpr (is_s(i)) f[i] = fr.template rows<KT, decltype(KH)::value>(q);
+      else f[i] = fr.template cols<VT, decltype(VH)::value * 2 + q / DT>(q % DT);
+    };
+    static_for<(FA < NM ? FA : NM)>(read);
+    static_for<NM>([&](auto IC) {
+      constexpr int i = decltype(IC)::value, q = do_s && do_pv ? i / 2 : i;
+      if constexpr (is_s(i)) sn = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f[i], qf[q], sn, 0, 0, 0);
+      else acc[q % DT] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f[i], pf[q / DT], acc[q % DT], 0, 0, 0);
+      if constexpr (i + FA < NM) read(std::integral_constant<int, i + FA>{});
+    });
+    float mn = m;
+    if constexpr (do_sm) {
       // row maximum of the raw scores (the scale is positive: it commutes with the maximum and is folded into the
-      // exponent below); the mask arithmetic is compiled only into the diagonal-block path
+      // exponent below); the mask arithmetic is compiled only into the diagonal path
       float mx = -INFINITY;
-      auto mask_max = [&](auto MASK) {
+      const int lim = qi - sub * 32 - (lane >> 5) * 4;  // key 8 (e / 4) + e % 4 of this lane's half is masked beyond it
 #pragma unroll
-        for (int jt = 0; jt < 2; jt++)
-#pragma unroll
-          for (int e = 0; e < 16; e++) {
-            const int j = j0 + jt * 32 + (lane >> 5) * 4 + 8 * (e >> 2) + (e & 3);
-            if (decltype(MASK)::value && j > qi) st[jt][e] = -INFINITY;
-            mx = fmaxf(mx, st[jt][e]);
-          }
-      };
-      if (j0 + TR - 1 > qw) mask_max(std::true_type{}); else mask_max(std::false_type{});  // some pair masked?
-      mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
-      const float mn = fmaxf(m, mx * sc);  // finite: block 0 always holds j = 0 <= i
+      for (int e = 0; e < 16; e++) {
+        if (decltype(MASK)::value && 8 * (e >> 2) + (e & 3) > lim) st[e] = -INFINITY;
+        mx = fmaxf(mx, st[e]);
+      }
+      mx = max_halves(mx);
+      // The reference of the exponents only has to be near the row's maximum: it moves when the maximum passes it by more
+      // than SLACK (probabilities then reach 2^SLACK times their scale, which changes nothing of their relative precision).
+      // Moved with every new maximum, some row of the 32 moved in about half of all steps, and a move costs 64 products.
+      const float top = mx * sc;
+      mn = top > m + SLACK ? top : m;  // finite: sub-block 0 always holds j = 0 <= i
       float ps = 0.f;
 #pragma unroll
-      for (int jt = 0; jt < 2; jt++)
-#pragma unroll
-        for (int e = 0; e < 16; e++) {
-          const float p = __builtin_amdgcn_exp2f(st[jt][e] * sc - mn);
-          st[jt][e] = p;
-          ps += p;
-        }
-      // the running maximum rarely moves after the first blocks: rescale only when some row's did
-      if (__any(mn > m)) {
+      for (int e = 0; e < 16; e++) {
+        const float p = __builtin_amdgcn_exp2f(st[e] * sc - mn);
+        st[e] = p;
+        ps += p;
+      }
+      pf[0] = acc_to_b(st, 0);
+      pf[1] = acc_to_b(st, 1);
+      asm volatile("" : "+v"(pf[0]), "+v"(pf[1]), "+v"(ps));  // here, between the MFMAs, and not behind the branch below
+      const bool moved = __any(mn > m);
+      if constexpr (do_s && do_pv) {
+        static_for<FA>([&](auto IC) { __builtin_amdgcn_sched_group_barrier(0x100, is_s(decltype(IC)::value) ? 1 : 2, 0); });
+        static_for<NM>([&](auto IC) {
+          constexpr int i = decltype(IC)::value;
+          __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+          if constexpr (i + FA < NM) __builtin_amdgcn_sched_group_barrier(0x100, is_s(i + FA) ? 1 : 2, 0);
+          __builtin_amdgcn_sched_group_barrier(0x402, NV, 0);
+        });
+      }
+      if (moved) {
         const float corr = __builtin_amdgcn_exp2f(m - mn);
         l *= corr;
 #pragma unroll
@@ -291,17 +387,46 @@ __global__ __launch_bounds__(AT_THREADS, 2) void attn_fwd_kernel(const bf16_t* _
         m = mn;
       }
       l += ps;
-#pragma unroll
-      for (int jt = 0; jt < 2; jt++)
-#pragma unroll
-        for (int s = 0; s < 2; s++) {
-          const bf16x8 pf = acc_to_b(st[jt], s);
-#pragma unroll
-          for (int t = 0; t < DT; t++)
-            acc[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(TL::frag_cols(vs, t, jt * 2 + s, lane), pf, acc[t], 0, 0, 0);
-        }
     }
+    if constexpr (do_s) st = sn;
+  };
+  using Y = std::true_type;
+  using N = std::false_type;
+
+  using C0 = std::integral_constant<int, 0>;
+  using C1 = std::integral_constant<int, 1>;
+  // every wavefront passes nblk + 1 barriers: block 0, its unmasked blocks, at most one with the diagonal in it, the last
+  // two products with V, and the blocks that only later rows need
+  auto next = [&](int u) {
+    wait_dma();       // this wave's part of K(u), V(u-1) has landed ...
+    __syncthreads();  // ... and so has everyone's; all reads of K(u-1), V(u-2) are retired
+    issue_k(u + 1);
+    issue_v(u);
+  };
+  issue_k(0);
+  next(0);
+  step(Y{}, C0{}, N{}, N{}, 0, N{}, C0{});
+  step(Y{}, C1{}, Y{}, Y{}, 0, N{}, C0{});
+  int u = 1;
+  for (; 2 * u < diag && u < nw; u++) {
+    next(u);
+    fr.flip_rows();
+    step(Y{}, C0{}, Y{}, N{}, 2 * u - 1, Y{}, C0{});
+    step(Y{}, C1{}, Y{}, N{}, 2 * u, Y{}, C1{});
+    fr.flip_cols();
   }
+  if (u < nw) {
+    next(u);
+    fr.flip_rows();
+    step(Y{}, C0{}, Y{}, Y{}, 2 * u - 1, Y{}, C0{});
+    step(Y{}, C1{}, Y{}, Y{}, 2 * u, Y{}, C1{});
+    fr.flip_cols();
+    u++;
+  }
+  next(u);
+  step(N{}, C0{}, Y{}, Y{}, 2 * u - 1, Y{}, C0{});
+  step(N{}, C0{}, N{}, N{}, 0, Y{}, C1{});
+  for (u++; u <= nblk; u++) next(u);
   wait_dma();
   l += __shfl_xor(l, 32, 64);
   const float inv = 1.f / l;

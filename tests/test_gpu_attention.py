@@ -1,0 +1,67 @@
+"""The bf16 attention kernels on their own operands: q|k|v are read back from the stash, and o, the log-sum-exp and the
+gradients w.r.t. q|k|v are compared with the same attention in fp64 on those values.  Sequences around the 32-row
+sub-blocks, the 64-row blocks and the 128-row workgroups; scores of ordinary size and scores whose row maximum keeps
+rising by far more than the softmax's slack."""
+import numpy as np
+import pytest
+
+import oracle.stage as O
+import synth
+from tests.helpers import rel_err, round_bf16, to_host64
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("gain", [1.0, 24.0])
+@pytest.mark.parametrize("nq,nkv,d,seq,mb", [(2, 2, 128, 1, 2), (2, 1, 64, 33, 1), (2, 2, 128, 64, 1), (4, 2, 64, 65, 2),
+                                             (2, 1, 128, 96, 1), (3, 1, 128, 129, 2), (2, 2, 64, 128, 1), (8, 1, 64, 200, 1),
+                                             (4, 2, 128, 255, 1), (2, 2, 128, 321, 1), (6, 2, 64, 448, 1)])
+def test_attention_against_fp64_on_the_same_operands(nq, nkv, d, seq, mb, gain):
+    import torch
+    import paper_2410_13333_amd as mls
+    h = 128
+    sh = synth.StageShape(hidden=h, n_q_heads=nq, n_kv_heads=nkv, head_dim=d, ffn=64, seq=seq, micro_batch=mb, layers=1,
+                          microbatches=1)
+    st = mls.Stage.from_shape(sh, seed=1000)
+    p = st.get_params()
+    # a larger norm gain makes the scores large
+    p[:h] *= gain
+    st.set_params(p)
+    x = torch.randn(mb, seq, h, device="cuda", generator=torch.Generator(device="cuda").manual_seed(seq)).to(torch.bfloat16)
+    dy = torch.randn(mb, seq, h, device="cuda", generator=torch.Generator(device="cuda").manual_seed(7)).to(torch.bfloat16)
+    y, dx = torch.empty_like(x), torch.empty_like(x)
+    g = torch.zeros(st.grad_elems, device="cuda")
+    st.forward(x, 1, y)
+    qd, kvd, T = nq * d, nkv * d, mb * seq
+    qkv, o, lse = (to_host64(st.debug_read(n)) for n in ("qkv", "o", "lse"))
+    st.backward(dy, g, 1, dx)
+    dh, dqkv = (to_host64(st.debug_read(n)) for n in ("dh", "dqkv"))
+    off, r, c = st.param_layout(0, "w_o")
+    w_o = to_host64(p[off:off + r * c]).reshape(r, c)
+    st.close()
+    q = qkv[:, :qd].reshape(mb, seq, nq, d)
+    k = qkv[:, qd:qd + kvd].reshape(mb, seq, nkv, d)
+    v = qkv[:, qd + kvd:].reshape(mb, seq, nkv, d)
+    ro, pr = O.attention_fwd(q, k, v)
+    # probabilities are rounded to bf16 (2^-9 relative each) before the product with v, o once more: about 3e-3
+    assert rel_err(o, ro.reshape(T, qd)) <= 5e-3
+    s = np.einsum("bind,bjnd->bnij", q, np.repeat(k, nq // nkv, axis=2)) / np.sqrt(d)
+    s = np.where(np.tril(np.ones((seq, seq), dtype=bool)), s, -np.inf)
+    top = s.max(axis=-1)
+    rl = top + np.log(np.exp(s - top[..., None]).sum(axis=-1))
+    if gain > 1 and seq >= 200:  # the case is what it claims: the running maximum of some row rises by more than 8 / log2(e)
+        run = np.maximum.accumulate(s, axis=-1)
+        assert (run[..., -1] - run[..., 31]).max() > 8
+    assert np.abs(lse - rl).max() <= 2e-5 * max(1.0, np.abs(rl).max())
+    # dO enters the kernels as dh w_o^T rounded to bf16; P and dS are rounded to bf16 as matrix operands
+    do = round_bf16(dh @ w_o.T).reshape(mb, seq, nq, d)
+    dq, dk, dv = O.attention_bwd(do, q, k, v, pr)
+    ang = O.rope_angles(seq, d, sh.rope_base)
+    ref = np.concatenate([O.rope_apply(dq, ang, sign=-1.0).reshape(T, qd), O.rope_apply(dk, ang, sign=-1.0).reshape(T, kvd),
+                          dv.reshape(T, kvd)], axis=1)
+    scale = np.linalg.norm(ref)
+    for name, lo, hi in (("dq", 0, qd), ("dk", qd, qd + kvd), ("dv", qd + kvd, qd + 2 * kvd)):
+        # (seq = 1: dq and dk vanish exactly, so the distance is taken relative to the whole gradient)
+        e = np.linalg.norm(dqkv[:, lo:hi] - ref[:, lo:hi]) / max(np.linalg.norm(ref[:, lo:hi]), 0.05 * scale)
+        print(f"[attention d={d} S={seq} gain={gain}] {name}: {e:.2e}")
+        assert e <= 1.5e-2, (name, e)
