@@ -1,5 +1,5 @@
 // Causal grouped-query attention for bf16 storage on the gfx950 matrix cores: forward with online softmax,
-// backward as three kernels (dQ, which also forms the row sums delta = dO . O; dK; dV) that recompute the
+// backward as two kernels (dQ, which also forms the row sums delta = dO . O; dK and dV) that recompute the
 // probabilities from the saved log-sum-exp.
 // Nothing of size S x S is ever written; no float atomics, so results are bitwise reproducible.
 //
@@ -31,6 +31,13 @@ __device__ __forceinline__ void dma16(i32x4 rsrc, uint32_t voff, uint32_t lds_by
   asm volatile("s_mov_b32 m0, %0\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds" ::"s"(lds_byte), "v"(voff), "s"(rsrc)
                : "memory");
 }
+// the same with 4 bytes per lane (256 bytes at lds_byte)
+__device__ __forceinline__ void dma4(i32x4 rsrc, uint32_t voff, uint32_t lds_byte) {
+  asm volatile("s_mov_b32 m0, %0\n\tbuffer_load_dword %1, %2, 0 offen lds" ::"s"(lds_byte), "v"(voff), "s"(rsrc)
+               : "memory");
+}
+template <int N>
+__device__ __forceinline__ void wait_vm() { asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory"); }
 __device__ __forceinline__ void wait_dma() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
 __device__ __forceinline__ i32x4 make_rsrc(const void* p, uint32_t bytes) {
   const uint64_t a = (uint64_t)p;
@@ -70,9 +77,9 @@ __device__ __forceinline__ void static_for(F&& f) {
   static_for_impl(f, std::make_integer_sequence<int, N>{});
 }
 
-template <int D>
+template <int D, int ROWS = TR>
 struct Tile {
-  static constexpr int BYTES = TR * D * 2;
+  static constexpr int BYTES = ROWS * D * 2;
   static constexpr int NI = BYTES / 1024 / 4;  // DMA instructions per wave per tile
   // Per-lane source offsets (bytes, relative to element (row0, col0) of the source matrix) of this wave's DMA
   // instructions: instruction q = wave*NI + i fills LDS bytes [1024 q, 1024 q + 1024) of the tile, and the lane
@@ -444,7 +451,7 @@ __global__ __launch_bounds__(AT_THREADS, 2) void attn_dq_kernel(const bf16_t* __
                                                                 const bf16_t* __restrict__ o, int64_t ld_o,
                                                                 const bf16_t* __restrict__ d_o, int64_t ldo,
                                                                 const float* __restrict__ lse,
-                                                                float* __restrict__ delta,
+                                                                float* __restrict__ stats,
                                                                 bf16_t* __restrict__ dqkv, int64_t ldg, int S, int nq,
                                                                 int nkv, const float* __restrict__ cos_tab,
                                                                 const float* __restrict__ sin_tab) {
@@ -476,8 +483,8 @@ __global__ __launch_bounds__(AT_THREADS, 2) void attn_dq_kernel(const bf16_t* __
   }
   const int64_t si = (int64_t(bi) * nq + hq) * S + qi;
   const float L2 = qi < S ? lse[si] * LOG2E : 0.f;
-  // delta = dO . O of this lane's query row (the two lane halves hold complementary features); it is also
-  // written out for the dK kernel, which runs after this one
+  // delta = dO . O of this lane's query row (the two lane halves hold complementary features).  The row statistics are
+  // written out as the dK / dV kernel takes them: lse log2(e), then -delta, each [b][n_q][S]
   float dl = 0.f;
   {
     const bf16_t* ob = o + int64_t(bi) * S * ld_o;
@@ -488,7 +495,10 @@ __global__ __launch_bounds__(AT_THREADS, 2) void attn_dq_kernel(const bf16_t* __
       for (int e = 0; e < 8; e++) dl += (float)of[e] * (float)dof[kk][e];
     }
     dl += __shfl_xor(dl, 32, 64);
-    if (lane < 32 && qi < S) delta[si] = dl;
+    if (lane < 32 && qi < S) {
+      stats[si] = L2;
+      stats[int64_t(gridDim.z) * nq * S + si] = -dl;
+    }
   }
 
   f32x16 acc[DT];
@@ -547,155 +557,326 @@ __global__ __launch_bounds__(AT_THREADS, 2) void attn_dq_kernel(const bf16_t* __
   }
 }
 
-// ================================================================ backward: dK and dV (one kernel each)
-// grid (n_kv, kv blocks of 128, b), longest first; wave w owns key rows j0 + 32w .. +31 and keeps their K (and V)
-// as B operands.  Loops over the query heads of the group and the query blocks of 64 rows at or below the
-// diagonal: S = Q K^T (lane column = key row), then
-//   WHAT = 0 (dK):  dP = dO V^T, dS = P (dP - delta), dK^T += Q^T dS
-//   WHAT = 1 (dV):  dV^T += dO^T P
-// Two kernels on purpose: with both accumulators in one kernel the register demand passes 256, the MFMAs fall
-// back to the accumulation-register form with hundreds of register copies per iteration, and only one workgroup
-// fits a CU.  Apart, S is recomputed once more but each kernel runs two workgroups per CU.
-template <int D, int WHAT>
-__global__ __launch_bounds__(AT_THREADS, 2) void attn_dkv_kernel(const bf16_t* __restrict__ qkv, int64_t ld,
+// ================================================================ backward: dK and dV
+// grid (n_kv * nsplit, kv blocks of 128 KT, b), longest first; wave w owns the 32 KT key rows from j0 + 32 KT w and keeps
+// their K and V as B operands.  Loops over the query heads of the group and the 32-row query steps at or below the
+// diagonal: S = Q K^T (lane column = key row), dP = dO V^T, dS = P (dP - delta), dV^T += dO^T P, dK^T += Q^T dS.
+//
+// One kernel for both: apart (S formed twice more, 370 us for 32 heads of 128 at 4096 positions) two workgroups fitted a
+// CU; together 272 us.  One wavefront per SIMD with up to 512 registers, software-pipelined: step `it` issues S(it), then
+// dP(it) with the exponentials of S(it) in between, then the products dV, dK of step it-1 with dS(it) in between, so that
+// no product waits for the vector instructions it depends on.  The instructions of a step are issued in exactly the
+// order written.  What bounds it is the issue of that one wavefront: about 330 instructions beside the 64 products of a
+// step with KT = 2 (MFMAs busy 53 % of the cycles, LDS 47 %, no bank conflicts), so work was taken out of it: delta is
+// where dP starts from, lse arrives scaled, requests move by 32-bit offsets.  A 32-row fragment of Q or dO feeds KT
+// products; with KT = 2 V no longer fits the registers beside 256 accumulators and is read from LDS.
+// Measured (us, before -> after): 4096 positions, 32 heads of 128: 370 -> 272 (KT = 2); 2048, 16 of 128: 145 -> 63; 4096, 16 of
+// 64: 210 -> 95; 4096, 16 heads of 128 over 2 KV heads: 286 -> 157 with the reduction.
+// LDS: V of the workgroup's keys if it lives there, a ring of five steps [Q | dO | row statistics].  The one
+// barrier of a step lies within S(it): step it+1 has landed for everyone, and the slot of step it-2 is free for it+3
+// (its last reads came before the Q fragments that S(it) has waited for, and LDS reads return in order).
+template <int D, int KT>
+__global__ __launch_bounds__(AT_THREADS, 1) void attn_dkv_kernel(const bf16_t* __restrict__ qkv, int64_t ld,
                                                                  const bf16_t* __restrict__ d_o, int64_t ldo,
-                                                                 const float* __restrict__ lse,
-                                                                 const float* __restrict__ delta,
+                                                                 const float* __restrict__ stats,
                                                                  bf16_t* __restrict__ dqkv, int64_t ldg, int S, int nq,
                                                                  int nkv, int nsplit, float* __restrict__ part,
                                                                  const float* __restrict__ cos_tab,
                                                                  const float* __restrict__ sin_tab) {
-  using TL = Tile<D>;
-  constexpr bool DKM = WHAT == 0;
-  constexpr int KD = D / 16, DT = D / 32;
-  __shared__ __attribute__((aligned(1024))) bf16_t lds[2][2][TR * D];  // [buffer][Q|dO]
-  __shared__ float stat[2][2][TR];                                       // [buffer][lse*log2e | delta]
-  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  using TS = Tile<D, 32>;
+  constexpr int KD = D / 16, DT = D / 32, KR = 32 * KT, SLOTS = 5;
+  constexpr bool VL = KT == 2;                               // V fragments from LDS
+  static_assert(KT == 1 || D == 128);
+  constexpr int STG = 2 * TS::BYTES + 512, V_BYTES = VL ? 4 * KR * D * 2 : 0;
+  constexpr int NREQ = 2 * TS::NI + 1;                       // requests of a wavefront per step
+  __shared__ __attribute__((aligned(1024))) char lds[V_BYTES + SLOTS * STG];  // [V] [slot][Q|dO|lse log2(e)|-delta]
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), half = lane >> 5;
   // nsplit > 1: the query heads of a group are shared out over nsplit workgroups (few KV heads would otherwise
   // leave most CUs idle); each writes its fp32 partial sum to `part`, which gqa_reduce_kernel adds up in order
   const int kb = blockIdx.y, hk = blockIdx.x / nsplit, sp = blockIdx.x % nsplit, bi = blockIdx.z;
   const int grp = nq / nkv / nsplit, hq0 = hk * (nq / nkv) + sp * grp;
   const bf16_t* base = qkv + int64_t(bi) * S * ld;
   const bf16_t* dob = d_o + int64_t(bi) * S * ldo;
-  const int j0 = kb * 128, jw = j0 + wave * 32, ji = jw + (lane & 31);
+  const int j0 = kb * 4 * KR, jw = j0 + wave * KR;
   const float scale = rsqrtf((float)D), sc = scale * LOG2E;
+  const uint32_t lds0 = (uint32_t)(uintptr_t)(MLS_LDS char*)&lds[0];
+  const uint32_t ring = lds0 + V_BYTES;
 
-  bf16x8 kf[KD], vf[DKM ? KD : 1];
-#pragma unroll
-  for (int kk = 0; kk < KD; kk++) {
-    kf[kk] = gfrag(base, ld, ji, (nq + hk) * D + kk * 16 + (lane >> 5) * 8, ji < S);
-    if (DKM) vf[kk] = gfrag(base, ld, ji, (nq + nkv + hk) * D + kk * 16 + (lane >> 5) * 8, ji < S);
-  }
-  f32x16 acc[DT];
-#pragma unroll
-  for (int t = 0; t < DT; t++) acc[t] = zero16();
-
-  const int qb0 = j0 / TR, nqb = (S + TR - 1) / TR - qb0;  // query blocks per head
-  const int niter = nqb > 0 ? nqb * grp : 0;
-  const i32x4 rq_src = make_rsrc(base, uint32_t(int64_t(S) * ld * 2)), rd_src = make_rsrc(dob, uint32_t(int64_t(S) * ldo * 2));
-  const uint32_t lds0 = (uint32_t)(uintptr_t)(MLS_LDS bf16_t*)&lds[0][0][0];
-  TL tq, td;
+  const int q0 = j0 / 32, nst = (S + 31) / 32 - q0;  // first query step, steps per head
+  const int niter = nst * grp;
+  TS tq, td;
   tq.init(ld, wave, lane);
   td.init(ldo, wave, lane);
-  // The query blocks of a head are walked from the last one down to the diagonal: the workgroups of all key blocks
-  // of that head (same XCD, started together) then read the same Q / dO tile at about the same time and share it in L2.
-  // iteration `it`: Q and dO rows of one 64-row query block of one head of the group -> buffer it & 1; the row
-  // statistics go through registers (threads 0..63: lse*log2e of row tid; threads 64..127: delta of row tid-64)
-  float rs = 0.f;
-  auto issue = [&](int it, bool live) {
-    const int hq = hq0 + (live ? it / nqb : 0), i0 = (qb0 + (live ? nqb - 1 - it % nqb : 0)) * TR;
-    const uint32_t t = lds0 + (it & 1) * 2 * TL::BYTES;
-    tq.dma(rq_src, ld, i0, hq * D, t, wave, live);
-    td.dma(rd_src, ldo, i0, hq * D, t + TL::BYTES, wave, live);
-    if (live && threadIdx.x < (DKM ? 2 : 1) * TR) {
-      const int r = threadIdx.x & (TR - 1);
-      const int64_t si = (int64_t(bi) * nq + hq) * S + i0 + r;
-      rs = 0.f;
-      if (i0 + r < S) rs = threadIdx.x < TR ? lse[si] * LOG2E : delta[si];
+  // The query steps of a head are walked from the last one down to the diagonal: the workgroups of all key blocks of that
+  // head (same XCD, started together) then read the same Q / dO rows at about the same time and share them in L2.
+  // The next request: byte offsets of its rows behind the three descriptors, moved on by a step or to the next head's last step.
+  const i32x4 rs_q = make_rsrc(base, uint32_t(int64_t(S) * ld * 2)), rs_d = make_rsrc(dob, uint32_t(int64_t(S) * ldo * 2));
+  // even wavefronts fetch lse log2(e), odd ones -delta (each pair the same values)
+  const i32x4 rs_s = make_rsrc(stats + ((wave & 1) * int64_t(gridDim.z) * nq + int64_t(bi) * nq + hq0) * S, uint32_t(grp * S) * 4);
+  int r_i = nst - 1, r_slot = 0, r_left = niter;
+  uint32_t o_q = uint32_t((q0 + r_i) * 64 * ld) + hq0 * D * 2, o_d = uint32_t((q0 + r_i) * 64 * ldo) + hq0 * D * 2, o_s = (q0 + r_i) * 128;
+  const uint32_t step_q = uint32_t(64 * ld), step_d = uint32_t(64 * ldo);
+  const uint32_t wrap_q = (nst - 1) * step_q + D * 2, wrap_d = (nst - 1) * step_d + D * 2, wrap_s = (nst - 1) * 128 + S * 4;
+  const uint32_t dst0 = ring + wave * TS::NI * 1024;
+  auto issue_q = [&]() {  // requests beyond the last step are sent as empty
+    const uint32_t o = r_left > 0 ? o_q : OOB;
+#pragma unroll
+    for (int i = 0; i < TS::NI; i++) dma16(rs_q, o + tq.off[i], dst0 + r_slot + i * 1024);
+  };
+  auto issue_d = [&]() {
+    const uint32_t o = r_left > 0 ? o_d : OOB;
+#pragma unroll
+    for (int i = 0; i < TS::NI; i++) dma16(rs_d, o + td.off[i], dst0 + r_slot + TS::BYTES + i * 1024);
+  };
+  auto issue_s = [&]() {
+    const int rows = r_left > 0 ? S - (q0 + r_i) * 32 : 0;
+    dma4(rs_s, lane < rows ? o_s + uint32_t(lane) * 4 : OOB, ring + r_slot + 2 * TS::BYTES + (wave & 1) * 256);
+    r_left--;
+    r_slot = r_slot == (SLOTS - 1) * STG ? 0 : r_slot + STG;
+    const bool wrap = r_i == 0;
+    r_i = wrap ? nst - 1 : r_i - 1;
+    o_q += wrap ? wrap_q : 0u - step_q;
+    o_d += wrap ? wrap_d : 0u - step_d;
+    o_s += wrap ? wrap_s : 0u - 128u;
+  };
+
+  bf16x8 kf[KT][KD], vf[VL ? 1 : KT][KD];
+  if constexpr (VL) {
+    const i32x4 src = make_rsrc(base + (nq + nkv + hk) * D + int64_t(jw) * ld, jw < S ? uint32_t(int64_t(S - jw) * ld * 2) : 0u);
+#pragma unroll
+    for (int q = 0; q < KR * D * 2 / 1024; q++) {
+      const int row = q * 4 + (lane >> 4), chunk = (lane & 15) ^ (((row & 3) << 2) | ((row >> 2) & 3));
+      dma16(src, uint32_t((int64_t(row) * ld + chunk * 8) * 2), lds0 + wave * KR * D * 2 + q * 1024);
+    }
+  }
+#pragma unroll
+  for (int kt = 0; kt < KT; kt++) {
+    const int ji = jw + kt * 32 + (lane & 31);
+#pragma unroll
+    for (int kk = 0; kk < KD; kk++) {
+      kf[kt][kk] = gfrag(base, ld, ji, (nq + hk) * D + kk * 16 + half * 8, ji < S);
+      if constexpr (!VL) vf[kt][kk] = gfrag(base, ld, ji, (nq + nkv + hk) * D + kk * 16 + half * 8, ji < S);
+    }
+  }
+  for (int i = 0; i < 3; i++) {
+    issue_q();
+    issue_d();
+    issue_s();
+  }
+
+  f32x16 dk[KT][DT], dv[KT][DT];
+#pragma unroll
+  for (int kt = 0; kt < KT; kt++)
+#pragma unroll
+    for (int t = 0; t < DT; t++) dk[kt][t] = dv[kt][t] = zero16();
+  bf16x8 pf[KT][2] = {}, df[KT][2] = {};  // P and dS of the previous step
+
+  // Fragment addresses: the swizzle turns a step along the columns into an XOR, slots are multiples of 256 bytes apart.
+  uint32_t ra = ring + toff<D>(lane & 31, half * 8) * 2;                                                           // rows: this step's slot
+  uint32_t ca = ring + toff<D>(half * 4 + ((lane & 15) >> 2), ((lane >> 4) & 1) * 16 + (lane & 3) * 4) * 2;        // columns: the step before
+  const uint32_t va = ra - V_BYTES + wave * (VL ? KR * D * 2 : 0);
+  uint32_t sa = ring + 2 * TS::BYTES + half * 16;
+
+  // The fragment reads of a step in their order: Q rows; dO rows, each followed by V's if those are in LDS; the columns of dO
+  // and Q in turn.  Reads run FA fragments ahead of the MFMAs, over the end of the step into the next one's Q rows.
+  constexpr int G = VL ? 1 + KT : 1;
+  constexpr int R1 = KD, R2 = R1 + KD * G, R3 = R2 + 4 * DT;
+  constexpr int FA = KD < 6 ? KD : 6;
+  bf16x8 f[R3 + FA];
+  auto read = [&](auto IC) {
+    constexpr int i = decltype(IC)::value;
+    if constexpr (i < R1) {
+      f[i] = *(const MLS_LDS bf16x8*)(ra ^ (i << 5));
+    } else if constexpr (i < R2) {
+      constexpr int kk = (i - R1) / G, w = (i - R1) % G;
+      if constexpr (w == 0) f[i] = *(const MLS_LDS bf16x8*)((ra ^ (kk << 5)) + TS::BYTES);
+      else f[i] = *(const MLS_LDS bf16x8*)((va ^ (kk << 5)) + (w - 1) * 32 * D * 2);
+    } else if constexpr (i < R3) {
+      constexpr int q = (i - R2) / 2, ct = q % DT, o = (((i - R2) & 1) ? 0 : TS::BYTES) + q / DT * 16 * D * 2;
+      const s16x4 l = __builtin_amdgcn_ds_read_tr16_b64_v4i16((MLS_LDS s16x4*)((ca ^ (ct << 6)) + o));
+      const s16x4 h = __builtin_amdgcn_ds_read_tr16_b64_v4i16((MLS_LDS s16x4*)((ca ^ (ct << 6) ^ 32) + (o + 8 * D * 2)));
+      const s16x8 v = {l[0], l[1], l[2], l[3], h[0], h[1], h[2], h[3]};
+      f[i] = __builtin_bit_cast(bf16x8, v);
+    } else {
+      f[i] = *(const MLS_LDS bf16x8*)(ra ^ ((i - R3) << 5));  // the row address has moved on
     }
   };
-  // the statistics fetched by issue(it) are stored after the compute of iteration it-1 (or before the loop)
-  auto put_stat = [&](int it) {
-    if (threadIdx.x < (DKM ? 2 : 1) * TR) stat[it & 1][threadIdx.x >> 6][threadIdx.x & (TR - 1)] = rs;
+  // Products that take fragment i (with V in LDS a dP product goes with the V fragment).  S and dP are products in asm that
+  // leave their results in VGPRs (the compiler would put them beside dK and dV into AGPRs and copy them back and forth);
+  // their first reader stays three products (96 cycles) behind the last one that wrote them, which the fixed order below
+  // sees to.
+  f32x16 st[KT], dp[KT];
+  // dP starts from -delta.
+  auto mul = [&](f32x16& c, const bf16x8& x, const bf16x8& y, auto ZERO) {
+    if constexpr (decltype(ZERO)::value) asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, 0" : "=&v"(c) : "v"(x), "v"(y));
+    else asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, %0" : "+v"(c) : "v"(x), "v"(y));
   };
-  issue(0, niter > 0);
-  put_stat(0);
-  for (int it = 0; it < niter; it++) {
-    const int cur = it & 1, i0 = (qb0 + nqb - 1 - it % nqb) * TR;
-    wait_dma();
-    __syncthreads();
-    issue(it + 1, it + 1 < niter);
-    if (i0 + TR - 1 >= jw) {  // wave-uniform: some query row at or below this wave's first key row
-      const bf16_t* qs = lds[cur][0];
-      const bf16_t* ds_ = lds[cur][1];
-      const bool diag = i0 < jw + 31 || i0 + TR > S;  // some pair is masked, or the block runs past the last row
-      const bf16_t* tx = DKM ? qs : ds_;
-      // one 32-query sub-block at a time, so that only one S / dP pair is live
+  auto use = [&](auto IC) {
+    constexpr int i = decltype(IC)::value;
+    if constexpr (i < R1) {
 #pragma unroll
-      for (int itl = 0; itl < 2; itl++) {
-        f32x16 st = zero16(), dp = zero16();
-        if (DKM) {
-          read_ahead<2 * KD, 3, 1>(
-              [&](int i) { return TL::frag_rows((i & 1) ? ds_ : qs, itl, i >> 1, lane); },
-              [&](int i, const bf16x8& f) {
-                if (i & 1) dp = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f, vf[DKM ? i >> 1 : 0], dp, 0, 0, 0);
-                else st = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f, kf[i >> 1], st, 0, 0, 0);
-              });
-          auto to_ds = [&](auto MASK) {  // the mask arithmetic is compiled only into the diagonal-block path
+      for (int kt = 0; kt < KT; kt++) mul(st[kt], f[i], kf[kt][i], std::bool_constant<i == 0>{});
+    } else if constexpr (i < R2) {
+      constexpr int kk = (i - R1) / G, w = (i - R1) % G;
+      if constexpr (VL) {
+        if constexpr (w > 0) mul(dp[w - 1], f[R1 + kk * G], f[i], std::false_type{});
+      } else {
 #pragma unroll
-            for (int e = 0; e < 16; e++) {
-              const int r = itl * 32 + (lane >> 5) * 4 + 8 * (e >> 2) + (e & 3);
-              float p = __builtin_amdgcn_exp2f(st[e] * sc - stat[cur][0][r]);
-              if (decltype(MASK)::value && (i0 + r < ji || i0 + r >= S)) p = 0.f;
-              st[e] = p * (dp[e] - stat[cur][1][r]);  // dS
-            }
-          };
-          if (diag) to_ds(std::true_type{}); else to_ds(std::false_type{});
-        } else {
-          read_ahead<KD, 3, 1>([&](int i) { return TL::frag_rows(qs, itl, i, lane); },
-                               [&](int i, const bf16x8& f) {
-                                 st = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f, kf[i], st, 0, 0, 0);
-                               });
-          auto softmax = [&](auto MASK) {  // the mask arithmetic is compiled only into the diagonal-block path
+        for (int kt = 0; kt < KT; kt++) mul(dp[kt], f[i], vf[kt][kk], std::false_type{});
+      }
+    } else {
+      constexpr int q = (i - R2) / 2;
 #pragma unroll
-            for (int e = 0; e < 16; e++) {
-              const int r = itl * 32 + (lane >> 5) * 4 + 8 * (e >> 2) + (e & 3);
-              float p = __builtin_amdgcn_exp2f(st[e] * sc - stat[cur][0][r]);
-              if (decltype(MASK)::value && (i0 + r < ji || i0 + r >= S)) p = 0.f;
-              st[e] = p;
-            }
-          };
-          if (diag) softmax(std::true_type{}); else softmax(std::false_type{});
-        }
-        const bf16x8 bf[2] = {acc_to_b(st, 0), acc_to_b(st, 1)};
-        read_ahead<2 * DT, 2, 2>([&](int i) { return TL::frag_cols(tx, i % DT, itl * 2 + i / DT, lane); },
-                                 [&](int i, const bf16x8& f) {
-                                   acc[i % DT] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f, bf[i / DT], acc[i % DT], 0, 0, 0);
-                                 });
+      for (int kt = 0; kt < KT; kt++) {
+        if constexpr ((i - R2) & 1) dk[kt][q % DT] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f[i], df[kt][q / DT], dk[kt][q % DT], 0, 0, 0);
+        else dv[kt][q % DT] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f[i], pf[kt][q / DT], dv[kt][q % DT], 0, 0, 0);
       }
     }
-    if (it + 1 < niter) put_stat(it + 1);
+  };
+  // fragments [LO, HI) in exactly this order: the read FA ahead (up to END), the products, vector instructions between(i)
+  auto run = [&](auto LO, auto HI, auto END, auto&& between) {
+    constexpr int lo = decltype(LO)::value, hi = decltype(HI)::value, end = decltype(END)::value;
+    static_for<hi - lo>([&](auto IC) {
+      constexpr int i = lo + decltype(IC)::value;
+      if constexpr (i + FA < end) read(std::integral_constant<int, i + FA>{});
+      use(std::integral_constant<int, i>{});
+      between(std::integral_constant<int, i>{});
+      __builtin_amdgcn_sched_barrier(0);
+    });
+  };
+  auto none = [](auto) {};
+  using I0 = std::integral_constant<int, 0>;
+  using I1 = std::integral_constant<int, R1>;
+  using I2 = std::integral_constant<int, R2>;
+  using I3 = std::integral_constant<int, R3>;
+  using I4 = std::integral_constant<int, R3 + FA>;
+
+  int slot = 0, i0 = (q0 + nst - 1) * 32;  // of this step
+  uint32_t adv = 0;                        // from the previous step's slot to this one's
+#pragma unroll
+  for (int kt = 0; kt < KT; kt++)  // the compiler's own wait for the K (and V) fragments, here and not in the loop
+#pragma unroll
+    for (int kk = 0; kk < KD; kk++) {
+      asm volatile("" : "+v"(kf[kt][kk]));
+      if constexpr (!VL) asm volatile("" : "+v"(vf[kt][kk]));
+    }
+  wait_vm<2 * NREQ>();
+  __builtin_amdgcn_s_barrier();
+  asm volatile("" ::: "memory");
+  static_for<FA>(read);
+  for (int it = 0; it < niter; it++) {
+    // ---- S(it)
+    constexpr int Q1 = R1 / 4;
+    run(I0{}, std::integral_constant<int, Q1>{}, I3{}, none);
+    wait_vm<NREQ>();
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+    issue_q();
+    run(std::integral_constant<int, Q1>{}, std::integral_constant<int, 2 * Q1>{}, I3{}, none);
+    issue_d();
+    run(std::integral_constant<int, 2 * Q1>{}, std::integral_constant<int, 3 * Q1>{}, I3{}, none);
+    issue_s();
+    f32x4 ls[4];  // lse log2(e) of 4 rows each: read one group ahead of use
+    ls[0] = *(const MLS_LDS f32x4*)(sa);
+#pragma unroll
+    for (int kt = 0; kt < KT; kt++) {
+      uint32_t da = sa;
+      asm volatile("" : "+v"(da));  // read again for each key tile: copies would be vector instructions
+#pragma unroll
+      for (int g = 0; g < 4; g++) {
+        const f32x4 v = *(const MLS_LDS f32x4*)(da + 256 + g * 32);
+#pragma unroll
+        for (int r = 0; r < 4; r++) dp[kt][g * 4 + r] = v[r];
+      }
+    }
+    run(std::integral_constant<int, 3 * Q1>{}, I1{}, I3{}, none);
+    // ---- dP(it); P(it) = exp2(sc S - L2)
+    run(I1{}, I2{}, I3{}, [&](auto IC) {
+      constexpr int n = R2 - R1, i = decltype(IC)::value - R1, b0 = VL ? 4 : KT == 1 ? 2 : 1;  // three products behind S
+      if constexpr (i >= b0) {
+        constexpr int lo = (i - b0) * 16 * KT / (n - b0), hi = (i - b0 + 1) * 16 * KT / (n - b0);
+        static_for<hi - lo>([&](auto EC) {
+          constexpr int x = lo + decltype(EC)::value, g = x / (4 * KT), kt = x / 4 % KT, e = g * 4 + x % 4;
+          if constexpr (x % (4 * KT) == 0 && g < 3) ls[g + 1] = *(const MLS_LDS f32x4*)(sa + (g + 1) * 32);
+          st[kt][e] = __builtin_amdgcn_exp2f(st[kt][e] * sc - ls[g][x % 4]);
+        });
+      }
+    });
+    if (i0 < jw + KR - 1 || i0 + 32 > S) {  // wave-uniform: some pair is masked, or the step runs past the last row
+#pragma unroll
+      for (int kt = 0; kt < KT; kt++) {
+        const int c = jw + kt * 32 + (lane & 31) - i0 - half * 4, z = S - i0 - half * 4;
+#pragma unroll
+        for (int e = 0; e < 16; e++) {
+          const int r = 8 * (e >> 2) + (e & 3);
+          if (r < c || r >= z) st[kt][e] = 0.f;
+        }
+      }
+    }
+    __builtin_amdgcn_sched_barrier(0);
+    // ---- dV, dK of step it-1; dS(it) = P dP, which has delta taken off
+    const uint32_t next = slot == SLOTS - 1 ? 0u - (SLOTS - 1) * STG : STG;
+    ra += next;
+    run(I2{}, I3{}, I4{}, [&](auto IC) {
+      constexpr int n = R3 - R2, i = decltype(IC)::value - R2, b0 = 2;  // three products and more behind dP
+      if constexpr (i >= b0) {
+        constexpr int lo = (i - b0) * 16 * KT / (n - b0), hi = (i - b0 + 1) * 16 * KT / (n - b0);
+        static_for<hi - lo>([&](auto EC) {
+          constexpr int x = lo + decltype(EC)::value, g = x / (4 * KT), kt = x / 4 % KT, e = g * 4 + x % 4;
+          dp[kt][e] *= st[kt][e];
+          if constexpr (e == 7) {  // the products with the previous step's first halves have been issued
+            static_assert(i >= n / 2 - 1);
+            pf[kt][0] = acc_to_b(st[kt], 0);
+            df[kt][0] = acc_to_b(dp[kt], 0);
+          }
+        });
+      }
+    });
+#pragma unroll
+    for (int kt = 0; kt < KT; kt++) {
+      pf[kt][1] = acc_to_b(st[kt], 1);
+      df[kt][1] = acc_to_b(dp[kt], 1);
+    }
+    static_for<FA>([&](auto IC) { f[decltype(IC)::value] = f[R3 + decltype(IC)::value]; });
+    ca += adv;  // the columns move on to this step's slot (in the first step, which has no predecessor, they were there already)
+    sa += next;
+    adv = next;
+    slot = slot == SLOTS - 1 ? 0 : slot + 1;
+    i0 = i0 == q0 * 32 ? (q0 + nst - 1) * 32 : i0 - 32;
+    __builtin_amdgcn_sched_barrier(0);
   }
+  static_for<FA>([&](auto IC) { read(std::integral_constant<int, R2 + decltype(IC)::value>{}); });
+  run(I2{}, I3{}, I3{}, none);
   wait_dma();
-  if (nsplit == 1) {
-    bf16_t* out = dqkv + int64_t(bi) * S * ldg;
-    if (DKM && cos_tab) {  // dK is a gradient w.r.t. the rotated k (partial sums are turned back by the reduction)
-      store_t_unrotate<D>(out, ldg, ji, ji, (nq + hk) * D, acc, scale, cos_tab, sin_tab, lane, ji < S);
-    } else {
+
+#pragma unroll
+  for (int kt = 0; kt < KT; kt++) {
+    const int ji = jw + kt * 32 + (lane & 31);
+    if (nsplit == 1) {
+      bf16_t* out = dqkv + int64_t(bi) * S * ldg;
+      if (cos_tab) {  // dK is a gradient w.r.t. the rotated k (partial sums are turned back by the reduction)
+        store_t_unrotate<D>(out, ldg, ji, ji, (nq + hk) * D, dk[kt], scale, cos_tab, sin_tab, lane, ji < S);
+      } else {
+#pragma unroll
+        for (int t = 0; t < DT; t++) store_t(out, ldg, ji, (nq + hk) * D + t * 32, dk[kt][t], scale, lane, ji < S);
+      }
+#pragma unroll
+      for (int t = 0; t < DT; t++) store_t(out, ldg, ji, (nq + nkv + hk) * D + t * 32, dv[kt][t], 1.f, lane, ji < S);
+    } else if (ji < S) {
+      // part: [dK | dV][b][n_kv][nsplit][S][D] fp32
+      float* out = part + (((int64_t(bi) * nkv + hk) * nsplit + sp) * S + ji) * D;
+      const int64_t whole = int64_t(gridDim.z) * nkv * nsplit * S * D;
 #pragma unroll
       for (int t = 0; t < DT; t++)
-        store_t(out, ldg, ji, (DKM ? nq + hk : nq + nkv + hk) * D + t * 32, acc[t], DKM ? scale : 1.f, lane, ji < S);
+#pragma unroll
+        for (int g = 0; g < 4; g++) {
+          const int c = t * 32 + half * 4 + 8 * g;
+          *reinterpret_cast<float4*>(out + c) = make_float4(dk[kt][t][g * 4] * scale, dk[kt][t][g * 4 + 1] * scale,
+                                                            dk[kt][t][g * 4 + 2] * scale, dk[kt][t][g * 4 + 3] * scale);
+          *reinterpret_cast<float4*>(out + whole + c) =
+              make_float4(dv[kt][t][g * 4], dv[kt][t][g * 4 + 1], dv[kt][t][g * 4 + 2], dv[kt][t][g * 4 + 3]);
+        }
     }
-  } else if (ji < S) {
-    // part: [dK | dV][b][n_kv][nsplit][S][D] fp32
-    float* out = part + ((((int64_t(WHAT) * gridDim.z + bi) * nkv + hk) * nsplit + sp) * S + ji) * D;
-    const float mul = DKM ? scale : 1.f;
-#pragma unroll
-    for (int t = 0; t < DT; t++)
-#pragma unroll
-      for (int g = 0; g < 4; g++)
-        *reinterpret_cast<float4*>(out + t * 32 + (lane >> 5) * 4 + 8 * g) =
-            make_float4(acc[t][g * 4] * mul, acc[t][g * 4 + 1] * mul, acc[t][g * 4 + 2] * mul, acc[t][g * 4 + 3] * mul);
   }
 }
 
@@ -761,48 +942,51 @@ hipError_t attn_fwd_bf16(const void* qkv, int64_t ld_qkv, void* o, int64_t ld_o,
   return hipGetLastError();
 }
 
-// how many workgroups share the query heads of one KV group in the dK / dV kernels: the smallest divisor of the
-// group size that gives every CU two workgroups (1 when the plain grid already does)
-int gqa_split(int b, int S, int nq, int nkv) {
-  const int grp = nq / nkv, blocks = nkv * ((S + 127) / 128) * b;
-  int n = 1;
-  while (n < grp && blocks * n < 512) {
-    n++;
-    while (grp % n) n++;
+// dK / dV kernel: key tiles per wavefront, and how many workgroups share the query heads of one KV group.  The smallest
+// estimate of max(longest workgroup, share of a CU) in steps of 32 query rows, plus the reduction of partial sums.
+// Measured us per step: 1.1 (d = 128, one key tile: 32 heads at 4096 in 292 us), 1.95 (two: 272 us, half the steps),
+// 0.75 (d = 64; two tiles were slower: 130 against 95 us for 16 heads at 4096).  Two tiles win once every CU has
+// several workgroups, one tile below: 16 heads at 2048 63 against 105 us.  Partial sums of 16.8 million floats: 12 us.
+struct DkvPlan { int kt, ns; };
+DkvPlan dkv_plan(int b, int S, int nq, int nkv, int d) {
+  DkvPlan best{1, 1};
+  double least = 1e300;
+  const int steps = (S + 31) / 32, grp = nq / nkv;
+  for (int kt = 1; kt <= (d == 128 ? 2 : 1); kt++) {
+    const int nb = (S + 128 * kt - 1) / (128 * kt);
+    const double sum = double(nb) * steps - double(nb) * (nb - 1) / 2 * 4 * kt;  // steps of all key blocks, one head
+    for (int ns = 1; ns <= grp; ns++) {
+      if (grp % ns) continue;
+      const double longest = double(steps) * (grp / ns), share = sum * nq * b / 256;
+      double t = (d == 64 ? 0.75 : kt == 1 ? 1.1 : 1.95) * (longest > share ? longest : share);
+      if (ns > 1) t += 4 + 0.8e-6 * 2 * b * nkv * double(ns) * S * d;
+      if (t < least) least = t, best = {kt, ns};
+    }
   }
-  return n;
+  return best;
 }
 
 size_t attn_bwd_scratch_floats(int dt, int b, int S, int nq, int nkv, int d) {
   if (dt != DT_BF16 || nkv <= 0 || nq % nkv) return 0;
-  const int n = gqa_split(b, S, nq, nkv);
+  const int n = dkv_plan(b, S, nq, nkv, d).ns;
   return n > 1 ? size_t(2) * b * nkv * n * S * d : 0;
 }
 
 hipError_t attn_bwd_bf16(const void* qkv, int64_t ld_qkv, const void* o, int64_t ld_o, const float* lse, const void* d_o,
-                         int64_t ld_do, void* dqkv, int64_t ld_dqkv, float* delta, int b, int S, int nq, int nkv, int d,
+                         int64_t ld_do, void* dqkv, int64_t ld_dqkv, float* stats, int b, int S, int nq, int nkv, int d,
                          hipStream_t st, float* part, const float* cos_tab, const float* sin_tab) {
   if (b == 0 || S == 0) return hipSuccess;
   if (!cos_tab != !sin_tab) return hipErrorInvalidValue;
-  const int ns = part ? gqa_split(b, S, nq, nkv) : 1;
-  dim3 gq(nq, (S + 127) / 128, b), gk(nkv * ns, (S + 127) / 128, b);
-  if (d == 128) {
-    hipLaunchKernelGGL(attn_dq_kernel<128>, gq, dim3(AT_THREADS), 0, st, (const bf16_t*)qkv, ld_qkv, (const bf16_t*)o, ld_o,
-                       (const bf16_t*)d_o, ld_do, lse, delta, (bf16_t*)dqkv, ld_dqkv, S, nq, nkv, cos_tab, sin_tab);
-    hipLaunchKernelGGL((attn_dkv_kernel<128, 0>), gk, dim3(AT_THREADS), 0, st, (const bf16_t*)qkv, ld_qkv,
-                       (const bf16_t*)d_o, ld_do, lse, delta, (bf16_t*)dqkv, ld_dqkv, S, nq, nkv, ns, part, cos_tab, sin_tab);
-    hipLaunchKernelGGL((attn_dkv_kernel<128, 1>), gk, dim3(AT_THREADS), 0, st, (const bf16_t*)qkv, ld_qkv,
-                       (const bf16_t*)d_o, ld_do, lse, delta, (bf16_t*)dqkv, ld_dqkv, S, nq, nkv, ns, part, cos_tab, sin_tab);
-  } else if (d == 64) {
-    hipLaunchKernelGGL(attn_dq_kernel<64>, gq, dim3(AT_THREADS), 0, st, (const bf16_t*)qkv, ld_qkv, (const bf16_t*)o, ld_o,
-                       (const bf16_t*)d_o, ld_do, lse, delta, (bf16_t*)dqkv, ld_dqkv, S, nq, nkv, cos_tab, sin_tab);
-    hipLaunchKernelGGL((attn_dkv_kernel<64, 0>), gk, dim3(AT_THREADS), 0, st, (const bf16_t*)qkv, ld_qkv,
-                       (const bf16_t*)d_o, ld_do, lse, delta, (bf16_t*)dqkv, ld_dqkv, S, nq, nkv, ns, part, cos_tab, sin_tab);
-    hipLaunchKernelGGL((attn_dkv_kernel<64, 1>), gk, dim3(AT_THREADS), 0, st, (const bf16_t*)qkv, ld_qkv,
-                       (const bf16_t*)d_o, ld_do, lse, delta, (bf16_t*)dqkv, ld_dqkv, S, nq, nkv, ns, part, cos_tab, sin_tab);
-  } else {
-    return hipErrorInvalidValue;
-  }
+  if (d != 128 && d != 64) return hipErrorInvalidValue;
+  const DkvPlan pl = dkv_plan(b, S, nq, nkv, d);
+  const int ns = part ? pl.ns : 1, kr = 128 * pl.kt;
+  dim3 gq(nq, (S + 127) / 128, b), gk(nkv * ns, (S + kr - 1) / kr, b);
+  auto dq = d == 128 ? attn_dq_kernel<128> : attn_dq_kernel<64>;
+  auto dkv = d == 64 ? attn_dkv_kernel<64, 1> : pl.kt == 1 ? attn_dkv_kernel<128, 1> : attn_dkv_kernel<128, 2>;
+  hipLaunchKernelGGL(dq, gq, dim3(AT_THREADS), 0, st, (const bf16_t*)qkv, ld_qkv, (const bf16_t*)o, ld_o,
+                     (const bf16_t*)d_o, ld_do, lse, stats, (bf16_t*)dqkv, ld_dqkv, S, nq, nkv, cos_tab, sin_tab);
+  hipLaunchKernelGGL(dkv, gk, dim3(AT_THREADS), 0, st, (const bf16_t*)qkv, ld_qkv, (const bf16_t*)d_o, ld_do, stats,
+                     (bf16_t*)dqkv, ld_dqkv, S, nq, nkv, ns, part, cos_tab, sin_tab);
   if (ns > 1) {
     const int64_t total = int64_t(2) * b * nkv * S * (d >> 4);
     hipLaunchKernelGGL(gqa_reduce_kernel, dim3(unsigned((total + 255) / 256)), dim3(256), 0, st, part, ns, b, S, d, nq, nkv,

@@ -146,9 +146,9 @@ hipError_t gu_permute(const void* src, int64_t ld_src, void* dst, int64_t ld_dst
 // (rotary already applied); o: [T, q_dim]; lse: natural-log softmax denominators [b, n_q, S] fp32.
 hipError_t attn_fwd(int dt, const void* qkv, int64_t ld_qkv, void* o, int64_t ld_o, float* lse, int b, int S, int nq,
                     int nkv, int d, hipStream_t st);
-// dqkv has the column layout of qkv; delta: workspace [b, n_q, S] fp32 (row sums of do*o); part: workspace of
-// attn_bwd_scratch_floats() floats, or null.  With few KV heads the dK / dV kernels share the query heads of a
-// group out over several workgroups, which leave fp32 partial sums in `part` for a fixed-order reduction; without
+// dqkv has the column layout of qkv; delta: workspace for row statistics, [b, n_q, S] fp32 (sums of do*o), for bf16 storage
+// twice that; part: workspace of attn_bwd_scratch_floats() floats, or null.  With few KV heads the dK / dV kernel shares the
+// query heads of a group out over several workgroups, which leave fp32 partial sums in `part` for a fixed-order reduction; without
 // the workspace one workgroup walks the whole group.  cos_tab, sin_tab ([S][d/2] fp32, bf16 storage only): the q and
 // k parts of dqkv come out turned back by the rotary angle of their position, i.e. as gradients w.r.t. the
 // projection's output; without them they are gradients w.r.t. the rotated q and k.
@@ -167,7 +167,7 @@ hipError_t attn_bwd_f32(const void* qkv, int64_t ld_qkv, const void* o, int64_t 
 hipError_t attn_fwd_bf16(const void* qkv, int64_t ld_qkv, void* o, int64_t ld_o, float* lse, int b, int S, int nq, int nkv,
                          int d, hipStream_t st);
 hipError_t attn_bwd_bf16(const void* qkv, int64_t ld_qkv, const void* o, int64_t ld_o, const float* lse, const void* d_o,
-                         int64_t ld_do, void* dqkv, int64_t ld_dqkv, float* delta, int b, int S, int nq, int nkv, int d,
+                         int64_t ld_do, void* dqkv, int64_t ld_dqkv, float* stats, int b, int S, int nq, int nkv, int d,
                          hipStream_t st, float* part, const float* cos_tab, const float* sin_tab);
 
 }  // namespace mls

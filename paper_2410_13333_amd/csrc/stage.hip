@@ -402,7 +402,7 @@ std::vector<Alloc> allocations(mls_stage* s) {
       {(void**)&s->dh, nmb * s->mb_h, 2},
       {(void**)&s->dc, T * s->ld_qd * s->es, 2},
       {(void**)&s->dqkv, nmb * s->mb_qkv, 2},
-      {(void**)&s->delta, size_t(c.micro_batch) * c.n_q_heads * c.seq * 4, 2},
+      {(void**)&s->delta, size_t(c.micro_batch) * c.n_q_heads * c.seq * (s->dt == mls::DT_BF16 ? 8 : 4), 2},
       {(void**)&s->partial, size_t(nb) * h * 4, 2},
       {(void**)&s->partial2, size_t(nb) * h * 4, 2},
       {(void**)&s->gqa_part, mls::attn_bwd_scratch_floats(s->dt, c.micro_batch, c.seq, c.n_q_heads, c.n_kv_heads, c.head_dim) * 4, 2},

@@ -65,3 +65,46 @@ def test_attention_against_fp64_on_the_same_operands(nq, nkv, d, seq, mb, gain):
         e = np.linalg.norm(dqkv[:, lo:hi] - ref[:, lo:hi]) / max(np.linalg.norm(ref[:, lo:hi]), 0.05 * scale)
         print(f"[attention d={d} S={seq} gain={gain}] {name}: {e:.2e}")
         assert e <= 1.5e-2, (name, e)
+
+
+@pytest.mark.parametrize("nq,nkv,d,seq,mb", [(128, 128, 128, 1000, 1), (104, 104, 128, 1057, 1), (24, 24, 128, 2049, 3),
+                                             (16, 2, 128, 1025, 1), (16, 1, 64, 1000, 2), (48, 4, 128, 40, 3)])
+def test_dk_dv_kernel_forms(nq, nkv, d, seq, mb):
+    """The forms of the dK / dV kernel on their own operands, against fp64: two key tiles per wavefront (many heads, long
+    sequences; a last key block and a last query step that are partly or just filled), query heads of a group in several
+    workgroups."""
+    import torch
+    import paper_2410_13333_amd as mls
+    h = 64
+    st = mls.Stage(h, nq, nkv, d, 64, seq, mb, 1, 1, seed=1003)
+    gen = torch.Generator(device="cuda").manual_seed(seq)
+    x, dy = (torch.randn(mb, seq, h, device="cuda", generator=gen).to(torch.bfloat16) for _ in range(2))
+    y, dx, g = torch.empty_like(x), torch.empty_like(x), torch.zeros(st.grad_elems, device="cuda")
+    st.forward(x, 1, y)
+    qd, kvd, T = nq * d, nkv * d, mb * seq
+    qkv = st.debug_read("qkv").double().cuda().reshape(mb, seq, -1)
+    st.backward(dy, g, 1, dx)
+    dh, dqkv = st.debug_read("dh").double().cuda(), st.debug_read("dqkv").double().cuda().reshape(mb, seq, -1)
+    off, r, c = st.param_layout(0, "w_o")
+    do = (dh.reshape(T, h) @ st.get_params()[off:off + r * c].double().cuda().reshape(r, c).t()).to(torch.bfloat16).double().reshape(mb, seq, qd)
+    st.close()
+    ang = torch.from_numpy(np.ascontiguousarray(O.rope_angles(seq, d, 10000.0))).cuda().double()
+    hidden = torch.ones(seq, seq, dtype=torch.bool, device="cuda").triu(1)
+    for b in range(mb):
+        for hk in range(nkv):
+            k, v = qkv[b, :, qd + hk * d:qd + (hk + 1) * d], qkv[b, :, qd + kvd + hk * d:qd + kvd + (hk + 1) * d]
+            dk, dv = torch.zeros_like(k), torch.zeros_like(v)
+            for hq in range(hk * (nq // nkv), (hk + 1) * (nq // nkv)):
+                q, go = qkv[b, :, hq * d:(hq + 1) * d], do[b, :, hq * d:(hq + 1) * d]
+                p = torch.softmax((q @ k.t() / d ** 0.5).masked_fill(hidden, -float("inf")), dim=-1)
+                dp = go @ v.t()
+                ds = p * (dp - (p * dp).sum(-1, keepdim=True)) / d ** 0.5
+                dk += ds.t() @ q
+                dv += p.t() @ go
+            dk1, dk2 = dk[:, :d // 2], dk[:, d // 2:]
+            dk = torch.cat([dk1 * ang.cos() + dk2 * ang.sin(), dk2 * ang.cos() - dk1 * ang.sin()], dim=1)
+            for name, ref, lo in (("dk", dk, qd), ("dv", dv, qd + kvd)):
+                got = dqkv[b, :, lo + hk * d:lo + (hk + 1) * d]
+                e = ((got - ref).norm() / ref.norm()).item()
+                # P, dS and the result are rounded to bf16 (2^-9 relative each), o and dO enter rounded
+                assert e <= 1e-2, (name, b, hk, e)
