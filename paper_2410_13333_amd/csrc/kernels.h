@@ -113,6 +113,9 @@ hipError_t rmsnorm_bwd(int dt, const void* da, int64_t ld_da, const void* x, int
                        const float* r, const void* dres, int64_t ld_dres, void* dx, int64_t ld_dx, float* dgamma,
                        float* partial, int T, int h, hipStream_t st, bool overwrite = false, bool acc_partial = false,
                        bool reduce = true);
+// the column reduction of one or (partial1 given) two such sequences over the same T in one launch
+hipError_t rmsnorm_bwd_reduce(const float* partial0, float* dgamma0, const float* partial1, float* dgamma1, int T, int h,
+                              hipStream_t st, bool overwrite);
 // rotate the pairs (i, i+d/2) of the first n_heads heads of every row of u [T, ld] by sign*angle(t % S, i)
 hipError_t rope_inplace(int dt, void* u, const float* cos_tab, const float* sin_tab, int T, int S, int n_heads, int d,
                         int64_t ld, float sign, hipStream_t st);

@@ -285,7 +285,7 @@ int layer_backward_data(mls_stage* s, int layer, const char* x, const char* e, i
   LAUNCH(CLS_SWIGLU, mls::swiglu_bwd(s->dt, s->dz, lf, e + L.gu, lg, dgu, lg, T, f, s->st, s->fuse_gu));
   LAUNCH(CLS_GEMM_NT, gemm(s, mls::GEMM_NT, dgu, s->param(layer, s->ioff_wgu), s->dbuf, nullptr, T, h, 2 * f, lg, lg, lh));
   LAUNCH(CLS_NORM, mls::rmsnorm_bwd(s->dt, s->dbuf, lh, e + L.h, lh, s->param(layer, s->ioff_g2), (const float*)(e + L.r2),
-                                    dy, ld_dy, dh, lh, g + s->off_g2, s->partial2, T, h, s->st, ow, !first, last));
+                                    dy, ld_dy, dh, lh, g + s->off_g2, s->partial2, T, h, s->st, ow, !first, false));
   // attention
   LAUNCH(CLS_GEMM_NT, gemm(s, mls::GEMM_NT, dh, s->param(layer, s->ioff_wo), s->dc, nullptr, T, qd, h, lh, lh, lo));
   // the bf16 attention-backward kernels turn dq and dk back by the rotary angle as they store them
@@ -298,7 +298,8 @@ int layer_backward_data(mls_stage* s, int layer, const char* x, const char* e, i
                                        c.head_dim, lq, -1.f, s->st));
   LAUNCH(CLS_GEMM_NT, gemm(s, mls::GEMM_NT, dqkv, s->param(layer, s->ioff_wqkv), s->dbuf, nullptr, T, h, wq, lq, lq, lh));
   LAUNCH(CLS_NORM, mls::rmsnorm_bwd(s->dt, s->dbuf, lh, x, lh, s->param(layer, s->ioff_g1), (const float*)(e + L.r1),
-                                    dh, lh, dx, ld_dx, g + s->off_g1, s->partial, T, h, s->st, ow, !first, last));
+                                    dh, lh, dx, ld_dx, g + s->off_g1, s->partial, T, h, s->st, ow, !first, false));
+  if (last) LAUNCH(CLS_NORM, mls::rmsnorm_bwd_reduce(s->partial, g + s->off_g1, s->partial2, g + s->off_g2, T, h, s->st, ow));
   return MLS_OK;
 }
 
