@@ -12,6 +12,7 @@ constexpr int CUS = 256;
 struct Plan {
   int n1;    // leading columns (a multiple of 256, possibly 0, or all) that run on 256x256 tiles
   int tile;  // T16_*: how the columns from n1 on run
+  double us;
 };
 
 // Estimated microseconds of M x N outputs over a contraction of `it` 64-deep k-tiles, from a fit to stand-alone timings of
@@ -25,39 +26,46 @@ struct Plan {
 // The plan with the smallest estimate is on average 0.4 % slower than the fastest one measured at those shapes; the worst
 // is 12 % (768 x 4096 over 1008: 18 us instead of 16).
 enum { TILE_M16 = -1 };
-double estimate(int tile, int64_t M, int64_t N, int64_t it) {
-  struct Round { int bm, bn; double lo, hi, base; };
-  struct Load { int bm, bn; double lone, c0, c1, base; };
-  const Round r = tile == TILE_M16 ? Round{256, 256, 1.00, 1.38, 7.0}
-                  : tile == mls::T16_256x128 ? Round{256, 128, 0.60, 0.85, 5.5} : Round{128, 128, 0.36, 0.51, 4.5};
+int64_t tiles_of(int tile, int64_t M, int64_t N) {
+  const int bm = tile == mls::T16_64x64 ? 64 : tile == TILE_M16 || tile == mls::T16_256x128 ? 256 : 128;
+  const int bn = tile == TILE_M16 ? 256 : tile == mls::T16_256x128 || tile == mls::T16_128x128 ? 128 : 64;
+  return ((M + bm - 1) / bm) * ((N + bn - 1) / bn);
+}
+double estimate(int tile, int64_t w, int64_t it) {  // w tiles
+  struct Round { double lo, hi, base; };
+  struct Load { double lone, c0, c1, base; };
+  const Round r = tile == TILE_M16 ? Round{1.00, 1.38, 7.0}
+                  : tile == mls::T16_256x128 ? Round{0.60, 0.85, 5.5} : Round{0.36, 0.51, 4.5};
   if (tile == TILE_M16 || tile == mls::T16_256x128 || tile == mls::T16_128x128) {
-    const int64_t w = ((M + r.bm - 1) / r.bm) * ((N + r.bn - 1) / r.bn), full = w / CUS;
+    const int64_t full = w / CUS;
     const double part = double(w % CUS) / CUS;
     return double(full) * (double(it) * r.hi + r.base) + (part > 0 ? double(it) * (r.lo + (r.hi - r.lo) * part) + r.base : 0.0);
   }
-  const Load l = tile == mls::T16_128x64 ? Load{128, 64, 0.26, 0.20, 0.215, 4.0} : Load{64, 64, 0.21, 0.15, 0.165, 3.2};
-  const double load = double(((M + l.bm - 1) / l.bm) * ((N + l.bn - 1) / l.bn)) / CUS;
+  const Load l = tile == mls::T16_128x64 ? Load{0.26, 0.20, 0.215, 4.0} : Load{0.21, 0.15, 0.165, 3.2};
+  const double load = double(w) / CUS;
   return l.base * std::max(1.0, load / 2) + double(it) * std::max(l.lone, l.c0 + l.c1 * load);
 }
+double estimate(int tile, int64_t M, int64_t N, int64_t it) { return estimate(tile, tiles_of(tile, M, N), it); }
 
 Plan plan(int M, int N, int64_t K, bool m16) {
   const int64_t it = (K + 63) / 64, tm = (M + 255) / 256, tn = (N + 255) / 256;
   const int n1 = int(tm * tn / CUS * CUS / tm) * 256;  // columns that whole rounds of 256x256 tiles cover
-  Plan best = {N, mls::T16_256x128};
+  Plan best = {N, mls::T16_256x128, 0};
   double t = m16 ? estimate(TILE_M16, M, N, it) : HUGE_VAL;
   for (int tile : {mls::T16_256x128, mls::T16_128x128, mls::T16_128x64, mls::T16_64x64}) {
     const double all = estimate(tile, M, N, it);
     if (all < t) {
       t = all;
-      best = {0, tile};
+      best = {0, tile, 0};
     }
     if (!m16 || n1 == 0 || n1 >= N) continue;
     const double both = estimate(TILE_M16, M, n1, it) + estimate(tile, M, N - n1, it) + 1.5;  // (and one more launch)
     if (both < t) {
       t = both;
-      best = {n1, tile};
+      best = {n1, tile, 0};
     }
   }
+  best.us = t;
   return best;
 }
 
@@ -97,6 +105,19 @@ mls::T16Problem problem(int form, const void* A, const void* B, void* C, int M, 
   return p;
 }
 
+mls::T16Problem tn_problem(const mls::TnProduct& t, int nseg, int kseg, bool overwrite) {
+  mls::T16Problem p = problem(mls::T16_TN_SEGS, t.A[0], nullptr, t.C, t.M, t.N, kseg, t.lda, t.ldb, t.ldc, uint32_t(int64_t(kseg) * t.lda * 2),
+                              uint32_t(int64_t(kseg) * t.ldb * 2));
+  p.nseg = nseg;
+  for (int i = 0; i < nseg; i++) {
+    p.seg_a[i] = t.A[i];
+    p.seg_b[i] = t.B[i];
+  }
+  p.ldx = overwrite ? 1 : 0;
+  p.xf = t.gu_f;
+  return p;
+}
+
 }  // namespace
 
 namespace mls {
@@ -128,18 +149,46 @@ hipError_t gemm_bf16_tn_segments(const void* const* A, const void* const* B, int
                                  int64_t lda, int64_t ldb, int64_t ldc, hipStream_t st, int gu_f, bool overwrite) {
   if (M == 0 || N == 0 || nseg == 0 || kseg == 0) return hipSuccess;
   if (nseg > 16 || (gu_f > 0 && (gu_f % 32 || N != 2 * gu_f))) return hipErrorInvalidValue;
-  const uint32_t ab = uint32_t(int64_t(kseg) * lda * 2), bb = uint32_t(int64_t(kseg) * ldb * 2);
-  T16Problem p = problem(T16_TN_SEGS, A[0], nullptr, C, M, N, kseg, lda, ldb, ldc, ab, bb);
-  p.nseg = nseg;
-  for (int i = 0; i < nseg; i++) {
-    p.seg_a[i] = A[i];
-    p.seg_b[i] = B[i];
-  }
-  p.ldx = overwrite ? 1 : 0;
-  p.xf = gu_f;
+  const T16Problem p = tn_problem({A, B, C, M, N, lda, ldb, ldc, gu_f}, nseg, kseg, overwrite);
   return run(p, GEMM_TN, st, [&](int n1) {
-    return gemm_m16_tn_segments(A, B, nseg, C, M, n1, kseg, lda, ldb, ldc, ab, bb, st, gu_f, overwrite);
+    return gemm_m16_tn_segments(A, B, nseg, C, M, n1, kseg, lda, ldb, ldc, p.ab, p.bb, st, gu_f, overwrite);
   });
+}
+
+// One launch of one tile size for all of them, or a launch (or two) for each, by the same estimates.  Small layers win the
+// empty last rounds and the launches, large ones keep their whole rounds of 256x256 tiles.  The four weight gradients of a
+// layer, apart -> in one (us): hidden 256, 256 tokens 25 -> 9; 1024 / ffn 2728, 2000 tokens 112 -> 80; 768, 2 x 1024 tokens
+// 80 -> 45; 1536, 700 tokens 125 -> 97 (the fastest tile: 89); 512, 4 x 4096 tokens 387 -> 157; 3072, 600 tokens 422 -> 420;
+// 2048, 2 x 2048 tokens stay apart: 469, in one 517.
+hipError_t gemm_bf16_tn_group(const TnProduct* p, int n, int nseg, int kseg, hipStream_t st, bool overwrite) {
+  if (nseg == 0 || kseg == 0) return hipSuccess;
+  if (n < 1 || n > MAX_T16_GROUP || nseg > 16) return hipErrorInvalidValue;
+  const int64_t depth = int64_t(kseg) * nseg, it = (depth + 63) / 64;
+  T16Problem q[MAX_T16_GROUP];
+  int m = 0;
+  double apart = 0;
+  for (int i = 0; i < n; i++) {
+    if (p[i].gu_f > 0 && (p[i].gu_f % 32 || p[i].N != 2 * p[i].gu_f)) return hipErrorInvalidValue;
+    if (p[i].M == 0 || p[i].N == 0) continue;
+    q[m++] = tn_problem(p[i], nseg, kseg, overwrite);
+    apart += plan(p[i].M, p[i].N, depth, gemm_m16_ok(GEMM_TN, kseg)).us;
+  }
+  if (m == 0) return hipSuccess;
+  int best = -1;
+  for (int tile : {T16_256x128, T16_128x128, T16_128x64, T16_64x64}) {
+    int64_t w = 0;
+    for (int i = 0; i < m; i++) w += tiles_of(tile, q[i].M, q[i].N);
+    const double t = estimate(tile, w, it);
+    if (t < apart) {
+      apart = t;
+      best = tile;
+    }
+  }
+  if (best >= 0) return gemm_t16_group(q, m, best, st);
+  for (int i = 0; i < n; i++)
+    if (hipError_t e = gemm_bf16_tn_segments(p[i].A, p[i].B, nseg, p[i].C, p[i].M, p[i].N, kseg, p[i].lda, p[i].ldb, p[i].ldc, st, p[i].gu_f, overwrite))
+      return e;
+  return hipSuccess;
 }
 
 bool gemm_swiglu_ok(int M, int f, int K, int64_t lda, int64_t ldw) {

@@ -53,11 +53,21 @@ __device__ __forceinline__ void static_for(F&& f) {
   static_for_impl(f, std::make_integer_sequence<int, N>{});
 }
 
-struct SegArgs {
+// The segmented form runs a list of problems in one launch (the weight gradients of a layer, whose tiles alone would each
+// leave most of a last round empty): all over the same pieces, each with operands and a result of its own.
+struct SegProblem {
   const bf16_t* a[MAX_SEGS];
   const bf16_t* b[MAX_SEGS];
-  int nseg;
+  void* C;
+  int64_t lda, ldb, ldc;
+  uint32_t a_bytes, b_bytes;
+  int M, N, col0, xf, tiles_m, tile0;  // tile0: its first tile in the launch
 };
+struct SegArgs {
+  int nseg, n;
+  SegProblem p[mls::MAX_T16_GROUP];
+};
+struct NoSegs {};
 struct RopeArgs {
   const float* cos_tab;
   const float* sin_tab;
@@ -131,18 +141,37 @@ struct Cfg {
 
 template <int WTM, int WTN, int WGM, bool ATR, bool BTR, int EPI, bool SEG, int NS>
 __global__ __launch_bounds__(256, (Cfg<WTM, WTN, WGM, ATR, BTR, EPI, SEG, NS>::PER_CU)) void gemm_t16_kernel(
-    const bf16_t* __restrict__ A, const bf16_t* __restrict__ B, void* __restrict__ Cv, const bf16_t* __restrict__ R, int M,
-    int N, int K, int64_t lda, int64_t ldb, int64_t ldc, int64_t ldr, uint32_t a_bytes, uint32_t b_bytes, int tiles_m,
-    int col0, void* __restrict__ Xv, int64_t ldx, int xf, SegArgs segs, RopeArgs rope) {
+    const bf16_t* __restrict__ A, const bf16_t* __restrict__ B, void* __restrict__ C_, const bf16_t* __restrict__ R, int M_,
+    int N_, int K, int64_t lda_, int64_t ldb_, int64_t ldc_, int64_t ldr, uint32_t a_bytes_, uint32_t b_bytes_, int tiles_m_,
+    int col0_, void* __restrict__ Xv, int64_t ldx, int xf_, std::conditional_t<SEG, SegArgs, NoSegs> segs, RopeArgs rope) {
   using G = Cfg<WTM, WTN, WGM, ATR, BTR, EPI, SEG, NS>;
   constexpr int BM = G::BM, BN = G::BN;
   extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
   // tile of this workgroup: each XCD gets a contiguous run of tiles, walked in groups of about 1024 rows, N fastest
   const int nwg = gridDim.x, pid = blockIdx.x;
   const int xcd = pid & 7, q8 = nwg >> 3, rem = nwg & 7;
-  const int tile = xcd * q8 + (xcd < rem ? xcd : rem) + (pid >> 3);
+  int tile = xcd * q8 + (xcd < rem ? xcd : rem) + (pid >> 3);
+  // the problem it belongs to
+  void* Cv = C_;
+  int M = M_, N = N_, tiles_m = tiles_m_, tiles = nwg, col0 = col0_, xf = xf_, pr = 0;
+  int64_t lda = lda_, ldb = ldb_, ldc = ldc_;
+  uint32_t a_bytes = a_bytes_, b_bytes = b_bytes_;
+  if constexpr (SEG) {
+    while (pr + 1 < segs.n && tile >= segs.p[pr + 1].tile0) pr++;
+    const SegProblem& p = segs.p[pr];
+    Cv = p.C;
+    M = p.M; N = p.N; tiles_m = p.tiles_m; col0 = p.col0; xf = p.xf;
+    lda = p.lda; ldb = p.ldb; ldc = p.ldc;
+    a_bytes = p.a_bytes; b_bytes = p.b_bytes;
+    tiles = (pr + 1 < segs.n ? segs.p[pr + 1].tile0 : nwg) - p.tile0;
+    tile -= p.tile0;
+  }
+  auto piece_a = [&](int i) { if constexpr (SEG) return segs.p[pr].a[i]; else return A; };
+  auto piece_b = [&](int i) { if constexpr (SEG) return segs.p[pr].b[i]; else return B; };
+  int nseg = 1;
+  if constexpr (SEG) nseg = segs.nseg;
   const int gm = min(1024 / BM, tiles_m);
-  const int per_group = gm * (nwg / tiles_m), grp = tile / per_group, first_m = grp * gm;
+  const int per_group = gm * (tiles / tiles_m), grp = tile / per_group, first_m = grp * gm;
   const int gsz = min(tiles_m - first_m, gm), in_grp = tile - grp * per_group;
   const int m0 = (first_m + in_grp % gsz) * BM, n0 = (in_grp / gsz) * BN;
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -180,10 +209,10 @@ __global__ __launch_bounds__(256, (Cfg<WTM, WTN, WGM, ATR, BTR, EPI, SEG, NS>::P
     }
   };
   const int tps = (K + BK - 1) / BK, krem = K - (tps - 1) * BK;  // k-tiles per piece, depth of the last one
-  const int nk = (SEG ? segs.nseg : 1) * tps;
+  const int nk = nseg * tps;
   const uint32_t ka = ATR ? uint32_t(lda * (BK * 2)) : BK * 2, kb = BTR ? uint32_t(ldb * (BK * 2)) : BK * 2;
-  const i32x4 dead_a = make_rsrc(A, 0), dead_b = make_rsrc(B, 0);
-  i32x4 ra = make_rsrc(SEG ? segs.a[0] : A, a_bytes), rb = make_rsrc(SEG ? segs.b[0] : B, b_bytes);
+  const i32x4 dead_a = make_rsrc(piece_a(0), 0), dead_b = make_rsrc(piece_b(0), 0);
+  i32x4 ra = make_rsrc(piece_a(0), a_bytes), rb = make_rsrc(piece_b(0), b_bytes);
   int rq_tile = 0, rq_seg = 0, rq_in = 0;  // request cursor: next k-tile, its piece and its index inside the piece
   set_offsets(tps == 1 ? krem : BK);
   auto request = [&](uint32_t stage, auto DC) {  // request D of this wavefront for the cursor's k-tile
@@ -198,9 +227,9 @@ __global__ __launch_bounds__(256, (Cfg<WTM, WTN, WGM, ATR, BTR, EPI, SEG, NS>::P
     if (SEG && rq_in == tps) {
       rq_in = 0;
       rq_seg++;
-      const int i = rq_seg < segs.nseg ? rq_seg : segs.nseg - 1;
-      ra = make_rsrc(segs.a[i], a_bytes);
-      rb = make_rsrc(segs.b[i], b_bytes);
+      const int i = rq_seg < nseg ? rq_seg : nseg - 1;
+      ra = make_rsrc(piece_a(i), a_bytes);
+      rb = make_rsrc(piece_b(i), b_bytes);
       if (krem < BK && tps > 1) set_offsets(BK);
     }
     if (krem < BK && tps > 1 && rq_in == tps - 1) set_offsets(krem);
@@ -447,9 +476,22 @@ hipError_t launch_t16(const Args& a) {
   auto kern = gemm_t16_kernel<WTM, WTN, WGM, ATR, BTR, EPI, SEG, NS>;
   static std::atomic<uint64_t> lds_raised{0};
   if (hipError_t e = mls::raise_lds_limit(reinterpret_cast<const void*>(kern), G::LDS, lds_raised)) return e;
-  const int tm = (a.M + G::BM - 1) / G::BM, tn = (a.N + G::BN - 1) / G::BN;
-  hipLaunchKernelGGL(kern, dim3(unsigned(tm) * tn), dim3(256), G::LDS, a.st, a.A, a.B, a.C, a.R, a.M, a.N, a.K, a.lda, a.ldb, a.ldc,
-                     a.ldr, a.ab, a.bb, tm, a.col0, a.X, a.ldx, a.xf, a.segs, a.rope);
+  if constexpr (SEG) {
+    SegArgs segs = a.segs;
+    int tiles = 0;
+    for (int i = 0; i < segs.n; i++) {
+      SegProblem& p = segs.p[i];
+      p.tiles_m = (p.M + G::BM - 1) / G::BM;
+      p.tile0 = tiles;
+      tiles += p.tiles_m * ((p.N + G::BN - 1) / G::BN);
+    }
+    hipLaunchKernelGGL(kern, dim3(unsigned(tiles)), dim3(256), G::LDS, a.st, a.A, a.B, a.C, a.R, a.M, a.N, a.K, a.lda, a.ldb, a.ldc, a.ldr,
+                       a.ab, a.bb, 0, a.col0, a.X, a.ldx, a.xf, segs, a.rope);
+  } else {
+    const int tm = (a.M + G::BM - 1) / G::BM, tn = (a.N + G::BN - 1) / G::BN;
+    hipLaunchKernelGGL(kern, dim3(unsigned(tm) * tn), dim3(256), G::LDS, a.st, a.A, a.B, a.C, a.R, a.M, a.N, a.K, a.lda, a.ldb, a.ldc,
+                       a.ldr, a.ab, a.bb, tm, a.col0, a.X, a.ldx, a.xf, NoSegs{}, a.rope);
+  }
   return hipGetLastError();
 }
 
@@ -487,20 +529,41 @@ hipError_t gemm_t16(const T16Problem& p, int tile, hipStream_t st) {
   a.col0 = p.col0;
   a.X = p.X; a.ldx = p.ldx; a.xf = p.xf;
   a.rope = {p.cos_tab, p.sin_tab, p.seq, p.rot_cols, p.head_dim};
-  a.segs.nseg = p.nseg;
-  for (int i = 0; i < p.nseg; i++) {
-    a.segs.a[i] = (const bf16_t*)p.seg_a[i];
-    a.segs.b[i] = (const bf16_t*)p.seg_b[i];
-  }
   switch (p.form) {
     case T16_NN: return run<false, true, E_BF16, false>(tile, a);
     case T16_NT: return run<false, false, E_BF16, false>(tile, a);
     case T16_TN: return run<true, true, E_F32, false>(tile, a);
-    case T16_TN_SEGS: return run<true, true, E_F32, true>(tile, a);
+    case T16_TN_SEGS: return gemm_t16_group(&p, 1, tile, st);
     case T16_NT_SWIGLU: return run<false, false, E_SWIGLU, false>(tile, a);
     case T16_NT_ROPE: return run<false, false, E_ROPE, false>(tile, a);
   }
   return hipErrorInvalidValue;
+}
+
+hipError_t gemm_t16_group(const T16Problem* p, int n, int tile, hipStream_t st) {
+  if (n < 1 || n > MAX_T16_GROUP) return hipErrorInvalidValue;
+  Args a = {};
+  a.K = p[0].K;
+  a.ldx = p[0].ldx;
+  a.st = st;
+  a.segs.nseg = p[0].nseg;
+  a.segs.n = n;
+  for (int i = 0; i < n; i++) {
+    const T16Problem& q = p[i];
+    if (q.form != T16_TN_SEGS || q.K != a.K || q.nseg != a.segs.nseg || q.ldx != a.ldx || q.M <= 0 || q.N <= 0 || q.K <= 0 || q.nseg < 1 ||
+        q.nseg > MAX_SEGS)
+      return hipErrorInvalidValue;
+    SegProblem& g = a.segs.p[i];
+    for (int j = 0; j < q.nseg; j++) {
+      g.a[j] = (const bf16_t*)q.seg_a[j];
+      g.b[j] = (const bf16_t*)q.seg_b[j];
+    }
+    g.C = q.C;
+    g.lda = q.lda; g.ldb = q.ldb; g.ldc = q.ldc;
+    g.a_bytes = q.ab; g.b_bytes = q.bb;
+    g.M = q.M; g.N = q.N; g.col0 = q.col0; g.xf = q.xf;
+  }
+  return run<true, true, E_F32, true>(tile, a);
 }
 
 }  // namespace mls

@@ -44,6 +44,16 @@ bool gemm_tn_segments_ok(int kseg, int64_t lda, int64_t ldb);
 hipError_t gemm_bf16_tn_segments(const void* const* A, const void* const* B, int nseg, void* C, int M, int N, int kseg,
                                  int64_t lda, int64_t ldb, int64_t ldc, hipStream_t st, int gu_f = 0,
                                  bool overwrite = false);
+// several such products over pieces of the same depth, in one launch where their tiles together fill the chip better
+// (n <= MAX_T16_GROUP)
+struct TnProduct {
+  const void *const *A, *const *B;
+  void* C;
+  int M, N;
+  int64_t lda, ldb, ldc;
+  int gu_f;
+};
+hipError_t gemm_bf16_tn_group(const TnProduct* p, int n, int nseg, int kseg, hipStream_t st, bool overwrite);
 // the 256x256 tiles of a problem on the 16x16x32 form of the matrix instruction (gemm_bf16_m16.hip); K % 32 == 0
 // (% 64 for NN and NT)
 bool gemm_m16_ok(int mode, int K);
@@ -80,6 +90,9 @@ struct T16Problem {
   int seq, rot_cols, head_dim;
 };
 hipError_t gemm_t16(const T16Problem& p, int tile, hipStream_t st);
+// up to four T16_TN_SEGS problems over pieces of the same number and depth in one launch
+constexpr int MAX_T16_GROUP = 4;
+hipError_t gemm_t16_group(const T16Problem* p, int n, int tile, hipStream_t st);
 hipError_t fill_zero_f32(float* p, size_t n, hipStream_t st);
 // SwiGLU fused into the gate/up contraction (bf16, f % 32 == 0, DMA path).  Interleaved gate/up column order:
 // 32 gate columns, the 32 up columns of the same indices, and so on (gu_interleaved_col in common.h).

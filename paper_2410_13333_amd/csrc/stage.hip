@@ -303,17 +303,32 @@ int layer_backward_data(mls_stage* s, int layer, const char* x, const char* e, i
   return MLS_OK;
 }
 
-// C[M,N] += sum_i A_i[T,M]^T B_i[T,N] over n micro-batches (fp32 C): one launch per 16 micro-batches on the bf16
-// DMA path, one launch per micro-batch otherwise
-int wgrad(mls_stage* s, const void* const* A, const void* const* B, int n, float* C, int M, int N, int64_t lda,
-          int64_t ldb, int gu_f, bool ow) {
-  if (s->dt == mls::DT_BF16 && mls::gemm_tn_segments_ok(s->T, lda, ldb)) {  // always true when gu_f > 0
-    for (int i = 0; i < n; i += 16)
-      LAUNCH(CLS_GEMM_TN, mls::gemm_bf16_tn_segments(A + i, B + i, n - i < 16 ? n - i : 16, C, M, N, s->T, lda, ldb, N, s->st,
-                                                     gu_f, ow && i == 0));
-  } else {
-    if (ow) HIP_TRY(mls::fill_zero_f32(C, size_t(M) * N, s->st));  // this path only accumulates
-    for (int i = 0; i < n; i++) LAUNCH(CLS_GEMM_TN, gemm(s, mls::GEMM_TN, A[i], B[i], C, nullptr, M, N, s->T, lda, ldb, N));
+// C[M,N] += sum_i A_i[T,M]^T B_i[T,N] over n micro-batches (fp32 C) for the weight gradients of a layer: in steps of 16
+// micro-batches on the bf16 DMA path, one launch per micro-batch and weight otherwise
+int wgrad(mls_stage* s, const mls::TnProduct (&p)[4], int n, bool ow) {
+  bool dma = s->dt == mls::DT_BF16;
+  for (auto& w : p) dma = dma && mls::gemm_tn_segments_ok(s->T, w.lda, w.ldb);  // always true when gu_f > 0
+  if (dma) {
+    for (int i = 0; i < n; i += 16) {
+      mls::TnProduct q[4];
+      for (int j = 0; j < 4; j++) {
+        q[j] = p[j];
+        q[j].A += i;
+        q[j].B += i;
+      }
+      LAUNCH(CLS_GEMM_TN, mls::gemm_bf16_tn_group(q, 4, n - i < 16 ? n - i : 16, s->T, s->st, ow && i == 0));
+    }
+    return MLS_OK;
+  }
+  for (auto& w : p) {
+    if (s->dt == mls::DT_BF16 && mls::gemm_tn_segments_ok(s->T, w.lda, w.ldb)) {
+      for (int i = 0; i < n; i += 16)
+        LAUNCH(CLS_GEMM_TN, mls::gemm_bf16_tn_segments(w.A + i, w.B + i, n - i < 16 ? n - i : 16, w.C, w.M, w.N, s->T, w.lda, w.ldb, w.ldc, s->st,
+                                                       w.gu_f, ow && i == 0));
+      continue;
+    }
+    if (ow) HIP_TRY(mls::fill_zero_f32((float*)w.C, size_t(w.M) * w.N, s->st));  // this path only accumulates
+    for (int i = 0; i < n; i++) LAUNCH(CLS_GEMM_TN, gemm(s, mls::GEMM_TN, w.A[i], w.B[i], w.C, nullptr, w.M, w.N, s->T, w.lda, w.ldb, w.ldc));
   }
   return MLS_OK;
 }
@@ -564,10 +579,13 @@ int mls_stage_backward_ex(mls_stage* s, const void* dY, float* grads, int32_t n,
       bdqkv.push_back(s->dqkv + size_t(i) * s->mb_qkv);
     }
     const int m = (int)az.size();
-    if (int rc = wgrad(s, az.data(), bdy.data(), m, g + s->off_wd, f, h, s->ld_f, s->ld_h, 0, ow)) return rc;
-    if (int rc = wgrad(s, ab.data(), bdgu.data(), m, g + s->off_wgu, h, 2 * f, s->ld_h, s->ld_gu, s->fuse_gu ? f : 0, ow)) return rc;
-    if (int rc = wgrad(s, ao.data(), bdh.data(), m, g + s->off_wo, s->qd, h, s->ld_qd, s->ld_h, 0, ow)) return rc;
-    if (int rc = wgrad(s, aa.data(), bdqkv.data(), m, g + s->off_wqkv, h, s->qkvw, s->ld_h, s->ld_qkv, 0, ow)) return rc;
+    const mls::TnProduct w[4] = {
+        {az.data(), bdy.data(), g + s->off_wd, f, h, s->ld_f, s->ld_h, h, 0},
+        {ab.data(), bdgu.data(), g + s->off_wgu, h, 2 * f, s->ld_h, s->ld_gu, 2 * int64_t(f), s->fuse_gu ? f : 0},
+        {ao.data(), bdh.data(), g + s->off_wo, s->qd, h, s->ld_qd, s->ld_h, h, 0},
+        {aa.data(), bdqkv.data(), g + s->off_wqkv, h, s->qkvw, s->ld_h, s->ld_qkv, s->qkvw, 0},
+    };
+    if (int rc = wgrad(s, w, m, ow)) return rc;
   }
   // overwrite mode: the layers no entry of this call reached hold no gradient
   if (ow && kmax < c.max_layers)

@@ -376,3 +376,30 @@ def test_fused_epilogues_on_mid_size_tiles(nq, nkv, d, ffn, seq, mb):
     sh = synth.StageShape(hidden=264, n_q_heads=nq, n_kv_heads=nkv, head_dim=d, ffn=ffn, seq=seq, micro_batch=mb, layers=1,
                           microbatches=1)
     _check(sh, [1], 1e-2)
+
+
+@pytest.mark.parametrize("hidden,nq,nkv,d,ffn,seq,mb,n", [(264, 3, 1, 64, 680, 129, 1, 1), (1032, 16, 4, 64, 2728, 999, 2, 1),
+                                                          (1544, 24, 8, 64, 4104, 700, 1, 2), (520, 4, 4, 128, 1056, 2050, 2, 2)])
+def test_weight_gradients_of_a_layer_in_one_launch(hidden, nq, nkv, d, ffn, seq, mb, n):
+    """Layers whose four weight gradients share a launch, on each of its tile sizes with ragged edges: every matrix against
+    fp64 on the captured operands, added to what the gradient vector held."""
+    import torch
+    import paper_2410_13333_amd as mls
+    st = mls.Stage(hidden, nq, nkv, d, ffn, seq, mb, 1, n, seed=1004)
+    gen = torch.Generator(device="cuda").manual_seed(ffn)
+    x, dy = (torch.randn(n, mb, seq, hidden, device="cuda", generator=gen).to(torch.bfloat16) for _ in range(2))
+    y, dx = torch.empty_like(x[0]), torch.empty_like(dy)
+    g0 = torch.randn(st.grad_elems, device="cuda", generator=gen)
+    g = g0.clone()
+    for i in range(n):
+        st.forward(x[i], 1, y)
+    pairs = {"w_d": ("z", "dy"), "w_gu": ("b", "dgu"), "w_o": ("o", "dh"), "w_qkv": ("a", "dqkv")}
+    left = {w: [st.debug_read(a, slot=i).double() for i in range(n)] for w, (a, _) in pairs.items()}
+    st.backward(dy, g, n, dx)
+    for w, (_, b) in pairs.items():
+        off, r, c = st.param_layout(0, w)
+        ref = sum(left[w][i].t().contiguous() @ st.debug_read(b, slot=i).double() for i in range(n))
+        got = (g[off:off + r * c].double() - g0[off:off + r * c].double()).reshape(r, c)
+        e = ((got - ref).norm() / ref.norm()).item()
+        assert e <= 1e-5, (w, e)  # fp32 sums over at most 8200 products, fp32 rounding of the sum with g0
+    st.close()
