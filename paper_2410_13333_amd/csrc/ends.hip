@@ -200,7 +200,9 @@ __global__ __launch_bounds__(1024) void mean_kernel(const float* __restrict__ v,
 
 inline int blocks_for(int64_t n) { return int((n + TH - 1) / TH); }
 size_t align256(size_t v) { return (v + 255) & ~size_t(255); }
-int64_t padded(int64_t n) { return n % 256 == 0 ? n + 64 : n; }
+// Row strides as in a stage: the columns from n on, up to whole 64-deep k-tiles, are zero and may be contracted over.
+int64_t depth64(int64_t n) { return (n + 63) / 64 * 64; }
+int64_t padded(int64_t n) { return depth64(n) % 256 == 0 ? depth64(n) + 64 : depth64(n); }
 
 }  // namespace
 
@@ -349,6 +351,15 @@ int mls_ends_init(const mls_ends_config* cfg, uint64_t seed, void* hip_stream, m
     release(s);
     return fail_hip(e, "hipMalloc");
   }
+  if (s->dt == mls::DT_BF16 && (h % 64 || V % 64)) {
+    if ((e = hipMemsetAsync(s->wlm, 0, h * s->ld_v * s->es, s->st)) != hipSuccess ||
+        (e = hipMemsetAsync(s->wlm_t, 0, V * s->ld_h * s->es, s->st)) != hipSuccess ||
+        (e = hipMemsetAsync(s->nrm, 0, nmb * s->mb_h, s->st)) != hipSuccess ||
+        (e = hipMemsetAsync(s->dlog, 0, nmb * s->mb_v, s->st)) != hipSuccess) {
+      release(s);
+      return fail_hip(e, "hipMemsetAsync");
+    }
+  }
   PT t[3];
   param_tensors(s, t);
   for (auto& q : t)
@@ -435,7 +446,7 @@ static int head_forward(mls_ends* s, const void* y, const int32_t* targets, floa
   float* r = s->r + size_t(slot) * T;
   HIP_TRY(copy2d(s, ys, s->ld_h, y, h, T, h));
   HIP_TRY(mls::rmsnorm_fwd(s->dt, ys, s->ld_h, s->gamma, nr, s->ld_h, r, T, h, s->c.rms_eps, s->st));
-  if (s->wlm_t) HIP_TRY(gemm(s, mls::GEMM_NT, nr, s->wlm_t, dl, T, V, h, s->ld_h, s->ld_h, s->ld_v));
+  if (s->wlm_t) HIP_TRY(gemm(s, mls::GEMM_NT, nr, s->wlm_t, dl, T, V, int(depth64(h)), s->ld_h, s->ld_h, s->ld_v));
   else HIP_TRY(gemm(s, mls::GEMM_NN, nr, s->wlm, dl, T, V, h, s->ld_h, s->ld_v, s->ld_v));
   const float scale = loss_weight / (float)T;
   if (s->dt == mls::DT_BF16)
@@ -482,7 +493,7 @@ int mls_head_backward(mls_ends* s, float* grads, int32_t n, void* dY) {
     const char* dl = s->dlog + size_t(slot) * s->mb_v;
     const float* r = s->r + size_t(slot) * T;
     // d nrm = dlogits w_lm^T; then the RMSNorm backward straight into the caller's dY
-    HIP_TRY(gemm(s, mls::GEMM_NT, dl, s->wlm, s->dn, T, h, V, s->ld_v, s->ld_v, s->ld_h));
+    HIP_TRY(gemm(s, mls::GEMM_NT, dl, s->wlm, s->dn, T, h, s->dt == mls::DT_BF16 ? int(depth64(V)) : V, s->ld_v, s->ld_v, s->ld_h));
     HIP_TRY(mls::rmsnorm_bwd(s->dt, s->dn, s->ld_h, ys, s->ld_h, s->gamma, r, nullptr, 0, (char*)dY + size_t(i) * act, h,
                              grads + s->off_g, s->partial, T, h, s->st));
     an.push_back(nr);

@@ -304,3 +304,35 @@ def test_embedding_gradient_of_crowded_rows(dtype, hidden, vocab, seq, kind):
     # a running fp32 sum of 4500 terms: well under 4500 * 2^-24 relative
     assert rel_err(g[:vocab * hidden].reshape(vocab, hidden), ref) <= 1e-5
     assert (g[vocab * hidden:] == 0.25).all()
+
+
+@pytest.mark.parametrize("h,V", [(264, 1032), (328, 520), (1000, 2056)])
+def test_widths_that_are_no_multiples_of_a_k_tile(h, V):
+    """Head forward and backward over rows padded to whole 64-deep k-tiles, against fp64; a second pass over reused buffers
+    gives the same bits."""
+    import torch
+    import paper_2410_13333_amd as mls
+    S = 77
+    en = mls.Ends(h, V, S, 1, 2, 1e-5, "bf16", seed=11)
+    gen = torch.Generator(device="cuda").manual_seed(h)
+    y = [torch.randn(1, S, h, device="cuda", generator=gen).to(torch.bfloat16) for _ in range(2)]
+    t = [torch.randint(0, V, (1, S), device="cuda", generator=gen, dtype=torch.int32) for _ in range(2)]
+    p = en.get_params().double()
+    gamma, w = p[V * h:V * h + h], p[V * h + h:].reshape(h, V)
+    out = []
+    for _ in range(2):
+        loss, g = torch.zeros(2, device="cuda"), torch.zeros(en.grad_elems, device="cuda")
+        dy = torch.empty(2, 1, S, h, device="cuda", dtype=torch.bfloat16)
+        for i in range(2):
+            en.head_forward(y[i], t[i], 0.5, loss[i:i + 1])
+        en.head_backward(g, 2, dy)
+        out.append((loss, g, dy))
+    assert all(torch.equal(a, b) for a, b in zip(*out))
+    for i in range(2):
+        x = y[i].reshape(S, h).double().requires_grad_()
+        z = (x * torch.rsqrt((x * x).mean(-1, keepdim=True) + 1e-5) * gamma) @ w
+        ref = torch.nn.functional.cross_entropy(z, t[i].reshape(-1).long(), reduction="sum") / (2 * S)
+        ref.backward()
+        e = ((dy[i].reshape(S, h).double() - x.grad).norm() / x.grad.norm()).item()
+        assert e <= 1e-2, e  # bf16 operands and result
+    en.close()
