@@ -53,7 +53,6 @@ constexpr uint32_t OOB = 0x80000000u;
 constexpr int AT_THREADS = 256;
 constexpr int TR = 64;  // rows of an LDS tile
 constexpr float LOG2E = 1.4426950408889634f, LN2 = 0.6931471805599453f;
-constexpr float SLACK = 8.f;
 
 // element offset of (row, col) inside a swizzled 64 x D tile
 template <int D>
@@ -285,9 +284,9 @@ __device__ __forceinline__ void store_t_unrotate(bf16_t* __restrict__ out, int64
 // 16 MFMAs of S(s+1) = K Q^T and of O += V^T P(s-1), neither of which needs the softmax of S(s) whose vector
 // instructions go out in between (about five fit behind one MFMA).  K runs one 64-row block ahead of V: both are
 // double-buffered and one barrier per block frees the buffers of K(u-1) and V(u-2).
-// Measured (us, before -> after): 4096 positions, 32 heads of 128: 177 -> 160; 2048, 16 of 128 (one workgroup per CU, where
-// the chain is everything): 62 -> 45; 4096, 16 of 128: 123 -> 95; 4096, 16 of 64: 90 -> 64.  With every CU full the vector
-// instructions and the MFMAs of a SIMD take about 300 000 of the 335 000 cycles one after the other.
+// Measured (us, unpipelined -> this): 4096 positions, 32 heads of 128: 163 -> 166; 2048, 16 of 128 (one workgroup per CU,
+// where the chain is everything): 60 -> 48.5; 4096, 16 of 128: 116 -> 102; 4096, 16 of 64: 84 -> 63.  With every CU full the
+// vector instructions and the MFMAs of a SIMD take about nine tenths of the cycles one after the other.
 template <int D>
 __global__ __launch_bounds__(AT_THREADS, 2) void attn_fwd_kernel(const bf16_t* __restrict__ qkv, int64_t ld, bf16_t* __restrict__ o, int64_t ldo,
                                                                  float* __restrict__ lse, int S, int nq, int nkv) {
@@ -359,11 +358,11 @@ __global__ __launch_bounds__(AT_THREADS, 2) void attn_fwd_kernel(const bf16_t* _
         mx = fmaxf(mx, st[e]);
       }
       mx = max_halves(mx);
-      // The reference of the exponents only has to be near the row's maximum: it moves when the maximum passes it by more
-      // than SLACK (probabilities then reach 2^SLACK times their scale, which changes nothing of their relative precision).
-      // Moved with every new maximum, some row of the 32 moved in about half of all steps, and a move costs 64 products.
-      const float top = mx * sc;
-      mn = top > m + SLACK ? top : m;  // finite: sub-block 0 always holds j = 0 <= i
+      // The reference of the exponents is the row's maximum itself, as far as it is known, so that the largest probability of a
+      // row is 1 and stays exact when P is rounded to bf16.  A reference that only follows when the maximum has passed it by a
+      // margin saves most of the rescaling below (some row of the 32 moves in about half of all steps), but then the row's
+      // largest term carries a rounding error of 2^-9 like the others: on rows that look at few keys that is most of the error.
+      mn = fmaxf(m, mx * sc);  // finite: sub-block 0 always holds j = 0 <= i
       float ps = 0.f;
 #pragma unroll
       for (int e = 0; e < 16; e++) {
