@@ -702,8 +702,8 @@ __global__ __launch_bounds__(AT_THREADS, 1) void attn_dkv_kernel(const bf16_t* _
   };
   // Products that take fragment i (with V in LDS a dP product goes with the V fragment).  S and dP are products in asm that
   // leave their results in VGPRs (the compiler would put them beside dK and dV into AGPRs and copy them back and forth);
-  // their first reader stays three products (96 cycles) behind the last one that wrote them, which the fixed order below
-  // sees to.
+  // their first reader stays three products (96 cycles; two would do) behind the last one that wrote them, which the fixed
+  // order below sees to: the compiler may move nothing across a product.
   f32x16 st[KT], dp[KT];
   // dP starts from -delta.
   auto mul = [&](f32x16& c, const bf16x8& x, const bf16x8& y, auto ZERO) {
@@ -739,6 +739,7 @@ __global__ __launch_bounds__(AT_THREADS, 1) void attn_dkv_kernel(const bf16_t* _
       constexpr int i = lo + decltype(IC)::value;
       if constexpr (i + FA < end) read(std::integral_constant<int, i + FA>{});
       use(std::integral_constant<int, i>{});
+      __builtin_amdgcn_sched_barrier(0);  // no vector instruction of this group ahead of its products
       between(std::integral_constant<int, i>{});
       __builtin_amdgcn_sched_barrier(0);
     });

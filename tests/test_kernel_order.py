@@ -1,0 +1,105 @@
+"""Products written as asm, whose results the compiler takes to be there at once: in the assembly of the kernels as built,
+every other instruction that touches such a result lies far enough behind the product that wrote it (no GPU)."""
+import os
+import re
+import shutil
+import subprocess
+
+import pytest
+
+from paper_2410_13333_amd import build as B
+
+PRODUCT = 8   # wait states of a 32x32x16 product (8 passes)
+NEEDED = 24   # three products; the hardware asks for 11 wait states
+
+
+def _regs(op):
+    m = re.match(r"v\[(\d+):(\d+)\]$", op)
+    if m:
+        return range(int(m[1]), int(m[2]) + 1)
+    m = re.match(r"v(\d+)$", op)
+    return [int(m[1])] if m else []
+
+
+def _blocks(lines):
+    """Basic blocks of a kernel: lists of (mnemonic, operands, written as asm), and the successors of each."""
+    blocks, names, asm = [[]], {}, False
+    for line in lines:
+        asm = (asm or "ASMSTART" in line) and "ASMEND" not in line
+        t = line.split(";")[0].strip()
+        if re.match(r"\.?L?\w*:$", t) and t.startswith(".L"):
+            blocks.append([])
+            names[t[:-1]] = len(blocks) - 1
+        elif t and not t.startswith(".") and not t.endswith(":"):
+            p = t.replace(",", " ").split()
+            blocks[-1].append((p[0], p[1:], asm))
+            if p[0].startswith(("s_branch", "s_cbranch", "s_endpgm")):
+                blocks.append([])
+    succ = []
+    for i, b in enumerate(blocks):
+        last = b[-1] if b else ("", [], False)
+        s = [names[last[1][-1]]] if last[0].startswith(("s_branch", "s_cbranch")) else []
+        if not last[0].startswith(("s_branch", "s_endpgm")) and i + 1 < len(blocks):
+            s.append(i + 1)
+        succ.append(s)
+    return blocks, succ
+
+
+def shortest_distances(lines):
+    """Per kernel: the smallest number of wait states, over all paths, between an asm product into VGPRs and the first
+    instruction that is no product and reads or writes them; only products and s_nop are counted."""
+    blocks, succ = _blocks(lines)
+    entry = [None] * len(blocks)
+    entry[0] = {}
+    work, least, seen = [0], 10 ** 6, 0
+    while work:
+        i = work.pop()
+        state = dict(entry[i])
+        for op, args, asm in blocks[i]:
+            if op.startswith("v_mfma"):
+                state = {r: d + PRODUCT for r, d in state.items() if d + PRODUCT < 8 * NEEDED}
+                if asm and args[0].startswith("v"):
+                    seen += 1
+                    state.update((r, 0) for r in _regs(args[0]))
+            elif op == "s_nop":
+                state = {r: d + int(args[0]) + 1 for r, d in state.items()}
+            elif op.startswith(("v_", "ds_", "buffer_", "global_")):
+                for r in {r for a in args for r in _regs(a)}:
+                    least = min(least, state.pop(r, 10 ** 6))
+        for j in succ[i]:
+            if entry[j] is None:
+                entry[j] = state
+                work.append(j)
+            else:
+                merged = {r: min(entry[j].get(r, 10 ** 6), state.get(r, 10 ** 6)) for r in {*entry[j], *state}}
+                if merged != entry[j]:
+                    entry[j] = merged
+                    work.append(j)
+    return least, seen
+
+
+@pytest.fixture(scope="module")
+def attention_asm(tmp_path_factory):
+    if not shutil.which("hipcc"):
+        pytest.skip("no hipcc")
+    out = tmp_path_factory.mktemp("asm") / "attention.s"
+    subprocess.run(["hipcc", *B.FLAGS, "-w", "--offload-device-only", "-S", os.path.join(B.CSRC, "attention_bf16.hip"), "-o", str(out)],
+                   check=True, capture_output=True)
+    kernels, cur = {}, None
+    for line in out.read_text().splitlines():
+        m = re.match(r"(_Z\w+):", line)
+        if m:
+            cur = kernels.setdefault(m[1], [])
+        elif line.startswith(".Lfunc_end"):
+            cur = None
+        elif cur is not None:
+            cur.append(line)
+    return kernels
+
+
+@pytest.mark.parametrize("form", ["ILi64ELi1E", "ILi128ELi1E", "ILi128ELi2E"])
+def test_first_reader_of_an_asm_product(attention_asm, form):
+    (lines,) = [v for k, v in attention_asm.items() if "attn_dkv_kernel" + form in k]
+    least, seen = shortest_distances(lines)
+    assert seen >= 8  # the kernel has such products
+    assert NEEDED <= least < 10 ** 6, least
