@@ -751,8 +751,8 @@ __global__ __launch_bounds__(AT_THREADS, 1) void attn_dkv_kernel(const bf16_t* _
   using I3 = std::integral_constant<int, R3>;
   using I4 = std::integral_constant<int, R3 + FA>;
 
-  int slot = 0, i0 = (q0 + nst - 1) * 32;  // of this step
-  uint32_t adv = 0;                        // from the previous step's slot to this one's
+  int slot = 0;
+  uint32_t adv = 0;  // from the previous step's slot to this one's
 #pragma unroll
   for (int kt = 0; kt < KT; kt++)  // the compiler's own wait for the K (and V) fragments, here and not in the loop
 #pragma unroll
@@ -763,90 +763,115 @@ __global__ __launch_bounds__(AT_THREADS, 1) void attn_dkv_kernel(const bf16_t* _
   wait_vm<2 * NREQ>();
   __builtin_amdgcn_s_barrier();
   asm volatile("" ::: "memory");
-  static_for<FA>(read);
-  for (int it = 0; it < niter; it++) {
-    // ---- S(it)
-    constexpr int Q1 = R1 / 4;
-    run(I0{}, std::integral_constant<int, Q1>{}, I3{}, none);
-    wait_vm<NREQ>();
-    __builtin_amdgcn_s_barrier();
-    asm volatile("" ::: "memory");
-    issue_q();
-    run(std::integral_constant<int, Q1>{}, std::integral_constant<int, 2 * Q1>{}, I3{}, none);
-    issue_d();
-    run(std::integral_constant<int, 2 * Q1>{}, std::integral_constant<int, 3 * Q1>{}, I3{}, none);
-    issue_s();
-    f32x4 ls[4];  // lse log2(e) of 4 rows each: read one group ahead of use
-    ls[0] = *(const MLS_LDS f32x4*)(sa);
-#pragma unroll
-    for (int kt = 0; kt < KT; kt++) {
-      uint32_t da = sa;
-      asm volatile("" : "+v"(da));  // read again for each key tile: copies would be vector instructions
-#pragma unroll
-      for (int g = 0; g < 4; g++) {
-        const f32x4 v = *(const MLS_LDS f32x4*)(da + 256 + g * 32);
-#pragma unroll
-        for (int r = 0; r < 4; r++) dp[kt][g * 4 + r] = v[r];
-      }
-    }
-    run(std::integral_constant<int, 3 * Q1>{}, I1{}, I3{}, none);
-    // ---- dP(it); P(it) = exp2(sc S - L2)
-    run(I1{}, I2{}, I3{}, [&](auto IC) {
-      constexpr int n = R2 - R1, i = decltype(IC)::value - R1, b0 = VL ? 4 : KT == 1 ? 2 : 1;  // three products behind S
-      if constexpr (i >= b0) {
-        constexpr int lo = (i - b0) * 16 * KT / (n - b0), hi = (i - b0 + 1) * 16 * KT / (n - b0);
-        static_for<hi - lo>([&](auto EC) {
-          constexpr int x = lo + decltype(EC)::value, g = x / (4 * KT), kt = x / 4 % KT, e = g * 4 + x % 4;
-          if constexpr (x % (4 * KT) == 0 && g < 3) ls[g + 1] = *(const MLS_LDS f32x4*)(sa + (g + 1) * 32);
-          st[kt][e] = __builtin_amdgcn_exp2f(st[kt][e] * sc - ls[g][x % 4]);
-        });
-      }
-    });
-    if (i0 < jw + KR - 1 || i0 + 32 > S) {  // wave-uniform: some pair is masked, or the step runs past the last row
+  // The last `dead` steps of a head have no row that sees a key of this wavefront.  They pass it by: their probabilities are
+  // zeros, which would take nothing from a finite row of Q or dO, but make NaN of one with an infinity in it.
+  const int dead = min(nst, (jw - j0) / 32), alive = nst - dead;
+  for (int hd = 0; hd < grp; hd++) {
+    int i0 = (q0 + nst - 1) * 32;  // of this step
+    static_for<FA>(read);
+    for (int it = 0; it < alive; it++) {
+      // ---- S(it)
+      constexpr int Q1 = R1 / 4;
+      run(I0{}, std::integral_constant<int, Q1>{}, I3{}, none);
+      wait_vm<NREQ>();
+      __builtin_amdgcn_s_barrier();
+      asm volatile("" ::: "memory");
+      issue_q();
+      run(std::integral_constant<int, Q1>{}, std::integral_constant<int, 2 * Q1>{}, I3{}, none);
+      issue_d();
+      run(std::integral_constant<int, 2 * Q1>{}, std::integral_constant<int, 3 * Q1>{}, I3{}, none);
+      issue_s();
+      f32x4 ls[4];  // lse log2(e) of 4 rows each: read one group ahead of use
+      ls[0] = *(const MLS_LDS f32x4*)(sa);
 #pragma unroll
       for (int kt = 0; kt < KT; kt++) {
-        const int c = jw + kt * 32 + (lane & 31) - i0 - half * 4, z = S - i0 - half * 4;
+        uint32_t da = sa;
+        asm volatile("" : "+v"(da));  // read again for each key tile: copies would be vector instructions
 #pragma unroll
-        for (int e = 0; e < 16; e++) {
-          const int r = 8 * (e >> 2) + (e & 3);
-          if (r < c || r >= z) st[kt][e] = 0.f;
+        for (int g = 0; g < 4; g++) {
+          const f32x4 v = *(const MLS_LDS f32x4*)(da + 256 + g * 32);
+#pragma unroll
+          for (int r = 0; r < 4; r++) dp[kt][g * 4 + r] = v[r];
         }
       }
-    }
-    __builtin_amdgcn_sched_barrier(0);
-    // ---- dV, dK of step it-1; dS(it) = P dP, which has delta taken off
-    const uint32_t next = slot == SLOTS - 1 ? 0u - (SLOTS - 1) * STG : STG;
-    ra += next;
-    run(I2{}, I3{}, I4{}, [&](auto IC) {
-      constexpr int n = R3 - R2, i = decltype(IC)::value - R2, b0 = 2;  // three products and more behind dP
-      if constexpr (i >= b0) {
-        constexpr int lo = (i - b0) * 16 * KT / (n - b0), hi = (i - b0 + 1) * 16 * KT / (n - b0);
-        static_for<hi - lo>([&](auto EC) {
-          constexpr int x = lo + decltype(EC)::value, g = x / (4 * KT), kt = x / 4 % KT, e = g * 4 + x % 4;
-          dp[kt][e] *= st[kt][e];
-          if constexpr (e == 7) {  // the products with the previous step's first halves have been issued
-            static_assert(i >= n / 2 - 1);
-            pf[kt][0] = acc_to_b(st[kt], 0);
-            df[kt][0] = acc_to_b(dp[kt], 0);
-          }
-        });
-      }
-    });
+      run(std::integral_constant<int, 3 * Q1>{}, I1{}, I3{}, none);
+      // ---- dP(it); P(it) = exp2(sc S - L2)
+      run(I1{}, I2{}, I3{}, [&](auto IC) {
+        constexpr int n = R2 - R1, i = decltype(IC)::value - R1, b0 = VL ? 4 : KT == 1 ? 2 : 1;  // three products behind S
+        if constexpr (i >= b0) {
+          constexpr int lo = (i - b0) * 16 * KT / (n - b0), hi = (i - b0 + 1) * 16 * KT / (n - b0);
+          static_for<hi - lo>([&](auto EC) {
+            constexpr int x = lo + decltype(EC)::value, g = x / (4 * KT), kt = x / 4 % KT, e = g * 4 + x % 4;
+            if constexpr (x % (4 * KT) == 0 && g < 3) ls[g + 1] = *(const MLS_LDS f32x4*)(sa + (g + 1) * 32);
+            st[kt][e] = __builtin_amdgcn_exp2f(st[kt][e] * sc - ls[g][x % 4]);
+          });
+        }
+      });
+      if (i0 < jw + KR - 1 || i0 + 32 > S) {  // wave-uniform: some pair is masked, or the step runs past the last row
 #pragma unroll
-    for (int kt = 0; kt < KT; kt++) {
-      pf[kt][1] = acc_to_b(st[kt], 1);
-      df[kt][1] = acc_to_b(dp[kt], 1);
+        for (int kt = 0; kt < KT; kt++) {
+          const int c = jw + kt * 32 + (lane & 31) - i0 - half * 4, z = S - i0 - half * 4;
+#pragma unroll
+          for (int e = 0; e < 16; e++) {
+            const int r = 8 * (e >> 2) + (e & 3);
+            if (r < c || r >= z) st[kt][e] = 0.f;
+          }
+        }
+      }
+      __builtin_amdgcn_sched_barrier(0);
+      // ---- dV, dK of step it-1; dS(it) = P dP, which has delta taken off
+      const uint32_t next = slot == SLOTS - 1 ? 0u - (SLOTS - 1) * STG : STG;
+      ra += next;
+      run(I2{}, I3{}, I4{}, [&](auto IC) {
+        constexpr int n = R3 - R2, i = decltype(IC)::value - R2, b0 = 2;  // three products and more behind dP
+        if constexpr (i >= b0) {
+          constexpr int lo = (i - b0) * 16 * KT / (n - b0), hi = (i - b0 + 1) * 16 * KT / (n - b0);
+          static_for<hi - lo>([&](auto EC) {
+            constexpr int x = lo + decltype(EC)::value, g = x / (4 * KT), kt = x / 4 % KT, e = g * 4 + x % 4;
+            dp[kt][e] *= st[kt][e];
+            if constexpr (e == 7) {  // the products with the previous step's first halves have been issued
+              static_assert(i >= n / 2 - 1);
+              pf[kt][0] = acc_to_b(st[kt], 0);
+              df[kt][0] = acc_to_b(dp[kt], 0);
+            }
+          });
+        }
+      });
+#pragma unroll
+      for (int kt = 0; kt < KT; kt++) {
+        pf[kt][1] = acc_to_b(st[kt], 1);
+        df[kt][1] = acc_to_b(dp[kt], 1);
+      }
+      static_for<FA>([&](auto IC) { f[decltype(IC)::value] = f[R3 + decltype(IC)::value]; });
+      ca += adv;  // the columns move on to this step's slot (in a head's first step, which has no predecessor, they were there already)
+      sa += next;
+      adv = next;
+      slot = slot == SLOTS - 1 ? 0 : slot + 1;
+      i0 -= 32;
+      __builtin_amdgcn_sched_barrier(0);
     }
-    static_for<FA>([&](auto IC) { f[decltype(IC)::value] = f[R3 + decltype(IC)::value]; });
-    ca += adv;  // the columns move on to this step's slot (in the first step, which has no predecessor, they were there already)
-    sa += next;
-    adv = next;
-    slot = slot == SLOTS - 1 ? 0 : slot + 1;
-    i0 = i0 == q0 * 32 ? (q0 + nst - 1) * 32 : i0 - 32;
-    __builtin_amdgcn_sched_barrier(0);
+    // the products of the last step
+    static_for<FA>([&](auto IC) { read(std::integral_constant<int, R2 + decltype(IC)::value>{}); });
+    run(I2{}, I3{}, I3{}, none);
+#pragma unroll
+    for (int kt = 0; kt < KT; kt++) pf[kt][0] = pf[kt][1] = df[kt][0] = df[kt][1] = bf16x8{};
+    for (int it = 0; it < dead; it++) {
+      wait_vm<NREQ>();
+      __builtin_amdgcn_s_barrier();
+      asm volatile("" ::: "memory");
+      issue_q();
+      issue_d();
+      issue_s();
+      const uint32_t next = slot == SLOTS - 1 ? 0u - (SLOTS - 1) * STG : STG;
+      ra += next;
+      ca += adv;
+      sa += next;
+      adv = next;
+      slot = slot == SLOTS - 1 ? 0 : slot + 1;
+    }
+    ca += adv;  // to the next head's first step
+    adv = 0;
   }
-  static_for<FA>([&](auto IC) { read(std::integral_constant<int, R2 + decltype(IC)::value>{}); });
-  run(I2{}, I3{}, I3{}, none);
   wait_dma();
 
 #pragma unroll

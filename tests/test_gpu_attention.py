@@ -102,11 +102,12 @@ def test_the_largest_probability_of_a_row_is_not_rounded(nq, nkv, d, seq, gain):
 
 
 @pytest.mark.parametrize("nq,nkv,d,seq,mb", [(128, 128, 128, 1000, 1), (104, 104, 128, 1057, 1), (24, 24, 128, 2049, 3),
-                                             (16, 2, 128, 1025, 1), (16, 1, 64, 1000, 2), (48, 4, 128, 40, 3)])
+                                             (16, 2, 128, 1025, 1), (16, 1, 64, 1000, 2), (48, 4, 128, 40, 3),
+                                             (128, 64, 128, 1000, 2), (96, 32, 128, 600, 2), (32, 16, 64, 200, 2)])
 def test_dk_dv_kernel_forms(nq, nkv, d, seq, mb):
     """The forms of the dK / dV kernel on their own operands, against fp64: two key tiles per wavefront (many heads, long
     sequences; a last key block and a last query step that are partly or just filled), query heads of a group in several
-    workgroups."""
+    workgroups, several heads of a group one after the other in one."""
     import torch
     import paper_2410_13333_amd as mls
     h = 64
@@ -142,3 +143,28 @@ def test_dk_dv_kernel_forms(nq, nkv, d, seq, mb):
                 e = ((got - ref).norm() / ref.norm()).item()
                 # P, dS and the result are rounded to bf16 (2^-9 relative each), o and dO enter rounded
                 assert e <= 1e-2, (name, b, hk, e)
+
+
+@pytest.mark.parametrize("at", [0, 261])
+@pytest.mark.parametrize("nq,nkv,d,seq,mb", [(128, 64, 128, 1000, 2), (96, 32, 128, 600, 2), (16, 2, 128, 1025, 1),
+                                             (32, 16, 64, 400, 2)])
+def test_a_non_finite_gradient_reaches_no_position_far_behind_it(nq, nkv, d, seq, mb, at):
+    """dK and dV of a position sum over the queries from it on.  An infinity in the upstream gradient of an earlier position
+    may touch the 64 rows of a product's tiles, no more: all others are bit for bit what they are without it."""
+    import torch
+    import paper_2410_13333_amd as mls
+    st = mls.Stage(64, nq, nkv, d, 64, seq, mb, 1, 1, seed=1003)
+    gen = torch.Generator(device="cuda").manual_seed(seq)
+    x, dy = (torch.randn(mb, seq, 64, device="cuda", generator=gen).to(torch.bfloat16) for _ in range(2))
+    y, dx, g, got = torch.empty_like(x), torch.empty_like(x), torch.zeros(st.grad_elems, device="cuda"), []
+    for value in (None, float("inf")):
+        if value is not None:
+            dy[0, at, 5] = value
+        st.forward(x, 1, y)
+        st.backward(dy, g, 1, dx)
+        got.append(st.debug_read("dqkv").reshape(mb, seq, -1))
+    st.close()
+    clean, hit = got
+    assert not bool(torch.isfinite(hit[0, at]).all())
+    assert torch.equal(hit[0, at + 64:], clean[0, at + 64:])
+    assert torch.equal(hit[1:], clean[1:])
