@@ -203,6 +203,13 @@ int mls_stage_timing_read(mls_stage* s, double* ms /*host*/, int64_t* launches /
 int mls_gemm(int32_t dtype, int32_t mode, const void* A, int64_t lda, const void* B, int64_t ldb, void* C, int64_t ldc,
              const void* R, int64_t M, int64_t N, int64_t K, void* hip_stream);
 
+/* Which tiles a bf16 contraction of these sizes runs on, without running it (host only, no device needed; for tests):
+ * mode 0..2 as mls_gemm (dense strides), 3 the gate/up projection with the SwiGLU in its epilogue (N = 2 ffn), 4 the
+ * q|k|v projection with the rotary embedding in it.  *big_cols: the leading columns that run on 256x256 tiles, 0 .. N;
+ * *tile_rows x *tile_cols: the tiles of the columns behind them, 0 x 0 if there are none.  All three are host values.
+ * Operands of 2 GiB and more run on a kernel of their own.  Errors: MLS_E_NULL, MLS_E_CONFIG. */
+int mls_gemm_plan(int32_t mode, int64_t M, int64_t N, int64_t K, int64_t* big_cols, int32_t* tile_rows, int32_t* tile_cols);
+
 /* Message for the last error returned on this thread (host string, never NULL). */
 const char* mls_last_error(void);
 

@@ -79,6 +79,7 @@ def lib():
         L.mls_stage_timing_read.argtypes = [vp, C.POINTER(C.c_double), C.POINTER(i64)]
         L.mls_stage_memory.argtypes = [C.POINTER(MlsConfig), C.POINTER(MlsMemory)]
         L.mls_gemm.argtypes = [i32, i32, vp, i64, vp, i64, vp, i64, vp, i64, i64, i64, vp]
+        L.mls_gemm_plan.argtypes = [i32, i64, i64, i64, C.POINTER(i64), C.POINTER(i32), C.POINTER(i32)]
         L.mls_last_error.restype = C.c_char_p
         L.mls_ends_init.argtypes = [C.POINTER(MlsEndsConfig), u64, vp, C.POINTER(vp)]
         L.mls_ends_free.argtypes = [vp]
@@ -262,6 +263,13 @@ def gemm(mode, a, b, c, r=None, stream=None):
     st = stream if stream is not None else torch.cuda.current_stream()
     _check(lib().mls_gemm(dtype, mode, _ptr(a), a.stride(0), _ptr(b), b.stride(0), _ptr(c), c.stride(0), _ptr(r),
                           M, N, K, C.c_void_p(st.cuda_stream)))
+
+
+def gemm_plan(mode, M, N, K):
+    """(leading columns on 256x256 tiles, rows, columns of the tiles behind them) of a bf16 contraction; see mls_gemm_plan."""
+    big, r, c = C.c_int64(), C.c_int32(), C.c_int32()
+    _check(lib().mls_gemm_plan(mode, M, N, K, C.byref(big), C.byref(r), C.byref(c)))
+    return big.value, r.value, c.value
 
 
 # ---- include/mls_ends.h: the non-uniform layers of the first and the last pipeline stage

@@ -47,6 +47,7 @@ double estimate(int tile, int64_t w, int64_t it) {  // w tiles
 }
 double estimate(int tile, int64_t M, int64_t N, int64_t it) { return estimate(tile, tiles_of(tile, M, N), it); }
 
+// m16: the 256x256 kernel takes the problem (the fused forms need whole 64-deep k-tiles there)
 Plan plan(int M, int N, int64_t K, bool m16) {
   const int64_t it = (K + 63) / 64, tm = (M + 255) / 256, tn = (N + 255) / 256;
   const int n1 = int(tm * tn / CUS * CUS / tm) * 256;  // columns that whole rounds of 256x256 tiles cover
@@ -84,10 +85,14 @@ mls::T16Problem columns_from(mls::T16Problem p, int n1) {
   return p;
 }
 
+bool fused(int form) { return form == mls::T16_NT_SWIGLU || form == mls::T16_NT_ROPE; }
+
+Plan plan(int form, int M, int N, int64_t K) { return plan(M, N, K, !fused(form) || K % 64 == 0); }
+
 // `big(n1)` runs the leading n1 columns on 256x256 tiles
 template <class Big>
-hipError_t run(const mls::T16Problem& p, int mode, hipStream_t st, Big&& big) {
-  const Plan pl = plan(p.M, p.N, int64_t(p.K) * std::max(1, p.nseg), mls::gemm_m16_ok(mode, p.K));
+hipError_t run(const mls::T16Problem& p, hipStream_t st, Big&& big) {
+  const Plan pl = plan(p.form, p.M, p.N, int64_t(p.K) * std::max(1, p.nseg));
   if (pl.n1 > 0)
     if (hipError_t e = big(pl.n1)) return e;
   if (pl.n1 == p.N) return hipSuccess;
@@ -138,7 +143,19 @@ hipError_t gemm_bf16_dma(int mode, const void* A, const void* B, void* C, const 
   T16Problem p = problem(mode == GEMM_NN ? T16_NN : mode == GEMM_NT ? T16_NT : T16_TN, A, B, C, M, N, K, lda, ldb, ldc, ab, bb);
   p.R = R;
   p.ldr = ldr;
-  return run(p, mode, st, [&](int n1) { return gemm_m16(mode, A, B, C, R, M, n1, K, lda, ldb, ldc, ldr, ab, bb, st); });
+  return run(p, st, [&](int n1) { return gemm_m16(mode, A, B, C, R, M, n1, K, lda, ldb, ldc, ldr, ab, bb, st); });
+}
+
+void t16_tile_size(int form, int tile, int& rows, int& cols) {
+  rows = tile == T16_256x128 ? 256 : tile == T16_64x64 || (fused(form) && tile == T16_128x64) ? 64 : 128;
+  cols = tile == T16_256x128 || tile == T16_128x128 || fused(form) ? 128 : 64;
+}
+
+GemmPlan gemm_bf16_plan(int form, int M, int N, int K) {
+  const Plan p = plan(form, M, N, K);
+  GemmPlan g = {p.n1, 0, 0};
+  if (p.n1 < N) t16_tile_size(form, p.tile, g.tile_rows, g.tile_cols);
+  return g;
 }
 
 bool gemm_tn_segments_ok(int kseg, int64_t lda, int64_t ldb) { return gemm_bf16_dma_ok(GEMM_TN, 8, 8, kseg, lda, ldb); }
@@ -150,7 +167,7 @@ hipError_t gemm_bf16_tn_segments(const void* const* A, const void* const* B, int
   if (M == 0 || N == 0 || nseg == 0 || kseg == 0) return hipSuccess;
   if (nseg > 16 || (gu_f > 0 && (gu_f % 32 || N != 2 * gu_f))) return hipErrorInvalidValue;
   const T16Problem p = tn_problem({A, B, C, M, N, lda, ldb, ldc, gu_f}, nseg, kseg, overwrite);
-  return run(p, GEMM_TN, st, [&](int n1) {
+  return run(p, st, [&](int n1) {
     return gemm_m16_tn_segments(A, B, nseg, C, M, n1, kseg, lda, ldb, ldc, p.ab, p.bb, st, gu_f, overwrite);
   });
 }
@@ -171,7 +188,7 @@ hipError_t gemm_bf16_tn_group(const TnProduct* p, int n, int nseg, int kseg, hip
     if (p[i].gu_f > 0 && (p[i].gu_f % 32 || p[i].N != 2 * p[i].gu_f)) return hipErrorInvalidValue;
     if (p[i].M == 0 || p[i].N == 0) continue;
     q[m++] = tn_problem(p[i], nseg, kseg, overwrite);
-    apart += plan(p[i].M, p[i].N, depth, gemm_m16_ok(GEMM_TN, kseg)).us;
+    apart += plan(T16_TN_SEGS, p[i].M, p[i].N, depth).us;
   }
   if (m == 0) return hipSuccess;
   int best = -1;
@@ -203,7 +220,7 @@ hipError_t gemm_bf16_swiglu(const void* A, const void* W, void* GU, void* Z, int
   T16Problem p = problem(T16_NT_SWIGLU, A, W, GU, M, 2 * f, K, lda, ldw, ldgu, ab, wb);
   p.X = Z;
   p.ldx = ldz;
-  return run(p, GEMM_NT, st, [&](int n1) { return gemm_m16_swiglu(A, W, GU, Z, M, n1, K, lda, ldw, ldgu, ldz, ab, wb, st); });
+  return run(p, st, [&](int n1) { return gemm_m16_swiglu(A, W, GU, Z, M, n1, K, lda, ldw, ldgu, ldz, ab, wb, st); });
 }
 
 bool gemm_rope_ok(int M, int N, int K, int64_t lda, int64_t ldw, int seq, int rot_cols, int head_dim) {
@@ -222,7 +239,7 @@ hipError_t gemm_bf16_rope(const void* A, const void* W, void* C, int M, int N, i
   p.seq = seq;
   p.rot_cols = rot_cols;
   p.head_dim = head_dim;
-  return run(p, GEMM_NT, st, [&](int n1) {
+  return run(p, st, [&](int n1) {
     return gemm_m16_rope(A, W, C, M, n1, K, lda, ldw, ldc, ab, wb, cos_tab, sin_tab, seq, rot_cols, head_dim, st);
   });
 }

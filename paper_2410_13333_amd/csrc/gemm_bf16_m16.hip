@@ -32,10 +32,14 @@
 // of the wavefront), alternating A and B pairs reached 1460.  NT is now the fastest form (NN 1350, TN 1410), so
 // the layer runs its forward products against transposed weight copies.
 //
-// Restrictions, checked by the launcher: K (and the piece length of a segmented contraction) a multiple of 32, of
-// 64 when A is stored [row][k], so that no k-tile is ragged and no pair straddles the end; everything else (ragged
-// M and N) is handled by out-of-range requests that zero-fill.  The launcher covers whole 256-column tiles; the
-// column remainder of a problem runs on the kernels of gemm_bf16_t16.hip.
+// Ragged M and N are handled by out-of-range requests that zero-fill.  A contraction length (or piece length of a segmented
+// one) that is no multiple of 32, of 64 when A is stored [row][k], ends inside a k-tile or a pair; such problems run on a
+// second instantiation (RAG).  There the descriptor of a [k][col] operand moves along with the k-tile, so that its length
+// cuts off the k-rows beyond the end, and the lanes of a [row][k] operand whose 16-byte chunk lies beyond the end (lengths
+// are multiples of 8 there) leave the range before the last pair is requested.  Measured (us; on the 256x128 tiles of
+// gemm_bf16_t16.hip -> here): 4096 x 4096 x 4104 NT 132 -> 102, TN 133 -> 111; 8192 x 8192 x 8168 NN 1004 -> 807; the weight
+// gradients of a 4096 / 11008 layer over 2 x 4095 tokens 3390 -> 2342.
+// The launcher covers whole 256-column tiles; the column remainder of a problem runs on the kernels of gemm_bf16_t16.hip.
 #include <type_traits>
 #include <utility>
 
@@ -131,7 +135,7 @@ __device__ __forceinline__ void lds_read16_tr(i32x4& f, uint32_t addr) {
 // eight different places of a round: bits 2, 3 from kr & 3, bit 1 from bit 3 of kr.
 __device__ __forceinline__ constexpr int swz_kcol(int kr) { return ((kr & 3) << 2) | (((kr >> 3) & 1) << 1); }
 
-template <bool ATR, bool BTR, int EPI, bool SEG>
+template <bool ATR, bool BTR, int EPI, bool SEG, bool RAG>
 __global__ __launch_bounds__(NW * 64) void gemm16_kernel(const bf16_t* __restrict__ A, const bf16_t* __restrict__ B,
                                                          void* __restrict__ Cv, const bf16_t* __restrict__ R, int M, int N,
                                                          int K, int64_t lda, int64_t ldb, int64_t ldc, int64_t ldr,
@@ -183,7 +187,7 @@ __global__ __launch_bounds__(NW * 64) void gemm16_kernel(const bf16_t* __restric
       gob[i] = n0 + r < N ? uint32_t((int64_t(n0 + r) * ldb + c * 8) * 2) : OOB;
     }
   }
-  const int tps = SEG ? segs.kseg / BK : K / BK;            // k-tiles per piece
+  const int tps = ((SEG ? segs.kseg : K) + (RAG ? BK - 1 : 0)) / BK;  // k-tiles per piece
   const int nk = (SEG ? segs.nseg : 1) * tps;
   const uint32_t ka = ATR ? uint32_t(lda * (BK * 2)) : BK * 2;  // byte step of one k-tile
   const uint32_t kb = BTR ? uint32_t(ldb * (BK * 2)) : BK * 2;
@@ -193,9 +197,23 @@ __global__ __launch_bounds__(NW * 64) void gemm16_kernel(const bf16_t* __restric
   // request D of this wavefront for the cursor's k-tile into `stage`: D = 0..3 of A (unpaired form), 4..7 of B
   auto request = [&](int stage, auto DC) {
     constexpr int d = decltype(DC)::value;
-    const bool live = rq_tile < nk;
-    if constexpr (d < 4) dma16s(live ? ra : dead_a, goa[d & (NGA - 1)], uint32_t(rq_in) * ka, lds0 + stage * A_BYTES + wave * 4096 + d * 1024);
-    else dma16s(live ? rb : dead_b, gob[(d - 4) & (NGB - 1)], uint32_t(rq_in) * kb, lds0 + B_OFF + stage * B_BYTES + wave * 4096 + (d - 4) * 1024);
+    const bool live = RAG || rq_tile < nk;
+    if constexpr (d < 4) dma16s(live ? ra : dead_a, goa[d & (NGA - 1)], RAG ? 0 : uint32_t(rq_in) * ka, lds0 + stage * A_BYTES + wave * 4096 + d * 1024);
+    else dma16s(live ? rb : dead_b, gob[(d - 4) & (NGB - 1)], RAG ? 0 : uint32_t(rq_in) * kb, lds0 + B_OFF + stage * B_BYTES + wave * 4096 + (d - 4) * 1024);
+  };
+  // RAG: the descriptor of a [k][col] operand moves on by one k-tile (nothing is left of it behind the last one)
+  auto move_on = [](i32x4& r, uint32_t by) {
+    const uint64_t a = ((uint64_t)(uint32_t)r[1] << 32 | (uint32_t)r[0]) + by;
+    r[0] = (int)(uint32_t)a;
+    r[1] = (int)(uint32_t)(a >> 32);
+    r[2] = max(r[2] - (int)by, 0);  // (lengths and steps stay below 2^31)
+  };
+  // RAG: the chunks beyond the end of the last pair (of `last_pair`) of a [row][k] operand leave the range
+  const int last_pair = (K - 1) / (2 * BK), klim = K - last_pair * (2 * BK);
+  auto cut = [&](auto& go) {
+#pragma unroll
+    for (int i = 0; i < 8; i++)
+      if (((lane & 7) ^ ((i & 1) * 4 + (lane >> 4))) * 8 >= klim) go[i] |= OOB;
   };
   // request D of this wavefront for the pair of k-tiles (2 pair, 2 pair + 1) of a [row][k] operand into stages 2 slot,
   // 2 slot + 1: D = 0..7 of A, 8..15 of B
@@ -211,22 +229,29 @@ __global__ __launch_bounds__(NW * 64) void gemm16_kernel(const bf16_t* __restric
   auto request_b_all = [&](int stage) { request(stage, IC(4)); request(stage, IC(5)); request(stage, IC(6)); request(stage, IC(7)); };
   auto request_a_all = [&](int stage) { request(stage, IC(0)); request(stage, IC(1)); request(stage, IC(2)); request(stage, IC(3)); };
   auto request_pair_all = [&](int slot, int pair) {
+    if constexpr (RAG && PAIR)
+      if (pair == last_pair) cut(goa);
     request_pair(slot, pair, IC(0)); request_pair(slot, pair, IC(1)); request_pair(slot, pair, IC(2)); request_pair(slot, pair, IC(3));
     request_pair(slot, pair, IC(4)); request_pair(slot, pair, IC(5)); request_pair(slot, pair, IC(6)); request_pair(slot, pair, IC(7));
   };
   auto request_pairb_all = [&](int slot, int pair) {
+    if constexpr (RAG && PAIRB)
+      if (pair == last_pair) cut(gob);
     request_pair(slot, pair, IC(8)); request_pair(slot, pair, IC(9)); request_pair(slot, pair, IC(10)); request_pair(slot, pair, IC(11));
     request_pair(slot, pair, IC(12)); request_pair(slot, pair, IC(13)); request_pair(slot, pair, IC(14)); request_pair(slot, pair, IC(15));
   };
   auto advance = [&]() {
     rq_tile++;
     rq_in++;
+    if constexpr (RAG && ATR) move_on(ra, ka);
+    if constexpr (RAG && BTR) move_on(rb, kb);
     if (SEG && rq_in == tps) {
       rq_in = 0;
       rq_seg++;
       const int i = rq_seg < segs.nseg ? rq_seg : segs.nseg - 1;
-      ra = make_rsrc(segs.a[i], a_bytes);
-      rb = make_rsrc(segs.b[i], b_bytes);
+      const bool none = RAG && rq_seg >= segs.nseg;
+      ra = make_rsrc(segs.a[i], none ? 0 : a_bytes);
+      rb = make_rsrc(segs.b[i], none ? 0 : b_bytes);
     }
   };
 
@@ -331,6 +356,11 @@ __global__ __launch_bounds__(NW * 64) void gemm16_kernel(const bf16_t* __restric
   auto iteration = [&](auto SETC, auto STC) {
     constexpr int set = decltype(SETC)::value, st = decltype(STC)::value;
     if constexpr (PAIRB && (st & 1) == 0) next_b_slot();  // t odd: tile t+1 opens a new pair
+    const int pair = (rq_tile - 1) >> 1;  // (see the requests below)
+    if constexpr (RAG && PAIR && (st & 1) != 0)
+      if (pair == last_pair) cut(goa);
+    if constexpr (RAG && PAIRB && (st & 1) == 0)
+      if (pair + 1 == last_pair) cut(gob);
     using SN = std::integral_constant<int, set ^ 1>;
     // first half: A fragments 0..3 against all of B, the 16 reads of tile t+1 in between
 #define MM(i, j) mfma16(c[i][j], fb[set][j], fa[set][i])
@@ -355,7 +385,6 @@ __global__ __launch_bounds__(NW * 64) void gemm16_kernel(const bf16_t* __restric
     // t+NS+1 into the stage just freed.  Paired, t even (ST odd): the pair (t+NS, t+NS+1) into stages ST-1, ST (tile t
     // was read in iteration t-1, tile t+1 just now), then B of tile t+NS+1; t odd: B only.  Both paired, t even: the
     // pair of A; t odd: the pair (t+5, t+6) of B into the slot of tiles t-1, t of its ring (read by the last barrier).
-    const int pair = (rq_tile - 1) >> 1;
     constexpr bool even = (st & 1) != 0;
     constexpr int nreq = !PAIR ? 8 : PAIRB ? 8 : even ? 12 : 4;
     auto rqn = [&](auto NC) {
@@ -571,11 +600,11 @@ __global__ __launch_bounds__(NW * 64) void gemm16_kernel(const bf16_t* __restric
   }
 }
 
-template <bool ATR, bool BTR, int EPI, bool SEG>
-hipError_t launch16(const bf16_t* A, const bf16_t* B, void* C, const bf16_t* R, int M, int N, int K, int64_t lda,
+template <bool ATR, bool BTR, int EPI, bool SEG, bool RAG>
+hipError_t launch16_as(const bf16_t* A, const bf16_t* B, void* C, const bf16_t* R, int M, int N, int K, int64_t lda,
                     int64_t ldb, int64_t ldc, int64_t ldr, uint32_t ab, uint32_t bb, hipStream_t st, const SegArgs* segs,
                     void* X, int64_t ldx, int xf, const RopeArgs* rope) {
-  auto kern = gemm16_kernel<ATR, BTR, EPI, SEG>;
+  auto kern = gemm16_kernel<ATR, BTR, EPI, SEG, RAG>;
   SegArgs sa = {};
   if (segs) sa = *segs;
   RopeArgs rp = {};
@@ -589,12 +618,21 @@ hipError_t launch16(const bf16_t* A, const bf16_t* B, void* C, const bf16_t* R, 
   return hipGetLastError();
 }
 
+// The fused epilogues take whole pairs of k-tiles only (their callers pad the contraction with zeros).
+template <bool ATR, bool BTR, int EPI, bool SEG>
+hipError_t launch16(const bf16_t* A, const bf16_t* B, void* C, const bf16_t* R, int M, int N, int K, int64_t lda,
+                    int64_t ldb, int64_t ldc, int64_t ldr, uint32_t ab, uint32_t bb, hipStream_t st, const SegArgs* segs,
+                    void* X, int64_t ldx, int xf, const RopeArgs* rope) {
+  if (K <= 0 || (!ATR && K % 8)) return hipErrorInvalidValue;
+  if (K % (ATR ? BK : 2 * BK) == 0)
+    return launch16_as<ATR, BTR, EPI, SEG, false>(A, B, C, R, M, N, K, lda, ldb, ldc, ldr, ab, bb, st, segs, X, ldx, xf, rope);
+  if constexpr (EPI == E_SWIGLU || EPI == E_ROPE) return hipErrorInvalidValue;
+  else return launch16_as<ATR, BTR, EPI, SEG, true>(A, B, C, R, M, N, K, lda, ldb, ldc, ldr, ab, bb, st, segs, X, ldx, xf, rope);
+}
+
 }  // namespace
 
 namespace mls {
-
-// k-tiles must be whole; an A stored [row][k] (NN, NT) is fetched in pairs of k-tiles
-bool gemm_m16_ok(int mode, int K) { return K > 0 && K % (mode == GEMM_TN ? BK : 2 * BK) == 0; }
 
 // C[M, N] (N a multiple of 256 or the whole problem) in one of the three modes; bf16 C (+ R) for NN and NT, fp32
 // C (+)= for TN.  Operand byte lengths as the DMA path takes them.
@@ -631,12 +669,11 @@ hipError_t gemm_m16_rope(const void* A, const void* W, void* C, int M, int N, in
   return launch16<false, false, E_ROPE, false>(a, w, C, nullptr, M, N, K, lda, ldw, ldc, 0, ab, bb, st, nullptr, nullptr, 0, 0, &ra);
 }
 
-// C[M, N] (+)= sum_i A_i[kseg, M]^T B_i[kseg, N] in fp32 over nseg <= 16 pieces (kseg a multiple of 32), N a multiple
-// of 256 or the whole problem; gu_f > 0: interleaved gate/up columns go to their public places; overwrite: C =.
+// C[M, N] (+)= sum_i A_i[kseg, M]^T B_i[kseg, N] in fp32 over nseg <= 16 pieces, N a multiple of 256 or the whole problem; gu_f > 0: interleaved gate/up columns go to their public places; overwrite: C =.
 hipError_t gemm_m16_tn_segments(const void* const* A, const void* const* B, int nseg, void* C, int M, int N, int kseg,
                                 int64_t lda, int64_t ldb, int64_t ldc, uint32_t ab, uint32_t bb, hipStream_t st, int gu_f,
                                 bool overwrite) {
-  if (nseg < 1 || nseg > MAX_SEGS || kseg % BK) return hipErrorInvalidValue;
+  if (nseg < 1 || nseg > MAX_SEGS) return hipErrorInvalidValue;
   SegArgs sa = {};
   for (int i = 0; i < nseg; i++) {
     sa.a[i] = static_cast<const bf16_t*>(A[i]);

@@ -36,6 +36,10 @@ hipError_t gemm_bf16(int mode, const void* A, const void* B, void* C, const void
 bool gemm_bf16_dma_ok(int mode, int M, int N, int K, int64_t lda, int64_t ldb);
 hipError_t gemm_bf16_dma(int mode, const void* A, const void* B, void* C, const void* R, int M, int N, int K,
                          int64_t lda, int64_t ldb, int64_t ldc, int64_t ldr, hipStream_t st);
+// What such a problem runs on (form: T16_NN .. T16_NT_ROPE below): the leading columns that get 256x256 tiles, and the size of
+// the tiles behind them (0 x 0 if there are none).  Host only.
+struct GemmPlan { int big_cols, tile_rows, tile_cols; };
+GemmPlan gemm_bf16_plan(int form, int M, int N, int K);
 // weight gradient of several micro-batches in one launch: C[M,N] += sum_i A_i[kseg,M]^T * B_i[kseg,N], C fp32,
 // at most 16 pieces, all with the same strides; true if the operands fit the DMA path's 31-bit offsets
 bool gemm_tn_segments_ok(int kseg, int64_t lda, int64_t ldb);
@@ -54,9 +58,8 @@ struct TnProduct {
   int gu_f;
 };
 hipError_t gemm_bf16_tn_group(const TnProduct* p, int n, int nseg, int kseg, hipStream_t st, bool overwrite);
-// the 256x256 tiles of a problem on the 16x16x32 form of the matrix instruction (gemm_bf16_m16.hip); K % 32 == 0
-// (% 64 for NN and NT)
-bool gemm_m16_ok(int mode, int K);
+// the 256x256 tiles of a problem on the 16x16x32 form of the matrix instruction (gemm_bf16_m16.hip); K % 8 == 0 where an
+// operand is stored [row][k], % 64 in the two fused forms
 hipError_t gemm_m16(int mode, const void* A, const void* B, void* C, const void* R, int M, int N, int K, int64_t lda,
                     int64_t ldb, int64_t ldc, int64_t ldr, uint32_t ab, uint32_t bb, hipStream_t st);
 hipError_t gemm_m16_swiglu(const void* A, const void* W, void* GU, void* Z, int M, int N, int K, int64_t lda, int64_t ldw,

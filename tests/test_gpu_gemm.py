@@ -41,8 +41,7 @@ def test_bf16_three_modes(M, N, K):
 def test_bf16_16x16x32_kernel_at_awkward_depths(M, N, K):
     """At least 256 tiles of 256x256, so that the problem runs on the 16x16x32 kernel: contraction depths of one to a
     few k-tiles (prologue with nothing behind it, rings that do not come round, a k-tile count that is no multiple of
-    the loop's period), ragged last tile rows, a column remainder beside it.  K % 64 != 0 exercises only the TN form
-    there; the other two then run on the 32x32x16 kernels."""
+    the loop's period), ragged last tile rows, a column remainder beside it."""
     import torch
     import paper_2410_13333_amd as mls
     g = torch.Generator(device="cpu").manual_seed(M + 3 * N + 7 * K)
@@ -61,6 +60,36 @@ def test_bf16_16x16x32_kernel_at_awkward_depths(M, N, K):
     mls.gemm(2, at, b, acc)
     torch.cuda.synchronize()
     assert rel_err(to_host64(acc), 0.5 + 2 * ref) < 1e-5
+
+
+@pytest.mark.parametrize("K", [8, 40, 72, 104, 136, 200, 264, 328])
+def test_bf16_256_tiles_over_contractions_that_end_inside_a_tile(K):
+    """256x256 tiles with a remainder beside them; what lies behind the end of the contraction in memory (the rest of a row,
+    the rows behind the last one) is NaN and must not be looked at."""
+    import torch
+    import paper_2410_13333_amd as mls
+    M, N = 3848, 4360
+    for mode in (0, 1, 2):
+        assert mls.gemm_plan(mode, M, N, K)[0] == 4096
+    g = torch.Generator(device="cuda").manual_seed(K)
+
+    def framed(r, c):  # an r x c matrix in a buffer that is wider and longer
+        buf = torch.full((r + 72, c + 72), float("nan"), dtype=torch.bfloat16, device="cuda")
+        buf[:r, :c] = torch.randn(r, c, device="cuda", generator=g)
+        return buf[:r, :c]
+    a, b, at, bt = framed(M, K), framed(K, N), framed(K, M), framed(N, K)
+    at.copy_(a.t())
+    bt.copy_(b.t())
+    ref = a.double() @ b.double()
+    off = lambda c, want: ((c.double() - want).norm() / want.norm()).item()  # noqa: E731
+    c = torch.empty(M, N, dtype=torch.bfloat16, device="cuda")
+    mls.gemm(0, a, b, c)
+    assert off(c, ref) < 4e-3
+    mls.gemm(1, a, bt, c)
+    assert off(c, ref) < 4e-3
+    acc = torch.full((M, N), 0.5, device="cuda")
+    mls.gemm(2, at, b, acc)
+    assert off(acc, 0.5 + ref) < 1e-5
 
 
 def test_fp32_three_modes():
@@ -148,7 +177,8 @@ def test_bf16_every_tile_size(M, N, K):
     test_bf16_three_modes(M, N, K)
 
 
-@pytest.mark.parametrize("M,N,K", [(72, 136, 77), (1000, 2056, 1091), (2040, 2040, 390), (2000, 3000, 1025)])
+@pytest.mark.parametrize("M,N,K", [(72, 136, 77), (1000, 2056, 1091), (2040, 2040, 390), (2000, 3000, 1025), (8200, 4104, 1091),
+                                   (4096, 4096, 45)])
 def test_bf16_weight_gradient_over_any_token_count(M, N, K):
     """C += A^T B over K tokens, K no multiple of 8 (the C ABI's mls_gemm refuses such a K; a stage's weight gradients
     have it): through a one-layer stage's w_d, whose operands are captured."""
