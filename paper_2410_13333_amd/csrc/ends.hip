@@ -5,6 +5,7 @@
 
 #include <mutex>
 #include <string>
+#include <type_traits>
 #include <vector>
 
 #include "../../include/mls.h"
@@ -42,87 +43,208 @@ __global__ __launch_bounds__(TH) void embed_gather_kernel(const int32_t* __restr
 
 // ---- grads_embed[v, :] += sum of the dX rows at the positions that hold token v, in ascending (micro-batch,
 // position) order.
-// HBM-bound: dX once, and the fp32 rows that some position names read and written.  A workgroup owns SC_ROWS table rows
-// and a slice of 2048 columns: it scans the token ids of all micro-batches (64 KB from L2 at 16384 positions; the
-// one-row-per-workgroup form this replaces read 2 GB of ids for 32000 rows), collects the matches as (row, position)
-// keys in LDS, sorts them, and then every thread walks the sorted list for its own eight columns, requesting up to
-// SC_AHEAD rows of dX at a time.  The list is emptied when it may overflow, and at the end.  Neither the sort nor the
-// owner of a row depends on the order in which the matches were found: bitwise reproducible, no float atomics.
-// Measured (4 micro-batches of 4096 uniform tokens, 32000 x 4096): 562 -> 143 us (610 MB, 4.3 TB/s).
+// HBM-bound: dX once, and the fp32 rows that some position names read and written.  A workgroup owns up to SC_ROWS table
+// rows, 2^shift apart (frequent ids are often neighbours), and a slice of 2048 columns.  It scans the token ids of all
+// micro-batches (64 KB from L2 at 16384 positions; one row per workgroup read 2 GB of ids for 32000 rows) and keeps the
+// matches as (row, position) keys in LDS, in the order of the positions: ballots count them.  Then the list is split by
+// rows, and every thread walks a row's positions for its own eight columns, requesting up to SC_AHEAD rows of dX at a time.
+// If the matches do not fit the list, the rows are taken one after the other, each with a scan of its own; a row's sum
+// stays in registers all the while, so that it does not depend on which way it came.  Bitwise reproducible, no atomics.
+// Measured with the gathers before it (us; one row per workgroup -> 16 neighbouring rows and a list sorted key against key ->
+// this): 32000 x 4096, 4 x 4096 uniform ids 606 -> 196 -> 193; ids by Zipf's law 1450 -> 3990 -> 295; half of them one id 7850
+// -> 6650 -> 1160; 512 x 256, 4 x 8192 uniform ids 90 -> 530 -> 35; 50304 x 768, 1024 ids 53 -> 9.4 -> 11.5.
 struct TokPtrs { const int32_t* p[MAX_MB]; };
-constexpr int SC_ROWS = 16;    // table rows of a workgroup: 4 bits of a key, 28 hold MAX_MB * 2^24 positions
-constexpr int SC_CAP = 2048;   // keys of the list (twice 8 KiB of LDS: eight workgroups per CU)
-constexpr int SC_SCAN = 4;     // ids per thread between two looks at the list's length
+// eight elements of a row as they were loaded
+template <typename T> struct Chunk8;
+template <> struct Chunk8<bf16_t> {
+  uint4 r;
+  __device__ __forceinline__ void load(const bf16_t* p) { r = *reinterpret_cast<const uint4*>(p); }
+  __device__ __forceinline__ void get(float (&v)[8]) const { load8(reinterpret_cast<const bf16_t*>(&r), v); }
+};
+template <> struct Chunk8<float> {
+  float4 a, b;
+  __device__ __forceinline__ void load(const float* p) { a = reinterpret_cast<const float4*>(p)[0]; b = reinterpret_cast<const float4*>(p)[1]; }
+  __device__ __forceinline__ void get(float (&v)[8]) const {
+    v[0] = a.x; v[1] = a.y; v[2] = a.z; v[3] = a.w; v[4] = b.x; v[5] = b.y; v[6] = b.z; v[7] = b.w;
+  }
+};
+constexpr int SC_ROWS = 16;    // 4 bits of a key, 28 hold MAX_MB * 2^24 positions
+constexpr int SC_CAP = 2048;   // keys of the list (twice 8 KiB of LDS)
+constexpr int SC_SCAN = 8;     // ids per thread between two looks at the list's length
+static_assert(SC_SCAN * TH <= SC_CAP);
 constexpr int SC_AHEAD = 8;
+constexpr int SC_GRID = 1024;  // workgroups from which on the rows of one are not made fewer
 template <typename T>
 __global__ __launch_bounds__(TH) void embed_scatter_kernel(TokPtrs tp, int n, const T* __restrict__ dX, int Ttok, int h,
-                                                           int V, float* __restrict__ gE) {
+                                                           int V, int shift, float* __restrict__ gE) {
+  constexpr int NW = TH / 64;
   __shared__ uint32_t key[SC_CAP], sorted[SC_CAP];
-  __shared__ int count;
-  const int v0 = blockIdx.x * SC_ROWS, rows = min(SC_ROWS, V - v0);
+  __shared__ int found[2][NW], per_row[SC_ROWS];
+  const int g0 = blockIdx.x, rows = (V - g0 + (1 << shift) - 1) >> shift;
   const int c = (blockIdx.y * TH + threadIdx.x) * 8;
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const uint64_t below = (uint64_t(1) << lane) - 1;
   const bool mine = c < h;
 
-  auto flush = [&](int L) {  // (called by the whole workgroup, the keys published)
-    for (int i = threadIdx.x; i < L; i += TH) {
-      const uint32_t k = key[i];
-      int rank = 0;
-      for (int q = 0; q < L; q++) rank += key[q] < k;
-      sorted[rank] = k;
+  // acc += the dX rows at the first `got` of N positions, in order.  All N are requested (those from `got` on name a valid row,
+  // too): with a condition around each, the compiler waits for every one before it requests the next.
+  auto add_rows = [&](auto N, const uint32_t (&pos)[SC_AHEAD], int got, float (&acc)[8]) {
+    constexpr int some = decltype(N)::value;
+    if (!mine) return;
+    Chunk8<T> d[some];
+#pragma unroll
+    for (int q = 0; q < some; q++) d[q].load(dX + int64_t(pos[q]) * h + c);
+#pragma unroll
+    for (int q = 0; q < some; q++) {
+      float v[8];
+      d[q].get(v);
+#pragma unroll
+      for (int e = 0; e < 8; e++) acc[e] = q < got ? acc[e] + v[e] : acc[e];
     }
-    __syncthreads();
-    for (int i = 0; i < L;) {
-      const uint32_t row = sorted[i] >> 28;
-      int end = i + 1;
-      while (end < L && sorted[end] >> 28 == row) end++;
-      if (mine) {
-        float* p = gE + int64_t(v0 + row) * h + c;
-        float g[8], acc[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-        load8(p, g);
-        for (int at = i; at < end; at += SC_AHEAD) {
-          float d[SC_AHEAD][8];
+  };
+  using One = std::integral_constant<int, 1>;
+  using Ahead = std::integral_constant<int, SC_AHEAD>;
+  auto walk = [&](const uint32_t* list, int i0, int i1, float (&acc)[8]) {  // ... at positions list[i0 .. i1)
+    for (int at = i0; at < i1; at += SC_AHEAD) {
+      uint32_t pos[SC_AHEAD];
 #pragma unroll
-          for (int q = 0; q < SC_AHEAD; q++)
-            if (at + q < end) load8(dX + int64_t(sorted[at + q] & 0x0fffffffu) * h + c, d[q]);
+      for (int q = 0; q < SC_AHEAD; q++) pos[q] = list[min(at + q, i1 - 1)] & 0x0fffffffu;
+      add_rows(Ahead{}, pos, min(SC_AHEAD, i1 - at), acc);
+    }
+  };
+  auto add_to_row = [&](int row, const float (&acc)[8]) {
+    if (!mine) return;
+    float* p = gE + (int64_t(g0) + (int64_t(row) << shift)) * h + c;
+    float g[8];
+    load8(p, g);
 #pragma unroll
-          for (int q = 0; q < SC_AHEAD; q++)
-            if (at + q < end)
+    for (int e = 0; e < 8; e++) g[e] += acc[e];
+    store8(p, g);
+  };
+  // Appends the keys that match(id) holds for to the list, ascending in position.  Where the next ones do not fit, full(L) is
+  // called first (by the whole workgroup, all keys published); it empties the list (true) or gives up.  Returns the length,
+  // or -1.  A wavefront takes SC_SCAN * 64 ids in a row, so that one count per wavefront tells where its keys go.
+  auto scan = [&](auto&& match, auto&& full) {
+    int L = 0, turn = 0;
+    for (int mb = 0; mb < n; mb++) {
+      const int32_t* tok = tp.p[mb];
+      for (int base = 0; base < Ttok; base += SC_SCAN * TH) {
+        const int first = base + wave * (SC_SCAN * 64) + lane;
+        int t[SC_SCAN], hits = 0;
+        uint64_t hit[SC_SCAN];
 #pragma unroll
-              for (int e = 0; e < 8; e++) acc[e] += d[q][e];
+        for (int q = 0; q < SC_SCAN; q++) t[q] = first + q * 64 < Ttok ? tok[first + q * 64] : -1;
+#pragma unroll
+        for (int q = 0; q < SC_SCAN; q++) {
+          hit[q] = __ballot(match(t[q]));
+          hits += __popcll(hit[q]);
         }
+        if (lane == 0) found[turn][wave] = hits;
+        __syncthreads();  // (the next counts go to the other half: one barrier is enough)
+        int at = L, total = 0;
 #pragma unroll
-        for (int e = 0; e < 8; e++) g[e] += acc[e];
-        store8(p, g);
+        for (int w = 0; w < NW; w++) {
+          at += w < wave ? found[turn][w] : 0;
+          total += found[turn][w];
+        }
+        turn ^= 1;
+        if (total == 0) continue;
+        if (L + total > SC_CAP) {
+          if (!full(L)) return -1;
+          at -= L;
+          L = 0;
+        }
+        if (hits > 0) {
+#pragma unroll
+          for (int q = 0; q < SC_SCAN; q++) {
+            if (hit[q] >> lane & 1)
+              key[at + __popcll(hit[q] & below)] = uint32_t(t[q] >> shift) << 28 | uint32_t(mb * Ttok + first + q * 64);
+            at += __popcll(hit[q]);
+          }
+        }
+        L += total;
       }
-      i = end;
     }
     __syncthreads();
-    if (threadIdx.x == 0) count = 0;
-    __syncthreads();
+    return L;
   };
 
-  if (threadIdx.x == 0) count = 0;
-  __syncthreads();
-  for (int mb = 0; mb < n; mb++) {
-    const int32_t* tok = tp.p[mb];
-    for (int base = 0; base < Ttok; base += SC_SCAN * TH) {
-      int t[SC_SCAN];
+  const int L = rows == 1 ? -1 : scan([&](int t) { return (t & ((1 << shift) - 1)) == g0 && uint32_t(t) < uint32_t(V); },
+                                      [](int) { return false; });
+  if (L > 0 && L <= 64) {  // a key per lane: the keys of a row are the bits of a mask
+    const uint32_t k = lane < L ? key[lane] : 0;
+    uint64_t rest = __ballot(lane < L);
+    while (rest) {
+      const uint32_t row = uint32_t(__builtin_amdgcn_readlane(int(k), __ffsll((unsigned long long)rest) - 1)) >> 28;
+      uint64_t m = __ballot(k >> 28 == row) & rest;
+      rest &= ~m;
+      float acc[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+      while (m) {
+        uint32_t pos[SC_AHEAD] = {};  // (read by all lanes, also those without columns)
+        int got = 0;
 #pragma unroll
-      for (int q = 0; q < SC_SCAN; q++) {
-        const int pos = base + q * TH + threadIdx.x;
-        t[q] = pos < Ttok ? tok[pos] : -1;
+        for (int q = 0; q < SC_AHEAD; q++) {
+          pos[q] = m ? uint32_t(__builtin_amdgcn_readlane(int(k), __ffsll((unsigned long long)m) - 1)) & 0x0fffffffu : pos[q ? q - 1 : 0];
+          got += m ? 1 : 0;
+          m &= m - 1;
+        }
+        if (got == 1) add_rows(One{}, pos, got, acc);
+        else add_rows(Ahead{}, pos, got, acc);
       }
-#pragma unroll
-      for (int q = 0; q < SC_SCAN; q++)
-        if (t[q] >= v0 && t[q] < v0 + rows)
-          key[atomicAdd(&count, 1)] = uint32_t(t[q] - v0) << 28 | uint32_t(mb * Ttok + base + q * TH + threadIdx.x);
-      __syncthreads();
-      const int L = count;
-      __syncthreads();
-      if (L > SC_CAP - SC_SCAN * TH) flush(L);  // uniform: the next scan may not fit
+      add_to_row(int(row), acc);
+    }
+  } else if (L > 0) {  // the keys of row r go to sorted[] behind those of the rows before it, in the same order
+    for (int r = wave; r < rows; r += NW) {
+      int m = 0;
+      for (int i = 0; i < L; i += 64) m += __popcll(__ballot(i + lane < L && key[i + lane] >> 28 == uint32_t(r)));
+      if (lane == 0) per_row[r] = m;
+    }
+    __syncthreads();
+    for (int r = wave; r < rows; r += NW) {
+      if (per_row[r] == 0) continue;
+      int at = 0;
+      for (int i = 0; i < r; i++) at += per_row[i];
+      for (int i = 0; i < L; i += 64) {
+        const uint32_t k = i + lane < L ? key[i + lane] : 0;
+        const bool it = i + lane < L && k >> 28 == uint32_t(r);
+        const uint64_t m = __ballot(it);
+        if (it) sorted[at + __popcll(m & below)] = k;
+        at += __popcll(m);
+      }
+    }
+    __syncthreads();
+    for (int r = 0, at = 0; r < rows; at += per_row[r++]) {
+      if (per_row[r] == 0) continue;
+      float acc[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+      walk(sorted, at, at + per_row[r], acc);
+      add_to_row(r, acc);
+    }
+  } else if (L < 0) {
+    for (int r = 0; r < rows; r++) {
+      __syncthreads();  // the list is free
+      const int v = g0 + (r << shift);
+      float acc[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+      bool any = false;
+      const int rest = scan([&](int t) { return t == v; }, [&](int m) {
+        any = true;
+        __syncthreads();
+        walk(key, 0, m, acc);
+        __syncthreads();
+        return true;
+      });
+      walk(key, 0, rest, acc);
+      if (any || rest > 0) add_to_row(r, acc);
     }
   }
-  if (count > 0) flush(count);
+}
+
+// Table rows of a workgroup of the kernel above: 2^shift workgroups share a column slice.  At most SC_ROWS rows each, fewer
+// while the grid leaves CUs idle (32 workgroups instead of 512 made most of the 530 us above).
+int scatter_shift(int V, int slices) {
+  int shift = 0;
+  while ((int64_t(SC_ROWS) << shift) < V) shift++;
+  while ((int64_t(slices) << shift) < SC_GRID && (1 << shift) < V) shift++;
+  return shift;
 }
 
 // ---- cross-entropy of one row of logits per workgroup, and its gradient in place:
@@ -423,9 +545,10 @@ int mls_embed_backward(mls_ends* s, const void* dX, float* grads, int32_t n) {
     for (int i = 0; i < m; i++) tp.p[i] = s->tok + size_t((s->e_head + i0 + i) % s->c.max_inflight) * s->T;
     const char* dx = (const char*)dX + size_t(i0) * act;
     float* gE = grads + s->off_e;
+    const int slices = (h / 8 + TH - 1) / TH, shift = scatter_shift(s->c.vocab, slices);
 #define SCATTER(TY)                                                                                                  \
-  hipLaunchKernelGGL(embed_scatter_kernel<TY>, dim3((s->c.vocab + SC_ROWS - 1) / SC_ROWS, (h / 8 + TH - 1) / TH), dim3(TH), 0, \
-                     s->st, tp, m, (const TY*)dx, s->T, h, s->c.vocab, gE)
+  hipLaunchKernelGGL(embed_scatter_kernel<TY>, dim3(std::min(1 << shift, s->c.vocab), slices), dim3(TH), 0, s->st, tp, m, \
+                     (const TY*)dx, s->T, h, s->c.vocab, shift, gE)
     if (s->dt == mls::DT_BF16) SCATTER(bf16_t); else SCATTER(float);
 #undef SCATTER
     HIP_TRY(hipGetLastError());

@@ -306,6 +306,37 @@ def test_embedding_gradient_of_crowded_rows(dtype, hidden, vocab, seq, kind):
     assert (g[vocab * hidden:] == 0.25).all()
 
 
+@pytest.mark.parametrize("hidden,vocab,seq,ids", [
+    (72, 20000, 2100, "far rows"),    # rows 2048 apart belong to one workgroup: more matches than its list holds, a few rows
+    (72, 20000, 900, "far rows"),     # ... and as many as it holds
+    (2056, 32, 3000, "any"),          # a table of fewer rows than there are CUs
+    (264, 520, 1000, "any"), (64, 50000, 2000, "any"), (4104, 9000, 333, "neighbours")])
+def test_embedding_gradient_bits(hidden, vocab, seq, ids):
+    """Every row's sum runs over its positions in ascending order, in fp32 from zero, and is added to the gradient once,
+    whatever else falls on the workgroup: the bits are those of that sum."""
+    import torch
+    import paper_2410_13333_amd as mls
+    n = 3
+    en = mls.Ends(hidden, vocab, seq, 1, n, 1e-5, "bf16", seed=1100)
+    rng = np.random.default_rng(seq)
+    toks = [{"far rows": 7 + 2048 * rng.integers(0, 9, seq), "any": rng.integers(-1, vocab + 1, seq),
+             "neighbours": rng.integers(100, 140, seq)}[ids].astype(np.int32) for _ in range(n)]
+    x = torch.empty((seq, hidden), dtype=torch.bfloat16, device="cuda")
+    for t in toks:
+        en.embed_forward(torch.from_numpy(t).cuda(), x)
+    dX = torch.randn(n, seq, hidden, device="cuda", generator=torch.Generator(device="cuda").manual_seed(3)).to(torch.bfloat16)
+    grads = torch.randn(en.grad_elems, device="cuda", generator=torch.Generator(device="cuda").manual_seed(4))
+    want = grads[:vocab * hidden].cpu().numpy().reshape(vocab, hidden).copy()
+    en.embed_backward(dX, grads, n)
+    en.close()
+    tok, rows = np.concatenate(toks), dX.float().cpu().numpy().reshape(n * seq, hidden)
+    for v in np.unique(tok):
+        if 0 <= v < vocab:
+            want[v] += np.add.accumulate(rows[tok == v], axis=0, dtype=np.float32)[-1]
+    got = grads[:vocab * hidden].cpu().numpy().reshape(vocab, hidden)
+    assert np.array_equal(got, want)
+
+
 @pytest.mark.parametrize("h,V", [(264, 1032), (328, 520), (1000, 2056)])
 def test_widths_that_are_no_multiples_of_a_k_tile(h, V):
     """Head forward and backward over rows padded to whole 64-deep k-tiles, against fp64; a second pass over reused buffers
