@@ -180,13 +180,14 @@ int mls_stage_reset(mls_stage* s);
 int mls_stage_debug_read(mls_stage* s, int32_t tensor_id, int32_t layer, int32_t slot, void* dst);
 
 /* Per-kernel-class timing with HIP events recorded on the stage's stream, for the benchmark's roofline figure.
- * enable != 0 brackets every kernel launch of forward/backward with a pair of events (no synchronisation unless
- * more than 4096 launches are pending); enable = 0 stops it.  mls_stage_timing_read synchronises on the last
- * event, writes the accumulated milliseconds and launch counts per class into two HOST arrays of
- * MLS_TIMING_CLASSES entries (order: GEMM forward, GEMM data-gradient, GEMM weight-gradient, attention
- * forward, attention backward, RMSNorm, rotary, SwiGLU) and clears the accumulators.  A step that runs fused into
- * a neighbouring kernel (bf16 storage: the rotary steps, SwiGLU forward when ffn % 32 == 0) is counted with that
- * kernel's class and leaves its own class at zero.
+ * enable != 0 brackets every step of forward/backward with a pair of events (no synchronisation unless more than
+ * 4096 are pending) and counts it as one launch: a contraction of two tile sizes runs as two kernels and counts once,
+ * the weight gradients of a layer count once where they share a kernel and once each where they do not; enable = 0
+ * stops it.  mls_stage_timing_read synchronises on the last event, writes the accumulated milliseconds and launch counts
+ * per class into two HOST arrays of MLS_TIMING_CLASSES entries (order: GEMM forward, GEMM data-gradient, GEMM
+ * weight-gradient, attention forward, attention backward, RMSNorm, rotary, SwiGLU) and clears the accumulators.  A step
+ * that runs fused into a neighbouring kernel (bf16 storage: the rotary steps, SwiGLU forward when ffn % 32 == 0) is
+ * counted with that kernel's class and leaves its own class at zero.
  * Errors: MLS_E_NULL, MLS_E_HIP. */
 #define MLS_TIMING_CLASSES 8
 int mls_stage_timing(mls_stage* s, int32_t enable);
@@ -209,6 +210,11 @@ int mls_gemm(int32_t dtype, int32_t mode, const void* A, int64_t lda, const void
  * *tile_rows x *tile_cols: the tiles of the columns behind them, 0 x 0 if there are none.  All three are host values.
  * Operands of 2 GiB and more run on a kernel of their own.  Errors: MLS_E_NULL, MLS_E_CONFIG. */
 int mls_gemm_plan(int32_t mode, int64_t M, int64_t N, int64_t K, int64_t* big_cols, int32_t* tile_rows, int32_t* tile_cols);
+
+/* The same for the weight gradients of a layer of this configuration over n_microbatches: the tile of the launch that all
+ * four share, or 0 x 0 if each has launches of its own (then mls_gemm_plan with mode 2 and K = tokens of all micro-batches
+ * tells their tiles; 16 micro-batches go into a launch).  Errors: MLS_E_NULL, MLS_E_CONFIG, MLS_E_RANGE. */
+int mls_stage_wgrad_plan(const mls_config* cfg, int32_t n_microbatches, int32_t* tile_rows, int32_t* tile_cols);
 
 /* Message for the last error returned on this thread (host string, never NULL). */
 const char* mls_last_error(void);

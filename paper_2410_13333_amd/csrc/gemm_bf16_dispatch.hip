@@ -177,35 +177,35 @@ hipError_t gemm_bf16_tn_segments(const void* const* A, const void* const* B, int
 // layer, apart -> in one (us): hidden 256, 256 tokens 25 -> 9; 1024 / ffn 2728, 2000 tokens 112 -> 80; 768, 2 x 1024 tokens
 // 80 -> 45; 1536, 700 tokens 125 -> 97 (the fastest tile: 89); 512, 4 x 4096 tokens 387 -> 157; 3072, 600 tokens 422 -> 420;
 // 2048, 2 x 2048 tokens stay apart: 469, in one 517.
-hipError_t gemm_bf16_tn_group(const TnProduct* p, int n, int nseg, int kseg, hipStream_t st, bool overwrite) {
-  if (nseg == 0 || kseg == 0) return hipSuccess;
-  if (n < 1 || n > MAX_T16_GROUP || nseg > 16) return hipErrorInvalidValue;
+int gemm_bf16_tn_group_tile(const TnProduct* p, int n, int nseg, int kseg) {
   const int64_t depth = int64_t(kseg) * nseg, it = (depth + 63) / 64;
-  T16Problem q[MAX_T16_GROUP];
-  int m = 0;
   double apart = 0;
-  for (int i = 0; i < n; i++) {
-    if (p[i].gu_f > 0 && (p[i].gu_f % 32 || p[i].N != 2 * p[i].gu_f)) return hipErrorInvalidValue;
-    if (p[i].M == 0 || p[i].N == 0) continue;
-    q[m++] = tn_problem(p[i], nseg, kseg, overwrite);
-    apart += plan(T16_TN_SEGS, p[i].M, p[i].N, depth).us;
-  }
-  if (m == 0) return hipSuccess;
+  for (int i = 0; i < n; i++)
+    if (p[i].M > 0 && p[i].N > 0) apart += plan(T16_TN_SEGS, p[i].M, p[i].N, depth).us;
   int best = -1;
   for (int tile : {T16_256x128, T16_128x128, T16_128x64, T16_64x64}) {
     int64_t w = 0;
-    for (int i = 0; i < m; i++) w += tiles_of(tile, q[i].M, q[i].N);
+    for (int i = 0; i < n; i++) w += tiles_of(tile, p[i].M, p[i].N);
     const double t = estimate(tile, w, it);
     if (t < apart) {
       apart = t;
       best = tile;
     }
   }
-  if (best >= 0) return gemm_t16_group(q, m, best, st);
-  for (int i = 0; i < n; i++)
-    if (hipError_t e = gemm_bf16_tn_segments(p[i].A, p[i].B, nseg, p[i].C, p[i].M, p[i].N, kseg, p[i].lda, p[i].ldb, p[i].ldc, st, p[i].gu_f, overwrite))
-      return e;
-  return hipSuccess;
+  return best;
+}
+
+hipError_t gemm_bf16_tn_group(const TnProduct* p, int n, int tile, int nseg, int kseg, hipStream_t st, bool overwrite) {
+  if (nseg == 0 || kseg == 0) return hipSuccess;
+  if (n < 1 || n > MAX_T16_GROUP || nseg > 16 || tile < 0) return hipErrorInvalidValue;
+  T16Problem q[MAX_T16_GROUP];
+  int m = 0;
+  for (int i = 0; i < n; i++) {
+    if (p[i].gu_f > 0 && (p[i].gu_f % 32 || p[i].N != 2 * p[i].gu_f)) return hipErrorInvalidValue;
+    if (p[i].M == 0 || p[i].N == 0) continue;
+    q[m++] = tn_problem(p[i], nseg, kseg, overwrite);
+  }
+  return m == 0 ? hipSuccess : gemm_t16_group(q, m, tile, st);
 }
 
 bool gemm_swiglu_ok(int M, int f, int K, int64_t lda, int64_t ldw) {

@@ -40,6 +40,7 @@ hipError_t gemm_bf16_dma(int mode, const void* A, const void* B, void* C, const 
 // the tiles behind them (0 x 0 if there are none).  Host only.
 struct GemmPlan { int big_cols, tile_rows, tile_cols; };
 GemmPlan gemm_bf16_plan(int form, int M, int N, int K);
+void t16_tile_size(int form, int tile, int& rows, int& cols);  // T16_* of a form in rows and columns
 // weight gradient of several micro-batches in one launch: C[M,N] += sum_i A_i[kseg,M]^T * B_i[kseg,N], C fp32,
 // at most 16 pieces, all with the same strides; true if the operands fit the DMA path's 31-bit offsets
 bool gemm_tn_segments_ok(int kseg, int64_t lda, int64_t ldb);
@@ -48,8 +49,7 @@ bool gemm_tn_segments_ok(int kseg, int64_t lda, int64_t ldb);
 hipError_t gemm_bf16_tn_segments(const void* const* A, const void* const* B, int nseg, void* C, int M, int N, int kseg,
                                  int64_t lda, int64_t ldb, int64_t ldc, hipStream_t st, int gu_f = 0,
                                  bool overwrite = false);
-// several such products over pieces of the same depth, in one launch where their tiles together fill the chip better
-// (n <= MAX_T16_GROUP)
+// several such products (n <= MAX_T16_GROUP) over pieces of the same depth
 struct TnProduct {
   const void *const *A, *const *B;
   void* C;
@@ -57,7 +57,10 @@ struct TnProduct {
   int64_t lda, ldb, ldc;
   int gu_f;
 };
-hipError_t gemm_bf16_tn_group(const TnProduct* p, int n, int nseg, int kseg, hipStream_t st, bool overwrite);
+// the tile (T16_*) of one launch for all of them, where their tiles together fill the chip better, or -1: a launch (or two)
+// for each is faster.  Host only.
+int gemm_bf16_tn_group_tile(const TnProduct* p, int n, int nseg, int kseg);
+hipError_t gemm_bf16_tn_group(const TnProduct* p, int n, int tile, int nseg, int kseg, hipStream_t st, bool overwrite);
 // the 256x256 tiles of a problem on the 16x16x32 form of the matrix instruction (gemm_bf16_m16.hip); K % 8 == 0 where an
 // operand is stored [row][k], % 64 in the two fused forms
 hipError_t gemm_m16(int mode, const void* A, const void* B, void* C, const void* R, int M, int N, int K, int64_t lda,

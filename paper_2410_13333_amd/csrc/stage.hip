@@ -311,32 +311,52 @@ int layer_backward_data(mls_stage* s, int layer, const char* x, const char* e, i
   return MLS_OK;
 }
 
-// C[M,N] += sum_i A_i[T,M]^T B_i[T,N] over n micro-batches (fp32 C) for the weight gradients of a layer: in steps of 16
-// micro-batches on the bf16 DMA path, one launch per micro-batch and weight otherwise
-int wgrad(mls_stage* s, const mls::TnProduct (&p)[4], int n, bool ow) {
-  bool dma = s->dt == mls::DT_BF16;
-  for (auto& w : p) dma = dma && mls::gemm_tn_segments_ok(s->T, w.lda, w.ldb);  // always true when gu_f > 0
-  if (dma) {
-    for (int i = 0; i < n; i += 16) {
-      mls::TnProduct q[4];
-      for (int j = 0; j < 4; j++) {
-        q[j] = p[j];
-        q[j].A += i;
-        q[j].B += i;
-      }
-      LAUNCH(CLS_GEMM_TN, mls::gemm_bf16_tn_group(q, 4, n - i < 16 ? n - i : 16, s->T, s->st, ow && i == 0));
-    }
-    return MLS_OK;
+// The weight gradients of a layer (w_d, w_gu, w_o, w_qkv) whose fp32 gradients lie at g; ops[i]: the lists of both operands of
+// product i (null where only the sizes are asked for).
+void weight_grads(const mls_stage* s, float* g, const std::vector<const void*> (*ops)[2], mls::TnProduct (&p)[4]) {
+  const int h = s->c.hidden, f = s->c.ffn;
+  p[0] = {nullptr, nullptr, g ? g + s->off_wd : nullptr, f, h, s->ld_f, s->ld_h, h, 0};
+  p[1] = {nullptr, nullptr, g ? g + s->off_wgu : nullptr, h, 2 * f, s->ld_h, s->ld_gu, 2 * int64_t(f), s->fuse_gu ? f : 0};
+  p[2] = {nullptr, nullptr, g ? g + s->off_wo : nullptr, s->qd, h, s->ld_qd, s->ld_h, h, 0};
+  p[3] = {nullptr, nullptr, g ? g + s->off_wqkv : nullptr, h, s->qkvw, s->ld_h, s->ld_qkv, s->qkvw, 0};
+  for (int i = 0; ops && i < 4; i++) {
+    p[i].A = ops[i][0].data();
+    p[i].B = ops[i][1].data();
   }
-  for (auto& w : p) {
-    if (s->dt == mls::DT_BF16 && mls::gemm_tn_segments_ok(s->T, w.lda, w.ldb)) {
-      for (int i = 0; i < n; i += 16)
-        LAUNCH(CLS_GEMM_TN, mls::gemm_bf16_tn_segments(w.A + i, w.B + i, n - i < 16 ? n - i : 16, w.C, w.M, w.N, s->T, w.lda, w.ldb, w.ldc, s->st,
-                                                       w.gu_f, ow && i == 0));
+}
+
+// The tile of the launch that the four share over n <= 16 micro-batches, or -1: each has launches of its own
+int shared_wgrad_tile(const mls_stage* s, const mls::TnProduct (&p)[4], int n) {
+  bool dma = s->dt == mls::DT_BF16;
+  for (auto& w : p) dma = dma && mls::gemm_tn_segments_ok(s->T, w.lda, w.ldb);
+  return dma ? mls::gemm_bf16_tn_group_tile(p, 4, n, s->T) : -1;
+}
+
+// C[M,N] += sum_i A_i[T,M]^T B_i[T,N] over n micro-batches (fp32 C) for each of them: in steps of 16 micro-batches on the bf16
+// DMA path (always taken when gu_f > 0), one launch per micro-batch and weight otherwise
+int wgrad(mls_stage* s, const mls::TnProduct (&p)[4], int n, bool ow) {
+  for (int i = 0; i < n; i += 16) {
+    const int m = n - i < 16 ? n - i : 16;
+    mls::TnProduct q[4];
+    for (int j = 0; j < 4; j++) {
+      q[j] = p[j];
+      q[j].A += i;
+      q[j].B += i;
+    }
+    const bool over = ow && i == 0;
+    const int tile = shared_wgrad_tile(s, q, m);
+    if (tile >= 0) {
+      LAUNCH(CLS_GEMM_TN, mls::gemm_bf16_tn_group(q, 4, tile, m, s->T, s->st, over));
       continue;
     }
-    if (ow) HIP_TRY(mls::fill_zero_f32((float*)w.C, size_t(w.M) * w.N, s->st));  // this path only accumulates
-    for (int i = 0; i < n; i++) LAUNCH(CLS_GEMM_TN, gemm(s, mls::GEMM_TN, w.A[i], w.B[i], w.C, nullptr, w.M, w.N, s->T, w.lda, w.ldb, w.ldc));
+    for (auto& w : q) {
+      if (s->dt == mls::DT_BF16 && mls::gemm_tn_segments_ok(s->T, w.lda, w.ldb)) {
+        LAUNCH(CLS_GEMM_TN, mls::gemm_bf16_tn_segments(w.A, w.B, m, w.C, w.M, w.N, s->T, w.lda, w.ldb, w.ldc, s->st, w.gu_f, over));
+        continue;
+      }
+      if (over) HIP_TRY(mls::fill_zero_f32((float*)w.C, size_t(w.M) * w.N, s->st));  // this path only accumulates
+      for (int j = 0; j < m; j++) LAUNCH(CLS_GEMM_TN, gemm(s, mls::GEMM_TN, w.A[j], w.B[j], w.C, nullptr, w.M, w.N, s->T, w.lda, w.ldb, w.ldc));
+    }
   }
   return MLS_OK;
 }
@@ -552,7 +572,7 @@ int mls_stage_backward_ex(mls_stage* s, const void* dY, float* grads, int32_t n,
   const mls_config& c = s->c;
   const LayerStash& L = s->ls;
   const size_t act = size_t(s->T) * c.hidden * s->es;
-  const int h = c.hidden, f = c.ffn;
+  const int h = c.hidden;
   // Layer-major order: for each layer, top down, first the data-gradient chain of every micro-batch that has this
   // layer (entries may have been forwarded with different layer counts), then ONE weight-gradient contraction
   // per weight over all of them, so the fp32 gradient is read and written once per layer, not once per micro-batch.
@@ -572,10 +592,10 @@ int mls_stage_backward_ex(mls_stage* s, const void* dY, float* grads, int32_t n,
       HIP_TRY(copy2d(s, pp(i, k[i] & 1), s->ld_h, dy, h, s->T, h));
     }
   }
-  std::vector<const void*> az, ab, ao, aa, bdy, bdgu, bdh, bdqkv;
+  std::vector<const void*> wg[4][2];  // operands of the weight gradients: z dy | b dgu | o dh | a dqkv
   for (int l = kmax - 1; l >= 0; l--) {
     float* g = grads + size_t(l) * s->layer_params;
-    az.clear(); ab.clear(); ao.clear(); aa.clear(); bdy.clear(); bdgu.clear(); bdh.clear(); bdqkv.clear();
+    for (auto& w : wg) w[0].clear(), w[1].clear();
     int have = 0, seen = 0;  // micro-batches of this call that contain layer l
     for (int i = 0; i < n; i++) have += k[i] > l;
     for (int i = 0; i < n; i++) {
@@ -591,20 +611,13 @@ int mls_stage_backward_ex(mls_stage* s, const void* dY, float* grads, int32_t n,
       const char* dy = pp(i, (l + 1) & 1);
       void* dx = l == 0 ? (void*)((char*)dX + size_t(i) * act) : (void*)pp(i, l & 1);
       if (int rc = layer_backward_data(s, l, x, e, i, dy, s->ld_h, dx, l == 0 ? h : s->ld_h, g, ow, seen == 1, seen == have)) return rc;
-      az.push_back(e + L.z); ab.push_back(e + L.b); ao.push_back(e + L.o); aa.push_back(e + L.a);
-      bdy.push_back(dy);
-      bdgu.push_back(s->dgu + size_t(i) * s->mb_gu);
-      bdh.push_back(s->dh + size_t(i) * s->mb_h);
-      bdqkv.push_back(s->dqkv + size_t(i) * s->mb_qkv);
+      const void* ops[4][2] = {{e + L.z, dy}, {e + L.b, s->dgu + size_t(i) * s->mb_gu}, {e + L.o, s->dh + size_t(i) * s->mb_h},
+                               {e + L.a, s->dqkv + size_t(i) * s->mb_qkv}};
+      for (int w = 0; w < 4; w++) wg[w][0].push_back(ops[w][0]), wg[w][1].push_back(ops[w][1]);
     }
-    const int m = (int)az.size();
-    const mls::TnProduct w[4] = {
-        {az.data(), bdy.data(), g + s->off_wd, f, h, s->ld_f, s->ld_h, h, 0},
-        {ab.data(), bdgu.data(), g + s->off_wgu, h, 2 * f, s->ld_h, s->ld_gu, 2 * int64_t(f), s->fuse_gu ? f : 0},
-        {ao.data(), bdh.data(), g + s->off_wo, s->qd, h, s->ld_qd, s->ld_h, h, 0},
-        {aa.data(), bdqkv.data(), g + s->off_wqkv, h, s->qkvw, s->ld_h, s->ld_qkv, s->qkvw, 0},
-    };
-    if (int rc = wgrad(s, w, m, ow)) return rc;
+    mls::TnProduct w[4];
+    weight_grads(s, g, wg, w);
+    if (int rc = wgrad(s, w, (int)wg[0][0].size(), ow)) return rc;
   }
   // overwrite mode: the layers no entry of this call reached hold no gradient
   if (ow && kmax < c.max_layers)
@@ -777,6 +790,21 @@ int mls_stage_timing_read(mls_stage* s, double* ms, int64_t* launches) {
     s->tm.ms[i] = 0;
     s->tm.launches[i] = 0;
   }
+  return MLS_OK;
+}
+
+int mls_stage_wgrad_plan(const mls_config* cfg, int32_t n, int32_t* tile_rows, int32_t* tile_cols) {
+  if (!cfg || !tile_rows || !tile_cols) return fail(MLS_E_NULL, "mls_stage_wgrad_plan: null argument");
+  if (int rc = check_config(*cfg)) return rc;
+  if (n < 1) return fail(MLS_E_RANGE, "mls_stage_wgrad_plan: n_microbatches must be positive");
+  mls_stage tmp;
+  tmp.c = *cfg;
+  layout(&tmp);
+  mls::TnProduct p[4];
+  weight_grads(&tmp, nullptr, nullptr, p);
+  const int tile = shared_wgrad_tile(&tmp, p, n < 16 ? n : 16);
+  *tile_rows = *tile_cols = 0;
+  if (tile >= 0) mls::t16_tile_size(mls::T16_TN_SEGS, tile, *tile_rows, *tile_cols);
   return MLS_OK;
 }
 

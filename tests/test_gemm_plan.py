@@ -22,3 +22,16 @@ def test_refusals():
     for bad in [(5, 8, 8, 8), (-1, 8, 8, 8), (0, 0, 8, 8), (0, 8, 1 << 25, 8), (0, 8, 8, 0)]:
         with pytest.raises(mls.MlsError):
             mls.gemm_plan(*bad)
+
+
+def _cfg(hidden, nq, nkv, d, ffn, seq, mb, n, dtype=0):
+    return mls.MlsConfig(hidden, nq, nkv, d, ffn, seq, mb, 1, n, 1e-5, 10000.0, dtype, 0)
+
+
+def test_weight_gradients_share_a_launch_on_small_layers_only():
+    assert mls.wgrad_plan(_cfg(256, 4, 4, 64, 688, 128, 2, 1), 1) == (64, 64)
+    for n in (1, 4, 16, 40):
+        assert mls.wgrad_plan(_cfg(4096, 32, 32, 128, 11008, 4096, 1, n), n) == (0, 0)
+    assert mls.wgrad_plan(_cfg(256, 4, 4, 64, 688, 128, 2, 1, dtype=1), 1) == (0, 0)
+    with pytest.raises(mls.MlsError):
+        mls.wgrad_plan(_cfg(256, 4, 4, 64, 688, 128, 2, 1), 0)

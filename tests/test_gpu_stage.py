@@ -403,3 +403,25 @@ def test_weight_gradients_of_a_layer_in_one_launch(hidden, nq, nkv, d, ffn, seq,
         e = ((got - ref).norm() / ref.norm()).item()
         assert e <= 1e-5, (w, e)  # fp32 sums over at most 8200 products, fp32 rounding of the sum with g0
     st.close()
+
+
+@pytest.mark.parametrize("hidden,nq,nkv,d,ffn,seq,n,shared", [(256, 4, 4, 64, 688, 256, 2, True), (2048, 16, 16, 128, 5504, 2048, 2, False),
+                                                              (64, 1, 1, 64, 64, 8, 17, True)])
+def test_launch_counts_of_the_timing_classes(hidden, nq, nkv, d, ffn, seq, n, shared):
+    """Weight gradients count once per layer (and 16 micro-batches) where they share a launch, four times where they do not."""
+    import torch
+    import paper_2410_13333_amd as mls
+    layers = 2
+    st = mls.Stage(hidden, nq, nkv, d, ffn, seq, 1, layers, n, seed=1)
+    assert (mls.wgrad_plan(st.cfg, n) != (0, 0)) == shared
+    x = torch.randn(n, 1, seq, hidden, device="cuda").to(torch.bfloat16)
+    y, dx, g = torch.empty_like(x[0]), torch.empty_like(x), torch.zeros(st.grad_elems, device="cuda")
+    st.timing(True)
+    for i in range(n):
+        st.forward(x[i], layers, y)
+    st.backward(x, g, n, dx)
+    torch.cuda.synchronize()
+    launches = {k: v[1] for k, v in st.timing_read().items()}
+    st.close()
+    assert launches["gemm_wgrad"] == layers * -(-n // 16) * (1 if shared else 4)
+    assert launches["gemm_fwd"] == launches["gemm_dgrad"] == 4 * layers * n
