@@ -324,7 +324,10 @@ inline int blocks_for(int64_t n) { return int((n + TH - 1) / TH); }
 size_t align256(size_t v) { return (v + 255) & ~size_t(255); }
 // Row strides as in a stage: the columns from n on, up to whole 64-deep k-tiles, are zero and may be contracted over.
 int64_t depth64(int64_t n) { return (n + 63) / 64 * 64; }
-int64_t padded(int64_t n) { return depth64(n) % 256 == 0 ? depth64(n) + 64 : depth64(n); }
+int64_t padded(int64_t n, int dt) {
+  if (dt == mls::DT_BF16) n = depth64(n);  // (no fp32 kernel reads them)
+  return n % 256 == 0 ? n + 64 : n;
+}
 
 }  // namespace
 
@@ -446,8 +449,8 @@ int mls_ends_init(const mls_ends_config* cfg, uint64_t seed, void* hip_stream, m
   s->es = c.dtype == MLS_BF16 ? 2 : 4;
   s->T = int(T);
   s->st = (hipStream_t)hip_stream;
-  s->ld_h = padded(c.hidden);
-  s->ld_v = padded(c.vocab);
+  s->ld_h = padded(c.hidden, s->dt);
+  s->ld_v = padded(c.vocab, s->dt);
   const size_t h = c.hidden, V = c.vocab;
   s->off_e = 0;
   s->off_g = V * h;

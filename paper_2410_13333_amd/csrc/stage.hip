@@ -173,7 +173,11 @@ int check_config(const mls_config& c) {
 // fused epilogues the 256x256 kernel takes whole 64-deep k-tiles only.  Forward products of a layer of hidden and ffn width 8160,
 // 64 / 8 heads, 8547 tokens: 5.9 ms unpadded, on tiles of the 32x32x16 instruction that took any depth, 4.8 padded.
 int64_t depth64(int64_t n) { return (n + 63) / 64 * 64; }
-int64_t padded(int64_t n) { return depth64(n) % 256 == 0 ? depth64(n) + 64 : depth64(n); }
+// fp32 storage has no kernel that reads them: its rows are only kept off power-of-two strides.
+int64_t padded(int64_t n, int dt) {
+  if (dt == mls::DT_BF16) n = depth64(n);
+  return n % 256 == 0 ? n + 64 : n;
+}
 
 // the six parameter tensors of a layer: public offset, internal offset, rows, cols, internal row stride; ld_t > 0: offset and
 // row stride of the transposed copy (bf16 storage)
@@ -378,11 +382,11 @@ void layout(mls_stage* s) {
   s->off_wgu = s->off_g2 + h;
   s->off_wd = s->off_wgu + h * 2 * f;
   s->layer_params = s->off_wd + f * h;
-  s->ld_h = padded(c.hidden);
-  s->ld_qkv = padded(s->qkvw);
-  s->ld_qd = padded(s->qd);
-  s->ld_gu = padded(2 * int64_t(c.ffn));
-  s->ld_f = padded(c.ffn);
+  s->ld_h = padded(c.hidden, s->dt);
+  s->ld_qkv = padded(s->qkvw, s->dt);
+  s->ld_qd = padded(s->qd, s->dt);
+  s->ld_gu = padded(2 * int64_t(c.ffn), s->dt);
+  s->ld_f = padded(c.ffn, s->dt);
   s->ioff_g1 = 0;
   s->ioff_wqkv = h;
   s->ioff_wo = s->ioff_wqkv + h * s->ld_qkv;

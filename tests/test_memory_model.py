@@ -68,3 +68,20 @@ def test_cap_from_the_report_is_the_largest_stage_that_fits(pp, j):
         m = mls.Stage.memory(sh, max_layers=layers, max_inflight=keep)
         return m["total_bytes"] + layers * (m["grad_bytes_per_layer"] + 12 * synth.layer_param_elems(sh))
     assert need(cap) <= C - G < need(cap + 1)
+
+
+def test_fp32_rows_are_padded_off_powers_of_two_only():
+    """bf16 rows are padded to whole 64-deep k-tiles; no fp32 kernel reads such columns."""
+    import paper_2410_13333_amd as mls
+
+    def up(n):
+        return (n + 255) // 256 * 256
+    sh = synth.StageShape(hidden=72, n_q_heads=3, n_kv_heads=1, head_dim=16, ffn=88, seq=50, micro_batch=2, layers=1,
+                          microbatches=1, dtype="fp32")
+    T, widths = 100, (72, 72, 5 * 16, 3 * 16, 72, 72, 2 * 88, 88)  # x a qkv o h b gu z
+    m = mls.Stage.memory(sh, max_layers=1, max_inflight=1)
+    assert m["stash_bytes_per_layer_microbatch"] == sum(up(4 * T * w) for w in widths) + 2 * up(4 * T) + up(4 * T * 3)
+    assert m["param_bytes_per_layer"] == 4 * synth.layer_param_elems(sh)
+    wide = sh.with_(hidden=256)
+    assert mls.Stage.memory(wide, max_layers=1, max_inflight=1)["param_bytes_per_layer"] == 4 * (
+        synth.layer_param_elems(wide) + 64 * (3 * 16 + 88))  # the rows of w_o and w_d
