@@ -211,10 +211,10 @@ int mls_gemm(int32_t dtype, int32_t mode, const void* A, int64_t lda, const void
  * Operands of 2 GiB and more run on a kernel of their own.  Errors: MLS_E_NULL, MLS_E_CONFIG. */
 int mls_gemm_plan(int32_t mode, int64_t M, int64_t N, int64_t K, int64_t* big_cols, int32_t* tile_rows, int32_t* tile_cols);
 
-/* The same for the weight gradients of a layer of this configuration over n_microbatches: the tile of the launch that all
+/* The same for the weight gradients of a layer in mls_stage_backward_ex over n_microbatches with these flags: the tile of the launch that all
  * four share, or 0 x 0 if each has launches of its own (then mls_gemm_plan with mode 2 and K = tokens of all micro-batches
  * tells their tiles; 16 micro-batches go into a launch).  Errors: MLS_E_NULL, MLS_E_CONFIG, MLS_E_RANGE. */
-int mls_stage_wgrad_plan(const mls_config* cfg, int32_t n_microbatches, int32_t* tile_rows, int32_t* tile_cols);
+int mls_stage_wgrad_plan(const mls_config* cfg, int32_t n_microbatches, int32_t flags, int32_t* tile_rows, int32_t* tile_cols);
 
 /* Message for the last error returned on this thread (host string, never NULL). */
 const char* mls_last_error(void);

@@ -80,7 +80,7 @@ def lib():
         L.mls_stage_memory.argtypes = [C.POINTER(MlsConfig), C.POINTER(MlsMemory)]
         L.mls_gemm.argtypes = [i32, i32, vp, i64, vp, i64, vp, i64, vp, i64, i64, i64, vp]
         L.mls_gemm_plan.argtypes = [i32, i64, i64, i64, C.POINTER(i64), C.POINTER(i32), C.POINTER(i32)]
-        L.mls_stage_wgrad_plan.argtypes = [C.POINTER(MlsConfig), i32, C.POINTER(i32), C.POINTER(i32)]
+        L.mls_stage_wgrad_plan.argtypes = [C.POINTER(MlsConfig), i32, i32, C.POINTER(i32), C.POINTER(i32)]
         L.mls_last_error.restype = C.c_char_p
         L.mls_ends_init.argtypes = [C.POINTER(MlsEndsConfig), u64, vp, C.POINTER(vp)]
         L.mls_ends_free.argtypes = [vp]
@@ -273,10 +273,10 @@ def gemm_plan(mode, M, N, K):
     return big.value, r.value, c.value
 
 
-def wgrad_plan(cfg, n_microbatches):
+def wgrad_plan(cfg, n_microbatches, overwrite=False):
     """(rows, columns) of the tiles of the launch that a layer's four weight gradients share, (0, 0) if they do not."""
     r, c = C.c_int32(), C.c_int32()
-    _check(lib().mls_stage_wgrad_plan(C.byref(cfg), n_microbatches, C.byref(r), C.byref(c)))
+    _check(lib().mls_stage_wgrad_plan(C.byref(cfg), n_microbatches, int(overwrite), C.byref(r), C.byref(c)))
     return r.value, c.value
 
 

@@ -15,52 +15,63 @@ struct Plan {
   double us;
 };
 
-// Estimated microseconds of M x N outputs over a contraction of `it` 64-deep k-tiles, from a fit to stand-alone timings of
-// every tile size at 66 shapes (the products of layers with 135 to 4096 tokens and hidden widths 256 to 8192, all three
-// forms, N(0,1) operands).
-//   256x256, 256x128, 128x128: one workgroup per CU.  A round costs base + it * c; c depends on how full the chip is
-//     (clock and L2 bandwidth are shared): 256x256 1.00 us per k-tile on a few CUs, 1.38 on all; 256x128 0.60 and 0.85;
-//     128x128 0.36 and 0.51.
-//   128x64, 64x64: two and three workgroups per CU.  A lone workgroup is a chain of waits (0.26, 0.21 us per k-tile);
-//     past that the loads of a CU's workgroups add up.
-// The plan with the smallest estimate is on average 0.4 % slower than the fastest one measured at those shapes; the worst
-// is 12 % (768 x 4096 over 1008: 18 us instead of 16).
+// Estimated microseconds of M x N outputs over a contraction of `it` 64-deep k-tiles.
+//   256x256, 256x128, 128x128: one workgroup per CU.  A round costs base + it * c; c depends on how full the chip is (clock and
+//     L2 bandwidth are shared).
+//   128x64, 64x64: two and three workgroups per CU.  A lone workgroup is a chain of waits; past that the loads of a CU's
+//     workgroups add up.
+// Results in bf16 (NN, NT): fitted to stand-alone timings of every tile size at 66 shapes (the products of layers with 135 to
+// 4096 tokens and hidden widths 256 to 8192, N(0,1) operands).  The plan with the smallest estimate is on average 0.4 %
+// slower than the fastest one measured there; the worst is 12 % (768 x 4096 over 1008: 18 us instead of 16).
+// Results in fp32 (TN): twice the bytes where they are stored, four times where they are added to, which a tile that has its CU
+// for itself moves while the matrix cores idle: fitted apart, to the weight gradients of 130 layers inside a stage (48 to 5400
+// tokens, hidden 192 to 8192), every tile size, in one launch and apart; 3 to 15 % (rms, from 256x256 to 64x64).  Choosing by it
+// between a shared launch and launches apart costs 1.3 % on average where results are added to and 1.7 % where they are stored
+// (worst: 18 and 16 %); with the figures of bf16 results it cost 6.6 and 3.0 % (73 and 61 %: hidden 1192, 186 tokens).
+// The fused epilogues have one 64x128 kernel where the plan says 128x64 or 64x64.
 enum { TILE_M16 = -1 };
+enum Result { R_BF16, R_F32_STORE, R_F32_ADD };
+constexpr double LAUNCH_GAP = 1.5;
 int64_t tiles_of(int tile, int64_t M, int64_t N) {
   const int bm = tile == mls::T16_64x64 ? 64 : tile == TILE_M16 || tile == mls::T16_256x128 ? 256 : 128;
   const int bn = tile == TILE_M16 ? 256 : tile == mls::T16_256x128 || tile == mls::T16_128x128 ? 128 : 64;
   return ((M + bm - 1) / bm) * ((N + bn - 1) / bn);
 }
-double estimate(int tile, int64_t w, int64_t it) {  // w tiles
-  struct Round { double lo, hi, base; };
-  struct Load { double lone, c0, c1, base; };
-  const Round r = tile == TILE_M16 ? Round{1.00, 1.38, 7.0}
-                  : tile == mls::T16_256x128 ? Round{0.60, 0.85, 5.5} : Round{0.36, 0.51, 4.5};
+double estimate(Result res, int tile, int64_t w, int64_t it) {  // w tiles
   if (tile == TILE_M16 || tile == mls::T16_256x128 || tile == mls::T16_128x128) {
-    const int64_t full = w / CUS;
-    const double part = double(w % CUS) / CUS;
-    return double(full) * (double(it) * r.hi + r.base) + (part > 0 ? double(it) * (r.lo + (r.hi - r.lo) * part) + r.base : 0.0);
+    // share: the part of `base` that a nearly empty round pays
+    struct Round { double lo, hi, base, share; };
+    const Round rounds[3][3] = {{{1.00, 1.38, 7.0, 1}, {0.60, 0.85, 5.5, 1}, {0.36, 0.51, 4.5, 1}},
+                                {{0.945, 1.269, 17.1, 0.9}, {0.719, 0.829, 10.0, 1}, {0.464, 0.529, 6.2, 1}},
+                                {{1.021, 1.236, 47.9, 0.5}, {0.741, 0.823, 23.1, 0.63}, {0.454, 0.534, 12.1, 0.74}}};
+    const Round& r = rounds[res][tile == TILE_M16 ? 0 : tile == mls::T16_256x128 ? 1 : 2];
+    const double part = double(w % CUS) / CUS, full = double(w / CUS) * (double(it) * r.hi + r.base);
+    return part > 0 ? full + double(it) * (r.lo + (r.hi - r.lo) * part) + r.base * (r.share + (1 - r.share) * part) : full;
   }
-  const Load l = tile == mls::T16_128x64 ? Load{0.26, 0.20, 0.215, 4.0} : Load{0.21, 0.15, 0.165, 3.2};
-  const double load = double(w) / CUS;
-  return l.base * std::max(1.0, load / 2) + double(it) * std::max(l.lone, l.c0 + l.c1 * load);
+  struct Load { double lone, c0, c1, base, each; };  // each: per workgroup of a CU
+  const Load loads[3][2] = {{{0.26, 0.20, 0.215, 4.0, 0}, {0.21, 0.15, 0.165, 3.2, 0}},
+                            {{0.344, 0.078, 0.319, 4.4, 2.11}, {0.266, 0.121, 0.195, 3.5, 1.05}},
+                            {{0.366, 0.063, 0.316, 5.0, 4.24}, {0.286, 0.076, 0.200, 3.7, 1.97}}};
+  const Load& l = loads[res][tile == mls::T16_128x64 ? 0 : 1];
+  const double load = double(w) / CUS, loop = double(it) * std::max(l.lone, l.c0 + l.c1 * load);
+  return loop + (res == R_BF16 ? l.base * std::max(1.0, load / 2) : l.base + l.each * load);
 }
-double estimate(int tile, int64_t M, int64_t N, int64_t it) { return estimate(tile, tiles_of(tile, M, N), it); }
+double estimate(Result res, int tile, int64_t M, int64_t N, int64_t it) { return estimate(res, tile, tiles_of(tile, M, N), it); }
 
 // m16: the 256x256 kernel takes the problem (the fused forms need whole 64-deep k-tiles there)
-Plan plan(int M, int N, int64_t K, bool m16) {
+Plan plan(Result res, int M, int N, int64_t K, bool m16) {
   const int64_t it = (K + 63) / 64, tm = (M + 255) / 256, tn = (N + 255) / 256;
   const int n1 = int(tm * tn / CUS * CUS / tm) * 256;  // columns that whole rounds of 256x256 tiles cover
   Plan best = {N, mls::T16_256x128, 0};
-  double t = m16 ? estimate(TILE_M16, M, N, it) : HUGE_VAL;
+  double t = m16 ? estimate(res, TILE_M16, M, N, it) : HUGE_VAL;
   for (int tile : {mls::T16_256x128, mls::T16_128x128, mls::T16_128x64, mls::T16_64x64}) {
-    const double all = estimate(tile, M, N, it);
+    const double all = estimate(res, tile, M, N, it);
     if (all < t) {
       t = all;
       best = {0, tile, 0};
     }
     if (!m16 || n1 == 0 || n1 >= N) continue;
-    const double both = estimate(TILE_M16, M, n1, it) + estimate(tile, M, N - n1, it) + 1.5;  // (and one more launch)
+    const double both = estimate(res, TILE_M16, M, n1, it) + estimate(res, tile, M, N - n1, it) + LAUNCH_GAP;
     if (both < t) {
       t = both;
       best = {n1, tile, 0};
@@ -87,12 +98,16 @@ mls::T16Problem columns_from(mls::T16Problem p, int n1) {
 
 bool fused(int form) { return form == mls::T16_NT_SWIGLU || form == mls::T16_NT_ROPE; }
 
-Plan plan(int form, int M, int N, int64_t K) { return plan(M, N, K, !fused(form) || K % 64 == 0); }
+Plan plan(int form, bool store, int M, int N, int64_t K) {
+  const Result res = form != mls::T16_TN && form != mls::T16_TN_SEGS ? R_BF16 : store ? R_F32_STORE : R_F32_ADD;
+  return plan(res, M, N, K, !fused(form) || K % 64 == 0);
+}
 
 // `big(n1)` runs the leading n1 columns on 256x256 tiles
 template <class Big>
 hipError_t run(const mls::T16Problem& p, hipStream_t st, Big&& big) {
-  const Plan pl = plan(p.form, p.M, p.N, int64_t(p.K) * std::max(1, p.nseg));
+  const int64_t depth = p.nseg > 0 ? (int64_t(p.K) + 63) / 64 * 64 * p.nseg : p.K;  // (every piece ends with a k-tile of its own)
+  const Plan pl = plan(p.form, p.form == mls::T16_TN_SEGS && p.ldx != 0, p.M, p.N, depth);
   if (pl.n1 > 0)
     if (hipError_t e = big(pl.n1)) return e;
   if (pl.n1 == p.N) return hipSuccess;
@@ -152,7 +167,7 @@ void t16_tile_size(int form, int tile, int& rows, int& cols) {
 }
 
 GemmPlan gemm_bf16_plan(int form, int M, int N, int K) {
-  const Plan p = plan(form, M, N, K);
+  const Plan p = plan(form, false, M, N, K);
   GemmPlan g = {p.n1, 0, 0};
   if (p.n1 < N) t16_tile_size(form, p.tile, g.tile_rows, g.tile_cols);
   return g;
@@ -177,16 +192,16 @@ hipError_t gemm_bf16_tn_segments(const void* const* A, const void* const* B, int
 // layer, apart -> in one (us): hidden 256, 256 tokens 25 -> 9; 1024 / ffn 2728, 2000 tokens 112 -> 80; 768, 2 x 1024 tokens
 // 80 -> 45; 1536, 700 tokens 125 -> 97 (the fastest tile: 89); 512, 4 x 4096 tokens 387 -> 157; 3072, 600 tokens 422 -> 420;
 // 2048, 2 x 2048 tokens stay apart: 469, in one 517.
-int gemm_bf16_tn_group_tile(const TnProduct* p, int n, int nseg, int kseg) {
-  const int64_t depth = int64_t(kseg) * nseg, it = (depth + 63) / 64;
-  double apart = 0;
+int gemm_bf16_tn_group_tile(const TnProduct* p, int n, int nseg, int kseg, bool overwrite) {
+  const int64_t it = int64_t(nseg) * ((kseg + 63) / 64), depth = it * 64;
+  double apart = -LAUNCH_GAP;
   for (int i = 0; i < n; i++)
-    if (p[i].M > 0 && p[i].N > 0) apart += plan(T16_TN_SEGS, p[i].M, p[i].N, depth).us;
+    if (p[i].M > 0 && p[i].N > 0) apart += LAUNCH_GAP + plan(T16_TN_SEGS, overwrite, p[i].M, p[i].N, depth).us;
   int best = -1;
   for (int tile : {T16_256x128, T16_128x128, T16_128x64, T16_64x64}) {
     int64_t w = 0;
     for (int i = 0; i < n; i++) w += tiles_of(tile, p[i].M, p[i].N);
-    const double t = estimate(tile, w, it);
+    const double t = estimate(overwrite ? R_F32_STORE : R_F32_ADD, tile, w, it);
     if (t < apart) {
       apart = t;
       best = tile;

@@ -59,7 +59,7 @@ struct TnProduct {
 };
 // the tile (T16_*) of one launch for all of them, where their tiles together fill the chip better, or -1: a launch (or two)
 // for each is faster.  Host only.
-int gemm_bf16_tn_group_tile(const TnProduct* p, int n, int nseg, int kseg);
+int gemm_bf16_tn_group_tile(const TnProduct* p, int n, int nseg, int kseg, bool overwrite);
 hipError_t gemm_bf16_tn_group(const TnProduct* p, int n, int tile, int nseg, int kseg, hipStream_t st, bool overwrite);
 // the 256x256 tiles of a problem on the 16x16x32 form of the matrix instruction (gemm_bf16_m16.hip); K % 8 == 0 where an
 // operand is stored [row][k], % 64 in the two fused forms

@@ -330,10 +330,10 @@ void weight_grads(const mls_stage* s, float* g, const std::vector<const void*> (
 }
 
 // The tile of the launch that the four share over n <= 16 micro-batches, or -1: each has launches of its own
-int shared_wgrad_tile(const mls_stage* s, const mls::TnProduct (&p)[4], int n) {
+int shared_wgrad_tile(const mls_stage* s, const mls::TnProduct (&p)[4], int n, bool overwrite) {
   bool dma = s->dt == mls::DT_BF16;
   for (auto& w : p) dma = dma && mls::gemm_tn_segments_ok(s->T, w.lda, w.ldb);
-  return dma ? mls::gemm_bf16_tn_group_tile(p, 4, n, s->T) : -1;
+  return dma ? mls::gemm_bf16_tn_group_tile(p, 4, n, s->T, overwrite) : -1;
 }
 
 // C[M,N] += sum_i A_i[T,M]^T B_i[T,N] over n micro-batches (fp32 C) for each of them: in steps of 16 micro-batches on the bf16
@@ -348,7 +348,7 @@ int wgrad(mls_stage* s, const mls::TnProduct (&p)[4], int n, bool ow) {
       q[j].B += i;
     }
     const bool over = ow && i == 0;
-    const int tile = shared_wgrad_tile(s, q, m);
+    const int tile = shared_wgrad_tile(s, q, m, over);
     if (tile >= 0) {
       LAUNCH(CLS_GEMM_TN, mls::gemm_bf16_tn_group(q, 4, tile, m, s->T, s->st, over));
       continue;
@@ -797,16 +797,17 @@ int mls_stage_timing_read(mls_stage* s, double* ms, int64_t* launches) {
   return MLS_OK;
 }
 
-int mls_stage_wgrad_plan(const mls_config* cfg, int32_t n, int32_t* tile_rows, int32_t* tile_cols) {
+int mls_stage_wgrad_plan(const mls_config* cfg, int32_t n, int32_t flags, int32_t* tile_rows, int32_t* tile_cols) {
   if (!cfg || !tile_rows || !tile_cols) return fail(MLS_E_NULL, "mls_stage_wgrad_plan: null argument");
   if (int rc = check_config(*cfg)) return rc;
+  if (flags & ~MLS_BWD_OVERWRITE) return fail(MLS_E_CONFIG, "mls_stage_wgrad_plan: unknown flag");
   if (n < 1) return fail(MLS_E_RANGE, "mls_stage_wgrad_plan: n_microbatches must be positive");
   mls_stage tmp;
   tmp.c = *cfg;
   layout(&tmp);
   mls::TnProduct p[4];
   weight_grads(&tmp, nullptr, nullptr, p);
-  const int tile = shared_wgrad_tile(&tmp, p, n < 16 ? n : 16);
+  const int tile = shared_wgrad_tile(&tmp, p, n < 16 ? n : 16, (flags & MLS_BWD_OVERWRITE) != 0);
   *tile_rows = *tile_cols = 0;
   if (tile >= 0) mls::t16_tile_size(mls::T16_TN_SEGS, tile, *tile_rows, *tile_cols);
   return MLS_OK;

@@ -12,6 +12,17 @@ def rel_err(got, ref):
     return float(np.linalg.norm(got - ref) / n) if n > 0 else float(np.linalg.norm(got))
 
 
+def worst_block(got, ref):
+    """Largest relative error of a CUDA matrix over blocks of 64 rows and over blocks of 64 columns (the last ones ragged), so
+    that a wrong edge shows; ref in fp64."""
+    import torch
+    d, worst = got.double() - ref, 0.0
+    for dim in (0, 1):
+        for e, n in zip(torch.split(d, 64, dim), torch.split(ref, 64, dim)):
+            worst = max(worst, (e.norm() / n.norm()).item())
+    return worst
+
+
 to_device = synth.to_device      # synth storage array -> CUDA tensor of the storage type
 
 

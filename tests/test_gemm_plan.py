@@ -3,6 +3,53 @@ import pytest
 
 import paper_2410_13333_amd as mls
 
+# Shapes that the GPU tests take through each tile size, with the plan they rely on: (leading columns on 256x256 tiles, rows,
+# columns of the tiles behind them).  test_plan_of_the_tested_shapes fails when a change of the plan drops one.
+GEMM_TILES = [  # NN and NT
+    ((72, 136, 24), (0, 64, 64)), ((72, 136, 1032), (0, 64, 64)), ((1000, 2056, 1096), (0, 128, 64)), ((2040, 2040, 392), (0, 128, 128)),
+    ((2000, 3000, 1032), (0, 256, 128)), ((4088, 4096, 192), (4096, 0, 0)), ((4096, 4360, 136), (4096, 64, 64)),
+    ((4088, 5128, 192), (4096, 128, 64)), ((4088, 5064, 264), (4096, 128, 128)), ((4088, 5448, 64), (4096, 256, 128))]
+TN_TILES = [
+    ((72, 136, 136), (0, 64, 64)), ((4088, 456, 1096), (0, 128, 64)), ((3848, 968, 136), (0, 128, 128)), ((2040, 3912, 264), (0, 256, 128)),
+    ((4088, 3720, 520), (3720, 0, 0)), ((4088, 4104, 776), (4096, 64, 64)), ((4088, 5128, 800), (4096, 128, 64)),
+    ((3848, 4936, 776), (4096, 128, 128)), ((3848, 5832, 776), (4096, 256, 128))]
+# hidden, q heads, kv heads, head dim, seq, micro-batch
+ROPE_TILES = [
+    ((264, 3, 1, 64, 129, 1), (0, 64, 128)), ((264, 3, 1, 128, 129, 1), (0, 64, 128)), ((264, 48, 16, 128, 129, 2), (0, 128, 128)),
+    ((520, 48, 16, 64, 257, 2), (0, 128, 128)), ((264, 48, 16, 128, 257, 2), (0, 256, 128)), ((72, 32, 16, 64, 700, 2), (0, 256, 128)),
+    ((328, 48, 16, 128, 999, 2), (8192, 128, 128)), ((328, 64, 16, 128, 999, 2), (8192, 256, 128))]
+# hidden, ffn, tokens
+SWIGLU_TILES = [
+    ((136, 64, 72), (0, 64, 128)), ((520, 2720, 514), (0, 128, 128)), ((520, 4128, 700), (0, 256, 128)),
+    ((264, 4128, 999), (8256, 0, 0)), ((136, 4128, 1998), (8192, 64, 128)), ((136, 2720, 4100), (3840, 256, 128))]
+# hidden, q heads, kv heads, head dim, ffn, seq, micro-batch, micro-batches: one shared launch, stored or added to
+WGRAD_TILES = [
+    ((264, 1, 1, 64, 680, 129, 1, 1), (64, 64)), ((264, 1, 1, 64, 352, 129, 1, 1), (64, 64)),
+    ((520, 8, 2, 64, 680, 300, 2, 3), (128, 64)), ((1032, 4, 2, 64, 352, 700, 2, 1), (128, 64)),
+    ((1032, 8, 2, 64, 680, 129, 1, 2), (128, 128)), ((520, 2, 1, 64, 2048, 129, 1, 2), (128, 128)),
+    ((2056, 4, 1, 128, 680, 129, 1, 3), (256, 128)), ((1032, 4, 1, 64, 2048, 129, 1, 3), (256, 128))]
+
+
+def _cfg(hidden, nq, nkv, d, ffn, seq, mb, n, dtype=0):
+    return mls.MlsConfig(hidden, nq, nkv, d, ffn, seq, mb, 1, n, 1e-5, 10000.0, dtype, 0)
+
+
+def _k_tiles(n):
+    return (n + 63) // 64 * 64
+
+
+def test_plan_of_the_tested_shapes():
+    for shape, plan in GEMM_TILES:
+        assert mls.gemm_plan(0, *shape) == mls.gemm_plan(1, *shape) == plan, shape
+    for shape, plan in TN_TILES:
+        assert mls.gemm_plan(2, *shape) == plan, shape
+    for (h, nq, nkv, d, seq, mb), plan in ROPE_TILES:
+        assert mls.gemm_plan(4, seq * mb, (nq + 2 * nkv) * d, _k_tiles(h)) == plan, (h, nq, nkv, d, seq, mb)
+    for (h, ffn, T), plan in SWIGLU_TILES:
+        assert mls.gemm_plan(3, T, 2 * ffn, _k_tiles(h)) == plan, (h, ffn, T)
+    for shape, tile in WGRAD_TILES:
+        assert mls.wgrad_plan(_cfg(*shape), shape[-1]) == mls.wgrad_plan(_cfg(*shape), shape[-1], True) == tile, shape
+
 
 # about a whole round or more of 256x256 tiles: the contraction length does not decide whether they are used
 @pytest.mark.parametrize("mode,M,N,K", [(0, 8192, 8192, 8168), (1, 8192, 8192, 8168), (0, 4096, 11008, 1000), (1, 4096, 4096, 4104),
@@ -24,10 +71,6 @@ def test_refusals():
             mls.gemm_plan(*bad)
 
 
-def _cfg(hidden, nq, nkv, d, ffn, seq, mb, n, dtype=0):
-    return mls.MlsConfig(hidden, nq, nkv, d, ffn, seq, mb, 1, n, 1e-5, 10000.0, dtype, 0)
-
-
 def test_weight_gradients_share_a_launch_on_small_layers_only():
     assert mls.wgrad_plan(_cfg(256, 4, 4, 64, 688, 128, 2, 1), 1) == (64, 64)
     for n in (1, 4, 16, 40):
@@ -35,3 +78,10 @@ def test_weight_gradients_share_a_launch_on_small_layers_only():
     assert mls.wgrad_plan(_cfg(256, 4, 4, 64, 688, 128, 2, 1, dtype=1), 1) == (0, 0)
     with pytest.raises(mls.MlsError):
         mls.wgrad_plan(_cfg(256, 4, 4, 64, 688, 128, 2, 1), 0)
+
+
+def test_short_contractions_into_fp32_results_take_small_tiles():
+    """What such a product costs is the traffic of its result, which several workgroups on a CU overlap with the products."""
+    assert mls.wgrad_plan(_cfg(1192, 32, 32, 64, 4120, 186, 1, 1), 1)[1] == 64
+    assert mls.wgrad_plan(_cfg(2048, 32, 4, 128, 4872, 49, 1, 1), 1)[1] == 64
+    assert mls.gemm_plan(2, 4120, 1192, 186)[0] == 0

@@ -2,7 +2,8 @@
 import numpy as np
 import pytest
 
-from tests.helpers import rel_err, to_host64
+from tests.helpers import rel_err, to_host64, worst_block
+from tests.test_gemm_plan import GEMM_TILES, TN_TILES
 
 pytestmark = pytest.mark.gpu
 
@@ -62,34 +63,49 @@ def test_bf16_16x16x32_kernel_at_awkward_depths(M, N, K):
     assert rel_err(to_host64(acc), 0.5 + 2 * ref) < 1e-5
 
 
-@pytest.mark.parametrize("K", [8, 40, 72, 104, 136, 200, 264, 328])
-def test_bf16_256_tiles_over_contractions_that_end_inside_a_tile(K):
-    """256x256 tiles with a remainder beside them; what lies behind the end of the contraction in memory (the rest of a row,
-    the rows behind the last one) is NaN and must not be looked at."""
+def _framed(r, c, g):
+    """An r x c matrix of N(0, 1) in a buffer that is wider and longer, NaN around it: what lies behind the end of the
+    contraction in memory (the rest of a row, the rows behind the last one) must not be looked at."""
+    import torch
+    buf = torch.full((r + 72, c + 72), float("nan"), dtype=torch.bfloat16, device="cuda")
+    buf[:r, :c] = torch.randn(r, c, device="cuda", generator=g)
+    return buf[:r, :c]
+
+
+def _framed_product(mode, M, N, K):
     import torch
     import paper_2410_13333_amd as mls
-    M, N = 3848, 4360
-    for mode in (0, 1, 2):
-        assert mls.gemm_plan(mode, M, N, K)[0] == 4096
-    g = torch.Generator(device="cuda").manual_seed(K)
-
-    def framed(r, c):  # an r x c matrix in a buffer that is wider and longer
-        buf = torch.full((r + 72, c + 72), float("nan"), dtype=torch.bfloat16, device="cuda")
-        buf[:r, :c] = torch.randn(r, c, device="cuda", generator=g)
-        return buf[:r, :c]
-    a, b, at, bt = framed(M, K), framed(K, N), framed(K, M), framed(N, K)
-    at.copy_(a.t())
-    bt.copy_(b.t())
-    ref = a.double() @ b.double()
-    off = lambda c, want: ((c.double() - want).norm() / want.norm()).item()  # noqa: E731
+    g = torch.Generator(device="cuda").manual_seed(M + 3 * N + 7 * K)
+    a, b = _framed(K, M, g) if mode == 2 else _framed(M, K, g), _framed(N, K, g) if mode == 1 else _framed(K, N, g)
+    ref = (a.double().t().contiguous() if mode == 2 else a.double()) @ (b.double().t().contiguous() if mode == 1 else b.double())
+    if mode == 2:
+        c = torch.full((M, N), 0.5, device="cuda")
+        mls.gemm(2, a, b, c)
+        # fp32 sums: a rounding of 6e-8 per step of the chain and the addition
+        assert worst_block(c, 0.5 + ref) < 1e-5
+        return
     c = torch.empty(M, N, dtype=torch.bfloat16, device="cuda")
-    mls.gemm(0, a, b, c)
-    assert off(c, ref) < 4e-3
-    mls.gemm(1, a, bt, c)
-    assert off(c, ref) < 4e-3
-    acc = torch.full((M, N), 0.5, device="cuda")
-    mls.gemm(2, at, b, acc)
-    assert off(acc, 0.5 + ref) < 1e-5
+    mls.gemm(mode, a, b, c)
+    assert worst_block(c, ref) < 4e-3  # one rounding to bf16
+    if mode == 0:
+        r = torch.randn(M, N, device="cuda", generator=g).to(torch.bfloat16)
+        mls.gemm(0, a, b, c, r)
+        assert worst_block(c, ref + r.double()) < 4e-3
+
+
+# a depth that ends inside a k-tile in every way, on 256x256 tiles with a remainder beside them (NN, NT; TN from 1000 on)
+@pytest.mark.parametrize("mode,K", [(m, K) for m in (0, 1) for K in (8, 40, 72, 104, 136, 200, 264, 328)] +
+                         [(2, K) for K in (1000, 1032, 1096, 1544)])
+def test_bf16_256_tiles_over_contractions_that_end_inside_a_tile(mode, K):
+    import paper_2410_13333_amd as mls
+    assert mls.gemm_plan(mode, 3848, 4360, K)[0] == 4096
+    _framed_product(mode, 3848, 4360, K)
+
+
+@pytest.mark.parametrize("mode,shape", [(m, s) for s, _ in GEMM_TILES for m in (0, 1)] + [(2, s) for s, _ in TN_TILES])
+def test_bf16_every_plan(mode, shape):
+    """Every tile size alone and behind whole 256x256 tiles, in each form (tests/test_gemm_plan.py holds the plans)."""
+    _framed_product(mode, *shape)
 
 
 def test_fp32_three_modes():
@@ -169,7 +185,8 @@ def test_empty_contraction():
     assert float(c.float().abs().max()) == 0.0 and float((acc - 0.5).abs().max()) == 0.0
 
 
-# by the plan of gemm_bf16_dispatch.hip: 64x64 tiles; 128x64; 128x128; 256x128; 256x256 tiles with a 64x64 and a 128x64 tail.
+# by the plan of gemm_bf16_dispatch.hip (NN and NT): 64x64 tiles; 128x64; 128x128; 256x128; 256x256 tiles with a 64x64 and a
+# 128x64 tail.
 # K: one k-tile that is not full, a last k-tile of one 16-byte chunk, more k-tiles than stages
 @pytest.mark.parametrize("M,N,K", [(72, 136, 24), (72, 136, 1032), (1000, 2056, 1096), (2040, 2040, 392), (2000, 3000, 1032),
                                    (2048, 4096, 328), (4096, 4360, 136), (4088, 5128, 200)])
