@@ -9,7 +9,8 @@ import pytest
 
 import synth
 from tests.helpers import (gpu_step, grad_errors, oracle_step, rel_err, round_bf16, storage_bits, to_device,
-                           to_host64)
+                           to_host64, worst_block)
+from tests.test_gemm_plan import ROPE_TILES, SWIGLU_TILES, WGRAD_TILES
 
 pytestmark = pytest.mark.gpu
 
@@ -305,10 +306,9 @@ def test_token_counts_that_are_not_multiples_of_eight(seq, mb):
 def test_rotary_epilogue_of_the_qkv_projection(nq, nkv, d, seq, mb):
     """q|k|v after the rotary step, read back from the stash, against RMSNorm -> projection -> rotation in fp64 where
     only what the matrix unit needs is rounded to bf16: the normalised input before the projection and q|k|v once, after
-    the rotation.  The shapes take the projection through every tiling of its kernel: (30, 2, 128) and (60, 4, 64) at
-    4096 tokens give 17 column tiles of 256 = a full round of 256x256 tiles plus a 256x128 tail launch; 3000 tokens x
-    1280 / 640 columns run on the 128x128 tiles with ragged rows.  The positions restart with every sequence of the
-    micro-batch."""
+    the rotation.  (30, 2, 128) and (60, 4, 64) at 4096 tokens give 17 column tiles of 256 = a full round of 256x256 tiles
+    plus a launch of 64x128 tiles; 3000 tokens x 1280 / 640 columns run on 64x128 tiles with ragged rows.  The positions
+    restart with every sequence of the micro-batch."""
     import paper_2410_13333_amd as mls
     import oracle.stage as O
     sh = synth.StageShape(hidden=256, n_q_heads=nq, n_kv_heads=nkv, head_dim=d, ffn=64, seq=seq, micro_batch=mb,
@@ -371,8 +371,8 @@ def test_rotary_epilogue_with_an_odd_number_of_rotated_64_column_heads(nq, nkv, 
 
 @pytest.mark.parametrize("nq,nkv,d,ffn,seq,mb", [(16, 16, 128, 544, 2048, 1), (33, 1, 64, 992, 700, 3), (12, 12, 128, 2048, 1500, 1)])
 def test_fused_epilogues_on_mid_size_tiles(nq, nkv, d, ffn, seq, mb):
-    """Rotary and SwiGLU epilogues on 256x128, 128x128 and 64x128 tiles with ragged rows: a whole layer against the exact
-    oracle."""
+    """Rotary and SwiGLU epilogues on 256x256, 256x128 and 64x128 tiles: a whole layer against the exact oracle (every tile
+    size of both: test_rotary_epilogue_on_every_plan, test_swiglu_epilogue_on_every_plan)."""
     sh = synth.StageShape(hidden=264, n_q_heads=nq, n_kv_heads=nkv, head_dim=d, ffn=ffn, seq=seq, micro_batch=mb, layers=1,
                           microbatches=1)
     _check(sh, [1], 1e-2)
@@ -381,8 +381,8 @@ def test_fused_epilogues_on_mid_size_tiles(nq, nkv, d, ffn, seq, mb):
 @pytest.mark.parametrize("hidden,nq,nkv,d,ffn,seq,mb,n", [(264, 3, 1, 64, 680, 129, 1, 1), (1032, 16, 4, 64, 2728, 999, 2, 1),
                                                           (1544, 24, 8, 64, 4104, 700, 1, 2), (520, 4, 4, 128, 1056, 2050, 2, 2)])
 def test_weight_gradients_of_a_layer_in_one_launch(hidden, nq, nkv, d, ffn, seq, mb, n):
-    """Layers whose four weight gradients share a launch, on each of its tile sizes with ragged edges: every matrix against
-    fp64 on the captured operands, added to what the gradient vector held."""
+    """Layers whose four weight gradients share a launch, with ragged edges: every matrix against fp64 on the captured operands,
+    added to what the gradient vector held (each tile size: test_weight_gradients_on_every_shared_tile)."""
     import torch
     import paper_2410_13333_amd as mls
     st = mls.Stage(hidden, nq, nkv, d, ffn, seq, mb, 1, n, seed=1004)
@@ -425,3 +425,49 @@ def test_launch_counts_of_the_timing_classes(hidden, nq, nkv, d, ffn, seq, n, sh
     st.close()
     assert launches["gemm_wgrad"] == layers * -(-n // 16) * (1 if shared else 4)
     assert launches["gemm_fwd"] == launches["gemm_dgrad"] == 4 * layers * n
+
+
+def _layer_matrix(st, name):
+    off, r, c = st.param_layout(0, name)
+    return st.get_params()[off:off + r * c].double().cuda().reshape(r, c)
+
+
+@pytest.mark.parametrize("hidden,nq,nkv,d,seq,mb", [s for s, _ in ROPE_TILES])
+def test_rotary_epilogue_on_every_plan(hidden, nq, nkv, d, seq, mb):
+    """The q|k|v projection with its rotary epilogue on each tile size, alone and behind 256x256 tiles, against fp64 on the
+    captured normalised input; blocks of 64 rows and columns one by one."""
+    import torch
+    import paper_2410_13333_amd as mls
+    import oracle.stage as O
+    st = mls.Stage(hidden, nq, nkv, d, 64, seq, mb, 1, 1, seed=1005)
+    x = torch.randn(mb, seq, hidden, device="cuda", generator=torch.Generator(device="cuda").manual_seed(seq)).to(torch.bfloat16)
+    st.forward(x, 1, torch.empty_like(x))
+    ref = st.debug_read("a").double().cuda() @ _layer_matrix(st, "w_qkv")
+    got = st.debug_read("qkv").double().cuda()
+    st.close()
+    rot = (nq + nkv) * d
+    u = ref[:, :rot].reshape(mb, seq, nq + nkv, d)
+    ang = torch.from_numpy(np.ascontiguousarray(O.rope_angles(seq, d, 10000.0))).cuda().double()[None, :, None]
+    u1, u2 = u[..., :d // 2], u[..., d // 2:]
+    ref[:, :rot] = torch.cat([u1 * ang.cos() - u2 * ang.sin(), u1 * ang.sin() + u2 * ang.cos()], dim=-1).reshape(mb * seq, rot)
+    assert worst_block(got, ref) <= 4e-3  # one rounding to bf16
+
+
+@pytest.mark.parametrize("hidden,ffn,tokens", [s for s, _ in SWIGLU_TILES])
+def test_swiglu_epilogue_on_every_plan(hidden, ffn, tokens):
+    """The gate/up projection with the SwiGLU in its epilogue, the same way."""
+    import torch
+    import paper_2410_13333_amd as mls
+    st = mls.Stage(hidden, 1, 1, 64, ffn, tokens, 1, 1, 1, seed=1006)
+    x = torch.randn(1, tokens, hidden, device="cuda", generator=torch.Generator(device="cuda").manual_seed(ffn)).to(torch.bfloat16)
+    st.forward(x, 1, torch.empty_like(x))
+    ref = st.debug_read("b").double().cuda() @ _layer_matrix(st, "w_gu")
+    gu, z = st.debug_read("gu").cuda(), st.debug_read("z").cuda()
+    st.close()
+    assert worst_block(gu, ref) <= 4e-3
+    assert worst_block(z, torch.nn.functional.silu(ref[:, :ffn]) * ref[:, ffn:]) <= 4e-3  # formed in fp32, rounded once
+
+
+@pytest.mark.parametrize("hidden,nq,nkv,d,ffn,seq,mb,n", [s for s, _ in WGRAD_TILES])
+def test_weight_gradients_on_every_shared_tile(hidden, nq, nkv, d, ffn, seq, mb, n):
+    test_weight_gradients_of_a_layer_in_one_launch(hidden, nq, nkv, d, ffn, seq, mb, n)
