@@ -153,11 +153,11 @@ struct Frags {
 #pragma unroll
     for (int i = 0; i < D / 16; i++) r[i] ^= TR * D * 2;
   }
-  __device__ __forceinline__ void flip_cols() {
+  __device__ __forceinline__ void move_cols(uint32_t by) {
 #pragma unroll
     for (int i = 0; i < D / 32; i++) {
-      lo[i] ^= TR * D * 2;
-      hi[i] ^= TR * D * 2;
+      lo[i] += by;
+      hi[i] += by;
     }
   }
   // A operand, rows = tile rows rt*32 .. +31, k = tile columns kk*16 .. +15; tile: its byte offset from lds0
@@ -281,25 +281,27 @@ __device__ __forceinline__ void store_t_unrotate(bf16_t* __restrict__ out, int64
 //
 // What bounded it was one wavefront's chain scores -> softmax -> product with V: the matrix pipe was busy 44 % of the
 // time with two wavefronts per SIMD.  The chain is therefore software-pipelined over the sub-blocks: a step issues the
-// 16 MFMAs of S(s+1) = K Q^T and of O += V^T P(s-1), neither of which needs the softmax of S(s) whose vector
-// instructions go out in between (about five fit behind one MFMA).  K runs one 64-row block ahead of V: both are
-// double-buffered and one barrier per block frees the buffers of K(u-1) and V(u-2).
-// Measured (us, unpipelined -> this): 4096 positions, 32 heads of 128: 163 -> 166; 2048, 16 of 128 (one workgroup per CU,
-// where the chain is everything): 60 -> 48.5; 4096, 16 of 128: 116 -> 102; 4096, 16 of 64: 84 -> 63.  With every CU full the
-// vector instructions and the MFMAs of a SIMD take about nine tenths of the cycles one after the other.
+// 16 MFMAs of one sub-block's S = K Q^T and of another's O += V^T P, neither of which needs the softmax whose vector
+// instructions go out in between (about five fit behind one MFMA).  S runs two sub-blocks ahead of the softmax, so that the
+// maximum is taken over a block of 64 keys at once and the accumulators are rescaled once per block at most, and P V runs one
+// behind it.  K has two buffers, V three; the one barrier per block frees those of K(u-1) and V(u-3).
+// Measured (us, unpipelined -> this): 4096 positions, 32 heads of 128: 163 -> 160; 2048, 16 of 128 (one workgroup per CU,
+// where the chain is everything): 60 -> 47.5; 4096, 16 of 128: 117 -> 100; 4096, 16 of 64: 85 -> 62.  Every bit of the result
+// is the unpipelined kernel's.  With every CU full the vector instructions and the MFMAs of a SIMD take about nine tenths of the
+// cycles one after the other.
 template <int D>
 __global__ __launch_bounds__(AT_THREADS, 2) void attn_fwd_kernel(const bf16_t* __restrict__ qkv, int64_t ld, bf16_t* __restrict__ o, int64_t ldo,
                                                                  float* __restrict__ lse, int S, int nq, int nkv) {
   using TL = Tile<D>;
-  constexpr int KD = D / 16, DT = D / 32, FA = 4, NV = 5;  // reads ahead; vector instructions per MFMA
-  __shared__ __attribute__((aligned(4 * TR * D))) bf16_t lds[2][2][TR * D];  // [K|V][buffer]
+  constexpr int KD = D / 16, DT = D / 32, FA = 6, NV = 5;  // reads ahead; vector instructions per MFMA
+  __shared__ __attribute__((aligned(4 * TR * D))) bf16_t lds[5][TR * D];  // two buffers of K, three of V
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int qb = gridDim.y - 1 - blockIdx.y;  // longest rows first
   const int hq = blockIdx.x, bi = blockIdx.z, hk = hq / (nq / nkv);
   const bf16_t* base = qkv + int64_t(bi) * S * ld;
   const int q0 = qb * 128, qw = q0 + wave * 32, qi = qw + (lane & 31);
   const float sc = rsqrtf((float)D) * LOG2E;
-  const uint32_t lds0 = (uint32_t)(uintptr_t)(MLS_LDS bf16_t*)&lds[0][0][0];
+  const uint32_t lds0 = (uint32_t)(uintptr_t)(MLS_LDS bf16_t*)&lds[0][0];
   TL tl;
   tl.init(ld, wave, lane);
   Frags<D> fr;
@@ -308,7 +310,7 @@ __global__ __launch_bounds__(AT_THREADS, 2) void attn_fwd_kernel(const bf16_t* _
   const int nblk = (min(S, q0 + 128) + TR - 1) / TR;  // KV blocks of the workgroup
   // blocks beyond the last one are requested as empty
   auto issue_k = [&](int u) { tl.dma(kp, ld, u * TR, u < nblk ? S : 0, lds0 + (u & 1) * TL::BYTES, wave); };
-  auto issue_v = [&](int u) { tl.dma(vp, ld, u * TR, u < nblk ? S : 0, lds0 + (2 + (u & 1)) * TL::BYTES, wave); };
+  auto issue_v = [&](int u) { tl.dma(vp, ld, u * TR, u < nblk ? S : 0, lds0 + (2 + u % 3) * TL::BYTES, wave); };
 
   bf16x8 qf[KD];
 #pragma unroll
@@ -318,16 +320,18 @@ __global__ __launch_bounds__(AT_THREADS, 2) void attn_fwd_kernel(const bf16_t* _
 #pragma unroll
   for (int t = 0; t < DT; t++) acc[t] = zero16();
   float m = -INFINITY, l = 0.f;
-  f32x16 st = zero16();            // S of the sub-block whose softmax comes next
-  bf16x8 pf[2] = {};               // P of the one before it
+  f32x16 st[2] = {zero16(), zero16()}, nx[2];  // S of the block whose softmax comes next, and of the one after it
+  bf16x8 pf[2][2] = {};                        // P of the two sub-blocks
 
   const int diag = qw >> 5;                           // the sub-block on this wavefront's diagonal; later ones are masked
-  const int nw = min(diag / 2 + 1, nblk);             // KV blocks this wavefront needs
+  const int nw = min(diag / 2 + 1, nblk);             // KV blocks this wavefront needs; only the last one has masked pairs
+  float ps = 0.f;
 
-  // one step: S of the sub-block after `sub` from sub-block KH of the current K tile; softmax of `st` = S(sub); O += V^T P of the
-  // one before `sub` from sub-block VH of the current V tile
-  auto step = [&](auto DO_S, auto KH, auto DO_SM, auto MASK, int sub, auto DO_PV, auto VH) {
-    constexpr int KT = 0, VT = 2 * TL::BYTES;
+  // One step.  DO_S: S of sub-block H of the current K tile, into nx[H].  DO_SM: the exponentials of sub-block H of the block in
+  // `st`; with H = 0 that block's maximum before, and the reference moves (BLK: its index, for the mask).  DO_PV: O += V^T P of
+  // the other sub-block, the one before in order.
+  auto step = [&](auto HC, auto DO_S, auto DO_SM, auto MASK, int blk, auto DO_PV) {
+    constexpr int KT = 0, VT = 2 * TL::BYTES, H = decltype(HC)::value;
     constexpr bool do_s = decltype(DO_S)::value, do_sm = decltype(DO_SM)::value, do_pv = decltype(DO_PV)::value;
     // MFMAs in their order: S and PV alternate (KD of each; S is one chain), each fragment read FA MFMAs ahead
     f32x16 sn = zero16();
@@ -336,44 +340,48 @@ __global__ __launch_bounds__(AT_THREADS, 2) void attn_fwd_kernel(const bf16_t* _
     bf16x8 f[NM > 0 ? NM : 1];
     auto read = [&](auto IC) {
       constexpr int i = decltype(IC)::value, q = do_s && do_pv ? i / 2 : i;
-      if constexpr (is_s(i)) f[i] = fr.template rows<KT, decltype(KH)::value>(q);
-      else f[i] = fr.template cols<VT, decltype(VH)::value * 2 + q / DT>(q % DT);
+      if constexpr (is_s(i)) f[i] = fr.template rows<KT, H>(q);
+      else f[i] = fr.template cols<VT, (1 - H) * 2 + q / DT>(q % DT);
     };
     static_for<(FA < NM ? FA : NM)>(read);
     static_for<NM>([&](auto IC) {
       constexpr int i = decltype(IC)::value, q = do_s && do_pv ? i / 2 : i;
       if constexpr (is_s(i)) sn = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f[i], qf[q], sn, 0, 0, 0);
-      else acc[q % DT] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f[i], pf[q / DT], acc[q % DT], 0, 0, 0);
+      else acc[q % DT] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f[i], pf[1 - H][q / DT], acc[q % DT], 0, 0, 0);
       if constexpr (i + FA < NM) read(std::integral_constant<int, i + FA>{});
     });
     float mn = m;
     if constexpr (do_sm) {
-      // row maximum of the raw scores (the scale is positive: it commutes with the maximum and is folded into the
-      // exponent below); the mask arithmetic is compiled only into the diagonal path
-      float mx = -INFINITY;
-      const int lim = qi - sub * 32 - (lane >> 5) * 4;  // key 8 (e / 4) + e % 4 of this lane's half is masked beyond it
+      if constexpr (H == 0) {
+        // row maximum of the raw scores (the scale is positive: it commutes with the maximum and is folded into the
+        // exponent below); the mask arithmetic is compiled only into the diagonal path
+        float mx = -INFINITY;
 #pragma unroll
-      for (int e = 0; e < 16; e++) {
-        if (decltype(MASK)::value && 8 * (e >> 2) + (e & 3) > lim) st[e] = -INFINITY;
-        mx = fmaxf(mx, st[e]);
+        for (int jt = 0; jt < 2; jt++) {
+          const int lim = qi - blk * 64 - jt * 32 - (lane >> 5) * 4;  // key 8 (e / 4) + e % 4 of this lane's half is masked beyond it
+#pragma unroll
+          for (int e = 0; e < 16; e++) {
+            if (decltype(MASK)::value && 8 * (e >> 2) + (e & 3) > lim) st[jt][e] = -INFINITY;
+            mx = fmaxf(mx, st[jt][e]);
+          }
+        }
+        mx = max_halves(mx);
+        // The reference of the exponents is the row's maximum itself, as far as it is known, so that the largest probability of
+        // a row is 1 and stays exact when P is rounded to bf16.  A reference that only follows when the maximum has passed it
+        // by a margin saves most of the rescaling below, but then the row's largest term carries a rounding error of 2^-9 like
+        // the others: on rows that look at few keys that is most of the error.
+        mn = fmaxf(m, mx * sc);  // finite: block 0 always holds j = 0 <= i
+        ps = 0.f;
       }
-      mx = max_halves(mx);
-      // The reference of the exponents is the row's maximum itself, as far as it is known, so that the largest probability of a
-      // row is 1 and stays exact when P is rounded to bf16.  A reference that only follows when the maximum has passed it by a
-      // margin saves most of the rescaling below (some row of the 32 moves in about half of all steps), but then the row's
-      // largest term carries a rounding error of 2^-9 like the others: on rows that look at few keys that is most of the error.
-      mn = fmaxf(m, mx * sc);  // finite: sub-block 0 always holds j = 0 <= i
-      float ps = 0.f;
 #pragma unroll
       for (int e = 0; e < 16; e++) {
-        const float p = __builtin_amdgcn_exp2f(st[e] * sc - mn);
-        st[e] = p;
+        const float p = __builtin_amdgcn_exp2f(st[H][e] * sc - mn);
+        st[H][e] = p;
         ps += p;
       }
-      pf[0] = acc_to_b(st, 0);
-      pf[1] = acc_to_b(st, 1);
-      asm volatile("" : "+v"(pf[0]), "+v"(pf[1]), "+v"(ps));  // here, between the MFMAs, and not behind the branch below
-      const bool moved = __any(mn > m);
+      pf[H][0] = acc_to_b(st[H], 0);
+      pf[H][1] = acc_to_b(st[H], 1);
+      asm volatile("" : "+v"(pf[H][0]), "+v"(pf[H][1]), "+v"(ps));  // here, between the MFMAs, and not behind the branch below
       if constexpr (do_s && do_pv) {
         static_for<FA>([&](auto IC) { __builtin_amdgcn_sched_group_barrier(0x100, is_s(decltype(IC)::value) ? 1 : 2, 0); });
         static_for<NM>([&](auto IC) {
@@ -383,56 +391,69 @@ __global__ __launch_bounds__(AT_THREADS, 2) void attn_fwd_kernel(const bf16_t* _
           __builtin_amdgcn_sched_group_barrier(0x402, NV, 0);
         });
       }
-      if (moved) {
-        const float corr = __builtin_amdgcn_exp2f(m - mn);
-        l *= corr;
+      if constexpr (H == 0) {
+        if (__any(mn > m)) {  // rescale only when some row's maximum moved
+          const float corr = __builtin_amdgcn_exp2f(m - mn);
+          l *= corr;
 #pragma unroll
-        for (int t = 0; t < DT; t++)
+          for (int t = 0; t < DT; t++)
 #pragma unroll
-          for (int e = 0; e < 16; e++) acc[t][e] *= corr;
-        m = mn;
+            for (int e = 0; e < 16; e++) acc[t][e] *= corr;
+          m = mn;
+        }
+      } else {
+        l += ps;
       }
-      l += ps;
     }
-    if constexpr (do_s) st = sn;
+    if constexpr (do_s) nx[H] = sn;
+    if constexpr (H == 1) {
+      st[0] = nx[0];
+      st[1] = nx[1];
+    }
   };
   using Y = std::true_type;
   using N = std::false_type;
-
   using C0 = std::integral_constant<int, 0>;
   using C1 = std::integral_constant<int, 1>;
-  // every wavefront passes nblk + 1 barriers: block 0, its unmasked blocks, at most one with the diagonal in it, the last
-  // two products with V, and the blocks that only later rows need
+  // every wavefront passes nblk + 1 barriers: block 0, its blocks, its last softmax, and the blocks that only later rows need
   auto next = [&](int u) {
     wait_dma();       // this wave's part of K(u), V(u-1) has landed ...
-    __syncthreads();  // ... and so has everyone's; all reads of K(u-1), V(u-2) are retired
+    __syncthreads();  // ... and so has everyone's; all reads of K(u-1), V(u-3) are retired
     issue_k(u + 1);
     issue_v(u);
   };
+  int vs = 0;  // V's buffer
+  auto next_v = [&]() {
+    vs = vs == 2 ? 0 : vs + 1;
+    fr.move_cols(vs == 0 ? 0u - 2 * TL::BYTES : TL::BYTES);
+  };
+  nx[0] = nx[1] = zero16();
   issue_k(0);
   next(0);
-  step(Y{}, C0{}, N{}, N{}, 0, N{}, C0{});
-  step(Y{}, C1{}, Y{}, Y{}, 0, N{}, C0{});
-  int u = 1;
-  for (; 2 * u < diag && u < nw; u++) {
-    next(u);
+  step(C0{}, Y{}, N{}, N{}, 0, N{});
+  step(C1{}, Y{}, N{}, N{}, 0, N{});
+  if (nw > 1) {
+    next(1);
     fr.flip_rows();
-    step(Y{}, C0{}, Y{}, N{}, 2 * u - 1, Y{}, C0{});
-    step(Y{}, C1{}, Y{}, N{}, 2 * u, Y{}, C1{});
-    fr.flip_cols();
+    step(C0{}, Y{}, Y{}, N{}, 0, N{});
+    step(C1{}, Y{}, Y{}, N{}, 0, Y{});
+    for (int u = 2; u < nw; u++) {
+      next(u);
+      fr.flip_rows();
+      step(C0{}, Y{}, Y{}, N{}, u - 1, Y{});
+      next_v();
+      step(C1{}, Y{}, Y{}, N{}, u - 1, Y{});
+    }
+    next(nw);
+    step(C0{}, N{}, Y{}, Y{}, nw - 1, Y{});
+    next_v();
+  } else {
+    next(1);
+    step(C0{}, N{}, Y{}, Y{}, 0, N{});
   }
-  if (u < nw) {
-    next(u);
-    fr.flip_rows();
-    step(Y{}, C0{}, Y{}, Y{}, 2 * u - 1, Y{}, C0{});
-    step(Y{}, C1{}, Y{}, Y{}, 2 * u, Y{}, C1{});
-    fr.flip_cols();
-    u++;
-  }
-  next(u);
-  step(N{}, C0{}, Y{}, Y{}, 2 * u - 1, Y{}, C0{});
-  step(N{}, C0{}, N{}, N{}, 0, Y{}, C1{});
-  for (u++; u <= nblk; u++) next(u);
+  step(C1{}, N{}, Y{}, N{}, nw - 1, Y{});
+  step(C0{}, N{}, N{}, N{}, 0, Y{});
+  for (int u = nw + 1; u <= nblk; u++) next(u);
   wait_dma();
   l += __shfl_xor(l, 32, 64);
   const float inv = 1.f / l;
