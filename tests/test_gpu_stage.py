@@ -471,3 +471,25 @@ def test_swiglu_epilogue_on_every_plan(hidden, ffn, tokens):
 @pytest.mark.parametrize("hidden,nq,nkv,d,ffn,seq,mb,n", [s for s, _ in WGRAD_TILES])
 def test_weight_gradients_on_every_shared_tile(hidden, nq, nkv, d, ffn, seq, mb, n):
     test_weight_gradients_of_a_layer_in_one_launch(hidden, nq, nkv, d, ffn, seq, mb, n)
+
+
+@pytest.mark.parametrize("hidden,nq,nkv,d,ffn,seq,mb,n", [
+    (264, 4, 4, 128, 2048, 45, 1, 1), (520, 8, 2, 128, 2728, 45, 1, 1), (4096, 16, 8, 128, 2048, 45, 2, 1),
+    (4096, 1, 1, 64, 2048, 129, 1, 2), (1544, 8, 2, 128, 4104, 999, 2, 1), (4096, 8, 8, 128, 2048, 129, 2, 3)])
+def test_overwrite_equals_zeroing_where_the_two_run_on_different_tiles(hidden, nq, nkv, d, ffn, seq, mb, n):
+    """Weight gradients that are stored and ones that are added to may be planned differently; the bits are the same."""
+    import torch
+    import paper_2410_13333_amd as mls
+    st = mls.Stage(hidden, nq, nkv, d, ffn, seq, mb, 1, n, seed=1008)
+    assert mls.wgrad_plan(st.cfg, n) != mls.wgrad_plan(st.cfg, n, True)
+    gen = torch.Generator(device="cuda").manual_seed(seq)
+    x, dy = (torch.randn(n, mb, seq, hidden, device="cuda", generator=gen).to(torch.bfloat16) for _ in range(2))
+    y, dx, got = torch.empty_like(x[0]), torch.empty_like(dy), []
+    for over in (False, True):
+        g = torch.full((st.grad_elems,), 3.0 if over else 0.0, device="cuda")
+        for i in range(n):
+            st.forward(x[i], 1, y)
+        st.backward(dy, g, n, dx, overwrite=over)
+        got.append(g)
+    st.close()
+    assert torch.equal(*got)
