@@ -669,7 +669,8 @@ hipError_t gemm_m16_rope(const void* A, const void* W, void* C, int M, int N, in
   return launch16<false, false, E_ROPE, false>(a, w, C, nullptr, M, N, K, lda, ldw, ldc, 0, ab, bb, st, nullptr, nullptr, 0, 0, &ra);
 }
 
-// C[M, N] (+)= sum_i A_i[kseg, M]^T B_i[kseg, N] in fp32 over nseg <= 16 pieces, N a multiple of 256 or the whole problem; gu_f > 0: interleaved gate/up columns go to their public places; overwrite: C =.
+// C[M, N] (+)= sum_i A_i[kseg, M]^T B_i[kseg, N] in fp32 over nseg <= 16 pieces, N a multiple of 256 or the whole problem;
+// gu_f > 0: interleaved gate/up columns go to their public places; overwrite: C =.
 hipError_t gemm_m16_tn_segments(const void* const* A, const void* const* B, int nseg, void* C, int M, int N, int kseg,
                                 int64_t lda, int64_t ldb, int64_t ldc, uint32_t ab, uint32_t bb, hipStream_t st, int gu_f,
                                 bool overwrite) {

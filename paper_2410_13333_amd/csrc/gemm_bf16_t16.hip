@@ -1,6 +1,6 @@
 // bf16 GEMM on v_mfma_f32_16x16x32_bf16 for everything that whole rounds of 256x256 tiles (gemm_bf16_m16.hip) do not
-// cover: the columns left over, problems with fewer tiles than CUs, contraction lengths that are no multiple of its
-// k-tile.  Smaller tiles of the same design, 4 wavefronts per workgroup:
+// suit: the columns left over, problems with fewer tiles than CUs, and fused forms whose contraction ends inside its
+// pair of k-tiles.  Smaller tiles of the same design, 4 wavefronts per workgroup:
 //   256x128   half the work per workgroup
 //   128x128   a quarter
 //   128x64    an eighth
