@@ -23,8 +23,6 @@
 
 namespace {
 
-typedef __attribute__((ext_vector_type(4))) int i32x4;
-
 // 16 bytes per lane from a raw buffer straight into LDS (64 lanes fill 1 KiB at lds_byte); out-of-range lanes
 // are zero-filled.  Inline asm so that the waits are placed by hand (see gemm_bf16_t16.hip).
 __device__ __forceinline__ void dma16(i32x4 rsrc, uint32_t voff, uint32_t lds_byte) {
@@ -36,19 +34,7 @@ __device__ __forceinline__ void dma4(i32x4 rsrc, uint32_t voff, uint32_t lds_byt
   asm volatile("s_mov_b32 m0, %0\n\tbuffer_load_dword %1, %2, 0 offen lds" ::"s"(lds_byte), "v"(voff), "s"(rsrc)
                : "memory");
 }
-template <int N>
-__device__ __forceinline__ void wait_vm() { asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory"); }
 __device__ __forceinline__ void wait_dma() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
-__device__ __forceinline__ i32x4 make_rsrc(const void* p, uint32_t bytes) {
-  const uint64_t a = (uint64_t)p;
-  i32x4 r;
-  r[0] = (int)(uint32_t)a;
-  r[1] = (int)((uint32_t)(a >> 32) & 0xffffu);
-  r[2] = (int)bytes;
-  r[3] = 0x00020000;
-  return r;
-}
-constexpr uint32_t OOB = 0x80000000u;
 
 constexpr int AT_THREADS = 256;
 constexpr int TR = 64;  // rows of an LDS tile
@@ -65,15 +51,6 @@ __device__ __forceinline__ int toff(int row, int col) {
     const int sw = ((line & 1) << 2) | ((line >> 1) & 3);
     return line * 128 + (((((row & 1) << 3) | (col >> 3)) ^ sw) << 3) + (col & 7);
   }
-}
-
-template <class F, int... I>
-__device__ __forceinline__ void static_for_impl(F&& f, std::integer_sequence<int, I...>) {
-  (f(std::integral_constant<int, I>{}), ...);
-}
-template <int N, class F>
-__device__ __forceinline__ void static_for(F&& f) {
-  static_for_impl(f, std::make_integer_sequence<int, N>{});
 }
 
 template <int D, int ROWS = TR>
@@ -782,7 +759,7 @@ __global__ __launch_bounds__(AT_THREADS, 1) void attn_dkv_kernel(const bf16_t* _
       asm volatile("" : "+v"(kf[kt][kk]));
       if constexpr (!VL) asm volatile("" : "+v"(vf[kt][kk]));
     }
-  wait_vm<2 * NREQ>();
+  wait_vmcnt<2 * NREQ>();
   __builtin_amdgcn_s_barrier();
   asm volatile("" ::: "memory");
   // The last `dead` steps of a head have no row that sees a key of this wavefront.  They pass it by: their probabilities are
@@ -795,7 +772,7 @@ __global__ __launch_bounds__(AT_THREADS, 1) void attn_dkv_kernel(const bf16_t* _
       // ---- S(it)
       constexpr int Q1 = R1 / 4;
       run(I0{}, std::integral_constant<int, Q1>{}, I3{}, none);
-      wait_vm<NREQ>();
+      wait_vmcnt<NREQ>();
       __builtin_amdgcn_s_barrier();
       asm volatile("" ::: "memory");
       issue_q();
@@ -878,7 +855,7 @@ __global__ __launch_bounds__(AT_THREADS, 1) void attn_dkv_kernel(const bf16_t* _
 #pragma unroll
     for (int kt = 0; kt < KT; kt++) pf[kt][0] = pf[kt][1] = df[kt][0] = df[kt][1] = bf16x8{};
     for (int it = 0; it < dead; it++) {
-      wait_vm<NREQ>();
+      wait_vmcnt<NREQ>();
       __builtin_amdgcn_s_barrier();
       asm volatile("" ::: "memory");
       issue_q();

@@ -3,6 +3,9 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <type_traits>
+#include <utility>
+
 typedef __bf16 bf16_t;
 typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
 typedef __attribute__((ext_vector_type(4))) __bf16 bf16x4;
@@ -10,8 +13,69 @@ typedef __attribute__((ext_vector_type(4))) short s16x4;
 typedef __attribute__((ext_vector_type(8))) short s16x8;
 typedef __attribute__((ext_vector_type(16))) float f32x16;
 typedef __attribute__((ext_vector_type(4))) float f32x4;
+typedef __attribute__((ext_vector_type(4))) int i32x4;
+typedef __attribute__((ext_vector_type(2))) int i32x2;
 
 #define MLS_LDS __attribute__((address_space(3)))
+
+// ---- loops over compile-time indices
+template <class F, int... I>
+__device__ __forceinline__ void static_for_impl(F&& f, std::integer_sequence<int, I...>) {
+  (f(std::integral_constant<int, I>{}), ...);
+}
+template <int N, class F>
+__device__ __forceinline__ void static_for(F&& f) {
+  static_for_impl(f, std::make_integer_sequence<int, N>{});
+}
+
+// ---- raw buffers, requests into LDS, waits: inline asm where the kernels place waits by hand
+constexpr uint32_t OOB = 0x80000000u;  // a byte offset beyond every buffer
+__device__ __forceinline__ i32x4 make_rsrc(const void* p, uint32_t bytes) {
+  const uint64_t a = (uint64_t)p;
+  i32x4 r;
+  r[0] = (int)(uint32_t)a;
+  r[1] = (int)((uint32_t)(a >> 32) & 0xffffu);  // stride 0: raw buffer, byte offsets
+  r[2] = (int)bytes;
+  r[3] = 0x00020000;
+  return r;
+}
+// 16 bytes per lane from a raw buffer straight into LDS: 64 lanes fill 1 KiB at lds_byte.  soff is a scalar byte
+// offset added to the address; it is not part of the range check (voff >= num_records zero-fills).
+__device__ __forceinline__ void dma16s(i32x4 rsrc, uint32_t voff, uint32_t soff, uint32_t lds_byte) {
+  asm volatile("s_mov_b32 m0, %0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds" ::"s"(lds_byte), "v"(voff), "s"(rsrc), "s"(soff)
+               : "memory");
+}
+template <int N>
+__device__ __forceinline__ void wait_vmcnt() {
+  asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");
+}
+__device__ __forceinline__ void wait_lgkm0() { asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory"); }
+__device__ __forceinline__ void wave_lds_sync() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+// ---- fragments of 16x16x32 products
+// C tile (16 columns x 16 rows, transposed product): lane l ends up with C[row l%16][cols 4*(l/16) .. +3]
+__device__ __forceinline__ void mfma16(f32x4& c, const i32x4& bfrag, const i32x4& afrag) {
+  asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+a"(c) : "v"(bfrag), "v"(afrag));
+}
+template <int OFF>
+__device__ __forceinline__ void lds_read16(i32x4& f, uint32_t addr) {
+  asm volatile("ds_read_b128 %0, %1 offset:%2" : "=v"(f) : "v"(addr), "n"(OFF) : "memory");
+}
+// transposing read of a [k][col] tile: two 8-byte reads (k-rows kr and kr+4 of the lane's group of eight); ROW bytes per
+// k-row
+template <int OFF, int ROW>
+__device__ __forceinline__ void lds_read16_tr(i32x4& f, uint32_t addr) {
+  i32x2 lo, hi;
+  asm volatile("ds_read_b64_tr_b16 %0, %2 offset:%3\n\tds_read_b64_tr_b16 %1, %2 offset:%4"
+               : "=&v"(lo), "=&v"(hi)
+               : "v"(addr), "n"(OFF), "n"(OFF + 4 * ROW)
+               : "memory");
+  f = i32x4{lo[0], lo[1], hi[0], hi[1]};  // (the two halves are allocated as one register quad: no copies)
+}
 
 // ---- 8-element (one 16-byte bf16 chunk / two 16-byte fp32 chunks) loads and stores, values as fp32
 __device__ __forceinline__ void load8(const bf16_t* p, float (&v)[8]) {

@@ -48,15 +48,11 @@
 
 namespace {
 
-typedef __attribute__((ext_vector_type(4))) int i32x4;
-typedef __attribute__((ext_vector_type(2))) int i32x2;
-
 constexpr int BM = 256, BN = 256, BK = 32, NS = 4, NW = 4;
 constexpr int A_BYTES = BM * BK * 2, B_BYTES = BN * BK * 2;
 constexpr int B_OFF = NS * A_BYTES;  // all A stages first, then all B stages
 constexpr int LDS_BYTES = NS * (A_BYTES + B_BYTES);
 constexpr int LDS_BYTES_NT = LDS_BYTES + 2 * B_BYTES;  // a [row][k] B has a ring of three pairs of stages
-constexpr uint32_t OOB = 0x80000000u;
 constexpr int MAX_SEGS = 16;
 
 enum { E_BF16 = 0, E_F32 = 1, E_SWIGLU = 2, E_ROPE = 3 };
@@ -64,15 +60,6 @@ enum { E_BF16 = 0, E_F32 = 1, E_SWIGLU = 2, E_ROPE = 3 };
 // with the barrier one row later the last reads are back when the wavefront gets there (measured: 5 is 1 % faster
 // than 4 for the [k][col] forms, 6 is 2 % slower for all: the requests then crowd into two rows).
 constexpr int ROW2 = 5;
-
-template <class F, int... I>
-__device__ __forceinline__ void static_for_impl(F&& f, std::integer_sequence<int, I...>) {
-  (f(std::integral_constant<int, I>{}), ...);
-}
-template <int N, class F>
-__device__ __forceinline__ void static_for(F&& f) {
-  static_for_impl(f, std::make_integer_sequence<int, N>{});
-}
 
 struct SegArgs {
   const bf16_t* a[MAX_SEGS];
@@ -84,50 +71,6 @@ struct RopeArgs {
   const float* sin_tab;
   int seq, rot_cols, head_dim;
 };
-
-__device__ __forceinline__ i32x4 make_rsrc(const void* p, uint32_t bytes) {
-  const uint64_t a = (uint64_t)p;
-  i32x4 r;
-  r[0] = (int)(uint32_t)a;
-  r[1] = (int)((uint32_t)(a >> 32) & 0xffffu);  // stride 0: raw buffer, byte offsets
-  r[2] = (int)bytes;
-  r[3] = 0x00020000;
-  return r;
-}
-// 16 bytes per lane from a raw buffer straight into LDS: 64 lanes fill 1 KiB at lds_byte.  soff is a scalar byte
-// offset added to the address; it is not part of the range check (voff >= num_records zero-fills).
-__device__ __forceinline__ void dma16s(i32x4 rsrc, uint32_t voff, uint32_t soff, uint32_t lds_byte) {
-  asm volatile("s_mov_b32 m0, %0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds" ::"s"(lds_byte), "v"(voff), "s"(rsrc), "s"(soff)
-               : "memory");
-}
-template <int N>
-__device__ __forceinline__ void wait_vmcnt() {
-  asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");
-}
-__device__ __forceinline__ void wait_lgkm0() { asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory"); }
-__device__ __forceinline__ void wave_lds_sync() {
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-  __builtin_amdgcn_wave_barrier();
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
-// C tile (16 columns x 16 rows, transposed product): lane l ends up with C[row l%16][cols 4*(l/16) .. +3]
-__device__ __forceinline__ void mfma16(f32x4& c, const i32x4& bfrag, const i32x4& afrag) {
-  asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+a"(c) : "v"(bfrag), "v"(afrag));
-}
-template <int OFF>
-__device__ __forceinline__ void lds_read16(i32x4& f, uint32_t addr) {
-  asm volatile("ds_read_b128 %0, %1 offset:%2" : "=v"(f) : "v"(addr), "n"(OFF) : "memory");
-}
-// transposing read of a [k][col] tile: two 8-byte reads (k-rows kr and kr+4 of the lane's group of eight)
-template <int OFF>
-__device__ __forceinline__ void lds_read16_tr(i32x4& f, uint32_t addr) {
-  i32x2 lo, hi;
-  asm volatile("ds_read_b64_tr_b16 %0, %2 offset:%3\n\tds_read_b64_tr_b16 %1, %2 offset:%4"
-               : "=&v"(lo), "=&v"(hi)
-               : "v"(addr), "n"(OFF), "n"(OFF + 4 * BN * 2)
-               : "memory");
-  f = i32x4{lo[0], lo[1], hi[0], hi[1]};  // (the two halves are allocated as one register quad: no copies)
-}
 
 // [k][col] tiles: XOR applied to the 16-byte chunk index (0..31) of k-row kr.  A transposing 8-byte read takes, per
 // group of 16 lanes, 32 bytes from each of k-rows kr0 .. kr0+3, and 32 lanes (two groups, k-rows 8 apart) go through
@@ -299,10 +242,10 @@ __global__ __launch_bounds__(NW * 64) void gemm16_kernel(const bf16_t* __restric
   auto rd = [&](auto SETC, auto STC, auto NC) {
     constexpr int set = decltype(SETC)::value, st = decltype(STC)::value, n = decltype(NC)::value;
     if constexpr (n < 8) {
-      if constexpr (ATR) lds_read16_tr<st * A_BYTES>(fa[set][n], fa_b[n]);
+      if constexpr (ATR) lds_read16_tr<st * A_BYTES, BN * 2>(fa[set][n], fa_b[n]);
       else lds_read16<(st >> 1) * (2 * A_BYTES) + n * 2048>(fa[set][n], fa_b[st & 1]);
     } else {
-      if constexpr (BTR) lds_read16_tr<st * B_BYTES>(fb[set][n - 8], fb_b[n - 8]);
+      if constexpr (BTR) lds_read16_tr<st * B_BYTES, BN * 2>(fb[set][n - 8], fb_b[n - 8]);
       else lds_read16<(n - 8) * 2048>(fb[set][n - 8], fb_cur[st & 1]);
     }
   };
