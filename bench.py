@@ -19,10 +19,10 @@ ROOT = os.path.dirname(os.path.abspath(__file__))
 sys.path.insert(0, ROOT)
 
 PEAK_BF16_TFLOPS = 2500.0   # MI355X dense bf16 MFMA
-# HBM bytes per GEMM launch (average over all gemm16_kernel and gemm_t16_kernel dispatches of a step), from the rocprofv3 --pmc
-# FETCH_SIZE / WRITE_SIZE runs summarised in profiles/stage_7b_4x4_hbm_traffic.txt:
-# (2.0 * 364396 KiB fetched + 1.0 * 85278 KiB written) * 1024.  Only valid for the default workload.
-PROFILED_GEMM_TRAFFIC = {"7b": 8.34e8}
+# HBM bytes of the GEMM kernels of a step, from the rocprofv3 --pmc FETCH_SIZE / WRITE_SIZE runs summarised in
+# profiles/stage_7b_4x4_hbm_traffic.txt: 164 dispatches of gemm16_kernel and gemm_t16_kernel per step, on average
+# (2.0 * 364396 KiB fetched + 1.0 * 85278 KiB written) * 1024 each.  Only valid for the default workload.
+PROFILED_GEMM_TRAFFIC = {"7b": 164 * 8.336e8}
 
 
 def cpu_baseline(sh):
@@ -394,6 +394,8 @@ def main():
     if a.recompute:  # the backward re-runs every forward contraction but the last one of the layer
         gemm_flops += 2 * sh.tokens * (sh.matrix_params() - sh.ffn * sh.hidden) * K * M * a.steps
     gemm_flops_launch = gemm_flops / gemm_n
+    # a contraction of two tile sizes is two kernels and counts as one launch: bytes of the step / its launches
+    traffic = None if a.recompute or a.workload not in PROFILED_GEMM_TRAFFIC else PROFILED_GEMM_TRAFFIC[a.workload] * a.steps / gemm_n
     achieved = gemm_flops / (gemm_ms * 1e-3) / 1e12
     out = {
         "metric": "stage fwd+bwd TFLOP/s (bf16)", "value": tflops, "unit": "TFLOP/s", "n_gpus": 1, "steps": a.steps,
@@ -409,7 +411,7 @@ def main():
         "tau_ms_per_layer_microbatch": ms / (K * M),
         "model_flops_per_step": flops_step,
         "roofline": {"bound": "mfma", "kernel": "gemm16_kernel (256x256 tiles) + gemm_t16_kernel (column remainders)", "achieved": achieved, "peak": PEAK_BF16_TFLOPS,
-                     "unit": "TFLOP/s", "frac": achieved / PEAK_BF16_TFLOPS, "traffic": PROFILED_GEMM_TRAFFIC.get(a.workload),
+                     "unit": "TFLOP/s", "frac": achieved / PEAK_BF16_TFLOPS, "traffic": traffic,
                      "flops_per_launch": gemm_flops_launch, "avg_launch_ms": gemm_ms / gemm_n},
         "kernel_classes": classes,
     }
