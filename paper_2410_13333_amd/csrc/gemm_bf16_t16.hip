@@ -266,24 +266,8 @@ __global__ __launch_bounds__(256, (Cfg<WTM, WTN, WGM, ATR, BTR, EPI, SEG, NS>::P
   // ---- epilogue.  Lane l holds, of MFMA tile (i, j): C[row 16 i + l%16][cols 16 j + 4 (l/16) .. +3].
   const int64_t crow0 = m0 + wm, ccol0 = n0 + wn;
   if constexpr (EPI == E_F32) {
-    // C (+)= acc in fp32, straight from the accumulator layout (16 bytes per lane); xf > 0: the columns are in the
-    // interleaved gate/up order and go to their public places
-    float* C = reinterpret_cast<float*>(Cv);
-#pragma unroll
-    for (int i = 0; i < WTM; i++) {
-      const int64_t row = crow0 + i * 16 + l16;
-      if (row >= M) continue;
-#pragma unroll
-      for (int j = 0; j < WTN; j++) {
-        const int col = int(ccol0) + j * 16 + g4 * 4;
-        if (col >= N) continue;
-        float4* p = reinterpret_cast<float4*>(C + row * ldc + (xf > 0 ? gu_public_col(col0 + col, xf) : col0 + col));
-        float4 t = make_float4(0.f, 0.f, 0.f, 0.f);
-        if (ldx == 0) t = *p;  // ldx != 0 in this mode: store, do not accumulate
-        t.x += c[i][j][0]; t.y += c[i][j][1]; t.z += c[i][j][2]; t.w += c[i][j][3];
-        *p = t;
-      }
-    }
+    // (ldx != 0 in this mode: store, do not accumulate)
+    f32_results<WTM, WTN>(reinterpret_cast<float*>(Cv), ldc, int(crow0), M, int(ccol0), N, col0, xf, ldx == 0, c, lane, smem + wave * (1024 * WTN));
   } else {
     // bf16 output through a per-wavefront staging area (16 rows x 16 WTN columns, 16-byte chunks XOR-swizzled by row) so
     // that the stores move whole rows.  The fused forms work on the fp32 accumulators first:

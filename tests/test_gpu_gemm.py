@@ -219,3 +219,20 @@ def test_bf16_weight_gradient_over_any_token_count(M, N, K):
     got = to_host64(g[off:off + r * c]).reshape(r, c)
     st.close()
     assert rel_err(got, ref) < 1e-5
+
+
+@pytest.mark.parametrize("ldc", [(1 << 25) - 8, 1 << 25])
+def test_fp32_results_in_very_wide_rows(ldc):
+    """Row strides on either side of 2^25, up to which 16 rows lie within the 31 bits of a store's offset; nothing outside the
+    result's columns changes."""
+    import torch
+    import paper_2410_13333_amd as mls
+    g = torch.Generator(device="cpu").manual_seed(5)
+    a = torch.randn(128, 40, generator=g).to(torch.bfloat16).cuda()
+    b = torch.randn(128, 72, generator=g).to(torch.bfloat16).cuda()
+    flat = torch.full((40 * ldc,), 0.25, dtype=torch.float32, device="cuda")
+    c = flat.view(40, ldc)[:, 8:80]
+    mls.gemm(2, a, b, c)
+    assert rel_err(to_host64(c), 0.25 + to_host64(a).T @ to_host64(b)) < 1e-5
+    c.fill_(0.25)
+    assert bool((flat == 0.25).all())
