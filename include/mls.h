@@ -216,6 +216,13 @@ int mls_gemm_plan(int32_t mode, int64_t M, int64_t N, int64_t K, int64_t* big_co
  * tells their tiles; 16 micro-batches go into a launch).  Errors: MLS_E_NULL, MLS_E_CONFIG, MLS_E_RANGE. */
 int mls_stage_wgrad_plan(const mls_config* cfg, int32_t n_microbatches, int32_t flags, int32_t* tile_rows, int32_t* tile_cols);
 
+/* The same for the products of a layer's forward and data gradient over one micro-batch (bf16 storage; product 0 .. 7: q|k|v, o,
+ * gate|up, down, and the data gradients of down, gate|up, o, q|k|v).  A stage has a workspace, so that several workgroups may
+ * share a tile's contraction: *big_parts of them on the 256x256 tiles of the leading *big_cols columns, *parts on the
+ * *tile_rows x *tile_cols tiles behind.  Errors: MLS_E_NULL, MLS_E_CONFIG, MLS_E_RANGE. */
+int mls_stage_product_plan(const mls_config* cfg, int32_t product, int64_t* big_cols, int32_t* big_parts, int32_t* tile_rows,
+                           int32_t* tile_cols, int32_t* parts);
+
 /* Message for the last error returned on this thread (host string, never NULL). */
 const char* mls_last_error(void);
 

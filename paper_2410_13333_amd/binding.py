@@ -81,6 +81,7 @@ def lib():
         L.mls_gemm.argtypes = [i32, i32, vp, i64, vp, i64, vp, i64, vp, i64, i64, i64, vp]
         L.mls_gemm_plan.argtypes = [i32, i64, i64, i64, C.POINTER(i64), C.POINTER(i32), C.POINTER(i32)]
         L.mls_stage_wgrad_plan.argtypes = [C.POINTER(MlsConfig), i32, i32, C.POINTER(i32), C.POINTER(i32)]
+        L.mls_stage_product_plan.argtypes = [C.POINTER(MlsConfig), i32, C.POINTER(i64)] + [C.POINTER(i32)] * 4
         L.mls_last_error.restype = C.c_char_p
         L.mls_ends_init.argtypes = [C.POINTER(MlsEndsConfig), u64, vp, C.POINTER(vp)]
         L.mls_ends_free.argtypes = [vp]
@@ -278,6 +279,14 @@ def wgrad_plan(cfg, n_microbatches, overwrite=False):
     r, c = C.c_int32(), C.c_int32()
     _check(lib().mls_stage_wgrad_plan(C.byref(cfg), n_microbatches, int(overwrite), C.byref(r), C.byref(c)))
     return r.value, c.value
+
+
+def product_plan(cfg, product):
+    """(leading columns on 256x256 tiles, workgroups per tile there, rows, columns of the tiles behind, workgroups per tile)
+    of one of the products of a layer's forward (0 .. 3) and data gradient (4 .. 7); see mls_stage_product_plan."""
+    big, v = C.c_int64(), [C.c_int32() for _ in range(4)]
+    _check(lib().mls_stage_product_plan(C.byref(cfg), product, C.byref(big), *[C.byref(x) for x in v]))
+    return (big.value,) + tuple(x.value for x in v)
 
 
 # ---- include/mls_ends.h: the non-uniform layers of the first and the last pipeline stage

@@ -133,6 +133,92 @@ __host__ __device__ __forceinline__ int gu_interleaved_col(int c, int f) {
   return (r >> 5) * 64 + w * 32 + (r & 31);
 }
 
+// ---- contractions shared out over several workgroups: `parts` of them per tile of the result, each over its share of the
+// contraction.  All but the last to finish leave their fp32 sums in `sums` (a slot of 256 threads x 16 WTM WTN bytes each) and
+// are done; the last one adds them up in the order of the parts, so that the bits do not depend on who came last, and goes on
+// to the epilogue.  state: two counters per tile, zero before the launch and after it: who has arrived, whose sums are there.
+// No workgroup waits for one that may not have started: the last one waits for stores that are on their way.
+// The exchange may cross XCDs, whose L2 caches are not coherent with each other: agent-scope accesses (sc1) on both sides, the
+// sums announced when their stores have completed.  (Release and acquire fences of that scope write back and invalidate the
+// whole L2 under the other workgroups: 2048 x 4096 x 22016 on 256x256 tiles in two parts 278 us instead of 254.  Announced in
+// four pieces, for the reader to start on the first: no faster.)
+struct SplitArgs {
+  float* sums;
+  uint32_t* state;
+  int parts;
+};
+constexpr int CP_AGENT = 16;  // cache policy bit sc1 of the buffer instructions
+template <int WTM, int WTN>
+__device__ __forceinline__ bool join_parts(const SplitArgs& sp, int tile, int part, f32x4 (&c)[WTM][WTN], uint32_t* word) {
+  constexpr int NT = WTM * WTN, SLOT = NT * 256 * 16;
+  const int tid = threadIdx.x, parts = sp.parts;
+  uint32_t* st = sp.state + 2 * int64_t(tile);
+  if (tid == 0) *word = __hip_atomic_fetch_add(st, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  __syncthreads();
+  const bool last = __builtin_amdgcn_readfirstlane(int(*word)) == parts - 1;
+  // (of two parts only one is ever stored)
+  auto slot = [&](int p, bool some) {
+    const int64_t at = parts == 2 ? tile : int64_t(tile) * parts + p;
+    return __builtin_amdgcn_make_buffer_rsrc(reinterpret_cast<unsigned char*>(sp.sums) + at * SLOT, 0, some ? SLOT : 0, 0x00020000);
+  };
+  if (!last) {
+    const auto r = slot(part, true);
+#pragma unroll
+    for (int i = 0; i < NT; i++)
+      __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, c[i / WTN][i % WTN]), r, tid * 16, i * 4096, CP_AGENT);
+    wait_vmcnt<0>();
+    __syncthreads();
+    if (tid == 0) __hip_atomic_fetch_add(st + 1, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    return false;
+  }
+  if (tid == 0) {
+    while (__hip_atomic_load(st + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != uint32_t(parts - 1)) __builtin_amdgcn_s_sleep(1);
+    __hip_atomic_store(st, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __hip_atomic_store(st + 1, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  }
+  __syncthreads();
+  asm volatile("" ::: "memory");
+  auto read = [&](auto r, int i) { return __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(r, tid * 16, i * 4096, CP_AGENT)); };
+  if (NT >= 32 || parts == 2) {  // two parts: a + b has the bits of b + a
+    const auto r = slot(0, true);
+    constexpr int B = NT < 16 ? NT : 16;  // read together (64 registers)
+#pragma unroll
+    for (int b = 0; b < NT; b += B) {
+      f32x4 v[B];
+#pragma unroll
+      for (int i = 0; i < B; i++) v[i] = read(r, b + i);
+#pragma unroll
+      for (int i = 0; i < B; i++) c[(b + i) / WTN][(b + i) % WTN] += v[i];
+      __builtin_amdgcn_sched_barrier(0);
+    }
+    return true;
+  }
+  if constexpr (NT < 32) {
+    constexpr int AT_ONCE = NT >= 16 ? 1 : 16 / NT;  // parts read together
+    f32x4 sum[NT];
+#pragma unroll
+    for (int i = 0; i < NT; i++) sum[i] = f32x4{0.f, 0.f, 0.f, 0.f};
+    for (int p0 = 0; p0 < parts; p0 += AT_ONCE) {
+      f32x4 v[AT_ONCE][NT];
+#pragma unroll
+      for (int q = 0; q < AT_ONCE; q++) {
+        const auto r = slot(p0 + q, p0 + q < parts && p0 + q != part);
+#pragma unroll
+        for (int i = 0; i < NT; i++) v[q][i] = read(r, i);
+      }
+#pragma unroll
+      for (int q = 0; q < AT_ONCE; q++) {
+        const bool own = p0 + q == part;
+#pragma unroll
+        for (int i = 0; i < NT; i++) sum[i] += own ? c[i / WTN][i % WTN] : v[q][i];
+      }
+    }
+#pragma unroll
+    for (int i = 0; i < NT; i++) c[i / WTN][i % WTN] = sum[i];
+  }
+  return true;
+}
+
 // ---- fp32 results of a wavefront's 16x16x32 tiles (lane l holds row l%16 of a block of 16, columns 4 (l/16) .. +3 of a tile):
 // C[row0 + 16 i + l%16][..] = c, or += c.  w0: the wavefront's first column, of N; column n lies at col0 + n of C, or, with
 // xf > 0, where the interleaved gate/up column col0 + n has its public place.  16 rows of C must span less than 2^31 bytes.

@@ -379,6 +379,8 @@ struct mls_ends {
   // workspace
   char* dn = nullptr;
   float *partial = nullptr, *row_loss = nullptr;
+  void* split_mem = nullptr;
+  mls::SplitSpace split;  // (split_mem) of the products whose contraction is shared out over several workgroups per tile
 };
 
 namespace {
@@ -401,12 +403,13 @@ hipError_t copy2d(const mls_ends* s, void* dst, int64_t ld_dst, const void* src,
 
 hipError_t gemm(const mls_ends* s, int mode, const void* A, const void* B, void* C, int M, int N, int K, int64_t lda,
                 int64_t ldb, int64_t ldc) {
-  return s->dt == mls::DT_BF16 ? mls::gemm_bf16(mode, A, B, C, nullptr, M, N, K, lda, ldb, ldc, 0, s->st)
+  return s->dt == mls::DT_BF16 ? mls::gemm_bf16(mode, A, B, C, nullptr, M, N, K, lda, ldb, ldc, 0, s->st, s->split)
                                : mls::gemm_f32(mode, A, B, C, nullptr, M, N, K, lda, ldb, ldc, 0, s->st);
 }
 
 void release(mls_ends* s) {
-  void* p[] = {s->embed, s->gamma, s->wlm, s->wlm_t, s->tok, s->y, s->nrm, s->dlog, s->r, s->dn, s->partial, s->row_loss};
+  void* p[] = {s->embed, s->gamma, s->wlm, s->wlm_t, s->tok, s->y, s->nrm, s->dlog, s->r, s->dn, s->partial, s->row_loss,
+               s->split_mem};
   for (void* q : p)
     if (q) (void)hipFree(q);
   delete s;
@@ -459,6 +462,9 @@ int mls_ends_init(const mls_ends_config* cfg, uint64_t seed, void* hip_stream, m
   s->mb_h = align256(size_t(T) * s->ld_h * s->es);
   s->mb_v = align256(size_t(T) * s->ld_v * s->es);
   const size_t nmb = c.max_inflight;
+  const size_t split = s->dt != mls::DT_BF16 ? 0 :
+      mls::split_bytes(std::max(mls::gemm_split_floats(mls::T16_NT, s->T, int(V), int(depth64(h))),
+                                mls::gemm_split_floats(mls::T16_NT, s->T, int(h), int(depth64(V)))));
   auto alloc = [&](void** p, size_t bytes) { return hipMalloc(p, bytes ? bytes : 256); };
   hipError_t e = hipSuccess;
   if ((e = alloc((void**)&s->embed, V * s->ld_h * s->es)) != hipSuccess ||
@@ -472,7 +478,8 @@ int mls_ends_init(const mls_ends_config* cfg, uint64_t seed, void* hip_stream, m
       (e = alloc((void**)&s->r, nmb * T * 4)) != hipSuccess ||
       (e = alloc((void**)&s->dn, s->mb_h)) != hipSuccess ||
       (e = alloc((void**)&s->partial, size_t(mls::rmsnorm_bwd_blocks(s->T)) * h * 4)) != hipSuccess ||
-      (e = alloc((void**)&s->row_loss, T * 4)) != hipSuccess) {
+      (e = alloc((void**)&s->row_loss, T * 4)) != hipSuccess ||
+      (split && (e = alloc(&s->split_mem, split)) != hipSuccess)) {
     release(s);
     return fail_hip(e, "hipMalloc");
   }
@@ -484,6 +491,11 @@ int mls_ends_init(const mls_ends_config* cfg, uint64_t seed, void* hip_stream, m
       release(s);
       return fail_hip(e, "hipMemsetAsync");
     }
+  }
+  s->split = mls::split_space(s->split_mem);
+  if (split && (e = hipMemsetAsync(s->split.state, 0, size_t(mls::SPLIT_TILES) * 8, s->st)) != hipSuccess) {
+    release(s);
+    return fail_hip(e, "hipMemsetAsync");
   }
   PT t[3];
   param_tensors(s, t);

@@ -198,13 +198,13 @@ hipError_t dispatch(const bf16_t* A, const bf16_t* B, void* C, const bf16_t* R, 
 namespace mls {
 
 hipError_t gemm_bf16(int mode, const void* A, const void* B, void* C, const void* R, int M, int N, int K, int64_t lda,
-                     int64_t ldb, int64_t ldc, int64_t ldr, hipStream_t st) {
+                     int64_t ldb, int64_t ldc, int64_t ldr, hipStream_t st, const SplitSpace& split) {
   const bf16_t* a = static_cast<const bf16_t*>(A);
   const bf16_t* b = static_cast<const bf16_t*>(B);
   const bf16_t* r = static_cast<const bf16_t*>(R);
   if (M == 0 || N == 0) return hipSuccess;
   const bool ld_ok = mode != GEMM_TN || ldc < (1 << 25);  // 16 rows of fp32 results lie within 31 bits
-  if (ld_ok && gemm_bf16_dma_ok(mode, M, N, K, lda, ldb)) return gemm_bf16_dma(mode, A, B, C, R, M, N, K, lda, ldb, ldc, ldr, st);
+  if (ld_ok && gemm_bf16_dma_ok(mode, M, N, K, lda, ldb)) return gemm_bf16_dma(mode, A, B, C, R, M, N, K, lda, ldb, ldc, ldr, st, split);
   switch (mode) {
     case GEMM_NN: return dispatch<false, true, EPI_BF16>(a, b, C, r, M, N, K, lda, ldb, ldc, ldr, st);
     case GEMM_NT: return dispatch<false, false, EPI_BF16>(a, b, C, r, M, N, K, lda, ldb, ldc, ldr, st);

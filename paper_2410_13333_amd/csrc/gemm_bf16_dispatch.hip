@@ -10,8 +10,10 @@ namespace {
 constexpr int CUS = 256;
 
 struct Plan {
-  int n1;    // leading columns (a multiple of 256, possibly 0, or all) that run on 256x256 tiles
-  int tile;  // T16_*: how the columns from n1 on run
+  int n1;         // leading columns (a multiple of 256, possibly 0, or all) that run on 256x256 tiles
+  int n1_parts;   // workgroups per tile there, each over a share of the contraction (1 or 2)
+  int tile;       // T16_*: how the columns from n1 on run
+  int parts;      // workgroups per tile there
   double us;
 };
 
@@ -19,10 +21,13 @@ struct Plan {
 //   256x256, 256x128, 128x128: one workgroup per CU.  A round costs base + it * c; c depends on how full the chip is (clock and
 //     L2 bandwidth are shared).
 //   128x64, 64x64: two and three workgroups per CU.  A lone workgroup is a chain of waits; past that the loads of a CU's
-//     workgroups add up.
-// Results in bf16 (NN, NT): fitted to stand-alone timings of every tile size at 66 shapes (the products of layers with 135 to
-// 4096 tokens and hidden widths 256 to 8192, N(0,1) operands).  The plan with the smallest estimate is on average 0.4 %
-// slower than the fastest one measured there; the worst is 12 % (768 x 4096 over 1008: 18 us instead of 16).
+//     workgroups add up.  deep: what a long contraction costs where many of them share a CU, whose panels leave the L2 between
+//     one k-tile and the next.
+// Results in bf16 (NN, NT): fitted to stand-alone timings of every tile size, whole and shared out, at 426 shapes (64 to 8192
+// tokens, widths 192 to 8192, contractions of 192 to 50304, N(0,1) operands).  The plan with the smallest estimate is on average
+// 1.6 % slower than the fastest one measured there, 1.2 % among the whole ones; the worst is 45 % (1650 x 1280 over 11840: 96 us
+// instead of 66).  Before, from 66 shapes that ended at a contraction of 11008: 2.6 % among the whole ones, the worst 76 %
+// (3532 x 4848 over 16320).
 // Results in fp32 (TN): twice the bytes where they are stored, four times where they are added to, which a tile that has its CU
 // for itself moves while the matrix cores idle: fitted apart, to the weight gradients of 130 layers inside a stage (48 to 5400
 // tokens, hidden 192 to 8192), every tile size, in one launch and apart; 3 to 15 % (rms, from 256x256 to 64x64).  Choosing by it
@@ -41,40 +46,81 @@ double estimate(Result res, int tile, int64_t w, int64_t it) {  // w tiles
   if (tile == TILE_M16 || tile == mls::T16_256x128 || tile == mls::T16_128x128) {
     // share: the part of `base` that a nearly empty round pays
     struct Round { double lo, hi, base, share; };
-    const Round rounds[3][3] = {{{1.00, 1.38, 7.0, 1}, {0.60, 0.85, 5.5, 1}, {0.36, 0.51, 4.5, 1}},
+    const Round rounds[3][3] = {{{0.92, 1.38, 8.5, 1}, {0.56, 0.80, 5.7, 1}, {0.33, 0.45, 4.7, 1}},
                                 {{0.945, 1.269, 17.1, 0.9}, {0.719, 0.829, 10.0, 1}, {0.464, 0.529, 6.2, 1}},
                                 {{1.021, 1.236, 47.9, 0.5}, {0.741, 0.823, 23.1, 0.63}, {0.454, 0.534, 12.1, 0.74}}};
     const Round& r = rounds[res][tile == TILE_M16 ? 0 : tile == mls::T16_256x128 ? 1 : 2];
     const double part = double(w % CUS) / CUS, full = double(w / CUS) * (double(it) * r.hi + r.base);
     return part > 0 ? full + double(it) * (r.lo + (r.hi - r.lo) * part) + r.base * (r.share + (1 - r.share) * part) : full;
   }
-  struct Load { double lone, c0, c1, base, each; };  // each: per workgroup of a CU
-  const Load loads[3][2] = {{{0.26, 0.20, 0.215, 4.0, 0}, {0.21, 0.15, 0.165, 3.2, 0}},
+  struct Load { double lone, c0, c1, base, each, deep; };  // each: per workgroup of a CU; deep: see above
+  const Load loads[3][2] = {{{0.265, 0.047, 0.291, 4.1, 0, 0.053}, {0.212, 0.105, 0.150, 3.1, 0, 0.153}},
                             {{0.344, 0.078, 0.319, 4.4, 2.11}, {0.266, 0.121, 0.195, 3.5, 1.05}},
                             {{0.366, 0.063, 0.316, 5.0, 4.24}, {0.286, 0.076, 0.200, 3.7, 1.97}}};
   const Load& l = loads[res][tile == mls::T16_128x64 ? 0 : 1];
-  const double load = double(w) / CUS, loop = double(it) * std::max(l.lone, l.c0 + l.c1 * load);
+  const double load = double(w) / CUS;
+  double deep = 1;
+  if (load > 2 && it > 64) deep += l.deep * std::min(1.0, load / 2 - 1) * std::min(std::log2(double(it) / 64), 2.5);
+  const double loop = double(it) * std::max(l.lone, (l.c0 + l.c1 * load) * deep);
   return loop + (res == R_BF16 ? l.base * std::max(1.0, load / 2) : l.base + l.each * load);
 }
 double estimate(Result res, int tile, int64_t M, int64_t N, int64_t it) { return estimate(res, tile, tiles_of(tile, M, N), it); }
 
-// m16: the 256x256 kernel takes the problem (the fused forms need whole 64-deep k-tiles there)
-Plan plan(Result res, int M, int N, int64_t K, bool m16) {
+// Sharing a tile's contraction out over `parts` workgroups (NT products of a caller with a workspace): the time of that many
+// tiles over a share of it each, and of the exchange, which grows with the parts to add and with what all of them move.
+// At 426 shapes (64 to 8192 tokens, widths 192 to 8192, contractions of 192 to 50304) the plan takes 143 of them apart, which
+// then run 1.53 times as fast on average; the worst choice among these loses 2 %.  us: 100 x 1024 x 50304 172 -> 34 (64x64 in 8),
+// 700 x 1536 x 8192 40 -> 31 (128x128 in 3), 2048 x 4096 x 22016 310 -> 254 (256x256 in 2), 2048 x 4096 x 4096 stays 59 (75).
+constexpr int MAX_PARTS = 8;
+double join_us(int tile, int parts, int64_t w) {
+  struct Join { double base, part, load; };
+  const Join joins[5] = {{4.2, 2.1, 3.7}, {2.4, 1.2, 4.0}, {1.6, 0.96, 3.0}, {1.37, 0.78, 2.36}, {1.2, 0.66, 1.25}};
+  const Join& j = joins[tile + 1];
+  return j.base + j.part * parts + j.load * double(w) / CUS;
+}
+// the sums they leave, 0 if a workspace does not hold them (a shape's own tile sizes: the fused forms have a 64x128 kernel for
+// both of the smallest)
+int64_t split_floats(int form, int tile, int parts, int64_t M, int64_t N, int64_t it) {
+  if (parts > (tile == TILE_M16 || tile == mls::T16_256x128 ? 2 : MAX_PARTS) || it < 4 * parts) return 0;
+  int bm = 256, bn = 256;
+  if (tile != TILE_M16) mls::t16_tile_size(form, tile, bm, bn);
+  const int64_t tiles = ((M + bm - 1) / bm) * ((N + bn - 1) / bn), floats = tiles * (parts == 2 ? 1 : parts) * bm * bn;
+  return tiles <= mls::SPLIT_TILES && floats <= mls::SPLIT_FLOATS ? floats : 0;
+}
+
+// m16: the 256x256 kernel takes the problem (the fused forms need whole 64-deep k-tiles there); split: tiles may be shared out
+Plan plan(Result res, int form, int M, int N, int64_t K, bool m16, bool split) {
   const int64_t it = (K + 63) / 64, tm = (M + 255) / 256, tn = (N + 255) / 256;
   const int n1 = int(tm * tn / CUS * CUS / tm) * 256;  // columns that whole rounds of 256x256 tiles cover
-  Plan best = {N, mls::T16_256x128, 0};
+  Plan best = {N, 1, mls::T16_256x128, 1, 0};
   double t = m16 ? estimate(res, TILE_M16, M, N, it) : HUGE_VAL;
-  for (int tile : {mls::T16_256x128, mls::T16_128x128, mls::T16_128x64, mls::T16_64x64}) {
-    const double all = estimate(res, tile, M, N, it);
+  auto shared = [&](int tile, int parts, int64_t n) {
+    const int64_t w = tiles_of(tile, M, n) * parts;
+    return estimate(res, tile, w, (it + parts - 1) / parts) + join_us(tile, parts, w);
+  };
+  const int most = !split ? 1 : int(std::max<int64_t>(1, std::min<int64_t>(MAX_PARTS, it / 4)));  // four k-tiles or more each
+  for (int tile : {mls::T16_256x128, mls::T16_128x128, mls::T16_128x64, mls::T16_64x64})
+    for (int parts = 1; parts <= most; parts++) {
+      if (parts == 1 || split_floats(form, tile, parts, M, N, it)) {
+        const double all = parts == 1 ? estimate(res, tile, M, N, it) : shared(tile, parts, N);
+        if (all < t) {
+          t = all;
+          best = {0, 1, tile, parts, 0};
+        }
+      }
+      if (!m16 || n1 == 0 || n1 >= N || (parts > 1 && !split_floats(form, tile, parts, M, N - n1, it))) continue;
+      const double rest = parts == 1 ? estimate(res, tile, M, N - n1, it) : shared(tile, parts, N - n1);
+      const double both = estimate(res, TILE_M16, M, n1, it) + rest + LAUNCH_GAP;
+      if (both < t) {
+        t = both;
+        best = {n1, 1, tile, parts, 0};
+      }
+    }
+  if (split && m16 && K % 64 == 0 && split_floats(form, TILE_M16, 2, M, N, it)) {
+    const double all = shared(TILE_M16, 2, N);
     if (all < t) {
       t = all;
-      best = {0, tile, 0};
-    }
-    if (!m16 || n1 == 0 || n1 >= N) continue;
-    const double both = estimate(res, TILE_M16, M, n1, it) + estimate(res, tile, M, N - n1, it) + LAUNCH_GAP;
-    if (both < t) {
-      t = both;
-      best = {n1, tile, 0};
+      best = {N, 2, mls::T16_256x128, 1, 0};
     }
   }
   best.us = t;
@@ -98,20 +144,22 @@ mls::T16Problem columns_from(mls::T16Problem p, int n1) {
 
 bool fused(int form) { return form == mls::T16_NT_SWIGLU || form == mls::T16_NT_ROPE; }
 
-Plan plan(int form, bool store, int M, int N, int64_t K) {
+Plan plan(int form, bool store, int M, int N, int64_t K, bool split = false) {
   const Result res = form != mls::T16_TN && form != mls::T16_TN_SEGS ? R_BF16 : store ? R_F32_STORE : R_F32_ADD;
-  return plan(res, M, N, K, !fused(form) || K % 64 == 0);
+  return plan(res, form, M, N, K, !fused(form) || K % 64 == 0, split && (form == mls::T16_NT || fused(form)));
 }
 
-// `big(n1)` runs the leading n1 columns on 256x256 tiles
+// `big(n1, space)` runs the leading n1 columns on 256x256 tiles, shared out where it gets a space
 template <class Big>
 hipError_t run(const mls::T16Problem& p, hipStream_t st, Big&& big) {
   const int64_t depth = p.nseg > 0 ? (int64_t(p.K) + 63) / 64 * 64 * p.nseg : p.K;  // (every piece ends with a k-tile of its own)
-  const Plan pl = plan(p.form, p.form == mls::T16_TN_SEGS && p.ldx != 0, p.M, p.N, depth);
+  const Plan pl = plan(p.form, p.form == mls::T16_TN_SEGS && p.ldx != 0, p.M, p.N, depth, p.split.sums != nullptr);
   if (pl.n1 > 0)
-    if (hipError_t e = big(pl.n1)) return e;
+    if (hipError_t e = big(pl.n1, pl.n1_parts > 1 ? &p.split : nullptr)) return e;
   if (pl.n1 == p.N) return hipSuccess;
-  return mls::gemm_t16(columns_from(p, pl.n1), pl.tile, st);
+  mls::T16Problem rest = columns_from(p, pl.n1);
+  rest.parts = pl.parts;
+  return mls::gemm_t16(rest, pl.tile, st);
 }
 
 mls::T16Problem problem(int form, const void* A, const void* B, void* C, int M, int N, int K, int64_t lda, int64_t ldb,
@@ -151,14 +199,15 @@ bool gemm_bf16_dma_ok(int mode, int M, int N, int K, int64_t lda, int64_t ldb) {
 }
 
 hipError_t gemm_bf16_dma(int mode, const void* A, const void* B, void* C, const void* R, int M, int N, int K,
-                         int64_t lda, int64_t ldb, int64_t ldc, int64_t ldr, hipStream_t st) {
+                         int64_t lda, int64_t ldb, int64_t ldc, int64_t ldr, hipStream_t st, const SplitSpace& split) {
   if (M == 0 || N == 0) return hipSuccess;
   const int64_t a_rows = mode == GEMM_TN ? K : M, b_rows = mode == GEMM_NT ? N : K;
   const uint32_t ab = uint32_t(a_rows * lda * 2), bb = uint32_t(b_rows * ldb * 2);
   T16Problem p = problem(mode == GEMM_NN ? T16_NN : mode == GEMM_NT ? T16_NT : T16_TN, A, B, C, M, N, K, lda, ldb, ldc, ab, bb);
   p.R = R;
   p.ldr = ldr;
-  return run(p, st, [&](int n1) { return gemm_m16(mode, A, B, C, R, M, n1, K, lda, ldb, ldc, ldr, ab, bb, st); });
+  p.split = split;
+  return run(p, st, [&](int n1, const SplitSpace* sp) { return gemm_m16(mode, A, B, C, R, M, n1, K, lda, ldb, ldc, ldr, ab, bb, st, sp); });
 }
 
 void t16_tile_size(int form, int tile, int& rows, int& cols) {
@@ -166,11 +215,19 @@ void t16_tile_size(int form, int tile, int& rows, int& cols) {
   cols = tile == T16_256x128 || tile == T16_128x128 || fused(form) ? 128 : 64;
 }
 
-GemmPlan gemm_bf16_plan(int form, int M, int N, int K) {
-  const Plan p = plan(form, false, M, N, K);
-  GemmPlan g = {p.n1, 0, 0};
+GemmPlan gemm_bf16_plan(int form, int M, int N, int K, bool split) {
+  const Plan p = plan(form, false, M, N, K, split);
+  GemmPlan g = {p.n1, 0, 0, p.n1_parts, p.parts};
   if (p.n1 < N) t16_tile_size(form, p.tile, g.tile_rows, g.tile_cols);
   return g;
+}
+
+int64_t gemm_split_floats(int form, int M, int N, int K) {
+  if (M <= 0 || N <= 0 || K <= 0) return 0;
+  const Plan p = plan(form, false, M, N, K, true);
+  const int64_t it = (int64_t(K) + 63) / 64;
+  if (p.n1_parts > 1) return split_floats(form, TILE_M16, p.n1_parts, M, N, it);
+  return p.parts > 1 ? split_floats(form, p.tile, p.parts, M, N - p.n1, it) : 0;
 }
 
 bool gemm_tn_segments_ok(int kseg, int64_t lda, int64_t ldb) { return gemm_bf16_dma_ok(GEMM_TN, 8, 8, kseg, lda, ldb); }
@@ -182,7 +239,7 @@ hipError_t gemm_bf16_tn_segments(const void* const* A, const void* const* B, int
   if (M == 0 || N == 0 || nseg == 0 || kseg == 0) return hipSuccess;
   if (nseg > 16 || (gu_f > 0 && (gu_f % 32 || N != 2 * gu_f))) return hipErrorInvalidValue;
   const T16Problem p = tn_problem({A, B, C, M, N, lda, ldb, ldc, gu_f}, nseg, kseg, overwrite);
-  return run(p, st, [&](int n1) {
+  return run(p, st, [&](int n1, const SplitSpace*) {
     return gemm_m16_tn_segments(A, B, nseg, C, M, n1, kseg, lda, ldb, ldc, p.ab, p.bb, st, gu_f, overwrite);
   });
 }
@@ -228,14 +285,15 @@ bool gemm_swiglu_ok(int M, int f, int K, int64_t lda, int64_t ldw) {
 }
 
 hipError_t gemm_bf16_swiglu(const void* A, const void* W, void* GU, void* Z, int M, int f, int K, int64_t lda,
-                            int64_t ldw, int64_t ldgu, int64_t ldz, hipStream_t st) {
+                            int64_t ldw, int64_t ldgu, int64_t ldz, hipStream_t st, const SplitSpace& split) {
   if (M == 0 || f == 0) return hipSuccess;
   if (!gemm_swiglu_ok(M, f, K, lda, ldw)) return hipErrorInvalidValue;
   const uint32_t ab = uint32_t(int64_t(M) * lda * 2), wb = uint32_t(int64_t(2 * f) * ldw * 2);
   T16Problem p = problem(T16_NT_SWIGLU, A, W, GU, M, 2 * f, K, lda, ldw, ldgu, ab, wb);
   p.X = Z;
   p.ldx = ldz;
-  return run(p, st, [&](int n1) { return gemm_m16_swiglu(A, W, GU, Z, M, n1, K, lda, ldw, ldgu, ldz, ab, wb, st); });
+  p.split = split;
+  return run(p, st, [&](int n1, const SplitSpace* sp) { return gemm_m16_swiglu(A, W, GU, Z, M, n1, K, lda, ldw, ldgu, ldz, ab, wb, st, sp); });
 }
 
 bool gemm_rope_ok(int M, int N, int K, int64_t lda, int64_t ldw, int seq, int rot_cols, int head_dim) {
@@ -244,7 +302,8 @@ bool gemm_rope_ok(int M, int N, int K, int64_t lda, int64_t ldw, int seq, int ro
 }
 
 hipError_t gemm_bf16_rope(const void* A, const void* W, void* C, int M, int N, int K, int64_t lda, int64_t ldw, int64_t ldc,
-                          const float* cos_tab, const float* sin_tab, int seq, int rot_cols, int head_dim, hipStream_t st) {
+                          const float* cos_tab, const float* sin_tab, int seq, int rot_cols, int head_dim, hipStream_t st,
+                          const SplitSpace& split) {
   if (M == 0 || N == 0) return hipSuccess;
   if (!cos_tab || !sin_tab || !gemm_rope_ok(M, N, K, lda, ldw, seq, rot_cols, head_dim)) return hipErrorInvalidValue;
   const uint32_t ab = uint32_t(int64_t(M) * lda * 2), wb = uint32_t(int64_t(N) * ldw * 2);
@@ -254,8 +313,9 @@ hipError_t gemm_bf16_rope(const void* A, const void* W, void* C, int M, int N, i
   p.seq = seq;
   p.rot_cols = rot_cols;
   p.head_dim = head_dim;
-  return run(p, st, [&](int n1) {
-    return gemm_m16_rope(A, W, C, M, n1, K, lda, ldw, ldc, ab, wb, cos_tab, sin_tab, seq, rot_cols, head_dim, st);
+  p.split = split;
+  return run(p, st, [&](int n1, const SplitSpace* sp) {
+    return gemm_m16_rope(A, W, C, M, n1, K, lda, ldw, ldc, ab, wb, cos_tab, sin_tab, seq, rot_cols, head_dim, st, sp);
   });
 }
 

@@ -48,6 +48,8 @@
 
 namespace {
 
+using mls::SplitSpace;
+
 constexpr int BM = 256, BN = 256, BK = 32, NS = 4, NW = 4;
 constexpr int A_BYTES = BM * BK * 2, B_BYTES = BN * BK * 2;
 constexpr int B_OFF = NS * A_BYTES;  // all A stages first, then all B stages
@@ -78,20 +80,25 @@ struct RopeArgs {
 // eight different places of a round: bits 2, 3 from kr & 3, bit 1 from bit 3 of kr.
 __device__ __forceinline__ constexpr int swz_kcol(int kr) { return ((kr & 3) << 2) | (((kr >> 3) & 1) << 1); }
 
-template <bool ATR, bool BTR, int EPI, bool SEG, bool RAG>
+template <bool ATR, bool BTR, int EPI, bool SEG, bool RAG, bool SPLIT>
 __global__ __launch_bounds__(NW * 64) void gemm16_kernel(const bf16_t* __restrict__ A, const bf16_t* __restrict__ B,
                                                          void* __restrict__ Cv, const bf16_t* __restrict__ R, int M, int N,
                                                          int K, int64_t lda, int64_t ldb, int64_t ldc, int64_t ldr,
                                                          uint32_t a_bytes, uint32_t b_bytes, int tiles_m, int col0,
                                                          void* __restrict__ Xv, int64_t ldx, int xf, SegArgs segs,
-                                                         RopeArgs rope) {
+                                                         RopeArgs rope, SplitArgs split) {
   extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
   // tile of this workgroup: each XCD gets a contiguous run of tiles, walked in groups of 4 tile rows, N fastest
   const int nwg = gridDim.x, pid = blockIdx.x;
   const int xcd = pid & 7, q8 = nwg >> 3, rem = nwg & 7;
-  const int tile = xcd * q8 + (xcd < rem ? xcd : rem) + (pid >> 3);
+  int tile = xcd * q8 + (xcd < rem ? xcd : rem) + (pid >> 3), tiles = nwg, part = 0;
+  if constexpr (SPLIT) {  // the first half of the workgroups takes the first half of the contraction
+    tiles = nwg / 2;
+    part = tile / tiles;
+    tile -= part * tiles;
+  }
   const int gm = 4 < tiles_m ? 4 : tiles_m;
-  const int per_group = gm * (nwg / tiles_m), grp = tile / per_group, first_m = grp * gm;
+  const int per_group = gm * (tiles / tiles_m), grp = tile / per_group, first_m = grp * gm;
   const int gsz = min(tiles_m - first_m, gm), in_grp = tile - grp * per_group;
   const int m0 = (first_m + in_grp % gsz) * BM, n0 = (in_grp / gsz) * BN;
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -131,7 +138,16 @@ __global__ __launch_bounds__(NW * 64) void gemm16_kernel(const bf16_t* __restric
     }
   }
   const int tps = ((SEG ? segs.kseg : K) + (RAG ? BK - 1 : 0)) / BK;  // k-tiles per piece
-  const int nk = (SEG ? segs.nseg : 1) * tps;
+  int nk = (SEG ? segs.nseg : 1) * tps;
+  if constexpr (SPLIT) {  // whole turns of the loop (four k-tiles); the descriptors start at the share's first k-tile
+    static_assert(PAIR && PAIRB && !RAG, "both operands [row][k], whole pairs of k-tiles");
+    const int kt0 = part ? (nk + 7) / 8 * 4 : 0;
+    nk = part ? nk - kt0 : (nk + 7) / 8 * 4;
+    A += kt0 * BK;
+    B += kt0 * BK;
+    a_bytes -= kt0 * (BK * 2);
+    b_bytes -= kt0 * (BK * 2);
+  }
   const uint32_t ka = ATR ? uint32_t(lda * (BK * 2)) : BK * 2;  // byte step of one k-tile
   const uint32_t kb = BTR ? uint32_t(ldb * (BK * 2)) : BK * 2;
   const i32x4 dead_a = make_rsrc(A, 0), dead_b = make_rsrc(B, 0);
@@ -366,6 +382,11 @@ __global__ __launch_bounds__(NW * 64) void gemm16_kernel(const bf16_t* __restric
   wait_vmcnt<0>();
   __syncthreads();
 
+  if constexpr (SPLIT) {
+    if (!join_parts<8, 8>(split, tile, part, c, reinterpret_cast<uint32_t*>(smem))) return;
+    __syncthreads();  // (the epilogue writes where the ticket was)
+  }
+
   // ---- epilogue.  Lane l holds, of MFMA tile (i, j): C[row 16 i + l%16][cols 16 j + 4 (l/16) .. +3].
   const int64_t crow0 = m0 + wm, ccol0 = n0 + wn;
   if constexpr (EPI == E_F32) {
@@ -527,11 +548,11 @@ __global__ __launch_bounds__(NW * 64) void gemm16_kernel(const bf16_t* __restric
   }
 }
 
-template <bool ATR, bool BTR, int EPI, bool SEG, bool RAG>
+template <bool ATR, bool BTR, int EPI, bool SEG, bool RAG, bool SPLIT = false>
 hipError_t launch16_as(const bf16_t* A, const bf16_t* B, void* C, const bf16_t* R, int M, int N, int K, int64_t lda,
                     int64_t ldb, int64_t ldc, int64_t ldr, uint32_t ab, uint32_t bb, hipStream_t st, const SegArgs* segs,
-                    void* X, int64_t ldx, int xf, const RopeArgs* rope) {
-  auto kern = gemm16_kernel<ATR, BTR, EPI, SEG, RAG>;
+                    void* X, int64_t ldx, int xf, const RopeArgs* rope, const SplitSpace* split = nullptr) {
+  auto kern = gemm16_kernel<ATR, BTR, EPI, SEG, RAG, SPLIT>;
   SegArgs sa = {};
   if (segs) sa = *segs;
   RopeArgs rp = {};
@@ -540,8 +561,10 @@ hipError_t launch16_as(const bf16_t* A, const bf16_t* B, void* C, const bf16_t* 
   constexpr int LDS = BTR ? LDS_BYTES : LDS_BYTES_NT;
   if (hipError_t e = mls::raise_lds_limit(reinterpret_cast<const void*>(kern), LDS, lds_raised)) return e;
   const int tm = (M + BM - 1) / BM, tn = (N + BN - 1) / BN;
-  hipLaunchKernelGGL(kern, dim3(tm * tn), dim3(NW * 64), LDS, st, A, B, C, R, M, N, K, lda, ldb, ldc, ldr, ab, bb, tm, 0, X,
-                     ldx, xf, sa, rp);
+  SplitArgs sp = {};
+  if (SPLIT) sp = {split->sums, split->state, 2};
+  hipLaunchKernelGGL(kern, dim3(tm * tn * (SPLIT ? 2 : 1)), dim3(NW * 64), LDS, st, A, B, C, R, M, N, K, lda, ldb, ldc, ldr, ab, bb, tm,
+                     0, X, ldx, xf, sa, rp, sp);
   return hipGetLastError();
 }
 
@@ -549,7 +572,13 @@ hipError_t launch16_as(const bf16_t* A, const bf16_t* B, void* C, const bf16_t* 
 template <bool ATR, bool BTR, int EPI, bool SEG>
 hipError_t launch16(const bf16_t* A, const bf16_t* B, void* C, const bf16_t* R, int M, int N, int K, int64_t lda,
                     int64_t ldb, int64_t ldc, int64_t ldr, uint32_t ab, uint32_t bb, hipStream_t st, const SegArgs* segs,
-                    void* X, int64_t ldx, int xf, const RopeArgs* rope) {
+                    void* X, int64_t ldx, int xf, const RopeArgs* rope, const SplitSpace* split = nullptr) {
+  if constexpr (!ATR && !BTR && !SEG) {
+    if (split) {  // at least one turn of the loop for each half
+      if (K % (2 * BK) || K < 8 * BK) return hipErrorInvalidValue;
+      return launch16_as<ATR, BTR, EPI, SEG, false, true>(A, B, C, R, M, N, K, lda, ldb, ldc, ldr, ab, bb, st, segs, X, ldx, xf, rope, split);
+    }
+  }
   if (K <= 0 || (!ATR && K % 8)) return hipErrorInvalidValue;
   if (K % (ATR ? BK : 2 * BK) == 0)
     return launch16_as<ATR, BTR, EPI, SEG, false>(A, B, C, R, M, N, K, lda, ldb, ldc, ldr, ab, bb, st, segs, X, ldx, xf, rope);
@@ -564,13 +593,14 @@ namespace mls {
 // C[M, N] (N a multiple of 256 or the whole problem) in one of the three modes; bf16 C (+ R) for NN and NT, fp32
 // C (+)= for TN.  Operand byte lengths as the DMA path takes them.
 hipError_t gemm_m16(int mode, const void* A, const void* B, void* C, const void* R, int M, int N, int K, int64_t lda,
-                    int64_t ldb, int64_t ldc, int64_t ldr, uint32_t ab, uint32_t bb, hipStream_t st) {
+                    int64_t ldb, int64_t ldc, int64_t ldr, uint32_t ab, uint32_t bb, hipStream_t st, const SplitSpace* split) {
+  if (split && mode != GEMM_NT) return hipErrorInvalidValue;
   const bf16_t* a = static_cast<const bf16_t*>(A);
   const bf16_t* b = static_cast<const bf16_t*>(B);
   const bf16_t* r = static_cast<const bf16_t*>(R);
   switch (mode) {
     case GEMM_NN: return launch16<false, true, E_BF16, false>(a, b, C, r, M, N, K, lda, ldb, ldc, ldr, ab, bb, st, nullptr, nullptr, 0, 0, nullptr);
-    case GEMM_NT: return launch16<false, false, E_BF16, false>(a, b, C, r, M, N, K, lda, ldb, ldc, ldr, ab, bb, st, nullptr, nullptr, 0, 0, nullptr);
+    case GEMM_NT: return launch16<false, false, E_BF16, false>(a, b, C, r, M, N, K, lda, ldb, ldc, ldr, ab, bb, st, nullptr, nullptr, 0, 0, nullptr, split);
     case GEMM_TN: return launch16<true, true, E_F32, false>(a, b, C, r, M, N, K, lda, ldb, ldc, ldr, ab, bb, st, nullptr, nullptr, 0, 0, nullptr);
   }
   return hipErrorInvalidValue;
@@ -580,20 +610,20 @@ hipError_t gemm_m16(int mode, const void* A, const void* B, void* C, const void*
 // GU[M, N = 2f] = A[M,K] W[K, 2f] (interleaved gate/up columns), Z[M, f] = silu(gate) * up; N a multiple of 256 here.
 // W is given transposed, [2f][K] with row stride ldw.
 hipError_t gemm_m16_swiglu(const void* A, const void* W, void* GU, void* Z, int M, int N, int K, int64_t lda, int64_t ldw,
-                           int64_t ldgu, int64_t ldz, uint32_t ab, uint32_t bb, hipStream_t st) {
+                           int64_t ldgu, int64_t ldz, uint32_t ab, uint32_t bb, hipStream_t st, const SplitSpace* split) {
   const bf16_t* a = static_cast<const bf16_t*>(A);
   const bf16_t* w = static_cast<const bf16_t*>(W);
-  return launch16<false, false, E_SWIGLU, false>(a, w, GU, nullptr, M, N, K, lda, ldw, ldgu, 0, ab, bb, st, nullptr, Z, ldz, 0, nullptr);
+  return launch16<false, false, E_SWIGLU, false>(a, w, GU, nullptr, M, N, K, lda, ldw, ldgu, 0, ab, bb, st, nullptr, Z, ldz, 0, nullptr, split);
 }
 // C[M, N] = A[M,K] W[K,N] with the head vectors in the columns below rot_cols rotated by the angle of their row's
 // position.  W is given transposed, [N][K] with row stride ldw.
 hipError_t gemm_m16_rope(const void* A, const void* W, void* C, int M, int N, int K, int64_t lda, int64_t ldw, int64_t ldc,
                          uint32_t ab, uint32_t bb, const float* cos_tab, const float* sin_tab, int seq, int rot_cols,
-                         int head_dim, hipStream_t st) {
+                         int head_dim, hipStream_t st, const SplitSpace* split) {
   const RopeArgs ra = {cos_tab, sin_tab, seq, rot_cols, head_dim};
   const bf16_t* a = static_cast<const bf16_t*>(A);
   const bf16_t* w = static_cast<const bf16_t*>(W);
-  return launch16<false, false, E_ROPE, false>(a, w, C, nullptr, M, N, K, lda, ldw, ldc, 0, ab, bb, st, nullptr, nullptr, 0, 0, &ra);
+  return launch16<false, false, E_ROPE, false>(a, w, C, nullptr, M, N, K, lda, ldw, ldc, 0, ab, bb, st, nullptr, nullptr, 0, 0, &ra, split);
 }
 
 // C[M, N] (+)= sum_i A_i[kseg, M]^T B_i[kseg, N] in fp32 over nseg <= 16 pieces, N a multiple of 256 or the whole problem;

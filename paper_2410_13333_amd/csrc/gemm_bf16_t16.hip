@@ -81,11 +81,11 @@ struct Cfg {
   static constexpr int PER_CU = LDS > 80 * 1024 ? 1 : LDS > 53 * 1024 ? 2 : 3;
 };
 
-template <int WTM, int WTN, int WGM, bool ATR, bool BTR, int EPI, bool SEG, int NS>
+template <int WTM, int WTN, int WGM, bool ATR, bool BTR, int EPI, bool SEG, int NS, bool SPLIT>
 __global__ __launch_bounds__(256, (Cfg<WTM, WTN, WGM, ATR, BTR, EPI, SEG, NS>::PER_CU)) void gemm_t16_kernel(
     const bf16_t* __restrict__ A, const bf16_t* __restrict__ B, void* __restrict__ C_, const bf16_t* __restrict__ R, int M_,
     int N_, int K, int64_t lda_, int64_t ldb_, int64_t ldc_, int64_t ldr, uint32_t a_bytes_, uint32_t b_bytes_, int tiles_m_,
-    int col0_, void* __restrict__ Xv, int64_t ldx, int xf_, std::conditional_t<SEG, SegArgs, NoSegs> segs, RopeArgs rope) {
+    int col0_, void* __restrict__ Xv, int64_t ldx, int xf_, std::conditional_t<SEG, SegArgs, NoSegs> segs, RopeArgs rope, SplitArgs split) {
   using G = Cfg<WTM, WTN, WGM, ATR, BTR, EPI, SEG, NS>;
   constexpr int BM = G::BM, BN = G::BN;
   extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
@@ -98,6 +98,12 @@ __global__ __launch_bounds__(256, (Cfg<WTM, WTN, WGM, ATR, BTR, EPI, SEG, NS>::P
   int M = M_, N = N_, tiles_m = tiles_m_, tiles = nwg, col0 = col0_, xf = xf_, pr = 0;
   int64_t lda = lda_, ldb = ldb_, ldc = ldc_;
   uint32_t a_bytes = a_bytes_, b_bytes = b_bytes_;
+  int part = 0;  // its share of the contraction
+  if constexpr (SPLIT) {
+    tiles = nwg / split.parts;
+    part = tile / tiles;
+    tile -= part * tiles;
+  }
   if constexpr (SEG) {
     while (pr + 1 < segs.n && tile >= segs.p[pr + 1].tile0) pr++;
     const SegProblem& p = segs.p[pr];
@@ -151,12 +157,16 @@ __global__ __launch_bounds__(256, (Cfg<WTM, WTN, WGM, ATR, BTR, EPI, SEG, NS>::P
     }
   };
   const int tps = (K + BK - 1) / BK, krem = K - (tps - 1) * BK;  // k-tiles per piece, depth of the last one
-  const int nk = nseg * tps;
+  int kt0 = 0, nk = nseg * tps;
+  if constexpr (SPLIT) {
+    kt0 = int(int64_t(tps) * part / split.parts);
+    nk = int(int64_t(tps) * (part + 1) / split.parts) - kt0;
+  }
   const uint32_t ka = ATR ? uint32_t(lda * (BK * 2)) : BK * 2, kb = BTR ? uint32_t(ldb * (BK * 2)) : BK * 2;
   const i32x4 dead_a = make_rsrc(piece_a(0), 0), dead_b = make_rsrc(piece_b(0), 0);
   i32x4 ra = make_rsrc(piece_a(0), a_bytes), rb = make_rsrc(piece_b(0), b_bytes);
-  int rq_tile = 0, rq_seg = 0, rq_in = 0;  // request cursor: next k-tile, its piece and its index inside the piece
-  set_offsets(tps == 1 ? krem : BK);
+  int rq_tile = 0, rq_seg = 0, rq_in = kt0;  // request cursor: next k-tile, its piece and its index inside the piece
+  set_offsets(kt0 == tps - 1 ? krem : BK);
   auto request = [&](uint32_t stage, auto DC) {  // request D of this wavefront for the cursor's k-tile
     constexpr int d = decltype(DC)::value;
     const bool live = rq_tile < nk;
@@ -262,6 +272,11 @@ __global__ __launch_bounds__(256, (Cfg<WTM, WTN, WGM, ATR, BTR, EPI, SEG, NS>::P
   }
   wait_vmcnt<0>();
   __syncthreads();
+
+  if constexpr (SPLIT) {
+    if (!join_parts<WTM, WTN>(split, tile, part, c, reinterpret_cast<uint32_t*>(smem))) return;
+    __syncthreads();  // (the epilogue writes where the ticket was)
+  }
 
   // ---- epilogue.  Lane l holds, of MFMA tile (i, j): C[row 16 i + l%16][cols 16 j + 4 (l/16) .. +3].
   const int64_t crow0 = m0 + wm, ccol0 = n0 + wn;
@@ -394,12 +409,13 @@ struct Args {
   int xf;
   SegArgs segs;
   RopeArgs rope;
+  SplitArgs split;
 };
 
-template <int WTM, int WTN, int WGM, bool ATR, bool BTR, int EPI, bool SEG, int NS>
-hipError_t launch_t16(const Args& a) {
+template <int WTM, int WTN, int WGM, bool ATR, bool BTR, int EPI, bool SEG, int NS, bool SPLIT>
+hipError_t launch_t16_as(const Args& a) {
   using G = Cfg<WTM, WTN, WGM, ATR, BTR, EPI, SEG, NS>;
-  auto kern = gemm_t16_kernel<WTM, WTN, WGM, ATR, BTR, EPI, SEG, NS>;
+  auto kern = gemm_t16_kernel<WTM, WTN, WGM, ATR, BTR, EPI, SEG, NS, SPLIT>;
   static std::atomic<uint64_t> lds_raised{0};
   if (hipError_t e = mls::raise_lds_limit(reinterpret_cast<const void*>(kern), G::LDS, lds_raised)) return e;
   if constexpr (SEG) {
@@ -412,13 +428,23 @@ hipError_t launch_t16(const Args& a) {
       tiles += p.tiles_m * ((p.N + G::BN - 1) / G::BN);
     }
     hipLaunchKernelGGL(kern, dim3(unsigned(tiles)), dim3(256), G::LDS, a.st, a.A, a.B, a.C, a.R, a.M, a.N, a.K, a.lda, a.ldb, a.ldc, a.ldr,
-                       a.ab, a.bb, 0, a.col0, a.X, a.ldx, a.xf, segs, a.rope);
+                       a.ab, a.bb, 0, a.col0, a.X, a.ldx, a.xf, segs, a.rope, SplitArgs{nullptr, nullptr, 1});
   } else {
     const int tm = (a.M + G::BM - 1) / G::BM, tn = (a.N + G::BN - 1) / G::BN;
-    hipLaunchKernelGGL(kern, dim3(unsigned(tm) * tn), dim3(256), G::LDS, a.st, a.A, a.B, a.C, a.R, a.M, a.N, a.K, a.lda, a.ldb, a.ldc,
-                       a.ldr, a.ab, a.bb, tm, a.col0, a.X, a.ldx, a.xf, NoSegs{}, a.rope);
+    hipLaunchKernelGGL(kern, dim3(unsigned(tm) * tn * (SPLIT ? a.split.parts : 1)), dim3(256), G::LDS, a.st, a.A, a.B, a.C, a.R, a.M, a.N, a.K, a.lda, a.ldb, a.ldc,
+                       a.ldr, a.ab, a.bb, tm, a.col0, a.X, a.ldx, a.xf, NoSegs{}, a.rope, a.split);
   }
   return hipGetLastError();
+}
+
+template <int WTM, int WTN, int WGM, bool ATR, bool BTR, int EPI, bool SEG, int NS>
+hipError_t launch_t16(const Args& a) {
+  if (a.split.parts <= 1) return launch_t16_as<WTM, WTN, WGM, ATR, BTR, EPI, SEG, NS, false>(a);
+  if constexpr (!ATR && !BTR) {
+    if (a.split.parts > (WTM * WTN >= 32 ? 2 : 8) || a.split.parts > (a.K + BK - 1) / BK || !a.split.sums) return hipErrorInvalidValue;
+    return launch_t16_as<WTM, WTN, WGM, ATR, BTR, EPI, SEG, NS, true>(a);
+  }
+  return hipErrorInvalidValue;
 }
 
 // the tile sizes of one form; the fused epilogues need 64 (gate/up) or 128 (head) columns per wavefront
@@ -455,6 +481,7 @@ hipError_t gemm_t16(const T16Problem& p, int tile, hipStream_t st) {
   a.col0 = p.col0;
   a.X = p.X; a.ldx = p.ldx; a.xf = p.xf;
   a.rope = {p.cos_tab, p.sin_tab, p.seq, p.rot_cols, p.head_dim};
+  a.split = {p.split.sums, p.split.state, p.parts > 1 ? p.parts : 1};
   switch (p.form) {
     case T16_NN: return run<false, true, E_BF16, false>(tile, a);
     case T16_NT: return run<false, false, E_BF16, false>(tile, a);

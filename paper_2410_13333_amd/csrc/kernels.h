@@ -27,19 +27,36 @@ inline hipError_t raise_lds_limit(const void* kern, int bytes, std::atomic<uint6
   return e;
 }
 
+// Workspace of contractions that are shared out over several workgroups per tile (join_parts in common.h); it belongs to the
+// launches of one stream.  state: SPLIT_TILES pairs of counters, zero between launches; sums: what the products need
+// (gemm_split_floats), at most SPLIT_FLOATS.  Null: none is shared out.
+constexpr int64_t SPLIT_FLOATS = int64_t(8) << 20, SPLIT_TILES = 1024;
+struct SplitSpace {
+  float* sums = nullptr;
+  uint32_t* state = nullptr;
+};
+// one allocation for both: the counters, then the sums; 0 bytes where no product needs it
+inline size_t split_bytes(int64_t floats) { return floats > 0 ? size_t(SPLIT_TILES) * 8 + size_t(floats) * 4 : 0; }
+inline SplitSpace split_space(void* p) {
+  if (!p) return {};
+  return {reinterpret_cast<float*>(static_cast<char*>(p) + SPLIT_TILES * 8), static_cast<uint32_t*>(p)};
+}
+
 // ---- contractions (gemm_bf16.hip, gemm_f32.hip); modes as documented at mls_gemm; leading dims in elements
 // (ldr: row stride of the residual R, ignored when R is null)
 hipError_t gemm_bf16(int mode, const void* A, const void* B, void* C, const void* R, int M, int N, int K, int64_t lda,
-                     int64_t ldb, int64_t ldc, int64_t ldr, hipStream_t st);
+                     int64_t ldb, int64_t ldc, int64_t ldr, hipStream_t st, const SplitSpace& split = {});
 // the two implementations behind gemm_bf16: LDS-DMA main path and the register-staged fallback for operands
 // too large for 31-bit buffer offsets
 bool gemm_bf16_dma_ok(int mode, int M, int N, int K, int64_t lda, int64_t ldb);
 hipError_t gemm_bf16_dma(int mode, const void* A, const void* B, void* C, const void* R, int M, int N, int K,
-                         int64_t lda, int64_t ldb, int64_t ldc, int64_t ldr, hipStream_t st);
-// What such a problem runs on (form: T16_NN .. T16_NT_ROPE below): the leading columns that get 256x256 tiles, and the size of
-// the tiles behind them (0 x 0 if there are none).  Host only.
-struct GemmPlan { int big_cols, tile_rows, tile_cols; };
-GemmPlan gemm_bf16_plan(int form, int M, int N, int K);
+                         int64_t lda, int64_t ldb, int64_t ldc, int64_t ldr, hipStream_t st, const SplitSpace& split = {});
+// What such a problem runs on (form: T16_NN .. T16_NT_ROPE below): the leading columns that get 256x256 tiles, the size of
+// the tiles behind them (0 x 0 if there are none), and, of a caller with a SplitSpace, the workgroups per tile of either.
+// Host only.
+struct GemmPlan { int big_cols, tile_rows, tile_cols, big_parts, parts; };
+GemmPlan gemm_bf16_plan(int form, int M, int N, int K, bool split = false);
+int64_t gemm_split_floats(int form, int M, int N, int K);  // what it needs of a SplitSpace (0: nothing).  Host only.
 void t16_tile_size(int form, int tile, int& rows, int& cols);  // T16_* of a form in rows and columns
 // weight gradient of several micro-batches in one launch: C[M,N] += sum_i A_i[kseg,M]^T * B_i[kseg,N], C fp32,
 // at most 16 pieces, all with the same strides; true if the operands fit the DMA path's 31-bit offsets
@@ -64,12 +81,12 @@ hipError_t gemm_bf16_tn_group(const TnProduct* p, int n, int tile, int nseg, int
 // the 256x256 tiles of a problem on the 16x16x32 form of the matrix instruction (gemm_bf16_m16.hip); K % 8 == 0 where an
 // operand is stored [row][k], % 64 in the two fused forms
 hipError_t gemm_m16(int mode, const void* A, const void* B, void* C, const void* R, int M, int N, int K, int64_t lda,
-                    int64_t ldb, int64_t ldc, int64_t ldr, uint32_t ab, uint32_t bb, hipStream_t st);
+                    int64_t ldb, int64_t ldc, int64_t ldr, uint32_t ab, uint32_t bb, hipStream_t st, const SplitSpace* split = nullptr);
 hipError_t gemm_m16_swiglu(const void* A, const void* W, void* GU, void* Z, int M, int N, int K, int64_t lda, int64_t ldw,
-                           int64_t ldgu, int64_t ldz, uint32_t ab, uint32_t bb, hipStream_t st);
+                           int64_t ldgu, int64_t ldz, uint32_t ab, uint32_t bb, hipStream_t st, const SplitSpace* split = nullptr);
 hipError_t gemm_m16_rope(const void* A, const void* W, void* C, int M, int N, int K, int64_t lda, int64_t ldw, int64_t ldc,
                          uint32_t ab, uint32_t bb, const float* cos_tab, const float* sin_tab, int seq, int rot_cols,
-                         int head_dim, hipStream_t st);
+                         int head_dim, hipStream_t st, const SplitSpace* split = nullptr);
 hipError_t gemm_m16_tn_segments(const void* const* A, const void* const* B, int nseg, void* C, int M, int N, int kseg,
                                 int64_t lda, int64_t ldb, int64_t ldc, uint32_t ab, uint32_t bb, hipStream_t st, int gu_f,
                                 bool overwrite);
@@ -94,6 +111,8 @@ struct T16Problem {
   const void *seg_a[16], *seg_b[16];
   const float *cos_tab, *sin_tab;
   int seq, rot_cols, head_dim;
+  SplitSpace split;
+  int parts;    // > 1: workgroups per tile, each over a share of K (all forms but TN_SEGS); the space has to hold them
 };
 hipError_t gemm_t16(const T16Problem& p, int tile, hipStream_t st);
 // up to four T16_TN_SEGS problems over pieces of the same number and depth in one launch
@@ -106,14 +125,15 @@ hipError_t fill_zero_f32(float* p, size_t n, hipStream_t st);
 // W is given transposed, [2f][K] (rows in the interleaved order) with row stride ldw.
 bool gemm_swiglu_ok(int M, int f, int K, int64_t lda, int64_t ldw);
 hipError_t gemm_bf16_swiglu(const void* A, const void* W, void* GU, void* Z, int M, int f, int K, int64_t lda,
-                            int64_t ldw, int64_t ldgu, int64_t ldz, hipStream_t st);
+                            int64_t ldw, int64_t ldgu, int64_t ldz, hipStream_t st, const SplitSpace& split = {});
 // The rotary embedding fused into the q|k|v projection (bf16, DMA path): C[M, N] = A[M,K] W[K,N] rounded to bf16, then
 // every head vector (head_dim = 64 or 128 columns) in the columns below rot_cols rotated by the angle of its row's
 // position row % seq, pairs (i, i + head_dim/2); cos_tab, sin_tab: [seq][head_dim/2] fp32.
 // W is given transposed, [N][K] with row stride ldw.
 bool gemm_rope_ok(int M, int N, int K, int64_t lda, int64_t ldw, int seq, int rot_cols, int head_dim);
 hipError_t gemm_bf16_rope(const void* A, const void* W, void* C, int M, int N, int K, int64_t lda, int64_t ldw, int64_t ldc,
-                          const float* cos_tab, const float* sin_tab, int seq, int rot_cols, int head_dim, hipStream_t st);
+                          const float* cos_tab, const float* sin_tab, int seq, int rot_cols, int head_dim, hipStream_t st,
+                          const SplitSpace& split = {});
 hipError_t gemm_f32(int mode, const void* A, const void* B, void* C, const void* R, int M, int N, int K, int64_t lda,
                     int64_t ldb, int64_t ldc, int64_t ldr, hipStream_t st);
 

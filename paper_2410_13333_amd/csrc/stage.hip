@@ -116,6 +116,8 @@ struct mls_stage {
        *dqkv = nullptr;
   size_t mb_h = 0, mb_gu = 0, mb_qkv = 0;  // bytes per micro-batch of the [T,ld_h], [T,ld_gu], [T,ld_qkv] buffers
   // partial, partial2: row-block sums of the two gain gradients of a layer, summed over a call's micro-batches
+  void* split_mem = nullptr;
+  mls::SplitSpace split;  // (split_mem) of the products whose contraction is shared out over several workgroups per tile
   float *delta = nullptr, *partial = nullptr, *partial2 = nullptr, *gqa_part = nullptr;  // gqa_part: partial dK/dV sums (few KV heads)
   std::vector<int> last_k;  // layer counts of the entries of the most recent backward call (for mls_stage_debug_read)
   Timing tm;
@@ -141,7 +143,7 @@ size_t align256(size_t v) { return (v + 255) & ~size_t(255); }
 
 hipError_t gemm(const mls_stage* s, int mode, const void* A, const void* B, void* C, const void* R, int M, int N, int K,
                 int64_t lda, int64_t ldb, int64_t ldc, int64_t ldr = 0) {
-  return s->dt == mls::DT_BF16 ? mls::gemm_bf16(mode, A, B, C, R, M, N, K, lda, ldb, ldc, ldr, s->st)
+  return s->dt == mls::DT_BF16 ? mls::gemm_bf16(mode, A, B, C, R, M, N, K, lda, ldb, ldc, ldr, s->st, s->split)
                                : mls::gemm_f32(mode, A, B, C, R, M, N, K, lda, ldb, ldc, ldr, s->st);
 }
 
@@ -248,7 +250,7 @@ int layer_forward(mls_stage* s, int layer, const char* x, char* e, void* out, in
   const bool wt = s->params_t != nullptr;
   if (s->fuse_rope) {  // the rotation of q and k is the epilogue of their projection
     LAUNCH(CLS_GEMM_NN, mls::gemm_bf16_rope(e + L.a, s->param_t(layer, s->toff_wqkv), e + L.qkv, T, s->qkvw, hk, lh, lh, lq, s->cos_tab,
-                                            s->sin_tab, c.seq, s->qd + s->kvd, c.head_dim, s->st));
+                                            s->sin_tab, c.seq, s->qd + s->kvd, c.head_dim, s->st, s->split));
   } else {
     if (wt) LAUNCH(CLS_GEMM_NN, gemm(s, mls::GEMM_NT, e + L.a, s->param_t(layer, s->toff_wqkv), e + L.qkv, nullptr, T, s->qkvw, hk, lh, lh, lq));
     else LAUNCH(CLS_GEMM_NN, gemm(s, mls::GEMM_NN, e + L.a, s->param(layer, s->ioff_wqkv), e + L.qkv, nullptr, T, s->qkvw, h, lh, lq, lq));
@@ -262,7 +264,7 @@ int layer_forward(mls_stage* s, int layer, const char* x, char* e, void* out, in
   LAUNCH(CLS_NORM, mls::rmsnorm_fwd(s->dt, e + L.h, lh, s->param(layer, s->ioff_g2), e + L.b, lh, (float*)(e + L.r2), T, h,
                                     c.rms_eps, s->st));
   if (s->fuse_gu) {
-    LAUNCH(CLS_GEMM_NN, mls::gemm_bf16_swiglu(e + L.b, s->param_t(layer, s->toff_wgu), e + L.gu, e + L.z, T, f, hk, lh, lh, lg, lf, s->st));
+    LAUNCH(CLS_GEMM_NN, mls::gemm_bf16_swiglu(e + L.b, s->param_t(layer, s->toff_wgu), e + L.gu, e + L.z, T, f, hk, lh, lh, lg, lf, s->st, s->split));
   } else {
     if (wt) LAUNCH(CLS_GEMM_NN, gemm(s, mls::GEMM_NT, e + L.b, s->param_t(layer, s->toff_wgu), e + L.gu, nullptr, T, 2 * f, hk, lh, lh, lg));
     else LAUNCH(CLS_GEMM_NN, gemm(s, mls::GEMM_NN, e + L.b, s->param(layer, s->ioff_wgu), e + L.gu, nullptr, T, 2 * f, h, lh, lg, lg));
@@ -429,6 +431,29 @@ void layout(mls_stage* s) {
   s->mb_qkv = align256(T * s->ld_qkv * s->es);
 }
 
+// the products of a layer and micro-batch that run as NT: form and sizes (bf16 storage)
+struct NtProduct { int form, N, K; };
+constexpr int NT_PRODUCTS = 8;
+void nt_products(const mls_stage* s, NtProduct (&p)[NT_PRODUCTS]) {
+  const int h = s->c.hidden, f = s->c.ffn, hk = int(depth64(h)), fk = int(depth64(f)), gk = int(depth64(2 * int64_t(f)));
+  p[0] = {s->fuse_rope ? mls::T16_NT_ROPE : mls::T16_NT, s->qkvw, hk};  // q|k|v
+  p[1] = {mls::T16_NT, h, s->qd};                                      // o
+  p[2] = {s->fuse_gu ? mls::T16_NT_SWIGLU : mls::T16_NT, 2 * f, hk};   // gate|up
+  p[3] = {mls::T16_NT, h, fk};                                         // down
+  p[4] = {mls::T16_NT, f, hk};                                         // data gradients: of down, gate|up, o, q|k|v
+  p[5] = {mls::T16_NT, h, gk};
+  p[6] = {mls::T16_NT, s->qd, hk};
+  p[7] = {mls::T16_NT, h, s->qkvw};
+}
+int64_t split_floats(const mls_stage* s) {
+  int64_t n = 0;
+  if (s->dt != mls::DT_BF16) return n;
+  NtProduct p[NT_PRODUCTS];
+  nt_products(s, p);
+  for (auto& q : p) n = std::max(n, mls::gemm_split_floats(q.form, s->T, q.N, q.K));
+  return n;
+}
+
 // the device allocations of a stage: name, bytes (what mls_stage_init allocates and mls_stage_memory reports)
 struct Alloc { void** p; size_t bytes; int kind; };  // kind: 0 parameters, 1 stash, 2 workspace
 std::vector<Alloc> allocations(mls_stage* s) {
@@ -451,6 +476,7 @@ std::vector<Alloc> allocations(mls_stage* s) {
       {(void**)&s->dc, T * s->ld_qd * s->es, 2},
       {(void**)&s->dqkv, nmb * s->mb_qkv, 2},
       {(void**)&s->delta, size_t(c.micro_batch) * c.n_q_heads * c.seq * (s->dt == mls::DT_BF16 ? 8 : 4), 2},
+      {&s->split_mem, mls::split_bytes(split_floats(s)), 2},
       {(void**)&s->partial, size_t(nb) * h * 4, 2},
       {(void**)&s->partial2, size_t(nb) * h * 4, 2},
       {(void**)&s->gqa_part, mls::attn_bwd_scratch_floats(s->dt, c.micro_batch, c.seq, c.n_q_heads, c.n_kv_heads, c.head_dim) * 4, 2},
@@ -459,7 +485,7 @@ std::vector<Alloc> allocations(mls_stage* s) {
 
 void release(mls_stage* s) {
   void* p[] = {s->params, s->params_t, s->cos_tab, s->sin_tab, s->stash, s->rc_scratch, s->g0, s->g1, s->dz, s->dgu, s->dbuf, s->dh, s->dc, s->dqkv,
-               s->delta, s->partial, s->partial2, s->gqa_part};
+               s->split_mem, s->delta, s->partial, s->partial2, s->gqa_part};
   for (void* q : p)
     if (q) (void)hipFree(q);
   for (hipEvent_t e : s->tm.ev) (void)hipEventDestroy(e);
@@ -495,6 +521,11 @@ int mls_stage_init(const mls_config* cfg, uint64_t seed, void* hip_stream, mls_s
         release(s);
         return fail_hip(e, "hipMemsetAsync");
       }
+  s->split = mls::split_space(s->split_mem);
+  if (s->split.state && (e = hipMemsetAsync(s->split.state, 0, size_t(mls::SPLIT_TILES) * 8, s->st)) != hipSuccess) {
+    release(s);
+    return fail_hip(e, "hipMemsetAsync");
+  }
   if ((e = hipStreamSynchronize(s->st)) != hipSuccess) {
     release(s);
     return fail_hip(e, "hipStreamSynchronize");
@@ -810,6 +841,27 @@ int mls_stage_wgrad_plan(const mls_config* cfg, int32_t n, int32_t flags, int32_
   const int tile = shared_wgrad_tile(&tmp, p, n < 16 ? n : 16, (flags & MLS_BWD_OVERWRITE) != 0);
   *tile_rows = *tile_cols = 0;
   if (tile >= 0) mls::t16_tile_size(mls::T16_TN_SEGS, tile, *tile_rows, *tile_cols);
+  return MLS_OK;
+}
+
+int mls_stage_product_plan(const mls_config* cfg, int32_t product, int64_t* big_cols, int32_t* big_parts, int32_t* tile_rows,
+                           int32_t* tile_cols, int32_t* parts) {
+  if (!cfg || !big_cols || !big_parts || !tile_rows || !tile_cols || !parts)
+    return fail(MLS_E_NULL, "mls_stage_product_plan: null argument");
+  if (int rc = check_config(*cfg)) return rc;
+  if (cfg->dtype != MLS_BF16) return fail(MLS_E_CONFIG, "mls_stage_product_plan: bf16 storage only");
+  if (product < 0 || product >= NT_PRODUCTS) return fail(MLS_E_RANGE, "mls_stage_product_plan: product must be 0 .. 7");
+  mls_stage tmp;
+  tmp.c = *cfg;
+  layout(&tmp);
+  NtProduct p[NT_PRODUCTS];
+  nt_products(&tmp, p);
+  const mls::GemmPlan g = mls::gemm_bf16_plan(p[product].form, tmp.T, p[product].N, p[product].K, true);
+  *big_cols = g.big_cols;
+  *big_parts = g.big_parts;
+  *tile_rows = g.tile_rows;
+  *tile_cols = g.tile_cols;
+  *parts = g.parts;
   return MLS_OK;
 }
 
