@@ -1,15 +1,17 @@
 // fp32 GEMM of the all-fp32 validation mode, on v_mfma_f32_32x32x2_f32 (full fp32 products and sums).  Same three modes
 // and epilogues as the bf16 kernel.
 //
-// The shapes of this mode are small, so what bounds a launch is the chain of K / 2 dependent MFMAs of an output tile and
-// the number of tiles: the four wavefronts of a workgroup share ONE output tile and take every fourth 32-deep piece of
-// the contraction each, and their partial sums meet in a fixed tree through LDS (the same sum order on every run).
-// Operands go straight from memory to registers: a lane's MFMA operand is one row (or column) at one k, and since the
-// order of the contraction is free as long as both operands agree, the two lane halves take k-values 8g .. 8g+3 and
-// 8g+4 .. 8g+7, so that an operand stored along k is read 16 bytes per lane and one stored across it in 128-byte rows.
-// The next piece is requested before the MFMAs of the current one.
-// Measured (512 tokens, hidden 512: 24 launches of a step, K = 512 .. 2752): 161 us per launch with the scalar-FMA kernel
-// this replaced (64x64 tiles through LDS), 21 us with this one.
+// The shapes of this mode are small.  What bounds a launch is the chain of K / 2 dependent MFMAs of an output tile, the number
+// of tiles, and what the tiles fetch (the 32x32 ones 10 TB/s in all at 512 x 512 x 2752, which is what the L2 caches give).
+// Few tiles: the four wavefronts of a workgroup share ONE 32x32 tile and take every fourth 32-deep piece of the contraction
+// each; their partial sums meet in a fixed tree through LDS.  Many: 64x64 tiles, a quadrant per wavefront.
+// Pieces come by global_load_lds_dwordx4 (whole lines of both operands, 64-bit addresses: any size and stride) and are read into
+// registers one piece ahead of their MFMAs.  A lane's MFMA operand is one row (or column) at one k; the order of the
+// contraction is free as long as both operands agree, so the two lane halves take k-values 8g .. 8g+3 and 8g+4 .. 8g+7 and an
+// operand stored along k is read 16 bytes at a time.
+// Measured (us; straight from memory to registers -> through LDS): the products of a layer of hidden 512, ffn 1376 over 512
+// tokens: q|k|v and o (512 x 1024 and 512 x 512 x 512) 13.4 -> 9.8 and 9.4 -> 7.4, gate|up 36.3 -> 26.7, its data gradient 26.6 -> 22.5
+// and weight gradient 36.8 -> 27.8; 1000 x 4096 x 1024 123 -> 89.  The same bits.
 #include "common.h"
 #include "kernels.h"
 
@@ -17,130 +19,231 @@ namespace {
 
 constexpr int KC = 32;  // contraction depth of one piece: whole 128-byte lines of an operand stored along k
 
-// element (row, k) of an operand at base[row * srow + k * sk]; ALONG_K: sk == 1, 16-byte loads (k a multiple of 4 and
-// rows 16-byte aligned, which the entry point checks)
-template <bool ALONG_K>
-__device__ __forceinline__ void load_piece(const float* __restrict__ base, int64_t ld, int row, int k0, int K, int hf,
-                                           float (&f)[KC / 2]) {
-#pragma unroll
-  for (int g = 0; g < KC / 8; g++) {
-    const int k = k0 + 8 * g + 4 * hf;
-    if (ALONG_K) {  // (K is a multiple of 8 here: groups are whole)
-      float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
-      if (k0 + 8 * g < K) v = *reinterpret_cast<const float4*>(base + int64_t(row) * ld + k);
-      f[4 * g] = v.x; f[4 * g + 1] = v.y; f[4 * g + 2] = v.z; f[4 * g + 3] = v.w;
-    } else {
-#pragma unroll
-      for (int j = 0; j < 4; j++) f[4 * g + j] = k + j < K ? base[int64_t(k + j) * ld + row] : 0.f;
-    }
-  }
+__device__ __forceinline__ void dma16g(const float* p, uint32_t lds_byte) {
+  asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dwordx4 %1, off" ::"s"(lds_byte), "v"(p) : "memory");
 }
 
-// One workgroup = one (32 NT) x (32 NT) tile of C.  A(m, k): AK ? A[m*lda + k] : A[k*lda + m]; B(k, n): BK ? B[n*ldb + k]
-// : B[k*ldb + n].
-template <int NT, bool AK, bool BK>
-__global__ __launch_bounds__(256) void gemm_f32_kernel(const float* __restrict__ A, const float* __restrict__ B, float* C,
-                                                       const float* R, int M, int N, int K, int64_t lda, int64_t ldb,
-                                                       int64_t ldc, int64_t ldr, int accumulate) {
-  __shared__ float part[2][NT * NT * 16][64];
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, l32 = lane & 31, hf = lane >> 5;
-  const int m0 = blockIdx.y * (32 * NT), n0 = blockIdx.x * (32 * NT);
-  // rows and columns past the end repeat the last one: their results are not stored
-  int ar[NT], bc[NT];
-#pragma unroll
-  for (int t = 0; t < NT; t++) {
-    ar[t] = min(m0 + t * 32 + l32, M - 1);
-    bc[t] = min(n0 + t * 32 + l32, N - 1);
+// One operand of a tile of 32 NT rows (of C's rows or columns): element (row, k) at base[row * ld + k] (ALONG_K; K a multiple
+// of 8, rows 16-byte aligned) or base[k * ld + row] (rows a multiple of 8).  A piece in LDS:
+//   ALONG_K   32 NT rows of 128 bytes, their 16-byte chunks permuted by row & 7
+//   else      32 k-rows of 32 NT floats; the two lane halves read rows four apart, which must not share banks: rows of 128 bytes
+//             change places with their neighbour where bit 2 of k is set, in rows of 256 bytes the halves do
+// A wavefront fetches the pieces at k0, k0 + stride, ... by requests q0 .. q0 + NQ - 1 (of 4 NT).  Their addresses move on by
+// additions; only a last piece that is not whole forms them anew.
+// Rows beyond the end repeat the last ones (their results are not stored); so do k-values, and `read` zeroes those.
+template <int NT, bool ALONG_K>
+struct Operand {
+  static constexpr int CPR = ALONG_K ? 8 : 8 * NT, RPQ = 64 / CPR;  // chunks per row, rows per request
+  static constexpr int NQ = NT == 1 ? 4 : 2;  // requests of a wavefront per piece: all, or its share of the workgroup's
+  const float* base;
+  int64_t ld, step;
+  int row0, rows, K, k0, stride, q0;
+  const float* at[NQ];
+  __device__ __forceinline__ const float* place(int i, int lane, int k0_) const {
+    const int s = (q0 + i) * RPQ + lane / CPR, c = lane % CPR;
+    if (ALONG_K) return base + int64_t(min(row0 + s, rows - 1)) * ld + min(k0_ + 4 * (c ^ (s & 7)), K - 4);
+    const int k = NT == 1 ? s ^ ((s >> 2) & 1) : s, col = 4 * (NT == 1 ? c : c ^ (((s >> 2) & 1) << 3));
+    return base + int64_t(min(k0_ + k, K - 1)) * ld + min(row0 + col, rows - 4);
   }
-  f32x16 acc[NT][NT];
+  __device__ __forceinline__ Operand(const float* base_, int64_t ld_, int row0_, int rows_, int K_, int k0_, int stride_, int q0_, int lane)
+      : base(base_), ld(ld_), step(ALONG_K ? stride_ : stride_ * ld_), row0(row0_), rows(rows_), K(K_), k0(k0_), stride(stride_), q0(q0_) {
 #pragma unroll
-  for (int i = 0; i < NT; i++)
+    for (int i = 0; i < NQ; i++) at[i] = place(i, lane, k0);
+  }
+  // the next piece into LDS byte lds on
+  __device__ __forceinline__ void request(int lane, uint32_t lds) {
+    const bool whole = k0 + KC <= K;
 #pragma unroll
-    for (int j = 0; j < NT; j++)
-#pragma unroll
-      for (int e = 0; e < 16; e++) acc[i][j][e] = 0.f;
-  float a[2][NT][KC / 2], b[2][NT][KC / 2];
-  auto load = [&](int k0, int s) {
-#pragma unroll
-    for (int t = 0; t < NT; t++) {
-      load_piece<AK>(A, lda, ar[t], k0, K, hf, a[s][t]);
-      load_piece<BK>(B, ldb, bc[t], k0, K, hf, b[s][t]);
+    for (int i = 0; i < NQ; i++) {
+      dma16g(whole ? at[i] : place(i, lane, min(k0, K - 1)), lds + (q0 + i) * 1024);
+      at[i] += step;
     }
+    k0 += stride;
+  }
+  // rows 32 t + l32 of the piece; left: k-values of it that exist
+  __device__ __forceinline__ static void read(const float* p, int t, int l32, int hf, int left, float (&f)[KC / 2]) {
+#pragma unroll
+    for (int g = 0; g < KC / 8; g++) {
+      const int k = 8 * g + 4 * hf;
+      if (ALONG_K) {
+        const float4 v = *reinterpret_cast<const float4*>(p + (t * 32 + l32) * 32 + (((2 * g + hf) ^ (l32 & 7)) << 2));
+        f[4 * g] = v.x; f[4 * g + 1] = v.y; f[4 * g + 2] = v.z; f[4 * g + 3] = v.w;
+      } else {
+#pragma unroll
+        for (int j = 0; j < 4; j++) f[4 * g + j] = NT == 1 ? p[((k + j) ^ hf) * 32 + l32] : p[(k + j) * 64 + ((t ^ hf) * 32 + l32)];
+      }
+      if (left < KC)
+#pragma unroll
+        for (int j = 0; j < 4; j++) f[4 * g + j] = k + j < left ? f[4 * g + j] : 0.f;
+    }
+  }
+};
+
+// ---- C (+ R, += ) of a 32x32 MFMA tile whose lane holds 4 consecutive columns of row l32
+__device__ __forceinline__ void store_tile(const f32x16& acc, float* C, const float* R, int row, int col0, int M, int N, int64_t ldc,
+                                           int64_t ldr, int add, int hf) {
+  if (row >= M) return;
+#pragma unroll
+  for (int g = 0; g < 4; g++) {
+    const int col = col0 + 8 * g + 4 * hf;  // N is a multiple of 8: groups of four are whole
+    if (col >= N) continue;
+    float4* c = reinterpret_cast<float4*>(C + int64_t(row) * ldc + col);
+    float4 o = make_float4(0.f, 0.f, 0.f, 0.f);
+    if (add) o = *c;
+    else if (R) o = *reinterpret_cast<const float4*>(R + int64_t(row) * ldr + col);
+    *c = make_float4(acc[4 * g] + o.x, acc[4 * g + 1] + o.y, acc[4 * g + 2] + o.z, acc[4 * g + 3] + o.w);
+  }
+}
+__device__ __forceinline__ f32x16 zero16() {
+  f32x16 z;
+#pragma unroll
+  for (int e = 0; e < 16; e++) z[e] = 0.f;
+  return z;
+}
+
+// A(m, k): AK ? A[m*lda + k] : A[k*lda + m]; B(k, n): BK ? B[n*ldb + k] : B[k*ldb + n].  add: C += instead of C =.
+// Few tiles: one workgroup per 32x32 tile of C, wavefront w takes pieces w, w + 4, ... through NS stages of its own.
+template <bool AK, bool BK>
+__global__ __launch_bounds__(256, 2) void gemm_f32_shared_kernel(const float* __restrict__ A, const float* __restrict__ B,
+                                                                               float* C, const float* R, int M, int N, int K,
+                                                                               int64_t lda, int64_t ldb, int64_t ldc, int64_t ldr,
+                                                                               int add) {
+  extern __shared__ __attribute__((aligned(1024))) float smem[];
+  constexpr int STAGE = 2 * 32 * KC, NS = 2, NREQ = 8;
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), l32 = lane & 31, hf = lane >> 5;
+  const int m0 = blockIdx.y * 32, n0 = blockIdx.x * 32;
+  Operand<1, AK> oa(A, lda, m0, M, K, wave * KC, 4 * KC, 0, lane);
+  Operand<1, BK> ob(B, ldb, n0, N, K, wave * KC, 4 * KC, 0, lane);
+  const float* mine = smem + wave * NS * STAGE;
+  const uint32_t lds = (uint32_t)(uintptr_t)(MLS_LDS float*)(smem) + wave * NS * STAGE * 4;
+  auto request = [&](int piece) {
+    const uint32_t at = lds + (piece % NS) * STAGE * 4;
+    oa.request(lane, at);
+    ob.request(lane, at + STAGE * 2);
   };
-  auto mul = [&](int s) {  // operands swapped: a lane ends up with 4 consecutive columns of one row of C
-#pragma unroll
-    for (int q = 0; q < KC / 2; q++)
-#pragma unroll
-      for (int i = 0; i < NT; i++)
-#pragma unroll
-        for (int j = 0; j < NT; j++)
-          acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(b[s][j][q], a[s][i][q], acc[i][j], 0, 0, 0);
+  f32x16 acc = zero16();
+  const int pieces = (K + KC - 1) / KC, n = (pieces - wave + 3) / 4;  // all, of this wavefront (0 if there are fewer than four)
+  float a[2][KC / 2], b[2][KC / 2];
+  auto read = [&](int p, int set) {
+    const float* st = mine + (p % NS) * STAGE;
+    const int left = K - (p * 4 + wave) * KC;
+    Operand<1, AK>::read(st, 0, l32, hf, left, a[set]);
+    Operand<1, BK>::read(st + STAGE / 2, 0, l32, hf, left, b[set]);
   };
-  const int step = 4 * KC;
-  int k0 = wave * KC;
-  if (k0 < K) load(k0, 0);
-  while (k0 < K) {  // two pieces per turn, so that the two register sets need no copies
-    if (k0 + step < K) load(k0 + step, 1);
-    mul(0);
-    k0 += step;
-    if (k0 >= K) break;
-    if (k0 + step < K) load(k0 + step, 0);
-    mul(1);
-    k0 += step;
+  auto step = [&](int p, int set) {  // the products of piece p; piece p + 1 is read meanwhile, p + 2 requested into its stage
+    if (p + 2 < n) request(p + 2);
+    if (p + 1 < n) {
+      if (p + 2 < n) wait_vmcnt<NREQ>(); else wait_vmcnt<0>();
+      read(p + 1, set ^ 1);
+    }
+    // operands swapped: a lane ends up with 4 consecutive columns of one row of C
+#pragma unroll
+    for (int q = 0; q < KC / 2; q++) acc = __builtin_amdgcn_mfma_f32_32x32x2f32(b[set][q], a[set][q], acc, 0, 0, 0);
+    wait_lgkm0();
+  };
+  if (n > 0) {
+    request(0);
+    if (n > 1) request(1);
+    if (n > 1) wait_vmcnt<NREQ>(); else wait_vmcnt<0>();
+    read(0, 0);
+    wait_lgkm0();
+  }
+  for (int p = 0; p < n; p += 2) {
+    step(p, 0);
+    if (p + 1 < n) step(p + 1, 1);
   }
   // wavefronts 2, 3 -> 0, 1; then 1 -> 0
+  float(*part)[16][64] = reinterpret_cast<float(*)[16][64]>(smem);
+  __syncthreads();
 #pragma unroll
   for (int half = 2; half > 0; half >>= 1) {
     if (wave >= half && wave < 2 * half)
 #pragma unroll
-      for (int i = 0; i < NT; i++)
-#pragma unroll
-        for (int j = 0; j < NT; j++)
-#pragma unroll
-          for (int e = 0; e < 16; e++) part[wave - half][(i * NT + j) * 16 + e][lane] = acc[i][j][e];
+      for (int e = 0; e < 16; e++) part[wave - half][e][lane] = acc[e];
     __syncthreads();
     if (wave < half)
 #pragma unroll
-      for (int i = 0; i < NT; i++)
-#pragma unroll
-        for (int j = 0; j < NT; j++)
-#pragma unroll
-          for (int e = 0; e < 16; e++) acc[i][j][e] += part[wave][(i * NT + j) * 16 + e][lane];
+      for (int e = 0; e < 16; e++) acc[e] += part[wave][e][lane];
     __syncthreads();
   }
-  if (wave != 0) return;
+  if (wave == 0) store_tile(acc, C, R, m0 + l32, n0, M, N, ldc, ldr, add, hf);
+}
+
+// Many tiles: one workgroup per 64x64 tile, a quadrant for each wavefront, pieces of both operands shared in a ring of four
+// stages.  Four accumulators take every fourth piece each and are added like the sums of the four wavefronts above: same bits.
+template <bool AK, bool BK>
+__global__ __launch_bounds__(256, 2) void gemm_f32_kernel(const float* __restrict__ A, const float* __restrict__ B, float* C,
+                                                          const float* R, int M, int N, int K, int64_t lda, int64_t ldb, int64_t ldc,
+                                                          int64_t ldr, int add) {
+  extern __shared__ __attribute__((aligned(1024))) float smem[];
+  constexpr int STAGE = 2 * 64 * KC, NS = 4, NREQ = 4;
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), l32 = lane & 31, hf = lane >> 5;
+  const int m0 = blockIdx.y * 64, n0 = blockIdx.x * 64, wm = wave & 1, wn = wave >> 1;
+  Operand<2, AK> oa(A, lda, m0, M, K, 0, KC, 2 * wave, lane);
+  Operand<2, BK> ob(B, ldb, n0, N, K, 0, KC, 2 * wave, lane);
+  const uint32_t lds = (uint32_t)(uintptr_t)(MLS_LDS float*)(smem);
+  const int pieces = (K + KC - 1) / KC;
+  auto request = [&](int piece) {  // (beyond the last one: its last k-value, so that the counts of the waits hold)
+    const uint32_t at = lds + (piece % NS) * STAGE * 4;
+    oa.request(lane, at);
+    ob.request(lane, at + STAGE * 2);
+  };
+  f32x16 acc[4] = {zero16(), zero16(), zero16(), zero16()};
+  if (pieces > 0) {
+    float a[2][KC / 2], b[2][KC / 2];
+    auto read = [&](int p, int set) {
+      const float* st = smem + (p % NS) * STAGE;
+      Operand<2, AK>::read(st, wm, l32, hf, K - p * KC, a[set]);
+      Operand<2, BK>::read(st + STAGE / 2, wn, l32, hf, K - p * KC, b[set]);
+    };
+    auto sync = [&]() {  // the next piece is there for everyone, and everyone has read the one before it
+      wait_vmcnt<(NS - 2) * NREQ>();
+      __builtin_amdgcn_s_barrier();
+      asm volatile("" ::: "memory");
+    };
 #pragma unroll
-  for (int i = 0; i < NT; i++) {
-    const int row = m0 + i * 32 + l32;
-    if (row >= M) continue;
-#pragma unroll
-    for (int j = 0; j < NT; j++)
-#pragma unroll
-      for (int g = 0; g < 4; g++) {
-        const int col = n0 + j * 32 + 8 * g + 4 * hf;  // N is a multiple of 8: groups of four are whole
-        if (col >= N) continue;
-        float4* c = reinterpret_cast<float4*>(C + int64_t(row) * ldc + col);
-        float4 v = make_float4(acc[i][j][4 * g], acc[i][j][4 * g + 1], acc[i][j][4 * g + 2], acc[i][j][4 * g + 3]);
-        float4 o = make_float4(0.f, 0.f, 0.f, 0.f);
-        if (accumulate) o = *c;
-        else if (R) o = *reinterpret_cast<const float4*>(R + int64_t(row) * ldr + col);
-        *c = make_float4(v.x + o.x, v.y + o.y, v.z + o.z, v.w + o.w);
+    for (int p = 0; p < NS - 1; p++) request(p);
+    sync();
+    request(NS - 1);
+    read(0, 0);
+    wait_lgkm0();
+    auto step = [&](int p, f32x16& c, int set) {  // the products of piece p, while piece p + 1 is read
+      if (p + 1 < pieces) {
+        sync();
+        request(p + NS);
+        read(p + 1, set ^ 1);
       }
+#pragma unroll
+      for (int q = 0; q < KC / 2; q++) c = __builtin_amdgcn_mfma_f32_32x32x2f32(b[set][q], a[set][q], c, 0, 0, 0);
+      wait_lgkm0();
+    };
+    for (int p = 0; p < pieces; p += 4) {
+      step(p, acc[0], 0);
+      if (p + 1 < pieces) step(p + 1, acc[1], 1);
+      if (p + 2 < pieces) step(p + 2, acc[2], 0);
+      if (p + 3 < pieces) step(p + 3, acc[3], 1);
+    }
+    wait_vmcnt<0>();
   }
+#pragma unroll
+  for (int e = 0; e < 16; e++) acc[0][e] = (acc[0][e] + acc[2][e]) + (acc[1][e] + acc[3][e]);
+  store_tile(acc[0], C, R, m0 + wm * 32 + l32, n0 + wn * 32, M, N, ldc, ldr, add, hf);
 }
 
 template <bool AK, bool BK>
-void launch_f32(const float* A, const float* B, float* C, const float* R, int M, int N, int K, int64_t lda, int64_t ldb,
-                int64_t ldc, int64_t ldr, int acc, hipStream_t st) {
-  // 64x64 tiles read half as much per product, 32x32 tiles make four times the workgroups: the big ones once they give
-  // every CU two workgroups
-  const int64_t big = int64_t((M + 63) / 64) * ((N + 63) / 64);
-  if (big >= 512)
-    hipLaunchKernelGGL((gemm_f32_kernel<2, AK, BK>), dim3((N + 63) / 64, (M + 63) / 64), dim3(256), 0, st, A, B, C, R, M, N, K,
-                       lda, ldb, ldc, ldr, acc);
-  else
-    hipLaunchKernelGGL((gemm_f32_kernel<1, AK, BK>), dim3((N + 31) / 32, (M + 31) / 32), dim3(256), 0, st, A, B, C, R, M, N, K,
-                       lda, ldb, ldc, ldr, acc);
+hipError_t launch_f32(const float* A, const float* B, float* C, const float* R, int M, int N, int K, int64_t lda, int64_t ldb,
+                      int64_t ldc, int64_t ldr, int add, hipStream_t st) {
+  // The 64x64 tiles read half as much per product; the 32x32 ones are four times as many.  us, 32x32 / 64x64: 1000 x 4096 x 1024
+  // (1024 big tiles) 110 / 89, 1024 x 2752 x 768 (688) 64 / 55, 512 x 2752 x 512 (344) 27.4 / 26.7, 1152 x 768 x 4096 (216) 98 / 104,
+  // 512 x 512 x 2752 (64) 24 / 70.
+  const bool large = int64_t((M + 63) / 64) * ((N + 63) / 64) >= 320;
+  constexpr int LDS = 4 * 2 * 2 * 32 * KC * 4;  // of both
+  auto kern = large ? gemm_f32_kernel<AK, BK> : gemm_f32_shared_kernel<AK, BK>;
+  static std::atomic<uint64_t> lds_raised[2] = {{0}, {0}};
+  if (hipError_t e = mls::raise_lds_limit(reinterpret_cast<const void*>(kern), LDS, lds_raised[large])) return e;
+  const int t = large ? 64 : 32;
+  hipLaunchKernelGGL(kern, dim3((N + t - 1) / t, (M + t - 1) / t), dim3(256), LDS, st, A, B, C, R, M, N, K, lda, ldb, ldc, ldr, add);
+  return hipGetLastError();
 }
 
 }  // namespace
@@ -148,19 +251,18 @@ void launch_f32(const float* A, const float* B, float* C, const float* R, int M,
 namespace mls {
 
 // M, N and row strides multiples of 8, operands 16-byte aligned (as every entry point checks); K a multiple of 8 in the
-// NN and NT forms, any length in the TN form (a weight gradient contracts over the tokens)
+// NN and NT forms, any length in the TN form (a weight gradient contracts over the tokens).  overwrite (TN): C = instead of +=
 hipError_t gemm_f32(int mode, const void* A, const void* B, void* C, const void* R, int M, int N, int K, int64_t lda,
-                    int64_t ldb, int64_t ldc, int64_t ldr, hipStream_t st) {
+                    int64_t ldb, int64_t ldc, int64_t ldr, hipStream_t st, bool overwrite) {
   if (M == 0 || N == 0) return hipSuccess;
   const float *a = (const float*)A, *b = (const float*)B, *r = (const float*)R;
   float* c = (float*)C;
   switch (mode) {
-    case GEMM_NN: launch_f32<true, false>(a, b, c, r, M, N, K, lda, ldb, ldc, ldr, 0, st); break;
-    case GEMM_NT: launch_f32<true, true>(a, b, c, r, M, N, K, lda, ldb, ldc, ldr, 0, st); break;
-    case GEMM_TN: launch_f32<false, false>(a, b, c, r, M, N, K, lda, ldb, ldc, ldr, 1, st); break;
+    case GEMM_NN: return launch_f32<true, false>(a, b, c, r, M, N, K, lda, ldb, ldc, ldr, 0, st);
+    case GEMM_NT: return launch_f32<true, true>(a, b, c, r, M, N, K, lda, ldb, ldc, ldr, 0, st);
+    case GEMM_TN: return launch_f32<false, false>(a, b, c, nullptr, M, N, K, lda, ldb, ldc, ldr, overwrite ? 0 : 1, st);
     default: return hipErrorInvalidValue;
   }
-  return hipGetLastError();
 }
 
 }  // namespace mls

@@ -134,8 +134,9 @@ bool gemm_rope_ok(int M, int N, int K, int64_t lda, int64_t ldw, int seq, int ro
 hipError_t gemm_bf16_rope(const void* A, const void* W, void* C, int M, int N, int K, int64_t lda, int64_t ldw, int64_t ldc,
                           const float* cos_tab, const float* sin_tab, int seq, int rot_cols, int head_dim, hipStream_t st,
                           const SplitSpace& split = {});
+// overwrite (GEMM_TN): C = instead of +=
 hipError_t gemm_f32(int mode, const void* A, const void* B, void* C, const void* R, int M, int N, int K, int64_t lda,
-                    int64_t ldb, int64_t ldc, int64_t ldr, hipStream_t st);
+                    int64_t ldb, int64_t ldc, int64_t ldr, hipStream_t st, bool overwrite = false);
 
 // ---- row-wise and elementwise kernels (elementwise.hip); dt selects the storage type; every matrix argument is
 // followed by its row stride in elements (all row strides are multiples of 8)

@@ -360,6 +360,12 @@ int wgrad(mls_stage* s, const mls::TnProduct (&p)[4], int n, bool ow) {
         LAUNCH(CLS_GEMM_TN, mls::gemm_bf16_tn_segments(w.A, w.B, m, w.C, w.M, w.N, s->T, w.lda, w.ldb, w.ldc, s->st, w.gu_f, over));
         continue;
       }
+      if (s->dt == mls::DT_FP32) {
+        for (int j = 0; j < m; j++)
+          LAUNCH(CLS_GEMM_TN, mls::gemm_f32(mls::GEMM_TN, w.A[j], w.B[j], w.C, nullptr, w.M, w.N, s->T, w.lda, w.ldb, w.ldc, 0, s->st,
+                                            over && j == 0));
+        continue;
+      }
       if (over) HIP_TRY(mls::fill_zero_f32((float*)w.C, size_t(w.M) * w.N, s->st));  // this path only accumulates
       for (int j = 0; j < m; j++) LAUNCH(CLS_GEMM_TN, gemm(s, mls::GEMM_TN, w.A[j], w.B[j], w.C, nullptr, w.M, w.N, s->T, w.lda, w.ldb, w.ldc));
     }

@@ -43,6 +43,41 @@ def test_gemm_fp32(M, N, K):
     assert rel_err(to_host64(acc), 0.5 + ref) < 1e-6
 
 
+@pytest.mark.parametrize("K", [8, 96, 136, 1000])
+@pytest.mark.parametrize("mode", [0, 1, 2])
+def test_both_tile_sizes_have_the_same_bits(mode, K):
+    """480 tiles of 64x64 with ragged edges, against their upper left corner computed alone on 32x32 tiles; the stretch of a
+    last piece that lies beyond K, and what it would read, hold no part of the result (NaN rows behind the operands)."""
+    import torch
+    import paper_2410_13333_amd as mls
+    M, N, m, n = 1240, 1528, 264, 392
+    g = torch.Generator(device="cpu").manual_seed(K)
+    a, b = torch.randn(M, K, generator=g).cuda(), torch.randn(K, N, generator=g).cuda()
+    ref = to_host64(a) @ to_host64(b)
+
+    def framed(t):  # the tensor inside a wider and longer one of NaN
+        big = torch.full((t.shape[0] + 64, t.shape[1] + 64), float("nan"), device="cuda")
+        big[:t.shape[0], :t.shape[1]] = t
+        return big[:t.shape[0], :t.shape[1]]
+    at, bt = (a.t().contiguous() if mode == 2 else a), (b.t().contiguous() if mode == 1 else b)
+    out = torch.zeros(M, N, device="cuda")
+    mls.gemm(mode, framed(at), framed(bt), out)
+    assert rel_err(to_host64(out), ref) < 1e-6
+    part = torch.zeros(m, n, device="cuda")
+    mls.gemm(mode, framed(at[:, :m] if mode == 2 else at[:m]), framed(bt[:n] if mode == 1 else bt[:, :n]), part)
+    assert torch.equal(part, out[:m, :n])
+
+
+def test_weight_gradients_over_an_odd_number_of_tokens_on_large_tiles():
+    sh = synth.StageShape(hidden=776, n_q_heads=2, n_kv_heads=1, head_dim=64, ffn=1400, seq=333, micro_batch=1, layers=1,
+                          microbatches=2, dtype="fp32")
+    ys, dxs, g, st = gpu_step(sh, 1000, 2000, 3000, [1, 1])
+    st.close()
+    rys, rdxs, rg = oracle_step(sh, 1000, 2000, 3000, [1, 1])
+    for e in [rel_err(a, b) for a, b in zip(ys + dxs, rys + rdxs)] + [grad_errors(sh, g, rg, 1)[0]]:
+        assert e <= 1e-5
+
+
 @pytest.mark.parametrize("bad", [float("inf"), float("nan")])
 def test_a_non_finite_position_reaches_no_earlier_one(bad):
     import torch
