@@ -11,11 +11,12 @@ constexpr int EW_THREADS = 256;
 // hidden <= MAXC * 8 * 256; instantiated for 2, 4 and 8 so that narrow rows do not pay for wide ones in registers
 
 // ---------------------------------------------------------------- RMSNorm forward: one workgroup per row
+// copy (may be null): receives x, row stride ldc, on the way (a caller's dense rows into a padded buffer)
 template <typename T, int NORM_MAXC>
 __global__ __launch_bounds__(EW_THREADS) void rmsnorm_fwd_kernel(const T* __restrict__ x, int64_t ldx,
                                                                  const T* __restrict__ gamma, T* __restrict__ a,
                                                                  int64_t lda, float* __restrict__ rstd, int h,
-                                                                 float eps) {
+                                                                 float eps, T* __restrict__ copy, int64_t ldc) {
   __shared__ float red[EW_THREADS / 64];
   const int64_t row = blockIdx.x;
   const T* xr = x + row * ldx;
@@ -27,6 +28,7 @@ __global__ __launch_bounds__(EW_THREADS) void rmsnorm_fwd_kernel(const T* __rest
     const int c = threadIdx.x + i * EW_THREADS;
     if (c < nchunk) {
       load8(xr + c * 8, v[i]);
+      if (copy) store8(copy + row * ldc + c * 8, v[i]);
 #pragma unroll
       for (int e = 0; e < 8; e++) ss += v[i][e] * v[i][e];
     }
@@ -44,6 +46,17 @@ __global__ __launch_bounds__(EW_THREADS) void rmsnorm_fwd_kernel(const T* __rest
       store8(a + row * lda + c * 8, o);
     }
   }
+}
+
+// rows of cpr 16-byte chunks; blockIdx.y: one of several matrices, next_* bytes apart
+__global__ __launch_bounds__(EW_THREADS) void copy_rows_kernel(const char* __restrict__ src, int64_t ld_src, int64_t next_src,
+                                                               char* __restrict__ dst, int64_t ld_dst, int64_t next_dst, int cpr,
+                                                               int64_t total) {
+  const int64_t id = int64_t(blockIdx.x) * EW_THREADS + threadIdx.x;
+  if (id >= total) return;
+  const int64_t row = id / cpr, at = (id - row * cpr) * 16;
+  *reinterpret_cast<uint4*>(dst + blockIdx.y * next_dst + row * ld_dst + at) =
+      *reinterpret_cast<const uint4*>(src + blockIdx.y * next_src + row * ld_src + at);
 }
 
 // eight consecutive bf16 elements as they lie in memory (16 bytes), converted on demand
@@ -422,11 +435,11 @@ inline int blocks_for(int64_t n) { return int((n + EW_THREADS - 1) / EW_THREADS)
 namespace mls {
 
 hipError_t rmsnorm_fwd(int dt, const void* x, int64_t ldx, const void* gamma, void* a, int64_t lda, float* r, int T,
-                       int h, float eps, hipStream_t st) {
+                       int h, float eps, hipStream_t st, void* copy, int64_t ldc) {
   if (T == 0) return hipSuccess;
 #define FWD(TY, C)                                                                                             \
   hipLaunchKernelGGL((rmsnorm_fwd_kernel<TY, C>), dim3(T), dim3(EW_THREADS), 0, st, (const TY*)x, ldx,             \
-                     (const TY*)gamma, (TY*)a, lda, r, h, eps)
+                     (const TY*)gamma, (TY*)a, lda, r, h, eps, (TY*)copy, ldc)
   const int mc = h <= 4096 ? 2 : h <= 8192 ? 4 : 8;
   if (dt == DT_BF16) {
     if (mc == 2) FWD(bf16_t, 2); else if (mc == 4) FWD(bf16_t, 4); else FWD(bf16_t, 8);
@@ -464,6 +477,16 @@ hipError_t rmsnorm_bwd_reduce(const float* partial0, float* dgamma0, const float
   if (T == 0) return hipSuccess;
   hipLaunchKernelGGL(colsum_add_kernel, dim3((h + 15) / 16, partial1 ? 2 : 1), dim3(256), 0, st, partial0, dgamma0, partial1, dgamma1,
                      rmsnorm_bwd_blocks(T), h, overwrite);
+  return hipGetLastError();
+}
+
+hipError_t copy_rows(const void* src, int64_t ld_src, int64_t next_src, void* dst, int64_t ld_dst, int64_t next_dst, int64_t bytes,
+                     int rows, int n, hipStream_t st) {
+  if (rows == 0 || n == 0 || bytes == 0) return hipSuccess;
+  if ((bytes | ld_src | ld_dst | next_src | next_dst) & 15) return hipErrorInvalidValue;
+  const int64_t cpr = bytes / 16, total = rows * cpr;
+  hipLaunchKernelGGL(copy_rows_kernel, dim3(blocks_for(total), n), dim3(EW_THREADS), 0, st, (const char*)src, ld_src, next_src, (char*)dst,
+                     ld_dst, next_dst, int(cpr), total);
   return hipGetLastError();
 }
 

@@ -582,8 +582,7 @@ static int head_forward(mls_ends* s, const void* y, const int32_t* targets, floa
   char* nr = s->nrm + size_t(slot) * s->mb_h;
   char* dl = s->dlog + size_t(slot) * s->mb_v;
   float* r = s->r + size_t(slot) * T;
-  HIP_TRY(copy2d(s, ys, s->ld_h, y, h, T, h));
-  HIP_TRY(mls::rmsnorm_fwd(s->dt, ys, s->ld_h, s->gamma, nr, s->ld_h, r, T, h, s->c.rms_eps, s->st));
+  HIP_TRY(mls::rmsnorm_fwd(s->dt, y, h, s->gamma, nr, s->ld_h, r, T, h, s->c.rms_eps, s->st, ys, s->ld_h));
   if (s->wlm_t) HIP_TRY(gemm(s, mls::GEMM_NT, nr, s->wlm_t, dl, T, V, int(depth64(h)), s->ld_h, s->ld_h, s->ld_v));
   else HIP_TRY(gemm(s, mls::GEMM_NN, nr, s->wlm, dl, T, V, h, s->ld_h, s->ld_v, s->ld_v));
   const float scale = loss_weight / (float)T;

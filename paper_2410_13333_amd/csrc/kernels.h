@@ -141,8 +141,12 @@ hipError_t gemm_f32(int mode, const void* A, const void* B, void* C, const void*
 // ---- row-wise and elementwise kernels (elementwise.hip); dt selects the storage type; every matrix argument is
 // followed by its row stride in elements (all row strides are multiples of 8)
 // a = x * r * gamma, r[t] = rsqrt(mean(x^2) + eps) saved as fp32
+// copy, if given, receives x with row stride ldc
 hipError_t rmsnorm_fwd(int dt, const void* x, int64_t ldx, const void* gamma, void* a, int64_t lda, float* r, int T,
-                       int h, float eps, hipStream_t st);
+                       int h, float eps, hipStream_t st, void* copy = nullptr, int64_t ldc = 0);
+// n matrices of `rows` rows of `bytes`, next_* apart: dense <-> row-padded.  Pointers, strides and bytes are multiples of 16.
+hipError_t copy_rows(const void* src, int64_t ld_src, int64_t next_src, void* dst, int64_t ld_dst, int64_t next_dst, int64_t bytes,
+                     int rows, int n, hipStream_t st);
 // dx = dres + r*(dn - n*mean(dn*n)), dn = da*gamma, n = x*r;  dgamma += sum_t da*n (two-stage, deterministic).
 // partial: workspace of rmsnorm_bwd_blocks(T) * h floats.  dres may be null (no residual branch: dx without it).
 // overwrite: dgamma = instead of +=.  A sequence of calls over several micro-batches may share one column

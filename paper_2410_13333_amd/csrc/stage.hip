@@ -237,15 +237,16 @@ hipError_t copy2d(const mls_stage* s, void* dst, int64_t ld_dst, const void* src
 
 // ---- one decoder layer, forward.  `x` lives in the stash entry already; `out` receives x + attention + MLP.
 // `x`: the layer input (row stride ld_h); `e`: the entry that receives the layer's other tensors (e + L.x itself
-// is not touched); out == nullptr skips the last contraction (recomputation needs only its operands).
-int layer_forward(mls_stage* s, int layer, const char* x, char* e, void* out, int64_t ld_out) {
+// is not touched); out == nullptr skips the last contraction (recomputation needs only its operands).  dense: the caller's
+// rows (stride h), which the first norm takes to x on the way; null: x holds the input.
+int layer_forward(mls_stage* s, int layer, char* x, char* e, void* out, int64_t ld_out, const void* dense = nullptr) {
   const mls_config& c = s->c;
   const LayerStash& L = s->ls;
   const int T = s->T, h = c.hidden, f = c.ffn;
   const int hk = int(depth64(h)), fk = int(depth64(f));  // contraction lengths over padded rows (bf16 storage)
   const int64_t lh = s->ld_h, lq = s->ld_qkv, lo = s->ld_qd, lg = s->ld_gu, lf = s->ld_f;
-  LAUNCH(CLS_NORM, mls::rmsnorm_fwd(s->dt, x, lh, s->param(layer, s->ioff_g1), e + L.a, lh, (float*)(e + L.r1), T, h,
-                                    c.rms_eps, s->st));
+  LAUNCH(CLS_NORM, mls::rmsnorm_fwd(s->dt, dense ? dense : x, dense ? h : lh, s->param(layer, s->ioff_g1), e + L.a, lh,
+                                    (float*)(e + L.r1), T, h, c.rms_eps, s->st, dense ? x : nullptr, lh));
   // with the transposed weight copies (bf16 storage) every product runs as X (W^T)^T, W^T being the [row][k] operand
   const bool wt = s->params_t != nullptr;
   if (s->fuse_rope) {  // the rotation of q and k is the epilogue of their projection
@@ -581,13 +582,13 @@ int mls_stage_forward(mls_stage* s, const void* x, int32_t k_layers, void* y) {
   if (k_layers == 0) {
     HIP_TRY(hipMemcpyAsync(y, x, act, hipMemcpyDeviceToDevice, s->st));
   } else {
-    HIP_TRY(copy2d(s, s->slot_layer(slot, 0) + s->ls.x, s->ld_h, x, s->c.hidden, s->T, s->c.hidden));
     for (int l = 0; l < k_layers; l++) {
       const bool last = l + 1 == k_layers;
       void* out = last ? y : (void*)(s->slot_layer(slot, l + 1) + s->ls.x);
       char* e = s->slot_layer(slot, l);
       // with recomputation only x is kept; the layer's other tensors are temporaries in the first scratch entry
-      if (int rc = layer_forward(s, l, e + s->ls.x, s->c.recompute ? s->rc_scratch : e, out, last ? s->c.hidden : s->ld_h))
+      if (int rc = layer_forward(s, l, e + s->ls.x, s->c.recompute ? s->rc_scratch : e, out, last ? s->c.hidden : s->ld_h,
+                                 l == 0 ? x : nullptr))
         return rc;
     }
   }
@@ -629,8 +630,6 @@ int mls_stage_backward_ex(mls_stage* s, const void* dY, float* grads, int32_t n,
     char* dx = (char*)dX + size_t(i) * act;
     if (k[i] == 0) {
       if (dx != dy) HIP_TRY(hipMemcpyAsync(dx, dy, act, hipMemcpyDeviceToDevice, s->st));
-    } else {
-      HIP_TRY(copy2d(s, pp(i, k[i] & 1), s->ld_h, dy, h, s->T, h));
     }
   }
   std::vector<const void*> wg[4][2];  // operands of the weight gradients: z dy | b dgu | o dh | a dqkv
@@ -641,8 +640,14 @@ int mls_stage_backward_ex(mls_stage* s, const void* dY, float* grads, int32_t n,
     for (int i = 0; i < n; i++) have += k[i] > l;
     for (int i = 0; i < n; i++) {
       if (k[i] <= l) continue;
+  for (int i = 0, m; i < n; i += m) {  // dY into the padded buffers: one launch for neighbours in the same set of them
+    for (m = 1; i + m < n && m < 65535 && k[i] > 0 && k[i + m] > 0 && ((k[i] ^ k[i + m]) & 1) == 0;) m++;
+    if (k[i] > 0)
+      HIP_TRY(mls::copy_rows((const char*)dY + size_t(i) * act, int64_t(h) * s->es, act, pp(i, k[i] & 1), s->ld_h * s->es, s->mb_h,
+                             int64_t(h) * s->es, s->T, m, s->st));
+  }
       seen++;
-      const char* x = s->slot_layer(slot[i], l) + L.x;
+      char* x = s->slot_layer(slot[i], l) + L.x;
       const char* e = s->slot_layer(slot[i], l);
       if (c.recompute) {  // rebuild this layer's tensors from its kept input, into scratch entry i
         char* sc = s->rc_scratch + size_t(i) * L.bytes;
