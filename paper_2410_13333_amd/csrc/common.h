@@ -125,8 +125,11 @@ __device__ __forceinline__ float round_bf16(float v) { return (float)(bf16_t)v; 
 __device__ __forceinline__ float sigmoidf_(float g) { return 1.f / (1.f + __expf(-g)); }
 
 // ---- gate/up column order.  Public: [gate 0..f) | up 0..f)].  Interleaved (internal, used when the SwiGLU is fused
-// into the contractions around it; needs f % 32 == 0): 32 gate columns, then the 32 up columns of the same indices,
-// and so on, so that a lane of the contraction's epilogue holds a gate and its up.
+// into the contractions around it): 32 gate columns, then the 32 up columns of the same indices, and so on, so that a lane of
+// the contraction's epilogue holds a gate and its up.  The last group is filled up with zero weights where f % 32 != 0: the
+// matrices are then 2 gu_width(f) columns wide.
+__host__ __device__ __forceinline__ int gu_width(int f) { return (f + 31) / 32 * 32; }
+__host__ __device__ __forceinline__ bool gu_column_exists(int n, int f) { return (n >> 6) * 32 + (n & 31) < f; }
 __host__ __device__ __forceinline__ int gu_public_col(int n, int f) { return ((n >> 5) & 1) * f + (n >> 6) * 32 + (n & 31); }
 __host__ __device__ __forceinline__ int gu_interleaved_col(int c, int f) {
   const int w = c >= f, r = c - w * f;
@@ -235,9 +238,10 @@ __device__ __forceinline__ void f32_results(float* C, int64_t ldc, int row0, int
   const int l16 = lane & 15, g4 = lane >> 4, chk = lane % CH, r0 = lane / CH;
   const int n = w0 + chk * 4;
   const int64_t at = xf > 0 ? gu_public_col(col0 + n, xf) : col0 + n;
+  const bool some = n < N && (xf <= 0 || gu_column_exists(col0 + n, xf));
   int off[NQ];
 #pragma unroll
-  for (int q = 0; q < NQ; q++) off[q] = n < N ? int(((q * RPI + r0) * ldc + at) * 4) : int(OOB);
+  for (int q = 0; q < NQ; q++) off[q] = some ? int(((q * RPI + r0) * ldc + at) * 4) : int(OOB);
   auto block = [&](int i) {
     const int r = row0 + 16 * i, rows = r >= M ? 0 : M - r < 16 ? M - r : 16;
     return __builtin_amdgcn_make_buffer_rsrc(C + (rows > 0 ? int64_t(r) * ldc : 0), 0, int(rows * ldc * 4), 0x00020000);

@@ -527,7 +527,7 @@ hipError_t swiglu_bwd(int dt, const void* dz, int64_t ld_dz, const void* gu, int
                       int T, int f, hipStream_t st, bool interleaved) {
   const int64_t total = int64_t(T) * (f >> 3);
   if (total == 0) return hipSuccess;
-  if (interleaved && (dt != DT_BF16 || f % 32)) return hipErrorInvalidValue;
+  if (interleaved && (dt != DT_BF16 || f % 8)) return hipErrorInvalidValue;
   if (interleaved)
     hipLaunchKernelGGL((swiglu_bwd_kernel<bf16_t, true>), dim3(blocks_for(total)), dim3(EW_THREADS), 0, st,
                        (const bf16_t*)dz, ld_dz, (const bf16_t*)gu, ld_gu, (bf16_t*)dgu, ld_dgu, total, f);

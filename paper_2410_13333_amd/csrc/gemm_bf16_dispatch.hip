@@ -3,6 +3,7 @@
 #include <algorithm>
 #include <cmath>
 
+#include "common.h"
 #include "kernels.h"
 
 namespace {
@@ -237,7 +238,7 @@ bool gemm_tn_segments_ok(int kseg, int64_t lda, int64_t ldb) { return gemm_bf16_
 hipError_t gemm_bf16_tn_segments(const void* const* A, const void* const* B, int nseg, void* C, int M, int N, int kseg,
                                  int64_t lda, int64_t ldb, int64_t ldc, hipStream_t st, int gu_f, bool overwrite) {
   if (M == 0 || N == 0 || nseg == 0 || kseg == 0) return hipSuccess;
-  if (nseg > 16 || (gu_f > 0 && (gu_f % 32 || N != 2 * gu_f))) return hipErrorInvalidValue;
+  if (nseg > 16 || (gu_f > 0 && (gu_f % 8 || N != 2 * gu_width(gu_f)))) return hipErrorInvalidValue;
   const T16Problem p = tn_problem({A, B, C, M, N, lda, ldb, ldc, gu_f}, nseg, kseg, overwrite);
   return run(p, st, [&](int n1, const SplitSpace*) {
     return gemm_m16_tn_segments(A, B, nseg, C, M, n1, kseg, lda, ldb, ldc, p.ab, p.bb, st, gu_f, overwrite);
@@ -273,7 +274,7 @@ hipError_t gemm_bf16_tn_group(const TnProduct* p, int n, int tile, int nseg, int
   T16Problem q[MAX_T16_GROUP];
   int m = 0;
   for (int i = 0; i < n; i++) {
-    if (p[i].gu_f > 0 && (p[i].gu_f % 32 || p[i].N != 2 * p[i].gu_f)) return hipErrorInvalidValue;
+    if (p[i].gu_f > 0 && (p[i].gu_f % 8 || p[i].N != 2 * gu_width(p[i].gu_f))) return hipErrorInvalidValue;
     if (p[i].M == 0 || p[i].N == 0) continue;
     q[m++] = tn_problem(p[i], nseg, kseg, overwrite);
   }

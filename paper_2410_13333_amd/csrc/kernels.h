@@ -61,7 +61,7 @@ void t16_tile_size(int form, int tile, int& rows, int& cols);  // T16_* of a for
 // weight gradient of several micro-batches in one launch: C[M,N] += sum_i A_i[kseg,M]^T * B_i[kseg,N], C fp32,
 // at most 16 pieces, all with the same strides; true if the operands fit the DMA path's 31-bit offsets
 bool gemm_tn_segments_ok(int kseg, int64_t lda, int64_t ldb);
-// gu_f > 0: the N = 2 gu_f columns of the B pieces are in the interleaved gate/up order and C is in the public one
+// gu_f > 0: the N = 2 gu_width(gu_f) columns of the B pieces are in the interleaved gate/up order and C is in the public one
 // overwrite: C = instead of C += (the fp32 gradient is then not read)
 hipError_t gemm_bf16_tn_segments(const void* const* A, const void* const* B, int nseg, void* C, int M, int N, int kseg,
                                  int64_t lda, int64_t ldb, int64_t ldc, hipStream_t st, int gu_f = 0,
@@ -119,7 +119,7 @@ hipError_t gemm_t16(const T16Problem& p, int tile, hipStream_t st);
 constexpr int MAX_T16_GROUP = 4;
 hipError_t gemm_t16_group(const T16Problem* p, int n, int tile, hipStream_t st);
 hipError_t fill_zero_f32(float* p, size_t n, hipStream_t st);
-// SwiGLU fused into the gate/up contraction (bf16, f % 32 == 0, DMA path).  Interleaved gate/up column order:
+// SwiGLU fused into the gate/up contraction (bf16, f % 32 == 0 here, DMA path).  Interleaved gate/up column order:
 // 32 gate columns, the 32 up columns of the same indices, and so on (gu_interleaved_col in common.h).
 //   GU[M, 2f] = A[M,K] W[K, 2f] (W and GU interleaved), Z[M, f] = silu(gate) * up
 // W is given transposed, [2f][K] (rows in the interleaved order) with row stride ldw.

@@ -67,9 +67,8 @@ def test_ragged_gqa_fp32_and_bf16_multi_microbatch():
 
 
 def test_ragged_shape_with_fused_swiglu():
-    """ffn % 32 == 0 switches w_gu, gu and dgu to the interleaved gate/up column order inside the library; weights
-    (generator and get/set), the captured gu / dgu operands and the w_gu gradient must still come out in the
-    public order."""
+    """w_gu, gu and dgu are in the interleaved gate/up column order inside the library; weights (generator and get/set), the
+    captured gu / dgu operands and the w_gu gradient must still come out in the public order."""
     import paper_2410_13333_amd as mls
     sh = FUSED_RAGGED
     st = mls.Stage.from_shape(sh, seed=1000)
@@ -81,6 +80,35 @@ def test_ragged_shape_with_fused_swiglu():
     st.close()
     _check(sh, [3, 3, 3], 1e-2)
     _check(sh, [1, 3, 2], 1e-2, interleave=True)
+
+
+@pytest.mark.parametrize("ffn", [8, 24, 40, 1016])
+def test_fused_swiglu_where_the_last_group_of_32_columns_is_not_full(ffn):
+    """What fills it up is zero inside and never seen outside: weights, captured operands and gradients (the fill would lie in
+    the next row of the w_gu gradient; the first overwriting call meets NaN there)."""
+    import torch
+    import paper_2410_13333_amd as mls
+    sh = RAGGED.with_(ffn=ffn, layers=2)
+    st = mls.Stage.from_shape(sh, seed=1000)
+    bits, _ = synth.make_params(sh, 1000)
+    assert np.array_equal(storage_bits(st.get_params()), bits)
+    p = st.get_params()
+    st.set_params(p.flip(0).contiguous())
+    assert np.array_equal(storage_bits(st.get_params()), bits[::-1])
+    st.set_params(p)
+    x, dy = to_device(synth.make_x(sh, 2000, 0)[0], "bf16"), to_device(synth.make_dy(sh, 3000, 0)[0], "bf16")
+    y, dx = torch.empty_like(x), torch.empty_like(dy)
+    a, b = torch.full((st.grad_elems,), float("nan"), device="cuda"), torch.zeros(st.grad_elems, device="cuda")
+    st.forward(x, 2, y)
+    gu, z = st.debug_read("gu", 1).float(), st.debug_read("z", 1).float()
+    ref = gu[:, :ffn] * torch.sigmoid(gu[:, :ffn]) * gu[:, ffn:]
+    assert ((z - ref).norm() / ref.norm()).item() < 2.0 ** -7  # two roundings of the gate and the up, one of the product
+    st.backward(dy.unsqueeze(0), a, 1, dx.unsqueeze(0), overwrite=True)
+    st.forward(x, 2, y)
+    st.backward(dy.unsqueeze(0), b, 1, dx.unsqueeze(0))
+    assert torch.equal(a, b)
+    st.close()
+    _check(sh, [2, 1, 2], 1e-2)
 
 
 def test_set_params_reaches_every_copy_of_the_weights():
