@@ -1,7 +1,8 @@
 // Causal grouped-query attention for bf16 storage on the gfx950 matrix cores: forward with online softmax,
 // backward as two kernels (dQ, which also forms the row sums delta = dO . O; dK and dV) that recompute the
-// probabilities from the saved log-sum-exp.
-// Nothing of size S x S is ever written; no float atomics, so results are bitwise reproducible.
+// probabilities from the saved log-sum-exp.  Where few workgroups share the chip, dQ is formed from the dS that the dK / dV
+// kernel leaves behind instead (dq_from_ds); nothing else of size S x S is ever written.  No float atomics, so results are
+// bitwise reproducible.
 //
 // Register-resident probabilities.  v_mfma_f32_32x32x16_bf16 leaves element (g*4+r) of lane l at
 // [row (l/32)*4 + 8g + r][col l%32] of the 32x32 result and expects the B operand as "lane l holds column
@@ -573,6 +574,14 @@ __global__ __launch_bounds__(AT_THREADS, 2) void attn_dq_kernel(const bf16_t* __
 // LDS: V of the workgroup's keys if it lives there, a ring of five steps [Q | dO | row statistics].  The one
 // barrier of a step lies within S(it): step it+1 has landed for everyone, and the slot of step it-2 is free for it+3
 // (its last reads came before the Q fragments that S(it) has waited for, and LDS reads return in order).
+// ds (may be null): dS of every head for the dQ kernel, in bf16 as it enters dK.  Tiles of 32 query rows x 32 keys at or below the
+// diagonal, a row of tiles after the other; a tile is 2 KiB as the accumulators hold it: rows 16 h .. 16 h + 15 in its half
+// h, 16 bytes per lane = key lane % 32, rows 4 (lane / 32) .. +3 and 8 + 4 (lane / 32) .. +3.
+constexpr int DS_TILE = 2048;
+__host__ __device__ __forceinline__ int64_t ds_head_bytes(int S) {
+  const int64_t n = (S + 31) / 32;
+  return n * (n + 1) / 2 * DS_TILE;
+}
 template <int D, int KT>
 __global__ __launch_bounds__(AT_THREADS, 1) void attn_dkv_kernel(const bf16_t* __restrict__ qkv, int64_t ld,
                                                                  const bf16_t* __restrict__ d_o, int64_t ldo,
@@ -580,13 +589,14 @@ __global__ __launch_bounds__(AT_THREADS, 1) void attn_dkv_kernel(const bf16_t* _
                                                                  bf16_t* __restrict__ dqkv, int64_t ldg, int S, int nq,
                                                                  int nkv, int nsplit, float* __restrict__ part,
                                                                  const float* __restrict__ cos_tab,
-                                                                 const float* __restrict__ sin_tab) {
+                                                                 const float* __restrict__ sin_tab, char* __restrict__ ds) {
   using TS = Tile<D, 32>;
   constexpr int KD = D / 16, DT = D / 32, KR = 32 * KT, SLOTS = 5;
   constexpr bool VL = KT == 2;                               // V fragments from LDS
   static_assert(KT == 1 || D == 128);
   constexpr int STG = 2 * TS::BYTES + 512, V_BYTES = VL ? 4 * KR * D * 2 : 0;
   constexpr int NREQ = 2 * TS::NI + 1;                       // requests of a wavefront per step
+  constexpr int NST = 2 * KT;                                // and stores of dS
   __shared__ __attribute__((aligned(1024))) char lds[V_BYTES + SLOTS * STG];  // [V] [slot][Q|dO|lse log2(e)|-delta]
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), half = lane >> 5;
   // nsplit > 1: the query heads of a group are shared out over nsplit workgroups (few KV heads would otherwise
@@ -767,12 +777,14 @@ __global__ __launch_bounds__(AT_THREADS, 1) void attn_dkv_kernel(const bf16_t* _
   const int dead = min(nst, (jw - j0) / 32), alive = nst - dead;
   for (int hd = 0; hd < grp; hd++) {
     int i0 = (q0 + nst - 1) * 32;  // of this step
+    const auto rs_ds = __builtin_amdgcn_make_buffer_rsrc(ds + (int64_t(bi) * nq + hq0 + hd) * ds_head_bytes(S), 0, int(ds_head_bytes(S)), 0x00020000);
     static_for<FA>(read);
     for (int it = 0; it < alive; it++) {
       // ---- S(it)
       constexpr int Q1 = R1 / 4;
       run(I0{}, std::integral_constant<int, Q1>{}, I3{}, none);
-      wait_vmcnt<NREQ>();
+      // (the stores of the step before may be on their way too; a head's first step follows on one without)
+      if (ds && it > 0) wait_vmcnt<NREQ + NST>(); else wait_vmcnt<NREQ>();
       __builtin_amdgcn_s_barrier();
       asm volatile("" ::: "memory");
       issue_q();
@@ -841,6 +853,15 @@ __global__ __launch_bounds__(AT_THREADS, 1) void attn_dkv_kernel(const bf16_t* _
         pf[kt][1] = acc_to_b(st[kt], 1);
         df[kt][1] = acc_to_b(dp[kt], 1);
       }
+      if (ds) {  // as many stores in every step: those above the diagonal go nowhere
+        const int qs = i0 / 32, kt0 = jw / 32;
+#pragma unroll
+        for (int kt = 0; kt < KT; kt++)
+#pragma unroll
+          for (int h = 0; h < 2; h++)
+            __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, df[kt][h]), rs_ds, kt0 + kt <= qs ? lane * 16 : int(OOB),
+                                                   (qs * (qs + 1) / 2 + kt0 + kt) * DS_TILE + h * 1024, 0);
+      }
       static_for<FA>([&](auto IC) { f[decltype(IC)::value] = f[R3 + decltype(IC)::value]; });
       ca += adv;  // the columns move on to this step's slot (in a head's first step, which has no predecessor, they were there already)
       sa += next;
@@ -901,6 +922,120 @@ __global__ __launch_bounds__(AT_THREADS, 1) void attn_dkv_kernel(const bf16_t* _
               make_float4(dv[kt][t][g * 4], dv[kt][t][g * 4 + 1], dv[kt][t][g * 4 + 2], dv[kt][t][g * 4 + 3]);
         }
     }
+  }
+}
+
+// ================================================================ backward: dQ from the dS of the dK / dV kernel
+// The row statistics that kernel takes, when no dQ kernel has formed them: lse log2(e), then -(dO . O), each [b][n_q][S].
+// grid (n_q, blocks of 64 positions, b).  HBM-bound.
+template <int D>
+__global__ __launch_bounds__(AT_THREADS) void attn_stats_kernel(const bf16_t* __restrict__ o, int64_t ld_o, const bf16_t* __restrict__ d_o,
+                                                                int64_t ldo, const float* __restrict__ lse, float* __restrict__ stats, int S,
+                                                                int nq) {
+  constexpr int L = D / 8, G = AT_THREADS / L;  // lanes per row, rows at a time
+  const int hq = blockIdx.x, bi = blockIdx.z, c = threadIdx.x % L * 8;
+  uint4 vo[64 / G], vd[64 / G];
+#pragma unroll
+  for (int i = 0; i < 64 / G; i++) {
+    const int64_t row = int64_t(bi) * S + min(int(blockIdx.y) * 64 + i * G + int(threadIdx.x) / L, S - 1);
+    vo[i] = *reinterpret_cast<const uint4*>(o + row * ld_o + hq * D + c);
+    vd[i] = *reinterpret_cast<const uint4*>(d_o + row * ldo + hq * D + c);
+  }
+#pragma unroll
+  for (int i = 0; i < 64 / G; i++) {
+    const bf16x8 a = __builtin_bit_cast(bf16x8, vo[i]), b = __builtin_bit_cast(bf16x8, vd[i]);
+    float dl = 0.f;
+#pragma unroll
+    for (int e = 0; e < 8; e++) dl += (float)a[e] * (float)b[e];
+#pragma unroll
+    for (int m = 1; m < L; m <<= 1) dl += __shfl_xor(dl, m, 64);
+    const int q = blockIdx.y * 64 + i * G + threadIdx.x / L;
+    if (threadIdx.x % L == 0 && q < S) {
+      const int64_t si = (int64_t(bi) * nq + hq) * S + q;
+      stats[si] = lse[si] * LOG2E;
+      stats[int64_t(gridDim.z) * nq * S + si] = -dl;
+    }
+  }
+}
+
+// dQ^T += K^T dS^T over the keys at or below the diagonal.  grid (n_q, q blocks of 128, b), longest first; wave w owns query rows
+// q0 + 32 w .. +31 and streams its own row of dS tiles; the K tiles of 64 keys are shared.  HBM-bound, if enough is on its way:
+// K comes two deep and dS three deep by LDS-DMA, two workgroups per CU.
+template <int D>
+__global__ __launch_bounds__(AT_THREADS, 2) void attn_dq_ds_kernel(const bf16_t* __restrict__ qkv, int64_t ld, const char* __restrict__ ds,
+                                                                   bf16_t* __restrict__ dqkv, int64_t ldg, int S, int nq, int nkv,
+                                                                   const float* __restrict__ cos_tab, const float* __restrict__ sin_tab) {
+  using TL = Tile<D>;
+  constexpr int DT = D / 32, DSB = 2 * DS_TILE;  // dS of a wavefront per block of 64 keys
+  constexpr int NDS = 3, RING = 2 * TL::BYTES;   // dS stages, behind the two of K
+  __shared__ __attribute__((aligned(1024))) char lds[RING + NDS * 4 * DSB];
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int qb = gridDim.y - 1 - blockIdx.y;
+  const int hq = blockIdx.x, bi = blockIdx.z, hk = hq / (nq / nkv);
+  const bf16_t* base = qkv + int64_t(bi) * S * ld;
+  const int q0 = qb * 128, qs = q0 / 32 + wave, qi = qs * 32 + (lane & 31);
+  const i32x4 rk = make_rsrc(base, uint32_t(int64_t(S) * ld * 2));
+  // this wavefront's row of tiles; what lies beyond the diagonal is out of its range
+  const i32x4 rd = make_rsrc(ds + (int64_t(bi) * nq + hq) * ds_head_bytes(S) + int64_t(qs) * (qs + 1) / 2 * DS_TILE,
+                             qs * 32 < S ? uint32_t(qs + 1) * DS_TILE : 0u);
+  const uint32_t lds0 = (uint32_t)(uintptr_t)(MLS_LDS char*)&lds[0];
+  TL tl;
+  tl.init(ld, wave, lane);
+  // LDS keeps the chunks of the second lane half with bit 2 of the key inverted (the transposing reads below)
+  const uint32_t src = ((lane & 32) + ((lane & 31) ^ (lane >> 5 << 2))) * 16;
+  const int nblk = (min(S, q0 + 128) + TR - 1) / TR;
+  auto issue_k = [&](int blk) { tl.dma(rk, ld, blk * TR, (nq + hk) * D, lds0 + (blk & 1) * TL::BYTES, wave, blk < nblk); };
+  int ds_slot = 0;  // of the next request
+  auto issue_ds = [&](int blk) {
+#pragma unroll
+    for (int i = 0; i < DSB / 1024; i++)
+      dma16(rd, blk < nblk ? blk * DSB + i * 1024 + src : OOB, lds0 + RING + (ds_slot * 4 + wave) * DSB + i * 1024);
+    ds_slot = ds_slot == NDS - 1 ? 0 : ds_slot + 1;
+  };
+  // 16 keys x 32 rows of a tile as an operand: key and row of this lane's share (see Tile::frag_cols)
+  const int kr = (lane >> 5) * 4 + ((lane & 15) >> 2), c4 = lane & 3;
+  const uint32_t fr = ((lane >> 4) & 1) * 1024 + (((c4 & 1) * 32 + (kr ^ ((c4 & 1) << 2))) * 16) + (c4 >> 1) * 8;
+  f32x16 acc[DT];
+#pragma unroll
+  for (int t = 0; t < DT; t++) acc[t] = zero16();
+  issue_ds(0);
+  issue_k(0);
+  issue_ds(1);
+  int at = 0;  // this block's stage of dS
+  for (int blk = 0; blk < nblk; blk++) {
+    wait_vmcnt<DSB / 1024>();  // all but the dS of the next block
+    __syncthreads();
+    issue_k(blk + 1);
+    issue_ds(blk + 2);
+    const bf16_t* ks = reinterpret_cast<const bf16_t*>(lds + (blk & 1) * TL::BYTES);
+    const char* dst = lds + RING + (at * 4 + wave) * DSB;
+    at = at == NDS - 1 ? 0 : at + 1;
+#pragma unroll
+    for (int jt = 0; jt < 2; jt++) {
+      if (blk * 2 + jt > qs) break;  // (wave-uniform: no row of this wavefront sees a key of the tile)
+      bf16x8 df[2];
+#pragma unroll
+      for (int k = 0; k < 2; k++) {
+        const char* a = dst + jt * DS_TILE + fr + k * 256;
+        const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((MLS_LDS s16x4*)a);
+        const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((MLS_LDS s16x4*)(a + 128));
+        const s16x8 v = {lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
+        df[k] = __builtin_bit_cast(bf16x8, v);
+      }
+      read_ahead<2 * DT, 3, 2>([&](int i) { return TL::frag_cols(ks, i % DT, jt * 2 + i / DT, lane); },
+                               [&](int i, const bf16x8& f) {
+                                 acc[i % DT] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f, df[i / DT], acc[i % DT], 0, 0, 0);
+                               });
+    }
+  }
+  wait_dma();
+  const float scale = rsqrtf((float)D);
+  bf16_t* out = dqkv + int64_t(bi) * S * ldg;
+  if (cos_tab) {
+    store_t_unrotate<D>(out, ldg, qi, qi, hq * D, acc, scale, cos_tab, sin_tab, lane, qi < S);
+  } else {
+#pragma unroll
+    for (int t = 0; t < DT; t++) store_t(out, ldg, qi, hq * D + t * 32, acc[t], scale, lane, qi < S);
   }
 }
 
@@ -990,10 +1125,24 @@ DkvPlan dkv_plan(int b, int S, int nq, int nkv, int d) {
   return best;
 }
 
+// dQ from dS as the dK / dV kernel leaves it in memory, instead of a kernel that forms S, P and dP once more: two of its three
+// products less, for 2 bytes of dS written and read per score and a launch more.  It pays where the dQ kernel is bound by the chain
+// of its few workgroups (about one per CU) and dS stays in the 256 MiB memory-side cache.  Whole backward, dS formed twice / once
+// (us): 16 heads of 128 at 2048 120 / 103, 8 at 4096 217 / 187, 32 at 1000 77 / 70, 32 at 512 49 / 47, 16 x 2 at 256 35 / 33; with
+// more workgroups 32 at 2048 152 / 146 (nothing is left of it in a whole step), 48 at 2048 233 / 236, 32 at 4096 461 / 476.  Heads of 64
+// have half the products for as much dS: 32 at 2048 103 / 108, 16 x 2 at 1000 55 / 53, a step of such a layer 1 029 / 1 038.
+bool dq_from_ds(int b, int S, int nq, int d) {
+  return d == 128 && S >= 256 && int64_t(b) * nq * ((S + 127) / 128) <= 320 && ds_head_bytes(S) * nq * b <= int64_t(256) << 20;
+}
+
+// partial sums of dK and dV, then dS
+size_t part_floats(int b, int S, int nq, int nkv, int d) {
+  const int n = dkv_plan(b, S, nq, nkv, d).ns;
+  return n > 1 ? (size_t(2) * b * nkv * n * S * d + 255) / 256 * 256 : 0;
+}
 size_t attn_bwd_scratch_floats(int dt, int b, int S, int nq, int nkv, int d) {
   if (dt != DT_BF16 || nkv <= 0 || nq % nkv) return 0;
-  const int n = dkv_plan(b, S, nq, nkv, d).ns;
-  return n > 1 ? size_t(2) * b * nkv * n * S * d : 0;
+  return part_floats(b, S, nq, nkv, d) + (dq_from_ds(b, S, nq, d) ? size_t(ds_head_bytes(S)) / 4 * nq * b : 0);
 }
 
 hipError_t attn_bwd_bf16(const void* qkv, int64_t ld_qkv, const void* o, int64_t ld_o, const float* lse, const void* d_o,
@@ -1005,12 +1154,20 @@ hipError_t attn_bwd_bf16(const void* qkv, int64_t ld_qkv, const void* o, int64_t
   const DkvPlan pl = dkv_plan(b, S, nq, nkv, d);
   const int ns = part ? pl.ns : 1, kr = 128 * pl.kt;
   dim3 gq(nq, (S + 127) / 128, b), gk(nkv * ns, (S + kr - 1) / kr, b);
-  auto dq = d == 128 ? attn_dq_kernel<128> : attn_dq_kernel<64>;
+  char* ds = part && dq_from_ds(b, S, nq, d) ? reinterpret_cast<char*>(part + part_floats(b, S, nq, nkv, d)) : nullptr;
   auto dkv = d == 64 ? attn_dkv_kernel<64, 1> : pl.kt == 1 ? attn_dkv_kernel<128, 1> : attn_dkv_kernel<128, 2>;
-  hipLaunchKernelGGL(dq, gq, dim3(AT_THREADS), 0, st, (const bf16_t*)qkv, ld_qkv, (const bf16_t*)o, ld_o,
-                     (const bf16_t*)d_o, ld_do, lse, stats, (bf16_t*)dqkv, ld_dqkv, S, nq, nkv, cos_tab, sin_tab);
+  if (ds) {
+    hipLaunchKernelGGL(attn_stats_kernel<128>, dim3(nq, (S + 63) / 64, b), dim3(AT_THREADS), 0, st, (const bf16_t*)o, ld_o, (const bf16_t*)d_o, ld_do, lse, stats, S, nq);
+  } else {
+    auto dq = d == 128 ? attn_dq_kernel<128> : attn_dq_kernel<64>;
+    hipLaunchKernelGGL(dq, gq, dim3(AT_THREADS), 0, st, (const bf16_t*)qkv, ld_qkv, (const bf16_t*)o, ld_o,
+                       (const bf16_t*)d_o, ld_do, lse, stats, (bf16_t*)dqkv, ld_dqkv, S, nq, nkv, cos_tab, sin_tab);
+  }
   hipLaunchKernelGGL(dkv, gk, dim3(AT_THREADS), 0, st, (const bf16_t*)qkv, ld_qkv, (const bf16_t*)d_o, ld_do, stats,
-                     (bf16_t*)dqkv, ld_dqkv, S, nq, nkv, ns, part, cos_tab, sin_tab);
+                     (bf16_t*)dqkv, ld_dqkv, S, nq, nkv, ns, part, cos_tab, sin_tab, ds);
+  if (ds) {
+    hipLaunchKernelGGL(attn_dq_ds_kernel<128>, gq, dim3(AT_THREADS), 0, st, (const bf16_t*)qkv, ld_qkv, ds, (bf16_t*)dqkv, ld_dqkv, S, nq, nkv, cos_tab, sin_tab);
+  }
   if (ns > 1) {
     const int64_t total = int64_t(2) * b * nkv * S * (d >> 4);
     hipLaunchKernelGGL(gqa_reduce_kernel, dim3(unsigned((total + 255) / 256)), dim3(256), 0, st, part, ns, b, S, d, nq, nkv,

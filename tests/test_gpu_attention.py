@@ -168,3 +168,50 @@ def test_a_non_finite_gradient_reaches_no_position_far_behind_it(nq, nkv, d, seq
     assert not bool(torch.isfinite(hit[0, at]).all())
     assert torch.equal(hit[0, at + 64:], clean[0, at + 64:])
     assert torch.equal(hit[1:], clean[1:])
+
+
+# dQ from the dS in memory (128-column heads from 256 positions on, at most 320 workgroups), and the shapes next to it that form dS
+# again (255 positions; 32 x 11 workgroups); a last step, tile and workgroup that are partly filled; query heads of a group in
+# several workgroups and one after the other
+@pytest.mark.parametrize("nq,nkv,d,seq,mb", [(2, 2, 128, 255, 1), (4, 2, 128, 256, 1), (2, 2, 128, 257, 2), (3, 1, 128, 287, 1), (2, 1, 128, 289, 2),
+                                             (6, 6, 128, 385, 1), (16, 2, 128, 1025, 1), (32, 4, 128, 600, 2), (32, 32, 128, 1280, 1), (32, 32, 128, 1281, 1),
+                                             (80, 80, 128, 500, 1), (10, 10, 128, 4000, 1), (4, 2, 64, 801, 2)])
+def test_dq_and_dkv_on_either_side_of_the_stored_ds(nq, nkv, d, seq, mb):
+    import torch
+    import paper_2410_13333_amd as mls
+    h = 64
+    st = mls.Stage(h, nq, nkv, d, 64, seq, mb, 1, 1, seed=1003)
+    gen = torch.Generator(device="cuda").manual_seed(seq)
+    x, dy = (torch.randn(mb, seq, h, device="cuda", generator=gen).to(torch.bfloat16) for _ in range(2))
+    y, dx, g = torch.empty_like(x), torch.empty_like(x), torch.zeros(st.grad_elems, device="cuda")
+    out = []
+    for _ in range(2):
+        st.forward(x, 1, y)
+        qkv = st.debug_read("qkv").double().reshape(mb, seq, nq + 2 * nkv, d)
+        st.backward(dy, g, 1, dx)
+        out.append(st.debug_read("dqkv"))
+    assert torch.equal(*out)
+    dqkv, dh = out[0].double().reshape(mb, seq, nq + 2 * nkv, d), st.debug_read("dh").double()
+    off, r, c = st.param_layout(0, "w_o")
+    do = (dh @ st.get_params()[off:off + r * c].double().reshape(r, c).t()).to(torch.bfloat16).double().reshape(mb, seq, nq, d)
+    st.close()
+    ang = torch.from_numpy(np.ascontiguousarray(O.rope_angles(seq, d, 10000.0))).cuda().double()
+    back = lambda u: torch.cat([u[:, :d // 2] * ang.cos() + u[:, d // 2:] * ang.sin(), u[:, d // 2:] * ang.cos() - u[:, :d // 2] * ang.sin()], 1)  # noqa: E731
+    hidden = torch.ones(seq, seq, dtype=torch.bool, device="cuda").triu(1)
+    for b in range(mb):
+        for hk in range(nkv):
+            k, v = qkv[b, :, nq + hk], qkv[b, :, nq + nkv + hk]
+            dk, dv = torch.zeros_like(k), torch.zeros_like(v)
+            for hq in range(hk * (nq // nkv), (hk + 1) * (nq // nkv)):
+                q, go = qkv[b, :, hq], do[b, :, hq]
+                p = torch.softmax((q @ k.t() / d ** 0.5).masked_fill(hidden, -float("inf")), dim=-1)
+                dp = go @ v.t()
+                ds = p * (dp - (p * dp).sum(-1, keepdim=True)) / d ** 0.5
+                dk += ds.t() @ q
+                dv += p.t() @ go
+                e = ((dqkv[b, :, hq] - back(ds @ k)).norm() / (ds @ k).norm()).item()
+                # P, dS and the result are rounded to bf16 (2^-9 relative each), o and dO enter rounded
+                assert e <= 1e-2, ("dq", b, hq, e)
+            for name, ref, got in (("dk", back(dk), dqkv[b, :, nq + hk]), ("dv", dv, dqkv[b, :, nq + nkv + hk])):
+                e = ((got - ref).norm() / ref.norm()).item()
+                assert e <= 1e-2, (name, b, hk, e)
