@@ -48,6 +48,130 @@ __global__ __launch_bounds__(EW_THREADS) void rmsnorm_fwd_kernel(const T* __rest
   }
 }
 
+// ---------------------------------------------------------------- RMSNorm of many narrow rows: one wavefront per row (bf16)
+// A workgroup per row leaves half of its threads or more without a chunk and waits for two barriers per row; here a row's sum is a
+// wavefront's own.  MAXC: 16-byte chunks per lane.  Both norms of a layer, forward and backward, with the reduction of the gains (us,
+// workgroup per row -> wavefront per row): 12288 rows of 256 90 -> 45, 4096 of 512 49 -> 37, 4096 of 1024 53 -> 45, 2048 of 256 37 -> 33.
+template <int MAXC>
+__global__ __launch_bounds__(EW_THREADS) void rmsnorm_fwd_wave_kernel(const bf16_t* __restrict__ x, int64_t ldx, const bf16_t* __restrict__ gamma,
+                                                                      bf16_t* __restrict__ a, int64_t lda, float* __restrict__ rstd, int rows,
+                                                                      int h, float eps, bf16_t* __restrict__ copy, int64_t ldc) {
+  const int lane = threadIdx.x & 63, nchunk = h >> 3;
+  const int64_t row = int64_t(blockIdx.x) * (EW_THREADS / 64) + (threadIdx.x >> 6);
+  if (row >= rows) return;
+  float v[MAXC][8], g[MAXC][8], ss = 0.f;
+#pragma unroll
+  for (int i = 0; i < MAXC; i++) {
+    const int c = lane + i * 64;
+    if (c < nchunk) {
+      load8(x + row * ldx + c * 8, v[i]);
+      load8(gamma + c * 8, g[i]);
+    }
+  }
+#pragma unroll
+  for (int i = 0; i < MAXC; i++) {
+    const int c = lane + i * 64;
+    if (c < nchunk) {
+      if (copy) store8(copy + row * ldc + c * 8, v[i]);
+#pragma unroll
+      for (int e = 0; e < 8; e++) ss += v[i][e] * v[i][e];
+    }
+  }
+  const float r = rsqrtf(wave_sum(ss) / (float)h + eps);
+  if (lane == 0) rstd[row] = r;
+#pragma unroll
+  for (int i = 0; i < MAXC; i++) {
+    const int c = lane + i * 64;
+    if (c < nchunk) {
+      float o[8];
+#pragma unroll
+      for (int e = 0; e < 8; e++) o[e] = v[i][e] * r * g[i][e];
+      store8(a + row * lda + c * 8, o);
+    }
+  }
+}
+
+// Wavefront w of workgroup b takes rows 4 b + w, 4 (b + gridDim.x) + w, ...; the four wavefronts' column sums for dgamma meet in
+// LDS, in their order, and go to partial[b][:].
+template <int MAXC>
+__global__ __launch_bounds__(EW_THREADS) void rmsnorm_bwd_wave_kernel(const bf16_t* __restrict__ da, int64_t ld_da, const bf16_t* __restrict__ x,
+                                                                      int64_t ldx, const bf16_t* __restrict__ gamma,
+                                                                      const float* __restrict__ rstd, const bf16_t* dres, int64_t ld_dres,
+                                                                      bf16_t* dx, int64_t ld_dx, float* __restrict__ partial, int rows, int h,
+                                                                      bool acc_partial) {
+  constexpr int W = EW_THREADS / 64;
+  __shared__ float sums[W][MAXC * 512];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, nchunk = h >> 3;
+  float g[MAXC][8], dg[MAXC][8];
+#pragma unroll
+  for (int i = 0; i < MAXC; i++) {
+    const int c = lane + i * 64;
+#pragma unroll
+    for (int e = 0; e < 8; e++) dg[i][e] = 0.f;
+    if (c < nchunk) load8(gamma + c * 8, g[i]);
+  }
+  for (int64_t row = int64_t(blockIdx.x) * W + wave; row < rows; row += int64_t(gridDim.x) * W) {
+    const float r = rstd[row];
+    float n[MAXC][8], dn[MAXC][8], res[MAXC][8], dot = 0.f;
+#pragma unroll
+    for (int i = 0; i < MAXC; i++) {
+      const int c = lane + i * 64;
+      if (c < nchunk) {
+        load8(x + row * ldx + c * 8, n[i]);
+        load8(da + row * ld_da + c * 8, dn[i]);
+        if (dres) {
+          load8(dres + row * ld_dres + c * 8, res[i]);
+        } else {
+#pragma unroll
+          for (int e = 0; e < 8; e++) res[i][e] = 0.f;
+        }
+      }
+    }
+#pragma unroll
+    for (int i = 0; i < MAXC; i++) {
+      const int c = lane + i * 64;
+      if (c < nchunk) {
+#pragma unroll
+        for (int e = 0; e < 8; e++) {
+          n[i][e] *= r;
+          dg[i][e] += dn[i][e] * n[i][e];
+          dn[i][e] *= g[i][e];
+          dot += dn[i][e] * n[i][e];
+        }
+      }
+    }
+    const float mean = wave_sum(dot) / (float)h;
+#pragma unroll
+    for (int i = 0; i < MAXC; i++) {
+      const int c = lane + i * 64;
+      if (c < nchunk) {
+        float o[8];
+#pragma unroll
+        for (int e = 0; e < 8; e++) o[e] = res[i][e] + r * (dn[i][e] - n[i][e] * mean);
+        store8(dx + row * ld_dx + c * 8, o);
+      }
+    }
+  }
+#pragma unroll
+  for (int i = 0; i < MAXC; i++)
+    if (lane + i * 64 < nchunk) store8(&sums[wave][(lane + i * 64) * 8], dg[i]);
+  __syncthreads();
+  for (int c = threadIdx.x * 4; c < h; c += EW_THREADS * 4) {
+    float4* p = reinterpret_cast<float4*>(partial + int64_t(blockIdx.x) * h + c);
+    float4 t = *reinterpret_cast<const float4*>(&sums[0][c]);
+#pragma unroll
+    for (int w = 1; w < W; w++) {
+      const float4 u = *reinterpret_cast<const float4*>(&sums[w][c]);
+      t.x += u.x; t.y += u.y; t.z += u.z; t.w += u.w;
+    }
+    if (acc_partial) {  // on top of what earlier calls left (same workgroup, same rows' share: a fixed order)
+      const float4 u = *p;
+      t.x += u.x; t.y += u.y; t.z += u.z; t.w += u.w;
+    }
+    *p = t;
+  }
+}
+
 // rows of cpr 16-byte chunks; blockIdx.y: one of several matrices, next_* bytes apart
 __global__ __launch_bounds__(EW_THREADS) void copy_rows_kernel(const char* __restrict__ src, int64_t ld_src, int64_t next_src,
                                                                char* __restrict__ dst, int64_t ld_dst, int64_t next_dst, int cpr,
@@ -434,9 +558,20 @@ inline int blocks_for(int64_t n) { return int((n + EW_THREADS - 1) / EW_THREADS)
 
 namespace mls {
 
+// (below 2048 rows the launch is what either form costs; wider rows are no faster by wavefront: 2 x 4096 rows of 2048 97 and 105 us)
+static bool norm_by_wave(int dt, int T, int h) { return dt == DT_BF16 && h <= 1024 && T >= 2048; }
+
 hipError_t rmsnorm_fwd(int dt, const void* x, int64_t ldx, const void* gamma, void* a, int64_t lda, float* r, int T,
                        int h, float eps, hipStream_t st, void* copy, int64_t ldc) {
   if (T == 0) return hipSuccess;
+  if (norm_by_wave(dt, T, h)) {
+#define FWDW(C)                                                                                                                        \
+  hipLaunchKernelGGL((rmsnorm_fwd_wave_kernel<C>), dim3((T + 3) / 4), dim3(EW_THREADS), 0, st, (const bf16_t*)x, ldx, (const bf16_t*)gamma, \
+                     (bf16_t*)a, lda, r, T, h, eps, (bf16_t*)copy, ldc)
+    if (h <= 512) FWDW(1); else FWDW(2);
+#undef FWDW
+    return hipGetLastError();
+  }
 #define FWD(TY, C)                                                                                             \
   hipLaunchKernelGGL((rmsnorm_fwd_kernel<TY, C>), dim3(T), dim3(EW_THREADS), 0, st, (const TY*)x, ldx,             \
                      (const TY*)gamma, (TY*)a, lda, r, h, eps, (TY*)copy, ldc)
@@ -457,16 +592,22 @@ hipError_t rmsnorm_bwd(int dt, const void* da, int64_t ld_da, const void* x, int
                        float* partial, int T, int h, hipStream_t st, bool overwrite, bool acc_partial, bool reduce) {
   if (T == 0) return hipSuccess;
   const int nb = rmsnorm_bwd_blocks(T);
+#define BWDW(C)                                                                                                                         \
+  hipLaunchKernelGGL((rmsnorm_bwd_wave_kernel<C>), dim3(nb), dim3(EW_THREADS), 0, st, (const bf16_t*)da, ld_da, (const bf16_t*)x, ldx,            \
+                     (const bf16_t*)gamma, r, (const bf16_t*)dres, ld_dres, (bf16_t*)dx, ld_dx, partial, T, h, acc_partial)
 #define BWD(TY, C)                                                                                               \
   hipLaunchKernelGGL((rmsnorm_bwd_kernel<TY, C>), dim3(nb), dim3(EW_THREADS), 0, st, (const TY*)da, ld_da,            \
                      (const TY*)x, ldx, (const TY*)gamma, r, (const TY*)dres, ld_dres, (TY*)dx, ld_dx, partial, T, h, acc_partial)
   const int mc = h <= 4096 ? 2 : h <= 8192 ? 4 : 8;
-  if (dt == DT_BF16) {
+  if (norm_by_wave(dt, T, h)) {
+    if (h <= 512) BWDW(1); else BWDW(2);
+  } else if (dt == DT_BF16) {
     if (mc == 2) BWD(bf16_t, 2); else if (mc == 4) BWD(bf16_t, 4); else BWD(bf16_t, 8);
   } else {
     if (mc == 2) BWD(float, 2); else if (mc == 4) BWD(float, 4); else BWD(float, 8);
   }
 #undef BWD
+#undef BWDW
   hipError_t e = hipGetLastError();
   if (e != hipSuccess || !reduce) return e;
   return rmsnorm_bwd_reduce(partial, dgamma, nullptr, nullptr, T, h, st, overwrite);

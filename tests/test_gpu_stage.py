@@ -111,6 +111,14 @@ def test_fused_swiglu_where_the_last_group_of_32_columns_is_not_full(ffn):
     _check(sh, [2, 1, 2], 1e-2)
 
 
+@pytest.mark.parametrize("hidden,tokens", [(72, 2047), (72, 2048), (512, 2051), (520, 2048), (1024, 2101), (1032, 2048)])
+def test_norms_of_many_narrow_rows(hidden, tokens):
+    """2048 rows of up to 1024 elements and more run by wavefronts: rows and columns that do not fill them, and the shapes next to
+    the rule."""
+    sh = synth.StageShape(hidden=hidden, n_q_heads=1, n_kv_heads=1, head_dim=64, ffn=64, seq=tokens, micro_batch=1, layers=1, microbatches=2)
+    _check(sh, [1, 1], 1e-2)
+
+
 def test_set_params_reaches_every_copy_of_the_weights():
     """The library keeps transposed copies of the weight matrices for its forward products: a stage whose parameters
     were replaced by another stage's must give that stage's output and input gradient bit for bit."""
