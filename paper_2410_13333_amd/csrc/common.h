@@ -279,6 +279,41 @@ __device__ __forceinline__ void f32_results(float* C, int64_t ldc, int row0, int
   }
 }
 
+// ---- out[c] (+)= sum_b partial[b][c] for one or two pairs (mls::Colsum): workgroup `w` of 256 threads takes 16 columns, 16 row groups
+// per column, in a fixed summation order.  What bounds it is the latency of a thread's up to 32 loads: eight are in flight at
+// a time, and the two gains of a layer share a launch (two launches that loaded one by one: 2 x 11 us at hidden 1024, 2 x 6.6 at
+// 256; then 4.7 and 2.7), or go along with the layer's weight gradients.
+constexpr int COLSUM_LDS = 16 * 17;  // floats
+template <class Colsum>
+__device__ __forceinline__ void colsum_block(const Colsum& cs, int w, float* red) {
+  const int per = (cs.h + 15) / 16;
+  const bool second = w >= per;
+  const float* partial = second ? cs.partial1 : cs.partial0;
+  float* out = second ? cs.out1 : cs.out0;
+  const int cl = threadIdx.x & 15, grp = threadIdx.x >> 4, h = cs.h;
+  const int c = (second ? w - per : w) * 16 + cl;
+  float s = 0.f;
+  if (c < h) {
+    int b = grp;
+    for (; b + 112 < cs.nblocks; b += 128) {
+      float v[8];
+#pragma unroll
+      for (int i = 0; i < 8; i++) v[i] = partial[int64_t(b + 16 * i) * h + c];
+#pragma unroll
+      for (int i = 0; i < 8; i++) s += v[i];
+    }
+    for (; b < cs.nblocks; b += 16) s += partial[int64_t(b) * h + c];
+  }
+  red[grp * 17 + cl] = s;
+  __syncthreads();
+  if (grp == 0 && c < h) {
+    float t = 0.f;
+#pragma unroll
+    for (int g = 0; g < 16; g++) t += red[g * 17 + cl];
+    out[c] = cs.overwrite ? t : out[c] + t;
+  }
+}
+
 __device__ __forceinline__ float to_f32(bf16_t v) { return (float)v; }
 __device__ __forceinline__ float to_f32(float v) { return v; }
 __device__ __forceinline__ void from_f32(bf16_t& d, float v) { d = (bf16_t)v; }

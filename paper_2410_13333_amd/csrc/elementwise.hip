@@ -339,37 +339,9 @@ __global__ __launch_bounds__(EW_THREADS) void rmsnorm_bwd_kernel(const T* __rest
   }
 }
 
-// out[c] += sum_b partial[b][c] for one or two pairs (grid y): 16 columns per workgroup, 16 row groups per column, fixed
-// summation order.  What bounds it is the latency of a thread's up to 32 loads: eight are in flight at a time, and the
-// two gains of a layer share a launch (two launches that loaded one by one: 2 x 11 us at hidden 1024, 2 x 6.6 at 256; now 4.7 and 2.7).
-__global__ __launch_bounds__(256) void colsum_add_kernel(const float* __restrict__ partial0, float* __restrict__ out0,
-                                                         const float* __restrict__ partial1, float* __restrict__ out1,
-                                                         int nblocks, int h, bool overwrite) {
-  __shared__ float red[16][17];
-  const float* partial = blockIdx.y ? partial1 : partial0;
-  float* out = blockIdx.y ? out1 : out0;
-  const int cl = threadIdx.x & 15, grp = threadIdx.x >> 4;
-  const int c = blockIdx.x * 16 + cl;
-  float s = 0.f;
-  if (c < h) {
-    int b = grp;
-    for (; b + 112 < nblocks; b += 128) {
-      float v[8];
-#pragma unroll
-      for (int i = 0; i < 8; i++) v[i] = partial[int64_t(b + 16 * i) * h + c];
-#pragma unroll
-      for (int i = 0; i < 8; i++) s += v[i];
-    }
-    for (; b < nblocks; b += 16) s += partial[int64_t(b) * h + c];
-  }
-  red[grp][cl] = s;
-  __syncthreads();
-  if (grp == 0 && c < h) {
-    float t = 0.f;
-#pragma unroll
-    for (int g = 0; g < 16; g++) t += red[g][cl];
-    out[c] = overwrite ? t : out[c] + t;
-  }
+__global__ __launch_bounds__(256) void colsum_add_kernel(mls::Colsum cs) {
+  __shared__ float red[COLSUM_LDS];
+  colsum_block(cs, blockIdx.x, red);
 }
 
 __global__ __launch_bounds__(256) void fill_zero_kernel(float4* __restrict__ p, size_t n4) {
@@ -610,14 +582,15 @@ hipError_t rmsnorm_bwd(int dt, const void* da, int64_t ld_da, const void* x, int
 #undef BWDW
   hipError_t e = hipGetLastError();
   if (e != hipSuccess || !reduce) return e;
-  return rmsnorm_bwd_reduce(partial, dgamma, nullptr, nullptr, T, h, st, overwrite);
+  return rmsnorm_bwd_reduce(rmsnorm_bwd_sums(partial, dgamma, nullptr, nullptr, T, h, overwrite), st);
 }
 
-hipError_t rmsnorm_bwd_reduce(const float* partial0, float* dgamma0, const float* partial1, float* dgamma1, int T, int h,
-                              hipStream_t st, bool overwrite) {
-  if (T == 0) return hipSuccess;
-  hipLaunchKernelGGL(colsum_add_kernel, dim3((h + 15) / 16, partial1 ? 2 : 1), dim3(256), 0, st, partial0, dgamma0, partial1, dgamma1,
-                     rmsnorm_bwd_blocks(T), h, overwrite);
+Colsum rmsnorm_bwd_sums(const float* partial0, float* dgamma0, const float* partial1, float* dgamma1, int T, int h, bool overwrite) {
+  return {partial0, dgamma0, partial1, dgamma1, rmsnorm_bwd_blocks(T), h, overwrite ? 1 : 0, (h + 15) / 16 * (partial1 ? 2 : 1)};
+}
+hipError_t rmsnorm_bwd_reduce(const Colsum& cs, hipStream_t st) {
+  if (cs.nblocks == 0 || cs.wgs == 0) return hipSuccess;
+  hipLaunchKernelGGL(colsum_add_kernel, dim3(cs.wgs), dim3(256), 0, st, cs);
   return hipGetLastError();
 }
 

@@ -268,7 +268,7 @@ int gemm_bf16_tn_group_tile(const TnProduct* p, int n, int nseg, int kseg, bool 
   return best;
 }
 
-hipError_t gemm_bf16_tn_group(const TnProduct* p, int n, int tile, int nseg, int kseg, hipStream_t st, bool overwrite) {
+hipError_t gemm_bf16_tn_group(const TnProduct* p, int n, int tile, int nseg, int kseg, hipStream_t st, bool overwrite, const Colsum& cs) {
   if (nseg == 0 || kseg == 0) return hipSuccess;
   if (n < 1 || n > MAX_T16_GROUP || nseg > 16 || tile < 0) return hipErrorInvalidValue;
   T16Problem q[MAX_T16_GROUP];
@@ -278,7 +278,7 @@ hipError_t gemm_bf16_tn_group(const TnProduct* p, int n, int tile, int nseg, int
     if (p[i].M == 0 || p[i].N == 0) continue;
     q[m++] = tn_problem(p[i], nseg, kseg, overwrite);
   }
-  return m == 0 ? hipSuccess : gemm_t16_group(q, m, tile, st);
+  return m == 0 ? hipSuccess : gemm_t16_group(q, m, tile, st, cs);
 }
 
 bool gemm_swiglu_ok(int M, int f, int K, int64_t lda, int64_t ldw) {

@@ -53,6 +53,7 @@ struct SegProblem {
 struct SegArgs {
   int nseg, n;
   SegProblem p[mls::MAX_T16_GROUP];
+  mls::Colsum cs;  // the last cs.wgs workgroups add columns up instead
 };
 struct NoSegs {};
 struct RopeArgs {
@@ -90,7 +91,15 @@ __global__ __launch_bounds__(256, (Cfg<WTM, WTN, WGM, ATR, BTR, EPI, SEG, NS>::P
   constexpr int BM = G::BM, BN = G::BN;
   extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
   // tile of this workgroup: each XCD gets a contiguous run of tiles, walked in groups of about 1024 rows, N fastest
-  const int nwg = gridDim.x, pid = blockIdx.x;
+  int nwg = gridDim.x;
+  const int pid = blockIdx.x;
+  if constexpr (SEG) {
+    nwg -= segs.cs.wgs;
+    if (pid >= nwg) {
+      colsum_block(segs.cs, pid - nwg, reinterpret_cast<float*>(smem));
+      return;
+    }
+  }
   const int xcd = pid & 7, q8 = nwg >> 3, rem = nwg & 7;
   int tile = xcd * q8 + (xcd < rem ? xcd : rem) + (pid >> 3);
   // the problem it belongs to
@@ -427,7 +436,7 @@ hipError_t launch_t16_as(const Args& a) {
       p.tile0 = tiles;
       tiles += p.tiles_m * ((p.N + G::BN - 1) / G::BN);
     }
-    hipLaunchKernelGGL(kern, dim3(unsigned(tiles)), dim3(256), G::LDS, a.st, a.A, a.B, a.C, a.R, a.M, a.N, a.K, a.lda, a.ldb, a.ldc, a.ldr,
+    hipLaunchKernelGGL(kern, dim3(unsigned(tiles + segs.cs.wgs)), dim3(256), G::LDS, a.st, a.A, a.B, a.C, a.R, a.M, a.N, a.K, a.lda, a.ldb, a.ldc, a.ldr,
                        a.ab, a.bb, 0, a.col0, a.X, a.ldx, a.xf, segs, a.rope, SplitArgs{nullptr, nullptr, 1});
   } else {
     const int tm = (a.M + G::BM - 1) / G::BM, tn = (a.N + G::BN - 1) / G::BN;
@@ -493,7 +502,7 @@ hipError_t gemm_t16(const T16Problem& p, int tile, hipStream_t st) {
   return hipErrorInvalidValue;
 }
 
-hipError_t gemm_t16_group(const T16Problem* p, int n, int tile, hipStream_t st) {
+hipError_t gemm_t16_group(const T16Problem* p, int n, int tile, hipStream_t st, const Colsum& cs) {
   if (n < 1 || n > MAX_T16_GROUP) return hipErrorInvalidValue;
   Args a = {};
   a.K = p[0].K;
@@ -501,6 +510,7 @@ hipError_t gemm_t16_group(const T16Problem* p, int n, int tile, hipStream_t st) 
   a.st = st;
   a.segs.nseg = p[0].nseg;
   a.segs.n = n;
+  a.segs.cs = cs;
   for (int i = 0; i < n; i++) {
     const T16Problem& q = p[i];
     if (q.form != T16_TN_SEGS || q.K != a.K || q.nseg != a.segs.nseg || q.ldx != a.ldx || q.M <= 0 || q.N <= 0 || q.K <= 0 || q.nseg < 1 ||

@@ -27,6 +27,16 @@ inline hipError_t raise_lds_limit(const void* kern, int bytes, std::atomic<uint6
   return e;
 }
 
+// Column sums: out[c] (+)= sum over nblocks rows of partial[.][h], one or two of them; wgs: workgroups of 256 threads (colsum_block in
+// common.h)
+struct Colsum {
+  const float* partial0;
+  float* out0;
+  const float* partial1;
+  float* out1;
+  int nblocks, h, overwrite, wgs;
+};
+
 // Workspace of contractions that are shared out over several workgroups per tile (join_parts in common.h); it belongs to the
 // launches of one stream.  state: SPLIT_TILES pairs of counters, zero between launches; sums: what the products need
 // (gemm_split_floats), at most SPLIT_FLOATS.  Null: none is shared out.
@@ -77,7 +87,8 @@ struct TnProduct {
 // the tile (T16_*) of one launch for all of them, where their tiles together fill the chip better, or -1: a launch (or two)
 // for each is faster.  Host only.
 int gemm_bf16_tn_group_tile(const TnProduct* p, int n, int nseg, int kseg, bool overwrite);
-hipError_t gemm_bf16_tn_group(const TnProduct* p, int n, int tile, int nseg, int kseg, hipStream_t st, bool overwrite);
+// cs: column sums that go along in the same launch (not done if there is nothing to launch: no product, no piece)
+hipError_t gemm_bf16_tn_group(const TnProduct* p, int n, int tile, int nseg, int kseg, hipStream_t st, bool overwrite, const Colsum& cs = {});
 // the 256x256 tiles of a problem on the 16x16x32 form of the matrix instruction (gemm_bf16_m16.hip); K % 8 == 0 where an
 // operand is stored [row][k], % 64 in the two fused forms
 hipError_t gemm_m16(int mode, const void* A, const void* B, void* C, const void* R, int M, int N, int K, int64_t lda,
@@ -117,7 +128,7 @@ struct T16Problem {
 hipError_t gemm_t16(const T16Problem& p, int tile, hipStream_t st);
 // up to four T16_TN_SEGS problems over pieces of the same number and depth in one launch
 constexpr int MAX_T16_GROUP = 4;
-hipError_t gemm_t16_group(const T16Problem* p, int n, int tile, hipStream_t st);
+hipError_t gemm_t16_group(const T16Problem* p, int n, int tile, hipStream_t st, const Colsum& cs = {});
 hipError_t fill_zero_f32(float* p, size_t n, hipStream_t st);
 // SwiGLU fused into the gate/up contraction (bf16, f % 32 == 0 here, DMA path).  Interleaved gate/up column order:
 // 32 gate columns, the 32 up columns of the same indices, and so on (gu_interleaved_col in common.h).
@@ -157,9 +168,10 @@ hipError_t rmsnorm_bwd(int dt, const void* da, int64_t ld_da, const void* x, int
                        const float* r, const void* dres, int64_t ld_dres, void* dx, int64_t ld_dx, float* dgamma,
                        float* partial, int T, int h, hipStream_t st, bool overwrite = false, bool acc_partial = false,
                        bool reduce = true);
-// the column reduction of one or (partial1 given) two such sequences over the same T in one launch
-hipError_t rmsnorm_bwd_reduce(const float* partial0, float* dgamma0, const float* partial1, float* dgamma1, int T, int h,
-                              hipStream_t st, bool overwrite);
+// the column reduction of one or (partial1 given) two such sequences over the same T, of a launch of its own or with
+// gemm_bf16_tn_group
+Colsum rmsnorm_bwd_sums(const float* partial0, float* dgamma0, const float* partial1, float* dgamma1, int T, int h, bool overwrite);
+hipError_t rmsnorm_bwd_reduce(const Colsum& cs, hipStream_t st);
 // rotate the pairs (i, i+d/2) of the first n_heads heads of every row of u [T, ld] by sign*angle(t % S, i)
 hipError_t rope_inplace(int dt, void* u, const float* cos_tab, const float* sin_tab, int T, int S, int n_heads, int d,
                         int64_t ld, float sign, hipStream_t st);

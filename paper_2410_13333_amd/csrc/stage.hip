@@ -283,12 +283,17 @@ int layer_forward(mls_stage* s, int layer, char* x, char* e, void* out, int64_t 
   return MLS_OK;
 }
 
+// the sums of both gains' gradients of a layer over the micro-batches of a call
+mls::Colsum gain_sums(const mls_stage* s, float* g, bool ow) {
+  return mls::rmsnorm_bwd_sums(s->partial, g + s->off_g1, s->partial2, g + s->off_g2, s->T, s->c.hidden, ow);
+}
+
 // ---- one decoder layer, backward, for micro-batch workspace `w`: everything except the four weight-gradient
 // contractions, whose operands (dy, dgu, dh, dqkv of this micro-batch) stay in the workspace for them.
 // dy: gradient w.r.t. the layer output (row stride ld_dy); dx receives the gradient w.r.t. its input (row stride
 // ld_dx); g: this layer's slice of the caller's fp32 gradient vector (gains only here).
 int layer_backward_data(mls_stage* s, int layer, const char* x, const char* e, int w, const void* dy, int64_t ld_dy,
-                        void* dx, int64_t ld_dx, float* g, bool ow, bool first, bool last) {
+                        void* dx, int64_t ld_dx, float* g, bool ow, bool first, bool reduce) {
   const mls_config& c = s->c;
   const LayerStash& L = s->ls;
   const int T = s->T, h = c.hidden, f = c.ffn, qd = s->qd, wq = s->qkvw;
@@ -318,7 +323,7 @@ int layer_backward_data(mls_stage* s, int layer, const char* x, const char* e, i
   LAUNCH(CLS_GEMM_NT, gemm(s, mls::GEMM_NT, dqkv, s->param(layer, s->ioff_wqkv), s->dbuf, nullptr, T, h, wq, lq, lq, lh));
   LAUNCH(CLS_NORM, mls::rmsnorm_bwd(s->dt, s->dbuf, lh, x, lh, s->param(layer, s->ioff_g1), (const float*)(e + L.r1),
                                     dh, lh, dx, ld_dx, g + s->off_g1, s->partial, T, h, s->st, ow, !first, false));
-  if (last) LAUNCH(CLS_NORM, mls::rmsnorm_bwd_reduce(s->partial, g + s->off_g1, s->partial2, g + s->off_g2, T, h, s->st, ow));
+  if (reduce) LAUNCH(CLS_NORM, mls::rmsnorm_bwd_reduce(gain_sums(s, g, ow), s->st));
   return MLS_OK;
 }
 
@@ -345,7 +350,8 @@ int shared_wgrad_tile(const mls_stage* s, const mls::TnProduct (&p)[4], int n, b
 
 // C[M,N] += sum_i A_i[T,M]^T B_i[T,N] over n micro-batches (fp32 C) for each of them: in steps of 16 micro-batches on the bf16
 // DMA path (always taken when gu_f > 0), one launch per micro-batch and weight otherwise
-int wgrad(mls_stage* s, const mls::TnProduct (&p)[4], int n, bool ow) {
+// cs: the gains' sums, which go along with the first launch that all four share (only given if there is one)
+int wgrad(mls_stage* s, const mls::TnProduct (&p)[4], int n, bool ow, const mls::Colsum& cs) {
   for (int i = 0; i < n; i += 16) {
     const int m = n - i < 16 ? n - i : 16;
     mls::TnProduct q[4];
@@ -357,7 +363,7 @@ int wgrad(mls_stage* s, const mls::TnProduct (&p)[4], int n, bool ow) {
     const bool over = ow && i == 0;
     const int tile = shared_wgrad_tile(s, q, m, over);
     if (tile >= 0) {
-      LAUNCH(CLS_GEMM_TN, mls::gemm_bf16_tn_group(q, 4, tile, m, s->T, s->st, over));
+      LAUNCH(CLS_GEMM_TN, mls::gemm_bf16_tn_group(q, 4, tile, m, s->T, s->st, over, i == 0 ? cs : mls::Colsum{}));
       continue;
     }
     for (auto& w : q) {
@@ -652,6 +658,9 @@ int mls_stage_backward_ex(mls_stage* s, const void* dY, float* grads, int32_t n,
     for (auto& w : wg) w[0].clear(), w[1].clear();
     int have = 0, seen = 0;  // micro-batches of this call that contain layer l
     for (int i = 0; i < n; i++) have += k[i] > l;
+    mls::TnProduct w[4];
+    weight_grads(s, g, nullptr, w);
+    const bool shared = shared_wgrad_tile(s, w, have < 16 ? have : 16, ow) >= 0;
     for (int i = 0; i < n; i++) {
       if (k[i] <= l) continue;
       seen++;
@@ -664,14 +673,13 @@ int mls_stage_backward_ex(mls_stage* s, const void* dY, float* grads, int32_t n,
       }
       const char* dy = pp(i, (l + 1) & 1);
       void* dx = l == 0 ? (void*)((char*)dX + size_t(i) * act) : (void*)pp(i, l & 1);
-      if (int rc = layer_backward_data(s, l, x, e, i, dy, s->ld_h, dx, l == 0 ? h : s->ld_h, g, ow, seen == 1, seen == have)) return rc;
+      if (int rc = layer_backward_data(s, l, x, e, i, dy, s->ld_h, dx, l == 0 ? h : s->ld_h, g, ow, seen == 1, seen == have && !shared)) return rc;
       const void* ops[4][2] = {{e + L.z, dy}, {e + L.b, s->dgu + size_t(i) * s->mb_gu}, {e + L.o, s->dh + size_t(i) * s->mb_h},
                                {e + L.a, s->dqkv + size_t(i) * s->mb_qkv}};
       for (int w = 0; w < 4; w++) wg[w][0].push_back(ops[w][0]), wg[w][1].push_back(ops[w][1]);
     }
-    mls::TnProduct w[4];
     weight_grads(s, g, wg, w);
-    if (int rc = wgrad(s, w, (int)wg[0][0].size(), ow)) return rc;
+    if (int rc = wgrad(s, w, have, ow, shared ? gain_sums(s, g, ow) : mls::Colsum{})) return rc;
   }
   // overwrite mode: the layers no entry of this call reached hold no gradient
   if (ow && kmax < c.max_layers)
