@@ -26,6 +26,12 @@ LARGE = [
     ((4104, 2, 1, 64, 16384, 700), 3, (0, 1, 256, 128, 2)), ((8200, 2, 1, 64, 16384, 513), 3, (8200, 2, 0, 0, 1))]
 
 
+@pytest.fixture(autouse=True)
+def _torch_first():
+    """torch brings a HIP runtime of its own: loaded after the library, it would be a second one in the process, without a device."""
+    import torch  # noqa: F401
+
+
 def _cfg(hidden, nq, nkv, d, ffn, T):
     return mls.MlsConfig(hidden, nq, nkv, d, ffn, T, 1, 1, 1, 1e-5, 10000.0, 0, 0)
 
