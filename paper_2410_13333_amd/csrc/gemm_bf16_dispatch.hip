@@ -23,12 +23,14 @@ struct Plan {
 //     L2 bandwidth are shared).
 //   128x64, 64x64: two and three workgroups per CU.  A lone workgroup is a chain of waits; past that the loads of a CU's
 //     workgroups add up.  deep: what a long contraction costs where many of them share a CU, whose panels leave the L2 between
-//     one k-tile and the next.
+//     one k-tile and the next.  top: how far the fullest CU counts beyond the average one, since the last of its workgroups ends
+//     the launch (128x64, us per k-tile: 0.29 with 254 tiles, 0.45 with 258, 0.56 with 490, 0.79 with 513).  By the average alone
+//     1141 x 2152 over 5248 (306 tiles of 128x64, 48 us) did not get its 128x128 tiles (36 us), nor 1650 x 1280 over 11840 its
+//     own (96 instead of 73, 66 shared out).
 // Results in bf16 (NN, NT): fitted to stand-alone timings of every tile size, whole and shared out, at 426 shapes (64 to 8192
-// tokens, widths 192 to 8192, contractions of 192 to 50304, N(0,1) operands).  The plan with the smallest estimate is on average
-// 1.6 % slower than the fastest one measured there, 1.2 % among the whole ones; the worst is 45 % (1650 x 1280 over 11840: 96 us
-// instead of 66).  Before, from 66 shapes that ended at a contraction of 11008: 2.6 % among the whole ones, the worst 76 %
-// (3532 x 4848 over 16320).
+// tokens, widths 192 to 8192, contractions of 192 to 50304, N(0,1) operands), top to these and 320 more.  The plan with the
+// smallest estimate is on average 0.8 % slower than the fastest one measured at all of them, 0.2 % among the whole ones; the worst
+// is 19 % (448 x 4392 over 25472, whole: 189 us instead of 159).
 // Results in fp32 (TN): twice the bytes where they are stored, four times where they are added to, which a tile that has its CU
 // for itself moves while the matrix cores idle: fitted apart, to the weight gradients of 130 layers inside a stage (48 to 5400
 // tokens, hidden 192 to 8192), every tile size, in one launch and apart; 3 to 15 % (rms, from 256x256 to 64x64).  Choosing by it
@@ -54,23 +56,23 @@ double estimate(Result res, int tile, int64_t w, int64_t it) {  // w tiles
     const double part = double(w % CUS) / CUS, full = double(w / CUS) * (double(it) * r.hi + r.base);
     return part > 0 ? full + double(it) * (r.lo + (r.hi - r.lo) * part) + r.base * (r.share + (1 - r.share) * part) : full;
   }
-  struct Load { double lone, c0, c1, base, each, deep; };  // each: per workgroup of a CU; deep: see above
-  const Load loads[3][2] = {{{0.265, 0.047, 0.291, 4.1, 0, 0.053}, {0.212, 0.105, 0.150, 3.1, 0, 0.153}},
+  struct Load { double lone, c0, c1, base, each, deep, top; };  // each: per workgroup of a CU; deep, top: see above
+  const Load loads[3][2] = {{{0.265, 0.047, 0.291, 4.1, 0, 0.053, 0.22}, {0.212, 0.105, 0.150, 3.1, 0, 0.153, 0.33}},
                             {{0.344, 0.078, 0.319, 4.4, 2.11}, {0.266, 0.121, 0.195, 3.5, 1.05}},
                             {{0.366, 0.063, 0.316, 5.0, 4.24}, {0.286, 0.076, 0.200, 3.7, 1.97}}};
   const Load& l = loads[res][tile == mls::T16_128x64 ? 0 : 1];
-  const double load = double(w) / CUS;
+  const double load = double(w) / CUS, felt = load + l.top * (double((w + CUS - 1) / CUS) - load);
   double deep = 1;
   if (load > 2 && it > 64) deep += l.deep * std::min(1.0, load / 2 - 1) * std::min(std::log2(double(it) / 64), 2.5);
-  const double loop = double(it) * std::max(l.lone, (l.c0 + l.c1 * load) * deep);
+  const double loop = double(it) * std::max(l.lone, (l.c0 + l.c1 * felt) * deep);
   return loop + (res == R_BF16 ? l.base * std::max(1.0, load / 2) : l.base + l.each * load);
 }
 double estimate(Result res, int tile, int64_t M, int64_t N, int64_t it) { return estimate(res, tile, tiles_of(tile, M, N), it); }
 
 // Sharing a tile's contraction out over `parts` workgroups (NT products of a caller with a workspace): the time of that many
 // tiles over a share of it each, and of the exchange, which grows with the parts to add and with what all of them move.
-// At 426 shapes (64 to 8192 tokens, widths 192 to 8192, contractions of 192 to 50304) the plan takes 143 of them apart, which
-// then run 1.53 times as fast on average; the worst choice among these loses 2 %.  us: 100 x 1024 x 50304 172 -> 34 (64x64 in 8),
+// At 426 shapes (64 to 8192 tokens, widths 192 to 8192, contractions of 192 to 50304) the plan takes 134 of them apart, which
+// then run 1.42 times as fast on average; the worst choice among these loses 6 % (187 x 232 x 1536: 8.5 us, whole 8.0).  us: 100 x 1024 x 50304 172 -> 34 (64x64 in 8),
 // 700 x 1536 x 8192 40 -> 31 (128x128 in 3), 2048 x 4096 x 22016 310 -> 254 (256x256 in 2), 2048 x 4096 x 4096 stays 59 (75).
 constexpr int MAX_PARTS = 8;
 double join_us(int tile, int parts, int64_t w) {

@@ -85,3 +85,11 @@ def test_short_contractions_into_fp32_results_take_small_tiles():
     assert mls.wgrad_plan(_cfg(1192, 32, 32, 64, 4120, 186, 1, 1), 1)[1] == 64
     assert mls.wgrad_plan(_cfg(2048, 32, 4, 128, 4872, 49, 1, 1), 1)[1] == 64
     assert mls.gemm_plan(2, 4120, 1192, 186)[0] == 0
+
+
+# us measured with the tiles named here / with the 128x64 ones that the average CU speaks for: 260 to 324 of them, two on some CUs only
+@pytest.mark.parametrize("M,N,K,us", [(1141, 2152, 5248, (36, 48)), (3350, 768, 2944, (23, 29)), (393, 4864, 23424, (138, 187)),
+                                      (1650, 1280, 11840, (73, 96))])
+def test_a_cu_with_a_workgroup_more_than_the_others_counts(M, N, K, us):
+    for mode in (0, 1):
+        assert mls.gemm_plan(mode, M, N, K) == (0, 128, 128), us
