@@ -574,7 +574,7 @@ __global__ __launch_bounds__(AT_THREADS, 2) void attn_dq_kernel(const bf16_t* __
 // LDS: V of the workgroup's keys if it lives there, a ring of five steps [Q | dO | row statistics].  The one
 // barrier of a step lies within S(it): step it+1 has landed for everyone, and the slot of step it-2 is free for it+3
 // (its last reads came before the Q fragments that S(it) has waited for, and LDS reads return in order).
-// ds (may be null): dS of every head for the dQ kernel, in bf16 as it enters dK.  Tiles of 32 query rows x 32 keys at or below the
+// With DS, ds takes dS of every head for the dQ kernel, in bf16 as it enters dK.  Tiles of 32 query rows x 32 keys at or below the
 // diagonal, a row of tiles after the other; a tile is 2 KiB as the accumulators hold it: rows 16 h .. 16 h + 15 in its half
 // h, 16 bytes per lane = key lane % 32, rows 4 (lane / 32) .. +3 and 8 + 4 (lane / 32) .. +3.
 constexpr int DS_TILE = 2048;
@@ -582,21 +582,18 @@ __host__ __device__ __forceinline__ int64_t ds_head_bytes(int S) {
   const int64_t n = (S + 31) / 32;
   return n * (n + 1) / 2 * DS_TILE;
 }
-template <int D, int KT>
-__global__ __launch_bounds__(AT_THREADS, 1) void attn_dkv_kernel(const bf16_t* __restrict__ qkv, int64_t ld,
-                                                                 const bf16_t* __restrict__ d_o, int64_t ldo,
-                                                                 const float* __restrict__ stats,
-                                                                 bf16_t* __restrict__ dqkv, int64_t ldg, int S, int nq,
-                                                                 int nkv, int nsplit, float* __restrict__ part,
-                                                                 const float* __restrict__ cos_tab,
-                                                                 const float* __restrict__ sin_tab, char* __restrict__ ds) {
+template <int D, int KT, bool DS>
+__device__ __forceinline__ void attn_dkv(const bf16_t* __restrict__ qkv, int64_t ld, const bf16_t* __restrict__ d_o, int64_t ldo,
+                                         const float* __restrict__ stats, bf16_t* __restrict__ dqkv, int64_t ldg, int S, int nq, int nkv,
+                                         int nsplit, float* __restrict__ part, const float* __restrict__ cos_tab,
+                                         const float* __restrict__ sin_tab, char* __restrict__ ds) {
   using TS = Tile<D, 32>;
   constexpr int KD = D / 16, DT = D / 32, KR = 32 * KT, SLOTS = 5;
   constexpr bool VL = KT == 2;                               // V fragments from LDS
   static_assert(KT == 1 || D == 128);
   constexpr int STG = 2 * TS::BYTES + 512, V_BYTES = VL ? 4 * KR * D * 2 : 0;
   constexpr int NREQ = 2 * TS::NI + 1;                       // requests of a wavefront per step
-  constexpr int NST = 2 * KT;                                // and stores of dS
+  constexpr int NST = DS ? 2 * KT : 0;                       // and stores of dS
   __shared__ __attribute__((aligned(1024))) char lds[V_BYTES + SLOTS * STG];  // [V] [slot][Q|dO|lse log2(e)|-delta]
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), half = lane >> 5;
   // nsplit > 1: the query heads of a group are shared out over nsplit workgroups (few KV heads would otherwise
@@ -777,14 +774,14 @@ __global__ __launch_bounds__(AT_THREADS, 1) void attn_dkv_kernel(const bf16_t* _
   const int dead = min(nst, (jw - j0) / 32), alive = nst - dead;
   for (int hd = 0; hd < grp; hd++) {
     int i0 = (q0 + nst - 1) * 32;  // of this step
-    const auto rs_ds = __builtin_amdgcn_make_buffer_rsrc(ds + (int64_t(bi) * nq + hq0 + hd) * ds_head_bytes(S), 0, int(ds_head_bytes(S)), 0x00020000);
+    const auto rs_ds = __builtin_amdgcn_make_buffer_rsrc(DS ? ds + (int64_t(bi) * nq + hq0 + hd) * ds_head_bytes(S) : nullptr, 0, DS ? int(ds_head_bytes(S)) : 0, 0x00020000);
     static_for<FA>(read);
     for (int it = 0; it < alive; it++) {
       // ---- S(it)
       constexpr int Q1 = R1 / 4;
       run(I0{}, std::integral_constant<int, Q1>{}, I3{}, none);
-      // (the stores of the step before may be on their way too; a head's first step follows on one without)
-      if (ds && it > 0) wait_vmcnt<NREQ + NST>(); else wait_vmcnt<NREQ>();
+      // (the stores of the step before may be on their way too; a head's first step may follow on one without)
+      if (DS && it > 0) wait_vmcnt<NREQ + NST>(); else wait_vmcnt<NREQ>();
       __builtin_amdgcn_s_barrier();
       asm volatile("" ::: "memory");
       issue_q();
@@ -853,7 +850,7 @@ __global__ __launch_bounds__(AT_THREADS, 1) void attn_dkv_kernel(const bf16_t* _
         pf[kt][1] = acc_to_b(st[kt], 1);
         df[kt][1] = acc_to_b(dp[kt], 1);
       }
-      if (ds) {  // as many stores in every step: those above the diagonal go nowhere
+      if constexpr (DS) {  // as many stores in every step: those above the diagonal go nowhere
         const int qs = i0 / 32, kt0 = jw / 32;
 #pragma unroll
         for (int kt = 0; kt < KT; kt++)
@@ -923,6 +920,22 @@ __global__ __launch_bounds__(AT_THREADS, 1) void attn_dkv_kernel(const bf16_t* _
         }
     }
   }
+}
+
+template <int D, int KT>
+__global__ __launch_bounds__(AT_THREADS, 1) void attn_dkv_kernel(const bf16_t* __restrict__ qkv, int64_t ld, const bf16_t* __restrict__ d_o,
+                                                                 int64_t ldo, const float* __restrict__ stats, bf16_t* __restrict__ dqkv,
+                                                                 int64_t ldg, int S, int nq, int nkv, int nsplit, float* __restrict__ part,
+                                                                 const float* __restrict__ cos_tab, const float* __restrict__ sin_tab) {
+  attn_dkv<D, KT, false>(qkv, ld, d_o, ldo, stats, dqkv, ldg, S, nq, nkv, nsplit, part, cos_tab, sin_tab, nullptr);
+}
+template <int D, int KT>
+__global__ __launch_bounds__(AT_THREADS, 1) void attn_dkv_ds_kernel(const bf16_t* __restrict__ qkv, int64_t ld, const bf16_t* __restrict__ d_o,
+                                                                    int64_t ldo, const float* __restrict__ stats, bf16_t* __restrict__ dqkv,
+                                                                    int64_t ldg, int S, int nq, int nkv, int nsplit, float* __restrict__ part,
+                                                                    const float* __restrict__ cos_tab, const float* __restrict__ sin_tab,
+                                                                    char* __restrict__ ds) {
+  attn_dkv<D, KT, true>(qkv, ld, d_o, ldo, stats, dqkv, ldg, S, nq, nkv, nsplit, part, cos_tab, sin_tab, ds);
 }
 
 // ================================================================ backward: dQ from the dS of the dK / dV kernel
@@ -1152,21 +1165,21 @@ hipError_t attn_bwd_bf16(const void* qkv, int64_t ld_qkv, const void* o, int64_t
   if (!cos_tab != !sin_tab) return hipErrorInvalidValue;
   if (d != 128 && d != 64) return hipErrorInvalidValue;
   const DkvPlan pl = dkv_plan(b, S, nq, nkv, d);
-  const int ns = part ? pl.ns : 1, kr = 128 * pl.kt;
-  dim3 gq(nq, (S + 127) / 128, b), gk(nkv * ns, (S + kr - 1) / kr, b);
   char* ds = part && dq_from_ds(b, S, nq, d) ? reinterpret_cast<char*>(part + part_floats(b, S, nq, nkv, d)) : nullptr;
-  auto dkv = d == 64 ? attn_dkv_kernel<64, 1> : pl.kt == 1 ? attn_dkv_kernel<128, 1> : attn_dkv_kernel<128, 2>;
+  const int ns = part ? pl.ns : 1, kt = ds ? 1 : pl.kt;  // (so few workgroups always get one key tile: their longest chain decides)
+  dim3 gq(nq, (S + 127) / 128, b), gk(nkv * ns, (S + 128 * kt - 1) / (128 * kt), b);
   if (ds) {
     hipLaunchKernelGGL(attn_stats_kernel<128>, dim3(nq, (S + 63) / 64, b), dim3(AT_THREADS), 0, st, (const bf16_t*)o, ld_o, (const bf16_t*)d_o, ld_do, lse, stats, S, nq);
+    hipLaunchKernelGGL((attn_dkv_ds_kernel<128, 1>), gk, dim3(AT_THREADS), 0, st, (const bf16_t*)qkv, ld_qkv, (const bf16_t*)d_o, ld_do, stats,
+                       (bf16_t*)dqkv, ld_dqkv, S, nq, nkv, ns, part, cos_tab, sin_tab, ds);
+    hipLaunchKernelGGL(attn_dq_ds_kernel<128>, gq, dim3(AT_THREADS), 0, st, (const bf16_t*)qkv, ld_qkv, ds, (bf16_t*)dqkv, ld_dqkv, S, nq, nkv, cos_tab, sin_tab);
   } else {
     auto dq = d == 128 ? attn_dq_kernel<128> : attn_dq_kernel<64>;
+    auto dkv = d == 64 ? attn_dkv_kernel<64, 1> : kt == 1 ? attn_dkv_kernel<128, 1> : attn_dkv_kernel<128, 2>;
     hipLaunchKernelGGL(dq, gq, dim3(AT_THREADS), 0, st, (const bf16_t*)qkv, ld_qkv, (const bf16_t*)o, ld_o,
                        (const bf16_t*)d_o, ld_do, lse, stats, (bf16_t*)dqkv, ld_dqkv, S, nq, nkv, cos_tab, sin_tab);
-  }
-  hipLaunchKernelGGL(dkv, gk, dim3(AT_THREADS), 0, st, (const bf16_t*)qkv, ld_qkv, (const bf16_t*)d_o, ld_do, stats,
-                     (bf16_t*)dqkv, ld_dqkv, S, nq, nkv, ns, part, cos_tab, sin_tab, ds);
-  if (ds) {
-    hipLaunchKernelGGL(attn_dq_ds_kernel<128>, gq, dim3(AT_THREADS), 0, st, (const bf16_t*)qkv, ld_qkv, ds, (bf16_t*)dqkv, ld_dqkv, S, nq, nkv, cos_tab, sin_tab);
+    hipLaunchKernelGGL(dkv, gk, dim3(AT_THREADS), 0, st, (const bf16_t*)qkv, ld_qkv, (const bf16_t*)d_o, ld_do, stats,
+                       (bf16_t*)dqkv, ld_dqkv, S, nq, nkv, ns, part, cos_tab, sin_tab);
   }
   if (ns > 1) {
     const int64_t total = int64_t(2) * b * nkv * S * (d >> 4);

@@ -103,3 +103,18 @@ def test_first_reader_of_an_asm_product(attention_asm, form):
     least, seen = shortest_distances(lines)
     assert seen >= 8  # the kernel has such products
     assert NEEDED <= least < 10 ** 6, least
+
+
+def test_first_reader_of_an_asm_product_where_ds_is_stored(attention_asm):
+    (lines,) = [v for k, v in attention_asm.items() if "attn_dkv_ds_kernel" in k]
+    least, seen = shortest_distances(lines)
+    assert seen >= 8
+    assert NEEDED <= least < 10 ** 6, least
+
+
+def test_only_the_kernel_of_few_workgroups_stores_ds(attention_asm):
+    """Two stores through a buffer descriptor per step and key tile there; the other forms of the kernel hold none of it."""
+    stores = {k: sum("buffer_store" in line for line in v) for k, v in attention_asm.items() if "attn_dkv" in k}
+    assert len(stores) == 4
+    for k, n in stores.items():
+        assert n == (2 if "attn_dkv_ds_kernel" in k else 0), k
