@@ -219,7 +219,8 @@ int mls_stage_wgrad_plan(const mls_config* cfg, int32_t n_microbatches, int32_t 
 /* The same for the products of a layer's forward and data gradient over one micro-batch (bf16 storage; product 0 .. 7: q|k|v, o,
  * gate|up, down, and the data gradients of down, gate|up, o, q|k|v).  A stage has a workspace, so that several workgroups may
  * share a tile's contraction: *big_parts of them on the 256x256 tiles of the leading *big_cols columns, *parts on the
- * *tile_rows x *tile_cols tiles behind.  Errors: MLS_E_NULL, MLS_E_CONFIG, MLS_E_RANGE. */
+ * *tile_rows x *tile_cols tiles behind.  No columns and 0 x 0 tiles: an operand of 2 GiB and more, which a kernel of its own takes.
+ * Errors: MLS_E_NULL, MLS_E_CONFIG, MLS_E_RANGE. */
 int mls_stage_product_plan(const mls_config* cfg, int32_t product, int64_t* big_cols, int32_t* big_parts, int32_t* tile_rows,
                            int32_t* tile_cols, int32_t* parts);
 

@@ -452,26 +452,29 @@ void layout(mls_stage* s) {
   s->mb_qkv = align256(T * s->ld_qkv * s->es);
 }
 
-// the products of a layer and micro-batch that run as NT: form and sizes (bf16 storage)
-struct NtProduct { int form, N, K; };
+// the products of a layer and micro-batch that run as NT: form, sizes, row strides of both operands (bf16 storage)
+struct NtProduct { int form, N, K; int64_t lda, ldb; };
 constexpr int NT_PRODUCTS = 8;
 void nt_products(const mls_stage* s, NtProduct (&p)[NT_PRODUCTS]) {
   const int h = s->c.hidden, f = s->c.ffn, hk = int(depth64(h)), fk = int(depth64(f)), gk = int(depth64(2 * int64_t(s->fgu)));
-  p[0] = {s->fuse_rope ? mls::T16_NT_ROPE : mls::T16_NT, s->qkvw, hk};  // q|k|v
-  p[1] = {mls::T16_NT, h, s->qd};                                      // o
-  p[2] = {s->fuse_gu ? mls::T16_NT_SWIGLU : mls::T16_NT, 2 * s->fgu, hk};   // gate|up
-  p[3] = {mls::T16_NT, h, fk};                                         // down
-  p[4] = {mls::T16_NT, f, hk};                                         // data gradients: of down, gate|up, o, q|k|v
-  p[5] = {mls::T16_NT, h, gk};
-  p[6] = {mls::T16_NT, s->qd, hk};
-  p[7] = {mls::T16_NT, h, s->qkvw};
+  const int64_t lh = s->ld_h, lo = s->ld_qd;
+  p[0] = {s->fuse_rope ? mls::T16_NT_ROPE : mls::T16_NT, s->qkvw, hk, lh, lh};             // q|k|v
+  p[1] = {mls::T16_NT, h, s->qd, lo, lo};                                                 // o
+  p[2] = {s->fuse_gu ? mls::T16_NT_SWIGLU : mls::T16_NT, 2 * s->fgu, hk, lh, lh};           // gate|up
+  p[3] = {mls::T16_NT, h, fk, s->ld_f, s->ld_f};                                          // down
+  p[4] = {mls::T16_NT, f, hk, lh, lh};                                                    // data gradients: of down, gate|up, o, q|k|v
+  p[5] = {mls::T16_NT, h, gk, s->ld_gu, s->ld_gu};
+  p[6] = {mls::T16_NT, s->qd, hk, lh, lh};
+  p[7] = {mls::T16_NT, h, s->qkvw, s->ld_qkv, s->ld_qkv};
 }
+bool tiled(const mls_stage* s, const NtProduct& p) { return mls::gemm_bf16_dma_ok(mls::GEMM_NT, s->T, p.N, p.K, p.lda, p.ldb); }
 int64_t split_floats(const mls_stage* s) {
   int64_t n = 0;
   if (s->dt != mls::DT_BF16) return n;
   NtProduct p[NT_PRODUCTS];
   nt_products(s, p);
-  for (auto& q : p) n = std::max(n, mls::gemm_split_floats(q.form, s->T, q.N, q.K));
+  for (auto& q : p)
+    if (tiled(s, q)) n = std::max(n, mls::gemm_split_floats(q.form, s->T, q.N, q.K));
   return n;
 }
 
@@ -883,7 +886,8 @@ int mls_stage_product_plan(const mls_config* cfg, int32_t product, int64_t* big_
   layout(&tmp);
   NtProduct p[NT_PRODUCTS];
   nt_products(&tmp, p);
-  const mls::GemmPlan g = mls::gemm_bf16_plan(p[product].form, tmp.T, p[product].N, p[product].K, true);
+  const NtProduct& q = p[product];
+  const mls::GemmPlan g = tiled(&tmp, q) ? mls::gemm_bf16_plan(q.form, tmp.T, q.N, q.K, true) : mls::GemmPlan{0, 0, 0, 1, 1};
   *big_cols = g.big_cols;
   *big_parts = g.big_parts;
   *tile_rows = g.tile_rows;

@@ -54,6 +54,12 @@ def test_plan_refusals():
         mls.product_plan(cfg, 0)
 
 
+def test_operands_of_two_gib_run_on_no_tile_of_these():
+    """dgu, the operand of the fifth product, on either side of the 31 bits that the tiles' offsets have."""
+    assert mls.product_plan(_cfg(64, 1, 1, 64, 65536, 7700), 5) == (0, 1, 0, 0, 1)
+    assert mls.product_plan(_cfg(64, 1, 1, 64, 65536, 7600), 5) == (0, 1, 128, 64, 8)
+
+
 def test_a_stage_without_such_products_has_no_workspace_for_them():
     big, small = (mls.Stage.memory(synth.StageShape(h, 2, 1, 64, f, 65, 1, 1, 1))["workspace_bytes"] for h, f in ((72, 16392), (72, 64)))
     assert big > small + 4 * 8 * 64 * 64 * 4 and small < 1 << 18
