@@ -25,6 +25,16 @@ LARGE = [
     ((12288, 2, 1, 64, 2048, 700), 2, (0, 1, 256, 128, 2)), ((12288, 2, 1, 64, 4096, 513), 2, (8192, 2, 0, 0, 1)),
     ((4104, 2, 1, 64, 16384, 700), 3, (0, 1, 256, 128, 2)), ((8200, 2, 1, 64, 16384, 513), 3, (8200, 2, 0, 0, 1))]
 
+# leading columns on whole 256x256 tiles, the columns behind them shared out
+BEHIND = [
+    ((4456, 32, 32, 64, 80, 2710), 0, (5888, 1, 64, 128, 2)), ((7744, 16, 16, 128, 168, 2804), 0, (5888, 1, 128, 128, 5)),
+    ((12976, 16, 16, 64, 88, 6310), 0, (2560, 1, 256, 128, 2)), ((7424, 32, 8, 128, 88, 2076), 1, (7168, 1, 128, 64, 3)),
+    ((2776, 16, 4, 64, 16456, 318), 2, (32768, 1, 64, 128, 4)), ((4536, 4, 2, 64, 18416, 393), 2, (32768, 1, 128, 128, 2)),
+    ((12024, 8, 2, 64, 20000, 430), 2, (32768, 1, 256, 128, 2)), ((13136, 8, 2, 64, 1776, 1070), 3, (13056, 1, 64, 64, 3)),
+    ((3144, 2, 1, 64, 4376, 5080), 3, (3072, 1, 128, 64, 3)), ((7160, 2, 1, 128, 4768, 2345), 3, (6400, 1, 128, 128, 2)),
+    ((4624, 4, 4, 64, 1104, 3389), 5, (4608, 1, 64, 64, 3)), ((3456, 4, 1, 128, 2168, 5214), 5, (3072, 1, 128, 128, 2)),
+    ((5768, 4, 1, 128, 5888, 3238), 5, (4864, 1, 256, 128, 2))]
+
 
 @pytest.fixture(autouse=True)
 def _torch_first():
@@ -52,6 +62,11 @@ def test_plan_refusals():
     cfg.dtype = 1
     with pytest.raises(mls.MlsError):
         mls.product_plan(cfg, 0)
+
+
+def test_plans_of_the_remainders():
+    for shape, product, plan in BEHIND:
+        assert mls.product_plan(_cfg(*shape), product) == plan, (shape, product)
 
 
 def test_operands_of_two_gib_run_on_no_tile_of_these():
@@ -121,6 +136,66 @@ def test_large_tiles_on_captured_operands(shape, product):
         y2 = torch.empty_like(y)
         st.forward(x, 1, y2)
         assert torch.equal(y, y2)
+    st.close()
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("shape,product,plan", BEHIND)
+def test_remainders_on_captured_operands(shape, product, plan):
+    """The product in 64 bits from the operands the stage kept: all of it and the columns of the shared-out tiles alone.  A result
+    is rounded to bf16 once (relative error below 2^-8); dh takes the rounded product and is rounded itself (2^-7)."""
+    import torch
+    h, nq, nkv, d, f, T = shape
+    st = mls.Stage(h, nq, nkv, d, f, T, 1, 1, 1, seed=7)
+    gen = torch.Generator("cuda").manual_seed(3)
+    x, dy = (torch.randn(1, T, h, device="cuda", generator=gen).bfloat16() for _ in range(2))
+    y, dx = torch.empty_like(x), torch.empty_like(x)
+    grads = torch.empty(st.grad_elems, device="cuda") if product == 5 else None
+
+    def once():
+        st.reset()
+        st.forward(x, 1, y)
+        if product == 5:
+            hid = st.debug_read("h").double()
+            st.backward(dy, grads, 1, dx, overwrite=True)
+            return [st.debug_read("dh"), hid]
+        return [st.debug_read("qkv") if product == 0 else st.debug_read("h") if product == 1 else st.debug_read("gu") if product == 2 else y.view(T, h).clone()]
+    got, *more = once()
+    params = st.get_params()
+
+    def weight(name):
+        off, r, c = st.param_layout(0, name)
+        return params[off:off + r * c].view(r, c).double()
+
+    def check(a, ref, cols, tol=2.0 ** -8):
+        for sel in (slice(None), cols):
+            e = ((a.double()[:, sel] - ref[:, sel]).norm() / ref[:, sel].norm()).item()
+            assert e < tol, (sel, e)
+    behind = slice(plan[0], None)
+    if product == 0:
+        qkv = st.debug_read("a").double() @ weight("w_qkv")
+        ang = torch.arange(T, dtype=torch.float64, device="cuda")[:, None] * 10000.0 ** (-2.0 * torch.arange(d // 2, dtype=torch.float64, device="cuda") / d)
+        cs, sn = ang.cos()[:, None], ang.sin()[:, None]
+        rot = (nq + nkv) * d
+        a, b = qkv[:, :rot].reshape(T, nq + nkv, d).chunk(2, dim=-1)
+        check(got, torch.cat([torch.cat([a * cs - b * sn, a * sn + b * cs], -1).reshape(T, rot), qkv[:, rot:]], 1), behind)
+    elif product == 1:
+        check(got, x.view(T, h).double() + st.debug_read("o").double() @ weight("w_o"), behind)
+    elif product == 2:
+        gu = st.debug_read("b").double() @ weight("w_gu")
+        at = plan[0] // 2  # 32 gate and 32 up columns in turn
+        for half in (gu[:, :f], got[:, :f]), (gu[:, f:], got[:, f:]):
+            check(half[1], half[0], slice(at, None))
+        check(st.debug_read("z"), gu[:, :f] * torch.sigmoid(gu[:, :f]) * gu[:, f:], slice(at, None))
+    elif product == 3:
+        check(got, st.debug_read("h").double() + st.debug_read("z").double() @ weight("w_d"), behind)
+    else:
+        hid = more[0]
+        dn = st.debug_read("dgu").double() @ weight("w_gu").t() * weight("gamma2").view(-1)
+        r = (hid.square().mean(-1, keepdim=True) + 1e-5).rsqrt()
+        check(got, dy.view(T, h).double() + r * (dn - hid * r * (dn * hid * r).mean(-1, keepdim=True)), behind, 2.0 ** -7)
+    for _ in range(2):
+        assert torch.equal(once()[0], got)
     st.close()
 
 
