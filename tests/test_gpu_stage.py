@@ -111,6 +111,55 @@ def test_fused_swiglu_where_the_last_group_of_32_columns_is_not_full(ffn):
     _check(sh, [2, 1, 2], 1e-2)
 
 
+def test_swiglu_as_a_kernel_of_its_own():
+    """gate/up operands of 2 GiB (here dgu, with the slack the tiles ask for) leave the fused form: public column order, a SwiGLU
+    kernel each way, the w_gu gradient and the data gradient on the register-staged kernel.  References in 64 bits from the
+    captured operands; a result is rounded to bf16 once (below 2^-8), dgu comes from a rounded dz (2^-7), gradients are fp32 sums."""
+    import torch
+    import paper_2410_13333_amd as mls
+    h, f, T = 64, 65536, 7700
+    st = mls.Stage(h, 1, 1, 64, f, T, 1, 1, 1, seed=1000)
+    assert mls.product_plan(st.cfg, 5) == (0, 1, 0, 0, 1)
+    p = st.get_params()
+    st.set_params(p.flip(0).contiguous())
+    assert torch.equal(st.get_params(), p.flip(0))
+    st.set_params(p)
+    assert torch.equal(st.get_params(), p)
+    gen = torch.Generator("cuda").manual_seed(3)
+    x, dy = (torch.randn(1, T, h, device="cuda", generator=gen).bfloat16() for _ in range(2))
+    y, dx = torch.empty_like(x), torch.empty_like(x)
+
+    def weight(name):
+        off, r, c = st.param_layout(0, name)
+        return p[off:off + r * c].view(r, c).double()
+
+    def err(got, ref):
+        return ((got.double() - ref).norm() / ref.norm()).item()
+    off, r, c = st.param_layout(0, "w_gu")
+    for add in (False, True):
+        st.forward(x, 1, y)
+        b, gu, z, hid = (st.debug_read(n) for n in ("b", "gu", "z", "h"))
+        g = torch.full((st.grad_elems,), 0.5 if add else float("nan"), device="cuda")
+        st.backward(dy, g, 1, dx, overwrite=not add)
+        dgu = st.debug_read("dgu")
+        dw = torch.cat([b.double().t() @ dgu[:, i:i + f].double() for i in (0, f)], 1)
+        assert err(g[off:off + r * c].view(r, c), dw + (0.5 if add else 0.0)) < 1e-5
+    for i in (0, f):
+        assert err(gu[:, i:i + f], b.double() @ weight("w_gu")[:, i:i + f]) < 2.0 ** -8
+    gate, up = gu[:, :f].double(), gu[:, f:].double()
+    s = torch.sigmoid(gate)
+    assert err(z, gate * s * up) < 2.0 ** -8
+    assert err(y.view(T, h), hid.double() + z.double() @ weight("w_d")) < 2.0 ** -8
+    dz = dy.view(T, h).double() @ weight("w_d").t()
+    assert err(dgu[:, :f], dz * up * s * (1 + gate * (1 - s))) < 2.0 ** -7
+    assert err(dgu[:, f:], dz * gate * s) < 2.0 ** -7
+    dn = sum(dgu[:, i:i + f].double() @ weight("w_gu")[:, i:i + f].t() for i in (0, f)) * weight("gamma2").view(-1)
+    inv = (hid.double().square().mean(-1, keepdim=True) + 1e-5).rsqrt()
+    n = hid.double() * inv
+    assert err(st.debug_read("dh"), dy.view(T, h).double() + inv * (dn - n * (dn * n).mean(-1, keepdim=True))) < 2.0 ** -7
+    st.close()
+
+
 @pytest.mark.parametrize("hidden,tokens", [(72, 2047), (72, 2048), (512, 2051), (520, 2048), (1024, 2101), (1032, 2048)])
 def test_norms_of_many_narrow_rows(hidden, tokens):
     """2048 rows of up to 1024 elements and more run by wavefronts: rows and columns that do not fill them, and the shapes next to
@@ -330,7 +379,7 @@ def test_token_counts_that_are_not_multiples_of_eight(seq, mb):
     """Tokens per micro-batch T = seq * micro_batch need not be a multiple of anything: T is the row count of
     every activation and the contraction length of the weight gradients (zero-filled beyond the last row).
     seq = 1: attention over a single position is the identity on v."""
-    for ffn in (40, 64):  # separate and fused SwiGLU
+    for ffn in (40, 64):  # a last group of 32 gate/up columns that is not full, and whole groups
         sh = synth.StageShape(hidden=72, n_q_heads=2, n_kv_heads=1, head_dim=64, ffn=ffn, seq=seq, micro_batch=mb,
                               layers=2, microbatches=2)
         _check(sh, [2, 1], 1e-2)
@@ -374,7 +423,7 @@ def test_rotary_epilogue_of_the_qkv_projection(nq, nkv, d, seq, mb):
     assert rel_err(got[-64:, qd + kvd - d:qd + kvd], ref[-64:, qd + kvd - d:qd + kvd]) <= 2e-3
 
 
-@pytest.mark.parametrize("ffn", [328, 352])  # separate and interleaved gate/up columns
+@pytest.mark.parametrize("ffn", [328, 352])  # gate/up columns with a last group that is not full, and whole groups
 @pytest.mark.parametrize("shift", [0, 1])    # a source at a 16-byte boundary (one pass) and off it (copies)
 def test_set_params_from_any_address(ffn, shift):
     """Rows and columns that are no multiple of a 128 x 128 tile; both routes leave the same parameters and the same
