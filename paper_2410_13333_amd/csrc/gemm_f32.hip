@@ -233,10 +233,7 @@ __global__ __launch_bounds__(256, 2) void gemm_f32_kernel(const float* __restric
 template <bool AK, bool BK>
 hipError_t launch_f32(const float* A, const float* B, float* C, const float* R, int M, int N, int K, int64_t lda, int64_t ldb,
                       int64_t ldc, int64_t ldr, int add, hipStream_t st) {
-  // The 64x64 tiles read half as much per product; the 32x32 ones are four times as many.  us, 32x32 / 64x64: 1000 x 4096 x 1024
-  // (1024 big tiles) 110 / 89, 1024 x 2752 x 768 (688) 64 / 55, 512 x 2752 x 512 (344) 27.4 / 26.7, 1152 x 768 x 4096 (216) 98 / 104,
-  // 512 x 512 x 2752 (64) 24 / 70.
-  const bool large = int64_t((M + 63) / 64) * ((N + 63) / 64) >= 320;
+  const bool large = mls::gemm_f32_large(M, N, K);
   constexpr int LDS = 4 * 2 * 2 * 32 * KC * 4;  // of both
   auto kern = large ? gemm_f32_kernel<AK, BK> : gemm_f32_shared_kernel<AK, BK>;
   static std::atomic<uint64_t> lds_raised[2] = {{0}, {0}};
@@ -249,6 +246,18 @@ hipError_t launch_f32(const float* A, const float* B, float* C, const float* R, 
 }  // namespace
 
 namespace mls {
+
+// The 64x64 tiles read half as much per product; the 32x32 ones are four times as many, two of them on a CU at a time, and their
+// wavefronts take every fourth piece.  So the large ones where they are many, and, of a short contraction, where the small ones
+// would queue for the CUs or leave wavefronts without a piece.  us, 32x32 / 64x64: 1000 x 4096 x 1024 (1024 big tiles) 110 / 89,
+// 1024 x 2752 x 768 (688) 64 / 55, 512 x 2752 x 512 (344) 27.4 / 26.7, 1152 x 768 x 4096 (216) 98 / 104, 512 x 512 x 2752 (64) 24 / 70;
+// by rows 768 x 768 (144 big tiles, 576 small) over 64 7.4 / 5.0, over 256 9.5 / 9.2, over 384 11.9 / 12.1, over 400 14.2 / 13.0, over
+// 512 13.8 / 15.1; 1024 x 1024 (256, 1024) over 64 8.4 / 5.3; 512 x 1024 (128, 512) over 64 5.0 / 4.9, over 256 6.6 / 9.1.
+bool gemm_f32_large(int M, int N, int K) {
+  const int64_t big = int64_t((M + 63) / 64) * ((N + 63) / 64), small = int64_t((M + 31) / 32) * ((N + 31) / 32);
+  const int pieces = (K + KC - 1) / KC;
+  return big >= 320 || (small > 512 && (pieces <= 8 || (pieces < 16 && pieces % 4)));
+}
 
 // M, N and row strides multiples of 8, operands 16-byte aligned (as every entry point checks); K a multiple of 8 in the
 // NN and NT forms, any length in the TN form (a weight gradient contracts over the tokens).  overwrite (TN): C = instead of +=

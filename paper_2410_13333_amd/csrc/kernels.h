@@ -145,6 +145,7 @@ bool gemm_rope_ok(int M, int N, int K, int64_t lda, int64_t ldw, int seq, int ro
 hipError_t gemm_bf16_rope(const void* A, const void* W, void* C, int M, int N, int K, int64_t lda, int64_t ldw, int64_t ldc,
                           const float* cos_tab, const float* sin_tab, int seq, int rot_cols, int head_dim, hipStream_t st,
                           const SplitSpace& split = {});
+bool gemm_f32_large(int M, int N, int K);  // whether such a product runs on 64x64 tiles, not on 32x32 ones.  Host only.
 // overwrite (GEMM_TN): C = instead of +=
 hipError_t gemm_f32(int mode, const void* A, const void* B, void* C, const void* R, int M, int N, int K, int64_t lda,
                     int64_t ldb, int64_t ldc, int64_t ldr, hipStream_t st, bool overwrite = false);

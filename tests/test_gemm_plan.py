@@ -1,4 +1,6 @@
 """Which tiles the bf16 contractions run on, as the library itself plans it (host code, no GPU)."""
+import ctypes
+
 import pytest
 
 import paper_2410_13333_amd as mls
@@ -93,3 +95,14 @@ def test_short_contractions_into_fp32_results_take_small_tiles():
 def test_a_cu_with_a_workgroup_more_than_the_others_counts(M, N, K, us):
     for mode in (0, 1):
         assert mls.gemm_plan(mode, M, N, K) == (0, 128, 128), us
+
+
+# fp32: 64x64 tiles from 320 on; of a short contraction also where more 32x32 tiles than two per CU would queue (us, 32x32 / 64x64)
+@pytest.mark.parametrize("M,N,K,large", [
+    (768, 768, 64, True), (2120, 232, 24, True), (1536, 768, 128, True), (768, 768, 256, True), (768, 768, 400, True),  # 7.4 / 5.0, 9.9 / 5.6, 11.2 / 9.0, 9.5 / 9.2, 14.2 / 13.0
+    (768, 768, 384, False), (768, 768, 512, False), (1152, 768, 4096, False),                                        # 11.9 / 12.1, 13.8 / 15.1, 98 / 104
+    (512, 1024, 256, False), (256, 256, 256, False), (512, 2752, 512, True)])                                        # 6.6 / 9.1, 5.3 / 9.3, 27.4 / 26.7
+def test_fp32_tiles(M, N, K, large):
+    f = mls.lib()._ZN3mls14gemm_f32_largeEiii
+    f.restype = ctypes.c_bool
+    assert f(M, N, K) is large
