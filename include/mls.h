@@ -149,7 +149,9 @@ typedef struct {
                                                bf16: plus the transposed copy of the four matrices of a layer
                                                that the forward products read                               */
   size_t stash_bytes;                       /* max_inflight * max_layers entries                           */
-  size_t workspace_bytes;                   /* backward workspace, recomputation scratch, rotary tables    */
+  size_t workspace_bytes;                   /* backward workspace, recomputation scratch, rotary tables;
+                                               bf16, where the shapes call for it: up to 256 MiB of dS between
+                                               two attention kernels, up to 32 MiB of partial sums of products */
   size_t param_bytes_per_layer;
   size_t grad_bytes_per_layer;              /* fp32, the caller's buffer (not part of total_bytes)         */
   size_t stash_bytes_per_layer_microbatch;
@@ -186,8 +188,9 @@ int mls_stage_debug_read(mls_stage* s, int32_t tensor_id, int32_t layer, int32_t
  * stops it.  mls_stage_timing_read synchronises on the last event, writes the accumulated milliseconds and launch counts
  * per class into two HOST arrays of MLS_TIMING_CLASSES entries (order: GEMM forward, GEMM data-gradient, GEMM
  * weight-gradient, attention forward, attention backward, RMSNorm, rotary, SwiGLU) and clears the accumulators.  A step
- * that runs fused into a neighbouring kernel (bf16 storage: the rotary steps, SwiGLU forward) is
- * counted with that kernel's class and leaves its own class at zero.
+ * that runs fused into a neighbouring kernel is counted with that kernel's class and leaves its own class at zero: with bf16
+ * storage the rotary steps and SwiGLU forward (both unless an operand has 2 GiB or more) and, where the weight gradients of a
+ * layer share a launch, the sums of its gain gradients (else RMSNorm's class).
  * Errors: MLS_E_NULL, MLS_E_HIP. */
 #define MLS_TIMING_CLASSES 8
 int mls_stage_timing(mls_stage* s, int32_t enable);

@@ -33,9 +33,11 @@ struct Plan {
 // is 19 % (448 x 4392 over 25472, whole: 189 us instead of 159).
 // Results in fp32 (TN): twice the bytes where they are stored, four times where they are added to, which a tile that has its CU
 // for itself moves while the matrix cores idle: fitted apart, to the weight gradients of 130 layers inside a stage (48 to 5400
-// tokens, hidden 192 to 8192), every tile size, in one launch and apart; 3 to 15 % (rms, from 256x256 to 64x64).  Choosing by it
-// between a shared launch and launches apart costs 1.3 % on average where results are added to and 1.7 % where they are stored
-// (worst: 18 and 16 %); with the figures of bf16 results it cost 6.6 and 3.0 % (73 and 61 %: hidden 1192, 186 tokens).
+// tokens, hidden 192 to 8192), every tile size, in one launch and apart, when results still left the kernels as pieces of rows.
+// Leaving as whole rows they cost less (f32_results in common.h; a round of added 256x256 results about 29 us instead of the 47.9
+// below), and the choice is on average this far above the fastest measured now: 0.9 % for a product by itself (313 shapes, stored and
+// added); between a shared launch and launches apart 3.7 % where results are added to and 2.3 % where they are stored (80 layers of
+// these ranges; the worst 20 %, hidden 4744 over 541 tokens 747 us instead of 621, and 25 %, hidden 3624 over 167 tokens 125 instead of 100).
 // The fused epilogues have one 64x128 kernel where the plan says 128x64 or 64x64.
 enum { TILE_M16 = -1 };
 enum Result { R_BF16, R_F32_STORE, R_F32_ADD };

@@ -123,7 +123,7 @@ struct T16Problem {
   const float *cos_tab, *sin_tab;
   int seq, rot_cols, head_dim;
   SplitSpace split;
-  int parts;    // > 1: workgroups per tile, each over a share of K (all forms but TN_SEGS); the space has to hold them
+  int parts;    // > 1: workgroups per tile, each over a share of K (the three NT forms); the space has to hold them
 };
 hipError_t gemm_t16(const T16Problem& p, int tile, hipStream_t st);
 // up to four T16_TN_SEGS problems over pieces of the same number and depth in one launch

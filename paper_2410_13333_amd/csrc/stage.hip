@@ -118,9 +118,9 @@ struct mls_stage {
   char *g0 = nullptr, *g1 = nullptr, *dz = nullptr, *dgu = nullptr, *dbuf = nullptr, *dh = nullptr, *dc = nullptr,
        *dqkv = nullptr;
   size_t mb_h = 0, mb_gu = 0, mb_qkv = 0;  // bytes per micro-batch of the [T,ld_h], [T,ld_gu], [T,ld_qkv] buffers
-  // partial, partial2: row-block sums of the two gain gradients of a layer, summed over a call's micro-batches
   void* split_mem = nullptr;
   mls::SplitSpace split;  // (split_mem) of the products whose contraction is shared out over several workgroups per tile
+  // partial, partial2: row-block sums of the two gain gradients of a layer, summed over a call's micro-batches
   float *delta = nullptr, *partial = nullptr, *partial2 = nullptr, *gqa_part = nullptr;  // gqa_part: partial dK/dV sums (few KV heads)
   std::vector<int> last_k;  // layer counts of the entries of the most recent backward call (for mls_stage_debug_read)
   Timing tm;
@@ -420,7 +420,7 @@ void layout(mls_stage* s) {
   s->ioff_wgu = s->ioff_g2 + h;
   s->ioff_wd = s->ioff_wgu + h * s->ld_gu;
   s->ilayer_params = s->ioff_wd + f * s->ld_h;
-  // transposed copies: w_qkv^T [qkvw, ld_h], w_o^T [h, ld_qd], w_gu^T [2f, ld_h], w_d^T [h, ld_f]
+  // transposed copies: w_qkv^T [qkvw, ld_h], w_o^T [h, ld_qd], w_gu^T [2 fgu, ld_h], w_d^T [h, ld_f]
   s->toff_wqkv = 0;
   s->toff_wo = s->toff_wqkv + size_t(s->qkvw) * s->ld_h;
   s->toff_wgu = s->toff_wo + h * s->ld_qd;
