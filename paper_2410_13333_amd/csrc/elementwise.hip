@@ -477,16 +477,19 @@ __global__ __launch_bounds__(EW_THREADS) void gu_permute_kernel(const bf16_t* __
 // ---------------------------------------------------------------- parameters into their places (bf16)
 // One launch places up to MAX_SPREAD matrices: dst (row stride ld_dst; columns in the interleaved gate/up order if gu_f > 0)
 // and the transposed copy dst_t, from one read of src.  HBM-bound.  128 x 128 tiles, so that every row piece of all three
-// matrices is 256 bytes; a tile goes through LDS with the 16-byte chunks of a row XORed by its group of eight rows (the
+// matrices is 256 bytes (gate/up: two of 128 in src; a tile is one of the interleaved order, since pieces of lines are dearer to
+// write than to read); a tile goes through LDS with the 16-byte chunks of a row XORed by its group of eight rows (the
 // transposing reads take one column of 16 groups: 16 different chunks, no bank conflicts).  Rows and columns are
 // multiples of 8 wherever dst_t is written.
 // Measured (the matrices of a 4096 x 11008 layer, 405 MB in, 810 MB out): 425 us as copies, a column permutation and
-// 64 x 64 transposes with 2-byte accesses; 256 us as one pass (4.75 TB/s).
+// 64 x 64 transposes with 2-byte accesses; 264 us as one pass in tiles of src, 238 in tiles of the interleaved order (5.1 TB/s).  With
+// an ffn of 10008, no multiple of 32, 268 and 233, as much as without the interleaving (230).
 struct SpreadList {
   mls::Spread m[mls::MAX_SPREAD];
   int first[mls::MAX_SPREAD];  // first tile of each matrix
   int n;
 };
+__host__ __device__ __forceinline__ int spread_cols(const mls::Spread& m) { return m.gu_f > 0 ? 2 * gu_width(m.gu_f) : m.cols; }
 __global__ __launch_bounds__(256) void spread_bf16_kernel(SpreadList L) {
   __shared__ uint4 tile[128 * 16];
   int w = 0;
@@ -494,16 +497,18 @@ __global__ __launch_bounds__(256) void spread_bf16_kernel(SpreadList L) {
   const mls::Spread& m = L.m[w];
   const bf16_t* src = (const bf16_t*)m.src;
   bf16_t *dst = (bf16_t*)m.dst, *dst_t = (bf16_t*)m.dst_t;
-  const int at = int(blockIdx.x) - L.first[w], tx = (m.cols + 127) / 128;
+  const int at = int(blockIdx.x) - L.first[w], tx = (spread_cols(m) + 127) / 128;
   const int r0 = at / tx * 128, c0 = at % tx * 128;
   const int ch = threadIdx.x & 15, tr = threadIdx.x >> 4;
-  const int col = c0 + ch * 8, icol = m.gu_f > 0 ? gu_interleaved_col(col, m.gu_f) : col;
+  auto exists = [&](int c) { return c < spread_cols(m) && (m.gu_f <= 0 || gu_column_exists(c, m.gu_f)); };
+  const int col = c0 + ch * 8, from = m.gu_f > 0 ? gu_public_col(col, m.gu_f) : col;
+  const bool some = exists(col);
 #pragma unroll
   for (int i = 0; i < 8; i++) {
     const int r = i * 16 + tr;
-    if (r0 + r < m.rows && col < m.cols) {
-      const uint4 v = *reinterpret_cast<const uint4*>(src + int64_t(r0 + r) * m.ld_src + col);
-      if (dst) *reinterpret_cast<uint4*>(dst + int64_t(r0 + r) * m.ld_dst + icol) = v;
+    if (r0 + r < m.rows && some) {
+      const uint4 v = *reinterpret_cast<const uint4*>(src + int64_t(r0 + r) * m.ld_src + from);
+      if (dst) *reinterpret_cast<uint4*>(dst + int64_t(r0 + r) * m.ld_dst + col) = v;
       tile[r * 16 + (ch ^ (r >> 3))] = v;
     }
   }
@@ -514,12 +519,12 @@ __global__ __launch_bounds__(256) void spread_bf16_kernel(SpreadList L) {
 #pragma unroll
   for (int i = 0; i < 8; i++) {
     const int c = i * 16 + (threadIdx.x >> 4), gc = c0 + c;
-    if (gc < m.cols && r0 + rg * 8 < m.rows) {
+    if (exists(gc) && r0 + rg * 8 < m.rows) {
       uint32_t e[8];
 #pragma unroll
       for (int q = 0; q < 8; q++) e[q] = t16[((rg * 8 + q) * 16 + ((c >> 3) ^ rg)) * 8 + (c & 7)];
       const uint4 v = make_uint4(e[0] | e[1] << 16, e[2] | e[3] << 16, e[4] | e[5] << 16, e[6] | e[7] << 16);
-      *reinterpret_cast<uint4*>(dst_t + int64_t(m.gu_f > 0 ? gu_interleaved_col(gc, m.gu_f) : gc) * m.ld_t + r0 + rg * 8) = v;
+      *reinterpret_cast<uint4*>(dst_t + int64_t(gc) * m.ld_t + r0 + rg * 8) = v;
     }
   }
 }
@@ -671,7 +676,7 @@ hipError_t spread_bf16(const Spread* list, int n, hipStream_t st) {
     if (list[i].rows <= 0 || list[i].cols <= 0) continue;
     L.m[L.n] = list[i];
     L.first[L.n++] = int(tiles);
-    tiles += int64_t((list[i].rows + 127) / 128) * ((list[i].cols + 127) / 128);
+    tiles += int64_t((list[i].rows + 127) / 128) * ((spread_cols(list[i]) + 127) / 128);
   }
   if (tiles == 0) return hipSuccess;
   if (tiles > INT32_MAX) return hipErrorInvalidValue;
