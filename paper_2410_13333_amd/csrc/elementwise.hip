@@ -461,7 +461,7 @@ __global__ __launch_bounds__(EW_THREADS) void fill_normal_kernel(T* __restrict__
 }
 
 // dst <- src with the columns of a [rows, 2f] matrix moved between the public and the interleaved gate/up order
-// (8 columns per thread; blocks of 32 columns move as a whole)
+// (8 columns per thread; blocks of 32 columns move as a whole).  The caller's side may begin at any element.
 __global__ __launch_bounds__(EW_THREADS) void gu_permute_kernel(const bf16_t* __restrict__ src, int64_t ld_src,
                                                                 bf16_t* __restrict__ dst, int64_t ld_dst,
                                                                 int64_t total, int f, bool to_interleaved) {
@@ -470,8 +470,9 @@ __global__ __launch_bounds__(EW_THREADS) void gu_permute_kernel(const bf16_t* __
   const int cpr = f >> 2;  // 16-byte chunks per row of 2f columns
   const int64_t t = id / cpr;
   const int c = int(id % cpr) * 8, ci = gu_interleaved_col(c, f);
-  const uint4 v = *reinterpret_cast<const uint4*>(src + t * ld_src + (to_interleaved ? c : ci));
-  *reinterpret_cast<uint4*>(dst + t * ld_dst + (to_interleaved ? ci : c)) = v;
+  uint4 v;
+  __builtin_memcpy(&v, src + t * ld_src + (to_interleaved ? c : ci), 16);
+  __builtin_memcpy(dst + t * ld_dst + (to_interleaved ? ci : c), &v, 16);
 }
 
 // ---------------------------------------------------------------- parameters into their places (bf16)

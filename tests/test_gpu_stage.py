@@ -4,6 +4,8 @@ Tolerances (relative Frobenius error per tensor, fp64 metric):
   fp32 storage: 1e-4 for every output and gradient (validates the algorithm with no bf16 in the way);
   bf16 storage: 1e-2 for y, dX and the parameter gradients against the oracle fed the same bf16 inputs;
   weight-gradient contraction + fp32 accumulation given identical bf16 operands: 1e-4."""
+import ctypes
+
 import numpy as np
 import pytest
 
@@ -371,6 +373,24 @@ def test_overwrite_mode_equals_zeroing_then_accumulating(base):
     st.backward(dy, grads, 0, dx, overwrite=True)                       # nothing to pop: everything zero
     torch.cuda.synchronize()
     assert not to_host64(grads).any()
+    st.close()
+
+
+@pytest.mark.parametrize("ffn", [328, 352])
+def test_parameters_and_operands_reach_any_address(ffn):
+    """The buffers of get_params and debug_read may begin at any element: nothing around them changes."""
+    import torch
+    import paper_2410_13333_amd as mls
+    st = mls.Stage.from_shape(RAGGED.with_(ffn=ffn, layers=1), seed=1000)
+    x = to_device(synth.make_x(RAGGED, 2000, 0)[0], "bf16")
+    st.forward(x, 1, torch.empty_like(x))
+    for ref, read in ((st.get_params(), lambda p: mls.lib().mls_stage_get_params(st._h, p)),
+                      (st.debug_read("gu"), lambda p: mls.lib().mls_stage_debug_read(st._h, mls.T_IDS["gu"], 0, 0, p))):
+        for shift in (1, 3):
+            buf = torch.full((ref.numel() + 16,), 7.0, dtype=ref.dtype, device="cuda")
+            assert read(ctypes.c_void_p(buf[shift:].data_ptr())) == 0
+            assert torch.equal(buf[shift:shift + ref.numel()], ref.reshape(-1))
+            assert bool((buf[:shift] == 7).all()) and bool((buf[shift + ref.numel():] == 7).all())
     st.close()
 
 
