@@ -441,6 +441,211 @@ __global__ __launch_bounds__(AT_THREADS, 2) void attn_fwd_kernel(const bf16_t* _
   if (lane < 32 && qi < S) lse[(int64_t(bi) * nq + hq) * S + qi] = (m + __builtin_amdgcn_logf(l)) * LN2;
 }
 
+// ---------------------------------------------------------------- forward, few workgroups
+// grid (n_q b, q blocks of 64), longest first.  Wave w owns query rows q0 + 32 (w / 2) .. +31 and, of every block of 64 keys, the
+// sub-block w % 2: half the chain of the kernel above for twice the workgroups.  The two partial softmaxes of a row meet in LDS at the end.
+//
+// What bounds it is a wavefront's issue: about 100 vector instructions, 16 of them exponentials, and 16 products per sub-block, 0.65 us,
+// whether it is alone on its SIMD or not.  The pipeline is therefore one of sub-blocks, two iterations per turn of the loop so that every
+// buffer and every fragment address is a constant, in exactly the order written: products with V of the block before the last on both
+// sides of the barrier, whose fragments were read before it, so that neither the barrier nor the first reads behind it are waited for.
+// Measured (us, the kernel above -> this): 2048 positions, 16 heads of 128: 43 -> 34; 1024, 16: 23.4 -> 16.6; 512, 16: 13.6 -> 10.5;
+// 4096, 8: 79 -> 58; 3000, 4: 57 -> 36; 2 x 1000, 16 of 64: 17.2 -> 13.0; 512, 16 of 64: 9.8 -> 7.6.
+template <int D>
+__global__ __launch_bounds__(AT_THREADS, 2) void attn_fwd_pair_kernel(const bf16_t* __restrict__ qkv, int64_t ld, bf16_t* __restrict__ o, int64_t ldo,
+                                                                      float* __restrict__ lse, int S, int nq, int nkv) {
+  using TL = Tile<D>;
+  constexpr int KD = D / 16, DT = D / 32, B = TL::BYTES, KA = 4;  // KA: fragments of K read ahead
+  __shared__ __attribute__((aligned(4 * TR * D))) bf16_t lds[4][TR * D];  // two buffers of K, two of V
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), kh = wave & 1;
+  const int qb = gridDim.y - 1 - blockIdx.y;  // longest rows first
+  const int hq = blockIdx.x % nq, bi = blockIdx.x / nq, hk = hq / (nq / nkv);
+  const bf16_t* base = qkv + int64_t(bi) * S * ld;
+  const int q0 = qb * 64, qw = q0 + (wave >> 1) * 32, qi = qw + (lane & 31);
+  const float sc = rsqrtf((float)D) * LOG2E;
+  const uint32_t lds0 = (uint32_t)(uintptr_t)(MLS_LDS bf16_t*)&lds[0][0];
+  TL tl;
+  tl.init(ld, wave, lane);
+  Frags<D> fr;
+  fr.init(lds0 + kh * (32 * D * 2), lane);  // (the swizzle repeats after 16 rows)
+  const int nblk = (min(S, q0 + 64) + TR - 1) / TR;
+  const uint32_t blk_bytes = uint32_t(TR * ld * 2), rec = uint32_t(int64_t(min(S, nblk * TR)) * ld * 2);
+  i32x4 rk = make_rsrc(base + (nq + hk) * D, rec), rv = make_rsrc(base + (nq + nkv + hk) * D, rec);
+  const uint32_t dst = lds0 + wave * TL::NI * 1024;
+  // the next block of K (V) into buffer `buf`
+  auto issue = [&](i32x4& r, int buf) {
+#pragma unroll
+    for (int i = 0; i < TL::NI; i++) dma16(r, tl.off[i], dst + buf * B + i * 1024);
+    const uint64_t a = ((uint64_t)(uint32_t)r[1] << 32 | (uint32_t)r[0]) + blk_bytes;
+    r[0] = (int)(uint32_t)a;
+    r[1] = (int)(uint32_t)(a >> 32);
+    r[2] = max(r[2] - (int)blk_bytes, 0);
+  };
+
+  bf16x8 qf[KD];
+#pragma unroll
+  for (int kk = 0; kk < KD; kk++) qf[kk] = gfrag(base, ld, qi, hq * D + kk * 16 + (lane >> 5) * 8, qi < S);
+  f32x16 acc[DT];
+#pragma unroll
+  for (int t = 0; t < DT; t++) acc[t] = zero16();
+  float m = -3e38f, l = 0.f;  // (finite: a wavefront may have no key at all)
+  f32x16 st[2];               // scores of a block, by its parity
+  bf16x8 pf[2][2];            // and its probabilities
+  bf16x8 vf[KD], kf[KD];      // fragments of V of block u - 2 and of K of block u
+#pragma unroll
+  for (int n = 0; n < KD; n++) vf[n] = bf16x8{};
+  pf[0][0] = pf[0][1] = pf[1][0] = pf[1][1] = bf16x8{};
+
+  // An iteration: O += V^T P of the block before the last, the exponentials of the last one, S of the next one, whose parity is P; in
+  // exactly the order written.  MASK: the last block is the one on the diagonal.
+  auto iter = [&](auto PC, auto DO_S, auto DO_SM, auto MASK, auto DO_PV) {
+    constexpr int P = decltype(PC)::value, Q = 1 - P;
+    constexpr bool do_s = decltype(DO_S)::value, do_sm = decltype(DO_SM)::value, do_pv = decltype(DO_PV)::value;
+    float mx = -INFINITY, mn = m, ps = 0.f;
+    constexpr int H = KD / 2;  // products before the barrier, and slots of the maximum
+    // softmax work of slot n (of 2 KD)
+    auto between = [&](auto NC) {
+      constexpr int n = decltype(NC)::value;
+      if constexpr (do_sm) {
+        if constexpr (n < H) {
+          if constexpr (n == 0 && decltype(MASK)::value) {
+            const int lim = qi - q0 - kh * 32 - (lane >> 5) * 4;
+#pragma unroll
+            for (int e = 0; e < 16; e++)
+              if (8 * (e >> 2) + (e & 3) > lim) st[Q][e] = -INFINITY;
+          }
+#pragma unroll
+          for (int e = 16 * n / H; e < 16 * (n + 1) / H; e++) mx = fmaxf(mx, st[Q][e]);
+          if constexpr (n == H - 1) {
+            mx = max_halves(mx);
+            mn = fmaxf(m, mx * sc);
+          }
+        } else {
+          constexpr int k = n - H, N = 2 * KD - H;
+          constexpr int lo = 16 * k / N, hi = 16 * (k + 1) / N;
+#pragma unroll
+          for (int e = lo; e < hi; e++) {
+            float p = __builtin_amdgcn_exp2f(st[Q][e] * sc - mn);
+            ps += p;
+            asm volatile("" : "+v"(p), "+v"(ps));  // (here, not where it is used)
+            st[Q][e] = p;
+          }
+          if constexpr (lo < 8 && hi >= 8) {
+            pf[Q][0] = acc_to_b(st[Q], 0);
+            asm volatile("" : "+v"(pf[Q][0]));
+          }
+          if constexpr (hi == 16) {
+            pf[Q][1] = acc_to_b(st[Q], 1);
+            asm volatile("" : "+v"(pf[Q][1]));
+          }
+        }
+      }
+      __builtin_amdgcn_sched_barrier(0);
+    };
+    auto pv = [&](auto NC) {
+      constexpr int n = decltype(NC)::value;
+      if constexpr (do_pv) acc[n % DT] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf[n], pf[P][n / DT], acc[n % DT], 0, 0, 0);
+      __builtin_amdgcn_sched_barrier(0);
+    };
+    static_for<H>([&](auto NC) {
+      pv(NC);
+      between(NC);
+    });
+    wait_dma();  // this wavefront's part of K(u), V(u - 1)
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+    issue(rk, Q);
+    if constexpr (do_s) {
+#pragma unroll
+      for (int i = 0; i < KD; i++)
+        if (i < KA) kf[i] = fr.template rows<P * B, 0>(i);
+    }
+    __builtin_amdgcn_sched_barrier(0);
+    static_for<KD - H>([&](auto NC) {
+      constexpr int n = H + decltype(NC)::value;
+      pv(std::integral_constant<int, n>{});
+      between(std::integral_constant<int, n>{});
+    });
+    issue(rv, 2 + P);
+    __builtin_amdgcn_sched_barrier(0);
+    static_for<KD>([&](auto NC) {
+      constexpr int n = decltype(NC)::value;
+      if constexpr (do_s) {
+        if constexpr (n + KA < KD) kf[n + KA] = fr.template rows<P * B, 0>(n + KA);
+      }
+      if constexpr (do_sm) vf[n] = fr.template cols<(2 + Q) * B, n / DT>(n % DT);
+      if constexpr (do_s) {
+        if constexpr (n == 0) st[P] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[0], qf[0], zero16(), 0, 0, 0);
+        else st[P] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[n], qf[n], st[P], 0, 0, 0);
+      }
+      __builtin_amdgcn_sched_barrier(0);
+      between(std::integral_constant<int, KD + n>{});
+    });
+    if constexpr (do_sm) {
+      if (__any(mn > m)) {  // rescale only when some row's maximum moved
+        const float corr = __builtin_amdgcn_exp2f(m - mn);
+        l *= corr;
+#pragma unroll
+        for (int t = 0; t < DT; t++)
+#pragma unroll
+          for (int e = 0; e < 16; e++) acc[t][e] *= corr;
+        m = mn;
+      }
+      l += ps;
+    }
+  };
+  using Y = std::true_type;
+  using N = std::false_type;
+  using P0 = std::integral_constant<int, 0>;
+  using P1 = std::integral_constant<int, 1>;
+  // The last block has parity 0.  The products of the first full iteration find zeros.
+  if (nblk & 1) {
+    issue(rk, 0);
+    iter(P0{}, Y{}, N{}, N{}, N{});
+  } else {
+    issue(rk, 1);
+    iter(P1{}, Y{}, N{}, N{}, N{});
+    iter(P0{}, Y{}, Y{}, N{}, Y{});
+  }
+  for (int u = 2; u < nblk; u += 2) {
+    iter(P1{}, Y{}, Y{}, N{}, Y{});
+    iter(P0{}, Y{}, Y{}, N{}, Y{});
+  }
+  iter(P1{}, N{}, Y{}, Y{}, Y{});
+#pragma unroll
+  for (int n = 0; n < KD; n++) acc[n % DT] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf[n], pf[0][n / DT], acc[n % DT], 0, 0, 0);
+  wait_dma();
+  __syncthreads();
+  l += __shfl_xor(l, 32, 64);
+  // the odd wavefront of a pair hands its sums over
+  f32x4* mine = reinterpret_cast<f32x4*>(&lds[0][0]) + (wave >> 1) * (DT * 4 + 1) * 64 + lane;
+  if (kh) {
+#pragma unroll
+    for (int t = 0; t < DT; t++)
+#pragma unroll
+      for (int g = 0; g < 4; g++) mine[(t * 4 + g) * 64] = f32x4{acc[t][4 * g], acc[t][4 * g + 1], acc[t][4 * g + 2], acc[t][4 * g + 3]};
+    mine[DT * 4 * 64] = f32x4{m, l, 0.f, 0.f};
+  }
+  __syncthreads();
+  if (kh) return;
+  const f32x4 other = mine[DT * 4 * 64];
+  const float mm = fmaxf(m, other[0]), a0 = __builtin_amdgcn_exp2f(m - mm), a1 = __builtin_amdgcn_exp2f(other[0] - mm);
+  l = l * a0 + other[1] * a1;
+#pragma unroll
+  for (int t = 0; t < DT; t++)
+#pragma unroll
+    for (int g = 0; g < 4; g++) {
+      const f32x4 v = mine[(t * 4 + g) * 64];
+#pragma unroll
+      for (int r = 0; r < 4; r++) acc[t][4 * g + r] = acc[t][4 * g + r] * a0 + v[r] * a1;
+    }
+  const float inv = 1.f / l;
+  bf16_t* ob = o + int64_t(bi) * S * ldo;
+#pragma unroll
+  for (int t = 0; t < DT; t++) store_t(ob, ldo, qi, hq * D + t * 32, acc[t], inv, lane, qi < S);
+  if (lane < 32 && qi < S) lse[(int64_t(bi) * nq + hq) * S + qi] = (mm + __builtin_amdgcn_logf(l)) * LN2;
+}
+
 // ================================================================ backward: dQ
 // Same decomposition as the forward.  Per KV block: S^T = K Q^T, dP^T = V dO^T, dS^T = P^T (dP^T - delta),
 // dQ^T += K^T dS^T.
@@ -1099,18 +1304,29 @@ __global__ __launch_bounds__(256) void gqa_reduce_kernel(const float* __restrict
 
 namespace mls {
 
+// The forward on pairs of wavefronts pays where the longest chain of the other kernel decides, that is up to about one of its workgroups
+// (of 128 rows) per CU; with more of them the second load of every key block costs more than the balance gains.  us, other / pairs:
+//   d = 128: 64 workgroups 6.7 / 6.5 (128 positions), 160 14.5 / 13.0 (512), 240 17.7 / 16.2 (700), 320 45.7 / 36.1 (2048), 384 46.5 / 42.8
+//            (2048) but 17.7 / 20.9 (384), 512 52 / 56 (2048); of short rows it is the workgroups that cost: 192 10.2 / 11.3 (256), 8.5 / 9.9 (200)
+//   d = 64:  320 12.0 / 10.7 (600), 384 8.9 / 8.6 (200), 28.9 / 23.8 (2048), 448 10.3 / 12.3 (256), 14.9 / 14.7 (800), 512 32.0 / 32.0 (2048)
+// Up to 64 positions a pair has one block and nothing to share (48: 5.4 / 5.8).
+bool fwd_pairs(int b, int S, int nq, int d) {
+  const int64_t wgs = int64_t(b) * nq * ((S + 127) / 128);
+  return S > 64 && wgs <= (d == 64 ? 384 : S >= 384 ? 320 : 128);
+}
+
 hipError_t attn_fwd_bf16(const void* qkv, int64_t ld_qkv, void* o, int64_t ld_o, float* lse, int b, int S, int nq, int nkv,
                          int d, hipStream_t st) {
   if (b == 0 || S == 0) return hipSuccess;
+  if (d != 128 && d != 64) return hipErrorInvalidValue;
+  if (fwd_pairs(b, S, nq, d)) {
+    auto kern = d == 128 ? attn_fwd_pair_kernel<128> : attn_fwd_pair_kernel<64>;
+    hipLaunchKernelGGL(kern, dim3(nq * b, (S + 63) / 64), dim3(AT_THREADS), 0, st, (const bf16_t*)qkv, ld_qkv, (bf16_t*)o, ld_o, lse, S, nq, nkv);
+    return hipGetLastError();
+  }
   dim3 grid(nq, (S + 127) / 128, b);
-  if (d == 128)
-    hipLaunchKernelGGL(attn_fwd_kernel<128>, grid, dim3(AT_THREADS), 0, st, (const bf16_t*)qkv, ld_qkv, (bf16_t*)o, ld_o,
-                       lse, S, nq, nkv);
-  else if (d == 64)
-    hipLaunchKernelGGL(attn_fwd_kernel<64>, grid, dim3(AT_THREADS), 0, st, (const bf16_t*)qkv, ld_qkv, (bf16_t*)o, ld_o,
-                       lse, S, nq, nkv);
-  else
-    return hipErrorInvalidValue;
+  auto kern = d == 128 ? attn_fwd_kernel<128> : attn_fwd_kernel<64>;
+  hipLaunchKernelGGL(kern, grid, dim3(AT_THREADS), 0, st, (const bf16_t*)qkv, ld_qkv, (bf16_t*)o, ld_o, lse, S, nq, nkv);
   return hipGetLastError();
 }
 

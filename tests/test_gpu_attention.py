@@ -67,6 +67,21 @@ def test_attention_against_fp64_on_the_same_operands(nq, nkv, d, seq, mb, gain):
         assert e <= 1.5e-2, (name, e)
 
 
+# Which forward kernel a grid gets: pairs of wavefronts up to the number of workgroups where the other one wins.  Sequences around the
+# blocks of either, at the last size of the one and the first of the other.
+@pytest.mark.parametrize("nq,nkv,d,seq,mb,pairs", [
+    (3, 1, 64, 64, 2, False), (3, 1, 64, 65, 2, True), (2, 1, 128, 127, 1, True), (4, 4, 128, 193, 1, True), (48, 16, 64, 70, 8, True),
+    (48, 16, 64, 70, 9, False), (16, 16, 128, 97, 8, True), (16, 16, 128, 97, 9, False), (48, 16, 64, 161, 5, False),
+    (16, 4, 128, 300, 3, False), (20, 4, 128, 385, 4, True), (27, 9, 128, 385, 3, False)])
+def test_forward_kernels_on_either_side_of_their_rule(nq, nkv, d, seq, mb, pairs):
+    import ctypes
+    import paper_2410_13333_amd as mls
+    f = mls.lib()._ZN3mls9fwd_pairsEiiii
+    f.restype = ctypes.c_bool
+    assert f(mb, seq, nq, d) is pairs
+    test_attention_against_fp64_on_the_same_operands(nq, nkv, d, seq, mb, 8.0)
+
+
 @pytest.mark.parametrize("gain", [16.0, 40.0])
 @pytest.mark.parametrize("nq,nkv,d,seq", [(4, 2, 64, 200), (4, 4, 128, 400)])
 def test_the_largest_probability_of_a_row_is_not_rounded(nq, nkv, d, seq, gain):
