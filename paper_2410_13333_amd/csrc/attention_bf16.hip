@@ -1,7 +1,7 @@
 // Causal grouped-query attention for bf16 storage on the gfx950 matrix cores: forward with online softmax,
 // backward as two kernels (dQ, which also forms the row sums delta = dO . O; dK and dV) that recompute the
-// probabilities from the saved log-sum-exp.  Where few workgroups share the chip, dQ is formed from the dS that the dK / dV
-// kernel leaves behind instead (dq_from_ds); nothing else of size S x S is ever written.  No float atomics, so results are
+// probabilities from the saved log-sum-exp.  Where few workgroups share the chip, both run in one launch (bwd_together), or dQ is formed
+// from the dS that the dK / dV kernel leaves behind instead (dq_from_ds); nothing else of size S x S is ever written.  No float atomics, so results are
 // bitwise reproducible.
 //
 // Register-resident probabilities.  v_mfma_f32_32x32x16_bf16 leaves element (g*4+r) of lane l at
@@ -649,27 +649,25 @@ __global__ __launch_bounds__(AT_THREADS, 2) void attn_fwd_pair_kernel(const bf16
 // ================================================================ backward: dQ
 // Same decomposition as the forward.  Per KV block: S^T = K Q^T, dP^T = V dO^T, dS^T = P^T (dP^T - delta),
 // dQ^T += K^T dS^T.
+// FORM: forms the row statistics and writes them out; otherwise they are there.
 template <int D>
-__global__ __launch_bounds__(AT_THREADS, 2) void attn_dq_kernel(const bf16_t* __restrict__ qkv, int64_t ld,
-                                                                const bf16_t* __restrict__ o, int64_t ld_o,
-                                                                const bf16_t* __restrict__ d_o, int64_t ldo,
-                                                                const float* __restrict__ lse,
-                                                                float* __restrict__ stats,
-                                                                bf16_t* __restrict__ dqkv, int64_t ldg, int S, int nq,
-                                                                int nkv, const float* __restrict__ cos_tab,
-                                                                const float* __restrict__ sin_tab) {
+constexpr int dq_lds() { return 4 * Tile<D>::BYTES; }
+template <int D, bool FORM>
+__device__ __forceinline__ void attn_dq(char* lds_, int qb, int hq, int bi, int nb, const bf16_t* __restrict__ qkv, int64_t ld,
+                                        const bf16_t* __restrict__ o, int64_t ld_o, const bf16_t* __restrict__ d_o, int64_t ldo,
+                                        const float* __restrict__ lse, float* __restrict__ stats, bf16_t* __restrict__ dqkv, int64_t ldg,
+                                        int S, int nq, int nkv, const float* __restrict__ cos_tab, const float* __restrict__ sin_tab) {
   using TL = Tile<D>;
   constexpr int KD = D / 16, DT = D / 32;
-  __shared__ __attribute__((aligned(1024))) bf16_t lds[2][2][TR * D];
+  bf16_t* lds = reinterpret_cast<bf16_t*>(lds_);  // [2][K | V][TR * D]
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int qb = gridDim.y - 1 - blockIdx.y;
-  const int hq = blockIdx.x, bi = blockIdx.z, hk = hq / (nq / nkv);
+  const int hk = hq / (nq / nkv);
   const bf16_t* base = qkv + int64_t(bi) * S * ld;
   const bf16_t* dob = d_o + int64_t(bi) * S * ldo;
   const int q0 = qb * 128, qw = q0 + wave * 32, qi = qw + (lane & 31);
   const float scale = rsqrtf((float)D), sc = scale * LOG2E;
   const i32x4 rsrc = make_rsrc(base, uint32_t(int64_t(S) * ld * 2));
-  const uint32_t lds0 = (uint32_t)(uintptr_t)(MLS_LDS bf16_t*)&lds[0][0][0];
+  const uint32_t lds0 = (uint32_t)(uintptr_t)(MLS_LDS bf16_t*)lds;
   TL tl;
   tl.init(ld, wave, lane);
   auto issue = [&](int blk, bool live) {
@@ -685,11 +683,11 @@ __global__ __launch_bounds__(AT_THREADS, 2) void attn_dq_kernel(const bf16_t* __
     dof[kk] = gfrag(dob, ldo, qi, hq * D + kk * 16 + (lane >> 5) * 8, qi < S);
   }
   const int64_t si = (int64_t(bi) * nq + hq) * S + qi;
-  const float L2 = qi < S ? lse[si] * LOG2E : 0.f;
-  // delta = dO . O of this lane's query row (the two lane halves hold complementary features).  The row statistics are
-  // written out as the dK / dV kernel takes them: lse log2(e), then -delta, each [b][n_q][S]
-  float dl = 0.f;
-  {
+  float L2, dl = 0.f;
+  if constexpr (FORM) {
+    L2 = qi < S ? lse[si] * LOG2E : 0.f;
+    // delta = dO . O of this lane's query row (the two lane halves hold complementary features).  The row statistics are
+    // written out as the dK / dV kernel takes them: lse log2(e), then -delta, each [b][n_q][S]
     const bf16_t* ob = o + int64_t(bi) * S * ld_o;
 #pragma unroll
     for (int kk = 0; kk < KD; kk++) {
@@ -700,8 +698,11 @@ __global__ __launch_bounds__(AT_THREADS, 2) void attn_dq_kernel(const bf16_t* __
     dl += __shfl_xor(dl, 32, 64);
     if (lane < 32 && qi < S) {
       stats[si] = L2;
-      stats[int64_t(gridDim.z) * nq * S + si] = -dl;
+      stats[int64_t(nb) * nq * S + si] = -dl;
     }
+  } else {
+    L2 = qi < S ? stats[si] : 0.f;
+    dl = qi < S ? -stats[int64_t(nb) * nq * S + si] : 0.f;
   }
 
   f32x16 acc[DT];
@@ -717,8 +718,8 @@ __global__ __launch_bounds__(AT_THREADS, 2) void attn_dq_kernel(const bf16_t* __
     __syncthreads();
     issue(blk + 1, blk + 1 < nblk);
     if (j0 <= qw + 31) {
-      const bf16_t* ks = lds[cur][0];
-      const bf16_t* vs = lds[cur][1];
+      const bf16_t* ks = lds + cur * 2 * TR * D;
+      const bf16_t* vs = ks + TR * D;
       const bool diag = j0 + TR - 1 > qw;  // some pair of this wave is masked
       // one 32-key sub-block at a time, so that only one S^T / dP^T pair is live
 #pragma unroll
@@ -760,6 +761,16 @@ __global__ __launch_bounds__(AT_THREADS, 2) void attn_dq_kernel(const bf16_t* __
   }
 }
 
+template <int D>
+__global__ __launch_bounds__(AT_THREADS, 2) void attn_dq_kernel(const bf16_t* __restrict__ qkv, int64_t ld, const bf16_t* __restrict__ o, int64_t ld_o,
+                                                                const bf16_t* __restrict__ d_o, int64_t ldo, const float* __restrict__ lse,
+                                                                float* __restrict__ stats, bf16_t* __restrict__ dqkv, int64_t ldg, int S, int nq,
+                                                                int nkv, const float* __restrict__ cos_tab, const float* __restrict__ sin_tab) {
+  __shared__ __attribute__((aligned(1024))) char lds[dq_lds<D>()];
+  attn_dq<D, true>(lds, gridDim.y - 1 - blockIdx.y, blockIdx.x, blockIdx.z, gridDim.z, qkv, ld, o, ld_o, d_o, ldo, lse, stats, dqkv, ldg, S, nq, nkv,
+                   cos_tab, sin_tab);
+}
+
 // ================================================================ backward: dK and dV
 // grid (n_kv * nsplit, kv blocks of 128 KT, b), longest first; wave w owns the 32 KT key rows from j0 + 32 KT w and keeps
 // their K and V as B operands.  Loops over the query heads of the group and the 32-row query steps at or below the
@@ -787,8 +798,11 @@ __host__ __device__ __forceinline__ int64_t ds_head_bytes(int S) {
   const int64_t n = (S + 31) / 32;
   return n * (n + 1) / 2 * DS_TILE;
 }
+template <int D, int KT>
+constexpr int dkv_lds() { return (KT == 2 ? 4 * 32 * KT * D * 2 : 0) + 5 * (2 * Tile<D, 32>::BYTES + 512); }
+// x: KV head and part of its group; kb: key block; bi: sequence, of nb
 template <int D, int KT, bool DS>
-__device__ __forceinline__ void attn_dkv(const bf16_t* __restrict__ qkv, int64_t ld, const bf16_t* __restrict__ d_o, int64_t ldo,
+__device__ __forceinline__ void attn_dkv(char* lds, int x, int kb, int bi, int nb, const bf16_t* __restrict__ qkv, int64_t ld, const bf16_t* __restrict__ d_o, int64_t ldo,
                                          const float* __restrict__ stats, bf16_t* __restrict__ dqkv, int64_t ldg, int S, int nq, int nkv,
                                          int nsplit, float* __restrict__ part, const float* __restrict__ cos_tab,
                                          const float* __restrict__ sin_tab, char* __restrict__ ds) {
@@ -799,17 +813,17 @@ __device__ __forceinline__ void attn_dkv(const bf16_t* __restrict__ qkv, int64_t
   constexpr int STG = 2 * TS::BYTES + 512, V_BYTES = VL ? 4 * KR * D * 2 : 0;
   constexpr int NREQ = 2 * TS::NI + 1;                       // requests of a wavefront per step
   constexpr int NST = DS ? 2 * KT : 0;                       // and stores of dS
-  __shared__ __attribute__((aligned(1024))) char lds[V_BYTES + SLOTS * STG];  // [V] [slot][Q|dO|lse log2(e)|-delta]
+  static_assert(dkv_lds<D, KT>() == V_BYTES + SLOTS * STG);    // lds: [V] [slot][Q|dO|lse log2(e)|-delta]
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), half = lane >> 5;
   // nsplit > 1: the query heads of a group are shared out over nsplit workgroups (few KV heads would otherwise
   // leave most CUs idle); each writes its fp32 partial sum to `part`, which gqa_reduce_kernel adds up in order
-  const int kb = blockIdx.y, hk = blockIdx.x / nsplit, sp = blockIdx.x % nsplit, bi = blockIdx.z;
+  const int hk = x / nsplit, sp = x % nsplit;
   const int grp = nq / nkv / nsplit, hq0 = hk * (nq / nkv) + sp * grp;
   const bf16_t* base = qkv + int64_t(bi) * S * ld;
   const bf16_t* dob = d_o + int64_t(bi) * S * ldo;
   const int j0 = kb * 4 * KR, jw = j0 + wave * KR;
   const float scale = rsqrtf((float)D), sc = scale * LOG2E;
-  const uint32_t lds0 = (uint32_t)(uintptr_t)(MLS_LDS char*)&lds[0];
+  const uint32_t lds0 = (uint32_t)(uintptr_t)(MLS_LDS char*)lds;
   const uint32_t ring = lds0 + V_BYTES;
 
   const int q0 = j0 / 32, nst = (S + 31) / 32 - q0;  // first query step, steps per head
@@ -822,7 +836,7 @@ __device__ __forceinline__ void attn_dkv(const bf16_t* __restrict__ qkv, int64_t
   // The next request: byte offsets of its rows behind the three descriptors, moved on by a step or to the next head's last step.
   const i32x4 rs_q = make_rsrc(base, uint32_t(int64_t(S) * ld * 2)), rs_d = make_rsrc(dob, uint32_t(int64_t(S) * ldo * 2));
   // even wavefronts fetch lse log2(e), odd ones -delta (each pair the same values)
-  const i32x4 rs_s = make_rsrc(stats + ((wave & 1) * int64_t(gridDim.z) * nq + int64_t(bi) * nq + hq0) * S, uint32_t(grp * S) * 4);
+  const i32x4 rs_s = make_rsrc(stats + ((wave & 1) * int64_t(nb) * nq + int64_t(bi) * nq + hq0) * S, uint32_t(grp * S) * 4);
   int r_i = nst - 1, r_slot = 0, r_left = niter;
   uint32_t o_q = uint32_t((q0 + r_i) * 64 * ld) + hq0 * D * 2, o_d = uint32_t((q0 + r_i) * 64 * ldo) + hq0 * D * 2, o_s = (q0 + r_i) * 128;
   const uint32_t step_q = uint32_t(64 * ld), step_d = uint32_t(64 * ldo);
@@ -1112,7 +1126,7 @@ __device__ __forceinline__ void attn_dkv(const bf16_t* __restrict__ qkv, int64_t
     } else if (ji < S) {
       // part: [dK | dV][b][n_kv][nsplit][S][D] fp32
       float* out = part + (((int64_t(bi) * nkv + hk) * nsplit + sp) * S + ji) * D;
-      const int64_t whole = int64_t(gridDim.z) * nkv * nsplit * S * D;
+      const int64_t whole = int64_t(nb) * nkv * nsplit * S * D;
 #pragma unroll
       for (int t = 0; t < DT; t++)
 #pragma unroll
@@ -1132,7 +1146,8 @@ __global__ __launch_bounds__(AT_THREADS, 1) void attn_dkv_kernel(const bf16_t* _
                                                                  int64_t ldo, const float* __restrict__ stats, bf16_t* __restrict__ dqkv,
                                                                  int64_t ldg, int S, int nq, int nkv, int nsplit, float* __restrict__ part,
                                                                  const float* __restrict__ cos_tab, const float* __restrict__ sin_tab) {
-  attn_dkv<D, KT, false>(qkv, ld, d_o, ldo, stats, dqkv, ldg, S, nq, nkv, nsplit, part, cos_tab, sin_tab, nullptr);
+  __shared__ __attribute__((aligned(1024))) char lds[dkv_lds<D, KT>()];
+  attn_dkv<D, KT, false>(lds, blockIdx.x, blockIdx.y, blockIdx.z, gridDim.z, qkv, ld, d_o, ldo, stats, dqkv, ldg, S, nq, nkv, nsplit, part, cos_tab, sin_tab, nullptr);
 }
 template <int D, int KT>
 __global__ __launch_bounds__(AT_THREADS, 1) void attn_dkv_ds_kernel(const bf16_t* __restrict__ qkv, int64_t ld, const bf16_t* __restrict__ d_o,
@@ -1140,11 +1155,34 @@ __global__ __launch_bounds__(AT_THREADS, 1) void attn_dkv_ds_kernel(const bf16_t
                                                                     int64_t ldg, int S, int nq, int nkv, int nsplit, float* __restrict__ part,
                                                                     const float* __restrict__ cos_tab, const float* __restrict__ sin_tab,
                                                                     char* __restrict__ ds) {
-  attn_dkv<D, KT, true>(qkv, ld, d_o, ldo, stats, dqkv, ldg, S, nq, nkv, nsplit, part, cos_tab, sin_tab, ds);
+  __shared__ __attribute__((aligned(1024))) char lds[dkv_lds<D, KT>()];
+  attn_dkv<D, KT, true>(lds, blockIdx.x, blockIdx.y, blockIdx.z, gridDim.z, qkv, ld, d_o, ldo, stats, dqkv, ldg, S, nq, nkv, nsplit, part, cos_tab, sin_tab, ds);
+}
+
+// ================================================================ backward: dQ, dK and dV in one launch
+// Both kernels above on row statistics that attn_stats_kernel has formed.  Apart, each lasts as long as its longest causal chain while
+// the CUs with short ones idle; together the one's short chains run beside the other's long ones.  grid ((n_kv nsplit + n_q) b, blocks of
+// 128): rank by rank, the longest first, a rank's key blocks before its query blocks.  Heads of 64 have two workgroups per CU, of 128 one
+// (the registers of the dK / dV part).  Whole backward (us, apart or with dQ from dS -> this): 2 x 1000 positions, 16 heads of 64 over 4:
+// 52 -> 39; 512, 16 of 64: 28 -> 18; 1024, 16 of 128: 59 -> 41.5; 2048, 16 of 128: 98.5 -> 83.5; 512, 16 of 128: 38.5 -> 27; 2 x 128, 4 of
+// 64: 15.7 -> 11.4.  The second half of the ranks in ascending order, so that two workgroups of a CU are long and short: slower (2048 x 16
+// of 128 98, 4096 x 16 of 64 155 instead of 147).
+template <int D>
+__global__ __launch_bounds__(AT_THREADS, D == 64 ? 2 : 1) void attn_bwd_kernel(const bf16_t* __restrict__ qkv, int64_t ld, const bf16_t* __restrict__ d_o,
+                                                                               int64_t ldo, float* __restrict__ stats, bf16_t* __restrict__ dqkv,
+                                                                               int64_t ldg, int S, int nq, int nkv, int nsplit, int b,
+                                                                               float* __restrict__ part, const float* __restrict__ cos_tab,
+                                                                               const float* __restrict__ sin_tab) {
+  __shared__ __attribute__((aligned(1024))) char lds[dq_lds<D>() > dkv_lds<D, 1>() ? dq_lds<D>() : dkv_lds<D, 1>()];
+  const int rank = blockIdx.y, bi = blockIdx.x % b, x = blockIdx.x / b;
+  if (x < nkv * nsplit)
+    attn_dkv<D, 1, false>(lds, x, rank, bi, b, qkv, ld, d_o, ldo, stats, dqkv, ldg, S, nq, nkv, nsplit, part, cos_tab, sin_tab, nullptr);
+  else
+    attn_dq<D, false>(lds, gridDim.y - 1 - rank, x - nkv * nsplit, bi, b, qkv, ld, nullptr, 0, d_o, ldo, nullptr, stats, dqkv, ldg, S, nq, nkv, cos_tab, sin_tab);
 }
 
 // ================================================================ backward: dQ from the dS of the dK / dV kernel
-// The row statistics that kernel takes, when no dQ kernel has formed them: lse log2(e), then -(dO . O), each [b][n_q][S].
+// The row statistics that the dK / dV kernel takes, when no dQ kernel forms them: lse log2(e), then -(dO . O), each [b][n_q][S].
 // grid (n_q, blocks of 64 positions, b).  HBM-bound.
 template <int D>
 __global__ __launch_bounds__(AT_THREADS) void attn_stats_kernel(const bf16_t* __restrict__ o, int64_t ld_o, const bf16_t* __restrict__ d_o,
@@ -1354,14 +1392,26 @@ DkvPlan dkv_plan(int b, int S, int nq, int nkv, int d) {
   return best;
 }
 
+// dQ, dK and dV in one launch: up to about as many workgroups of 128 query rows as have a place on the chip at once, beyond which the
+// workgroups that follow balance the chip by themselves and the launch costs dQ the second (64: the third) workgroup per CU it has alone.  Whole
+// backward, best other / together (us):
+//   d = 128: 128 workgroups 32.3 / 25.6 (120 positions), 59 / 41.5 (1024), 256 98.5 / 83.5 (2048), 43.1 / 43.3 (256), 288 90.8 / 91.5 (1500), 320
+//            115 / 123 (2048), 512 150 / 167; of one row block 192 28.4 / 30.3, 34.4 / 36.0, 224 36.8 / 38.9
+//   d = 64:  320 87 / 63 (2048), 512 99 / 86 (2048), 768 131 / 124 (2048), 25.9 / 19.9 (64), 1024 302 / 278 (4096), 54.4 / 55.9 (128), 2048 295 / 313
+//            (2048), 4096 1008 / 1118 (4096)
+bool bwd_together(int b, int S, int nq, int d) {
+  const int64_t wgs = int64_t(b) * nq * ((S + 127) / 128);
+  return wgs <= (d == 64 ? (S > 128 ? 1024 : 768) : (S > 128 ? 256 : 128));
+}
+
 // dQ from dS as the dK / dV kernel leaves it in memory, instead of a kernel that forms S, P and dP once more: two of its three
 // products less, for 2 bytes of dS written and read per score and a launch more.  It pays where the dQ kernel is bound by the chain
-// of its few workgroups (about one per CU) and dS stays in the 256 MiB memory-side cache.  Whole backward, dS formed twice / once
-// (us): 16 heads of 128 at 2048 120 / 103, 8 at 4096 217 / 187, 32 at 1000 77 / 70, 32 at 512 49 / 47, 16 x 2 at 256 35 / 33; with
-// more workgroups 32 at 2048 152 / 146 (nothing is left of it in a whole step), 48 at 2048 233 / 236, 32 at 4096 461 / 476.  Heads of 64
-// have half the products for as much dS: 32 at 2048 103 / 108, 16 x 2 at 1000 55 / 53, a step of such a layer 1 029 / 1 038.
+// of its few workgroups (about one per CU) and dS stays in the 256 MiB memory-side cache, where a little more than one workgroup per CU
+// keeps dQ out of the launch of dK and dV (up to 256: 2048 positions, 16 heads of 128 120 twice, 98.5 once, 83.5 together).  Whole backward,
+// dS formed once / in one launch (us): 20 heads of 128 over 4 at 2048 positions 115 / 123, 32 over 8 at 1280 86 / 91; twice / once with more
+// workgroups: 32 at 2048 152 / 146 (nothing is left of it in a whole step), 48 at 2048 233 / 236, 32 at 4096 461 / 476.
 bool dq_from_ds(int b, int S, int nq, int d) {
-  return d == 128 && S >= 256 && int64_t(b) * nq * ((S + 127) / 128) <= 320 && ds_head_bytes(S) * nq * b <= int64_t(256) << 20;
+  return d == 128 && S >= 256 && !bwd_together(b, S, nq, d) && int64_t(b) * nq * ((S + 127) / 128) <= 320 && ds_head_bytes(S) * nq * b <= int64_t(256) << 20;
 }
 
 // partial sums of dK and dV, then dS
@@ -1384,7 +1434,13 @@ hipError_t attn_bwd_bf16(const void* qkv, int64_t ld_qkv, const void* o, int64_t
   char* ds = part && dq_from_ds(b, S, nq, d) ? reinterpret_cast<char*>(part + part_floats(b, S, nq, nkv, d)) : nullptr;
   const int ns = part ? pl.ns : 1, kt = ds ? 1 : pl.kt;  // (so few workgroups always get one key tile: their longest chain decides)
   dim3 gq(nq, (S + 127) / 128, b), gk(nkv * ns, (S + 128 * kt - 1) / (128 * kt), b);
-  if (ds) {
+  if (bwd_together(b, S, nq, d)) {
+    auto stat = d == 128 ? attn_stats_kernel<128> : attn_stats_kernel<64>;
+    auto bwd = d == 128 ? attn_bwd_kernel<128> : attn_bwd_kernel<64>;
+    hipLaunchKernelGGL(stat, dim3(nq, (S + 63) / 64, b), dim3(AT_THREADS), 0, st, (const bf16_t*)o, ld_o, (const bf16_t*)d_o, ld_do, lse, stats, S, nq);
+    hipLaunchKernelGGL(bwd, dim3((nkv * ns + nq) * b, (S + 127) / 128), dim3(AT_THREADS), 0, st, (const bf16_t*)qkv, ld_qkv, (const bf16_t*)d_o, ld_do, stats,
+                       (bf16_t*)dqkv, ld_dqkv, S, nq, nkv, ns, b, part, cos_tab, sin_tab);
+  } else if (ds) {
     hipLaunchKernelGGL(attn_stats_kernel<128>, dim3(nq, (S + 63) / 64, b), dim3(AT_THREADS), 0, st, (const bf16_t*)o, ld_o, (const bf16_t*)d_o, ld_do, lse, stats, S, nq);
     hipLaunchKernelGGL((attn_dkv_ds_kernel<128, 1>), gk, dim3(AT_THREADS), 0, st, (const bf16_t*)qkv, ld_qkv, (const bf16_t*)d_o, ld_do, stats,
                        (bf16_t*)dqkv, ld_dqkv, S, nq, nkv, ns, part, cos_tab, sin_tab, ds);

@@ -82,6 +82,22 @@ def test_forward_kernels_on_either_side_of_their_rule(nq, nkv, d, seq, mb, pairs
     test_attention_against_fp64_on_the_same_operands(nq, nkv, d, seq, mb, 8.0)
 
 
+# How the backward's kernels are launched: dQ, dK and dV together up to a number of workgroups, dQ from the stored dS a little beyond it
+# (heads of 128, 256 positions and more), else apart.
+@pytest.mark.parametrize("nq,nkv,d,seq,mb,together,from_ds", [
+    (3, 1, 64, 64, 2, True, False), (6, 2, 64, 193, 1, True, False), (16, 1, 128, 33, 8, True, False), (16, 4, 128, 128, 9, False, False),
+    (43, 43, 128, 129, 3, False, False), (16, 8, 128, 161, 8, True, False), (22, 11, 128, 385, 3, False, True), (80, 16, 128, 260, 1, True, False),
+    (24, 24, 64, 97, 32, True, False), (24, 8, 64, 97, 33, False, False), (32, 16, 64, 129, 16, True, False), (32, 16, 64, 129, 17, False, False)])
+def test_backward_launches_on_either_side_of_their_rules(nq, nkv, d, seq, mb, together, from_ds):
+    import ctypes
+    import paper_2410_13333_amd as mls
+    for name, want in (("_ZN3mls12bwd_togetherEiiii", together), ("_ZN3mls10dq_from_dsEiiii", from_ds)):
+        f = getattr(mls.lib(), name)
+        f.restype = ctypes.c_bool
+        assert f(mb, seq, nq, d) is want
+    test_attention_against_fp64_on_the_same_operands(nq, nkv, d, seq, mb, 1.0)
+
+
 @pytest.mark.parametrize("gain", [16.0, 40.0])
 @pytest.mark.parametrize("nq,nkv,d,seq", [(4, 2, 64, 200), (4, 4, 128, 400)])
 def test_the_largest_probability_of_a_row_is_not_rounded(nq, nkv, d, seq, gain):

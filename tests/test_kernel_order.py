@@ -112,6 +112,14 @@ def test_first_reader_of_an_asm_product_where_ds_is_stored(attention_asm):
     assert NEEDED <= least < 10 ** 6, least
 
 
+@pytest.mark.parametrize("form", ["ILi64E", "ILi128E"])
+def test_first_reader_of_an_asm_product_in_the_shared_launch(attention_asm, form):
+    (lines,) = [v for k, v in attention_asm.items() if "attn_bwd_kernel" + form in k]
+    least, seen = shortest_distances(lines)
+    assert seen >= 8
+    assert NEEDED <= least < 10 ** 6, least
+
+
 def test_only_the_kernel_of_few_workgroups_stores_ds(attention_asm):
     """Two stores through a buffer descriptor per step and key tile there; the other forms of the kernel hold none of it."""
     stores = {k: sum("buffer_store" in line for line in v) for k, v in attention_asm.items() if "attn_dkv" in k}
