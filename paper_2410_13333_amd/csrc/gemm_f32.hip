@@ -29,9 +29,10 @@ __device__ __forceinline__ void dma16g(const float* p, uint32_t lds_byte) {
 //   else      32 k-rows of 32 NT floats; the two lane halves read rows four apart, which must not share banks: rows of 128 bytes
 //             change places with their neighbour where bit 2 of k is set, in rows of 256 bytes the halves do
 // A wavefront fetches the pieces at k0, k0 + stride, ... by requests q0 .. q0 + NQ - 1 (of 4 NT).  Their addresses move on by
-// additions; only a last piece that is not whole forms them anew.
+// additions; only a last piece that is not whole forms them anew, and the first one of another matrix: with SEG the contraction runs on
+// through nseg matrices of depth K each (list), every one of which ends with a piece of its own.
 // Rows beyond the end repeat the last ones (their results are not stored); so do k-values, and `read` zeroes those.
-template <int NT, bool ALONG_K>
+template <int NT, bool ALONG_K, bool SEG>
 struct Operand {
   static constexpr int CPR = ALONG_K ? 8 : 8 * NT, RPQ = 64 / CPR;  // chunks per row, rows per request
   static constexpr int NQ = NT == 1 ? 4 : 2;  // requests of a wavefront per piece: all, or its share of the workgroup's
@@ -39,6 +40,8 @@ struct Operand {
   int64_t ld, step;
   int row0, rows, K, k0, stride, q0;
   const float* at[NQ];
+  const float* const* list = nullptr;
+  int nseg = 1, seg = 0;
   __device__ __forceinline__ const float* place(int i, int lane, int k0_) const {
     const int s = (q0 + i) * RPQ + lane / CPR, c = lane % CPR;
     if (ALONG_K) return base + int64_t(min(row0 + s, rows - 1)) * ld + min(k0_ + 4 * (c ^ (s & 7)), K - 4);
@@ -50,8 +53,17 @@ struct Operand {
 #pragma unroll
     for (int i = 0; i < NQ; i++) at[i] = place(i, lane, k0);
   }
-  // the next piece into LDS byte lds on
+  // the next piece into LDS byte lds on (SEG: beyond the last matrix some piece of it)
   __device__ __forceinline__ void request(int lane, uint32_t lds) {
+    if constexpr (SEG) {
+      const int span = (K + KC - 1) / KC * KC;
+      if (k0 >= span) {
+        for (; k0 >= span; seg++) k0 -= span;
+        base = list[min(seg, nseg - 1)];
+#pragma unroll
+        for (int i = 0; i < NQ; i++) at[i] = place(i, lane, k0);
+      }
+    }
     const bool whole = k0 + KC <= K;
 #pragma unroll
     for (int i = 0; i < NQ; i++) {
@@ -102,18 +114,23 @@ __device__ __forceinline__ f32x16 zero16() {
 }
 
 // A(m, k): AK ? A[m*lda + k] : A[k*lda + m]; B(k, n): BK ? B[n*ldb + k] : B[k*ldb + n].  add: C += instead of C =.
+// SEG: A and B are the first of nseg matrices each.
+struct Source {
+  const float *A, *B;
+  int M, N, K;
+  int64_t lda, ldb;
+  const float *const *a, *const *b;
+  int nseg;
+};
 // Few tiles: one workgroup per 32x32 tile of C, wavefront w takes pieces w, w + 4, ... through NS stages of its own.
-template <bool AK, bool BK>
-__global__ __launch_bounds__(256, 2) void gemm_f32_shared_kernel(const float* __restrict__ A, const float* __restrict__ B,
-                                                                               float* C, const float* R, int M, int N, int K,
-                                                                               int64_t lda, int64_t ldb, int64_t ldc, int64_t ldr,
-                                                                               int add) {
-  extern __shared__ __attribute__((aligned(1024))) float smem[];
+template <bool AK, bool BK, bool SEG>
+__device__ __forceinline__ void tile32(float* smem, const Source& s, int m0, int n0, float* C, const float* R, int64_t ldc, int64_t ldr, int add) {
+  const int M = s.M, N = s.N, K = s.K;
   constexpr int STAGE = 2 * 32 * KC, NS = 2, NREQ = 8;
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), l32 = lane & 31, hf = lane >> 5;
-  const int m0 = blockIdx.y * 32, n0 = blockIdx.x * 32;
-  Operand<1, AK> oa(A, lda, m0, M, K, wave * KC, 4 * KC, 0, lane);
-  Operand<1, BK> ob(B, ldb, n0, N, K, wave * KC, 4 * KC, 0, lane);
+  Operand<1, AK, SEG> oa(s.A, s.lda, m0, M, K, wave * KC, 4 * KC, 0, lane);
+  Operand<1, BK, SEG> ob(s.B, s.ldb, n0, N, K, wave * KC, 4 * KC, 0, lane);
+  if constexpr (SEG) oa.list = s.a, ob.list = s.b, oa.nseg = ob.nseg = s.nseg;
   const float* mine = smem + wave * NS * STAGE;
   const uint32_t lds = (uint32_t)(uintptr_t)(MLS_LDS float*)(smem) + wave * NS * STAGE * 4;
   auto request = [&](int piece) {
@@ -122,13 +139,14 @@ __global__ __launch_bounds__(256, 2) void gemm_f32_shared_kernel(const float* __
     ob.request(lane, at + STAGE * 2);
   };
   f32x16 acc = zero16();
-  const int pieces = (K + KC - 1) / KC, n = (pieces - wave + 3) / 4;  // all, of this wavefront (0 if there are fewer than four)
+  const int each = (K + KC - 1) / KC, pieces = SEG ? each * s.nseg : each;
+  const int n = (pieces - wave + 3) / 4;  // of this wavefront (0 if there are fewer than four)
   float a[2][KC / 2], b[2][KC / 2];
   auto read = [&](int p, int set) {
     const float* st = mine + (p % NS) * STAGE;
-    const int left = K - (p * 4 + wave) * KC;
-    Operand<1, AK>::read(st, 0, l32, hf, left, a[set]);
-    Operand<1, BK>::read(st + STAGE / 2, 0, l32, hf, left, b[set]);
+    const int left = !SEG ? K - (p * 4 + wave) * KC : K % KC ? K - (p * 4 + wave) % each * KC : KC;
+    Operand<1, AK, SEG>::read(st, 0, l32, hf, left, a[set]);
+    Operand<1, BK, SEG>::read(st + STAGE / 2, 0, l32, hf, left, b[set]);
   };
   auto step = [&](int p, int set) {  // the products of piece p; piece p + 1 is read meanwhile, p + 2 requested into its stage
     if (p + 2 < n) request(p + 2);
@@ -171,18 +189,17 @@ __global__ __launch_bounds__(256, 2) void gemm_f32_shared_kernel(const float* __
 
 // Many tiles: one workgroup per 64x64 tile, a quadrant for each wavefront, pieces of both operands shared in a ring of four
 // stages.  Four accumulators take every fourth piece each and are added like the sums of the four wavefronts above: same bits.
-template <bool AK, bool BK>
-__global__ __launch_bounds__(256, 2) void gemm_f32_kernel(const float* __restrict__ A, const float* __restrict__ B, float* C,
-                                                          const float* R, int M, int N, int K, int64_t lda, int64_t ldb, int64_t ldc,
-                                                          int64_t ldr, int add) {
-  extern __shared__ __attribute__((aligned(1024))) float smem[];
+template <bool AK, bool BK, bool SEG>
+__device__ __forceinline__ void tile64(float* smem, const Source& s, int m0, int n0, float* C, const float* R, int64_t ldc, int64_t ldr, int add) {
+  const int M = s.M, N = s.N, K = s.K;
   constexpr int STAGE = 2 * 64 * KC, NS = 4, NREQ = 4;
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), l32 = lane & 31, hf = lane >> 5;
-  const int m0 = blockIdx.y * 64, n0 = blockIdx.x * 64, wm = wave & 1, wn = wave >> 1;
-  Operand<2, AK> oa(A, lda, m0, M, K, 0, KC, 2 * wave, lane);
-  Operand<2, BK> ob(B, ldb, n0, N, K, 0, KC, 2 * wave, lane);
+  const int wm = wave & 1, wn = wave >> 1;
+  Operand<2, AK, SEG> oa(s.A, s.lda, m0, M, K, 0, KC, 2 * wave, lane);
+  Operand<2, BK, SEG> ob(s.B, s.ldb, n0, N, K, 0, KC, 2 * wave, lane);
+  if constexpr (SEG) oa.list = s.a, ob.list = s.b, oa.nseg = ob.nseg = s.nseg;
   const uint32_t lds = (uint32_t)(uintptr_t)(MLS_LDS float*)(smem);
-  const int pieces = (K + KC - 1) / KC;
+  const int each = (K + KC - 1) / KC, pieces = SEG ? each * s.nseg : each;
   auto request = [&](int piece) {  // (beyond the last one: its last k-value, so that the counts of the waits hold)
     const uint32_t at = lds + (piece % NS) * STAGE * 4;
     oa.request(lane, at);
@@ -193,8 +210,9 @@ __global__ __launch_bounds__(256, 2) void gemm_f32_kernel(const float* __restric
     float a[2][KC / 2], b[2][KC / 2];
     auto read = [&](int p, int set) {
       const float* st = smem + (p % NS) * STAGE;
-      Operand<2, AK>::read(st, wm, l32, hf, K - p * KC, a[set]);
-      Operand<2, BK>::read(st + STAGE / 2, wn, l32, hf, K - p * KC, b[set]);
+      const int left = !SEG ? K - p * KC : K % KC ? K - p % each * KC : KC;
+      Operand<2, AK, SEG>::read(st, wm, l32, hf, left, a[set]);
+      Operand<2, BK, SEG>::read(st + STAGE / 2, wn, l32, hf, left, b[set]);
     };
     auto sync = [&]() {  // the next piece is there for everyone, and everyone has read the one before it
       wait_vmcnt<(NS - 2) * NREQ>();
@@ -230,12 +248,54 @@ __global__ __launch_bounds__(256, 2) void gemm_f32_kernel(const float* __restric
   store_tile(acc[0], C, R, m0 + wm * 32 + l32, n0 + wn * 32, M, N, ldc, ldr, add, hf);
 }
 
+template <bool AK, bool BK, bool LARGE>
+__global__ __launch_bounds__(256, 2) void gemm_f32_kernel(const float* __restrict__ A, const float* __restrict__ B, float* C, const float* R,
+                                                          int M, int N, int K, int64_t lda, int64_t ldb, int64_t ldc, int64_t ldr, int add) {
+  extern __shared__ __attribute__((aligned(1024))) float smem[];
+  const Source s = {A, B, M, N, K, lda, ldb, nullptr, nullptr, 1};
+  if constexpr (LARGE) tile64<AK, BK, false>(smem, s, blockIdx.y * 64, blockIdx.x * 64, C, R, ldc, ldr, add);
+  else tile32<AK, BK, false>(smem, s, blockIdx.y * 32, blockIdx.x * 32, C, R, ldc, ldr, add);
+}
+
+// The weight gradients of a layer over all micro-batches of a call: C (+)= sum_i A_i^T B_i for each problem of a list, all over matrices of
+// the same depth, in one launch.  A launch for each of them and each micro-batch left most of the chip idle between its few tiles' chains
+// (weight gradients of a call, us, as events around the launches: hidden 512, ffn 1376, 2 x 512 tokens 142 -> 95; 768, 2048, 3 x 1152 652 -> 424;
+// 192, 600, 2 x 384 72 -> 21) and rounded the sums once per micro-batch.
+constexpr int MAX_SEGS = 16, MAX_GROUP = 4;
+struct TnGroup {
+  int nseg, n, K, add;
+  struct {
+    const float *a[MAX_SEGS], *b[MAX_SEGS];
+    float* C;
+    int64_t lda, ldb, ldc;
+    int M, N, tiles_n, tile0;
+  } p[MAX_GROUP];
+  mls::Colsum cs;  // the last cs.wgs workgroups add columns up instead
+};
+template <bool LARGE>
+__global__ __launch_bounds__(256, 2) void gemm_f32_tn_group_kernel(TnGroup g) {
+  extern __shared__ __attribute__((aligned(1024))) float smem[];
+  const int tiles = gridDim.x - g.cs.wgs, t = blockIdx.x;
+  if (t >= tiles) {
+    colsum_block(g.cs, t - tiles, smem);
+    return;
+  }
+  int i = 0;
+  while (i + 1 < g.n && t >= g.p[i + 1].tile0) i++;
+  const auto& p = g.p[i];
+  const int at = t - p.tile0, m = at / p.tiles_n, n = at - m * p.tiles_n;
+  const Source s = {p.a[0], p.b[0], p.M, p.N, g.K, p.lda, p.ldb, p.a, p.b, g.nseg};
+  if constexpr (LARGE) tile64<false, false, true>(smem, s, m * 64, n * 64, p.C, nullptr, p.ldc, 0, g.add);
+  else tile32<false, false, true>(smem, s, m * 32, n * 32, p.C, nullptr, p.ldc, 0, g.add);
+}
+
+constexpr int LDS = 4 * 2 * 2 * 32 * KC * 4;  // of every form
+
 template <bool AK, bool BK>
 hipError_t launch_f32(const float* A, const float* B, float* C, const float* R, int M, int N, int K, int64_t lda, int64_t ldb,
                       int64_t ldc, int64_t ldr, int add, hipStream_t st) {
   const bool large = mls::gemm_f32_large(M, N, K);
-  constexpr int LDS = 4 * 2 * 2 * 32 * KC * 4;  // of both
-  auto kern = large ? gemm_f32_kernel<AK, BK> : gemm_f32_shared_kernel<AK, BK>;
+  auto kern = large ? gemm_f32_kernel<AK, BK, true> : gemm_f32_kernel<AK, BK, false>;
   static std::atomic<uint64_t> lds_raised[2] = {{0}, {0}};
   if (hipError_t e = mls::raise_lds_limit(reinterpret_cast<const void*>(kern), LDS, lds_raised[large])) return e;
   const int t = large ? 64 : 32;
@@ -272,6 +332,46 @@ hipError_t gemm_f32(int mode, const void* A, const void* B, void* C, const void*
     case GEMM_TN: return launch_f32<false, false>(a, b, c, nullptr, M, N, K, lda, ldb, ldc, ldr, overwrite ? 0 : 1, st);
     default: return hipErrorInvalidValue;
   }
+}
+
+// The 64x64 tiles where all problems together have 320 of them and more, as for a single product (us, 32x32 / 64x64: hidden 512, ffn 1376
+// over 48 tokens 35 / 19, 768 / 2048 over 3 x 1152 518 / 424, 708 tiles over 2 x 512 96 / 95; 156 over 2 x 384 21 / 29).
+hipError_t gemm_f32_tn_group(const TnProduct* p, int n, int nseg, int kseg, hipStream_t st, bool overwrite, const Colsum& cs) {
+  if (nseg == 0 || kseg == 0) return hipSuccess;
+  if (n < 1 || n > MAX_GROUP || nseg > MAX_SEGS) return hipErrorInvalidValue;
+  TnGroup g = {};
+  int64_t tiles[2] = {0, 0};
+  auto up = [](int v, int t) { return int64_t((v + t - 1) / t); };
+  for (int i = 0; i < n; i++)
+    for (int l = 0; l < 2; l++) tiles[l] += up(p[i].M, l ? 64 : 32) * up(p[i].N, l ? 64 : 32);
+  const bool large = tiles[1] >= 320;
+  const int t = large ? 64 : 32;
+  if (tiles[large] + cs.wgs >= (int64_t(1) << 31)) return hipErrorInvalidValue;
+  g.nseg = nseg;
+  g.K = kseg;
+  g.add = overwrite ? 0 : 1;
+  g.cs = cs;
+  int64_t at = 0;
+  for (int i = 0; i < n; i++) {
+    if (p[i].M == 0 || p[i].N == 0) continue;
+    auto& q = g.p[g.n++];
+    for (int j = 0; j < nseg; j++) {
+      q.a[j] = (const float*)p[i].A[j];
+      q.b[j] = (const float*)p[i].B[j];
+    }
+    q.C = (float*)p[i].C;
+    q.lda = p[i].lda; q.ldb = p[i].ldb; q.ldc = p[i].ldc;
+    q.M = p[i].M; q.N = p[i].N;
+    q.tiles_n = int(up(p[i].N, t));
+    q.tile0 = int(at);
+    at += up(p[i].M, t) * q.tiles_n;
+  }
+  if (g.n == 0) return hipSuccess;
+  auto kern = large ? gemm_f32_tn_group_kernel<true> : gemm_f32_tn_group_kernel<false>;
+  static std::atomic<uint64_t> lds_raised[2] = {{0}, {0}};
+  if (hipError_t e = raise_lds_limit(reinterpret_cast<const void*>(kern), LDS, lds_raised[large])) return e;
+  hipLaunchKernelGGL(kern, dim3(unsigned(at + cs.wgs)), dim3(256), LDS, st, g);
+  return hipGetLastError();
 }
 
 }  // namespace mls

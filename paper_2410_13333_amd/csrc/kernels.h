@@ -149,6 +149,9 @@ bool gemm_f32_large(int M, int N, int K);  // whether such a product runs on 64x
 // overwrite (GEMM_TN): C = instead of +=
 hipError_t gemm_f32(int mode, const void* A, const void* B, void* C, const void* R, int M, int N, int K, int64_t lda,
                     int64_t ldb, int64_t ldc, int64_t ldr, hipStream_t st, bool overwrite = false);
+// p[i].C (+)= sum_j p[i].A[j][kseg, M]^T * p[i].B[j][kseg, N] over nseg <= 16 pieces for up to four products, fp32 throughout, and the
+// column sums of cs, in one launch (nothing at all without a piece)
+hipError_t gemm_f32_tn_group(const TnProduct* p, int n, int nseg, int kseg, hipStream_t st, bool overwrite, const Colsum& cs = {});
 
 // ---- row-wise and elementwise kernels (elementwise.hip); dt selects the storage type; every matrix argument is
 // followed by its row stride in elements (all row strides are multiples of 8)

@@ -348,8 +348,8 @@ int shared_wgrad_tile(const mls_stage* s, const mls::TnProduct (&p)[4], int n, b
   return dma ? mls::gemm_bf16_tn_group_tile(p, 4, n, s->T, overwrite) : -1;
 }
 
-// C[M,N] += sum_i A_i[T,M]^T B_i[T,N] over n micro-batches (fp32 C) for each of them: in steps of 16 micro-batches on the bf16
-// DMA path (always taken when gu_f > 0), one launch per micro-batch and weight otherwise
+// C[M,N] += sum_i A_i[T,M]^T B_i[T,N] over n micro-batches (fp32 C) for each of them, in steps of 16 micro-batches: fp32 storage in one
+// launch; on the bf16 DMA path (always taken when gu_f > 0) in one launch or one for each; otherwise one per micro-batch and weight
 // cs: the gains' sums, which go along with the first launch that all four share (only given if there is one)
 int wgrad(mls_stage* s, const mls::TnProduct (&p)[4], int n, bool ow, const mls::Colsum& cs) {
   for (int i = 0; i < n; i += 16) {
@@ -361,20 +361,18 @@ int wgrad(mls_stage* s, const mls::TnProduct (&p)[4], int n, bool ow, const mls:
       q[j].B += i;
     }
     const bool over = ow && i == 0;
+    if (s->dt == mls::DT_FP32) {
+      LAUNCH(CLS_GEMM_TN, mls::gemm_f32_tn_group(q, 4, m, s->T, s->st, over, i == 0 ? cs : mls::Colsum{}));
+      continue;
+    }
     const int tile = shared_wgrad_tile(s, q, m, over);
     if (tile >= 0) {
       LAUNCH(CLS_GEMM_TN, mls::gemm_bf16_tn_group(q, 4, tile, m, s->T, s->st, over, i == 0 ? cs : mls::Colsum{}));
       continue;
     }
     for (auto& w : q) {
-      if (s->dt == mls::DT_BF16 && mls::gemm_tn_segments_ok(s->T, w.lda, w.ldb)) {
+      if (mls::gemm_tn_segments_ok(s->T, w.lda, w.ldb)) {
         LAUNCH(CLS_GEMM_TN, mls::gemm_bf16_tn_segments(w.A, w.B, m, w.C, w.M, w.N, s->T, w.lda, w.ldb, w.ldc, s->st, w.gu_f, over));
-        continue;
-      }
-      if (s->dt == mls::DT_FP32) {
-        for (int j = 0; j < m; j++)
-          LAUNCH(CLS_GEMM_TN, mls::gemm_f32(mls::GEMM_TN, w.A[j], w.B[j], w.C, nullptr, w.M, w.N, s->T, w.lda, w.ldb, w.ldc, 0, s->st,
-                                            over && j == 0));
         continue;
       }
       if (over) HIP_TRY(mls::fill_zero_f32((float*)w.C, size_t(w.M) * w.N, s->st));  // this path only accumulates
@@ -663,7 +661,7 @@ int mls_stage_backward_ex(mls_stage* s, const void* dY, float* grads, int32_t n,
     for (int i = 0; i < n; i++) have += k[i] > l;
     mls::TnProduct w[4];
     weight_grads(s, g, nullptr, w);
-    const bool shared = shared_wgrad_tile(s, w, have < 16 ? have : 16, ow) >= 0;
+    const bool shared = s->dt == mls::DT_FP32 || shared_wgrad_tile(s, w, have < 16 ? have : 16, ow) >= 0;
     for (int i = 0; i < n; i++) {
       if (k[i] <= l) continue;
       seen++;

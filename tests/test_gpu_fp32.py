@@ -78,6 +78,21 @@ def test_weight_gradients_over_an_odd_number_of_tokens_on_large_tiles():
         assert e <= 1e-5
 
 
+# one launch for the weight gradients of all micro-batches: 32x32 tiles, then 64x64 ones; pieces shorter than the four wavefronts' shares,
+# of one token, not whole, whole; more micro-batches than a launch takes; a last call that adds to the first
+@pytest.mark.parametrize("hidden,ffn,seq,n", [(72, 88, 1, 3), (72, 88, 40, 17), (72, 88, 96, 2), (264, 136, 133, 4), (520, 1400, 37, 3),
+                                              (520, 1400, 64, 2)])
+def test_weight_gradients_over_many_micro_batches(hidden, ffn, seq, n):
+    sh = synth.StageShape(hidden=hidden, n_q_heads=2, n_kv_heads=1, head_dim=64, ffn=ffn, seq=seq, micro_batch=1, layers=1,
+                          microbatches=n, dtype="fp32")
+    for interleave in (False, True):
+        ys, dxs, g, st = gpu_step(sh, 1000, 2000, 3000, [1] * n, interleave=interleave)
+        st.close()
+        rys, rdxs, rg = oracle_step(sh, 1000, 2000, 3000, [1] * n)
+        for e in [rel_err(a, b) for a, b in zip(ys + dxs, rys + rdxs)] + [grad_errors(sh, g, rg, 1)[0]]:
+            assert e <= 1e-5
+
+
 @pytest.mark.parametrize("bad", [float("inf"), float("nan")])
 def test_a_non_finite_position_reaches_no_earlier_one(bad):
     import torch
