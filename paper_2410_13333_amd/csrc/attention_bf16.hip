@@ -1420,7 +1420,8 @@ size_t part_floats(int b, int S, int nq, int nkv, int d) {
   return n > 1 ? (size_t(2) * b * nkv * n * S * d + 255) / 256 * 256 : 0;
 }
 size_t attn_bwd_scratch_floats(int dt, int b, int S, int nq, int nkv, int d) {
-  if (dt != DT_BF16 || nkv <= 0 || nq % nkv) return 0;
+  if (nkv <= 0 || nq % nkv) return 0;
+  if (dt != DT_BF16) return attn_bwd_f32_scratch_floats(b, S, nq, nkv, d);
   return part_floats(b, S, nq, nkv, d) + (dq_from_ds(b, S, nq, d) ? size_t(ds_head_bytes(S)) / 4 * nq * b : 0);
 }
 
@@ -1472,7 +1473,7 @@ hipError_t attn_bwd(int dt, const void* qkv, int64_t ld_qkv, const void* o, int6
   if (dt != DT_BF16 && cos_tab) return hipErrorInvalidValue;  // only the bf16 kernels turn the rotation back themselves
   return dt == DT_BF16
              ? attn_bwd_bf16(qkv, ld_qkv, o, ld_o, lse, d_o, ld_do, dqkv, ld_dqkv, delta, b, S, nq, nkv, d, st, part, cos_tab, sin_tab)
-             : attn_bwd_f32(qkv, ld_qkv, o, ld_o, lse, d_o, ld_do, dqkv, ld_dqkv, delta, b, S, nq, nkv, d, st);
+             : attn_bwd_f32(qkv, ld_qkv, o, ld_o, lse, d_o, ld_do, dqkv, ld_dqkv, delta, b, S, nq, nkv, d, st, part);
 }
 
 }  // namespace mls

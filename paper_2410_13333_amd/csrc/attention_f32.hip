@@ -13,7 +13,8 @@
 // wavefront walks, not the rate: a workgroup owns 32 rows, its four wavefronts take every fourth block of the other
 // sequence index, and their partial results meet in a fixed tree through LDS.
 // Measured (2 x 256 positions, 8 / 4 heads of 64): forward 3415 -> 13 us, dQ 4313 -> 17 us, dK and dV 13468 -> 38 us
-// against the kernels this replaced (one thread per row, scalar loops).
+// against the kernels this replaced (one thread per row, scalar loops); dQ, dK and dV in one launch, every query head's share of dK and dV
+// in a workgroup of its own: 56 -> 30 us.
 #include <type_traits>
 
 #include "common.h"
@@ -211,22 +212,24 @@ __global__ __launch_bounds__(256) void attn_fwd_f32_kernel(const float* __restri
   if (hf == 0) lse[(int64_t(bi) * nq + hq) * S + qi] = M + __logf(L);
 }
 
-// grid as the forward: dQ of 32 rows, and their delta
+// ---- backward: dQ, dK and dV.  TOGETHER: in one launch, where both parts form delta = dO . O of the rows they need; apart the dQ kernel
+// forms it and the dK / dV kernel reads it.
+// LDS of a workgroup: sums of wavefronts, and blocks on the diagonal
 template <int DT>
-__global__ __launch_bounds__(256) void attn_dq_f32_kernel(const float* __restrict__ qkv, int64_t ld, const float* __restrict__ o,
-                                                          int64_t ldo, const float* __restrict__ lse,
-                                                          const float* __restrict__ d_o, int64_t ldd, float* __restrict__ delta,
-                                                          float* __restrict__ dqkv, int64_t ldg, int b, int S, int nq, int nkv, int d) {
-  __shared__ float part[2][DT * 16][64];
-  __shared__ float sp[4][32][32];
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, l32 = lane & 31, hf = lane >> 5;
-  const int hq = blockIdx.x % nq, bi = blockIdx.x / nq % b, q0 = ((S + 31) / 32 - 1 - blockIdx.x / nq / b) * 32, hk = hq / (nq / nkv);
+struct BwdLds {
+  float part[2][DT * 16][64], sp[4][32][32];
+};
+// dQ of query rows q0 .. q0 + 31
+template <int DT, bool TOGETHER>
+__device__ __forceinline__ void dq_block(BwdLds<DT>& lds, int q0, int hq, int bi, const float* __restrict__ qkv, int64_t ld, const float* __restrict__ o,
+                                         int64_t ldo, const float* __restrict__ lse, const float* __restrict__ d_o, int64_t ldd,
+                                         float* __restrict__ delta, float* __restrict__ dqkv, int64_t ldg, int S, int nq, int nkv, int d) {
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, l32 = lane & 31, hf = lane >> 5, hk = hq / (nq / nkv);
   const float* base = qkv + int64_t(bi) * S * ld;
   const float *K = base + int64_t(nq + hk) * d, *V = base + int64_t(nq + nkv + hk) * d;
   const int qi = q0 + l32;
   const bool live = qi < S;
   const float sc = rsqrtf((float)d);
-  const int64_t si = (int64_t(bi) * nq + hq) * S + qi;
   float q[DT * 16], dO[DT * 16];
   float dl = 0.f;
   load_row<DT>(live ? d_o + (int64_t(bi) * S + qi) * ldd + int64_t(hq) * d : nullptr, d, hf, dO);
@@ -234,7 +237,8 @@ __global__ __launch_bounds__(256) void attn_dq_f32_kernel(const float* __restric
 #pragma unroll
   for (int i = 0; i < DT * 16; i++) dl += q[i] * dO[i];
   dl += __shfl_xor(dl, 32, 64);
-  if (wave == 0 && hf == 0 && live) delta[si] = dl;
+  const int64_t si = (int64_t(bi) * nq + hq) * S + qi;
+  if (!TOGETHER && wave == 0 && hf == 0 && live) delta[si] = dl;
   const float L = live ? lse[si] : 0.f;
   load_row<DT>(live ? base + int64_t(qi) * ld + int64_t(hq) * d : nullptr, d, hf, q);
   f32x16 acc[DT];
@@ -252,25 +256,21 @@ __global__ __launch_bounds__(256) void attn_dq_f32_kernel(const float* __restric
       s[e] = j <= qi ? __expf(s[e] * sc - L) * (dp[e] - dl) : 0.f;
     }
     if (j0 < q0) accumulate<DT>(acc, kc, s);
-    else accumulate_diagonal<DT>(acc, kc, s, K, ld, j0, S, d, l32, hf, sp[wave], [&](int j) { return j <= qi; });
+    else accumulate_diagonal<DT>(acc, kc, s, K, ld, j0, S, d, l32, hf, lds.sp[wave], [&](int j) { return j <= qi; });
   }
-  sum_waves<DT>(acc, part, wave, lane);
+  sum_waves<DT>(acc, lds.part, wave, lane);
   if (wave == 0 && live) store_row<DT>(dqkv + (int64_t(bi) * S + qi) * ldg + int64_t(hq) * d, acc, sc, d, hf);
 }
 
-// grid over (key blocks of 32, longest first; batch rows; KV heads): dK and dV of 32 rows; the wavefronts share out the (query head of the
-// group, query block at or below the diagonal) pairs
-template <int DT>
-__global__ __launch_bounds__(256) void attn_dkv_f32_kernel(const float* __restrict__ qkv, int64_t ld, const float* __restrict__ lse,
-                                                           const float* __restrict__ d_o, int64_t ldd,
-                                                           const float* __restrict__ delta, float* __restrict__ dqkv, int64_t ldg,
-                                                           int b, int S, int nq, int nkv, int d) {
-  __shared__ float part[2][DT * 16][64];
-  __shared__ float sp[4][32][32];
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, l32 = lane & 31, hf = lane >> 5;
-  const int hk = blockIdx.x % nkv, bi = blockIdx.x / nkv % b, j0 = blockIdx.x / nkv / b * 32, grp = nq / nkv;
+// dK and dV of key rows j0 .. j0 + 31 from the query heads hq0 .. hq0 + heads - 1 of their group: the wavefronts share out the (head, query
+// block at or below the diagonal) pairs.  part: the sums go there, [dK | dV][b][n_q][S][d], at hq0.
+template <int DT, bool TOGETHER>
+__device__ __forceinline__ void dkv_block(BwdLds<DT>& lds, int j0, int hq0, int heads, int bi, int nb_all, const float* __restrict__ qkv, int64_t ld,
+                                          const float* __restrict__ o, int64_t ldo, const float* __restrict__ lse, const float* __restrict__ d_o,
+                                          int64_t ldd, const float* __restrict__ delta, float* __restrict__ dqkv, int64_t ldg, int S, int nq,
+                                          int nkv, int d, float* __restrict__ part) {
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, l32 = lane & 31, hf = lane >> 5, hk = hq0 / (nq / nkv);
   const float* base = qkv + int64_t(bi) * S * ld;
-  const float* dob = d_o + int64_t(bi) * S * ldd;
   const int ji = j0 + l32;
   const float sc = rsqrtf((float)d);
   float k[DT * 16], v[DT * 16];
@@ -280,20 +280,30 @@ __global__ __launch_bounds__(256) void attn_dkv_f32_kernel(const float* __restri
   clear(dk);
   clear(dv);
   const int nb = (S - j0 + 31) / 32;  // query blocks of a head at or below the diagonal
-  for (int it = wave; it < nb * grp; it += 4) {
-    const int hq = hk * grp + it / nb, i0 = j0 + (it % nb) * 32;
-    const int64_t si = (int64_t(bi) * nq + hq) * S;
-    const float *Q = base + int64_t(hq) * d, *dO = dob + int64_t(hq) * d;
+  for (int it = wave; it < nb * heads; it += 4) {
+    const int hq = hq0 + it / nb, i0 = j0 + (it % nb) * 32;
+    const int64_t si = (int64_t(bi) * nq + hq) * S, row = int64_t(bi) * S + i0 + l32;
+    const float *Q = base + int64_t(hq) * d, *dO = d_o + int64_t(bi) * S * ldd + int64_t(hq) * d;
+    const bool live = i0 + l32 < S;
     float r[DT * 16], rc[16][DT], L[16], dl[16];
 #pragma unroll
     for (int e = 0; e < 16; e++) {
       const int i = i0 + 8 * (e >> 2) + 4 * hf + (e & 3);
       L[e] = i < S ? lse[si + i] : 0.f;
-      dl[e] = i < S ? delta[si + i] : 0.f;
+      if (!TOGETHER) dl[e] = i < S ? delta[si + i] : 0.f;
     }
-    load_row<DT>(i0 + l32 < S ? Q + int64_t(i0 + l32) * ld : nullptr, d, hf, r);
+    load_row<DT>(live ? Q + int64_t(i0 + l32) * ld : nullptr, d, hf, r);
     f32x16 p = dot_rows(r, k);
-    load_row<DT>(i0 + l32 < S ? dO + int64_t(i0 + l32) * ldd : nullptr, d, hf, r);
+    load_row<DT>(live ? dO + int64_t(i0 + l32) * ldd : nullptr, d, hf, r);
+    if constexpr (TOGETHER) {
+      float f[DT * 16], own = 0.f;  // of row i0 + l32
+      load_row<DT>(live ? o + row * ldo + int64_t(hq) * d : nullptr, d, hf, f);
+#pragma unroll
+      for (int i = 0; i < DT * 16; i++) own += f[i] * r[i];
+      own += __shfl_xor(own, 32, 64);
+#pragma unroll
+      for (int e = 0; e < 16; e++) dl[e] = __shfl(own, 8 * (e >> 2) + 4 * hf + (e & 3), 64);
+    }
     load_cols<DT>(dO, ldd, i0, S, d, l32, hf, rc);
     f32x16 dp = dot_rows(r, v);
 #pragma unroll
@@ -303,17 +313,72 @@ __global__ __launch_bounds__(256) void attn_dkv_f32_kernel(const float* __restri
       dp[e] = i >= ji && i < S ? p[e] * (dp[e] - dl[e]) : 0.f;  // dS
     }
     if (i0 > j0) accumulate<DT>(dv, rc, p);
-    else accumulate_diagonal<DT>(dv, rc, p, dO, ldd, i0, S, d, l32, hf, sp[wave], [&](int i) { return i >= ji; });
+    else accumulate_diagonal<DT>(dv, rc, p, dO, ldd, i0, S, d, l32, hf, lds.sp[wave], [&](int i) { return i >= ji; });
     load_cols<DT>(Q, ld, i0, S, d, l32, hf, rc);
     if (i0 > j0) accumulate<DT>(dk, rc, dp);
-    else accumulate_diagonal<DT>(dk, rc, dp, Q, ld, i0, S, d, l32, hf, sp[wave], [&](int i) { return i >= ji; });
+    else accumulate_diagonal<DT>(dk, rc, dp, Q, ld, i0, S, d, l32, hf, lds.sp[wave], [&](int i) { return i >= ji; });
   }
-  sum_waves<DT>(dk, part, wave, lane);
-  sum_waves<DT>(dv, part, wave, lane);
+  sum_waves<DT>(dk, lds.part, wave, lane);
+  sum_waves<DT>(dv, lds.part, wave, lane);
   if (wave != 0 || ji >= S) return;
+  if (part) {
+    float* out = part + ((int64_t(bi) * nq + hq0) * S + ji) * d;
+    store_row<DT>(out, dk, sc, d, hf);
+    store_row<DT>(out + int64_t(nb_all) * nq * S * d, dv, 1.f, d, hf);
+    return;
+  }
   float* out = dqkv + (int64_t(bi) * S + ji) * ldg;
   store_row<DT>(out + int64_t(nq + hk) * d, dk, sc, d, hf);
   store_row<DT>(out + int64_t(nq + nkv + hk) * d, dv, 1.f, d, hf);
+}
+
+// One-dimensional grid: rank by rank of the blocks of 32, the longest first; in a rank the key blocks of every KV head (part: of every query
+// head), then the query blocks; batch rows fastest.
+template <int DT>
+__global__ __launch_bounds__(256) void attn_bwd_f32_kernel(const float* __restrict__ qkv, int64_t ld, const float* __restrict__ o, int64_t ldo,
+                                                           const float* __restrict__ lse, const float* __restrict__ d_o, int64_t ldd,
+                                                           float* __restrict__ dqkv, int64_t ldg, int b, int S, int nq, int nkv, int d,
+                                                           float* __restrict__ part) {
+  __shared__ BwdLds<DT> lds;
+  const int kv = part ? nq : nkv, per = (kv + nq) * b, rank = blockIdx.x / per, x = blockIdx.x % per / b, bi = blockIdx.x % b;
+  const int heads = part ? 1 : nq / nkv;
+  if (x < kv) dkv_block<DT, true>(lds, rank * 32, x * heads, heads, bi, b, qkv, ld, o, ldo, lse, d_o, ldd, nullptr, dqkv, ldg, S, nq, nkv, d, part);
+  else dq_block<DT, true>(lds, ((S + 31) / 32 - 1 - rank) * 32, x - kv, bi, qkv, ld, o, ldo, lse, d_o, ldd, nullptr, dqkv, ldg, S, nq, nkv, d);
+}
+// apart: grid as the forward's; and over (key blocks of 32, longest first; batch rows; KV heads)
+template <int DT>
+__global__ __launch_bounds__(256, DT <= 2 ? 2 : 1) void attn_dq_f32_kernel(const float* __restrict__ qkv, int64_t ld, const float* __restrict__ o, int64_t ldo,
+                                                          const float* __restrict__ lse, const float* __restrict__ d_o, int64_t ldd,
+                                                          float* __restrict__ delta, float* __restrict__ dqkv, int64_t ldg, int b, int S, int nq,
+                                                          int nkv, int d) {
+  __shared__ BwdLds<DT> lds;
+  dq_block<DT, false>(lds, ((S + 31) / 32 - 1 - blockIdx.x / nq / b) * 32, blockIdx.x % nq, blockIdx.x / nq % b, qkv, ld, o, ldo, lse, d_o, ldd, delta,
+                      dqkv, ldg, S, nq, nkv, d);
+}
+template <int DT>
+__global__ __launch_bounds__(256) void attn_dkv_f32_kernel(const float* __restrict__ qkv, int64_t ld, const float* __restrict__ lse,
+                                                           const float* __restrict__ d_o, int64_t ldd, const float* __restrict__ delta,
+                                                           float* __restrict__ dqkv, int64_t ldg, int b, int S, int nq, int nkv, int d) {
+  __shared__ BwdLds<DT> lds;
+  const int grp = nq / nkv;
+  dkv_block<DT, false>(lds, blockIdx.x / nkv / b * 32, blockIdx.x % nkv * grp, grp, blockIdx.x / nkv % b, b, qkv, ld, nullptr, 0, lse, d_o, ldd, delta,
+                       dqkv, ldg, S, nq, nkv, d, nullptr);
+}
+// dK and dV from the parts of the query heads of a group, in ascending order; a thread owns four features
+__global__ __launch_bounds__(256) void gqa_reduce_f32_kernel(const float* __restrict__ part, int b, int S, int nq, int nkv, int d,
+                                                             float* __restrict__ dqkv, int64_t ldg) {
+  const int64_t id = int64_t(blockIdx.x) * 256 + threadIdx.x, whole = int64_t(b) * nkv * S * (d / 4);
+  if (id >= 2 * whole) return;
+  const int what = id >= whole, grp = nq / nkv;
+  const int64_t r = what ? id - whole : id;
+  const int c = int(r % (d / 4)) * 4, token = int(r / (d / 4) % S), hk = int(r / (d / 4) / S % nkv), bi = int(r / (d / 4) / S / nkv);
+  const float* p = part + (((int64_t(what) * b + bi) * nq + hk * grp) * S + token) * d + c;
+  float4 a = *reinterpret_cast<const float4*>(p);
+  for (int i = 1; i < grp; i++) {
+    const float4 v = *reinterpret_cast<const float4*>(p + int64_t(i) * S * d);
+    a.x += v.x; a.y += v.y; a.z += v.z; a.w += v.w;
+  }
+  *reinterpret_cast<float4*>(dqkv + (int64_t(bi) * S + token) * ldg + int64_t(nq + (what ? nkv : 0) + hk) * d + c) = a;
 }
 
 template <class F>
@@ -339,16 +404,36 @@ hipError_t attn_fwd_f32(const void* qkv, int64_t ld_qkv, void* o, int64_t ld_o, 
   });
 }
 
+// dQ, dK and dV in one launch up to 544 blocks of query rows, a good two per CU; with more of them the rows of O that the dK / dV part reads
+// for delta, and the registers that part costs the other, outweigh what the balance gains.  Backward (us, apart / together): 16 heads of 64
+// over 2 x 256 positions 56 / 30, 3 over 1 at 2 x 384 100 / 39, 36 at 384 (432 blocks) 79 / 75, 24 over 12 at 700 (528) 145 / 123, 16 at 1500
+// (752) 282 / 353.
+bool bwd_f32_together(int b, int S, int nq) { return int64_t(b) * nq * ((S + 31) / 32) <= 544; }
+// The query heads of a group apart where their key blocks alone would leave CUs without one: a float of workspace per element of dK and dV
+// and query head.
+size_t attn_bwd_f32_scratch_floats(int b, int S, int nq, int nkv, int d) {
+  return nq > nkv && bwd_f32_together(b, S, nq) && int64_t(b) * nkv * ((S + 31) / 32) < 256 ? size_t(2) * b * nq * S * d : 0;
+}
+
 hipError_t attn_bwd_f32(const void* qkv, int64_t ld_qkv, const void* o, int64_t ld_o, const float* lse, const void* d_o,
-                        int64_t ld_do, void* dqkv, int64_t ld_dqkv, float* delta, int b, int S, int nq, int nkv, int d,
-                        hipStream_t st) {
+                        int64_t ld_do, void* dqkv, int64_t ld_dqkv, float* delta, int b, int S, int nq, int nkv, int d, hipStream_t st, float* part) {
   if (b == 0 || S == 0 || nq == 0) return hipSuccess;
-  return for_tiles(d, [&](auto DT) {
-    hipLaunchKernelGGL(attn_dq_f32_kernel<decltype(DT)::value>, dim3(unsigned((S + 31) / 32) * nq * b), dim3(256), 0, st,
-                       (const float*)qkv, ld_qkv, (const float*)o, ld_o, lse, (const float*)d_o, ld_do, delta, (float*)dqkv,
-                       ld_dqkv, b, S, nq, nkv, d);
-    hipLaunchKernelGGL(attn_dkv_f32_kernel<decltype(DT)::value>, dim3(unsigned((S + 31) / 32) * nkv * b), dim3(256), 0, st,
-                       (const float*)qkv, ld_qkv, lse, (const float*)d_o, ld_do, delta, (float*)dqkv, ld_dqkv, b, S, nq, nkv, d);
+  if (!attn_bwd_f32_scratch_floats(b, S, nq, nkv, d)) part = nullptr;
+  const unsigned n = unsigned((S + 31) / 32);
+  return for_tiles(d, [&](auto DTC) {
+    constexpr int DT = decltype(DTC)::value;
+    if (!bwd_f32_together(b, S, nq)) {
+      hipLaunchKernelGGL(attn_dq_f32_kernel<DT>, dim3(n * nq * b), dim3(256), 0, st, (const float*)qkv, ld_qkv, (const float*)o, ld_o, lse,
+                         (const float*)d_o, ld_do, delta, (float*)dqkv, ld_dqkv, b, S, nq, nkv, d);
+      hipLaunchKernelGGL(attn_dkv_f32_kernel<DT>, dim3(n * nkv * b), dim3(256), 0, st, (const float*)qkv, ld_qkv, lse, (const float*)d_o, ld_do, delta,
+                         (float*)dqkv, ld_dqkv, b, S, nq, nkv, d);
+      return;
+    }
+    hipLaunchKernelGGL(attn_bwd_f32_kernel<DT>, dim3(n * ((part ? nq : nkv) + nq) * b), dim3(256), 0, st, (const float*)qkv, ld_qkv, (const float*)o,
+                       ld_o, lse, (const float*)d_o, ld_do, (float*)dqkv, ld_dqkv, b, S, nq, nkv, d, part);
+    if (part)
+      hipLaunchKernelGGL(gqa_reduce_f32_kernel, dim3(unsigned((int64_t(2) * b * nkv * S * (d / 4) + 255) / 256)), dim3(256), 0, st, part, b, S, nq,
+                         nkv, d, (float*)dqkv, ld_dqkv);
   });
 }
 

@@ -93,6 +93,20 @@ def test_weight_gradients_over_many_micro_batches(hidden, ffn, seq, n):
             assert e <= 1e-5
 
 
+# the backward in one launch, up to 544 blocks of 32 query rows, and apart; the query heads of a group apart (fewer than 256 blocks of key rows)
+# or in one workgroup
+@pytest.mark.parametrize("nq,nkv,d,seq,mb,together,apart", [
+    (6, 2, 64, 33, 1, True, True), (6, 3, 80, 97, 3, True, True), (34, 17, 64, 481, 1, True, False), (34, 17, 64, 513, 1, False, False),
+    (16, 15 + 1, 64, 200, 2, True, False), (32, 8, 16, 250, 2, True, True), (3, 1, 128, 160, 2, True, True), (46, 23, 128, 129, 3, False, False)])
+def test_backward_launches_on_either_side_of_their_rules(nq, nkv, d, seq, mb, together, apart):
+    import ctypes
+    import paper_2410_13333_amd as mls
+    f, w = mls.lib()._ZN3mls16bwd_f32_togetherEiii, mls.lib()._ZN3mls27attn_bwd_f32_scratch_floatsEiiiii
+    f.restype, w.restype = ctypes.c_bool, ctypes.c_size_t
+    assert f(mb, seq, nq) is together and (w(mb, seq, nq, nkv, d) > 0) is apart
+    test_stage_fp32_against_the_exact_oracle(nq, nkv, d, seq, mb)
+
+
 @pytest.mark.parametrize("bad", [float("inf"), float("nan")])
 def test_a_non_finite_position_reaches_no_earlier_one(bad):
     import torch
