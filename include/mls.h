@@ -216,7 +216,7 @@ int mls_gemm_plan(int32_t mode, int64_t M, int64_t N, int64_t K, int64_t* big_co
 
 /* The same for the weight gradients of a layer in mls_stage_backward_ex over n_microbatches with these flags: the tile of the launch that all
  * four share, or 0 x 0 if each has launches of its own (then mls_gemm_plan with mode 2 and K = tokens of all micro-batches
- * tells their tiles; 16 micro-batches go into a launch).  bf16 storage; with fp32 storage the four always share one, and 0 x 0 is reported.
+ * tells their tiles; 16 micro-batches go into a launch) or they share one of 256x256 tiles (mls_stage_timing counts four then too).  bf16 storage; with fp32 storage the four always share one, and 0 x 0 is reported.
  * Errors: MLS_E_NULL, MLS_E_CONFIG, MLS_E_RANGE. */
 int mls_stage_wgrad_plan(const mls_config* cfg, int32_t n_microbatches, int32_t flags, int32_t* tile_rows, int32_t* tile_cols);
 

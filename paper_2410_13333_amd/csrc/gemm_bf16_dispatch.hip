@@ -244,45 +244,66 @@ hipError_t gemm_bf16_tn_segments(const void* const* A, const void* const* B, int
   if (M == 0 || N == 0 || nseg == 0 || kseg == 0) return hipSuccess;
   if (nseg > 16 || (gu_f > 0 && (gu_f % 8 || N != 2 * gu_width(gu_f)))) return hipErrorInvalidValue;
   const T16Problem p = tn_problem({A, B, C, M, N, lda, ldb, ldc, gu_f}, nseg, kseg, overwrite);
-  return run(p, st, [&](int n1, const SplitSpace*) {
-    return gemm_m16_tn_segments(A, B, nseg, C, M, n1, kseg, lda, ldb, ldc, p.ab, p.bb, st, gu_f, overwrite);
-  });
+  return run(p, st, [&](int n1, const SplitSpace*) { return gemm_m16_group(&p, &n1, 1, st); });
 }
 
 // One launch of one tile size for all of them, or a launch (or two) for each, by the same estimates.  Small layers win the
 // empty last rounds and the launches, large ones keep their whole rounds of 256x256 tiles.  The four weight gradients of a
 // layer, apart -> in one (us): hidden 256, 256 tokens 25 -> 9; 1024 / ffn 2728, 2000 tokens 112 -> 80; 768, 2 x 1024 tokens
-// 80 -> 45; 1536, 700 tokens 125 -> 97 (the fastest tile: 89); 512, 4 x 4096 tokens 387 -> 157; 3072, 600 tokens 422 -> 420;
-// 2048, 2 x 2048 tokens stay apart: 469, in one 517.
-int gemm_bf16_tn_group_tile(const TnProduct* p, int n, int nseg, int kseg, bool overwrite) {
+// 80 -> 45; 1536, 700 tokens 125 -> 97 (the fastest tile: 89); 512, 4 x 4096 tokens 387 -> 157; 3072, 600 tokens 422 -> 420.
+// 256x256 tiles: together their partly empty last rounds become one, and where that one would be nearly empty a product's last columns
+// that make it up go to smaller tiles (2048 / 5504, 2 x 2048 tokens: 776 tiles as 768 and 2048 x 256 columns on 64x64 ones; a step of that layer
+// 1 652 -> 1 602 us, hidden 5120 / 13824 over 2 x 4096 0.7 % faster; over 4 x 4096 tokens at 4096 / 11008, at the power limit, equal).
+TnGroupPlan gemm_bf16_tn_group_plan(const TnProduct* p, int n, int nseg, int kseg, bool overwrite) {
   const int64_t it = int64_t(nseg) * ((kseg + 63) / 64), depth = it * 64;
-  double apart = -LAUNCH_GAP;
-  for (int i = 0; i < n; i++)
-    if (p[i].M > 0 && p[i].N > 0) apart += LAUNCH_GAP + plan(T16_TN_SEGS, overwrite, p[i].M, p[i].N, depth).us;
-  int best = -1;
+  const Result res = overwrite ? R_F32_STORE : R_F32_ADD;
+  double least = -LAUNCH_GAP;
+  int64_t big = 0;
+  for (int i = 0; i < n; i++) {
+    if (p[i].M <= 0 || p[i].N <= 0) continue;
+    least += LAUNCH_GAP + plan(T16_TN_SEGS, overwrite, p[i].M, p[i].N, depth).us;
+    big += tiles_of(TILE_M16, p[i].M, p[i].N);
+  }
+  TnGroupPlan best = {false, -1, -1, 0, 0};
+  auto consider = [&](double t, const TnGroupPlan& g) {
+    if (t < least) least = t, best = g;
+  };
   for (int tile : {T16_256x128, T16_128x128, T16_128x64, T16_64x64}) {
     int64_t w = 0;
     for (int i = 0; i < n; i++) w += tiles_of(tile, p[i].M, p[i].N);
-    const double t = estimate(overwrite ? R_F32_STORE : R_F32_ADD, tile, w, it);
-    if (t < apart) {
-      apart = t;
-      best = tile;
-    }
+    consider(estimate(res, tile, w, it), {true, tile, -1, 0, 0});
+  }
+  if (big < 2 * CUS || it < 32) return best;  // (fewer or shorter ones are mostly epilogue, which smaller tiles overlap)
+  consider(estimate(res, TILE_M16, big, it), {true, -1, -1, 0, 0});
+  for (int i = 0; i < n; i++) {
+    if (p[i].M <= 0 || p[i].N <= 0) continue;
+    const int64_t tm = (p[i].M + 255) / 256, tn = (p[i].N + 255) / 256, drop = (big % CUS + tm - 1) / tm;  // tile columns that end the last round
+    if (drop < 1 || drop >= tn || big - drop * tm < CUS) continue;
+    const int n1 = int(tn - drop) * 256;
+    for (int rest : {T16_256x128, T16_128x128, T16_128x64, T16_64x64})
+      consider(estimate(res, TILE_M16, big - drop * tm, it) + LAUNCH_GAP + estimate(res, rest, p[i].M, p[i].N - n1, it), {true, -1, i, n1, rest});
   }
   return best;
 }
 
-hipError_t gemm_bf16_tn_group(const TnProduct* p, int n, int tile, int nseg, int kseg, hipStream_t st, bool overwrite, const Colsum& cs) {
+hipError_t gemm_bf16_tn_group(const TnProduct* p, int n, const TnGroupPlan& plan, int nseg, int kseg, hipStream_t st, bool overwrite, const Colsum& cs) {
   if (nseg == 0 || kseg == 0) return hipSuccess;
-  if (n < 1 || n > MAX_T16_GROUP || nseg > 16 || tile < 0) return hipErrorInvalidValue;
+  if (n < 1 || n > MAX_T16_GROUP || nseg > 16 || !plan.together) return hipErrorInvalidValue;
   T16Problem q[MAX_T16_GROUP];
-  int m = 0;
+  int n1[MAX_T16_GROUP], m = 0, split = -1;
   for (int i = 0; i < n; i++) {
     if (p[i].gu_f > 0 && (p[i].gu_f % 8 || p[i].N != 2 * gu_width(p[i].gu_f))) return hipErrorInvalidValue;
     if (p[i].M == 0 || p[i].N == 0) continue;
+    if (i == plan.split) split = m;
+    n1[m] = i == plan.split ? plan.n1 : p[i].N;
     q[m++] = tn_problem(p[i], nseg, kseg, overwrite);
   }
-  return m == 0 ? hipSuccess : gemm_t16_group(q, m, tile, st, cs);
+  if (m == 0) return hipSuccess;
+  if (plan.tile >= 0) return gemm_t16_group(q, m, plan.tile, st, cs);
+  if (hipError_t e = gemm_m16_group(q, n1, m, st, cs)) return e;
+  if (split < 0) return hipSuccess;
+  const T16Problem rest = columns_from(q[split], plan.n1);
+  return gemm_t16_group(&rest, 1, plan.rest, st);
 }
 
 bool gemm_swiglu_ok(int M, int f, int K, int64_t lda, int64_t ldw) {

@@ -63,11 +63,21 @@ enum { E_BF16 = 0, E_F32 = 1, E_SWIGLU = 2, E_ROPE = 3 };
 // than 4 for the [k][col] forms, 6 is 2 % slower for all: the requests then crowd into two rows).
 constexpr int ROW2 = 5;
 
-struct SegArgs {
+// The segmented form runs a list of problems in one launch, all over the same pieces, each with operands and a result of its own.
+struct SegProblem {
   const bf16_t* a[MAX_SEGS];
   const bf16_t* b[MAX_SEGS];
-  int nseg, kseg;
+  void* C;
+  int64_t lda, ldb, ldc;
+  uint32_t a_bytes, b_bytes;
+  int M, N, xf, tiles_m, tile0;  // tile0: its first tile in the launch
 };
+struct SegArgs {
+  int nseg, n;
+  SegProblem p[mls::MAX_T16_GROUP];
+  mls::Colsum cs;  // the last cs.wgs workgroups add columns up instead
+};
+struct NoSegs {};
 struct RopeArgs {
   const float* cos_tab;
   const float* sin_tab;
@@ -82,14 +92,36 @@ __device__ __forceinline__ constexpr int swz_kcol(int kr) { return ((kr & 3) << 
 
 template <bool ATR, bool BTR, int EPI, bool SEG, bool RAG, bool SPLIT>
 __global__ __launch_bounds__(NW * 64) void gemm16_kernel(const bf16_t* __restrict__ A, const bf16_t* __restrict__ B,
-                                                         void* __restrict__ Cv, const bf16_t* __restrict__ R, int M, int N,
-                                                         int K, int64_t lda, int64_t ldb, int64_t ldc, int64_t ldr,
-                                                         uint32_t a_bytes, uint32_t b_bytes, int tiles_m, int col0,
-                                                         void* __restrict__ Xv, int64_t ldx, int xf, SegArgs segs,
+                                                         void* __restrict__ C_, const bf16_t* __restrict__ R, int M_, int N_,
+                                                         int K, int64_t lda_, int64_t ldb_, int64_t ldc_, int64_t ldr,
+                                                         uint32_t a_bytes_, uint32_t b_bytes_, int tiles_m_, int col0,
+                                                         void* __restrict__ Xv, int64_t ldx, int xf_, std::conditional_t<SEG, SegArgs, NoSegs> segs,
                                                          RopeArgs rope, SplitArgs split) {
   extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
+  int nwg = gridDim.x, pid = blockIdx.x;
+  // the problem it belongs to; one after the other, so that all XCDs share its operands in the memory-side cache (each XCD with an eighth of
+  // the whole list: the step of a 7B layer shape 1 % slower than with launches apart)
+  void* Cv = C_;
+  int M = M_, N = N_, tiles_m = tiles_m_, xf = xf_, pr = 0, nseg = 1;
+  int64_t lda = lda_, ldb = ldb_, ldc = ldc_;
+  uint32_t a_bytes = a_bytes_, b_bytes = b_bytes_;
+  if constexpr (SEG) {
+    nwg -= segs.cs.wgs;
+    if (pid >= nwg) {
+      colsum_block(segs.cs, pid - nwg, reinterpret_cast<float*>(smem));
+      return;
+    }
+    nseg = segs.nseg;
+    while (pr + 1 < segs.n && pid >= segs.p[pr + 1].tile0) pr++;
+    const SegProblem& p = segs.p[pr];
+    Cv = p.C;
+    M = p.M; N = p.N; tiles_m = p.tiles_m; xf = p.xf;
+    lda = p.lda; ldb = p.ldb; ldc = p.ldc;
+    a_bytes = p.a_bytes; b_bytes = p.b_bytes;
+    nwg = (pr + 1 < segs.n ? segs.p[pr + 1].tile0 : nwg) - p.tile0;
+    pid -= p.tile0;
+  }
   // tile of this workgroup: each XCD gets a contiguous run of tiles, walked in groups of 4 tile rows, N fastest
-  const int nwg = gridDim.x, pid = blockIdx.x;
   const int xcd = pid & 7, q8 = nwg >> 3, rem = nwg & 7;
   int tile = xcd * q8 + (xcd < rem ? xcd : rem) + (pid >> 3), tiles = nwg, part = 0;
   if constexpr (SPLIT) {  // the first half of the workgroups takes the first half of the contraction
@@ -97,6 +129,8 @@ __global__ __launch_bounds__(NW * 64) void gemm16_kernel(const bf16_t* __restric
     part = tile / tiles;
     tile -= part * tiles;
   }
+  auto piece_a = [&](int i) { if constexpr (SEG) return segs.p[pr].a[i]; else return A; };
+  auto piece_b = [&](int i) { if constexpr (SEG) return segs.p[pr].b[i]; else return B; };
   const int gm = 4 < tiles_m ? 4 : tiles_m;
   const int per_group = gm * (tiles / tiles_m), grp = tile / per_group, first_m = grp * gm;
   const int gsz = min(tiles_m - first_m, gm), in_grp = tile - grp * per_group;
@@ -137,8 +171,8 @@ __global__ __launch_bounds__(NW * 64) void gemm16_kernel(const bf16_t* __restric
       gob[i] = n0 + r < N ? uint32_t((int64_t(n0 + r) * ldb + c * 8) * 2) : OOB;
     }
   }
-  const int tps = ((SEG ? segs.kseg : K) + (RAG ? BK - 1 : 0)) / BK;  // k-tiles per piece
-  int nk = (SEG ? segs.nseg : 1) * tps;
+  const int tps = (K + (RAG ? BK - 1 : 0)) / BK;  // k-tiles per piece
+  int nk = nseg * tps;
   if constexpr (SPLIT) {  // whole turns of the loop (four k-tiles); the descriptors start at the share's first k-tile
     static_assert(PAIR && PAIRB && !RAG, "both operands [row][k], whole pairs of k-tiles");
     const int kt0 = part ? (nk + 7) / 8 * 4 : 0;
@@ -150,8 +184,8 @@ __global__ __launch_bounds__(NW * 64) void gemm16_kernel(const bf16_t* __restric
   }
   const uint32_t ka = ATR ? uint32_t(lda * (BK * 2)) : BK * 2;  // byte step of one k-tile
   const uint32_t kb = BTR ? uint32_t(ldb * (BK * 2)) : BK * 2;
-  const i32x4 dead_a = make_rsrc(A, 0), dead_b = make_rsrc(B, 0);
-  i32x4 ra = make_rsrc(SEG ? segs.a[0] : A, a_bytes), rb = make_rsrc(SEG ? segs.b[0] : B, b_bytes);
+  const i32x4 dead_a = make_rsrc(piece_a(0), 0), dead_b = make_rsrc(piece_b(0), 0);
+  i32x4 ra = make_rsrc(piece_a(0), a_bytes), rb = make_rsrc(piece_b(0), b_bytes);
   int rq_tile = 0, rq_seg = 0, rq_in = 0;  // request cursor: next k-tile, its piece and its index inside the piece
   // request D of this wavefront for the cursor's k-tile into `stage`: D = 0..3 of A (unpaired form), 4..7 of B
   auto request = [&](int stage, auto DC) {
@@ -207,10 +241,10 @@ __global__ __launch_bounds__(NW * 64) void gemm16_kernel(const bf16_t* __restric
     if (SEG && rq_in == tps) {
       rq_in = 0;
       rq_seg++;
-      const int i = rq_seg < segs.nseg ? rq_seg : segs.nseg - 1;
-      const bool none = RAG && rq_seg >= segs.nseg;
-      ra = make_rsrc(segs.a[i], none ? 0 : a_bytes);
-      rb = make_rsrc(segs.b[i], none ? 0 : b_bytes);
+      const int i = rq_seg < nseg ? rq_seg : nseg - 1;
+      const bool none = RAG && rq_seg >= nseg;
+      ra = make_rsrc(piece_a(i), none ? 0 : a_bytes);
+      rb = make_rsrc(piece_b(i), none ? 0 : b_bytes);
     }
   };
 
@@ -553,18 +587,27 @@ hipError_t launch16_as(const bf16_t* A, const bf16_t* B, void* C, const bf16_t* 
                     int64_t ldb, int64_t ldc, int64_t ldr, uint32_t ab, uint32_t bb, hipStream_t st, const SegArgs* segs,
                     void* X, int64_t ldx, int xf, const RopeArgs* rope, const SplitSpace* split = nullptr) {
   auto kern = gemm16_kernel<ATR, BTR, EPI, SEG, RAG, SPLIT>;
-  SegArgs sa = {};
-  if (segs) sa = *segs;
   RopeArgs rp = {};
   if (rope) rp = *rope;
   static std::atomic<uint64_t> lds_raised{0};
   constexpr int LDS = BTR ? LDS_BYTES : LDS_BYTES_NT;
   if (hipError_t e = mls::raise_lds_limit(reinterpret_cast<const void*>(kern), LDS, lds_raised)) return e;
-  const int tm = (M + BM - 1) / BM, tn = (N + BN - 1) / BN;
   SplitArgs sp = {};
   if (SPLIT) sp = {split->sums, split->state, 2};
-  hipLaunchKernelGGL(kern, dim3(tm * tn * (SPLIT ? 2 : 1)), dim3(NW * 64), LDS, st, A, B, C, R, M, N, K, lda, ldb, ldc, ldr, ab, bb, tm,
-                     0, X, ldx, xf, sa, rp, sp);
+  if constexpr (SEG) {
+    SegArgs sa = *segs;
+    int tiles = 0;
+    for (int i = 0; i < sa.n; i++) {
+      sa.p[i].tiles_m = (sa.p[i].M + BM - 1) / BM;
+      sa.p[i].tile0 = tiles;
+      tiles += sa.p[i].tiles_m * ((sa.p[i].N + BN - 1) / BN);
+    }
+    hipLaunchKernelGGL(kern, dim3(tiles + sa.cs.wgs), dim3(NW * 64), LDS, st, A, B, C, R, M, N, K, lda, ldb, ldc, ldr, ab, bb, 0, 0, X, ldx, xf, sa, rp, sp);
+  } else {
+    const int tm = (M + BM - 1) / BM, tn = (N + BN - 1) / BN;
+    hipLaunchKernelGGL(kern, dim3(tm * tn * (SPLIT ? 2 : 1)), dim3(NW * 64), LDS, st, A, B, C, R, M, N, K, lda, ldb, ldc, ldr, ab, bb, tm,
+                       0, X, ldx, xf, NoSegs{}, rp, sp);
+  }
   return hipGetLastError();
 }
 
@@ -626,21 +669,31 @@ hipError_t gemm_m16_rope(const void* A, const void* W, void* C, int M, int N, in
   return launch16<false, false, E_ROPE, false>(a, w, C, nullptr, M, N, K, lda, ldw, ldc, 0, ab, bb, st, nullptr, nullptr, 0, 0, &ra, split);
 }
 
-// C[M, N] (+)= sum_i A_i[kseg, M]^T B_i[kseg, N] in fp32 over nseg <= 16 pieces, N a multiple of 256 or the whole problem;
-// gu_f > 0: interleaved gate/up columns go to their public places; overwrite: C =.
-hipError_t gemm_m16_tn_segments(const void* const* A, const void* const* B, int nseg, void* C, int M, int N, int kseg,
-                                int64_t lda, int64_t ldb, int64_t ldc, uint32_t ab, uint32_t bb, hipStream_t st, int gu_f,
-                                bool overwrite) {
-  if (nseg < 1 || nseg > MAX_SEGS) return hipErrorInvalidValue;
+// The leading n1[i] columns (a multiple of 256 or all) of each of n T16_TN_SEGS problems over pieces of the same number and depth, in one
+// launch; the column sums of cs go along.
+hipError_t gemm_m16_group(const T16Problem* p, const int* n1, int n, hipStream_t st, const Colsum& cs) {
+  if (n < 1 || n > MAX_T16_GROUP) return hipErrorInvalidValue;
   SegArgs sa = {};
-  for (int i = 0; i < nseg; i++) {
-    sa.a[i] = static_cast<const bf16_t*>(A[i]);
-    sa.b[i] = static_cast<const bf16_t*>(B[i]);
+  sa.nseg = p[0].nseg;
+  sa.cs = cs;
+  for (int i = 0; i < n; i++) {
+    const T16Problem& q = p[i];
+    if (q.form != T16_TN_SEGS || q.col0 != 0 || q.K != p[0].K || q.nseg != sa.nseg || q.ldx != p[0].ldx || q.nseg < 1 || q.nseg > MAX_SEGS || q.M <= 0 ||
+        n1[i] < 0 || n1[i] > q.N)
+      return hipErrorInvalidValue;
+    if (n1[i] == 0) continue;
+    SegProblem& g = sa.p[sa.n++];
+    for (int j = 0; j < q.nseg; j++) {
+      g.a[j] = static_cast<const bf16_t*>(q.seg_a[j]);
+      g.b[j] = static_cast<const bf16_t*>(q.seg_b[j]);
+    }
+    g.C = q.C;
+    g.lda = q.lda; g.ldb = q.ldb; g.ldc = q.ldc;
+    g.a_bytes = q.ab; g.b_bytes = q.bb;
+    g.M = q.M; g.N = n1[i]; g.xf = q.xf;
   }
-  sa.nseg = nseg;
-  sa.kseg = kseg;
-  return launch16<true, true, E_F32, true>(sa.a[0], sa.b[0], C, nullptr, M, N, kseg, lda, ldb, ldc, 0, ab, bb, st, &sa, nullptr,
-                                           overwrite ? 1 : 0, gu_f, nullptr);
+  if (sa.n == 0) return hipErrorInvalidValue;
+  return launch16<true, true, E_F32, true>(nullptr, nullptr, nullptr, nullptr, 0, 0, p[0].K, 0, 0, 0, 0, 0, 0, st, &sa, nullptr, p[0].ldx, 0, nullptr);
 }
 
 }  // namespace mls

@@ -84,11 +84,16 @@ struct TnProduct {
   int64_t lda, ldb, ldc;
   int gu_f;
 };
-// the tile (T16_*) of one launch for all of them, where their tiles together fill the chip better, or -1: a launch (or two)
-// for each is faster.  Host only.
-int gemm_bf16_tn_group_tile(const TnProduct* p, int n, int nseg, int kseg, bool overwrite);
+// How they run where one launch for all of them fills the chip better than a launch (or two) for each (together).  tile >= 0: all on tiles of
+// that size (T16_*); else 256x256 tiles but for the columns from n1 on of product `split` (if >= 0), which get tiles of size `rest` in a
+// launch of their own.  Host only.
+struct TnGroupPlan {
+  bool together;
+  int tile, split, n1, rest;
+};
+TnGroupPlan gemm_bf16_tn_group_plan(const TnProduct* p, int n, int nseg, int kseg, bool overwrite);
 // cs: column sums that go along in the same launch (not done if there is nothing to launch: no product, no piece)
-hipError_t gemm_bf16_tn_group(const TnProduct* p, int n, int tile, int nseg, int kseg, hipStream_t st, bool overwrite, const Colsum& cs = {});
+hipError_t gemm_bf16_tn_group(const TnProduct* p, int n, const TnGroupPlan& plan, int nseg, int kseg, hipStream_t st, bool overwrite, const Colsum& cs = {});
 // the 256x256 tiles of a problem on the 16x16x32 form of the matrix instruction (gemm_bf16_m16.hip); K % 8 == 0 where an
 // operand is stored [row][k], % 64 in the two fused forms
 hipError_t gemm_m16(int mode, const void* A, const void* B, void* C, const void* R, int M, int N, int K, int64_t lda,
@@ -98,9 +103,6 @@ hipError_t gemm_m16_swiglu(const void* A, const void* W, void* GU, void* Z, int 
 hipError_t gemm_m16_rope(const void* A, const void* W, void* C, int M, int N, int K, int64_t lda, int64_t ldw, int64_t ldc,
                          uint32_t ab, uint32_t bb, const float* cos_tab, const float* sin_tab, int seq, int rot_cols,
                          int head_dim, hipStream_t st, const SplitSpace* split = nullptr);
-hipError_t gemm_m16_tn_segments(const void* const* A, const void* const* B, int nseg, void* C, int M, int N, int kseg,
-                                int64_t lda, int64_t ldb, int64_t ldc, uint32_t ab, uint32_t bb, hipStream_t st, int gu_f,
-                                bool overwrite);
 // everything else on smaller tiles of the same instruction (gemm_bf16_t16.hip): any K (a multiple of 8 where an operand is
 // stored [row][k]).  The columns of B (for NN / TN from pointer B on, for NT from row 0 of B on) are columns col0 .. of C
 // (and R, X), which are not offset.
@@ -129,6 +131,8 @@ hipError_t gemm_t16(const T16Problem& p, int tile, hipStream_t st);
 // up to four T16_TN_SEGS problems over pieces of the same number and depth in one launch
 constexpr int MAX_T16_GROUP = 4;
 hipError_t gemm_t16_group(const T16Problem* p, int n, int tile, hipStream_t st, const Colsum& cs = {});
+// the leading n1[i] columns (a multiple of 256, possibly 0, or all) of such problems on 256x256 tiles in one launch
+hipError_t gemm_m16_group(const T16Problem* p, const int* n1, int n, hipStream_t st, const Colsum& cs = {});
 hipError_t fill_zero_f32(float* p, size_t n, hipStream_t st);
 // SwiGLU fused into the gate/up contraction (bf16, f % 32 == 0 here, DMA path).  Interleaved gate/up column order:
 // 32 gate columns, the 32 up columns of the same indices, and so on (gu_interleaved_col in common.h).

@@ -341,11 +341,11 @@ void weight_grads(const mls_stage* s, float* g, const std::vector<const void*> (
   }
 }
 
-// The tile of the launch that the four share over n <= 16 micro-batches, or -1: each has launches of its own
-int shared_wgrad_tile(const mls_stage* s, const mls::TnProduct (&p)[4], int n, bool overwrite) {
+// Whether and how the four share a launch over n <= 16 micro-batches (bf16 storage; fp32 storage always does, its own way)
+mls::TnGroupPlan wgrad_group(const mls_stage* s, const mls::TnProduct (&p)[4], int n, bool overwrite) {
   bool dma = s->dt == mls::DT_BF16;
   for (auto& w : p) dma = dma && mls::gemm_tn_segments_ok(s->T, w.lda, w.ldb);
-  return dma ? mls::gemm_bf16_tn_group_tile(p, 4, n, s->T, overwrite) : -1;
+  return dma ? mls::gemm_bf16_tn_group_plan(p, 4, n, s->T, overwrite) : mls::TnGroupPlan{false, -1, -1, 0, 0};
 }
 
 // C[M,N] += sum_i A_i[T,M]^T B_i[T,N] over n micro-batches (fp32 C) for each of them, in steps of 16 micro-batches: fp32 storage in one
@@ -365,9 +365,10 @@ int wgrad(mls_stage* s, const mls::TnProduct (&p)[4], int n, bool ow, const mls:
       LAUNCH(CLS_GEMM_TN, mls::gemm_f32_tn_group(q, 4, m, s->T, s->st, over, i == 0 ? cs : mls::Colsum{}));
       continue;
     }
-    const int tile = shared_wgrad_tile(s, q, m, over);
-    if (tile >= 0) {
-      LAUNCH(CLS_GEMM_TN, mls::gemm_bf16_tn_group(q, 4, tile, m, s->T, s->st, over, i == 0 ? cs : mls::Colsum{}));
+    const mls::TnGroupPlan plan = wgrad_group(s, q, m, over);
+    if (plan.together) {
+      LAUNCH(CLS_GEMM_TN, mls::gemm_bf16_tn_group(q, 4, plan, m, s->T, s->st, over, i == 0 ? cs : mls::Colsum{}));
+      if (s->tm.on && plan.tile < 0) s->tm.launches[CLS_GEMM_TN] += 3;  // (products of their own size, as where they run apart)
       continue;
     }
     for (auto& w : q) {
@@ -661,7 +662,7 @@ int mls_stage_backward_ex(mls_stage* s, const void* dY, float* grads, int32_t n,
     for (int i = 0; i < n; i++) have += k[i] > l;
     mls::TnProduct w[4];
     weight_grads(s, g, nullptr, w);
-    const bool shared = s->dt == mls::DT_FP32 || shared_wgrad_tile(s, w, have < 16 ? have : 16, ow) >= 0;
+    const bool shared = s->dt == mls::DT_FP32 || wgrad_group(s, w, have < 16 ? have : 16, ow).together;
     for (int i = 0; i < n; i++) {
       if (k[i] <= l) continue;
       seen++;
@@ -866,7 +867,7 @@ int mls_stage_wgrad_plan(const mls_config* cfg, int32_t n, int32_t flags, int32_
   layout(&tmp);
   mls::TnProduct p[4];
   weight_grads(&tmp, nullptr, nullptr, p);
-  const int tile = shared_wgrad_tile(&tmp, p, n < 16 ? n : 16, (flags & MLS_BWD_OVERWRITE) != 0);
+  const int tile = wgrad_group(&tmp, p, n < 16 ? n : 16, (flags & MLS_BWD_OVERWRITE) != 0).tile;
   *tile_rows = *tile_cols = 0;
   if (tile >= 0) mls::t16_tile_size(mls::T16_TN_SEGS, tile, *tile_rows, *tile_cols);
   return MLS_OK;

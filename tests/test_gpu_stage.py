@@ -598,3 +598,19 @@ def test_overwrite_equals_zeroing_where_the_two_run_on_different_tiles(hidden, n
         got.append(g)
     st.close()
     assert torch.equal(*got)
+
+
+@pytest.mark.parametrize("hidden,nq,nkv,d,ffn,seq,mb,n", [
+    (2048, 16, 16, 128, 5504, 700, 1, 3),    # 776 tiles of 256x256: whole rounds, a product's last columns on smaller tiles
+    (2056, 16, 8, 128, 5512, 2049, 1, 1),    # ragged rows, columns and pieces, gate/up columns with a last group that is not full
+    (3072, 24, 8, 128, 8192, 1088, 2, 1)])   # a last round that is kept
+def test_weight_gradients_that_share_a_launch_of_256x256_tiles(hidden, nq, nkv, d, ffn, seq, mb, n):
+    """They have no tile of their own to report, and more than two rounds of 256x256 ones (the rule for sharing them)."""
+    import paper_2410_13333_amd as mls
+    cfg = mls.MlsConfig(hidden, nq, nkv, d, ffn, seq, mb, 1, n, 1e-5, 10000.0, 0, 0)
+    assert mls.wgrad_plan(cfg, n) == mls.wgrad_plan(cfg, n, True) == (0, 0)
+    up = lambda v: -(-v // 256)  # noqa: E731
+    qd, qkv = nq * d, (nq + 2 * nkv) * d
+    tiles = up(ffn) * up(hidden) + up(hidden) * up(2 * -(-ffn // 32) * 32) + up(qd) * up(hidden) + up(hidden) * up(qkv)
+    assert tiles > 512 and n * -(-seq * mb // 64) >= 32
+    test_weight_gradients_of_a_layer_in_one_launch(hidden, nq, nkv, d, ffn, seq, mb, n)
