@@ -184,8 +184,8 @@ int mls_stage_debug_read(mls_stage* s, int32_t tensor_id, int32_t layer, int32_t
 /* Per-kernel-class timing with HIP events recorded on the stage's stream, for the benchmark's roofline figure.
  * enable != 0 brackets every step of forward/backward with a pair of events (no synchronisation unless more than
  * 4096 are pending) and counts it as one launch: a contraction of two tile sizes runs as two kernels and counts once,
- * the weight gradients of a layer count once where they share a kernel and once each where they do not; enable = 0
- * stops it.  mls_stage_timing_read synchronises on the last event, writes the accumulated milliseconds and launch counts
+ * the weight gradients of a layer count once where they share a kernel and once each where they do not or share one of 256x256 tiles;
+ * enable = 0 stops it.  mls_stage_timing_read synchronises on the last event, writes the accumulated milliseconds and launch counts
  * per class into two HOST arrays of MLS_TIMING_CLASSES entries (order: GEMM forward, GEMM data-gradient, GEMM
  * weight-gradient, attention forward, attention backward, RMSNorm, rotary, SwiGLU) and clears the accumulators.  A step
  * that runs fused into a neighbouring kernel is counted with that kernel's class and leaves its own class at zero: with bf16

@@ -1344,14 +1344,12 @@ namespace mls {
 
 // The forward on pairs of wavefronts pays where the longest chain of the other kernel decides, that is up to about one of its workgroups
 // (of 128 rows) per CU; with more of them the second load of every key block costs more than the balance gains.  us, other / pairs:
-//   d = 128: 64 workgroups 6.7 / 6.5 (128 positions), 160 14.5 / 13.0 (512), 240 17.7 / 16.2 (700), 320 45.7 / 36.1 (2048), 384 46.5 / 42.8
-//            (2048) but 17.7 / 20.9 (384), 512 52 / 56 (2048); of short rows it is the workgroups that cost: 192 10.2 / 11.3 (256), 8.5 / 9.9 (200)
-//   d = 64:  320 12.0 / 10.7 (600), 384 8.9 / 8.6 (200), 28.9 / 23.8 (2048), 448 10.3 / 12.3 (256), 14.9 / 14.7 (800), 512 32.0 / 32.0 (2048)
-// Up to 64 positions a pair has one block and nothing to share (48: 5.4 / 5.8).
-bool fwd_pairs(int b, int S, int nq, int d) {
-  const int64_t wgs = int64_t(b) * nq * ((S + 127) / 128);
-  return S > 64 && wgs <= (d == 64 ? 384 : S >= 384 ? 320 : 128);
-}
+//   d = 128: 160 workgroups 14.5 / 13.0 (512 positions), 240 17.7 / 16.2 (700), 320 45.7 / 36.1 (2048), 384 46.5 / 42.8 (2048) but
+//            17.7 / 20.9 (384), 512 52 / 56 (2048)
+//   d = 64:  320 12.0 / 10.7 (600), 384 11.3 / 9.7 (384), 28.9 / 23.8 (2048), 448 14.9 / 14.7 (800), 480 12.3 / 13.5 (384), 512 32.0 / 32.0 (2048)
+// Short sequences have short chains: the pairs gain half a microsecond on few workgroups (128 positions 6.7 / 6.5, 300 9.3 / 8.6) and lose one
+// on more (192 workgroups of 256 10.2 / 11.3, 256 of 256 10.3 / 11.6), so they stay with the other kernel.
+bool fwd_pairs(int b, int S, int nq, int d) { return S >= 384 && int64_t(b) * nq * ((S + 127) / 128) <= (d == 64 ? 384 : 320); }
 
 hipError_t attn_fwd_bf16(const void* qkv, int64_t ld_qkv, void* o, int64_t ld_o, float* lse, int b, int S, int nq, int nkv,
                          int d, hipStream_t st) {

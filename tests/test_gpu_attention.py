@@ -70,9 +70,9 @@ def test_attention_against_fp64_on_the_same_operands(nq, nkv, d, seq, mb, gain):
 # Which forward kernel a grid gets: pairs of wavefronts up to the number of workgroups where the other one wins.  Sequences around the
 # blocks of either, at the last size of the one and the first of the other.
 @pytest.mark.parametrize("nq,nkv,d,seq,mb,pairs", [
-    (3, 1, 64, 64, 2, False), (3, 1, 64, 65, 2, True), (2, 1, 128, 127, 1, True), (4, 4, 128, 193, 1, True), (48, 16, 64, 70, 8, True),
-    (48, 16, 64, 70, 9, False), (16, 16, 128, 97, 8, True), (16, 16, 128, 97, 9, False), (48, 16, 64, 161, 5, False),
-    (16, 4, 128, 300, 3, False), (20, 4, 128, 385, 4, True), (27, 9, 128, 385, 3, False)])
+    (3, 1, 64, 383, 2, False), (3, 1, 64, 384, 2, True), (2, 1, 128, 385, 1, True), (4, 4, 128, 447, 1, True), (2, 2, 64, 449, 1, True),
+    (2, 1, 64, 511, 1, True), (2, 1, 128, 577, 1, True), (32, 16, 64, 384, 4, True), (43, 43, 64, 384, 3, False), (20, 4, 128, 385, 4, True),
+    (27, 9, 128, 385, 3, False), (16, 4, 128, 300, 3, False)])
 def test_forward_kernels_on_either_side_of_their_rule(nq, nkv, d, seq, mb, pairs):
     import ctypes
     import paper_2410_13333_amd as mls
