@@ -322,6 +322,26 @@ hipError_t gemm_bf16_swiglu(const void* A, const void* W, void* GU, void* Z, int
   return run(p, st, [&](int n1, const SplitSpace* sp) { return gemm_m16_swiglu(A, W, GU, Z, M, n1, K, lda, ldw, ldgu, ldz, ab, wb, st, sp); });
 }
 
+// Not on 256x256 tiles, whose only wavefront per SIMD would move the three times as many bytes with the matrix cores idle; on the smaller ones
+// it saves a pass over dZ and a launch (hidden 1024, ffn 2728, 3 x 2000 tokens one by one 929 -> 919 us a step; 512, 1376, 500 tokens and the like
+// 1 to 4 %).
+bool gemm_dswiglu_ok(int M, int f, int K, int64_t lda, int64_t ldw, bool split) {
+  return f > 0 && f % 8 == 0 && gemm_bf16_dma_ok(GEMM_NT, M, f, K, lda, ldw) && plan(T16_NT, false, M, f, K, split).n1 == 0;
+}
+
+hipError_t gemm_bf16_dswiglu(const void* dY, const void* W, const void* GU, void* DGU, int M, int f, int K, int64_t lda, int64_t ldw,
+                             int64_t ldgu, int64_t lddgu, hipStream_t st, const SplitSpace& split) {
+  if (M == 0 || f == 0) return hipSuccess;
+  if (!gemm_dswiglu_ok(M, f, K, lda, ldw, split.sums != nullptr)) return hipErrorInvalidValue;
+  const Plan pl = plan(T16_NT, false, M, f, K, split.sums != nullptr);
+  T16Problem p = problem(T16_NT_DSWIGLU, dY, W, DGU, M, f, K, lda, ldw, lddgu, uint32_t(int64_t(M) * lda * 2), uint32_t(int64_t(f) * ldw * 2));
+  p.R = GU;
+  p.ldr = ldgu;
+  p.split = split;
+  p.parts = pl.parts;
+  return gemm_t16(p, pl.tile, st);
+}
+
 bool gemm_rope_ok(int M, int N, int K, int64_t lda, int64_t ldw, int seq, int rot_cols, int head_dim) {
   return (head_dim == 64 || head_dim == 128) && seq > 0 && rot_cols >= 0 && rot_cols <= N && rot_cols % head_dim == 0 &&
          N % head_dim == 0 && gemm_bf16_dma_ok(GEMM_NT, M, N, K, lda, ldw);

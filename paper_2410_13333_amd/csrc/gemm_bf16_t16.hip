@@ -38,7 +38,7 @@ namespace {
 constexpr int BK = 64;
 constexpr int MAX_SEGS = 16;
 
-enum { E_BF16 = 0, E_F32 = 1, E_SWIGLU = 2, E_ROPE = 3 };
+enum { E_BF16 = 0, E_F32 = 1, E_SWIGLU = 2, E_ROPE = 3, E_DSWIGLU = 4 };
 
 // The segmented form runs a list of problems in one launch (the weight gradients of a layer, whose tiles alone would each
 // leave most of a last round empty): all over the same pieces, each with operands and a result of its own.
@@ -292,6 +292,55 @@ __global__ __launch_bounds__(256, (Cfg<WTM, WTN, WGM, ATR, BTR, EPI, SEG, NS>::P
   if constexpr (EPI == E_F32) {
     // (ldx != 0 in this mode: store, do not accumulate)
     f32_results<WTM, WTN>(reinterpret_cast<float*>(Cv), ldc, int(crow0), M, int(ccol0), N, col0, xf, ldx == 0, c, lane, smem + wave * (1024 * WTN));
+  } else if constexpr (EPI == E_DSWIGLU) {
+    // The product is the gradient w.r.t. silu(gate) * up; C gets the gradients w.r.t. both, in the interleaved order of R = gate | up.  Each
+    // block of 16 rows passes through fp32 staging so that a lane has eight neighbouring columns: whole 64-byte pieces of gates and ups.
+    // All gates and ups are on their way before the first block is needed.  The product is rounded to bf16 first: the bits of the two
+    // kernels that run where 256x256 tiles take part.
+    constexpr int CH = 4 * WTN, C8 = 2 * WTN, RPI = 64 / C8, NP = 16 / RPI;  // 4-column chunks and 8-column pieces per row, rows per pass, passes
+    unsigned char* ws = smem + wave * (1024 * WTN);
+    bf16_t* C = reinterpret_cast<bf16_t*>(Cv);
+    const int c8 = lane % C8, r0 = lane / C8, n = int(ccol0) + c8 * 8;
+    const int64_t at = ((n >> 5) << 6) + (n & 31);  // of the gates; their ups 32 columns further on
+    uint4 g[WTM][NP], u[WTM][NP];
+#pragma unroll
+    for (int i = 0; i < WTM; i++)
+#pragma unroll
+      for (int q = 0; q < NP; q++) {
+        const int64_t row = crow0 + i * 16 + q * RPI + r0;
+        g[i][q] = u[i][q] = make_uint4(0, 0, 0, 0);
+        if (row < M && n < N) {
+          g[i][q] = *reinterpret_cast<const uint4*>(R + row * ldr + at);
+          u[i][q] = *reinterpret_cast<const uint4*>(R + row * ldr + at + 32);
+        }
+      }
+#pragma unroll
+    for (int i = 0; i < WTM; i++) {
+#pragma unroll
+      for (int j = 0; j < WTN; j++) *reinterpret_cast<f32x4*>(ws + l16 * (CH * 16) + (((j * 4 + g4) ^ (l16 & (CH - 1))) << 4)) = c[i][j];
+      wave_lds_sync();
+#pragma unroll
+      for (int q = 0; q < NP; q++) {
+        const int r = q * RPI + r0;
+        const int64_t row = crow0 + i * 16 + r;
+        const f32x4 lo = *reinterpret_cast<const f32x4*>(ws + r * (CH * 16) + (((2 * c8) ^ (r & (CH - 1))) << 4));
+        const f32x4 hi = *reinterpret_cast<const f32x4*>(ws + r * (CH * 16) + (((2 * c8 + 1) ^ (r & (CH - 1))) << 4));
+        float gv[8], uv[8], og[8], ou[8];
+        load8(reinterpret_cast<const bf16_t*>(&g[i][q]), gv);
+        load8(reinterpret_cast<const bf16_t*>(&u[i][q]), uv);
+#pragma unroll
+        for (int e = 0; e < 8; e++) {
+          const float d = round_bf16(e < 4 ? lo[e] : hi[e - 4]), s = sigmoidf_(gv[e]);
+          og[e] = d * uv[e] * s * (1.f + gv[e] * (1.f - s));
+          ou[e] = d * gv[e] * s;
+        }
+        if (row < M && n < N) {
+          store8(C + row * ldc + at, og);
+          store8(C + row * ldc + at + 32, ou);
+        }
+      }
+      wave_lds_sync();
+    }
   } else {
     // bf16 output through a per-wavefront staging area (16 rows x 16 WTN columns, 16-byte chunks XOR-swizzled by row) so
     // that the stores move whole rows.  The fused forms work on the fp32 accumulators first:
@@ -498,6 +547,7 @@ hipError_t gemm_t16(const T16Problem& p, int tile, hipStream_t st) {
     case T16_TN_SEGS: return gemm_t16_group(&p, 1, tile, st);
     case T16_NT_SWIGLU: return run<false, false, E_SWIGLU, false>(tile, a);
     case T16_NT_ROPE: return run<false, false, E_ROPE, false>(tile, a);
+    case T16_NT_DSWIGLU: return run<false, false, E_DSWIGLU, false>(tile, a);
   }
   return hipErrorInvalidValue;
 }

@@ -107,7 +107,7 @@ hipError_t gemm_m16_rope(const void* A, const void* W, void* C, int M, int N, in
 // stored [row][k]).  The columns of B (for NN / TN from pointer B on, for NT from row 0 of B on) are columns col0 .. of C
 // (and R, X), which are not offset.
 enum { T16_256x128 = 0, T16_128x128 = 1, T16_128x64 = 2, T16_64x64 = 3 };  // (the last two: 64x128 for the fused epilogues)
-enum { T16_NN, T16_NT, T16_TN, T16_TN_SEGS, T16_NT_SWIGLU, T16_NT_ROPE };
+enum { T16_NN, T16_NT, T16_TN, T16_TN_SEGS, T16_NT_SWIGLU, T16_NT_ROPE, T16_NT_DSWIGLU };
 struct T16Problem {
   int form;
   const void *A, *B;
@@ -141,6 +141,12 @@ hipError_t fill_zero_f32(float* p, size_t n, hipStream_t st);
 bool gemm_swiglu_ok(int M, int f, int K, int64_t lda, int64_t ldw);
 hipError_t gemm_bf16_swiglu(const void* A, const void* W, void* GU, void* Z, int M, int f, int K, int64_t lda,
                             int64_t ldw, int64_t ldgu, int64_t ldz, hipStream_t st, const SplitSpace& split = {});
+// The SwiGLU backward fused into the data gradient of the down-projection (bf16, f % 8 == 0, DMA path), where all of that product runs on
+// the smaller tiles (gemm_dswiglu_ok; host only): dZ[M, f] = dY[M,K] W[f,K]^T stays in registers,
+//   DGU[M, 2f] = (dZ up silu'(gate), dZ silu(gate)), GU and DGU in the interleaved order.
+bool gemm_dswiglu_ok(int M, int f, int K, int64_t lda, int64_t ldw, bool split);
+hipError_t gemm_bf16_dswiglu(const void* dY, const void* W, const void* GU, void* DGU, int M, int f, int K, int64_t lda, int64_t ldw,
+                             int64_t ldgu, int64_t lddgu, hipStream_t st, const SplitSpace& split = {});
 // The rotary embedding fused into the q|k|v projection (bf16, DMA path): C[M, N] = A[M,K] W[K,N] rounded to bf16, then
 // every head vector (head_dim = 64 or 128 columns) in the columns below rot_cols rotated by the angle of its row's
 // position row % seq, pairs (i, i + head_dim/2); cos_tab, sin_tab: [seq][head_dim/2] fp32.

@@ -305,8 +305,12 @@ int layer_backward_data(mls_stage* s, int layer, const char* x, const char* e, i
   char* dqkv = s->dqkv + size_t(w) * s->mb_qkv;
   // MLP
   // data gradients dX = dY W^T: W is the [row][k] operand
-  LAUNCH(CLS_GEMM_NT, gemm(s, mls::GEMM_NT, dy, s->param(layer, s->ioff_wd), s->dz, nullptr, T, f, hk, ld_dy, lh, lf));
-  LAUNCH(CLS_SWIGLU, mls::swiglu_bwd(s->dt, s->dz, lf, e + L.gu, lg, dgu, lg, T, f, s->st, s->fuse_gu));
+  if (s->fuse_gu && mls::gemm_dswiglu_ok(T, f, hk, ld_dy, lh, s->split.sums != nullptr)) {
+    LAUNCH(CLS_GEMM_NT, mls::gemm_bf16_dswiglu(dy, s->param(layer, s->ioff_wd), e + L.gu, dgu, T, f, hk, ld_dy, lh, lg, lg, s->st, s->split));
+  } else {
+    LAUNCH(CLS_GEMM_NT, gemm(s, mls::GEMM_NT, dy, s->param(layer, s->ioff_wd), s->dz, nullptr, T, f, hk, ld_dy, lh, lf));
+    LAUNCH(CLS_SWIGLU, mls::swiglu_bwd(s->dt, s->dz, lf, e + L.gu, lg, dgu, lg, T, f, s->st, s->fuse_gu));
+  }
   LAUNCH(CLS_GEMM_NT, gemm(s, mls::GEMM_NT, dgu, s->param(layer, s->ioff_wgu), s->dbuf, nullptr, T, h, gk, lg, lg, lh));
   LAUNCH(CLS_NORM, mls::rmsnorm_bwd(s->dt, s->dbuf, lh, e + L.h, lh, s->param(layer, s->ioff_g2), (const float*)(e + L.r2),
                                     dy, ld_dy, dh, lh, g + s->off_g2, s->partial2, T, h, s->st, ow, !first, false));

@@ -614,3 +614,36 @@ def test_weight_gradients_that_share_a_launch_of_256x256_tiles(hidden, nq, nkv, 
     tiles = up(ffn) * up(hidden) + up(hidden) * up(2 * -(-ffn // 32) * 32) + up(qd) * up(hidden) + up(hidden) * up(qkv)
     assert tiles > 512 and n * -(-seq * mb // 64) >= 32
     test_weight_gradients_of_a_layer_in_one_launch(hidden, nq, nkv, d, ffn, seq, mb, n)
+
+
+# hidden, ffn, tokens -> (columns on 256x256 tiles, parts there, tile rows, columns, parts) of the down-projection's data gradient
+DSWIGLU_TILES = [
+    ((72, 72, 65), (0, 1, 64, 64, 1)), ((2056, 72, 65), (0, 1, 64, 64, 3)), ((72, 1384, 2049), (0, 1, 128, 64, 1)),
+    ((4104, 680, 1000), (0, 1, 128, 64, 2)), ((520, 1384, 2049), (0, 1, 128, 128, 1)), ((4104, 8200, 65), (0, 1, 128, 128, 3)),
+    ((72, 2728, 2049), (0, 1, 256, 128, 1)), ((72, 8200, 2049), (7168, 1, 64, 64, 1))]
+
+
+@pytest.mark.parametrize("shape,plan", DSWIGLU_TILES)
+def test_swiglu_backward_on_every_plan(shape, plan):
+    """In the epilogue of the product on every smaller tile, whole and shared out; as a kernel of its own where 256x256 tiles take part.
+    The product is rounded to bf16, then the results: relative error below 2^-8 + 2^-8 in every element, a third of it in the norm."""
+    import torch
+    import paper_2410_13333_amd as mls
+    h, f, T = shape
+    st = mls.Stage(h, 2, 1, 64, f, T, 1, 1, 1, seed=1009)
+    assert mls.product_plan(st.cfg, 4) == plan
+    gen = torch.Generator(device="cuda").manual_seed(T)
+    x, dy = (torch.randn(1, T, h, device="cuda", generator=gen).to(torch.bfloat16) for _ in range(2))
+    g, dx = torch.zeros(st.grad_elems, device="cuda"), torch.empty_like(dy)
+    st.forward(x, 1, torch.empty_like(x))
+    gu = st.debug_read("gu").double()
+    st.backward(dy, g, 1, dx)
+    dgu = st.debug_read("dgu").double()
+    off, r, c = st.param_layout(0, "w_d")
+    w_d = st.get_params()[off:off + r * c].double().reshape(r, c)
+    dz = dy.double().reshape(T, h) @ w_d.t().contiguous()
+    st.close()
+    gate, up = gu[:, :f], gu[:, f:]
+    s = torch.sigmoid(gate)
+    assert worst_block(dgu[:, :f], dz * up * s * (1 + gate * (1 - s))) <= 6e-3
+    assert worst_block(dgu[:, f:], dz * gate * s) <= 6e-3
