@@ -9,9 +9,13 @@
 // registers one piece ahead of their MFMAs.  A lane's MFMA operand is one row (or column) at one k; the order of the
 // contraction is free as long as both operands agree, so the two lane halves take k-values 8g .. 8g+3 and 8g+4 .. 8g+7 and an
 // operand stored along k is read 16 bytes at a time.
-// Measured (us; straight from memory to registers -> through LDS): the products of a layer of hidden 512, ffn 1376 over 512
-// tokens: q|k|v and o (512 x 1024 and 512 x 512 x 512) 13.4 -> 9.8 and 9.4 -> 7.4, gate|up 36.3 -> 26.7, its data gradient 26.6 -> 22.5
-// and weight gradient 36.8 -> 27.8; 1000 x 4096 x 1024 123 -> 89.  The same bits.
+// The loop is issued in its written order: the LDS reads of the next piece go out between the MFMAs (64 clocks each), requests and what ends
+// inside a piece are branches that are the same for all lanes.  With reads first and every lane's address selected anew the matrix cores waited
+// some 130 instructions per piece.  us, before -> after, the same bits: 512 x 512 x 2752 21.0 -> 16.9, 96 x 512 x 2048 17.1 -> 12.2,
+// 1000 x 4096 x 1024 83 -> 73.5 (114 TFLOP/s; these MFMAs alone reach 131 to 137), weight gradient 1024 x 2752 over 1000 tokens 73 -> 59.  Deeper rings
+// (four pieces per wavefront, one workgroup per CU: 1000 x 4096 x 1024 77), three workgroups per CU and tiles dealt out by XCD gave nothing.
+#include <type_traits>
+
 #include "common.h"
 #include "kernels.h"
 
@@ -25,7 +29,7 @@ __device__ __forceinline__ void dma16g(const float* p, uint32_t lds_byte) {
 
 // One operand of a tile of 32 NT rows (of C's rows or columns): element (row, k) at base[row * ld + k] (ALONG_K; K a multiple
 // of 8, rows 16-byte aligned) or base[k * ld + row] (rows a multiple of 8).  A piece in LDS:
-//   ALONG_K   32 NT rows of 128 bytes, their 16-byte chunks permuted by row & 7
+//   ALONG_K   32 NT rows of 128 bytes, their 16-byte chunks permuted by (row >> 1) & 7
 //   else      32 k-rows of 32 NT floats; the two lane halves read rows four apart, which must not share banks: rows of 128 bytes
 //             change places with their neighbour where bit 2 of k is set, in rows of 256 bytes the halves do
 // A wavefront fetches the pieces at k0, k0 + stride, ... by requests q0 .. q0 + NQ - 1 (of 4 NT).  Their addresses move on by
@@ -44,7 +48,7 @@ struct Operand {
   int nseg = 1, seg = 0;
   __device__ __forceinline__ const float* place(int i, int lane, int k0_) const {
     const int s = (q0 + i) * RPQ + lane / CPR, c = lane % CPR;
-    if (ALONG_K) return base + int64_t(min(row0 + s, rows - 1)) * ld + min(k0_ + 4 * (c ^ (s & 7)), K - 4);
+    if (ALONG_K) return base + int64_t(min(row0 + s, rows - 1)) * ld + min(k0_ + 4 * (c ^ ((s >> 1) & 7)), K - 4);
     const int k = NT == 1 ? s ^ ((s >> 2) & 1) : s, col = 4 * (NT == 1 ? c : c ^ (((s >> 2) & 1) << 3));
     return base + int64_t(min(k0_ + k, K - 1)) * ld + min(row0 + col, rows - 4);
   }
@@ -64,30 +68,33 @@ struct Operand {
         for (int i = 0; i < NQ; i++) at[i] = place(i, lane, k0);
       }
     }
-    const bool whole = k0 + KC <= K;
+    if (k0 + KC <= K) {
 #pragma unroll
-    for (int i = 0; i < NQ; i++) {
-      dma16g(whole ? at[i] : place(i, lane, min(k0, K - 1)), lds + (q0 + i) * 1024);
-      at[i] += step;
+      for (int i = 0; i < NQ; i++) dma16g(at[i], lds + (q0 + i) * 1024);
+    } else {
+#pragma unroll
+      for (int i = 0; i < NQ; i++) dma16g(place(i, lane, min(k0, K - 1)), lds + (q0 + i) * 1024);
     }
+#pragma unroll
+    for (int i = 0; i < NQ; i++) at[i] += step;
     k0 += stride;
   }
-  // rows 32 t + l32 of the piece; left: k-values of it that exist
-  __device__ __forceinline__ static void read(const float* p, int t, int l32, int hf, int left, float (&f)[KC / 2]) {
+  // k-values 8 G + 4 hf .. + 3 of rows 32 t + l32 of the piece at p
+  template <int G>
+  __device__ __forceinline__ static void read(const float* p, int t, int l32, int hf, float (&f)[KC / 2]) {
+    const int k = 8 * G + 4 * hf;
+    if (ALONG_K) {
+      const float4 v = *reinterpret_cast<const float4*>(p + (t * 32 + l32) * 32 + (((2 * G + hf) ^ ((l32 >> 1) & 7)) << 2));
+      f[4 * G] = v.x; f[4 * G + 1] = v.y; f[4 * G + 2] = v.z; f[4 * G + 3] = v.w;
+    } else {
 #pragma unroll
-    for (int g = 0; g < KC / 8; g++) {
-      const int k = 8 * g + 4 * hf;
-      if (ALONG_K) {
-        const float4 v = *reinterpret_cast<const float4*>(p + (t * 32 + l32) * 32 + (((2 * g + hf) ^ (l32 & 7)) << 2));
-        f[4 * g] = v.x; f[4 * g + 1] = v.y; f[4 * g + 2] = v.z; f[4 * g + 3] = v.w;
-      } else {
-#pragma unroll
-        for (int j = 0; j < 4; j++) f[4 * g + j] = NT == 1 ? p[((k + j) ^ hf) * 32 + l32] : p[(k + j) * 64 + ((t ^ hf) * 32 + l32)];
-      }
-      if (left < KC)
-#pragma unroll
-        for (int j = 0; j < 4; j++) f[4 * g + j] = k + j < left ? f[4 * g + j] : 0.f;
+      for (int j = 0; j < 4; j++) f[4 * G + j] = NT == 1 ? p[((k + j) ^ hf) * 32 + l32] : p[(k + j) * 64 + ((t ^ hf) * 32 + l32)];
     }
+  }
+  // left: k-values of the piece that exist
+  __device__ __forceinline__ static void cut(int hf, int left, float (&f)[KC / 2]) {
+#pragma unroll
+    for (int e = 0; e < KC / 2; e++) f[e] = 8 * (e / 4) + 4 * hf + e % 4 < left ? f[e] : 0.f;
   }
 };
 
@@ -113,6 +120,20 @@ __device__ __forceinline__ f32x16 zero16() {
   return z;
 }
 
+// The products of one piece, in this order: two MFMAs, `between` (waits, the requests of a piece to come), the others with the LDS reads of the
+// next piece (eight groups, read(0) .. read(7)) in their shadow.  Operands swapped: a lane ends up with 4 consecutive columns of one row of C.
+template <class Between, class Read>
+__device__ __forceinline__ void products(f32x16& c, const float (&a)[KC / 2], const float (&b)[KC / 2], Between&& between, Read&& read) {
+  static_for<KC / 2>([&](auto Q) {
+    constexpr int q = decltype(Q)::value;
+    c = __builtin_amdgcn_mfma_f32_32x32x2f32(b[q], a[q], c, 0, 0, 0);
+    __builtin_amdgcn_sched_barrier(0);
+    if constexpr (q == 1) between();
+    if constexpr (q >= 2 && q < 10) read(std::integral_constant<int, q - 2>{});
+    __builtin_amdgcn_sched_barrier(0);
+  });
+}
+
 // A(m, k): AK ? A[m*lda + k] : A[k*lda + m]; B(k, n): BK ? B[n*ldb + k] : B[k*ldb + n].  add: C += instead of C =.
 // SEG: A and B are the first of nseg matrices each.
 struct Source {
@@ -123,18 +144,20 @@ struct Source {
   int nseg;
 };
 // Few tiles: one workgroup per 32x32 tile of C, wavefront w takes pieces w, w + 4, ... through NS stages of its own.
-template <bool AK, bool BK, bool SEG>
+template <bool AK, bool BK, bool SEG, int NS>
 __device__ __forceinline__ void tile32(float* smem, const Source& s, int m0, int n0, float* C, const float* R, int64_t ldc, int64_t ldr, int add) {
   const int M = s.M, N = s.N, K = s.K;
-  constexpr int STAGE = 2 * 32 * KC, NS = 2, NREQ = 8;
+  constexpr int STAGE = 2 * 32 * KC, NREQ = 8;
+  using OA = Operand<1, AK, SEG>;
+  using OB = Operand<1, BK, SEG>;
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), l32 = lane & 31, hf = lane >> 5;
-  Operand<1, AK, SEG> oa(s.A, s.lda, m0, M, K, wave * KC, 4 * KC, 0, lane);
-  Operand<1, BK, SEG> ob(s.B, s.ldb, n0, N, K, wave * KC, 4 * KC, 0, lane);
+  OA oa(s.A, s.lda, m0, M, K, wave * KC, 4 * KC, 0, lane);
+  OB ob(s.B, s.ldb, n0, N, K, wave * KC, 4 * KC, 0, lane);
   if constexpr (SEG) oa.list = s.a, ob.list = s.b, oa.nseg = ob.nseg = s.nseg;
   const float* mine = smem + wave * NS * STAGE;
   const uint32_t lds = (uint32_t)(uintptr_t)(MLS_LDS float*)(smem) + wave * NS * STAGE * 4;
-  auto request = [&](int piece) {
-    const uint32_t at = lds + (piece % NS) * STAGE * 4;
+  auto request = [&](int stage) {
+    const uint32_t at = lds + stage * STAGE * 4;
     oa.request(lane, at);
     ob.request(lane, at + STAGE * 2);
   };
@@ -142,34 +165,48 @@ __device__ __forceinline__ void tile32(float* smem, const Source& s, int m0, int
   const int each = (K + KC - 1) / KC, pieces = SEG ? each * s.nseg : each;
   const int n = (pieces - wave + 3) / 4;  // of this wavefront (0 if there are fewer than four)
   float a[2][KC / 2], b[2][KC / 2];
-  auto read = [&](int p, int set) {
-    const float* st = mine + (p % NS) * STAGE;
-    const int left = !SEG ? K - (p * 4 + wave) * KC : K % KC ? K - (p * 4 + wave) % each * KC : KC;
-    Operand<1, AK, SEG>::read(st, 0, l32, hf, left, a[set]);
-    Operand<1, BK, SEG>::read(st + STAGE / 2, 0, l32, hf, left, b[set]);
+  auto read = [&](auto I, int stage, int set) {
+    constexpr int i = decltype(I)::value;
+    const float* st = mine + stage * STAGE;
+    if constexpr (i % 2 == 0) OA::template read<i / 2>(st, 0, l32, hf, a[set]);
+    else OB::template read<i / 2>(st + STAGE / 2, 0, l32, hf, b[set]);
   };
-  auto step = [&](int p, int set) {  // the products of piece p; piece p + 1 is read meanwhile, p + 2 requested into its stage
-    if (p + 2 < n) request(p + 2);
-    if (p + 1 < n) {
-      if (p + 2 < n) wait_vmcnt<NREQ>(); else wait_vmcnt<0>();
-      read(p + 1, set ^ 1);
+  auto cut = [&](int p, int set) {
+    const int left = !SEG ? K - (p * 4 + wave) * KC : K % KC ? K - (p * 4 + wave) % each * KC : KC;
+    if (left < KC) {
+      OA::cut(hf, left, a[set]);
+      OB::cut(hf, left, b[set]);
     }
-    // operands swapped: a lane ends up with 4 consecutive columns of one row of C
-#pragma unroll
-    for (int q = 0; q < KC / 2; q++) acc = __builtin_amdgcn_mfma_f32_32x32x2f32(b[set][q], a[set][q], acc, 0, 0, 0);
-    wait_lgkm0();
   };
   if (n > 0) {
-    request(0);
-    if (n > 1) request(1);
-    if (n > 1) wait_vmcnt<NREQ>(); else wait_vmcnt<0>();
-    read(0, 0);
+#pragma unroll
+    for (int p = 0; p < NS; p++)
+      if (p < n) request(p);
+    if (n >= NS) wait_vmcnt<(NS - 1) * NREQ>(); else wait_vmcnt<0>();
+    static_for<8>([&](auto I) { read(I, 0, 0); });
     wait_lgkm0();
+    cut(0, 0);
   }
-  for (int p = 0; p < n; p += 2) {
-    step(p, 0);
-    if (p + 1 < n) step(p + 1, 1);
-  }
+  auto step = [&](int p, auto STAGE_OF_P) {  // the products of piece p; piece p + 1 is read meanwhile, p + NS requested into its stage
+    constexpr int stage = decltype(STAGE_OF_P)::value, set = stage & 1;
+    products(acc, a[set], b[set],
+             [&] {
+               wait_lgkm0();
+               if (p + NS < n) {
+                 request(stage);
+                 wait_vmcnt<(NS - 1) * NREQ>();
+               } else {
+                 wait_vmcnt<0>();
+               }
+             },
+             [&](auto I) { read(I, (stage + 1) % NS, set ^ 1); });  // (after the last piece: not used)
+    cut(p + 1, set ^ 1);
+  };
+  for (int p = 0; p < n; p += NS)
+    static_for<NS>([&](auto I) {
+      if (p + decltype(I)::value < n) step(p + decltype(I)::value, I);
+    });
+  wait_lgkm0();
   // wavefronts 2, 3 -> 0, 1; then 1 -> 0
   float(*part)[16][64] = reinterpret_cast<float(*)[16][64]>(smem);
   __syncthreads();
@@ -193,28 +230,38 @@ template <bool AK, bool BK, bool SEG>
 __device__ __forceinline__ void tile64(float* smem, const Source& s, int m0, int n0, float* C, const float* R, int64_t ldc, int64_t ldr, int add) {
   const int M = s.M, N = s.N, K = s.K;
   constexpr int STAGE = 2 * 64 * KC, NS = 4, NREQ = 4;
+  using OA = Operand<2, AK, SEG>;
+  using OB = Operand<2, BK, SEG>;
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), l32 = lane & 31, hf = lane >> 5;
   const int wm = wave & 1, wn = wave >> 1;
-  Operand<2, AK, SEG> oa(s.A, s.lda, m0, M, K, 0, KC, 2 * wave, lane);
-  Operand<2, BK, SEG> ob(s.B, s.ldb, n0, N, K, 0, KC, 2 * wave, lane);
+  OA oa(s.A, s.lda, m0, M, K, 0, KC, 2 * wave, lane);
+  OB ob(s.B, s.ldb, n0, N, K, 0, KC, 2 * wave, lane);
   if constexpr (SEG) oa.list = s.a, ob.list = s.b, oa.nseg = ob.nseg = s.nseg;
   const uint32_t lds = (uint32_t)(uintptr_t)(MLS_LDS float*)(smem);
   const int each = (K + KC - 1) / KC, pieces = SEG ? each * s.nseg : each;
-  auto request = [&](int piece) {  // (beyond the last one: its last k-value, so that the counts of the waits hold)
-    const uint32_t at = lds + (piece % NS) * STAGE * 4;
+  auto request = [&](int stage) {  // (beyond the last piece: its last k-value, so that the counts of the waits hold)
+    const uint32_t at = lds + stage * STAGE * 4;
     oa.request(lane, at);
     ob.request(lane, at + STAGE * 2);
   };
   f32x16 acc[4] = {zero16(), zero16(), zero16(), zero16()};
   if (pieces > 0) {
     float a[2][KC / 2], b[2][KC / 2];
-    auto read = [&](int p, int set) {
-      const float* st = smem + (p % NS) * STAGE;
+    auto read = [&](auto I, int stage, int set) {
+      constexpr int i = decltype(I)::value;
+      const float* st = smem + stage * STAGE;
+      if constexpr (i % 2 == 0) OA::template read<i / 2>(st, wm, l32, hf, a[set]);
+      else OB::template read<i / 2>(st + STAGE / 2, wn, l32, hf, b[set]);
+    };
+    auto cut = [&](int p, int set) {
       const int left = !SEG ? K - p * KC : K % KC ? K - p % each * KC : KC;
-      Operand<2, AK, SEG>::read(st, wm, l32, hf, left, a[set]);
-      Operand<2, BK, SEG>::read(st + STAGE / 2, wn, l32, hf, left, b[set]);
+      if (left < KC) {
+        OA::cut(hf, left, a[set]);
+        OB::cut(hf, left, b[set]);
+      }
     };
     auto sync = [&]() {  // the next piece is there for everyone, and everyone has read the one before it
+      wait_lgkm0();
       wait_vmcnt<(NS - 2) * NREQ>();
       __builtin_amdgcn_s_barrier();
       asm volatile("" ::: "memory");
@@ -223,24 +270,23 @@ __device__ __forceinline__ void tile64(float* smem, const Source& s, int m0, int
     for (int p = 0; p < NS - 1; p++) request(p);
     sync();
     request(NS - 1);
-    read(0, 0);
+    static_for<8>([&](auto I) { read(I, 0, 0); });
     wait_lgkm0();
-    auto step = [&](int p, f32x16& c, int set) {  // the products of piece p, while piece p + 1 is read
-      if (p + 1 < pieces) {
-        sync();
-        request(p + NS);
-        read(p + 1, set ^ 1);
-      }
-#pragma unroll
-      for (int q = 0; q < KC / 2; q++) c = __builtin_amdgcn_mfma_f32_32x32x2f32(b[set][q], a[set][q], c, 0, 0, 0);
-      wait_lgkm0();
+    cut(0, 0);
+    auto step = [&](int p, auto I) {  // the products of piece p, while piece p + 1 is read (after the last one: not used)
+      constexpr int i = decltype(I)::value, set = i & 1;
+      products(acc[i], a[set], b[set],
+               [&] {
+                 sync();
+                 request(i);
+               },
+               [&](auto J) { read(J, (i + 1) % NS, set ^ 1); });
+      cut(p + 1, set ^ 1);
     };
-    for (int p = 0; p < pieces; p += 4) {
-      step(p, acc[0], 0);
-      if (p + 1 < pieces) step(p + 1, acc[1], 1);
-      if (p + 2 < pieces) step(p + 2, acc[2], 0);
-      if (p + 3 < pieces) step(p + 3, acc[3], 1);
-    }
+    for (int p = 0; p < pieces; p += 4)
+      static_for<4>([&](auto I) {
+        if (p + decltype(I)::value < pieces) step(p + decltype(I)::value, I);
+      });
     wait_vmcnt<0>();
   }
 #pragma unroll
@@ -254,7 +300,7 @@ __global__ __launch_bounds__(256, 2) void gemm_f32_kernel(const float* __restric
   extern __shared__ __attribute__((aligned(1024))) float smem[];
   const Source s = {A, B, M, N, K, lda, ldb, nullptr, nullptr, 1};
   if constexpr (LARGE) tile64<AK, BK, false>(smem, s, blockIdx.y * 64, blockIdx.x * 64, C, R, ldc, ldr, add);
-  else tile32<AK, BK, false>(smem, s, blockIdx.y * 32, blockIdx.x * 32, C, R, ldc, ldr, add);
+  else tile32<AK, BK, false, 2>(smem, s, blockIdx.y * 32, blockIdx.x * 32, C, R, ldc, ldr, add);
 }
 
 // The weight gradients of a layer over all micro-batches of a call: C (+)= sum_i A_i^T B_i for each problem of a list, all over matrices of
@@ -286,7 +332,7 @@ __global__ __launch_bounds__(256, 2) void gemm_f32_tn_group_kernel(TnGroup g) {
   const int at = t - p.tile0, m = at / p.tiles_n, n = at - m * p.tiles_n;
   const Source s = {p.a[0], p.b[0], p.M, p.N, g.K, p.lda, p.ldb, p.a, p.b, g.nseg};
   if constexpr (LARGE) tile64<false, false, true>(smem, s, m * 64, n * 64, p.C, nullptr, p.ldc, 0, g.add);
-  else tile32<false, false, true>(smem, s, m * 32, n * 32, p.C, nullptr, p.ldc, 0, g.add);
+  else tile32<false, false, true, 2>(smem, s, m * 32, n * 32, p.C, nullptr, p.ldc, 0, g.add);
 }
 
 constexpr int LDS = 4 * 2 * 2 * 32 * KC * 4;  // of every form
