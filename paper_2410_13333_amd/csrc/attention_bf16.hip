@@ -1468,10 +1468,9 @@ hipError_t attn_fwd(int dt, const void* qkv, int64_t ld_qkv, void* o, int64_t ld
 hipError_t attn_bwd(int dt, const void* qkv, int64_t ld_qkv, const void* o, int64_t ld_o, const float* lse,
                     const void* d_o, int64_t ld_do, void* dqkv, int64_t ld_dqkv, float* delta, int b, int S, int nq,
                     int nkv, int d, hipStream_t st, float* part, const float* cos_tab, const float* sin_tab) {
-  if (dt != DT_BF16 && cos_tab) return hipErrorInvalidValue;  // only the bf16 kernels turn the rotation back themselves
   return dt == DT_BF16
              ? attn_bwd_bf16(qkv, ld_qkv, o, ld_o, lse, d_o, ld_do, dqkv, ld_dqkv, delta, b, S, nq, nkv, d, st, part, cos_tab, sin_tab)
-             : attn_bwd_f32(qkv, ld_qkv, o, ld_o, lse, d_o, ld_do, dqkv, ld_dqkv, delta, b, S, nq, nkv, d, st, part);
+             : attn_bwd_f32(qkv, ld_qkv, o, ld_o, lse, d_o, ld_do, dqkv, ld_dqkv, delta, b, S, nq, nkv, d, st, part, cos_tab, sin_tab);
 }
 
 }  // namespace mls

@@ -124,6 +124,37 @@ __device__ __forceinline__ void sum_waves(f32x16 (&acc)[DT], float (*part)[DT * 
         for (int e = 0; e < 16; e++) acc[t][e] += part[wave][t * 16 + e][lane];
   }
 }
+// Rotary tables; with them the backward turns dQ and dK back by the angle of their position as it stores them (cos null: not at all).
+struct Unrotate {
+  const float *cos_tab, *sin_tab;  // [S][d / 2]
+};
+// a row's two halves of H groups of eight features; group G of a transposed result is registers 4 (G % 4) .. of tile G / 4
+template <int H, int DT>
+__device__ __forceinline__ void unrotate_halves(f32x16 (&acc)[DT], const float* cs, const float* sn, int hf) {
+#pragma unroll
+  for (int g = 0; g < H; g++) {
+    const float4 c = *reinterpret_cast<const float4*>(cs + 8 * g + 4 * hf), n = *reinterpret_cast<const float4*>(sn + 8 * g + 4 * hf);
+    const float cv[4] = {c.x, c.y, c.z, c.w}, nv[4] = {n.x, n.y, n.z, n.w};
+#pragma unroll
+    for (int e = 0; e < 4; e++) {
+      const float x = acc[g / 4][4 * (g % 4) + e], y = acc[(g + H) / 4][4 * ((g + H) % 4) + e];
+      acc[g / 4][4 * (g % 4) + e] = x * cv[e] + y * nv[e];
+      acc[(g + H) / 4][4 * ((g + H) % 4) + e] = y * cv[e] - x * nv[e];
+    }
+  }
+}
+// acc *= mul, then rotated; d is 32 DT or 16 less
+template <int DT>
+__device__ __forceinline__ void unrotate(f32x16 (&acc)[DT], float mul, const Unrotate& un, int pos, int d, int hf) {
+#pragma unroll
+  for (int t = 0; t < DT; t++)
+#pragma unroll
+    for (int e = 0; e < 16; e++) acc[t][e] *= mul;
+  if (!un.cos_tab) return;
+  const float *cs = un.cos_tab + int64_t(pos) * (d >> 1), *sn = un.sin_tab + int64_t(pos) * (d >> 1);
+  if (d == 32 * DT) unrotate_halves<2 * DT, DT>(acc, cs, sn, hf);
+  else unrotate_halves<2 * DT - 1, DT>(acc, cs, sn, hf);
+}
 // store a transposed result (lane column = row `row` of the output): four consecutive features per group
 template <int DT>
 __device__ __forceinline__ void store_row(float* row, const f32x16 (&acc)[DT], float mul, int d, int hf) {
@@ -223,7 +254,7 @@ struct BwdLds {
 template <int DT, bool TOGETHER>
 __device__ __forceinline__ void dq_block(BwdLds<DT>& lds, int q0, int hq, int bi, const float* __restrict__ qkv, int64_t ld, const float* __restrict__ o,
                                          int64_t ldo, const float* __restrict__ lse, const float* __restrict__ d_o, int64_t ldd,
-                                         float* __restrict__ delta, float* __restrict__ dqkv, int64_t ldg, int S, int nq, int nkv, int d) {
+                                         float* __restrict__ delta, float* __restrict__ dqkv, int64_t ldg, int S, int nq, int nkv, int d, Unrotate un) {
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, l32 = lane & 31, hf = lane >> 5, hk = hq / (nq / nkv);
   const float* base = qkv + int64_t(bi) * S * ld;
   const float *K = base + int64_t(nq + hk) * d, *V = base + int64_t(nq + nkv + hk) * d;
@@ -259,7 +290,9 @@ __device__ __forceinline__ void dq_block(BwdLds<DT>& lds, int q0, int hq, int bi
     else accumulate_diagonal<DT>(acc, kc, s, K, ld, j0, S, d, l32, hf, lds.sp[wave], [&](int j) { return j <= qi; });
   }
   sum_waves<DT>(acc, lds.part, wave, lane);
-  if (wave == 0 && live) store_row<DT>(dqkv + (int64_t(bi) * S + qi) * ldg + int64_t(hq) * d, acc, sc, d, hf);
+  if (wave != 0 || !live) return;
+  unrotate<DT>(acc, sc, un, qi, d, hf);
+  store_row<DT>(dqkv + (int64_t(bi) * S + qi) * ldg + int64_t(hq) * d, acc, 1.f, d, hf);
 }
 
 // dK and dV of key rows j0 .. j0 + 31 from the query heads hq0 .. hq0 + heads - 1 of their group: the wavefronts share out the (head, query
@@ -268,7 +301,7 @@ template <int DT, bool TOGETHER>
 __device__ __forceinline__ void dkv_block(BwdLds<DT>& lds, int j0, int hq0, int heads, int bi, int nb_all, const float* __restrict__ qkv, int64_t ld,
                                           const float* __restrict__ o, int64_t ldo, const float* __restrict__ lse, const float* __restrict__ d_o,
                                           int64_t ldd, const float* __restrict__ delta, float* __restrict__ dqkv, int64_t ldg, int S, int nq,
-                                          int nkv, int d, float* __restrict__ part) {
+                                          int nkv, int d, float* __restrict__ part, Unrotate un) {
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, l32 = lane & 31, hf = lane >> 5, hk = hq0 / (nq / nkv);
   const float* base = qkv + int64_t(bi) * S * ld;
   const int ji = j0 + l32;
@@ -328,7 +361,8 @@ __device__ __forceinline__ void dkv_block(BwdLds<DT>& lds, int j0, int hq0, int 
     return;
   }
   float* out = dqkv + (int64_t(bi) * S + ji) * ldg;
-  store_row<DT>(out + int64_t(nq + hk) * d, dk, sc, d, hf);
+  unrotate<DT>(dk, sc, un, ji, d, hf);
+  store_row<DT>(out + int64_t(nq + hk) * d, dk, 1.f, d, hf);
   store_row<DT>(out + int64_t(nq + nkv + hk) * d, dv, 1.f, d, hf);
 }
 
@@ -338,47 +372,56 @@ template <int DT>
 __global__ __launch_bounds__(256) void attn_bwd_f32_kernel(const float* __restrict__ qkv, int64_t ld, const float* __restrict__ o, int64_t ldo,
                                                            const float* __restrict__ lse, const float* __restrict__ d_o, int64_t ldd,
                                                            float* __restrict__ dqkv, int64_t ldg, int b, int S, int nq, int nkv, int d,
-                                                           float* __restrict__ part) {
+                                                           float* __restrict__ part, Unrotate un) {
   __shared__ BwdLds<DT> lds;
   const int kv = part ? nq : nkv, per = (kv + nq) * b, rank = blockIdx.x / per, x = blockIdx.x % per / b, bi = blockIdx.x % b;
   const int heads = part ? 1 : nq / nkv;
-  if (x < kv) dkv_block<DT, true>(lds, rank * 32, x * heads, heads, bi, b, qkv, ld, o, ldo, lse, d_o, ldd, nullptr, dqkv, ldg, S, nq, nkv, d, part);
-  else dq_block<DT, true>(lds, ((S + 31) / 32 - 1 - rank) * 32, x - kv, bi, qkv, ld, o, ldo, lse, d_o, ldd, nullptr, dqkv, ldg, S, nq, nkv, d);
+  if (x < kv) dkv_block<DT, true>(lds, rank * 32, x * heads, heads, bi, b, qkv, ld, o, ldo, lse, d_o, ldd, nullptr, dqkv, ldg, S, nq, nkv, d, part, un);
+  else dq_block<DT, true>(lds, ((S + 31) / 32 - 1 - rank) * 32, x - kv, bi, qkv, ld, o, ldo, lse, d_o, ldd, nullptr, dqkv, ldg, S, nq, nkv, d, un);
 }
 // apart: grid as the forward's; and over (key blocks of 32, longest first; batch rows; KV heads)
 template <int DT>
 __global__ __launch_bounds__(256, DT <= 2 ? 2 : 1) void attn_dq_f32_kernel(const float* __restrict__ qkv, int64_t ld, const float* __restrict__ o, int64_t ldo,
                                                           const float* __restrict__ lse, const float* __restrict__ d_o, int64_t ldd,
                                                           float* __restrict__ delta, float* __restrict__ dqkv, int64_t ldg, int b, int S, int nq,
-                                                          int nkv, int d) {
+                                                          int nkv, int d, Unrotate un) {
   __shared__ BwdLds<DT> lds;
   dq_block<DT, false>(lds, ((S + 31) / 32 - 1 - blockIdx.x / nq / b) * 32, blockIdx.x % nq, blockIdx.x / nq % b, qkv, ld, o, ldo, lse, d_o, ldd, delta,
-                      dqkv, ldg, S, nq, nkv, d);
+                      dqkv, ldg, S, nq, nkv, d, un);
 }
 template <int DT>
 __global__ __launch_bounds__(256) void attn_dkv_f32_kernel(const float* __restrict__ qkv, int64_t ld, const float* __restrict__ lse,
                                                            const float* __restrict__ d_o, int64_t ldd, const float* __restrict__ delta,
-                                                           float* __restrict__ dqkv, int64_t ldg, int b, int S, int nq, int nkv, int d) {
+                                                           float* __restrict__ dqkv, int64_t ldg, int b, int S, int nq, int nkv, int d, Unrotate un) {
   __shared__ BwdLds<DT> lds;
   const int grp = nq / nkv;
   dkv_block<DT, false>(lds, blockIdx.x / nkv / b * 32, blockIdx.x % nkv * grp, grp, blockIdx.x / nkv % b, b, qkv, ld, nullptr, 0, lse, d_o, ldd, delta,
-                       dqkv, ldg, S, nq, nkv, d, nullptr);
+                       dqkv, ldg, S, nq, nkv, d, nullptr, un);
 }
-// dK and dV from the parts of the query heads of a group, in ascending order; a thread owns four features
+// dK and dV from the parts of the query heads of a group, in ascending order; a thread owns four features and the four half a head on
 __global__ __launch_bounds__(256) void gqa_reduce_f32_kernel(const float* __restrict__ part, int b, int S, int nq, int nkv, int d,
-                                                             float* __restrict__ dqkv, int64_t ldg) {
-  const int64_t id = int64_t(blockIdx.x) * 256 + threadIdx.x, whole = int64_t(b) * nkv * S * (d / 4);
+                                                             float* __restrict__ dqkv, int64_t ldg, Unrotate un) {
+  const int64_t id = int64_t(blockIdx.x) * 256 + threadIdx.x, whole = int64_t(b) * nkv * S * (d / 8);
   if (id >= 2 * whole) return;
-  const int what = id >= whole, grp = nq / nkv;
+  const int what = id >= whole, grp = nq / nkv, half = d / 2;
   const int64_t r = what ? id - whole : id;
-  const int c = int(r % (d / 4)) * 4, token = int(r / (d / 4) % S), hk = int(r / (d / 4) / S % nkv), bi = int(r / (d / 4) / S / nkv);
+  const int c = int(r % (d / 8)) * 4, token = int(r / (d / 8) % S), hk = int(r / (d / 8) / S % nkv), bi = int(r / (d / 8) / S / nkv);
   const float* p = part + (((int64_t(what) * b + bi) * nq + hk * grp) * S + token) * d + c;
-  float4 a = *reinterpret_cast<const float4*>(p);
+  auto at4 = [](const float* q) { return *reinterpret_cast<const float4*>(q); };
+  float4 x = at4(p), y = at4(p + half);
   for (int i = 1; i < grp; i++) {
-    const float4 v = *reinterpret_cast<const float4*>(p + int64_t(i) * S * d);
-    a.x += v.x; a.y += v.y; a.z += v.z; a.w += v.w;
+    const float4 u = at4(p + int64_t(i) * S * d), v = at4(p + int64_t(i) * S * d + half);
+    x.x += u.x; x.y += u.y; x.z += u.z; x.w += u.w;
+    y.x += v.x; y.y += v.y; y.z += v.z; y.w += v.w;
   }
-  *reinterpret_cast<float4*>(dqkv + (int64_t(bi) * S + token) * ldg + int64_t(nq + (what ? nkv : 0) + hk) * d + c) = a;
+  if (!what && un.cos_tab) {
+    const float4 cs = at4(un.cos_tab + int64_t(token) * half + c), sn = at4(un.sin_tab + int64_t(token) * half + c), u = x, v = y;
+    x = make_float4(u.x * cs.x + v.x * sn.x, u.y * cs.y + v.y * sn.y, u.z * cs.z + v.z * sn.z, u.w * cs.w + v.w * sn.w);
+    y = make_float4(v.x * cs.x - u.x * sn.x, v.y * cs.y - u.y * sn.y, v.z * cs.z - u.z * sn.z, v.w * cs.w - u.w * sn.w);
+  }
+  float* out = dqkv + (int64_t(bi) * S + token) * ldg + int64_t(nq + (what ? nkv : 0) + hk) * d + c;
+  *reinterpret_cast<float4*>(out) = x;
+  *reinterpret_cast<float4*>(out + half) = y;
 }
 
 template <class F>
@@ -416,24 +459,26 @@ size_t attn_bwd_f32_scratch_floats(int b, int S, int nq, int nkv, int d) {
 }
 
 hipError_t attn_bwd_f32(const void* qkv, int64_t ld_qkv, const void* o, int64_t ld_o, const float* lse, const void* d_o,
-                        int64_t ld_do, void* dqkv, int64_t ld_dqkv, float* delta, int b, int S, int nq, int nkv, int d, hipStream_t st, float* part) {
+                        int64_t ld_do, void* dqkv, int64_t ld_dqkv, float* delta, int b, int S, int nq, int nkv, int d, hipStream_t st, float* part,
+                        const float* cos_tab, const float* sin_tab) {
   if (b == 0 || S == 0 || nq == 0) return hipSuccess;
   if (!attn_bwd_f32_scratch_floats(b, S, nq, nkv, d)) part = nullptr;
   const unsigned n = unsigned((S + 31) / 32);
+  const Unrotate un = {cos_tab, sin_tab};
   return for_tiles(d, [&](auto DTC) {
     constexpr int DT = decltype(DTC)::value;
     if (!bwd_f32_together(b, S, nq)) {
       hipLaunchKernelGGL(attn_dq_f32_kernel<DT>, dim3(n * nq * b), dim3(256), 0, st, (const float*)qkv, ld_qkv, (const float*)o, ld_o, lse,
-                         (const float*)d_o, ld_do, delta, (float*)dqkv, ld_dqkv, b, S, nq, nkv, d);
+                         (const float*)d_o, ld_do, delta, (float*)dqkv, ld_dqkv, b, S, nq, nkv, d, un);
       hipLaunchKernelGGL(attn_dkv_f32_kernel<DT>, dim3(n * nkv * b), dim3(256), 0, st, (const float*)qkv, ld_qkv, lse, (const float*)d_o, ld_do, delta,
-                         (float*)dqkv, ld_dqkv, b, S, nq, nkv, d);
+                         (float*)dqkv, ld_dqkv, b, S, nq, nkv, d, un);
       return;
     }
     hipLaunchKernelGGL(attn_bwd_f32_kernel<DT>, dim3(n * ((part ? nq : nkv) + nq) * b), dim3(256), 0, st, (const float*)qkv, ld_qkv, (const float*)o,
-                       ld_o, lse, (const float*)d_o, ld_do, (float*)dqkv, ld_dqkv, b, S, nq, nkv, d, part);
+                       ld_o, lse, (const float*)d_o, ld_do, (float*)dqkv, ld_dqkv, b, S, nq, nkv, d, part, un);
     if (part)
-      hipLaunchKernelGGL(gqa_reduce_f32_kernel, dim3(unsigned((int64_t(2) * b * nkv * S * (d / 4) + 255) / 256)), dim3(256), 0, st, part, b, S, nq,
-                         nkv, d, (float*)dqkv, ld_dqkv);
+      hipLaunchKernelGGL(gqa_reduce_f32_kernel, dim3(unsigned((int64_t(2) * b * nkv * S * (d / 8) + 255) / 256)), dim3(256), 0, st, part, b, S, nq,
+                         nkv, d, (float*)dqkv, ld_dqkv, un);
   });
 }
 

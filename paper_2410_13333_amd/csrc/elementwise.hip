@@ -349,12 +349,11 @@ __global__ __launch_bounds__(256) void fill_zero_kernel(float4* __restrict__ p, 
   if (i < n4) p[i] = make_float4(0.f, 0.f, 0.f, 0.f);
 }
 
-// ---------------------------------------------------------------- rotary embedding, in place
+// ---------------------------------------------------------------- rotary embedding, in place (bf16 storage; fp32: in the product before it)
 // One thread rotates 8 pairs (i .. i+7, i+d/2 .. i+d/2+7) of one head of one token.
-template <typename T>
-__global__ __launch_bounds__(EW_THREADS) void rope_kernel(T* __restrict__ u, const float* __restrict__ cos_tab,
+__global__ __launch_bounds__(EW_THREADS) void rope_kernel(bf16_t* __restrict__ u, const float* __restrict__ cos_tab,
                                                           const float* __restrict__ sin_tab, int64_t total, int S,
-                                                          int n_heads, int d, int64_t ld, float sign) {
+                                                          int n_heads, int d, int64_t ld) {
   const int64_t id = int64_t(blockIdx.x) * EW_THREADS + threadIdx.x;
   if (id >= total) return;
   const int cph = d >> 4;  // chunks of 8 pairs per head
@@ -362,7 +361,7 @@ __global__ __launch_bounds__(EW_THREADS) void rope_kernel(T* __restrict__ u, con
   const int head = int((id / cph) % n_heads);
   const int64_t t = id / (int64_t(cph) * n_heads);
   const int pos = int(t % S);
-  T* p = u + t * ld + head * d + c * 8;
+  bf16_t* p = u + t * ld + head * d + c * 8;
   float a[8], b[8], cs[8], sn[8], oa[8], ob[8];
   load8(p, a);
   load8(p + (d >> 1), b);
@@ -370,19 +369,17 @@ __global__ __launch_bounds__(EW_THREADS) void rope_kernel(T* __restrict__ u, con
   load8(sin_tab + int64_t(pos) * (d >> 1) + c * 8, sn);
 #pragma unroll
   for (int e = 0; e < 8; e++) {
-    const float s = sign * sn[e];
-    oa[e] = a[e] * cs[e] - b[e] * s;
-    ob[e] = a[e] * s + b[e] * cs[e];
+    oa[e] = a[e] * cs[e] - b[e] * sn[e];
+    ob[e] = a[e] * sn[e] + b[e] * cs[e];
   }
   store8(p, oa);
   store8(p + (d >> 1), ob);
 }
 
-// ---------------------------------------------------------------- SwiGLU
+// ---------------------------------------------------------------- SwiGLU (bf16 storage; fp32: epilogues of the products)
 
-template <typename T>
-__global__ __launch_bounds__(EW_THREADS) void swiglu_fwd_kernel(const T* __restrict__ gu, int64_t ld_gu,
-                                                                T* __restrict__ z, int64_t ld_z, int64_t total,
+__global__ __launch_bounds__(EW_THREADS) void swiglu_fwd_kernel(const bf16_t* __restrict__ gu, int64_t ld_gu,
+                                                                bf16_t* __restrict__ z, int64_t ld_z, int64_t total,
                                                                 int f) {
   const int64_t id = int64_t(blockIdx.x) * EW_THREADS + threadIdx.x;
   if (id >= total) return;
@@ -398,10 +395,10 @@ __global__ __launch_bounds__(EW_THREADS) void swiglu_fwd_kernel(const T* __restr
 }
 
 // IL: gu and dgu are in the interleaved gate/up column order (32 gates, their 32 ups, ...), else [gates | ups]
-template <typename T, bool IL>
-__global__ __launch_bounds__(EW_THREADS) void swiglu_bwd_kernel(const T* __restrict__ dz, int64_t ld_dz,
-                                                                const T* __restrict__ gu, int64_t ld_gu,
-                                                                T* __restrict__ dgu, int64_t ld_dgu, int64_t total,
+template <bool IL>
+__global__ __launch_bounds__(EW_THREADS) void swiglu_bwd_kernel(const bf16_t* __restrict__ dz, int64_t ld_dz,
+                                                                const bf16_t* __restrict__ gu, int64_t ld_gu,
+                                                                bf16_t* __restrict__ dgu, int64_t ld_dgu, int64_t total,
                                                                 int f) {
   const int64_t id = int64_t(blockIdx.x) * EW_THREADS + threadIdx.x;
   if (id >= total) return;
@@ -619,45 +616,28 @@ hipError_t fill_zero_f32(float* p, size_t n, hipStream_t st) {
   return hipGetLastError();
 }
 
-hipError_t rope_inplace(int dt, void* u, const float* cos_tab, const float* sin_tab, int T, int S, int n_heads, int d,
-                        int64_t ld, float sign, hipStream_t st) {
+hipError_t rope_inplace(void* u, const float* cos_tab, const float* sin_tab, int T, int S, int n_heads, int d, int64_t ld, hipStream_t st) {
   const int64_t total = int64_t(T) * n_heads * (d >> 4);
   if (total == 0) return hipSuccess;
-  if (dt == DT_BF16)
-    hipLaunchKernelGGL(rope_kernel<bf16_t>, dim3(blocks_for(total)), dim3(EW_THREADS), 0, st, (bf16_t*)u, cos_tab,
-                       sin_tab, total, S, n_heads, d, ld, sign);
-  else
-    hipLaunchKernelGGL(rope_kernel<float>, dim3(blocks_for(total)), dim3(EW_THREADS), 0, st, (float*)u, cos_tab,
-                       sin_tab, total, S, n_heads, d, ld, sign);
+  hipLaunchKernelGGL(rope_kernel, dim3(blocks_for(total)), dim3(EW_THREADS), 0, st, (bf16_t*)u, cos_tab, sin_tab, total, S, n_heads, d, ld);
   return hipGetLastError();
 }
 
-hipError_t swiglu_fwd(int dt, const void* gu, int64_t ld_gu, void* z, int64_t ld_z, int T, int f, hipStream_t st) {
+hipError_t swiglu_fwd(const void* gu, int64_t ld_gu, void* z, int64_t ld_z, int T, int f, hipStream_t st) {
   const int64_t total = int64_t(T) * (f >> 3);
   if (total == 0) return hipSuccess;
-  if (dt == DT_BF16)
-    hipLaunchKernelGGL(swiglu_fwd_kernel<bf16_t>, dim3(blocks_for(total)), dim3(EW_THREADS), 0, st, (const bf16_t*)gu,
-                       ld_gu, (bf16_t*)z, ld_z, total, f);
-  else
-    hipLaunchKernelGGL(swiglu_fwd_kernel<float>, dim3(blocks_for(total)), dim3(EW_THREADS), 0, st, (const float*)gu,
-                       ld_gu, (float*)z, ld_z, total, f);
+  hipLaunchKernelGGL(swiglu_fwd_kernel, dim3(blocks_for(total)), dim3(EW_THREADS), 0, st, (const bf16_t*)gu, ld_gu, (bf16_t*)z, ld_z, total, f);
   return hipGetLastError();
 }
 
-hipError_t swiglu_bwd(int dt, const void* dz, int64_t ld_dz, const void* gu, int64_t ld_gu, void* dgu, int64_t ld_dgu,
-                      int T, int f, hipStream_t st, bool interleaved) {
+hipError_t swiglu_bwd(const void* dz, int64_t ld_dz, const void* gu, int64_t ld_gu, void* dgu, int64_t ld_dgu, int T, int f, hipStream_t st,
+                      bool interleaved) {
   const int64_t total = int64_t(T) * (f >> 3);
   if (total == 0) return hipSuccess;
-  if (interleaved && (dt != DT_BF16 || f % 8)) return hipErrorInvalidValue;
-  if (interleaved)
-    hipLaunchKernelGGL((swiglu_bwd_kernel<bf16_t, true>), dim3(blocks_for(total)), dim3(EW_THREADS), 0, st,
-                       (const bf16_t*)dz, ld_dz, (const bf16_t*)gu, ld_gu, (bf16_t*)dgu, ld_dgu, total, f);
-  else if (dt == DT_BF16)
-    hipLaunchKernelGGL((swiglu_bwd_kernel<bf16_t, false>), dim3(blocks_for(total)), dim3(EW_THREADS), 0, st,
-                       (const bf16_t*)dz, ld_dz, (const bf16_t*)gu, ld_gu, (bf16_t*)dgu, ld_dgu, total, f);
-  else
-    hipLaunchKernelGGL((swiglu_bwd_kernel<float, false>), dim3(blocks_for(total)), dim3(EW_THREADS), 0, st,
-                       (const float*)dz, ld_dz, (const float*)gu, ld_gu, (float*)dgu, ld_dgu, total, f);
+  if (interleaved && f % 8) return hipErrorInvalidValue;
+  auto kern = interleaved ? swiglu_bwd_kernel<true> : swiglu_bwd_kernel<false>;
+  hipLaunchKernelGGL(kern, dim3(blocks_for(total)), dim3(EW_THREADS), 0, st, (const bf16_t*)dz, ld_dz, (const bf16_t*)gu, ld_gu, (bf16_t*)dgu,
+                     ld_dgu, total, f);
   return hipGetLastError();
 }
 

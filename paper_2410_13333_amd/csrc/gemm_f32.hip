@@ -23,6 +23,30 @@ namespace {
 
 constexpr int KC = 32;  // contraction depth of one piece: whole 128-byte lines of an operand stored along k
 
+// What becomes of a product: stored (+ R, += ); gate|up, whose SwiGLU is stored besides; q|k|v, whose q and k heads are rotated; dZ of
+// the down-projection, which stays in registers, its SwiGLU backward stored.
+enum { E_STORE, E_SWIGLU, E_ROPE, E_DSWIGLU };
+constexpr bool paired(int epi) { return epi == E_SWIGLU || epi == E_ROPE; }
+struct Epilogue {
+  float* X;            // Z (E_SWIGLU)
+  const float *cos_tab, *sin_tab;
+  int64_t ldx;
+  int half;            // columns between the two of a pair: ffn, or half a head
+  int seq, rot_cols;
+};
+// Where column r of a tile whose first column is n0 lies in C if its columns come in pairs half apart: eight first ones, then their eight
+// partners, so that both of a pair end up in one lane (n0: a multiple of 16, half: of 8).  N: all columns, which the last ones repeat.  GROUPS:
+// more than one pair of halves.
+struct PairedCol {
+  int group, at;  // the pair of halves and the column in its first one
+  __device__ __forceinline__ int first(int half) const { return group * 2 * half + at; }
+};
+template <bool GROUPS>
+__device__ __forceinline__ PairedCol paired_col(int n0, int r, int half, int N) {
+  const int p = min((n0 + r) >> 4, (N >> 4) - 1), w = half >> 3, group = GROUPS ? p / w : 0;  // p: its eight pairs
+  return {group, 8 * (p - group * w) + (r & 7)};
+}
+
 __device__ __forceinline__ void dma16g(const float* p, uint32_t lds_byte) {
   asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dwordx4 %1, off" ::"s"(lds_byte), "v"(p) : "memory");
 }
@@ -36,13 +60,14 @@ __device__ __forceinline__ void dma16g(const float* p, uint32_t lds_byte) {
 // additions; only a last piece that is not whole forms them anew, and the first one of another matrix: with SEG the contraction runs on
 // through nseg matrices of depth K each (list), every one of which ends with a piece of its own.
 // Rows beyond the end repeat the last ones (their results are not stored); so do k-values, and `read` zeroes those.
-template <int NT, bool ALONG_K, bool SEG>
+// EPI, if paired (not ALONG_K): its columns in the order of paired_col.
+template <int NT, bool ALONG_K, bool SEG, int EPI = E_STORE>
 struct Operand {
   static constexpr int CPR = ALONG_K ? 8 : 8 * NT, RPQ = 64 / CPR;  // chunks per row, rows per request
   static constexpr int NQ = NT == 1 ? 4 : 2;  // requests of a wavefront per piece: all, or its share of the workgroup's
   const float* base;
   int64_t ld, step;
-  int row0, rows, K, k0, stride, q0;
+  int row0, rows, K, k0, stride, q0, half;
   const float* at[NQ];
   const float* const* list = nullptr;
   int nseg = 1, seg = 0;
@@ -50,10 +75,12 @@ struct Operand {
     const int s = (q0 + i) * RPQ + lane / CPR, c = lane % CPR;
     if (ALONG_K) return base + int64_t(min(row0 + s, rows - 1)) * ld + min(k0_ + 4 * (c ^ ((s >> 1) & 7)), K - 4);
     const int k = NT == 1 ? s ^ ((s >> 2) & 1) : s, col = 4 * (NT == 1 ? c : c ^ (((s >> 2) & 1) << 3));
-    return base + int64_t(min(k0_ + k, K - 1)) * ld + min(row0 + col, rows - 4);
+    const float* at_k = base + int64_t(min(k0_ + k, K - 1)) * ld;
+    if constexpr (paired(EPI)) return at_k + (paired_col<EPI == E_ROPE>(row0, col, half, rows).first(half) + ((col >> 3) & 1) * half);
+    else return at_k + min(row0 + col, rows - 4);
   }
-  __device__ __forceinline__ Operand(const float* base_, int64_t ld_, int row0_, int rows_, int K_, int k0_, int stride_, int q0_, int lane)
-      : base(base_), ld(ld_), step(ALONG_K ? stride_ : stride_ * ld_), row0(row0_), rows(rows_), K(K_), k0(k0_), stride(stride_), q0(q0_) {
+  __device__ __forceinline__ Operand(const float* base_, int64_t ld_, int row0_, int rows_, int K_, int k0_, int stride_, int q0_, int lane, int half_ = 8)
+      : base(base_), ld(ld_), step(ALONG_K ? stride_ : stride_ * ld_), row0(row0_), rows(rows_), K(K_), k0(k0_), stride(stride_), q0(q0_), half(half_) {
 #pragma unroll
     for (int i = 0; i < NQ; i++) at[i] = place(i, lane, k0);
   }
@@ -98,19 +125,77 @@ struct Operand {
   }
 };
 
-// ---- C (+ R, += ) of a 32x32 MFMA tile whose lane holds 4 consecutive columns of row l32
+// ---- the results of a 32x32 MFMA tile whose lane holds 4 consecutive columns of row l32 four times, 8 apart
+template <int EPI>
 __device__ __forceinline__ void store_tile(const f32x16& acc, float* C, const float* R, int row, int col0, int M, int N, int64_t ldc,
-                                           int64_t ldr, int add, int hf) {
+                                           int64_t ldr, int add, int hf, const Epilogue& ep) {
   if (row >= M) return;
+  auto at4 = [](float* p) { return reinterpret_cast<float4*>(p); };
+  auto get4 = [](const float* p, float (&v)[4]) {
+    const float4 x = *reinterpret_cast<const float4*>(p);
+    v[0] = x.x; v[1] = x.y; v[2] = x.z; v[3] = x.w;
+  };
+  if constexpr (paired(EPI)) {
+#pragma unroll
+    for (int g = 0; g < 4; g += 2) {
+      if (col0 + 8 * g >= N) continue;  // N is a multiple of 16 here
+      const PairedCol pc = paired_col<EPI == E_ROPE>(col0, 8 * g + 4 * hf, ep.half, N);
+      const int first = pc.first(ep.half);
+      float a[4], b[4];
+#pragma unroll
+      for (int e = 0; e < 4; e++) a[e] = acc[4 * g + e], b[e] = acc[4 * g + 4 + e];
+      float* c = C + int64_t(row) * ldc + first;
+      if constexpr (EPI == E_SWIGLU) {
+        float z[4];
+#pragma unroll
+        for (int e = 0; e < 4; e++) z[e] = a[e] * sigmoidf_(a[e]) * b[e];
+        *at4(ep.X + int64_t(row) * ep.ldx + first) = make_float4(z[0], z[1], z[2], z[3]);
+      } else if (first < ep.rot_cols) {
+        const int64_t t = int64_t(row % ep.seq) * ep.half + pc.at;
+        float cs[4], sn[4];
+        get4(ep.cos_tab + t, cs);
+        get4(ep.sin_tab + t, sn);
+#pragma unroll
+        for (int e = 0; e < 4; e++) {
+          const float u = a[e], v = b[e];
+          a[e] = u * cs[e] - v * sn[e];
+          b[e] = u * sn[e] + v * cs[e];
+        }
+      }
+      *at4(c) = make_float4(a[0], a[1], a[2], a[3]);
+      *at4(c + ep.half) = make_float4(b[0], b[1], b[2], b[3]);
+    }
+    return;
+  }
+  float gate[4][4], up[4][4];
+  if constexpr (EPI == E_DSWIGLU)
+#pragma unroll
+    for (int g = 0; g < 4; g++) {  // all on their way together
+      const float* p = R + int64_t(row) * ldr + min(col0 + 8 * g + 4 * hf, N - 4);
+      get4(p, gate[g]);
+      get4(p + ep.half, up[g]);
+    }
 #pragma unroll
   for (int g = 0; g < 4; g++) {
     const int col = col0 + 8 * g + 4 * hf;  // N is a multiple of 8: groups of four are whole
     if (col >= N) continue;
-    float4* c = reinterpret_cast<float4*>(C + int64_t(row) * ldc + col);
-    float4 o = make_float4(0.f, 0.f, 0.f, 0.f);
-    if (add) o = *c;
-    else if (R) o = *reinterpret_cast<const float4*>(R + int64_t(row) * ldr + col);
-    *c = make_float4(acc[4 * g] + o.x, acc[4 * g + 1] + o.y, acc[4 * g + 2] + o.z, acc[4 * g + 3] + o.w);
+    float* c = C + int64_t(row) * ldc + col;
+    if constexpr (EPI == E_DSWIGLU) {
+      float dg[4], du[4];
+#pragma unroll
+      for (int e = 0; e < 4; e++) {
+        const float d = acc[4 * g + e], sg = sigmoidf_(gate[g][e]);
+        dg[e] = d * up[g][e] * sg * (1.f + gate[g][e] * (1.f - sg));
+        du[e] = d * gate[g][e] * sg;
+      }
+      *at4(c) = make_float4(dg[0], dg[1], dg[2], dg[3]);
+      *at4(c + ep.half) = make_float4(du[0], du[1], du[2], du[3]);
+      continue;
+    }
+    float o[4] = {0.f, 0.f, 0.f, 0.f};
+    if (add) get4(c, o);
+    else if (R) get4(R + int64_t(row) * ldr + col, o);
+    *at4(c) = make_float4(acc[4 * g] + o[0], acc[4 * g + 1] + o[1], acc[4 * g + 2] + o[2], acc[4 * g + 3] + o[3]);
   }
 }
 __device__ __forceinline__ f32x16 zero16() {
@@ -144,15 +229,16 @@ struct Source {
   int nseg;
 };
 // Few tiles: one workgroup per 32x32 tile of C, wavefront w takes pieces w, w + 4, ... through NS stages of its own.
-template <bool AK, bool BK, bool SEG, int NS>
-__device__ __forceinline__ void tile32(float* smem, const Source& s, int m0, int n0, float* C, const float* R, int64_t ldc, int64_t ldr, int add) {
+template <bool AK, bool BK, bool SEG, int NS, int EPI>
+__device__ __forceinline__ void tile32(float* smem, const Source& s, int m0, int n0, float* C, const float* R, int64_t ldc, int64_t ldr, int add,
+                                       const Epilogue& ep) {
   const int M = s.M, N = s.N, K = s.K;
   constexpr int STAGE = 2 * 32 * KC, NREQ = 8;
   using OA = Operand<1, AK, SEG>;
-  using OB = Operand<1, BK, SEG>;
+  using OB = Operand<1, BK, SEG, EPI>;
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), l32 = lane & 31, hf = lane >> 5;
   OA oa(s.A, s.lda, m0, M, K, wave * KC, 4 * KC, 0, lane);
-  OB ob(s.B, s.ldb, n0, N, K, wave * KC, 4 * KC, 0, lane);
+  OB ob(s.B, s.ldb, n0, N, K, wave * KC, 4 * KC, 0, lane, ep.half);
   if constexpr (SEG) oa.list = s.a, ob.list = s.b, oa.nseg = ob.nseg = s.nseg;
   const float* mine = smem + wave * NS * STAGE;
   const uint32_t lds = (uint32_t)(uintptr_t)(MLS_LDS float*)(smem) + wave * NS * STAGE * 4;
@@ -221,21 +307,22 @@ __device__ __forceinline__ void tile32(float* smem, const Source& s, int m0, int
       for (int e = 0; e < 16; e++) acc[e] += part[wave][e][lane];
     __syncthreads();
   }
-  if (wave == 0) store_tile(acc, C, R, m0 + l32, n0, M, N, ldc, ldr, add, hf);
+  if (wave == 0) store_tile<EPI>(acc, C, R, m0 + l32, n0, M, N, ldc, ldr, add, hf, ep);
 }
 
 // Many tiles: one workgroup per 64x64 tile, a quadrant for each wavefront, pieces of both operands shared in a ring of four
 // stages.  Four accumulators take every fourth piece each and are added like the sums of the four wavefronts above: same bits.
-template <bool AK, bool BK, bool SEG>
-__device__ __forceinline__ void tile64(float* smem, const Source& s, int m0, int n0, float* C, const float* R, int64_t ldc, int64_t ldr, int add) {
+template <bool AK, bool BK, bool SEG, int EPI>
+__device__ __forceinline__ void tile64(float* smem, const Source& s, int m0, int n0, float* C, const float* R, int64_t ldc, int64_t ldr, int add,
+                                       const Epilogue& ep) {
   const int M = s.M, N = s.N, K = s.K;
   constexpr int STAGE = 2 * 64 * KC, NS = 4, NREQ = 4;
   using OA = Operand<2, AK, SEG>;
-  using OB = Operand<2, BK, SEG>;
+  using OB = Operand<2, BK, SEG, EPI>;
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), l32 = lane & 31, hf = lane >> 5;
   const int wm = wave & 1, wn = wave >> 1;
   OA oa(s.A, s.lda, m0, M, K, 0, KC, 2 * wave, lane);
-  OB ob(s.B, s.ldb, n0, N, K, 0, KC, 2 * wave, lane);
+  OB ob(s.B, s.ldb, n0, N, K, 0, KC, 2 * wave, lane, ep.half);
   if constexpr (SEG) oa.list = s.a, ob.list = s.b, oa.nseg = ob.nseg = s.nseg;
   const uint32_t lds = (uint32_t)(uintptr_t)(MLS_LDS float*)(smem);
   const int each = (K + KC - 1) / KC, pieces = SEG ? each * s.nseg : each;
@@ -291,16 +378,16 @@ __device__ __forceinline__ void tile64(float* smem, const Source& s, int m0, int
   }
 #pragma unroll
   for (int e = 0; e < 16; e++) acc[0][e] = (acc[0][e] + acc[2][e]) + (acc[1][e] + acc[3][e]);
-  store_tile(acc[0], C, R, m0 + wm * 32 + l32, n0 + wn * 32, M, N, ldc, ldr, add, hf);
+  store_tile<EPI>(acc[0], C, R, m0 + wm * 32 + l32, n0 + wn * 32, M, N, ldc, ldr, add, hf, ep);
 }
 
-template <bool AK, bool BK, bool LARGE>
+template <bool AK, bool BK, bool LARGE, int EPI>
 __global__ __launch_bounds__(256, 2) void gemm_f32_kernel(const float* __restrict__ A, const float* __restrict__ B, float* C, const float* R,
-                                                          int M, int N, int K, int64_t lda, int64_t ldb, int64_t ldc, int64_t ldr, int add) {
+                                                          int M, int N, int K, int64_t lda, int64_t ldb, int64_t ldc, int64_t ldr, int add, Epilogue ep) {
   extern __shared__ __attribute__((aligned(1024))) float smem[];
   const Source s = {A, B, M, N, K, lda, ldb, nullptr, nullptr, 1};
-  if constexpr (LARGE) tile64<AK, BK, false>(smem, s, blockIdx.y * 64, blockIdx.x * 64, C, R, ldc, ldr, add);
-  else tile32<AK, BK, false, 2>(smem, s, blockIdx.y * 32, blockIdx.x * 32, C, R, ldc, ldr, add);
+  if constexpr (LARGE) tile64<AK, BK, false, EPI>(smem, s, blockIdx.y * 64, blockIdx.x * 64, C, R, ldc, ldr, add, ep);
+  else tile32<AK, BK, false, 2, EPI>(smem, s, blockIdx.y * 32, blockIdx.x * 32, C, R, ldc, ldr, add, ep);
 }
 
 // The weight gradients of a layer over all micro-batches of a call: C (+)= sum_i A_i^T B_i for each problem of a list, all over matrices of
@@ -331,21 +418,21 @@ __global__ __launch_bounds__(256, 2) void gemm_f32_tn_group_kernel(TnGroup g) {
   const auto& p = g.p[i];
   const int at = t - p.tile0, m = at / p.tiles_n, n = at - m * p.tiles_n;
   const Source s = {p.a[0], p.b[0], p.M, p.N, g.K, p.lda, p.ldb, p.a, p.b, g.nseg};
-  if constexpr (LARGE) tile64<false, false, true>(smem, s, m * 64, n * 64, p.C, nullptr, p.ldc, 0, g.add);
-  else tile32<false, false, true, 2>(smem, s, m * 32, n * 32, p.C, nullptr, p.ldc, 0, g.add);
+  if constexpr (LARGE) tile64<false, false, true, E_STORE>(smem, s, m * 64, n * 64, p.C, nullptr, p.ldc, 0, g.add, Epilogue{});
+  else tile32<false, false, true, 2, E_STORE>(smem, s, m * 32, n * 32, p.C, nullptr, p.ldc, 0, g.add, Epilogue{});
 }
 
 constexpr int LDS = 4 * 2 * 2 * 32 * KC * 4;  // of every form
 
-template <bool AK, bool BK>
+template <bool AK, bool BK, int EPI = E_STORE>
 hipError_t launch_f32(const float* A, const float* B, float* C, const float* R, int M, int N, int K, int64_t lda, int64_t ldb,
-                      int64_t ldc, int64_t ldr, int add, hipStream_t st) {
+                      int64_t ldc, int64_t ldr, int add, hipStream_t st, const Epilogue& ep = {}) {
   const bool large = mls::gemm_f32_large(M, N, K);
-  auto kern = large ? gemm_f32_kernel<AK, BK, true> : gemm_f32_kernel<AK, BK, false>;
+  auto kern = large ? gemm_f32_kernel<AK, BK, true, EPI> : gemm_f32_kernel<AK, BK, false, EPI>;
   static std::atomic<uint64_t> lds_raised[2] = {{0}, {0}};
   if (hipError_t e = mls::raise_lds_limit(reinterpret_cast<const void*>(kern), LDS, lds_raised[large])) return e;
   const int t = large ? 64 : 32;
-  hipLaunchKernelGGL(kern, dim3((N + t - 1) / t, (M + t - 1) / t), dim3(256), LDS, st, A, B, C, R, M, N, K, lda, ldb, ldc, ldr, add);
+  hipLaunchKernelGGL(kern, dim3((N + t - 1) / t, (M + t - 1) / t), dim3(256), LDS, st, A, B, C, R, M, N, K, lda, ldb, ldc, ldr, add, ep);
   return hipGetLastError();
 }
 
@@ -378,6 +465,30 @@ hipError_t gemm_f32(int mode, const void* A, const void* B, void* C, const void*
     case GEMM_TN: return launch_f32<false, false>(a, b, c, nullptr, M, N, K, lda, ldb, ldc, ldr, overwrite ? 0 : 1, st);
     default: return hipErrorInvalidValue;
   }
+}
+
+// A launch less than the product and an elementwise kernel after it, and no second pass over its results.  With the rotation back in the
+// attention backward's stores, a step: hidden 512, ffn 1376, 2 micro-batches of 2 x 256 tokens (eight launches less) 411 -> 394 us; 768, 2048,
+// 3 x 1152 1832 -> 1795; 256, 512, 100 tokens 104 -> 97.  The same arithmetic on the same values.
+hipError_t gemm_f32_swiglu(const void* A, const void* W, void* GU, void* Z, int M, int f, int K, int64_t lda, int64_t ldw, int64_t ldgu,
+                           int64_t ldz, hipStream_t st) {
+  if (M == 0 || f == 0) return hipSuccess;
+  if (f % 8) return hipErrorInvalidValue;
+  const Epilogue ep = {(float*)Z, nullptr, nullptr, ldz, f, 0, 0};
+  return launch_f32<true, false, E_SWIGLU>((const float*)A, (const float*)W, (float*)GU, nullptr, M, 2 * f, K, lda, ldw, ldgu, 0, 0, st, ep);
+}
+hipError_t gemm_f32_rope(const void* A, const void* W, void* C, int M, int N, int K, int64_t lda, int64_t ldw, int64_t ldc, const float* cos_tab,
+                         const float* sin_tab, int seq, int rot_cols, int head_dim, hipStream_t st) {
+  if (M == 0 || N == 0) return hipSuccess;
+  if (head_dim < 16 || head_dim % 16 || N % head_dim || rot_cols % head_dim || seq < 1) return hipErrorInvalidValue;
+  const Epilogue ep = {nullptr, cos_tab, sin_tab, 0, head_dim / 2, seq, rot_cols};
+  return launch_f32<true, false, E_ROPE>((const float*)A, (const float*)W, (float*)C, nullptr, M, N, K, lda, ldw, ldc, 0, 0, st, ep);
+}
+hipError_t gemm_f32_dswiglu(const void* dY, const void* W, const void* GU, void* DGU, int M, int f, int K, int64_t lda, int64_t ldw,
+                            int64_t ldgu, int64_t lddgu, hipStream_t st) {
+  if (M == 0 || f == 0) return hipSuccess;
+  const Epilogue ep = {nullptr, nullptr, nullptr, 0, f, 0, 0};
+  return launch_f32<true, true, E_DSWIGLU>((const float*)dY, (const float*)W, (float*)DGU, (const float*)GU, M, f, K, lda, ldw, lddgu, ldgu, 0, st, ep);
 }
 
 // The 64x64 tiles where all problems together have 320 of them and more, as for a single product (us, 32x32 / 64x64: hidden 512, ffn 1376

@@ -161,6 +161,15 @@ hipError_t gemm_f32(int mode, const void* A, const void* B, void* C, const void*
                     int64_t ldb, int64_t ldc, int64_t ldr, hipStream_t st, bool overwrite = false);
 // p[i].C (+)= sum_j p[i].A[j][kseg, M]^T * p[i].B[j][kseg, N] over nseg <= 16 pieces for up to four products, fp32 throughout, and the
 // column sums of cs, in one launch (nothing at all without a piece)
+// The fp32 products with an elementwise step as their epilogue (operands as gemm_f32 takes them): gate|up [M, 2f] and Z = silu(gate) up, both
+// stored; C with the head vectors below column rot_cols rotated by row % seq (head_dim a multiple of 16; tables [seq][head_dim/2]);
+// the SwiGLU backward of dZ = dY W^T (W [f, K]) from GU [M, 2f].
+hipError_t gemm_f32_swiglu(const void* A, const void* W, void* GU, void* Z, int M, int f, int K, int64_t lda, int64_t ldw, int64_t ldgu,
+                           int64_t ldz, hipStream_t st);
+hipError_t gemm_f32_rope(const void* A, const void* W, void* C, int M, int N, int K, int64_t lda, int64_t ldw, int64_t ldc, const float* cos_tab,
+                         const float* sin_tab, int seq, int rot_cols, int head_dim, hipStream_t st);
+hipError_t gemm_f32_dswiglu(const void* dY, const void* W, const void* GU, void* DGU, int M, int f, int K, int64_t lda, int64_t ldw,
+                            int64_t ldgu, int64_t lddgu, hipStream_t st);
 hipError_t gemm_f32_tn_group(const TnProduct* p, int n, int nseg, int kseg, hipStream_t st, bool overwrite, const Colsum& cs = {});
 
 // ---- row-wise and elementwise kernels (elementwise.hip); dt selects the storage type; every matrix argument is
@@ -186,11 +195,11 @@ hipError_t rmsnorm_bwd(int dt, const void* da, int64_t ld_da, const void* x, int
 // gemm_bf16_tn_group
 Colsum rmsnorm_bwd_sums(const float* partial0, float* dgamma0, const float* partial1, float* dgamma1, int T, int h, bool overwrite);
 hipError_t rmsnorm_bwd_reduce(const Colsum& cs, hipStream_t st);
-// rotate the pairs (i, i+d/2) of the first n_heads heads of every row of u [T, ld] by sign*angle(t % S, i)
-hipError_t rope_inplace(int dt, void* u, const float* cos_tab, const float* sin_tab, int T, int S, int n_heads, int d,
-                        int64_t ld, float sign, hipStream_t st);
-hipError_t swiglu_fwd(int dt, const void* gu, int64_t ld_gu, void* z, int64_t ld_z, int T, int f, hipStream_t st);
-hipError_t swiglu_bwd(int dt, const void* dz, int64_t ld_dz, const void* gu, int64_t ld_gu, void* dgu, int64_t ld_dgu,
+// bf16 storage (fp32: gemm_f32_rope): rotate the pairs (i, i+d/2) of the first n_heads heads of every row of u [T, ld] by angle(t % S, i)
+hipError_t rope_inplace(void* u, const float* cos_tab, const float* sin_tab, int T, int S, int n_heads, int d, int64_t ld, hipStream_t st);
+// bf16 (fp32 storage: gemm_f32_swiglu, gemm_f32_dswiglu)
+hipError_t swiglu_fwd(const void* gu, int64_t ld_gu, void* z, int64_t ld_z, int T, int f, hipStream_t st);
+hipError_t swiglu_bwd(const void* dz, int64_t ld_dz, const void* gu, int64_t ld_gu, void* dgu, int64_t ld_dgu,
                       int T, int f, hipStream_t st, bool interleaved = false);  // interleaved: gu, dgu in that order
 // weights from the counter-based generator: element (r, c) of a rows x cols tensor stored with row stride ld is
 // offset + scale*z(seed, tensor, layer, r*cols + c), rounded once
@@ -222,7 +231,7 @@ hipError_t attn_fwd(int dt, const void* qkv, int64_t ld_qkv, void* o, int64_t ld
 // dqkv has the column layout of qkv; delta: workspace for row statistics, [b, n_q, S] fp32 (sums of do*o), for bf16 storage
 // twice that; part: workspace of attn_bwd_scratch_floats() floats, or null.  With few KV heads the dK / dV kernel shares the
 // query heads of a group out over several workgroups, which leave fp32 partial sums in `part` for a fixed-order reduction; without
-// the workspace one workgroup walks the whole group.  cos_tab, sin_tab ([S][d/2] fp32, bf16 storage only): the q and
+// the workspace one workgroup walks the whole group.  cos_tab, sin_tab ([S][d/2] fp32): the q and
 // k parts of dqkv come out turned back by the rotary angle of their position, i.e. as gradients w.r.t. the
 // projection's output; without them they are gradients w.r.t. the rotated q and k.
 size_t attn_bwd_scratch_floats(int dt, int b, int S, int nq, int nkv, int d);
@@ -236,7 +245,8 @@ hipError_t attn_fwd_f32(const void* qkv, int64_t ld_qkv, void* o, int64_t ld_o, 
                         int d, hipStream_t st);
 size_t attn_bwd_f32_scratch_floats(int b, int S, int nq, int nkv, int d);
 hipError_t attn_bwd_f32(const void* qkv, int64_t ld_qkv, const void* o, int64_t ld_o, const float* lse, const void* d_o,
-                        int64_t ld_do, void* dqkv, int64_t ld_dqkv, float* delta, int b, int S, int nq, int nkv, int d, hipStream_t st, float* part);
+                        int64_t ld_do, void* dqkv, int64_t ld_dqkv, float* delta, int b, int S, int nq, int nkv, int d, hipStream_t st, float* part,
+                        const float* cos_tab, const float* sin_tab);
 bool bwd_f32_together(int b, int S, int nq);  // whether its dQ, dK and dV share a launch.  Host only.
 hipError_t attn_fwd_bf16(const void* qkv, int64_t ld_qkv, void* o, int64_t ld_o, float* lse, int b, int S, int nq, int nkv,
                          int d, hipStream_t st);

@@ -256,11 +256,13 @@ int layer_forward(mls_stage* s, int layer, char* x, char* e, void* out, int64_t 
   if (s->fuse_rope) {  // the rotation of q and k is the epilogue of their projection
     LAUNCH(CLS_GEMM_NN, mls::gemm_bf16_rope(e + L.a, s->param_t(layer, s->toff_wqkv), e + L.qkv, T, s->qkvw, hk, lh, lh, lq, s->cos_tab,
                                             s->sin_tab, c.seq, s->qd + s->kvd, c.head_dim, s->st, s->split));
+  } else if (wt) {
+    LAUNCH(CLS_GEMM_NN, gemm(s, mls::GEMM_NT, e + L.a, s->param_t(layer, s->toff_wqkv), e + L.qkv, nullptr, T, s->qkvw, hk, lh, lh, lq));
+    LAUNCH(CLS_ROPE, mls::rope_inplace(e + L.qkv, s->cos_tab, s->sin_tab, T, c.seq, c.n_q_heads + c.n_kv_heads,
+                                       c.head_dim, lq, s->st));
   } else {
-    if (wt) LAUNCH(CLS_GEMM_NN, gemm(s, mls::GEMM_NT, e + L.a, s->param_t(layer, s->toff_wqkv), e + L.qkv, nullptr, T, s->qkvw, hk, lh, lh, lq));
-    else LAUNCH(CLS_GEMM_NN, gemm(s, mls::GEMM_NN, e + L.a, s->param(layer, s->ioff_wqkv), e + L.qkv, nullptr, T, s->qkvw, h, lh, lq, lq));
-    LAUNCH(CLS_ROPE, mls::rope_inplace(s->dt, e + L.qkv, s->cos_tab, s->sin_tab, T, c.seq, c.n_q_heads + c.n_kv_heads,
-                                       c.head_dim, lq, 1.f, s->st));
+    LAUNCH(CLS_GEMM_NN, mls::gemm_f32_rope(e + L.a, s->param(layer, s->ioff_wqkv), e + L.qkv, T, s->qkvw, h, lh, lq, lq, s->cos_tab, s->sin_tab,
+                                           c.seq, s->qd + s->kvd, c.head_dim, s->st));
   }
   LAUNCH(CLS_ATTN_FWD, mls::attn_fwd(s->dt, e + L.qkv, lq, e + L.o, lo, (float*)(e + L.lse), c.micro_batch, c.seq,
                                      c.n_q_heads, c.n_kv_heads, c.head_dim, s->st));
@@ -270,10 +272,11 @@ int layer_forward(mls_stage* s, int layer, char* x, char* e, void* out, int64_t 
                                     c.rms_eps, s->st));
   if (s->fuse_gu) {
     LAUNCH(CLS_GEMM_NN, mls::gemm_bf16_swiglu(e + L.b, s->param_t(layer, s->toff_wgu), e + L.gu, e + L.z, T, s->fgu, hk, lh, lh, lg, lf, s->st, s->split));
+  } else if (wt) {
+    LAUNCH(CLS_GEMM_NN, gemm(s, mls::GEMM_NT, e + L.b, s->param_t(layer, s->toff_wgu), e + L.gu, nullptr, T, 2 * f, hk, lh, lh, lg));
+    LAUNCH(CLS_SWIGLU, mls::swiglu_fwd(e + L.gu, lg, e + L.z, lf, T, f, s->st));
   } else {
-    if (wt) LAUNCH(CLS_GEMM_NN, gemm(s, mls::GEMM_NT, e + L.b, s->param_t(layer, s->toff_wgu), e + L.gu, nullptr, T, 2 * f, hk, lh, lh, lg));
-    else LAUNCH(CLS_GEMM_NN, gemm(s, mls::GEMM_NN, e + L.b, s->param(layer, s->ioff_wgu), e + L.gu, nullptr, T, 2 * f, h, lh, lg, lg));
-    LAUNCH(CLS_SWIGLU, mls::swiglu_fwd(s->dt, e + L.gu, lg, e + L.z, lf, T, f, s->st));
+    LAUNCH(CLS_GEMM_NN, mls::gemm_f32_swiglu(e + L.b, s->param(layer, s->ioff_wgu), e + L.gu, e + L.z, T, f, h, lh, lg, lg, lf, s->st));
   }
   // `out` is either the next layer's x (row stride ld_h) or the caller's dense y
   if (out) {
@@ -307,23 +310,21 @@ int layer_backward_data(mls_stage* s, int layer, const char* x, const char* e, i
   // data gradients dX = dY W^T: W is the [row][k] operand
   if (s->fuse_gu && mls::gemm_dswiglu_ok(T, f, hk, ld_dy, lh, s->split.sums != nullptr)) {
     LAUNCH(CLS_GEMM_NT, mls::gemm_bf16_dswiglu(dy, s->param(layer, s->ioff_wd), e + L.gu, dgu, T, f, hk, ld_dy, lh, lg, lg, s->st, s->split));
+  } else if (!bf16) {
+    LAUNCH(CLS_GEMM_NT, mls::gemm_f32_dswiglu(dy, s->param(layer, s->ioff_wd), e + L.gu, dgu, T, f, hk, ld_dy, lh, lg, lg, s->st));
   } else {
     LAUNCH(CLS_GEMM_NT, gemm(s, mls::GEMM_NT, dy, s->param(layer, s->ioff_wd), s->dz, nullptr, T, f, hk, ld_dy, lh, lf));
-    LAUNCH(CLS_SWIGLU, mls::swiglu_bwd(s->dt, s->dz, lf, e + L.gu, lg, dgu, lg, T, f, s->st, s->fuse_gu));
+    LAUNCH(CLS_SWIGLU, mls::swiglu_bwd(s->dz, lf, e + L.gu, lg, dgu, lg, T, f, s->st, s->fuse_gu));
   }
   LAUNCH(CLS_GEMM_NT, gemm(s, mls::GEMM_NT, dgu, s->param(layer, s->ioff_wgu), s->dbuf, nullptr, T, h, gk, lg, lg, lh));
   LAUNCH(CLS_NORM, mls::rmsnorm_bwd(s->dt, s->dbuf, lh, e + L.h, lh, s->param(layer, s->ioff_g2), (const float*)(e + L.r2),
                                     dy, ld_dy, dh, lh, g + s->off_g2, s->partial2, T, h, s->st, ow, !first, false));
   // attention
   LAUNCH(CLS_GEMM_NT, gemm(s, mls::GEMM_NT, dh, s->param(layer, s->ioff_wo), s->dc, nullptr, T, qd, hk, lh, lh, lo));
-  // the bf16 attention-backward kernels turn dq and dk back by the rotary angle as they store them
-  const bool unrot = s->dt == mls::DT_BF16;
+  // (which turns dq and dk back by the rotary angle as it stores them)
   LAUNCH(CLS_ATTN_BWD, mls::attn_bwd(s->dt, e + L.qkv, lq, e + L.o, lo, (const float*)(e + L.lse), s->dc, lo, dqkv, lq,
                                      s->delta, c.micro_batch, c.seq, c.n_q_heads, c.n_kv_heads, c.head_dim, s->st, s->gqa_part,
-                                     unrot ? s->cos_tab : nullptr, unrot ? s->sin_tab : nullptr));
-  if (!unrot)
-    LAUNCH(CLS_ROPE, mls::rope_inplace(s->dt, dqkv, s->cos_tab, s->sin_tab, T, c.seq, c.n_q_heads + c.n_kv_heads,
-                                       c.head_dim, lq, -1.f, s->st));
+                                     s->cos_tab, s->sin_tab));
   LAUNCH(CLS_GEMM_NT, gemm(s, mls::GEMM_NT, dqkv, s->param(layer, s->ioff_wqkv), s->dbuf, nullptr, T, h, wq, lq, lq, lh));
   LAUNCH(CLS_NORM, mls::rmsnorm_bwd(s->dt, s->dbuf, lh, x, lh, s->param(layer, s->ioff_g1), (const float*)(e + L.r1),
                                     dh, lh, dx, ld_dx, g + s->off_g1, s->partial, T, h, s->st, ow, !first, false));

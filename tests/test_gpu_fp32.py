@@ -107,6 +107,20 @@ def test_backward_launches_on_either_side_of_their_rules(nq, nkv, d, seq, mb, to
     test_stage_fp32_against_the_exact_oracle(nq, nkv, d, seq, mb)
 
 
+# rotary, SwiGLU and its backward as epilogues of the products: pairs of columns 8 to 64 apart and ffn apart, ending anywhere in a tile; 32x32
+# tiles of one row to several, then 64x64 ones (q|k|v: 340 rows x 1536 columns and more; gate|up, its backward: 2 728, 2 720 columns)
+@pytest.mark.parametrize("hidden,nq,nkv,d,ffn,seq", [(72, 1, 1, 16, 8, 1), (72, 3, 1, 48, 24, 33), (64, 2, 2, 80, 40, 70), (40, 2, 1, 112, 1000, 5),
+                                                     (264, 18, 3, 64, 1360, 1021), (136, 30, 10, 48, 2728, 517), (72, 5, 5, 128, 2720, 600)])
+def test_epilogues_of_the_products(hidden, nq, nkv, d, ffn, seq):
+    sh = synth.StageShape(hidden=hidden, n_q_heads=nq, n_kv_heads=nkv, head_dim=d, ffn=ffn, seq=seq, micro_batch=1, layers=1,
+                          microbatches=1, dtype="fp32")
+    ys, dxs, g, st = gpu_step(sh, 1000, 2000, 3000, [1])
+    st.close()
+    rys, rdxs, rg = oracle_step(sh, 1000, 2000, 3000, [1])
+    for e in [rel_err(a, b) for a, b in zip(ys + dxs, rys + rdxs)] + [grad_errors(sh, g, rg, 1)[0]]:
+        assert e <= 1e-5
+
+
 @pytest.mark.parametrize("bad", [float("inf"), float("nan")])
 def test_a_non_finite_position_reaches_no_earlier_one(bad):
     import torch
