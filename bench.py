@@ -20,9 +20,9 @@ sys.path.insert(0, ROOT)
 
 PEAK_BF16_TFLOPS = 2500.0   # MI355X dense bf16 MFMA
 # HBM bytes of the GEMM kernels of a step, from the rocprofv3 --pmc FETCH_SIZE / WRITE_SIZE runs summarised in
-# profiles/stage_7b_4x4_hbm_traffic.txt: 164 dispatches of gemm16_kernel and gemm_t16_kernel per step, on average
-# (2.0 * 364312 KiB fetched + 1.0 * 85131 KiB written) * 1024 each.  Only valid for the default workload.
-PROFILED_GEMM_TRAFFIC = {"7b": 164 * 8.333e8}
+# profiles/stage_7b_4x4_hbm_traffic.txt: 152 dispatches of gemm16_kernel and gemm_t16_kernel per step, on average
+# (2.0 * 402013 KiB fetched + 1.0 * 91853 KiB written) * 1024 each.  Only valid for the default workload.
+PROFILED_GEMM_TRAFFIC = {"7b": 152 * 9.174e8}
 
 
 def cpu_baseline(sh):
