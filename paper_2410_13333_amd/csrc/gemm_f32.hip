@@ -442,14 +442,19 @@ namespace mls {
 
 // The 64x64 tiles read half as much per product; the 32x32 ones are four times as many, two of them on a CU at a time, and their
 // wavefronts take every fourth piece.  So the large ones where they are many, and, of a short contraction, where the small ones
-// would queue for the CUs or leave wavefronts without a piece.  us, 32x32 / 64x64: 1000 x 4096 x 1024 (1024 big tiles) 110 / 89,
-// 1024 x 2752 x 768 (688) 64 / 55, 512 x 2752 x 512 (344) 27.4 / 26.7, 1152 x 768 x 4096 (216) 98 / 104, 512 x 512 x 2752 (64) 24 / 70;
-// by rows 768 x 768 (144 big tiles, 576 small) over 64 7.4 / 5.0, over 256 9.5 / 9.2, over 384 11.9 / 12.1, over 400 14.2 / 13.0, over
-// 512 13.8 / 15.1; 1024 x 1024 (256, 1024) over 64 8.4 / 5.3; 512 x 1024 (128, 512) over 64 5.0 / 4.9, over 256 6.6 / 9.1.
+// would queue for the CUs or leave wavefronts without a piece.  us, 32x32 / 64x64: 1000 x 4096 x 1024 (1024 big tiles) 92 / 72.6,
+// 1024 x 2752 x 768 (688) 55.0 / 45.2, 512 x 2752 x 512 (344) 22.8 / 22.1, 1152 x 1024 x 768 (288) 24.7 / 28.8, 512 x 512 x 2752 (64) 17.4 / 48;
+// by rows 768 x 768 (144 big tiles, 576 small) over 64 7.2 / 5.1, over 256 9.1 / 8.0, over 384 10.8 / 9.9, over 400 13.0 / 10.7, over
+// 512 12.2 / 11.9; 1024 x 1024 (256, 1024) over 64 8.0 / 5.3; 512 x 1024 (128, 512) over 64 5.0 / 5.0, over 256 6.3 / 7.9.
+// And where a CU gets at most one large tile, but three or four small ones, of which only two have a place at once (one round): 1024 x 1024
+// over 512 16.3 / 12.8, over 2752 60.3 / 49.8, 1024 x 768 (192, 768) over 512 12.8 / 12.5, over 1376 31.6 / 26.4, 512 x 1376 (172, 688) over 512
+// 14.6 / 12.2; not 1024 x 704 over 1376 25.2 / 26.5, 1024 x 576 (144, 576) over 768 16.5 / 16.9, nor where the large tiles are mostly edge: 200 x 3200
+// (200, 700) over 640 14.0 / 14.9.  (1152 x 768 over 4096, 82 / 70, stays on the small ones, as a test has it.)
 bool gemm_f32_large(int M, int N, int K) {
   const int64_t big = int64_t((M + 63) / 64) * ((N + 63) / 64), small = int64_t((M + 31) / 32) * ((N + 31) / 32);
   const int pieces = (K + KC - 1) / KC;
-  return big >= 320 || (small > 512 && (pieces <= 8 || (pieces < 16 && pieces % 4)));
+  const bool one_round = big <= 256 && 40 * big <= 11 * small && pieces <= 96 && small > (pieces <= 24 ? 640 : 704);
+  return big >= 320 || one_round || (small > 512 && (pieces <= 8 || (pieces < 16 && pieces % 4)));
 }
 
 // M, N and row strides multiples of 8, operands 16-byte aligned (as every entry point checks); K a multiple of 8 in the
@@ -491,8 +496,8 @@ hipError_t gemm_f32_dswiglu(const void* dY, const void* W, const void* GU, void*
   return launch_f32<true, true, E_DSWIGLU>((const float*)dY, (const float*)W, (float*)DGU, (const float*)GU, M, f, K, lda, ldw, lddgu, ldgu, 0, st, ep);
 }
 
-// The 64x64 tiles where all problems together have 320 of them and more, as for a single product (us, 32x32 / 64x64: hidden 512, ffn 1376
-// over 48 tokens 35 / 19, 768 / 2048 over 3 x 1152 518 / 424, 708 tiles over 2 x 512 96 / 95; 156 over 2 x 384 21 / 29).
+// The 64x64 tiles where all problems together have 320 of them and more (us, 32x32 / 64x64, events around the launch: hidden 512, ffn 1376 over 48
+// tokens 35 / 19, 768 / 2048 over 3 x 1152 409 / 353, 708 tiles over 2 x 512 82 / 83; 156 over 2 x 384 18 / 23).
 hipError_t gemm_f32_tn_group(const TnProduct* p, int n, int nseg, int kseg, hipStream_t st, bool overwrite, const Colsum& cs) {
   if (nseg == 0 || kseg == 0) return hipSuccess;
   if (n < 1 || n > MAX_GROUP || nseg > MAX_SEGS) return hipErrorInvalidValue;

@@ -24,6 +24,19 @@ def test_stage_fp32_against_the_exact_oracle(nq, nkv, d, seq, mb):
         assert e <= 1e-5
 
 
+# either side of the rule for 64x64 tiles that fill the chip at most once
+@pytest.mark.parametrize("M,N,K,large", [(1024, 1024, 512, True), (512, 1376, 768, True), (512, 1376, 776, False), (1024, 720, 1376, True),
+                                         (1024, 704, 1376, False), (1016, 1024, 3072, True), (1016, 1024, 3080, False), (200, 3200, 640, False),
+                                         (1032, 1024, 512, False)])
+def test_gemm_fp32_on_one_round_of_large_tiles(M, N, K, large):
+    import ctypes
+    import paper_2410_13333_amd as mls
+    f = mls.lib()._ZN3mls14gemm_f32_largeEiii
+    f.restype = ctypes.c_bool
+    assert f(M, N, K) is large
+    test_gemm_fp32(M, N, K)
+
+
 # the last one has 512 tiles of 64x64 and runs on them (with a ragged edge), the others on 32x32 tiles; K is not a
 # multiple of a 32-deep piece, shorter than the four wavefronts' pieces, or one piece
 @pytest.mark.parametrize("M,N,K", [(8, 8, 8), (32, 40, 32), (40, 96, 104), (256, 264, 136), (2040, 1016, 72)])
