@@ -552,6 +552,8 @@ __global__ __launch_bounds__(AT_THREADS, 2) void attn_fwd_pair_kernel(const bf16
       between(NC);
     });
     wait_dma();  // this wavefront's part of K(u), V(u - 1)
+    // and its reads of V(u - 2), a block's softmax ago: behind the barrier V(u) takes their buffer, and a wavefront waits only for its own.
+    wait_lgkm0();
     __builtin_amdgcn_s_barrier();
     asm volatile("" ::: "memory");
     issue(rk, Q);

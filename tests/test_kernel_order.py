@@ -1,5 +1,6 @@
-"""Products written as asm, whose results the compiler takes to be there at once: in the assembly of the kernels as built,
-every other instruction that touches such a result lies far enough behind the product that wrote it (no GPU)."""
+"""What the compiler cannot see, in the assembly of the kernels as built (no GPU): products written as asm, whose results it takes to be
+there at once, have every other instruction that touches such a result far enough behind them; barriers written by hand, which it
+does not wait in front of, have no LDS read of a buffer they free behind them."""
 import os
 import re
 import shutil
@@ -126,3 +127,33 @@ def test_only_the_kernel_of_few_workgroups_stores_ds(attention_asm):
     assert len(stores) == 4
     for k, n in stores.items():
         assert n == (2 if "attn_dkv_ds_kernel" in k else 0), k
+
+
+def reads_at_barriers(lines):
+    """For every barrier of a kernel the largest number of LDS reads, over all paths, that may not have returned there."""
+    blocks, succ = _blocks(lines)
+    entry, work, at = {0: 0}, [0], {}
+    while work:
+        i = work.pop()
+        n = entry[i]
+        for j, (op, args, _) in enumerate(blocks[i]):
+            if op.startswith("ds_read"):
+                n = min(n + 1, 64)
+            elif op == "s_waitcnt":
+                n = min([n] + [int(m[1]) for m in (re.match(r"lgkmcnt\((\d+)\)", a) for a in args) if m])
+            elif op == "s_barrier":
+                at[i, j] = max(at.get((i, j), 0), n)
+        for k in succ[i]:
+            if k not in entry or entry[k] < n:
+                entry[k] = n
+                work.append(k)
+    return list(at.values())
+
+
+@pytest.mark.parametrize("kernel", ["attn_fwd_pair_kernelILi64E", "attn_fwd_pair_kernelILi128E", "attn_fwd_kernelILi64E", "attn_fwd_kernelILi128E",
+                                    "attn_dq_kernelILi64E", "attn_dq_kernelILi128E", "attn_dq_ds_kernelILi128E"])
+def test_no_lds_read_is_under_way_at_a_barrier_that_frees_its_buffer(attention_asm, kernel):
+    """Behind the barrier any wavefront may have the buffer filled again."""
+    (lines,) = [v for k, v in attention_asm.items() if kernel in k]
+    at = reads_at_barriers(lines)
+    assert at and max(at) == 0, at
