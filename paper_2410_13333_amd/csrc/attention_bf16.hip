@@ -448,9 +448,10 @@ __global__ __launch_bounds__(AT_THREADS, 2) void attn_fwd_kernel(const bf16_t* _
 // What bounds it is a wavefront's issue: about 100 vector instructions, 16 of them exponentials, and 16 products per sub-block, 0.65 us,
 // whether it is alone on its SIMD or not.  The pipeline is therefore one of sub-blocks, two iterations per turn of the loop so that every
 // buffer and every fragment address is a constant, in exactly the order written: products with V of the block before the last on both
-// sides of the barrier, whose fragments were read before it, so that neither the barrier nor the first reads behind it are waited for.
-// Measured (us, the kernel above -> this): 2048 positions, 16 heads of 128: 43 -> 34; 1024, 16: 23.4 -> 16.6; 512, 16: 13.6 -> 10.5;
-// 4096, 8: 79 -> 58; 3000, 4: 57 -> 36; 2 x 1000, 16 of 64: 17.2 -> 13.0; 512, 16 of 64: 9.8 -> 7.6.
+// sides of the barrier, whose fragments were read an iteration before, so that neither the barrier nor the first reads behind it are waited for.
+// Measured (us, the kernel above -> this): 2048 positions, 16 heads of 128: 45.4 -> 32.0; 1024, 16: 23.7 -> 15.8; 512, 16: 13.5 -> 10.0;
+// 4096, 8: 80 -> 54; 3000, 4: 57 -> 33; 2 x 1000, 16 of 64: 17.4 -> 12.4; 512, 16 of 64: 9.9 -> 7.3.  (With a wait for the rows of Q left to
+// the compiler, which put it into the loop: 34.8, 16.8, 10.5, 58.9, 35.9, 13.1, 7.7.)
 template <int D>
 __global__ __launch_bounds__(AT_THREADS, 2) void attn_fwd_pair_kernel(const bf16_t* __restrict__ qkv, int64_t ld, bf16_t* __restrict__ o, int64_t ldo,
                                                                       float* __restrict__ lse, int S, int nq, int nkv) {
@@ -495,6 +496,9 @@ __global__ __launch_bounds__(AT_THREADS, 2) void attn_fwd_pair_kernel(const bf16
 #pragma unroll
   for (int n = 0; n < KD; n++) vf[n] = bf16x8{};
   pf[0][0] = pf[0][1] = pf[1][0] = pf[1][1] = bf16x8{};
+  // the compiler's own wait for the rows of Q, here and not in the loop, where it would be one for the requests of the next block
+#pragma unroll
+  for (int kk = 0; kk < KD; kk++) asm volatile("" : "+v"(qf[kk]));
 
   // An iteration: O += V^T P of the block before the last, the exponentials of the last one, S of the next one, whose parity is P; in
   // exactly the order written.  MASK: the last block is the one on the diagonal.
@@ -1346,11 +1350,11 @@ namespace mls {
 
 // The forward on pairs of wavefronts pays where the longest chain of the other kernel decides, that is up to about one of its workgroups
 // (of 128 rows) per CU; with more of them the second load of every key block costs more than the balance gains.  us, other / pairs:
-//   d = 128: 160 workgroups 14.5 / 13.0 (512 positions), 240 17.7 / 16.2 (700), 320 45.7 / 36.1 (2048), 384 46.5 / 42.8 (2048) but
-//            17.7 / 20.9 (384), 512 52 / 56 (2048)
-//   d = 64:  320 12.0 / 10.7 (600), 384 11.3 / 9.7 (384), 28.9 / 23.8 (2048), 448 14.9 / 14.7 (800), 480 12.3 / 13.5 (384), 512 32.0 / 32.0 (2048)
-// Short sequences have short chains: the pairs gain half a microsecond on few workgroups (128 positions 6.7 / 6.5, 300 9.3 / 8.6) and lose one
-// on more (192 workgroups of 256 10.2 / 11.3, 256 of 256 10.3 / 11.6), so they stay with the other kernel.
+//   d = 128: 160 workgroups 14.9 / 12.7 (512 positions), 240 17.5 / 15.2 (700), 320 45.5 / 34.7 (2048), 384 47.1 / 43.6 (2048) but
+//            17.7 / 18.7 (384), 448 49.4 / 47.9 (2048), 512 53.2 / 53.0 (2048), 768 68 / 74 (2048)
+//   d = 64:  320 12.0 / 10.0 (600), 384 11.3 / 9.2 (384), 29.5 / 24.1 (2048), 448 14.5 / 13.9 (800), 480 11.8 / 13.1 (384), 512 31.5 / 28.8 (2048)
+// Short sequences have short chains: the pairs gain half a microsecond on few workgroups (128 positions 6.8 / 6.5, 300 9.3 / 8.1) and lose one
+// on more (192 workgroups of 256 9.9 / 10.6, 256 of 256 10.5 / 11.3), so they stay with the other kernel.
 bool fwd_pairs(int b, int S, int nq, int d) { return S >= 384 && int64_t(b) * nq * ((S + 127) / 128) <= (d == 64 ? 384 : 320); }
 
 hipError_t attn_fwd_bf16(const void* qkv, int64_t ld_qkv, void* o, int64_t ld_o, float* lse, int b, int S, int nq, int nkv,

@@ -1,6 +1,7 @@
 """What the compiler cannot see, in the assembly of the kernels as built (no GPU): products written as asm, whose results it takes to be
 there at once, have every other instruction that touches such a result far enough behind them; barriers written by hand, which it
-does not wait in front of, have no LDS read of a buffer they free behind them."""
+does not wait in front of, have no LDS read of a buffer they free behind them; requests written as asm, which it does not count, are
+waited for by no wait of its own inside a loop."""
 import os
 import re
 import shutil
@@ -157,3 +158,25 @@ def test_no_lds_read_is_under_way_at_a_barrier_that_frees_its_buffer(attention_a
     (lines,) = [v for k, v in attention_asm.items() if kernel in k]
     at = reads_at_barriers(lines)
     assert at and max(at) == 0, at
+
+
+def compiler_waits_in_loops(lines):
+    """The waits for memory requests inside a kernel's loops that are not written as asm."""
+    blocks, succ = _blocks(lines)
+
+    def in_loop(i):
+        seen, work = set(), list(succ[i])
+        while work:
+            k = work.pop()
+            if k not in seen:
+                seen.add(k)
+                work += succ[k]
+        return i in seen
+    return [a for i, b in enumerate(blocks) if in_loop(i) for op, args, asm in b if op == "s_waitcnt" and not asm for a in args if a.startswith("vmcnt")]
+
+
+@pytest.mark.parametrize("kernel", ["attn_fwd_pair_kernelILi64E", "attn_fwd_pair_kernelILi128E", "attn_fwd_kernelILi64E", "attn_fwd_kernelILi128E"])
+def test_the_compiler_waits_for_no_request_of_the_loop(attention_asm, kernel):
+    """Its wait for what it loaded before the loop (the rows of Q) would be one for the next block's requests too."""
+    (lines,) = [v for k, v in attention_asm.items() if kernel in k]
+    assert compiler_waits_in_loops(lines) == []
