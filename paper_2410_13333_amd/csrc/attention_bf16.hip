@@ -710,6 +710,10 @@ __device__ __forceinline__ void attn_dq(char* lds_, int qb, int hq, int bi, int 
     L2 = qi < S ? stats[si] : 0.f;
     dl = qi < S ? -stats[int64_t(nb) * nq * S + si] : 0.f;
   }
+  // the compiler's own wait for what was loaded, here and not in the loop, where it would be one for the requests of the next block
+#pragma unroll
+  for (int kk = 0; kk < KD; kk++) asm volatile("" : "+v"(qf[kk]), "+v"(dof[kk]));
+  asm volatile("" : "+v"(L2), "+v"(dl));
 
   f32x16 acc[DT];
 #pragma unroll
@@ -1170,9 +1174,10 @@ __global__ __launch_bounds__(AT_THREADS, 1) void attn_dkv_ds_kernel(const bf16_t
 // the CUs with short ones idle; together the one's short chains run beside the other's long ones.  grid ((n_kv nsplit + n_q) b, blocks of
 // 128): rank by rank, the longest first, a rank's key blocks before its query blocks.  Heads of 64 have two workgroups per CU, of 128 one
 // (the registers of the dK / dV part).  Whole backward (us, apart or with dQ from dS -> this): 2 x 1000 positions, 16 heads of 64 over 4:
-// 52 -> 39; 512, 16 of 64: 28 -> 18; 1024, 16 of 128: 59 -> 41.5; 2048, 16 of 128: 98.5 -> 83.5; 512, 16 of 128: 38.5 -> 27; 2 x 128, 4 of
-// 64: 15.7 -> 11.4.  The second half of the ranks in ascending order, so that two workgroups of a CU are long and short: slower (2048 x 16
-// of 128 98, 4096 x 16 of 64 155 instead of 147).
+// 51 -> 39; 512, 16 of 64: 28 -> 18; 1024, 16 of 128: 59 -> 40; 2048, 16 of 128: 100 -> 84; 512, 16 of 128: 38.5 -> 27; 2 x 128, 4 of
+// 64: 16.3 -> 11.9.  The second half of the ranks in ascending order, so that two workgroups of a CU are long and short: slower (2048 x 16
+// of 128 98, 4096 x 16 of 64 155 instead of 147).  With heads of 128 the compiler keeps the results of the dQ part in AGPRs here, which costs
+// it 192 copies per 48 products.
 template <int D>
 __global__ __launch_bounds__(AT_THREADS, D == 64 ? 2 : 1) void attn_bwd_kernel(const bf16_t* __restrict__ qkv, int64_t ld, const bf16_t* __restrict__ d_o,
                                                                                int64_t ldo, float* __restrict__ stats, bf16_t* __restrict__ dqkv,

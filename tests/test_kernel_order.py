@@ -175,8 +175,10 @@ def compiler_waits_in_loops(lines):
     return [a for i, b in enumerate(blocks) if in_loop(i) for op, args, asm in b if op == "s_waitcnt" and not asm for a in args if a.startswith("vmcnt")]
 
 
-@pytest.mark.parametrize("kernel", ["attn_fwd_pair_kernelILi64E", "attn_fwd_pair_kernelILi128E", "attn_fwd_kernelILi64E", "attn_fwd_kernelILi128E"])
+@pytest.mark.parametrize("kernel", ["attn_fwd_pair_kernelILi64E", "attn_fwd_pair_kernelILi128E", "attn_fwd_kernelILi64E", "attn_fwd_kernelILi128E",
+                                    "attn_bwd_kernelILi64E", "attn_bwd_kernelILi128E", "attn_dq_kernelILi64E", "attn_dq_kernelILi128E",
+                                    "attn_dkv_kernelILi64ELi1E", "attn_dkv_kernelILi128ELi1E", "attn_dkv_kernelILi128ELi2E", "attn_dkv_ds_kernelILi128ELi1E"])
 def test_the_compiler_waits_for_no_request_of_the_loop(attention_asm, kernel):
-    """Its wait for what it loaded before the loop (the rows of Q) would be one for the next block's requests too."""
+    """Its wait for what it loaded before the loop (rows of Q or dO, row statistics) would be one for the next block's requests too."""
     (lines,) = [v for k, v in attention_asm.items() if kernel in k]
     assert compiler_waits_in_loops(lines) == []
