@@ -1360,7 +1360,20 @@ namespace mls {
 //   d = 64:  320 12.0 / 10.0 (600), 384 11.3 / 9.2 (384), 29.5 / 24.1 (2048), 448 14.5 / 13.9 (800), 480 11.8 / 13.1 (384), 512 31.5 / 28.8 (2048)
 // Short sequences have short chains: the pairs gain half a microsecond on few workgroups (128 positions 6.8 / 6.5, 300 9.3 / 8.1) and lose one
 // on more (192 workgroups of 256 9.9 / 10.6, 256 of 256 10.5 / 11.3), so they stay with the other kernel.
-bool fwd_pairs(int b, int S, int nq, int d) { return S >= 384 && int64_t(b) * nq * ((S + 127) / 128) <= (d == 64 ? 384 : 320); }
+// From 384 positions on, where the pairs' own workgroups (of 64 rows) outnumber their places, or where heads x sequences is no multiple of 8, so
+// that the blocks of a head, 8 and 8 more apart, lie on several XCDs and each fetches its keys for itself, on all eight if the number is odd:
+//   d = 128, no more pairs than places (512): 41 heads of 448 positions 12.8 / 13.1, 63 of 448 14.3 / 15.7, 43 of 576 16.3 / 17.1 but 54 of 448
+//            13.3 / 12.8, 37 of 600 16.5 / 15.9; more: 92 of 384 15.3 / 19.6, 80 of 430 14.9 / 16.9, 62 of 600 20.2 / 22.5 but 64 of 576 20.8 / 16.9;
+//            from 832 positions on pairs all the same: 46 of 896 25.4 / 25.5, 42 29.8 / 20.2
+//   d = 64:  83 of 400 9.7 / 10.2, 107 of 384 10.0 / 10.8, 74 of 513 11.8 / 12.4 but 96 of 384 9.4 / 9.2, 66 of 513 14.2 / 10.2, 58 of 700 13.8 / 13.6
+bool fwd_pairs(int b, int S, int nq, int d) {
+  const int64_t heads = int64_t(b) * nq, pairs = heads * ((S + 63) / 64);
+  if (S < 384 || heads * ((S + 127) / 128) > (d == 64 ? 384 : 320)) return false;
+  const bool own_xcd = heads % 8 == 0;
+  if (d == 64) return own_xcd || S >= 640 || pairs <= (S > 512 ? 600 : 576);
+  if (S >= 832) return true;
+  return pairs <= 512 ? heads % 2 == 0 || heads <= 40 : own_xcd && S > 512;
+}
 
 hipError_t attn_fwd_bf16(const void* qkv, int64_t ld_qkv, void* o, int64_t ld_o, float* lse, int b, int S, int nq, int nkv,
                          int d, hipStream_t st) {

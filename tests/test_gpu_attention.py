@@ -67,12 +67,16 @@ def test_attention_against_fp64_on_the_same_operands(nq, nkv, d, seq, mb, gain):
         assert e <= 1.5e-2, (name, e)
 
 
-# Which forward kernel a grid gets: pairs of wavefronts up to the number of workgroups where the other one wins.  Sequences around the
-# blocks of either, at the last size of the one and the first of the other.
+# Which forward kernel a grid gets: pairs of wavefronts up to the number of workgroups where the other one wins, with exceptions for heads whose
+# blocks lie on several XCDs and for more pairs than places.  Sequences around the blocks of either, at the last size of the one and the
+# first of the other.
 @pytest.mark.parametrize("nq,nkv,d,seq,mb,pairs", [
     (3, 1, 64, 383, 2, False), (3, 1, 64, 384, 2, True), (2, 1, 128, 385, 1, True), (4, 4, 128, 447, 1, True), (2, 2, 64, 449, 1, True),
-    (2, 1, 64, 511, 1, True), (2, 1, 128, 577, 1, True), (32, 16, 64, 384, 4, True), (43, 43, 64, 384, 3, False), (20, 4, 128, 385, 4, True),
-    (27, 9, 128, 385, 3, False), (16, 4, 128, 300, 3, False)])
+    (2, 1, 64, 511, 1, True), (2, 1, 128, 577, 1, True), (32, 16, 64, 384, 4, True), (43, 43, 64, 384, 3, False), (20, 4, 128, 385, 4, False),
+    (27, 9, 128, 385, 3, False), (16, 4, 128, 300, 3, False), (13, 13, 128, 448, 3, True), (41, 41, 128, 448, 1, False), (42, 14, 128, 448, 1, True),
+    (32, 8, 128, 512, 2, True), (33, 11, 128, 512, 2, False), (32, 8, 128, 513, 2, True), (31, 31, 128, 513, 2, False), (43, 43, 128, 831, 1, False),
+    (45, 15, 128, 832, 1, True), (97, 97, 64, 384, 1, False), (104, 26, 64, 384, 1, True), (66, 22, 64, 513, 1, True), (67, 67, 64, 513, 1, False),
+    (70, 70, 64, 640, 1, True)])
 def test_forward_kernels_on_either_side_of_their_rule(nq, nkv, d, seq, mb, pairs):
     import ctypes
     import paper_2410_13333_amd as mls
