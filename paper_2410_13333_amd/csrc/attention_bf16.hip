@@ -1417,13 +1417,24 @@ DkvPlan dkv_plan(int b, int S, int nq, int nkv, int d) {
 // dQ, dK and dV in one launch: up to about as many workgroups of 128 query rows as have a place on the chip at once, beyond which the
 // workgroups that follow balance the chip by themselves and the launch costs dQ the second (64: the third) workgroup per CU it has alone.  Whole
 // backward, best other / together (us):
-//   d = 128: 128 workgroups 32.3 / 25.6 (120 positions), 59 / 41.5 (1024), 256 98.5 / 83.5 (2048), 43.1 / 43.3 (256), 288 90.8 / 91.5 (1500), 320
-//            115 / 123 (2048), 512 150 / 167; of one row block 192 28.4 / 30.3, 34.4 / 36.0, 224 36.8 / 38.9
-//   d = 64:  320 87 / 63 (2048), 512 99 / 86 (2048), 768 131 / 124 (2048), 25.9 / 19.9 (64), 1024 302 / 278 (4096), 54.4 / 55.9 (128), 2048 295 / 313
+//   d = 128: 128 workgroups 32.3 / 25.6 (120 positions), 59 / 40 (1024), 256 100 / 84 (2048), 43.1 / 42.7 (256), 288 90.9 / 89.6 (1500), 320
+//            114 / 120 (2048), 512 151 / 161; of one row block 192 28.4 / 29.7, 34.5 / 35.7, 224 36.8 / 38.7
+//   d = 64:  320 87 / 64 (2048), 512 101 / 86 (2048), 768 132 / 125 (2048), 26.4 / 20.1 (64), 1024 303 / 280 (4096), 54.4 / 55.9 (128), 2048 295 / 313
 //            (2048), 4096 1008 / 1118 (4096)
-bool bwd_together(int b, int S, int nq, int d) {
-  const int64_t wgs = int64_t(b) * nq * ((S + 127) / 128);
-  return wgs <= (d == 64 ? (S > 128 ? 1024 : 768) : (S > 128 ? 256 : 128));
+// Where every query head has KV heads of its own, a launch of short chains is decided by its last round, and heads x sequences that are no
+// multiple of 8 spread a head's blocks over the XCDs: fewer workgroups there.
+//   d = 128, up to 256 positions: 230 workgroups 31.8 / 33.8 (200 positions), 255 42.6 / 44.4 (384) but 208 (of 104 heads) 35.8 / 33.8 (256)
+//   d = 64, one row block: 360 22.0 / 20.7 (100), 402 26.0 / 27.0 (128), 462 15.6 / 18.0 (64), 536 22.0 / 19.2 (64; both take two rounds), 765
+//            23.5 / 25.7 (64); two: 500 22.8 / 25.5 (147); up to 448 positions: 662 28.9 / 30.6 (129), 723 43.1 / 45.3 (300), 956 64.6 / 66.3 (448)
+//            but 640 (of 160 heads) 45.4 / 38.7 (400)
+bool bwd_together(int b, int S, int nq, int nkv, int d) {
+  const int64_t heads = int64_t(b) * nq, wgs = heads * ((S + 127) / 128);
+  const bool own_xcd = heads % 8 == 0;
+  if (nq > nkv) return wgs <= (d == 64 ? (S > 128 ? 1024 : 768) : (S > 128 ? 256 : 128));
+  if (d == 128) return wgs <= (S <= 128 ? 128 : own_xcd ? 256 : S <= 256 ? 200 : 250);
+  if (S <= 128) return wgs <= 360 || (wgs > 512 && wgs <= (own_xcd ? 700 : 620));
+  if (S <= 256 && wgs > 420 && wgs <= 512) return false;
+  return wgs <= (S <= 448 && !own_xcd ? 600 : 1024);
 }
 
 // dQ from dS as the dK / dV kernel leaves it in memory, instead of a kernel that forms S, P and dP once more: two of its three
@@ -1432,8 +1443,9 @@ bool bwd_together(int b, int S, int nq, int d) {
 // keeps dQ out of the launch of dK and dV (up to 256: 2048 positions, 16 heads of 128 120 twice, 98.5 once, 83.5 together).  Whole backward,
 // dS formed once / in one launch (us): 20 heads of 128 over 4 at 2048 positions 115 / 123, 32 over 8 at 1280 86 / 91; twice / once with more
 // workgroups: 32 at 2048 152 / 146 (nothing is left of it in a whole step), 48 at 2048 233 / 236, 32 at 4096 461 / 476.
-bool dq_from_ds(int b, int S, int nq, int d) {
-  return d == 128 && S >= 256 && !bwd_together(b, S, nq, d) && int64_t(b) * nq * ((S + 127) / 128) <= 320 && ds_head_bytes(S) * nq * b <= int64_t(256) << 20;
+bool dq_from_ds(int b, int S, int nq, int nkv, int d) {
+  return d == 128 && S >= 256 && !bwd_together(b, S, nq, nkv, d) && int64_t(b) * nq * ((S + 127) / 128) <= 320 &&
+         ds_head_bytes(S) * nq * b <= int64_t(256) << 20;
 }
 
 // partial sums of dK and dV, then dS
@@ -1444,7 +1456,7 @@ size_t part_floats(int b, int S, int nq, int nkv, int d) {
 size_t attn_bwd_scratch_floats(int dt, int b, int S, int nq, int nkv, int d) {
   if (nkv <= 0 || nq % nkv) return 0;
   if (dt != DT_BF16) return attn_bwd_f32_scratch_floats(b, S, nq, nkv, d);
-  return part_floats(b, S, nq, nkv, d) + (dq_from_ds(b, S, nq, d) ? size_t(ds_head_bytes(S)) / 4 * nq * b : 0);
+  return part_floats(b, S, nq, nkv, d) + (dq_from_ds(b, S, nq, nkv, d) ? size_t(ds_head_bytes(S)) / 4 * nq * b : 0);
 }
 
 hipError_t attn_bwd_bf16(const void* qkv, int64_t ld_qkv, const void* o, int64_t ld_o, const float* lse, const void* d_o,
@@ -1454,10 +1466,10 @@ hipError_t attn_bwd_bf16(const void* qkv, int64_t ld_qkv, const void* o, int64_t
   if (!cos_tab != !sin_tab) return hipErrorInvalidValue;
   if (d != 128 && d != 64) return hipErrorInvalidValue;
   const DkvPlan pl = dkv_plan(b, S, nq, nkv, d);
-  char* ds = part && dq_from_ds(b, S, nq, d) ? reinterpret_cast<char*>(part + part_floats(b, S, nq, nkv, d)) : nullptr;
+  char* ds = part && dq_from_ds(b, S, nq, nkv, d) ? reinterpret_cast<char*>(part + part_floats(b, S, nq, nkv, d)) : nullptr;
   const int ns = part ? pl.ns : 1, kt = ds ? 1 : pl.kt;  // (so few workgroups always get one key tile: their longest chain decides)
   dim3 gq(nq, (S + 127) / 128, b), gk(nkv * ns, (S + 128 * kt - 1) / (128 * kt), b);
-  if (bwd_together(b, S, nq, d)) {
+  if (bwd_together(b, S, nq, nkv, d)) {
     auto stat = d == 128 ? attn_stats_kernel<128> : attn_stats_kernel<64>;
     auto bwd = d == 128 ? attn_bwd_kernel<128> : attn_bwd_kernel<64>;
     hipLaunchKernelGGL(stat, dim3(nq, (S + 63) / 64, b), dim3(AT_THREADS), 0, st, (const bf16_t*)o, ld_o, (const bf16_t*)d_o, ld_do, lse, stats, S, nq);

@@ -86,19 +86,25 @@ def test_forward_kernels_on_either_side_of_their_rule(nq, nkv, d, seq, mb, pairs
     test_attention_against_fp64_on_the_same_operands(nq, nkv, d, seq, mb, 8.0)
 
 
-# How the backward's kernels are launched: dQ, dK and dV together up to a number of workgroups, dQ from the stored dS a little beyond it
-# (heads of 128, 256 positions and more), else apart.
+# How the backward's kernels are launched: dQ, dK and dV together up to a number of workgroups (fewer where every query head has KV heads of its
+# own), dQ from the stored dS a little beyond it (heads of 128, 256 positions and more), else apart.
 @pytest.mark.parametrize("nq,nkv,d,seq,mb,together,from_ds", [
     (3, 1, 64, 64, 2, True, False), (6, 2, 64, 193, 1, True, False), (16, 1, 128, 33, 8, True, False), (16, 4, 128, 128, 9, False, False),
     (43, 43, 128, 129, 3, False, False), (16, 8, 128, 161, 8, True, False), (22, 11, 128, 385, 3, False, True), (80, 16, 128, 260, 1, True, False),
-    (24, 24, 64, 97, 32, True, False), (24, 8, 64, 97, 33, False, False), (32, 16, 64, 129, 16, True, False), (32, 16, 64, 129, 17, False, False)])
+    (24, 24, 64, 97, 32, False, False), (24, 8, 64, 97, 32, True, False), (24, 8, 64, 97, 33, False, False), (32, 16, 64, 129, 16, True, False),
+    (32, 16, 64, 129, 17, False, False), (16, 16, 128, 33, 8, True, False), (43, 43, 128, 33, 3, False, False), (50, 50, 128, 200, 2, True, False),
+    (51, 51, 128, 200, 2, False, False), (13, 13, 128, 256, 8, True, False), (83, 83, 128, 257, 1, True, False), (17, 17, 128, 257, 5, False, True),
+    (45, 45, 64, 65, 8, True, False), (46, 46, 64, 65, 8, False, False), (57, 57, 64, 33, 9, True, False), (39, 39, 64, 33, 16, True, False),
+    (69, 69, 64, 33, 9, False, False), (39, 39, 64, 33, 18, False, False), (42, 42, 64, 129, 5, True, False), (43, 43, 64, 129, 5, False, False),
+    (60, 60, 64, 129, 5, True, False), (43, 43, 64, 129, 7, False, False),
+    (19, 19, 64, 129, 16, True, False)])
 def test_backward_launches_on_either_side_of_their_rules(nq, nkv, d, seq, mb, together, from_ds):
     import ctypes
     import paper_2410_13333_amd as mls
-    for name, want in (("_ZN3mls12bwd_togetherEiiii", together), ("_ZN3mls10dq_from_dsEiiii", from_ds)):
+    for name, want in (("_ZN3mls12bwd_togetherEiiiii", together), ("_ZN3mls10dq_from_dsEiiiii", from_ds)):
         f = getattr(mls.lib(), name)
         f.restype = ctypes.c_bool
-        assert f(mb, seq, nq, d) is want
+        assert f(mb, seq, nq, nkv, d) is want
     test_attention_against_fp64_on_the_same_operands(nq, nkv, d, seq, mb, 1.0)
 
 
