@@ -446,15 +446,28 @@ hipError_t attn_fwd_f32(const void* qkv, int64_t ld_qkv, void* o, int64_t ld_o, 
   });
 }
 
-// dQ, dK and dV in one launch up to 544 blocks of query rows, a good two per CU; with more of them the rows of O that the dK / dV part reads
-// for delta, and the registers that part costs the other, outweigh what the balance gains.  Backward (us, apart / together): 16 heads of 64
-// over 2 x 256 positions 56 / 30, 3 over 1 at 2 x 384 100 / 39, 36 at 384 (432 blocks) 79 / 75, 24 over 12 at 700 (528) 145 / 123, 16 at 1500
-// (752) 282 / 353.
-bool bwd_f32_together(int b, int S, int nq) { return int64_t(b) * nq * ((S + 31) / 32) <= 544; }
-// The query heads of a group apart where their key blocks alone would leave CUs without one: a float of workspace per element of dK and dV
-// and query head.
+// dQ, dK and dV in one launch, by blocks of 32 query rows, a workgroup each and as many for the key rows; a CU has a place for one.  Many more of
+// them than places balance by themselves, and then the rows of O that the dK / dV part reads for delta, and the registers that part costs the
+// other, outweigh what the balance gains; so do two rounds of short chains instead of one for either part.  Backward, us, apart / together:
+//   d <= 64: 250 blocks (1598 positions) 165 / 107, 246 (176) 38.7 / 37.7 but 252 (100) 26.4 / 28.9, 384 (252) 59 / 53, 400 (1592) 117 / 126, 456 (58) 43.5 / 48.3,
+//            483 (203) 34.6 / 40.2; wider: 265 (150) 110 / 75, 270 (1433) 360 / 287, 300 (633) 185 / 200, 364 (210) 143 / 119, 425 (796) 268 / 319,
+//            476 of 80 (888) 170 / 199, 516 of 112 (115) 162 / 122
+//   grouped: 24 heads over 12 at 700 positions (528 blocks) 145 / 123, 22 over 11 of 112 at 856 (594) 400 / 584, 2 x 64 over 32 at 118 (512) 23.5 / 26.2
+bool bwd_f32_together(int b, int S, int nq, int nkv, int d) {
+  const int64_t n = (S + 31) / 32, q = int64_t(b) * nq * n, k = int64_t(b) * nkv * n;
+  if (nq > nkv) return q <= 544 && (k < 256 || n > 4);
+  if (q > 180 && q <= 256 && n <= 4) return false;
+  if (d <= 64) return q <= 384;
+  return q <= 288 || (d <= 96 ? q <= 400 && n <= 8 : q <= 544 && n <= 12);
+}
+// The query heads of a group apart where that shortens a chain of key blocks by more than the additional workgroups and the sum cost: us, in one
+// workgroup / apart: 8 heads over 1 at 563 positions (144 blocks, chains of 18 blocks x 8 heads) 297 / 55, 4 over 1 at 437 (448, 56) 122 / 83, 2
+// over 1 at 246 (16, 16) 40.6 / 26.9 but at 38 (168, 4) 9.1 / 16.1, 42 (384, 4) 28.4 / 39.9, 4 over 1 at 83 (480, 12) 34 / 54.  A float of workspace per
+// element of dK and dV and query head.
 size_t attn_bwd_f32_scratch_floats(int b, int S, int nq, int nkv, int d) {
-  return nq > nkv && bwd_f32_together(b, S, nq) && int64_t(b) * nkv * ((S + 31) / 32) < 256 ? size_t(2) * b * nq * S * d : 0;
+  const int64_t n = (S + 31) / 32, q = int64_t(b) * nq * n, chain = n * (nq / nkv);
+  const bool apart = nq > nkv && chain > 4 && (q <= 180 || 16 * chain >= q) && int64_t(b) * nkv * n < 256;
+  return apart && bwd_f32_together(b, S, nq, nkv, d) ? size_t(2) * b * nq * S * d : 0;
 }
 
 hipError_t attn_bwd_f32(const void* qkv, int64_t ld_qkv, const void* o, int64_t ld_o, const float* lse, const void* d_o,
@@ -466,7 +479,7 @@ hipError_t attn_bwd_f32(const void* qkv, int64_t ld_qkv, const void* o, int64_t 
   const Unrotate un = {cos_tab, sin_tab};
   return for_tiles(d, [&](auto DTC) {
     constexpr int DT = decltype(DTC)::value;
-    if (!bwd_f32_together(b, S, nq)) {
+    if (!bwd_f32_together(b, S, nq, nkv, d)) {
       hipLaunchKernelGGL(attn_dq_f32_kernel<DT>, dim3(n * nq * b), dim3(256), 0, st, (const float*)qkv, ld_qkv, (const float*)o, ld_o, lse,
                          (const float*)d_o, ld_do, delta, (float*)dqkv, ld_dqkv, b, S, nq, nkv, d, un);
       hipLaunchKernelGGL(attn_dkv_f32_kernel<DT>, dim3(n * nkv * b), dim3(256), 0, st, (const float*)qkv, ld_qkv, lse, (const float*)d_o, ld_do, delta,

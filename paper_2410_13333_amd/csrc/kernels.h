@@ -247,7 +247,7 @@ size_t attn_bwd_f32_scratch_floats(int b, int S, int nq, int nkv, int d);
 hipError_t attn_bwd_f32(const void* qkv, int64_t ld_qkv, const void* o, int64_t ld_o, const float* lse, const void* d_o,
                         int64_t ld_do, void* dqkv, int64_t ld_dqkv, float* delta, int b, int S, int nq, int nkv, int d, hipStream_t st, float* part,
                         const float* cos_tab, const float* sin_tab);
-bool bwd_f32_together(int b, int S, int nq);  // whether its dQ, dK and dV share a launch.  Host only.
+bool bwd_f32_together(int b, int S, int nq, int nkv, int d);  // whether its dQ, dK and dV share a launch.  Host only.
 hipError_t attn_fwd_bf16(const void* qkv, int64_t ld_qkv, void* o, int64_t ld_o, float* lse, int b, int S, int nq, int nkv,
                          int d, hipStream_t st);
 hipError_t attn_bwd_bf16(const void* qkv, int64_t ld_qkv, const void* o, int64_t ld_o, const float* lse, const void* d_o,

@@ -106,17 +106,21 @@ def test_weight_gradients_over_many_micro_batches(hidden, ffn, seq, n):
             assert e <= 1e-5
 
 
-# the backward in one launch, up to 544 blocks of 32 query rows, and apart; the query heads of a group apart (fewer than 256 blocks of key rows)
-# or in one workgroup
+# the backward in one launch, up to a number of blocks of 32 query rows that depends on the head width, the blocks of a sequence and the grouping,
+# or apart; the query heads of a group apart, where their key blocks are few and long, or in one workgroup
 @pytest.mark.parametrize("nq,nkv,d,seq,mb,together,apart", [
     (6, 2, 64, 33, 1, True, True), (6, 3, 80, 97, 3, True, True), (34, 17, 64, 481, 1, True, False), (34, 17, 64, 513, 1, False, False),
-    (16, 15 + 1, 64, 200, 2, True, False), (32, 8, 16, 250, 2, True, True), (3, 1, 128, 160, 2, True, True), (46, 23, 128, 129, 3, False, False)])
+    (16, 15 + 1, 64, 200, 2, True, False), (32, 8, 16, 250, 2, True, True), (3, 1, 128, 160, 2, True, True), (46, 23, 128, 129, 3, False, False),
+    (8, 4, 64, 32, 1, True, False), (45, 15, 16, 128, 1, True, True), (46, 23, 16, 128, 1, True, False), (64, 32, 32, 118, 2, False, False),
+    (45, 45, 64, 128, 1, True, False), (46, 46, 64, 128, 1, False, False), (51, 51, 32, 160, 1, True, False), (48, 48, 48, 256, 1, True, False),
+    (49, 49, 48, 256, 1, False, False), (32, 32, 80, 288, 1, True, False), (33, 33, 80, 288, 1, False, False), (57, 57, 96, 224, 1, True, False),
+    (58, 58, 96, 224, 1, False, False), (45, 45, 112, 384, 1, True, False), (46, 46, 112, 384, 1, False, False), (41, 41, 112, 416, 1, False, False)])
 def test_backward_launches_on_either_side_of_their_rules(nq, nkv, d, seq, mb, together, apart):
     import ctypes
     import paper_2410_13333_amd as mls
-    f, w = mls.lib()._ZN3mls16bwd_f32_togetherEiii, mls.lib()._ZN3mls27attn_bwd_f32_scratch_floatsEiiiii
+    f, w = mls.lib()._ZN3mls16bwd_f32_togetherEiiiii, mls.lib()._ZN3mls27attn_bwd_f32_scratch_floatsEiiiii
     f.restype, w.restype = ctypes.c_bool, ctypes.c_size_t
-    assert f(mb, seq, nq) is together and (w(mb, seq, nq, nkv, d) > 0) is apart
+    assert f(mb, seq, nq, nkv, d) is together and (w(mb, seq, nq, nkv, d) > 0) is apart
     test_stage_fp32_against_the_exact_oracle(nq, nkv, d, seq, mb)
 
 
