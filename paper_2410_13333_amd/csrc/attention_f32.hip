@@ -449,8 +449,8 @@ hipError_t attn_fwd_f32(const void* qkv, int64_t ld_qkv, void* o, int64_t ld_o, 
 // dQ, dK and dV in one launch, by blocks of 32 query rows, a workgroup each and as many for the key rows; a CU has a place for one.  Many more of
 // them than places balance by themselves, and then the rows of O that the dK / dV part reads for delta, and the registers that part costs the
 // other, outweigh what the balance gains; so do two rounds of short chains instead of one for either part.  Backward, us, apart / together:
-//   d <= 64: 250 blocks (1598 positions) 165 / 107, 246 (176) 38.7 / 37.7 but 252 (100) 26.4 / 28.9, 384 (252) 59 / 53, 400 (1592) 117 / 126, 456 (58) 43.5 / 48.3,
-//            483 (203) 34.6 / 40.2; wider: 265 (150) 110 / 75, 270 (1433) 360 / 287, 300 (633) 185 / 200, 364 (210) 143 / 119, 425 (796) 268 / 319,
+//   d <= 64: 250 blocks (1598 positions) 165 / 107, 246 (176) 38.7 / 37.7 but 252 (100) 26.4 / 28.9, 384 (252) 59 / 53, 400 (1592) 112 / 121, 456 (58) 43.5 / 48.3,
+//            483 (203) 34.6 / 40.2; wider: 265 (150) 110 / 75, 270 (1410) 360 / 287, 300 (633) 185 / 200, 364 (210) 143 / 119, 425 (796) 268 / 319,
 //            476 of 80 (888) 170 / 199, 516 of 112 (115) 162 / 122
 //   grouped: 24 heads over 12 at 700 positions (528 blocks) 145 / 123, 22 over 11 of 112 at 856 (594) 400 / 584, 2 x 64 over 32 at 118 (512) 23.5 / 26.2
 bool bwd_f32_together(int b, int S, int nq, int nkv, int d) {

@@ -14,6 +14,7 @@
 // some 130 instructions per piece.  us, before -> after, the same bits: 512 x 512 x 2752 21.0 -> 16.9, 96 x 512 x 2048 17.1 -> 12.2,
 // 1000 x 4096 x 1024 83 -> 73.5 (114 TFLOP/s; these MFMAs alone reach 131 to 137), weight gradient 1024 x 2752 over 1000 tokens 73 -> 59.  Deeper rings
 // (four pieces per wavefront, one workgroup per CU: 1000 x 4096 x 1024 77), three workgroups per CU and tiles dealt out by XCD gave nothing.
+#include <algorithm>
 #include <type_traits>
 
 #include "common.h"
@@ -440,21 +441,18 @@ hipError_t launch_f32(const float* A, const float* B, float* C, const float* R, 
 
 namespace mls {
 
-// The 64x64 tiles read half as much per product; the 32x32 ones are four times as many, two of them on a CU at a time, and their
-// wavefronts take every fourth piece.  So the large ones where they are many, and, of a short contraction, where the small ones
-// would queue for the CUs or leave wavefronts without a piece.  us, 32x32 / 64x64: 1000 x 4096 x 1024 (1024 big tiles) 92 / 72.6,
-// 1024 x 2752 x 768 (688) 55.0 / 45.2, 512 x 2752 x 512 (344) 22.8 / 22.1, 1152 x 1024 x 768 (288) 24.7 / 28.8, 512 x 512 x 2752 (64) 17.4 / 48;
-// by rows 768 x 768 (144 big tiles, 576 small) over 64 7.2 / 5.1, over 256 9.1 / 8.0, over 384 10.8 / 9.9, over 400 13.0 / 10.7, over
-// 512 12.2 / 11.9; 1024 x 1024 (256, 1024) over 64 8.0 / 5.3; 512 x 1024 (128, 512) over 64 5.0 / 5.0, over 256 6.3 / 7.9.
-// And where a CU gets at most one large tile, but three or four small ones, of which only two have a place at once (one round): 1024 x 1024
-// over 512 16.3 / 12.8, over 2752 60.3 / 49.8, 1024 x 768 (192, 768) over 512 12.8 / 12.5, over 1376 31.6 / 26.4, 512 x 1376 (172, 688) over 512
-// 14.6 / 12.2; not 1024 x 704 over 1376 25.2 / 26.5, 1024 x 576 (144, 576) over 768 16.5 / 16.9, nor where the large tiles are mostly edge: 200 x 3200
-// (200, 700) over 640 14.0 / 14.9.  (1152 x 768 over 4096, 82 / 70, stays on the small ones, as a test has it.)
+// The 64x64 tiles read half as much per product, one to a CU (a second one shares its matrix cores); the 32x32 ones are four times as many, two of
+// them on a CU at a time, and their wavefronts take every fourth piece.  Microseconds as rounds times a tile's chain, fitted to both tile
+// sizes at 1 609 shapes (48 to 3000 rows, 64 to 4400 columns, contractions of 64 to 5000); the fullest CU counts more than the average one.  The
+// choice is on average 0.3 % slower than the faster of the two.  us, 32x32 / 64x64: 1000 x 4096 x 1024 (1024 large tiles) 92 / 74, 512 x 2752 x 512
+// (344) 23.0 / 22.4, 288 x 4096 x 4672 (320) 120 / 156, 1152 x 1024 x 768 (288) 24.7 / 29.0, 1024 x 1024 (256, 1024 small) over 64 8.3 / 5.6, over
+// 512 15.7 / 12.4, over 2752 59 / 49, 1152 x 768 (216, 864) over 4096 83 / 70, 1024 x 704 (176, 704) over 768 19.4 / 17.2, over 1376 25.3 / 26.5, 768 x 768
+// (144, 576) over 256 9.2 / 8.1, over 512 12.3 / 12.0, 512 x 1024 (128, 512) over 256 6.2 / 8.3, 512 x 512 x 2752 (64, 256) 16.9 / 47.6.
 bool gemm_f32_large(int M, int N, int K) {
-  const int64_t big = int64_t((M + 63) / 64) * ((N + 63) / 64), small = int64_t((M + 31) / 32) * ((N + 31) / 32);
-  const int pieces = (K + KC - 1) / KC;
-  const bool one_round = big <= 256 && 40 * big <= 11 * small && pieces <= 96 && small > (pieces <= 24 ? 640 : 704);
-  return big >= 320 || one_round || (small > 512 && (pieces <= 8 || (pieces < 16 && pieces % 4)));
+  auto up = [](int64_t v, int64_t t) { return (v + t - 1) / t; };
+  const int64_t big = up(M, 64) * up(N, 64), small = up(M, 32) * up(N, 32), pieces = up(K, KC);
+  const double load = 0.8 * double(up(small, 256)) + 0.2 * std::max(1.0, double(small) / 256);
+  return 2 + 0.54 * double(pieces * up(big, 256)) < (0.72 * double(up(pieces, 4)) + 0.9) * load;
 }
 
 // M, N and row strides multiples of 8, operands 16-byte aligned (as every entry point checks); K a multiple of 8 in the

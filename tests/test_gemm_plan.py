@@ -97,11 +97,13 @@ def test_a_cu_with_a_workgroup_more_than_the_others_counts(M, N, K, us):
         assert mls.gemm_plan(mode, M, N, K) == (0, 128, 128), us
 
 
-# fp32: 64x64 tiles from 320 on; of a short contraction also where more 32x32 tiles than two per CU would queue (us, 32x32 / 64x64)
+# fp32: 64x64 tiles where their rounds of whole chains are estimated shorter than those of the 32x32 ones (us, 32x32 / 64x64)
 @pytest.mark.parametrize("M,N,K,large", [
-    (768, 768, 64, True), (2120, 232, 24, True), (1536, 768, 128, True), (768, 768, 256, True), (768, 768, 400, True),  # 7.4 / 5.0, 9.9 / 5.6, 11.2 / 9.0, 9.5 / 9.2, 14.2 / 13.0
-    (768, 768, 384, False), (768, 768, 512, False), (1152, 768, 4096, False),                                        # 11.9 / 12.1, 13.8 / 15.1, 98 / 104
-    (512, 1024, 256, False), (256, 256, 256, False), (512, 2752, 512, True)])                                        # 6.6 / 9.1, 5.3 / 9.3, 27.4 / 26.7
+    (768, 768, 64, True), (2120, 232, 24, True), (1536, 768, 128, True), (768, 768, 256, True), (768, 768, 400, True),  # 7.2 / 5.9, 7.2 / 5.8, 11.2 / 8.9, 9.2 / 8.1, 13.1 / 10.8
+    (768, 768, 384, True), (768, 768, 512, True), (1152, 768, 4096, True), (1024, 704, 768, True),                    # 10.9 / 10.1, 12.3 / 12.0, 83 / 70, 19.4 / 17.2
+    (2568, 264, 1064, True), (1016, 1024, 3080, True), (1000, 4096, 1024, True),                                      # 29.3 / 22.1, 67 / 55, 92 / 74
+    (512, 1024, 256, False), (256, 256, 256, False), (512, 2752, 512, True), (512, 512, 2752, False),                 # 6.2 / 8.3, 5.8 / 7.9, 23.0 / 22.4, 16.9 / 47.6
+    (1152, 1024, 768, False), (1024, 576, 768, False), (288, 4096, 4672, False), (624, 2048, 1984, False)])           # 24.7 / 29.0, 16.0 / 16.6, 120 / 156, 58 / 68
 def test_fp32_tiles(M, N, K, large):
     f = mls.lib()._ZN3mls14gemm_f32_largeEiii
     f.restype = ctypes.c_bool

@@ -24,10 +24,9 @@ def test_stage_fp32_against_the_exact_oracle(nq, nkv, d, seq, mb):
         assert e <= 1e-5
 
 
-# either side of the rule for 64x64 tiles that fill the chip at most once
-@pytest.mark.parametrize("M,N,K,large", [(1024, 1024, 512, True), (512, 1376, 768, True), (512, 1376, 776, False), (1024, 720, 1376, True),
-                                         (1024, 704, 1376, False), (1016, 1024, 3072, True), (1016, 1024, 3080, False), (200, 3200, 640, False),
-                                         (1032, 1024, 512, False)])
+# either side of the rule for 64x64 tiles that fill the chip at most once, and of a second round of them
+@pytest.mark.parametrize("M,N,K,large", [(1024, 1024, 512, True), (512, 1376, 776, True), (1024, 720, 1376, True), (1024, 576, 1376, False),
+                                         (1016, 1024, 3080, True), (1024, 512, 512, False), (1032, 1024, 512, False), (1032, 1024, 64, True)])
 def test_gemm_fp32_on_one_round_of_large_tiles(M, N, K, large):
     import ctypes
     import paper_2410_13333_amd as mls
