@@ -189,8 +189,8 @@ int mls_stage_debug_read(mls_stage* s, int32_t tensor_id, int32_t layer, int32_t
  * per class into two HOST arrays of MLS_TIMING_CLASSES entries (order: GEMM forward, GEMM data-gradient, GEMM
  * weight-gradient, attention forward, attention backward, RMSNorm, rotary, SwiGLU) and clears the accumulators.  A step
  * that runs fused into a neighbouring kernel is counted with that kernel's class and leaves its own class at zero: the
- * rotary steps and SwiGLU (with bf16 storage unless an operand has 2 GiB or more, and SwiGLU backward where no 256x256
- * tile takes part in the product before it) and, where the weight gradients of a layer share a launch, the sums of its
+ * rotary steps and SwiGLU (with bf16 storage unless an operand has 2 GiB or more, and SwiGLU backward where the
+ * product before it runs on smaller tiles than 256x256, whole ones if larger than 128x64) and, where the weight gradients of a layer share a launch, the sums of its
  * gain gradients (else RMSNorm's class).
  * Errors: MLS_E_NULL, MLS_E_HIP. */
 #define MLS_TIMING_CLASSES 8

@@ -498,7 +498,7 @@ hipError_t launch_t16_as(const Args& a) {
 template <int WTM, int WTN, int WGM, bool ATR, bool BTR, int EPI, bool SEG, int NS>
 hipError_t launch_t16(const Args& a) {
   if (a.split.parts <= 1) return launch_t16_as<WTM, WTN, WGM, ATR, BTR, EPI, SEG, NS, false>(a);
-  if constexpr (!ATR && !BTR) {
+  if constexpr (!ATR && !BTR && (EPI != E_DSWIGLU || WTM * WTN < 16)) {
     if (a.split.parts > (WTM * WTN >= 32 ? 2 : 8) || a.split.parts > (a.K + BK - 1) / BK || !a.split.sums) return hipErrorInvalidValue;
     return launch_t16_as<WTM, WTN, WGM, ATR, BTR, EPI, SEG, NS, true>(a);
   }

@@ -142,7 +142,7 @@ bool gemm_swiglu_ok(int M, int f, int K, int64_t lda, int64_t ldw);
 hipError_t gemm_bf16_swiglu(const void* A, const void* W, void* GU, void* Z, int M, int f, int K, int64_t lda,
                             int64_t ldw, int64_t ldgu, int64_t ldz, hipStream_t st, const SplitSpace& split = {});
 // The SwiGLU backward fused into the data gradient of the down-projection (bf16, f % 8 == 0, DMA path), where all of that product runs on
-// the smaller tiles (gemm_dswiglu_ok; host only): dZ[M, f] = dY[M,K] W[f,K]^T stays in registers,
+// the smaller tiles, the larger of them whole (gemm_dswiglu_ok; host only): dZ[M, f] = dY[M,K] W[f,K]^T stays in registers,
 //   DGU[M, 2f] = (dZ up silu'(gate), dZ silu(gate)), GU and DGU in the interleaved order.
 bool gemm_dswiglu_ok(int M, int f, int K, int64_t lda, int64_t ldw, bool split);
 hipError_t gemm_bf16_dswiglu(const void* dY, const void* W, const void* GU, void* DGU, int M, int f, int K, int64_t lda, int64_t ldw,

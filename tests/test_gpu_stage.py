@@ -616,16 +616,17 @@ def test_weight_gradients_that_share_a_launch_of_256x256_tiles(hidden, nq, nkv, 
     test_weight_gradients_of_a_layer_in_one_launch(hidden, nq, nkv, d, ffn, seq, mb, n)
 
 
-# hidden, ffn, tokens -> (columns on 256x256 tiles, parts there, tile rows, columns, parts) of the down-projection's data gradient
+# hidden, ffn, tokens -> (columns on 256x256 tiles, parts there, tile rows, columns, parts) of the down-projection's data gradient, and whether
+# the SwiGLU backward is its epilogue
 DSWIGLU_TILES = [
-    ((72, 72, 65), (0, 1, 64, 64, 1)), ((2056, 72, 65), (0, 1, 64, 64, 3)), ((72, 1384, 2049), (0, 1, 128, 64, 1)),
-    ((4104, 680, 1000), (0, 1, 128, 64, 2)), ((520, 1384, 2049), (0, 1, 128, 128, 1)), ((4104, 8200, 65), (0, 1, 128, 128, 3)),
-    ((72, 2728, 2049), (0, 1, 256, 128, 1)), ((72, 8200, 2049), (7168, 1, 64, 64, 1))]
+    ((72, 72, 65), (0, 1, 64, 64, 1), True), ((2056, 72, 65), (0, 1, 64, 64, 3), True), ((72, 1384, 2049), (0, 1, 128, 64, 1), True),
+    ((4104, 680, 1000), (0, 1, 128, 64, 2), True), ((520, 1384, 2049), (0, 1, 128, 128, 1), True), ((4104, 8200, 65), (0, 1, 128, 128, 3), False),
+    ((72, 2728, 2049), (0, 1, 256, 128, 1), True), ((72, 8200, 2049), (7168, 1, 64, 64, 1), False)]
 
 
-@pytest.mark.parametrize("shape,plan", DSWIGLU_TILES)
-def test_swiglu_backward_on_every_plan(shape, plan):
-    """In the epilogue of the product on every smaller tile, whole and shared out; as a kernel of its own where 256x256 tiles take part.
+@pytest.mark.parametrize("shape,plan,fused", DSWIGLU_TILES)
+def test_swiglu_backward_on_every_plan(shape, plan, fused):
+    """In the epilogue of the product on every smaller tile, the smallest ones shared out too; as a kernel of its own otherwise.
     The product is rounded to bf16, then the results: relative error below 2^-8 + 2^-8 in every element, a third of it in the norm."""
     import torch
     import paper_2410_13333_amd as mls
@@ -637,7 +638,9 @@ def test_swiglu_backward_on_every_plan(shape, plan):
     g, dx = torch.zeros(st.grad_elems, device="cuda"), torch.empty_like(dy)
     st.forward(x, 1, torch.empty_like(x))
     gu = st.debug_read("gu").double()
+    st.timing(True)
     st.backward(dy, g, 1, dx)
+    assert st.timing_read()["swiglu"][1] == (0 if fused else 1)
     dgu = st.debug_read("dgu").double()
     off, r, c = st.param_layout(0, "w_d")
     w_d = st.get_params()[off:off + r * c].double().reshape(r, c)
