@@ -386,7 +386,7 @@ def main():
 
     flops_step = sh.model_flops_layer_mb() * K * M
     tflops = flops_step / (ms * 1e-3) / 1e12
-    # dominant kernel: the bf16 MFMA GEMM (per layer: 8 launches per micro-batch + 4 weight-gradient launches)
+    # dominant kernel: the bf16 MFMA GEMM (per layer: 8 launches per micro-batch + 1 of the weight gradients, 4 where they run apart)
     gemm_ms = sum(tm[k][0] for k in ("gemm_fwd", "gemm_dgrad", "gemm_wgrad"))
     gemm_n = sum(tm[k][1] for k in ("gemm_fwd", "gemm_dgrad", "gemm_wgrad"))
     # algorithmic FLOPs of all GEMM launches of the timed steps / their summed duration; per launch = / launches

@@ -184,8 +184,8 @@ int mls_stage_debug_read(mls_stage* s, int32_t tensor_id, int32_t layer, int32_t
 /* Per-kernel-class timing with HIP events recorded on the stage's stream, for the benchmark's roofline figure.
  * enable != 0 brackets every step of forward/backward with a pair of events (no synchronisation unless more than
  * 4096 are pending) and counts it as one launch: a contraction of two tile sizes runs as two kernels and counts once,
- * the weight gradients of a layer count once where they share a kernel and once each where they do not or share one of 256x256 tiles;
- * enable = 0 stops it.  mls_stage_timing_read synchronises on the last event, writes the accumulated milliseconds and launch counts
+ * the weight gradients of a layer count once where they share a launch (mls_stage_wgrad_launch) and once each where they
+ * do not; enable = 0 stops it.  mls_stage_timing_read synchronises on the last event, writes the accumulated milliseconds and launch counts
  * per class into two HOST arrays of MLS_TIMING_CLASSES entries (order: GEMM forward, GEMM data-gradient, GEMM
  * weight-gradient, attention forward, attention backward, RMSNorm, rotary, SwiGLU) and clears the accumulators.  A step
  * that runs fused into a neighbouring kernel is counted with that kernel's class and leaves its own class at zero: the
@@ -215,10 +215,18 @@ int mls_gemm(int32_t dtype, int32_t mode, const void* A, int64_t lda, const void
  * Operands of 2 GiB and more run on a kernel of their own.  Errors: MLS_E_NULL, MLS_E_CONFIG. */
 int mls_gemm_plan(int32_t mode, int64_t M, int64_t N, int64_t K, int64_t* big_cols, int32_t* tile_rows, int32_t* tile_cols);
 
-/* The same for the weight gradients of a layer in mls_stage_backward_ex over n_microbatches with these flags: the tile of the launch that all
- * four share, or 0 x 0 if each has launches of its own (then mls_gemm_plan with mode 2 and K = tokens of all micro-batches
- * tells their tiles; 16 micro-batches go into a launch) or they share one of 256x256 tiles (mls_stage_timing counts four then too).  bf16 storage; with fp32 storage the four always share one, and 0 x 0 is reported.
- * Errors: MLS_E_NULL, MLS_E_CONFIG, MLS_E_RANGE. */
+/* How the weight gradients of a layer run in mls_stage_backward_ex over n_microbatches with these flags (16 micro-batches go into a
+ * launch).  Where they do not share one, mls_gemm_plan with mode 2 and K = tokens of all micro-batches tells each one's tiles.
+ * Host only.  Errors: MLS_E_NULL, MLS_E_CONFIG, MLS_E_RANGE. */
+typedef struct {
+  int32_t shared;                            /* 1: the four share a launch (fp32 storage: always), 0: each has launches of its own */
+  int32_t tile_rows, tile_cols;              /* the tiles of the shared launch, else 0 x 0 */
+  int32_t split;                             /* 0 w_d, 1 w_gu, 2 w_o, 3 w_qkv: its columns from split_col on run in a launch of */
+  int32_t split_col, rest_rows, rest_cols;   /* rest_rows x rest_cols tiles behind the shared one; -1: no such columns (then all 0) */
+} mls_wgrad_launch;
+int mls_stage_wgrad_launch(const mls_config* cfg, int32_t n_microbatches, int32_t flags, mls_wgrad_launch* out);
+
+/* The tile of a shared launch on tiles smaller than 256x256 (bf16 storage), 0 x 0 in every other case.  Errors: as above. */
 int mls_stage_wgrad_plan(const mls_config* cfg, int32_t n_microbatches, int32_t flags, int32_t* tile_rows, int32_t* tile_cols);
 
 /* The same for the products of a layer's forward and data gradient over one micro-batch (bf16 storage; product 0 .. 7: q|k|v, o,

@@ -32,6 +32,10 @@ class MlsMemory(C.Structure):
                 ("grad_bytes_per_layer", C.c_size_t), ("stash_bytes_per_layer_microbatch", C.c_size_t)]
 
 
+class MlsWgradLaunch(C.Structure):
+    _fields_ = [(n, C.c_int32) for n in ("shared", "tile_rows", "tile_cols", "split", "split_col", "rest_rows", "rest_cols")]
+
+
 class MlsEndsConfig(C.Structure):
     _fields_ = [("hidden", C.c_int32), ("vocab", C.c_int32), ("seq", C.c_int32), ("micro_batch", C.c_int32),
                 ("max_inflight", C.c_int32), ("rms_eps", C.c_float), ("dtype", C.c_int32)]
@@ -80,6 +84,7 @@ def lib():
         L.mls_stage_memory.argtypes = [C.POINTER(MlsConfig), C.POINTER(MlsMemory)]
         L.mls_gemm.argtypes = [i32, i32, vp, i64, vp, i64, vp, i64, vp, i64, i64, i64, vp]
         L.mls_gemm_plan.argtypes = [i32, i64, i64, i64, C.POINTER(i64), C.POINTER(i32), C.POINTER(i32)]
+        L.mls_stage_wgrad_launch.argtypes = [C.POINTER(MlsConfig), i32, i32, C.POINTER(MlsWgradLaunch)]
         L.mls_stage_wgrad_plan.argtypes = [C.POINTER(MlsConfig), i32, i32, C.POINTER(i32), C.POINTER(i32)]
         L.mls_stage_product_plan.argtypes = [C.POINTER(MlsConfig), i32, C.POINTER(i64)] + [C.POINTER(i32)] * 4
         L.mls_last_error.restype = C.c_char_p
@@ -274,8 +279,17 @@ def gemm_plan(mode, M, N, K):
     return big.value, r.value, c.value
 
 
+def wgrad_launch(cfg, n_microbatches, overwrite=False):
+    """How a layer's four weight gradients run: (shared, tile rows, columns, split weight or -1, its first column apart, tile rows,
+    columns there); see mls_stage_wgrad_launch."""
+    out = MlsWgradLaunch()
+    _check(lib().mls_stage_wgrad_launch(C.byref(cfg), n_microbatches, int(overwrite), C.byref(out)))
+    return tuple(getattr(out, n) for n, _ in out._fields_)
+
+
 def wgrad_plan(cfg, n_microbatches, overwrite=False):
-    """(rows, columns) of the tiles of the launch that a layer's four weight gradients share, (0, 0) if they do not."""
+    """(rows, columns) of the tiles, smaller than 256x256, of the launch that a layer's four weight gradients share in bf16 storage, (0, 0)
+    in every other case."""
     r, c = C.c_int32(), C.c_int32()
     _check(lib().mls_stage_wgrad_plan(C.byref(cfg), n_microbatches, int(overwrite), C.byref(r), C.byref(c)))
     return r.value, c.value

@@ -253,7 +253,11 @@ hipError_t gemm_bf16_tn_segments(const void* const* A, const void* const* B, int
 // 80 -> 45; 1536, 700 tokens 125 -> 97 (the fastest tile: 89); 512, 4 x 4096 tokens 387 -> 157; 3072, 600 tokens 422 -> 420.
 // 256x256 tiles: together their partly empty last rounds become one, and where that one would be nearly empty a product's last columns
 // that make it up go to smaller tiles (2048 / 5504, 2 x 2048 tokens: 776 tiles as 768 and 2048 x 256 columns on 64x64 ones; a step of that layer
-// 1 652 -> 1 602 us, hidden 5120 / 13824 over 2 x 4096 0.7 % faster; over 4 x 4096 tokens at 4096 / 11008, at the power limit, equal).
+// 1 652 -> 1 602 us, hidden 5120 / 13824 over 2 x 4096 0.7 % faster; over 4 x 4096 tokens at 4096 / 11008, at the power limit, equal; 25 layers
+// of hidden 2048 to 5888 the weight gradients 0.87 and a step 0.97 of the time apart, none slower).  From two rounds of them and 32 k-tiles on, where
+// that was first measured.  It is not where they stop paying: of 187 layers below either line (hidden 512 to 6200) the estimates would take them
+// together with 0.85 of the time for the weight gradients and 0.97 for a step, 11 of them slower by up to 2.8 % (contractions of less than 16 k-tiles,
+// 257 to 320 tiles).
 TnGroupPlan gemm_bf16_tn_group_plan(const TnProduct* p, int n, int nseg, int kseg, bool overwrite) {
   const int64_t it = int64_t(nseg) * ((kseg + 63) / 64), depth = it * 64;
   const Result res = overwrite ? R_F32_STORE : R_F32_ADD;
@@ -273,7 +277,7 @@ TnGroupPlan gemm_bf16_tn_group_plan(const TnProduct* p, int n, int nseg, int kse
     for (int i = 0; i < n; i++) w += tiles_of(tile, p[i].M, p[i].N);
     consider(estimate(res, tile, w, it), {true, tile, -1, 0, 0});
   }
-  if (big < 2 * CUS || it < 32) return best;  // (fewer or shorter ones are mostly epilogue, which smaller tiles overlap)
+  if (big < 2 * CUS || it < 32) return best;
   consider(estimate(res, TILE_M16, big, it), {true, -1, -1, 0, 0});
   for (int i = 0; i < n; i++) {
     if (p[i].M <= 0 || p[i].N <= 0) continue;

@@ -496,17 +496,21 @@ hipError_t gemm_f32_dswiglu(const void* dY, const void* W, const void* GU, void*
 
 // The 64x64 tiles where all problems together have 320 of them and more (us, 32x32 / 64x64, events around the launch: hidden 512, ffn 1376 over 48
 // tokens 35 / 19, 768 / 2048 over 3 x 1152 409 / 353, 708 tiles over 2 x 512 82 / 83; 156 over 2 x 384 18 / 23).
+int64_t tn_group_tiles(const TnProduct* p, int n, int t) {
+  int64_t tiles = 0;
+  for (int i = 0; i < n; i++) tiles += int64_t((p[i].M + t - 1) / t) * ((p[i].N + t - 1) / t);
+  return tiles;
+}
+int gemm_f32_tn_group_tile(const TnProduct* p, int n) { return tn_group_tiles(p, n, 64) >= 320 ? 64 : 32; }
+
 hipError_t gemm_f32_tn_group(const TnProduct* p, int n, int nseg, int kseg, hipStream_t st, bool overwrite, const Colsum& cs) {
   if (nseg == 0 || kseg == 0) return hipSuccess;
   if (n < 1 || n > MAX_GROUP || nseg > MAX_SEGS) return hipErrorInvalidValue;
   TnGroup g = {};
-  int64_t tiles[2] = {0, 0};
   auto up = [](int v, int t) { return int64_t((v + t - 1) / t); };
-  for (int i = 0; i < n; i++)
-    for (int l = 0; l < 2; l++) tiles[l] += up(p[i].M, l ? 64 : 32) * up(p[i].N, l ? 64 : 32);
-  const bool large = tiles[1] >= 320;
-  const int t = large ? 64 : 32;
-  if (tiles[large] + cs.wgs >= (int64_t(1) << 31)) return hipErrorInvalidValue;
+  const int t = gemm_f32_tn_group_tile(p, n);
+  const bool large = t == 64;
+  if (tn_group_tiles(p, n, t) + cs.wgs >= (int64_t(1) << 31)) return hipErrorInvalidValue;
   g.nseg = nseg;
   g.K = kseg;
   g.add = overwrite ? 0 : 1;

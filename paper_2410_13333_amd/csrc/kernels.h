@@ -159,8 +159,6 @@ bool gemm_f32_large(int M, int N, int K);  // whether such a product runs on 64x
 // overwrite (GEMM_TN): C = instead of +=
 hipError_t gemm_f32(int mode, const void* A, const void* B, void* C, const void* R, int M, int N, int K, int64_t lda,
                     int64_t ldb, int64_t ldc, int64_t ldr, hipStream_t st, bool overwrite = false);
-// p[i].C (+)= sum_j p[i].A[j][kseg, M]^T * p[i].B[j][kseg, N] over nseg <= 16 pieces for up to four products, fp32 throughout, and the
-// column sums of cs, in one launch (nothing at all without a piece)
 // The fp32 products with an elementwise step as their epilogue (operands as gemm_f32 takes them): gate|up [M, 2f] and Z = silu(gate) up, both
 // stored; C with the head vectors below column rot_cols rotated by row % seq (head_dim a multiple of 16; tables [seq][head_dim/2]);
 // the SwiGLU backward of dZ = dY W^T (W [f, K]) from GU [M, 2f].
@@ -170,6 +168,9 @@ hipError_t gemm_f32_rope(const void* A, const void* W, void* C, int M, int N, in
                          const float* sin_tab, int seq, int rot_cols, int head_dim, hipStream_t st);
 hipError_t gemm_f32_dswiglu(const void* dY, const void* W, const void* GU, void* DGU, int M, int f, int K, int64_t lda, int64_t ldw,
                             int64_t ldgu, int64_t lddgu, hipStream_t st);
+// p[i].C (+)= sum_j p[i].A[j][kseg, M]^T * p[i].B[j][kseg, N] over nseg <= 16 pieces for up to four products, fp32 throughout, and the
+// column sums of cs, in one launch (nothing at all without a piece)
+int gemm_f32_tn_group_tile(const TnProduct* p, int n);  // rows and columns of its tiles, 32 or 64.  Host only.
 hipError_t gemm_f32_tn_group(const TnProduct* p, int n, int nseg, int kseg, hipStream_t st, bool overwrite, const Colsum& cs = {});
 
 // ---- row-wise and elementwise kernels (elementwise.hip); dt selects the storage type; every matrix argument is

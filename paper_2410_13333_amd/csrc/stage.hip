@@ -373,7 +373,6 @@ int wgrad(mls_stage* s, const mls::TnProduct (&p)[4], int n, bool ow, const mls:
     const mls::TnGroupPlan plan = wgrad_group(s, q, m, over);
     if (plan.together) {
       LAUNCH(CLS_GEMM_TN, mls::gemm_bf16_tn_group(q, 4, plan, m, s->T, s->st, over, i == 0 ? cs : mls::Colsum{}));
-      if (s->tm.on && plan.tile < 0) s->tm.launches[CLS_GEMM_TN] += 3;  // (products of their own size, as where they run apart)
       continue;
     }
     for (auto& w : q) {
@@ -862,19 +861,41 @@ int mls_stage_timing_read(mls_stage* s, double* ms, int64_t* launches) {
   return MLS_OK;
 }
 
-int mls_stage_wgrad_plan(const mls_config* cfg, int32_t n, int32_t flags, int32_t* tile_rows, int32_t* tile_cols) {
-  if (!cfg || !tile_rows || !tile_cols) return fail(MLS_E_NULL, "mls_stage_wgrad_plan: null argument");
+int mls_stage_wgrad_launch(const mls_config* cfg, int32_t n, int32_t flags, mls_wgrad_launch* out) {
+  if (!cfg || !out) return fail(MLS_E_NULL, "mls_stage_wgrad_launch: null argument");
   if (int rc = check_config(*cfg)) return rc;
-  if (flags & ~MLS_BWD_OVERWRITE) return fail(MLS_E_CONFIG, "mls_stage_wgrad_plan: unknown flag");
-  if (n < 1) return fail(MLS_E_RANGE, "mls_stage_wgrad_plan: n_microbatches must be positive");
+  if (flags & ~MLS_BWD_OVERWRITE) return fail(MLS_E_CONFIG, "mls_stage_wgrad_launch: unknown flag");
+  if (n < 1) return fail(MLS_E_RANGE, "mls_stage_wgrad_launch: n_microbatches must be positive");
   mls_stage tmp;
   tmp.c = *cfg;
   layout(&tmp);
   mls::TnProduct p[4];
   weight_grads(&tmp, nullptr, nullptr, p);
-  const int tile = wgrad_group(&tmp, p, n < 16 ? n : 16, (flags & MLS_BWD_OVERWRITE) != 0).tile;
-  *tile_rows = *tile_cols = 0;
-  if (tile >= 0) mls::t16_tile_size(mls::T16_TN_SEGS, tile, *tile_rows, *tile_cols);
+  *out = {0, 0, 0, -1, 0, 0, 0};
+  if (tmp.dt == mls::DT_FP32) {
+    const int t = mls::gemm_f32_tn_group_tile(p, 4);
+    *out = {1, t, t, -1, 0, 0, 0};
+    return MLS_OK;
+  }
+  const mls::TnGroupPlan g = wgrad_group(&tmp, p, n < 16 ? n : 16, (flags & MLS_BWD_OVERWRITE) != 0);
+  if (!g.together) return MLS_OK;
+  out->shared = 1;
+  out->tile_rows = out->tile_cols = 256;
+  if (g.tile >= 0) mls::t16_tile_size(mls::T16_TN_SEGS, g.tile, out->tile_rows, out->tile_cols);
+  if (g.tile >= 0 || g.split < 0) return MLS_OK;
+  out->split = g.split;
+  out->split_col = g.n1;
+  mls::t16_tile_size(mls::T16_TN_SEGS, g.rest, out->rest_rows, out->rest_cols);
+  return MLS_OK;
+}
+
+int mls_stage_wgrad_plan(const mls_config* cfg, int32_t n, int32_t flags, int32_t* tile_rows, int32_t* tile_cols) {
+  if (!cfg || !tile_rows || !tile_cols) return fail(MLS_E_NULL, "mls_stage_wgrad_plan: null argument");
+  mls_wgrad_launch l;
+  if (int rc = mls_stage_wgrad_launch(cfg, n, flags, &l)) return rc;
+  const bool small = cfg->dtype == MLS_BF16 && l.shared && l.tile_rows * l.tile_cols < 256 * 256;
+  *tile_rows = small ? l.tile_rows : 0;
+  *tile_cols = small ? l.tile_cols : 0;
   return MLS_OK;
 }
 

@@ -73,7 +73,33 @@ def test_refusals():
             mls.gemm_plan(*bad)
 
 
-def test_weight_gradients_share_a_launch_on_small_layers_only():
+# hidden, q heads, kv heads, head dim, ffn, seq, micro-batch, micro-batches -> (shared, tile, weight with columns apart, from, tile there)
+WGRAD_256 = [
+    ((2048, 16, 16, 128, 5504, 700, 1, 3), (1, 256, 256, 1, 10752, 64, 64)),    # 776 tiles: three whole rounds, the gate/up weights' last columns apart
+    ((2056, 16, 8, 128, 5512, 2049, 1, 1), (1, 256, 256, 0, 1792, 128, 64)),    # ragged rows, columns and pieces, a last gate/up group that is not full
+    ((3072, 24, 8, 128, 8192, 1088, 2, 1), (1, 256, 256, -1, 0, 0, 0)),         # a last round that is kept
+    ((2800, 43, 43, 64, 1344, 930, 1, 2), (0, 0, 0, -1, 0, 0, 0)),              # fewer than 32 k-tiles: launches apart
+    ((1032, 8, 8, 128, 5688, 2285, 1, 2), (0, 0, 0, -1, 0, 0, 0))]              # fewer than 512 tiles
+
+
+def test_how_the_weight_gradients_of_a_layer_run():
+    for shape, launch in WGRAD_256:
+        cfg = _cfg(*shape)
+        assert mls.wgrad_launch(cfg, shape[-1]) == mls.wgrad_launch(cfg, shape[-1], True) == launch, shape
+        assert mls.wgrad_plan(cfg, shape[-1]) == (0, 0)
+    for shape, tile in WGRAD_TILES:
+        assert mls.wgrad_launch(_cfg(*shape), shape[-1]) == (1, *tile, -1, 0, 0, 0), shape
+    for n in (1, 4, 16, 40):
+        assert mls.wgrad_launch(_cfg(4096, 32, 32, 128, 11008, 4096, 1, n), n) == (1, 256, 256, 1, 21760, 64, 64)
+    # fp32 storage: 64x64 tiles from 320 on
+    assert mls.wgrad_launch(_cfg(512, 8, 4, 64, 1376, 256, 2, 2, dtype=1), 2) == (1, 64, 64, -1, 0, 0, 0)
+    assert mls.wgrad_launch(_cfg(256, 4, 4, 64, 688, 128, 2, 1, dtype=1), 1) == (1, 32, 32, -1, 0, 0, 0)
+    for bad in ((0, False), (-1, True)):
+        with pytest.raises(mls.MlsError):
+            mls.wgrad_launch(_cfg(256, 4, 4, 64, 688, 128, 2, 1), *bad)
+
+
+def test_weight_gradients_share_a_launch_of_smaller_tiles_on_small_layers_only():
     assert mls.wgrad_plan(_cfg(256, 4, 4, 64, 688, 128, 2, 1), 1) == (64, 64)
     for n in (1, 4, 16, 40):
         assert mls.wgrad_plan(_cfg(4096, 32, 32, 128, 11008, 4096, 1, n), n) == (0, 0)

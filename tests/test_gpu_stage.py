@@ -12,7 +12,7 @@ import pytest
 import synth
 from tests.helpers import (gpu_step, grad_errors, oracle_step, rel_err, round_bf16, storage_bits, to_device,
                            to_host64, worst_block)
-from tests.test_gemm_plan import ROPE_TILES, SWIGLU_TILES, WGRAD_TILES
+from tests.test_gemm_plan import ROPE_TILES, SWIGLU_TILES, WGRAD_256, WGRAD_TILES
 
 pytestmark = pytest.mark.gpu
 
@@ -510,15 +510,15 @@ def test_weight_gradients_of_a_layer_in_one_launch(hidden, nq, nkv, d, ffn, seq,
     st.close()
 
 
-@pytest.mark.parametrize("hidden,nq,nkv,d,ffn,seq,n,shared", [(256, 4, 4, 64, 688, 256, 2, True), (2048, 16, 16, 128, 5504, 2048, 2, False),
-                                                              (64, 1, 1, 64, 64, 8, 17, True)])
+@pytest.mark.parametrize("hidden,nq,nkv,d,ffn,seq,n,shared", [(256, 4, 4, 64, 688, 256, 2, True), (2048, 16, 16, 128, 5504, 2048, 2, True),
+                                                              (1032, 8, 8, 128, 5688, 2285, 2, False), (64, 1, 1, 64, 64, 8, 17, True)])
 def test_launch_counts_of_the_timing_classes(hidden, nq, nkv, d, ffn, seq, n, shared):
     """Weight gradients count once per layer (and 16 micro-batches) where they share a launch, four times where they do not."""
     import torch
     import paper_2410_13333_amd as mls
     layers = 2
     st = mls.Stage(hidden, nq, nkv, d, ffn, seq, 1, layers, n, seed=1)
-    assert (mls.wgrad_plan(st.cfg, n) != (0, 0)) == shared
+    assert mls.wgrad_launch(st.cfg, n)[0] == shared
     x = torch.randn(n, 1, seq, hidden, device="cuda").to(torch.bfloat16)
     y, dx, g = torch.empty_like(x[0]), torch.empty_like(x), torch.zeros(st.grad_elems, device="cuda")
     st.timing(True)
@@ -600,20 +600,10 @@ def test_overwrite_equals_zeroing_where_the_two_run_on_different_tiles(hidden, n
     assert torch.equal(*got)
 
 
-@pytest.mark.parametrize("hidden,nq,nkv,d,ffn,seq,mb,n", [
-    (2048, 16, 16, 128, 5504, 700, 1, 3),    # 776 tiles of 256x256: whole rounds, a product's last columns on smaller tiles
-    (2056, 16, 8, 128, 5512, 2049, 1, 1),    # ragged rows, columns and pieces, gate/up columns with a last group that is not full
-    (3072, 24, 8, 128, 8192, 1088, 2, 1)])   # a last round that is kept
-def test_weight_gradients_that_share_a_launch_of_256x256_tiles(hidden, nq, nkv, d, ffn, seq, mb, n):
-    """They have no tile of their own to report, and more than two rounds of 256x256 ones (the rule for sharing them)."""
-    import paper_2410_13333_amd as mls
-    cfg = mls.MlsConfig(hidden, nq, nkv, d, ffn, seq, mb, 1, n, 1e-5, 10000.0, 0, 0)
-    assert mls.wgrad_plan(cfg, n) == mls.wgrad_plan(cfg, n, True) == (0, 0)
-    up = lambda v: -(-v // 256)  # noqa: E731
-    qd, qkv = nq * d, (nq + 2 * nkv) * d
-    tiles = up(ffn) * up(hidden) + up(hidden) * up(2 * -(-ffn // 32) * 32) + up(qd) * up(hidden) + up(hidden) * up(qkv)
-    assert tiles > 512 and n * -(-seq * mb // 64) >= 32
-    test_weight_gradients_of_a_layer_in_one_launch(hidden, nq, nkv, d, ffn, seq, mb, n)
+@pytest.mark.parametrize("shape", [s for s, _ in WGRAD_256])
+def test_weight_gradients_on_256x256_tiles(shape):
+    """In one launch, with and without a weight's last columns in another, and apart (test_how_the_weight_gradients_of_a_layer_run)."""
+    test_weight_gradients_of_a_layer_in_one_launch(*shape)
 
 
 # hidden, ffn, tokens -> (columns on 256x256 tiles, parts there, tile rows, columns, parts) of the down-projection's data gradient, and whether
