@@ -114,7 +114,7 @@ struct mls_stage {
   int head = 0, count = 0;  // FIFO ring over the slots
   // backward workspace.  g0, g1 (ping-pong gradient of the residual stream), dgu, dh and dqkv exist once per
   // in-flight micro-batch (they are the operands of the weight-gradient contractions, which run once per layer
-  // over all micro-batches of a backward call); dz, dbuf and dc are transient and shared.
+  // over all micro-batches of a backward call); dz (bf16 storage), dbuf and dc are transient and shared.
   char *g0 = nullptr, *g1 = nullptr, *dz = nullptr, *dgu = nullptr, *dbuf = nullptr, *dh = nullptr, *dc = nullptr,
        *dqkv = nullptr;
   size_t mb_h = 0, mb_gu = 0, mb_qkv = 0;  // bytes per micro-batch of the [T,ld_h], [T,ld_gu], [T,ld_qkv] buffers
@@ -496,7 +496,7 @@ std::vector<Alloc> allocations(mls_stage* s) {
       {(void**)&s->rc_scratch, c.recompute ? nmb * s->ls.bytes : 0, 2},
       {(void**)&s->g0, nmb * s->mb_h, 2},
       {(void**)&s->g1, nmb * s->mb_h, 2},
-      {(void**)&s->dz, T * s->ld_f * s->es, 2},
+      {(void**)&s->dz, s->dt == mls::DT_BF16 ? T * s->ld_f * s->es : 0, 2},
       {(void**)&s->dgu, nmb * s->mb_gu, 2},
       {(void**)&s->dbuf, T * s->ld_h * s->es, 2},
       {(void**)&s->dh, nmb * s->mb_h, 2},

@@ -70,6 +70,16 @@ def test_cap_from_the_report_is_the_largest_stage_that_fits(pp, j):
     assert need(cap) <= C - G < need(cap + 1)
 
 
+def test_workspace_holds_no_dz_with_fp32_storage():
+    """dZ of the down-projection never leaves the registers there: dgu alone grows with the ffn width."""
+    import paper_2410_13333_amd as mls
+
+    def workspace(ffn):
+        sh = synth.StageShape(hidden=72, n_q_heads=3, n_kv_heads=3, head_dim=16, ffn=ffn, seq=50, micro_batch=2, layers=1, microbatches=1, dtype="fp32")
+        return mls.Stage.memory(sh, max_layers=1, max_inflight=1)["workspace_bytes"]
+    assert workspace(168) - workspace(88) == 4 * 100 * 2 * (168 - 88)
+
+
 def test_fp32_rows_are_padded_off_powers_of_two_only():
     """bf16 rows are padded to whole 64-deep k-tiles; no fp32 kernel reads such columns."""
     import paper_2410_13333_amd as mls
