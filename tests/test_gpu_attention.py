@@ -211,15 +211,21 @@ def test_a_non_finite_gradient_reaches_no_position_far_behind_it(nq, nkv, d, seq
     assert torch.equal(hit[1:], clean[1:])
 
 
-# dQ from the dS in memory (128-column heads from 256 positions on, at most 320 workgroups), and the shapes next to it that form dS
-# again (255 positions; 32 x 11 workgroups); a last step, tile and workgroup that are partly filled; query heads of a group in
-# several workgroups and one after the other
-@pytest.mark.parametrize("nq,nkv,d,seq,mb", [(2, 2, 128, 255, 1), (4, 2, 128, 256, 1), (2, 2, 128, 257, 2), (3, 1, 128, 287, 1), (2, 1, 128, 289, 2),
-                                             (6, 6, 128, 385, 1), (16, 2, 128, 1025, 1), (32, 4, 128, 600, 2), (32, 32, 128, 1280, 1), (32, 32, 128, 1281, 1),
-                                             (80, 80, 128, 500, 1), (10, 10, 128, 4000, 1), (4, 2, 64, 801, 2)])
-def test_dq_and_dkv_on_either_side_of_the_stored_ds(nq, nkv, d, seq, mb):
+# dQ from the dS in memory (128-column heads from 256 positions on, more workgroups than share a launch and at most 320), and the shapes next to
+# it that form dS again; a last step, tile and workgroup that are partly filled; query heads of a group in several workgroups and one
+# after the other
+@pytest.mark.parametrize("nq,nkv,d,seq,mb,from_ds", [
+    (2, 2, 128, 255, 1, False), (4, 2, 128, 256, 1, False), (2, 2, 128, 257, 2, False), (3, 1, 128, 287, 1, False), (2, 1, 128, 289, 2, False),
+    (6, 6, 128, 385, 1, False), (16, 2, 128, 1025, 1, False), (32, 4, 128, 600, 2, True), (32, 32, 128, 1280, 1, True), (32, 32, 128, 1281, 1, False),
+    (80, 80, 128, 500, 1, True), (10, 10, 128, 4000, 1, True), (4, 2, 64, 801, 2, False), (43, 43, 128, 255, 3, False), (43, 43, 128, 256, 3, True),
+    (17, 17, 128, 257, 5, True), (29, 29, 128, 287, 3, True), (44, 22, 128, 289, 2, True)])
+def test_dq_and_dkv_on_either_side_of_the_stored_ds(nq, nkv, d, seq, mb, from_ds):
+    import ctypes
     import torch
     import paper_2410_13333_amd as mls
+    f = mls.lib()._ZN3mls10dq_from_dsEiiiii
+    f.restype = ctypes.c_bool
+    assert f(mb, seq, nq, nkv, d) is from_ds
     h = 64
     st = mls.Stage(h, nq, nkv, d, 64, seq, mb, 1, 1, seed=1003)
     gen = torch.Generator(device="cuda").manual_seed(seq)
