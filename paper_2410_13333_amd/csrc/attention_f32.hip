@@ -142,8 +142,8 @@ __device__ __forceinline__ void store_row(float* row, const f32x16 (&acc)[DT], f
     }
 }
 // the same turned back: the two halves of H groups of eight features each; group G is registers 4 (G % 4) .. of tile G / 4.  Straight to
-// memory: turned back in place, for either head width of DT = 3, the accumulators had the compiler take 48 registers less, and the loops before lost
-// (heads of 80, 681 positions, 25 heads: dQ 71.6 -> 83.5 us, dK and dV 111 -> 117).
+// memory: turned back in place, for either head width of DT = 3, the compiler kept accumulators in scratch memory (192 bytes a lane), and the loops
+// before lost (heads of 80, 681 positions, 25 heads: dQ 71.6 -> 83.5 us, dK and dV 111 -> 117).
 template <int H, int DT>
 __device__ __forceinline__ void store_row_halves(float* row, const f32x16 (&acc)[DT], float mul, const float* cs, const float* sn, int hf) {
 #pragma unroll

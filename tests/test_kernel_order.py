@@ -80,15 +80,27 @@ def shortest_distances(lines):
     return least, seen
 
 
-@pytest.fixture(scope="module")
-def attention_asm(tmp_path_factory):
+def _assembly(tmp_path_factory, source):
     if not shutil.which("hipcc"):
         pytest.skip("no hipcc")
-    out = tmp_path_factory.mktemp("asm") / "attention.s"
-    subprocess.run(["hipcc", *B.FLAGS, "-w", "--offload-device-only", "-S", os.path.join(B.CSRC, "attention_bf16.hip"), "-o", str(out)],
+    out = tmp_path_factory.mktemp("asm") / "kernels.s"
+    subprocess.run(["hipcc", *B.FLAGS, "-w", "--offload-device-only", "-S", os.path.join(B.CSRC, source), "-o", str(out)],
                    check=True, capture_output=True)
+    return out.read_text()
+
+
+def test_fp32_attention_up_to_heads_of_96_uses_no_scratch_memory(tmp_path_factory):
+    """(Above that the dK / dV part spills.)"""
+    text = _assembly(tmp_path_factory, "attention_f32.hip")
+    scratch = {m[1]: int(m[2]) for m in re.finditer(r"\.name:\s+(\S*attn_\w+)\n\s+\.private_segment_fixed_size:\s+(\d+)", text)}
+    assert len(scratch) == 16
+    assert all(n == 0 for k, n in scratch.items() if "kernelILi4E" not in k), scratch
+
+
+@pytest.fixture(scope="module")
+def attention_asm(tmp_path_factory):
     kernels, cur = {}, None
-    for line in out.read_text().splitlines():
+    for line in _assembly(tmp_path_factory, "attention_bf16.hip").splitlines():
         m = re.match(r"(_Z\w+):", line)
         if m:
             cur = kernels.setdefault(m[1], [])
