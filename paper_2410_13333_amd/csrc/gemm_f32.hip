@@ -205,6 +205,12 @@ __device__ __forceinline__ f32x16 zero16() {
   for (int e = 0; e < 16; e++) z[e] = 0.f;
   return z;
 }
+__device__ __forceinline__ f32x16 add16(const f32x16& a, const f32x16& b) {
+  f32x16 c;
+#pragma unroll
+  for (int e = 0; e < 16; e++) c[e] = a[e] + b[e];
+  return c;
+}
 
 // The products of one piece, in this order: two MFMAs, `between` (waits, the requests of a piece to come), the others with the LDS reads of the
 // next piece (eight groups, read(0) .. read(7)) in their shadow.  Operands swapped: a lane ends up with 4 consecutive columns of one row of C.
@@ -221,7 +227,8 @@ __device__ __forceinline__ void products(f32x16& c, const float (&a)[KC / 2], co
 }
 
 // A(m, k): AK ? A[m*lda + k] : A[k*lda + m]; B(k, n): BK ? B[n*ldb + k] : B[k*ldb + n].  add: C += instead of C =.
-// SEG: A and B are the first of nseg matrices each.
+// SEG: A and B are the first of nseg matrices each.  Every matrix has sums of its own, which are added up: one chain through all of them would
+// round on the growing sum at every product (weight gradients of three micro-batches up to 1.25 times as far from the exact ones).
 struct Source {
   const float *A, *B;
   int M, N, K;
@@ -248,9 +255,10 @@ __device__ __forceinline__ void tile32(float* smem, const Source& s, int m0, int
     oa.request(lane, at);
     ob.request(lane, at + STAGE * 2);
   };
-  f32x16 acc = zero16();
+  f32x16 acc = zero16(), total = zero16();
   const int each = (K + KC - 1) / KC, pieces = SEG ? each * s.nseg : each;
   const int n = (pieces - wave + 3) / 4;  // of this wavefront (0 if there are fewer than four)
+  int in_seg = SEG ? wave % each : 0;     // this piece's place in its matrix
   float a[2][KC / 2], b[2][KC / 2];
   auto read = [&](auto I, int stage, int set) {
     constexpr int i = decltype(I)::value;
@@ -288,12 +296,21 @@ __device__ __forceinline__ void tile32(float* smem, const Source& s, int m0, int
              },
              [&](auto I) { read(I, (stage + 1) % NS, set ^ 1); });  // (after the last piece: not used)
     cut(p + 1, set ^ 1);
+    if constexpr (SEG) {
+      in_seg += 4;
+      if (in_seg >= each) {
+        in_seg %= each;
+        total = add16(total, acc);
+        acc = zero16();
+      }
+    }
   };
   for (int p = 0; p < n; p += NS)
     static_for<NS>([&](auto I) {
       if (p + decltype(I)::value < n) step(p + decltype(I)::value, I);
     });
   wait_lgkm0();
+  if constexpr (SEG) acc = add16(total, acc);  // (the wavefront's last piece may not be the end of its matrix)
   // wavefronts 2, 3 -> 0, 1; then 1 -> 0
   float(*part)[16][64] = reinterpret_cast<float(*)[16][64]>(smem);
   __syncthreads();
@@ -332,7 +349,9 @@ __device__ __forceinline__ void tile64(float* smem, const Source& s, int m0, int
     oa.request(lane, at);
     ob.request(lane, at + STAGE * 2);
   };
-  f32x16 acc[4] = {zero16(), zero16(), zero16(), zero16()};
+  f32x16 acc[4] = {zero16(), zero16(), zero16(), zero16()}, total = zero16();
+  auto sum = [&] { return add16(add16(acc[0], acc[2]), add16(acc[1], acc[3])); };
+  int in_seg = 0;  // this piece's place in its matrix
   if (pieces > 0) {
     float a[2][KC / 2], b[2][KC / 2];
     auto read = [&](auto I, int stage, int set) {
@@ -370,6 +389,13 @@ __device__ __forceinline__ void tile64(float* smem, const Source& s, int m0, int
                },
                [&](auto J) { read(J, (i + 1) % NS, set ^ 1); });
       cut(p + 1, set ^ 1);
+      if constexpr (SEG) {
+        if (++in_seg == each) {
+          in_seg = 0;
+          total = add16(total, sum());
+          acc[0] = acc[1] = acc[2] = acc[3] = zero16();
+        }
+      }
     };
     for (int p = 0; p < pieces; p += 4)
       static_for<4>([&](auto I) {
@@ -377,9 +403,8 @@ __device__ __forceinline__ void tile64(float* smem, const Source& s, int m0, int
       });
     wait_vmcnt<0>();
   }
-#pragma unroll
-  for (int e = 0; e < 16; e++) acc[0][e] = (acc[0][e] + acc[2][e]) + (acc[1][e] + acc[3][e]);
-  store_tile<EPI>(acc[0], C, R, m0 + wm * 32 + l32, n0 + wn * 32, M, N, ldc, ldr, add, hf, ep);
+  if constexpr (!SEG) total = sum();
+  store_tile<EPI>(total, C, R, m0 + wm * 32 + l32, n0 + wn * 32, M, N, ldc, ldr, add, hf, ep);
 }
 
 template <bool AK, bool BK, bool LARGE, int EPI>
@@ -394,7 +419,7 @@ __global__ __launch_bounds__(256, 2) void gemm_f32_kernel(const float* __restric
 // The weight gradients of a layer over all micro-batches of a call: C (+)= sum_i A_i^T B_i for each problem of a list, all over matrices of
 // the same depth, in one launch.  A launch for each of them and each micro-batch left most of the chip idle between its few tiles' chains
 // (weight gradients of a call, us, as events around the launches: hidden 512, ffn 1376, 2 x 512 tokens 142 -> 95; 768, 2048, 3 x 1152 652 -> 424;
-// 192, 600, 2 x 384 72 -> 21) and rounded the sums once per micro-batch.
+// 192, 600, 2 x 384 72 -> 21).  The micro-batches' sums are added up in registers, as the launches added them up in C.
 constexpr int MAX_SEGS = 16, MAX_GROUP = 4;
 struct TnGroup {
   int nseg, n, K, add;

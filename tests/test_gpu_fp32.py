@@ -105,6 +105,39 @@ def test_weight_gradients_over_many_micro_batches(hidden, ffn, seq, n):
             assert e <= 1e-5
 
 
+# 32x32 tiles and 64x64 ones; tokens that are whole pieces of the four wavefronts or accumulators, and ones that are not
+@pytest.mark.parametrize("hidden,nq,ffn,seq,n,tile", [(256, 4, 480, 222, 3, 32), (192, 3, 600, 384, 2, 32), (136, 2, 328, 37, 16, 32), (512, 8, 1376, 512, 2, 64),
+                                                      (512, 4, 1400, 330, 4, 64), (520, 8, 1376, 45, 9, 64)])
+def test_weight_gradients_of_one_call_are_as_exact_as_those_of_many(hidden, nq, ffn, seq, n, tile):
+    """A call over n micro-batches adds up n sums, as n calls do: within 2 % as far from the exact gradients as those (64x64 tiles: the same
+    bits), where one chain of additions through all of them was up to a quarter further."""
+    import torch
+    import paper_2410_13333_amd as mls
+    st = mls.Stage(hidden, nq, nq, 64, ffn, seq, 1, 1, n, seed=1011, dtype="fp32")
+    assert mls.wgrad_launch(st.cfg, n)[1] == tile
+    gen = torch.Generator(device="cuda").manual_seed(seq)
+    x, dy = (torch.randn(n, 1, seq, hidden, device="cuda", generator=gen) for _ in range(2))
+    y, dx = torch.empty_like(x[0]), torch.empty_like(dy)
+    one, many = (torch.empty(st.grad_elems, device="cuda") for _ in range(2))
+    pairs = {"w_d": ("z", "dy"), "w_gu": ("b", "dgu"), "w_o": ("o", "dh"), "w_qkv": ("a", "dqkv")}
+    ref = dict.fromkeys(pairs, 0.0)
+    for i in range(n):
+        st.forward(x[i], 1, y)
+        left = {w: st.debug_read(a).double() for w, (a, _) in pairs.items()}
+        st.backward(dy[i:i + 1], many, 1, dx[i:i + 1], overwrite=i == 0)
+        for w, (_, b) in pairs.items():
+            ref[w] = ref[w] + left[w].t().contiguous() @ st.debug_read(b).double()
+    for i in range(n):
+        st.forward(x[i], 1, y)
+    st.backward(dy, one, n, dx, overwrite=True)
+    for w in pairs:
+        off, r, c = st.param_layout(0, w)
+        e = [((g[off:off + r * c].view(r, c).double() - ref[w]).norm() / ref[w].norm()).item() for g in (one, many)]
+        assert e[0] <= 1.02 * e[1], (w, e)
+        assert tile == 32 or torch.equal(one[off:off + r * c], many[off:off + r * c]), w
+    st.close()
+
+
 # the backward in one launch, up to a number of blocks of 32 query rows that depends on the head width, the blocks of a sequence and the grouping,
 # or apart; the query heads of a group apart, where their key blocks are few and long, or in one workgroup
 @pytest.mark.parametrize("nq,nkv,d,seq,mb,together,apart", [
