@@ -521,7 +521,7 @@ hipError_t gemm_f32_dswiglu(const void* dY, const void* W, const void* GU, void*
 
 // The 64x64 tiles where all problems together have 320 of them and more (us, 32x32 / 64x64, events around the launch: hidden 512, ffn 1376 over 48
 // tokens 35 / 19, 768 / 2048 over 3 x 1152 409 / 353, 708 tiles over 2 x 512 82 / 83; 156 over 2 x 384 18 / 23).
-int64_t tn_group_tiles(const TnProduct* p, int n, int t) {
+static int64_t tn_group_tiles(const TnProduct* p, int n, int t) {
   int64_t tiles = 0;
   for (int i = 0; i < n; i++) tiles += int64_t((p[i].M + t - 1) / t) * ((p[i].N + t - 1) / t);
   return tiles;
